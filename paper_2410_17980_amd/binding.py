@@ -1,18 +1,25 @@
-"""Thin ctypes binding of libsbattn.so (include/sb_attn.h, include/sb_diag.h): same names, argument
+"""Thin binding of libsbattn.so (include/sb_attn.h, include/sb_diag.h): same names, argument
 marshalling only.  torch is used to own device memory and to name the stream;
 every step of the computation runs inside the library's kernels.
+
+The calls of the method are marshalled by a small native module (csrc/sb_torch.cpp), the
+measurement aids and load()'s handle by ctypes.  Enqueue time of one call, ctypes -> native:
+decode 16.9 -> 6.8 us, a short forward 11.5 -> 4.3 us, forward and backward 46 -> 18 us (kernels
+launched by them: 2, 1, 5); the kernels of such calls run for 5 to 10 us, so the host set the pace.
 
 There is no fallback: if the library is missing or a call fails, this raises.
 """
 from __future__ import annotations
 
 import ctypes
+import importlib.util
 import os
 
 import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libsbattn.so")
+EXT_PATH = os.path.join(_HERE, "_sbtorch.so")
 
 EXPORTS = (
     "sb_attn_fwd", "sb_attn_fwd_halt", "sb_attn_fwd_train", "sb_attn_fwd_f32",
@@ -25,6 +32,7 @@ EXPORTS = (
 )
 
 _lib = None
+_ext = None
 
 
 class SbAttnError(RuntimeError):
@@ -36,9 +44,10 @@ def load(build_if_missing: bool = True):
     global _lib
     if _lib is not None:
         return _lib
-    if not os.path.exists(LIB_PATH):
+    missing = [p for p in (LIB_PATH, EXT_PATH) if not os.path.exists(p)]
+    if missing:
         if not build_if_missing:
-            raise SbAttnError(f"{LIB_PATH} not built; run `python -m paper_2410_17980_amd.build`")
+            raise SbAttnError(f"{missing[0]} not built; run `python -m paper_2410_17980_amd.build`")
         from . import build as _build
         _build.build()
     lib = ctypes.CDLL(LIB_PATH)
@@ -97,6 +106,17 @@ def load(build_if_missing: bool = True):
     return lib
 
 
+def _load_ext():
+    global _ext
+    load()
+    spec = importlib.util.spec_from_file_location("_sbtorch", EXT_PATH)
+    ext = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(ext)
+    ext.set_errors(SbAttnError, torch.cuda.OutOfMemoryError)
+    _ext = ext
+    return ext
+
+
 def sb_status_string(status: int) -> str:
     return load().sb_status_string(int(status)).decode()
 
@@ -135,57 +155,28 @@ def _stream(stream=None):
     return ctypes.c_void_p(s.cuda_stream)
 
 
+# The calls of the method go through the native module: it checks the tensors, allocates what was
+# not passed in, takes the stream and calls the C ABI (csrc/sb_torch.cpp).
+
+
 def sb_attn_fwd(q, k, v, o=None, stream=None):
     """bf16 forward.  Returns o (allocated when not given)."""
-    B, H, T, d = _dims(q)
-    if o is None:
-        o = torch.empty_like(q)
-    rc = load().sb_attn_fwd(_ptr(q, torch.bfloat16, None, "q"), _ptr(k, torch.bfloat16, q.shape, "k"),
-                            _ptr(v, torch.bfloat16, q.shape, "v"), _ptr(o, torch.bfloat16, q.shape, "o"),
-                            B, H, T, d, _stream(stream))
-    _check(rc, "sb_attn_fwd")
-    return o
+    return (_ext or _load_ext()).forward("sb_attn_fwd", False, q, k, v, None, o, None, False, stream)
 
 
 def sb_attn_fwd_halt(q, k, v, eps, o=None, tile_counts=None, stream=None):
     """bf16 forward with early halt.  tile_counts: optional int64 tensor of 2 on the GPU (added to)."""
-    B, H, T, d = _dims(q)
-    if o is None:
-        o = torch.empty_like(q)
-    tc = _ptr(tile_counts, torch.int64, (2,), "tile_counts") if tile_counts is not None else None
-    rc = load().sb_attn_fwd_halt(_ptr(q, torch.bfloat16, None, "q"), _ptr(k, torch.bfloat16, q.shape, "k"),
-                                 _ptr(v, torch.bfloat16, q.shape, "v"), _ptr(o, torch.bfloat16, q.shape, "o"),
-                                 ctypes.c_float(eps), tc, B, H, T, d, _stream(stream))
-    _check(rc, "sb_attn_fwd_halt")
-    return o
+    return (_ext or _load_ext()).halt(q, k, v, eps, o, tile_counts, stream)
 
 
 def sb_attn_fwd_train(q, k, v, o=None, m=None, stream=None):
     """bf16 forward that also returns m[B,H,T] (fp32) for the backward."""
-    B, H, T, d = _dims(q)
-    if o is None:
-        o = torch.empty_like(q)
-    if m is None:
-        m = torch.empty((B, H, T), dtype=torch.float32, device=q.device)
-    rc = load().sb_attn_fwd_train(_ptr(q, torch.bfloat16, None, "q"), _ptr(k, torch.bfloat16, q.shape, "k"),
-                                  _ptr(v, torch.bfloat16, q.shape, "v"), _ptr(o, torch.bfloat16, q.shape, "o"),
-                                  _ptr(m, torch.float32, (B, H, T), "m"), B, H, T, d, _stream(stream))
-    _check(rc, "sb_attn_fwd_train")
-    return o, m
+    return (_ext or _load_ext()).forward("sb_attn_fwd_train", False, q, k, v, None, o, m, True, stream)
 
 
 def sb_attn_fwd_f32(q, k, v, o=None, m=None, want_m=False, stream=None):
     """fp32 forward.  Returns o, or (o, m) when m is given or want_m is set."""
-    B, H, T, d = _dims(q)
-    if o is None:
-        o = torch.empty_like(q)
-    if m is None and want_m:
-        m = torch.empty((B, H, T), dtype=torch.float32, device=q.device)
-    rc = load().sb_attn_fwd_f32(_ptr(q, torch.float32, None, "q"), _ptr(k, torch.float32, q.shape, "k"),
-                                _ptr(v, torch.float32, q.shape, "v"), _ptr(o, torch.float32, q.shape, "o"),
-                                _ptr(m, torch.float32, (B, H, T), "m"), B, H, T, d, _stream(stream))
-    _check(rc, "sb_attn_fwd_f32")
-    return (o, m) if m is not None else o
+    return (_ext or _load_ext()).forward_f32(q, k, v, o, m, want_m, stream)
 
 
 def sb_attn_bwd_workspace_bytes(B, H, T, d) -> int:
@@ -194,127 +185,42 @@ def sb_attn_bwd_workspace_bytes(B, H, T, d) -> int:
 
 def sb_attn_bwd(q, k, v, m, dout, dq=None, dk=None, dv=None, workspace=None, stream=None):
     """bf16 backward.  Returns (dq, dk, dv) in fp32."""
-    B, H, T, d = _dims(q)
-    mk = lambda: torch.empty(q.shape, dtype=torch.float32, device=q.device)
-    dq = mk() if dq is None else dq
-    dk = mk() if dk is None else dk
-    dv = mk() if dv is None else dv
-    need = sb_attn_bwd_workspace_bytes(B, H, T, d)
-    if workspace is None and need > 0:
-        workspace = torch.empty(need, dtype=torch.uint8, device=q.device)
-    ws_ptr = ctypes.c_void_p(workspace.data_ptr()) if workspace is not None else None
-    ws_bytes = workspace.numel() * workspace.element_size() if workspace is not None else 0
-    rc = load().sb_attn_bwd(_ptr(q, torch.bfloat16, None, "q"), _ptr(k, torch.bfloat16, q.shape, "k"),
-                            _ptr(v, torch.bfloat16, q.shape, "v"), _ptr(m, torch.float32, (B, H, T), "m"),
-                            _ptr(dout, torch.bfloat16, q.shape, "dout"),
-                            _ptr(dq, torch.float32, q.shape, "dq"), _ptr(dk, torch.float32, q.shape, "dk"),
-                            _ptr(dv, torch.float32, q.shape, "dv"), ws_ptr, ws_bytes,
-                            B, H, T, d, _stream(stream))
-    _check(rc, "sb_attn_bwd")
-    return dq, dk, dv
+    return (_ext or _load_ext()).backward("sb_attn_bwd", False, q, k, v, None, m, dout, dq, dk, dv, None,
+                                          workspace, stream)
 
 
 def sb_attn_fwd_rb(q, k, v, r, o=None, m=None, want_m=True, stream=None):
     """bf16 forward with remainder bias r [H,d] (bf16).  Returns (o, m), or o when want_m is off."""
-    B, H, T, d = _dims(q)
-    if o is None:
-        o = torch.empty_like(q)
-    if m is None and want_m:
-        m = torch.empty((B, H, T), dtype=torch.float32, device=q.device)
-    rc = load().sb_attn_fwd_rb(_ptr(q, torch.bfloat16, None, "q"), _ptr(k, torch.bfloat16, q.shape, "k"),
-                               _ptr(v, torch.bfloat16, q.shape, "v"), _ptr(r, torch.bfloat16, (H, d), "r"),
-                               _ptr(o, torch.bfloat16, q.shape, "o"), _ptr(m, torch.float32, (B, H, T), "m"),
-                               B, H, T, d, _stream(stream))
-    _check(rc, "sb_attn_fwd_rb")
-    return (o, m) if m is not None else o
+    if r is None:
+        raise SbAttnError("sb_attn_fwd_rb failed: r is required")
+    return (_ext or _load_ext()).forward("sb_attn_fwd_rb", False, q, k, v, r, o, m, want_m, stream)
 
 
 def sb_attn_bwd_rb(q, k, v, r, m, dout, dq=None, dk=None, dv=None, dr=None, workspace=None, stream=None):
     """bf16 backward with remainder bias.  Returns (dq, dk, dv, dr) in fp32; dr is [H,d]."""
-    B, H, T, d = _dims(q)
-    mk = lambda: torch.empty(q.shape, dtype=torch.float32, device=q.device)
-    dq = mk() if dq is None else dq
-    dk = mk() if dk is None else dk
-    dv = mk() if dv is None else dv
-    dr = torch.empty((H, d), dtype=torch.float32, device=q.device) if dr is None else dr
-    workspace, ws_ptr, ws_bytes = _workspace(workspace, B, H, T, d, q.device)
-    rc = load().sb_attn_bwd_rb(_ptr(q, torch.bfloat16, None, "q"), _ptr(k, torch.bfloat16, q.shape, "k"),
-                               _ptr(v, torch.bfloat16, q.shape, "v"), _ptr(r, torch.bfloat16, (H, d), "r"),
-                               _ptr(m, torch.float32, (B, H, T), "m"),
-                               _ptr(dout, torch.bfloat16, q.shape, "dout"),
-                               _ptr(dq, torch.float32, q.shape, "dq"), _ptr(dk, torch.float32, q.shape, "dk"),
-                               _ptr(dv, torch.float32, q.shape, "dv"), _ptr(dr, torch.float32, (H, d), "dr"),
-                               ws_ptr, ws_bytes, B, H, T, d, _stream(stream))
-    _check(rc, "sb_attn_bwd_rb")
-    return dq, dk, dv, dr
+    if r is None:
+        raise SbAttnError("sb_attn_bwd_rb failed: r is required")
+    return (_ext or _load_ext()).backward("sb_attn_bwd_rb", False, q, k, v, r, m, dout, dq, dk, dv, dr,
+                                          workspace, stream)
 
 
 def sb_attn_fwd_gqa(q, k, v, r=None, o=None, m=None, want_m=True, stream=None):
     """bf16 forward with grouped kv heads: q [B,H,T,d], k, v [B,Hkv,T,d]; optional remainder
     bias r [H,d].  Returns (o, m), or o when want_m is off."""
-    B, H, T, d = _dims(q)
-    Hkv = _dims(k)[1]
-    if o is None:
-        o = torch.empty_like(q)
-    if m is None and want_m:
-        m = torch.empty((B, H, T), dtype=torch.float32, device=q.device)
-    kv_shape = (B, Hkv, T, d)
-    rc = load().sb_attn_fwd_gqa(_ptr(q, torch.bfloat16, None, "q"), _ptr(k, torch.bfloat16, kv_shape, "k"),
-                                _ptr(v, torch.bfloat16, kv_shape, "v"), _ptr(r, torch.bfloat16, (H, d), "r"),
-                                _ptr(o, torch.bfloat16, q.shape, "o"), _ptr(m, torch.float32, (B, H, T), "m"),
-                                B, H, Hkv, T, d, _stream(stream))
-    _check(rc, "sb_attn_fwd_gqa")
-    return (o, m) if m is not None else o
+    return (_ext or _load_ext()).forward("sb_attn_fwd_gqa", True, q, k, v, r, o, m, want_m, stream)
 
 
 def sb_attn_bwd_gqa(q, k, v, m, dout, r=None, dq=None, dk=None, dv=None, dr=None, workspace=None, stream=None):
     """bf16 backward with grouped kv heads.  Returns (dq, dk, dv) in fp32 (dk, dv [B,Hkv,T,d]),
     and dr [H,d] as a fourth item when r is given."""
-    B, H, T, d = _dims(q)
-    Hkv = _dims(k)[1]
-    kv_shape = (B, Hkv, T, d)
-    mk = lambda shape: torch.empty(shape, dtype=torch.float32, device=q.device)
-    dq = mk(q.shape) if dq is None else dq
-    dk = mk(kv_shape) if dk is None else dk
-    dv = mk(kv_shape) if dv is None else dv
-    if r is not None and dr is None:
-        dr = mk((H, d))
-    workspace, ws_ptr, ws_bytes = _workspace(workspace, B, H, T, d, q.device)
-    rc = load().sb_attn_bwd_gqa(_ptr(q, torch.bfloat16, None, "q"), _ptr(k, torch.bfloat16, kv_shape, "k"),
-                                _ptr(v, torch.bfloat16, kv_shape, "v"), _ptr(r, torch.bfloat16, (H, d), "r"),
-                                _ptr(m, torch.float32, (B, H, T), "m"),
-                                _ptr(dout, torch.bfloat16, q.shape, "dout"),
-                                _ptr(dq, torch.float32, q.shape, "dq"), _ptr(dk, torch.float32, kv_shape, "dk"),
-                                _ptr(dv, torch.float32, kv_shape, "dv"), _ptr(dr, torch.float32, (H, d), "dr"),
-                                ws_ptr, ws_bytes, B, H, Hkv, T, d, _stream(stream))
-    _check(rc, "sb_attn_bwd_gqa")
-    return (dq, dk, dv, dr) if r is not None else (dq, dk, dv)
-
-
-def _dims3(t, name):
-    if t.dim() != 3:
-        raise SbAttnError(f"{name}: expected a packed [H, Ttot, d] tensor")
-    return tuple(int(x) for x in t.shape)
+    return (_ext or _load_ext()).backward("sb_attn_bwd_gqa", True, q, k, v, r, m, dout, dq, dk, dv, dr,
+                                          workspace, stream)
 
 
 def sb_attn_varlen_fwd(q, k, v, cu_seqlens, max_T, r=None, o=None, m=None, want_m=True, stream=None):
     """bf16 forward on a packed variable-length batch: q [H,Ttot,d], k, v [Hkv,Ttot,d],
     cu_seqlens int32 [nseq+1] on the GPU, max_T >= the longest sequence.  Returns (o, m) or o."""
-    H, Ttot, d = _dims3(q, "q")
-    Hkv = _dims3(k, "k")[0]
-    nseq = int(cu_seqlens.numel()) - 1
-    if o is None:
-        o = torch.empty_like(q)
-    if m is None and want_m:
-        m = torch.empty((H, Ttot), dtype=torch.float32, device=q.device)
-    kv_shape = (Hkv, Ttot, d)
-    rc = load().sb_attn_varlen_fwd(_ptr(q, torch.bfloat16, None, "q"), _ptr(k, torch.bfloat16, kv_shape, "k"),
-                                   _ptr(v, torch.bfloat16, kv_shape, "v"), _ptr(r, torch.bfloat16, (H, d), "r"),
-                                   _ptr(o, torch.bfloat16, q.shape, "o"), _ptr(m, torch.float32, (H, Ttot), "m"),
-                                   _ptr(cu_seqlens, torch.int32, None, "cu_seqlens"),
-                                   nseq, H, Hkv, Ttot, int(max_T), d, _stream(stream))
-    _check(rc, "sb_attn_varlen_fwd")
-    return (o, m) if m is not None else o
+    return (_ext or _load_ext()).varlen_forward(q, k, v, cu_seqlens, max_T, r, o, m, want_m, stream)
 
 
 def sb_attn_varlen_bwd_workspace_bytes(nseq, H, Ttot, max_T, d) -> int:
@@ -324,112 +230,33 @@ def sb_attn_varlen_bwd_workspace_bytes(nseq, H, Ttot, max_T, d) -> int:
 def sb_attn_varlen_bwd(q, k, v, m, dout, cu_seqlens, max_T, r=None, dq=None, dk=None, dv=None, dr=None,
                        workspace=None, stream=None):
     """bf16 backward on a packed variable-length batch.  Returns (dq, dk, dv[, dr]) in fp32."""
-    H, Ttot, d = _dims3(q, "q")
-    Hkv = _dims3(k, "k")[0]
-    nseq = int(cu_seqlens.numel()) - 1
-    kv_shape = (Hkv, Ttot, d)
-    mk = lambda shape: torch.empty(shape, dtype=torch.float32, device=q.device)
-    dq = mk(q.shape) if dq is None else dq
-    dk = mk(kv_shape) if dk is None else dk
-    dv = mk(kv_shape) if dv is None else dv
-    if r is not None and dr is None:
-        dr = mk((H, d))
-    need = sb_attn_varlen_bwd_workspace_bytes(nseq, H, Ttot, int(max_T), d)
-    if workspace is None and need > 0:
-        workspace = torch.empty(need, dtype=torch.uint8, device=q.device)
-    ws_ptr = ctypes.c_void_p(workspace.data_ptr()) if workspace is not None else None
-    ws_bytes = workspace.numel() * workspace.element_size() if workspace is not None else 0
-    rc = load().sb_attn_varlen_bwd(_ptr(q, torch.bfloat16, None, "q"), _ptr(k, torch.bfloat16, kv_shape, "k"),
-                                   _ptr(v, torch.bfloat16, kv_shape, "v"), _ptr(r, torch.bfloat16, (H, d), "r"),
-                                   _ptr(m, torch.float32, (H, Ttot), "m"),
-                                   _ptr(dout, torch.bfloat16, q.shape, "dout"),
-                                   _ptr(dq, torch.float32, q.shape, "dq"), _ptr(dk, torch.float32, kv_shape, "dk"),
-                                   _ptr(dv, torch.float32, kv_shape, "dv"), _ptr(dr, torch.float32, (H, d), "dr"),
-                                   _ptr(cu_seqlens, torch.int32, None, "cu_seqlens"),
-                                   nseq, H, Hkv, Ttot, int(max_T), d, ws_ptr, ws_bytes, _stream(stream))
-    _check(rc, "sb_attn_varlen_bwd")
-    return (dq, dk, dv, dr) if r is not None else (dq, dk, dv)
+    return (_ext or _load_ext()).varlen_backward(q, k, v, m, dout, cu_seqlens, max_T, r, dq, dk, dv, dr,
+                                                 workspace, stream)
 
 
 def sb_attn_decode(q, k, v, T=None, r=None, o=None, m=None, want_m=False, workspace=None, stream=None):
     """Single-token decode: q [B,H,d], cache k, v [B,Hkv,Tcap,d] with the first T rows valid
     (T defaults to Tcap).  Returns o [B,H,d] (bf16), or (o, m) when m is wanted."""
-    if q.dim() != 3:
-        raise SbAttnError("q: expected [B, H, d]")
-    B, H, d = (int(x) for x in q.shape)
-    _, Hkv, Tcap, _ = _dims(k)
-    T = Tcap if T is None else int(T)
-    if o is None:
-        o = torch.empty_like(q)
-    if m is None and want_m:
-        m = torch.empty((B, H), dtype=torch.float32, device=q.device)
-    need = int(load().sb_attn_decode_workspace_bytes(B, H, T, d))
-    if workspace is None and need > 0:
-        workspace = torch.empty(need, dtype=torch.uint8, device=q.device)
-    ws_ptr = ctypes.c_void_p(workspace.data_ptr()) if workspace is not None else None
-    ws_bytes = workspace.numel() * workspace.element_size() if workspace is not None else 0
-    kv_shape = (B, Hkv, Tcap, d)
-    rc = load().sb_attn_decode(_ptr(q, torch.bfloat16, None, "q"), _ptr(k, torch.bfloat16, kv_shape, "k"),
-                               _ptr(v, torch.bfloat16, kv_shape, "v"), _ptr(r, torch.bfloat16, (H, d), "r"),
-                               _ptr(o, torch.bfloat16, q.shape, "o"), _ptr(m, torch.float32, (B, H), "m"),
-                               ws_ptr, ws_bytes, B, H, Hkv, T, Tcap, d, _stream(stream))
-    _check(rc, "sb_attn_decode")
-    return (o, m) if m is not None else o
+    return (_ext or _load_ext()).decode(q, k, v, T, r, o, m, want_m, workspace, stream, False)
 
 
 def sb_attn_decode_static(q, k, v, o, T=None, r=None, m=None, stream=None):
     """sb_attn_decode on the library's own static device scratch: nothing is allocated, so the
     caller passes every output (o [B,H,d] bf16, optionally m [B,H] fp32)."""
-    if q.dim() != 3:
-        raise SbAttnError("q: expected [B, H, d]")
-    B, H, d = (int(x) for x in q.shape)
-    _, Hkv, Tcap, _ = _dims(k)
-    T = Tcap if T is None else int(T)
-    kv_shape = (B, Hkv, Tcap, d)
-    rc = load().sb_attn_decode_static(_ptr(q, torch.bfloat16, None, "q"), _ptr(k, torch.bfloat16, kv_shape, "k"),
-                                      _ptr(v, torch.bfloat16, kv_shape, "v"), _ptr(r, torch.bfloat16, (H, d), "r"),
-                                      _ptr(o, torch.bfloat16, q.shape, "o"), _ptr(m, torch.float32, (B, H), "m"),
-                                      B, H, Hkv, T, Tcap, d, _stream(stream))
-    _check(rc, "sb_attn_decode_static")
-    return (o, m) if m is not None else o
-
-
-def _workspace(workspace, B, H, T, d, device):
-    need = sb_attn_bwd_workspace_bytes(B, H, T, d)
-    if workspace is None and need > 0:
-        workspace = torch.empty(need, dtype=torch.uint8, device=device)
-    ws_ptr = ctypes.c_void_p(workspace.data_ptr()) if workspace is not None else None
-    ws_bytes = workspace.numel() * workspace.element_size() if workspace is not None else 0
-    return workspace, ws_ptr, ws_bytes
+    return (_ext or _load_ext()).decode(q, k, v, T, r, o, m, False, None, stream, True)
 
 
 def sb_attn_bwd_dq(q, k, v, m, dout, dq=None, workspace=None, stream=None):
     """Query-stationary pass of the backward.  Returns (dq, workspace)."""
-    B, H, T, d = _dims(q)
-    dq = torch.empty(q.shape, dtype=torch.float32, device=q.device) if dq is None else dq
-    workspace, ws_ptr, ws_bytes = _workspace(workspace, B, H, T, d, q.device)
-    rc = load().sb_attn_bwd_dq(_ptr(q, torch.bfloat16, None, "q"), _ptr(k, torch.bfloat16, q.shape, "k"),
-                               _ptr(v, torch.bfloat16, q.shape, "v"), _ptr(m, torch.float32, (B, H, T), "m"),
-                               _ptr(dout, torch.bfloat16, q.shape, "dout"),
-                               _ptr(dq, torch.float32, q.shape, "dq"), ws_ptr, ws_bytes,
-                               B, H, T, d, _stream(stream))
-    _check(rc, "sb_attn_bwd_dq")
-    return dq, workspace
+    if workspace is None:
+        need = sb_attn_bwd_workspace_bytes(*_dims(q))
+        workspace = torch.empty(need, dtype=torch.uint8, device=q.device) if need > 0 else None
+    return (_ext or _load_ext()).backward_dq(q, k, v, m, dout, dq, workspace, stream), workspace
 
 
 def sb_attn_bwd_dkdv(q, k, v, dout, workspace, dk=None, dv=None, stream=None):
     """Key-stationary pass of the backward (after sb_attn_bwd_dq on the same workspace).  Returns (dk, dv)."""
-    B, H, T, d = _dims(q)
-    mk = lambda: torch.empty(q.shape, dtype=torch.float32, device=q.device)
-    dk = mk() if dk is None else dk
-    dv = mk() if dv is None else dv
-    _, ws_ptr, ws_bytes = _workspace(workspace, B, H, T, d, q.device)
-    rc = load().sb_attn_bwd_dkdv(_ptr(q, torch.bfloat16, None, "q"), _ptr(k, torch.bfloat16, q.shape, "k"),
-                                 _ptr(v, torch.bfloat16, q.shape, "v"), _ptr(dout, torch.bfloat16, q.shape, "dout"),
-                                 _ptr(dk, torch.float32, q.shape, "dk"), _ptr(dv, torch.float32, q.shape, "dv"),
-                                 ws_ptr, ws_bytes, B, H, T, d, _stream(stream))
-    _check(rc, "sb_attn_bwd_dkdv")
-    return dk, dv
+    return (_ext or _load_ext()).backward_dkdv(q, k, v, dout, workspace, dk, dv, stream)
 
 
 def sb_diag_mfma_rate(operands, iters=2000, stream=None):
