@@ -21,13 +21,19 @@
 //                   accumulates dV += A^T dO, dK += dZ^T Q.
 // The element-wise arithmetic runs in the linear domain inside a lane (one exponential
 // and one reciprocal per element, see subtile_stage1/2); where its running product
-// leaves the fp32 range (sharp logits) the kernel only records that in a per-block
-// flag, and a second launch of the same kernel in its log-domain variant (SLOW)
-// redoes exactly the flagged blocks and returns at once for the others.  Keeping the
-// overflow-proof form out of the fast kernels keeps them within their register budget.
+// leaves the fp32 range (sharp logits) the wave takes the logits of that subtile once
+// more from LDS and redoes its first stage in the log domain (subtile_stage1_log).
+// Recomputing them there, instead of keeping the accumulator for the case, is what keeps
+// the kernels within their register budget; a second launch of a log-domain variant for
+// flagged blocks, which this replaces, cost 7 us a pass with nothing flagged.
+// Far keys: once every row of a query block has less than 2^-160 of its stick left, all
+// weights and logit gradients beyond are zero (CARRY_EXHAUSTED).  The query-stationary
+// pass first looks for that point from the diagonal, with the logits alone (find_start()),
+// starts its sweep there and leaves the tile in `first`, one per query block; the
+// key-stationary pass visits only the query blocks that reach its keys.
 // Both kernels give a workgroup two blocks, p and n-1-p, whose causal costs add up
-// to the same total for every p, and stage their streamed tiles with direct
-// global->LDS loads, double buffered, one barrier per 64-row tile.  The 1/sqrt(d)
+// to the same total for every p (or one, see share_of()), and stage their streamed tiles
+// with direct global->LDS loads, double buffered, one barrier per 64-row tile.  The 1/sqrt(d)
 // of dQ and dK is applied once, to the accumulators, on store.
 //
 // Register layout is the forward's: S^T = K Q^T and P^T = V dO^T with the
@@ -83,59 +89,12 @@ struct SubtileOut {
     float g_tot;     // sum of G over the subtile's 32 keys
 };
 
-// Log-domain form (Eq. 2 / Eq. 4 as printed), overflow-proof; used only where the
-// linear-domain chain of subtile_math leaves its range.
-template <bool CA_INCLUDES_SUBTILE, bool MASK>
-__device__ __forceinline__ void subtile_math_log(SubtileOut& out, const f32x16& sacc, const f32x16& pacc,
-                                              float ca, float cb, float c2, int n, int hh)
-{
-    float x[16], sp[16], cs[16];
-#pragma unroll
-    for (int r = 0; r < 16; ++r) x[r] = sacc[r] * c2;
-    if (MASK) {
-#pragma unroll
-        for (int r = 0; r < 16; ++r) x[r] = (16 * hh + r < n) ? x[r] : -INFINITY;
-    }
-    float run = 0.0f;
-#pragma unroll
-    for (int r = 15; r >= 0; --r) {
-        sp[r] = sp2(x[r]);
-        run += sp[r];
-        cs[r] = run;                                       // keys r..15 of this lane
-    }
-    float tot_lo, tot_hi;
-    both_halves(run, tot_lo, tot_hi);
-    const float car = CA_INCLUDES_SUBTILE ? ca - (tot_lo + tot_hi) : ca;
-    out.ca_right = car;
-    const float off = car + (hh == 0 ? tot_hi : 0.0f);
-    float g[16], pre[16];
-    float grun = 0.0f;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-        const float w = fast_exp2((x[r] - off) - cs[r]);   // A (Eq. 2)
-        out.pa[r >> 3][r & 7] = (__bf16)w;
-        g[r] = w * pacc[r];                                // dL/dlogA = A * dL/dA
-        grun += g[r];
-        pre[r] = grun;                                     // inclusive prefix inside the lane
-    }
-    float g_lo, g_hi;
-    both_halves(grun, g_lo, g_hi);
-    out.g_tot = g_lo + g_hi;
-    const float boff = cb + (hh == 1 ? g_lo : 0.0f);
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-        const float beta = fast_exp2(x[r] - sp[r]);        // sigma(z)
-        const float dz = g[r] - beta * (pre[r] + boff);    // Eq. 4
-        out.pz[r >> 3][r & 7] = (__bf16)dz;
-    }
-}
-
-// The same in the linear domain inside the lane, as in the forward: with e_r = 2^{x_r}
+// In the linear domain inside the lane, as in the forward: with e_r = 2^{x_r}
 // the chain t_r = W_r e_r, W_{r+1} = W_r + t_r over ascending keys gives
 // A[r] = t_r / W_16 * 2^-(sp2 total of all nearer keys), and sigma = e / (1 + e):
 // one exponential and one reciprocal per element instead of three exponentials and
 // a logarithm.  W_0 = 2^-60; a chain that gets beyond 2^80 (or overflows) makes the
-// caller redo the subtile with subtile_math_log.  Two stages, so that the dO.v
+// caller redo the stage with subtile_stage1_log.  Two stages, so that the dO.v
 // accumulator need not be live during the first:
 //   stage 1 (logits only): sigma, chain.  Returns false in a lane whose chain left its range.
 //   stage 2 (needs dO.v): A, G, dZ.
@@ -146,8 +105,9 @@ __device__ __forceinline__ void subtile_math_log(SubtileOut& out, const f32x16& 
 // visible to query n iff 16hh + r < n (the subtile on the diagonal).
 struct Chain {
     float be[16];    // sigma(z)
-    float t[16];     // chain terms, later G
-    float W;         // end of the chain
+    float t[16];     // chain terms: A = t * 2^-(norm + sp2 total of all nearer lanes' keys); later G
+    float l;         // sp2 total of this lane's 16 keys
+    float norm;      // log2 of what t is still to be divided by
 };
 
 // How sigma = e / (1 + e) is formed (SIGMA):
@@ -170,7 +130,8 @@ __device__ __forceinline__ bool subtile_stage1(Chain& ch, const f32x16& sacc, fl
         else if (SIGMA == 1) ch.be[r] = ch.t[r] * __builtin_amdgcn_rcpf(W);
         else ch.be[r] = e;                                 // kept for the backward chain below
     }
-    ch.W = W;
+    ch.norm = fast_log2(W);                                // W_16 = 2^(l - 60)
+    ch.l = ch.norm + 60.0f;
     if (SIGMA == 2) {
         float inv = __builtin_amdgcn_rcpf(W);              // 1 / W_16; 0 where the chain overflowed
 #pragma unroll
@@ -183,17 +144,35 @@ __device__ __forceinline__ bool subtile_stage1(Chain& ch, const f32x16& sacc, fl
     return W < 0x1p80f;                                    // false: this lane's chain left its range
 }
 
+// Stage 1 in the log form of Eq. 2, overflow-proof: t = 2^(x - sum of sp2 over this lane's keys
+// from its own on), sigma = 2^(x - sp2(x)).
+template <bool MASK>
+__device__ __forceinline__ void subtile_stage1_log(Chain& ch, const f32x16& sacc, float c2, int n, int hh)
+{
+    float run = 0.0f;
+#pragma unroll
+    for (int r = 15; r >= 0; --r) {
+        float x = sacc[r] * c2;
+        if (MASK) x = (16 * hh + r < n) ? x : -INFINITY;
+        const float sp = sp2(x);
+        run += sp;
+        ch.be[r] = fast_exp2(x - sp);
+        ch.t[r] = fast_exp2(x - run);
+    }
+    ch.l = run;
+    ch.norm = 0.0f;
+}
+
 template <bool CA_INCLUDES_SUBTILE, bool NEED_A>
 __device__ __forceinline__ void subtile_stage2(SubtileOut& out, Chain& ch, const f32x16& pacc,
                                                float ca, float cb, int hh)
 {
-    const float l = fast_log2(ch.W) + 60.0f;               // sp2 total of this lane's 16 keys
     float l_lo, l_hi;
-    both_halves(l, l_lo, l_hi);
+    both_halves(ch.l, l_lo, l_hi);
     const float car = CA_INCLUDES_SUBTILE ? ca - (l_lo + l_hi) : ca;
     out.ca_right = car;
     // keys 16..31 (hh = 1) are nearer to the query than keys 0..15
-    const float kf = fast_exp2(60.0f - (car + l_hi + (hh == 0 ? l_lo : 0.0f)));
+    const float kf = fast_exp2(-(car + (hh == 0 ? l_hi : 0.0f) + ch.norm));
     // dZ = G - sigma * (prefix of G + boff), boff = cb + the partner half's total for the
     // nearer half: the part that needs boff is added once boff is known
     float grun = 0.0f;
@@ -242,59 +221,60 @@ __device__ __forceinline__ void stage_offsets(int (&goff)[StageCfg<D>::NPW], int
     }
 }
 
+// one 64-row tile of X alone
+template <int D, bool PERM>
+__device__ __forceinline__ void stage_one(const uint16_t* X, int jt, int T, char* sp,
+                                          const int (&goff)[StageCfg<D>::NPW], int wave, int lane)
+{
+    using C = StageCfg<D>;
+    if ((jt + 1) * TK <= T) {                           // all 64 rows exist
+        dma16_to_lds_run(X + (long)jt * TK * D, goff, sp + wave * C::NPW * 1024);
+    } else {                                            // rows past T are clamped (their results are masked)
+#pragma unroll
+        for (int i = 0; i < C::NPW; ++i) {
+            const int row = (wave * C::NPW + i) * C::BLK_ROWS + lane / C::CPR;
+            const int c = (lane % C::CPR) ^ (PERM ? swz_perm<D>(row) : swz_nat<D>(row));
+            const long gr = min(jt * TK + row, T - 1);
+            dma16_to_lds(X + gr * D + c * 8, sp + (wave * C::NPW + i) * 1024);
+        }
+    }
+}
+
+// and of X, then Y
 template <int D, bool PERM>
 __device__ __forceinline__ void stage_tile(const uint16_t* X, const uint16_t* Y, int jt, int T, char* sp,
                                            const int (&goff)[StageCfg<D>::NPW], int wave, int lane)
 {
     using C = StageCfg<D>;
-    if ((jt + 1) * TK <= T) {                           // all 64 rows exist
-        const uint16_t* xb = X + (long)jt * TK * D;
-        const uint16_t* yb = Y + (long)jt * TK * D;
-#pragma unroll
-        for (int i = 0; i < C::NPW; ++i) dma16_to_lds_saddr(xb, goff[i], sp + (wave * C::NPW + i) * 1024);
-#pragma unroll
-        for (int i = 0; i < C::NPW; ++i) dma16_to_lds_saddr(yb, goff[i], sp + C::TILE + (wave * C::NPW + i) * 1024);
-    } else {                                            // rows past T are clamped (their results are masked)
-#pragma unroll
-        for (int m = 0; m < 2; ++m) {
-            const uint16_t* G = m == 0 ? X : Y;
-#pragma unroll
-            for (int i = 0; i < C::NPW; ++i) {
-                const int row = (wave * C::NPW + i) * C::BLK_ROWS + lane / C::CPR;
-                const int swz = PERM ? swz_perm<D>(row) : swz_nat<D>(row);
-                const int c = (lane % C::CPR) ^ swz;
-                const long gr = min(jt * TK + row, T - 1);
-                dma16_to_lds(G + gr * D + c * 8, sp + m * C::TILE + (wave * C::NPW + i) * 1024);
-            }
-        }
-    }
+    stage_one<D, PERM>(X, jt, T, sp, goff, wave, lane);
+    stage_one<D, PERM>(Y, jt, T, sp + C::TILE, goff, wave, lane);
 }
 
 // ------------------------------------------------------------------ dQ kernel
 // VL (both kernels): packed variable-length batch, tensors [H][Ttot][D] ([H/G][Ttot][D] for
 // k, v, dk, dv) with sequence s at rows cu[s] .. cu[s+1]-1.  BH counts (sequence, head)
 // pairs; T_arg and the block counts describe the longest sequence (they size the grid, the
-// flag arrays and the carries, which are then laid out [head][strip][Ttot]); a workgroup
+// array `first` and the carries, which are then laid out [head][strip][Ttot]); a workgroup
 // whose blocks lie beyond its own sequence's end returns at once.
-template <int D, bool SLOW, bool RB, bool VL>
-__global__ void __launch_bounds__(NTHREADS, SLOW ? 1 : 2)
+template <int D, bool RB, bool VL>
+__global__ void __launch_bounds__(NTHREADS, 2)
 bwd_dq_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
               const uint16_t* __restrict__ v, const uint16_t* __restrict__ rb,
               const float* __restrict__ m,
               const uint16_t* __restrict__ dout, float* __restrict__ dq,
-              float* __restrict__ ca, float* __restrict__ cb, int* __restrict__ flags,
-              int T_arg, int BH, int H, int G, int nqb_arg, int nt32, const int* __restrict__ cu, int Ttot)
+              float* __restrict__ ca, float* __restrict__ cb, int* __restrict__ first,
+              int T_arg, int BH, int H, int G, int nqb_arg, int nt32, const int* __restrict__ cu, int Ttot,
+              int spread, int single)
 {
     using C = StageCfg<D>;
     __shared__ __attribute__((aligned(1024))) char smem[2 * C::STAGE];
-    __shared__ int s_dirty;
+    __shared__ __attribute__((aligned(16))) int s_done[2][NW];   // find_start(): per parity and wave
 
     const int wg = blockIdx.x;
-    const int xcd = wg & 7, slot = wg >> 3;
-    const int npair = (nqb_arg + 1) >> 1;
-    const long bh = xcd + 8L * (slot / npair);
-    const int pidx = slot % npair;
-    if (bh >= BH) return;
+    Share sh;
+    if (!share_of(sh, wg, BH, (nqb_arg + 1) >> 1, spread, single)) return;
+    const long bh = sh.bh;
+    const int pidx = sh.p;
     int T = T_arg, nqb = nqb_arg;
     long row0, kvrow0, cbase, cstride;      // first q / k row of this head; carries: base and strip stride
     int head;
@@ -357,7 +337,6 @@ bwd_dq_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     float a2 = 0.0f;                        // sum of sp2 from the sweep position up to the query
     float bsum = 0.0f;                      // sum of G over the keys already passed
     int q0 = 0;
-    bool dirty = false;                     // a chain of this lane left its range (fast variant)
 
     // one 32-key subtile at keys key0 .. key0+31
     // ktile: LDS address of the subtile's K rows (its V rows lie C::TILE further)
@@ -391,17 +370,11 @@ bwd_dq_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
             return acc;
         };
         SubtileOut so;
-        if constexpr (SLOW) {
-            const f32x16 sacc = s_mfma();
-            const f32x16 pacc = p_mfma();
-            subtile_math_log<true, MASK>(so, sacc, pacc, a2, bsum, c2, n, hh);
-        } else {
-            Chain ch;
-            const f32x16 sacc = s_mfma();
-            dirty |= !subtile_stage1<MASK, SIGMA_DQ>(ch, sacc, c2, n, hh);
-            const f32x16 pacc = p_mfma();
-            subtile_stage2<true, false>(so, ch, pacc, a2, bsum, hh);
-        }
+        Chain ch;
+        const bool fits = subtile_stage1<MASK, SIGMA_DQ>(ch, s_mfma(), c2, n, hh);
+        if (__builtin_amdgcn_ballot_w64(!fits) != 0) subtile_stage1_log<MASK>(ch, s_mfma(), c2, n, hh);
+        const f32x16 pacc = p_mfma();
+        subtile_stage2<true, false>(so, ch, pacc, a2, bsum, hh);
         // carries of this (subtile, query) for the key-stationary kernel
         if (hh == 0 && q0 + n < T) {
             const long ci = (long)(key0 >> 5) * cstride + q0 + n;
@@ -427,16 +400,76 @@ bwd_dq_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
                 dqacc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(so.pz[s], kt[2 * b + s], dqacc[b], 0, 0, 0);
     };
 
-    for (int part = 0; part < 2; ++part) {
+    // Where the sweep of the block at Q0 has to start: the tile beyond which every row is exhausted,
+    // 0 if there is none or if looking for it would not pay.  From the diagonal towards key 0, two K
+    // tiles per staging buffer and barrier, logits and softplus totals only (a third of the sweep's
+    // matrix work, a quarter of its vector work).  Sets a2 to the carry at that tile's left edge,
+    // which also spares the start a sum over all keys that is then subtracted again.
+    // Tried only where m says that the rows have at least twice what exhausts them, so that the
+    // point is expected in the nearer half, and given up after that half: at worst a sixth more.
+    auto find_start = [&](const uint16_t* Kg, int T, int ntile, int nclean, bool wave_live) __attribute__((always_inline)) {
+        const int limit = ntile >> 2;                        // pairs of tiles
+        if (wave_live ? __builtin_amdgcn_ballot_w64(!(a2 >= 2.0f * CARRY_EXHAUSTED)) == 0 : true) {
+            if (lane == 0) s_done[1][wave] = 1;
+        } else if (lane == 0) s_done[1][wave] = 0;
+        barrier_lds();
+        if (nclean < 6 || !waves_done(s_done[1])) return 0;
+        auto stage_pair = [&](int i) __attribute__((always_inline)) {
+            char* sp = smem + (i & 1) * C::STAGE;
+            const int t = ntile - 1 - 2 * i;                 // the upper tile of the pair; 2 * limit <= ntile
+            stage_one<D, true>(Kg, t, T, sp, goff, wave, lane);
+            stage_one<D, true>(Kg, t - 1, T, sp + C::TILE, goff, wave, lane);
+        };
+        float l = 0.0f, left = 0.0f;                         // this lane's keys only; both halves'
+        auto sum_subtile = [&](auto mask_c, uint32_t ktile) __attribute__((always_inline)) {
+            constexpr bool MASK = decltype(mask_c)::value;
+            const uint32_t ka = ktile + aoff0;
+            u32x4 kw[D / 16];
+#pragma unroll
+            for (int s = 0; s < D / 16; ++s) kw[s] = lds_load16(ka ^ (s << 5));
+            f32x16 acc;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
+#pragma unroll
+            for (int s = 0; s < D / 16; ++s)
+                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kw[s]), qf[s], acc, 0, 0, 0);
+            l += sp2_total<MASK>(acc, c2, n, hh);
+        };
+        stage_pair(0);
+        for (int i = 0;; ++i) {
+            dma_wait<0>();
+            barrier_lds();
+            // the flags of pair i - 1; all waves read the same words and leave together
+            if (i > 0 && waves_done(s_done[(i + 1) & 1])) {
+                a2 = left;
+                return ntile - 2 * i;
+            }
+            if (i == limit) return 0;
+            if (i + 1 < limit) stage_pair(i + 1);
+            if (wave_live) {
+#pragma unroll
+                for (int x = 0; x < 4; ++x) {
+                    const int key0 = (ntile - 2 * i) * TK - 32 * (x + 1);
+                    const uint32_t kt = smem0 + (i & 1) * C::STAGE + (x >> 1) * C::TILE + (1 - (x & 1)) * 32 * C::ROW;
+                    if (key0 == q0) sum_subtile(bc<true>{}, kt);
+                    else if (key0 < q0) sum_subtile(bc<false>{}, kt);
+                }
+            }
+            float l_lo, l_hi;
+            both_halves(l, l_lo, l_hi);
+            left = l_lo + l_hi;
+            const int d = !wave_live || __builtin_amdgcn_ballot_w64(!(left >= CARRY_EXHAUSTED)) == 0;
+            if (lane == 0) s_done[i & 1][wave] = d;
+        }
+    };
+
+    for (int part = sh.part0; part < sh.part1; ++part) {
         const int qb = part == 0 ? nqb - 1 - pidx : pidx;
         if (part == 1 && 2 * pidx == nqb - 1) break;     // odd block count: the middle block is alone
-        if (SLOW && flags[bh * nqb_arg + qb] == 0) continue;  // only the blocks the fast variant flagged
         const int Q0 = qb * BQ;
         q0 = Q0 + wave * 32;
         const bool wave_live = q0 < T;
         const int jq = min(q0 + n, T - 1);
-        if (tid == 0) s_dirty = 0;
-        dirty = false;
         barrier_nofence();                               // everyone is done with the stages of the block before
         {
             const u32x4* qs = reinterpret_cast<const u32x4*>(q + base + (long)jq * D + 8 * hh);
@@ -483,7 +516,9 @@ bwd_dq_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
         const int kmax = min(T, Q0 + BQ) - 1;            // keys 0 .. kmax-1 are visible to some row
         const int ntile = (kmax + TK - 1) / TK;
         const int nclean = min(ntile, Q0 / TK);          // tiles entirely left of the block's rows
-        stage_tile<D, true>(Kg, Vg, 0, T, smem, goff, wave, lane);
+        const int t0 = find_start(Kg, T, ntile, nclean, wave_live);
+        if (tid == 0) first[bh * nqb_arg + qb] = t0;
+        stage_tile<D, true>(Kg, Vg, t0, T, smem + (t0 & 1) * C::STAGE, goff, wave, lane);
         auto begin_iter = [&](int it) __attribute__((always_inline)) {
             dma_wait<0>();                               // this wave's share of tile `it` has landed
             barrier_nofence();                           // ... everyone's has, and tile it-1 is no longer read
@@ -491,7 +526,7 @@ bwd_dq_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
             stage_tile<D, true>(Kg, Vg, it + 1 < ntile ? it + 1 : 0, T, smem + ((it + 1) & 1) * C::STAGE, goff, wave, lane);
             return smem0 + (it & 1) * C::STAGE;
         };
-        int it = 0;
+        int it = t0;
         for (; it < nclean; ++it) {                      // fully visible tiles
             const uint32_t sp = begin_iter(it);
             subtile(bc<false>{}, sp, it * TK);
@@ -522,11 +557,6 @@ bwd_dq_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
                 }
             }
         }
-        if constexpr (!SLOW) {
-            if (__builtin_amdgcn_ballot_w64(dirty) != 0 && lane == 0) atomicOr(&s_dirty, 1);
-            __syncthreads();
-            if (tid == 0) flags[bh * nqb_arg + qb] = s_dirty;
-        }
     }
 }
 
@@ -538,6 +568,7 @@ struct KvHead {
     long base;                              // first element of the kv head's K / V / dK / dV rows
     long qrow0, qrow_step;                  // first Q / dO row of query head qh0, step to the next head
     long cbase, cbase_step, cstride;        // carries: start for head qh0, step per head, strip stride
+    long qhead0;                            // index of head qh0 in `first`
 };
 
 template <int D, bool VL>
@@ -556,6 +587,7 @@ __device__ __forceinline__ bool kv_head(KvHead& kh, long bh, int pidx, int T_arg
         kh.base = ((long)hkv * Ttot + c0) * D;
         kh.qrow0 = (long)hkv * G * Ttot + c0;
         kh.qrow_step = Ttot;
+        kh.qhead0 = (long)seq * H + hkv * G;
         kh.cbase = (long)hkv * G * nt32 * Ttot + c0;
         kh.cbase_step = (long)nt32 * Ttot;
         kh.cstride = Ttot;
@@ -565,12 +597,33 @@ __device__ __forceinline__ bool kv_head(KvHead& kh, long bh, int pidx, int T_arg
         kh.nkb = nkb_arg;
         kh.base = bh * (long)T_arg * D;
         kh.qrow0 = qh0 * (long)T_arg;
+        kh.qhead0 = qh0;
         kh.qrow_step = T_arg;
         kh.cbase = qh0 * (long)nt32 * T_arg;
         kh.cbase_step = (long)nt32 * T_arg;
         kh.cstride = T_arg;
     }
     return true;
+}
+
+// Which query tiles reach key block kb, from the query blocks' start tiles f[0 .. nqb-1]: none
+// from tile `end` on; all tiles before `sure` reach every key of it.  In between a tile reaches
+// a strip's keys iff f[tile / 2] <= the strip's 64-key tile.  The block's own queries always do.
+struct Reach {
+    int sure, end;
+};
+__device__ __forceinline__ Reach reach_of(const int* __restrict__ f, int kb, int nqb, int lane)
+{
+    static_assert(BQ == 2 * TK && BKW == 2 * TK, "two tiles per block on either side");
+    int last = kb, cut = nqb;
+    for (int b = kb + 1; b < nqb; b += 64) {
+        const int t = b + lane < nqb ? f[b + lane] : 0x7fffffff;
+        const unsigned long long some = __builtin_amdgcn_ballot_w64(t <= 2 * kb + 1);
+        const unsigned long long not_all = __builtin_amdgcn_ballot_w64(t > 2 * kb);
+        if (some) last = b + 63 - __builtin_clzll(some);
+        if (not_all && cut == nqb) cut = min(nqb, b + __builtin_ctzll(not_all));
+    }
+    return {2 * cut, 2 * (last + 1)};
 }
 
 // ------------------------------------------------------------------ dK / dV kernel
@@ -580,26 +633,25 @@ template <int D> struct DkvCfg {
     static constexpr int LDS_BYTES = T_OFF + NW * T_WAVE;
 };
 
-template <int D, bool SLOW, bool GQA, bool VL>
-__global__ void __launch_bounds__(NTHREADS, (D == 128 || SLOW) ? 1 : 2)
+template <int D, bool GQA, bool VL>
+__global__ void __launch_bounds__(NTHREADS, 2)
 bwd_dkv_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
                const uint16_t* __restrict__ v, const uint16_t* __restrict__ dout,
                const float* __restrict__ ca, const float* __restrict__ cb,
-               float* __restrict__ dk, float* __restrict__ dv, int* __restrict__ flags,
-               int T_arg, int BH, int H, int G_arg, int nkb_arg, int nt32, const int* __restrict__ cu, int Ttot)
+               float* __restrict__ dk, float* __restrict__ dv, const int* __restrict__ first,
+               int T_arg, int BH, int H, int G_arg, int nkb_arg, int nt32, const int* __restrict__ cu, int Ttot,
+               int spread, int single)
 {
     using C = StageCfg<D>;
     using CK = DkvCfg<D>;
     const int G = GQA ? G_arg : 1;                      // query heads per kv head
     __shared__ __attribute__((aligned(1024))) char smem[CK::LDS_BYTES];
-    __shared__ int s_dirty;
 
     const int wg = blockIdx.x;
-    const int xcd = wg & 7, slot = wg >> 3;
-    const int npair = (nkb_arg + 1) >> 1;
-    const long bh = xcd + 8L * (slot / npair);
-    const int pidx = slot % npair;
-    if (bh >= BH) return;
+    Share sh;
+    if (!share_of(sh, wg, BH, (nkb_arg + 1) >> 1, spread, single)) return;
+    const long bh = sh.bh;
+    const int pidx = sh.p;
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -646,7 +698,6 @@ bwd_dkv_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     f32x16 dkacc[D / 32], dvacc[D / 32];
     const float* cag = nullptr;
     const float* cbg = nullptr;
-    bool dirty = false;                     // a chain of this lane left its range (fast variant)
 
     // one 32-query subtile at query rows j0 .. j0+31
     // the steps of one 32-query subtile (Q rows at qtile, dO rows C::TILE further).  All
@@ -723,28 +774,29 @@ bwd_dkv_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
         sp_mfma(qtile, sacc, pacc);
         bf16x8 gop[D / 16], qop[D / 16];
         mm2_fetch(qtile, gop, qop);                          // lands during the element-wise work
-        if constexpr (SLOW) {
-            subtile_math_log<false, MASK>(so, sacc, pacc, car, cbl, c2, n, hh);
-        } else {
-            Chain ch;
-            dirty |= !subtile_stage1<MASK, SIGMA_DKV>(ch, sacc, c2, n, hh);
-            subtile_stage2<false, true>(so, ch, pacc, car, cbl, hh);
+        Chain ch;
+        if (__builtin_amdgcn_ballot_w64(!subtile_stage1<MASK, SIGMA_DKV>(ch, sacc, c2, n, hh)) != 0) {
+            f32x16 again;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) again[r] = 0.0f;
+#pragma unroll
+            for (int s = 0; s < D / 16; ++s)
+                again = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[s], *reinterpret_cast<const bf16x8*>(qtile + boff[s]), again, 0, 0, 0);
+            subtile_stage1_log<MASK>(ch, again, c2, n, hh);
         }
+        subtile_stage2<false, true>(so, ch, pacc, car, cbl, hh);
         bf16x8 at[2], zt[2];
         transpose(so, at, zt);
         mm2(gop, qop, at, zt);
     };
 
-    for (int part = 0; part < 2; ++part) {
+    for (int part = sh.part0; part < sh.part1; ++part) {
         const int kb = part == 0 ? pidx : nkb - 1 - pidx;    // small kb = most later queries = first
         if (part == 1 && 2 * pidx == nkb - 1) break;
-        if (SLOW && flags[bh * nkb_arg + kb] == 0) continue; // only the blocks the fast variant flagged
         const int K0 = kb * BKW;
         const int k0 = K0 + wave * 32;                       // this wave's 32 keys
         const int kt32 = k0 >> 5;
         const bool wave_live = k0 < T;
-        if (tid == 0) s_dirty = 0;
-        dirty = false;
         barrier_nofence();                                   // everyone is done with the stages of the block before
         {
             const long kr = min(k0 + perm_row(n), T - 1);
@@ -777,16 +829,20 @@ bwd_dkv_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
         // issued: vector memory operations complete in order, so a wait for a carry
         // issued after the staging loads would wait for those as well.
         const int jt0 = K0 / TK;
-        const int ntile = max((T + TK - 1) / TK - jt0, 0);
+        const int* const fg = first + (kh.qhead0 + g) * nkb_arg;
+        const Reach reach = reach_of(fg, kb, nkb, lane);
+        const int ntile = max(min((T + TK - 1) / TK, reach.end) - jt0, 0);
         const int ndiag = min(ntile, BKW / TK);              // tiles that touch the diagonal band
         float cn[2][2];                                      // [subtile][ca, cb] of the next tile
         auto load_carries = [&](int jt) __attribute__((always_inline)) {
+            const bool there = wave_live && (jt < reach.sure || fg[jt >> 1] <= kt32 >> 1);
 #pragma unroll
             for (int u = 0; u < 2; ++u) {
                 const int j = jt * TK + 32 * u + n;
-                // rows past T: an infinite carry gives A = 0 and G = 0, and with cb = 0 also dZ = 0
-                cn[u][0] = (j < T && wave_live) ? cag[j] : INFINITY;   // a dead wave's rows lie outside the arrays
-                cn[u][1] = (j < T && wave_live) ? cbg[j] : 0.0f;
+                // rows past T, tiles that do not reach these keys: an infinite carry gives A = 0 and
+                // G = 0, and with cb = 0 also dZ = 0
+                cn[u][0] = (j < T && there) ? cag[j] : INFINITY;   // a dead wave's rows lie outside the arrays
+                cn[u][1] = (j < T && there) ? cbg[j] : 0.0f;
             }
         };
         if (ntile > 0) {
@@ -842,11 +898,6 @@ bwd_dkv_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
                 }
             }
         }
-        if constexpr (!SLOW) {
-            if (__builtin_amdgcn_ballot_w64(dirty) != 0 && lane == 0) atomicOr(&s_dirty, 1);
-            __syncthreads();
-            if (tid == 0) flags[bh * nkb_arg + kb] = s_dirty;
-        }
     }
 }
 
@@ -890,13 +941,14 @@ template <int D> struct Dkv3Cfg {
     static constexpr int NPW = (LOADS + NW2 - 1) / NW2;
 };
 
-template <int D, bool SLOW, bool GQA, bool VL>
+template <int D, bool GQA, bool VL>
 __global__ void __launch_bounds__(NTHREADS2, 1)
 bwd_dkv_pair_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
                     const uint16_t* __restrict__ v, const uint16_t* __restrict__ dout,
                     const float* __restrict__ ca, const float* __restrict__ cb,
-                    float* __restrict__ dk, float* __restrict__ dv, int* __restrict__ flags,
-                    int T_arg, int BH, int H, int G_arg, int nkb_arg, int nt32, const int* __restrict__ cu, int Ttot)
+                    float* __restrict__ dk, float* __restrict__ dv, const int* __restrict__ first,
+                    int T_arg, int BH, int H, int G_arg, int nkb_arg, int nt32, const int* __restrict__ cu, int Ttot,
+               int spread, int single)
 {
     using C = StageCfg<D>;
     using CK = Dkv3Cfg<D>;
@@ -905,11 +957,10 @@ bwd_dkv_pair_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
     __shared__ __attribute__((aligned(1024))) char smem[CK::LDS_BYTES];
 
     const int wg = blockIdx.x;
-    const int xcd = wg & 7, slot = wg >> 3;
-    const int npair = (nkb_arg + 1) >> 1;
-    const long bh = xcd + 8L * (slot / npair);
-    const int pidx = slot % npair;
-    if (bh >= BH) return;
+    Share sh;
+    if (!share_of(sh, wg, BH, (nkb_arg + 1) >> 1, spread, single)) return;
+    const long bh = sh.bh;
+    const int pidx = sh.p;
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -986,8 +1037,17 @@ bwd_dkv_pair_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
     f32x16 acc[D / 32];                     // dV (role 0) or dK (role 1) of the strip's 32 keys
     const float* cag = nullptr;
     const float* cbg = nullptr;
-    bool dirty = false;                     // a chain of this lane left its range (fast variant)
 
+    // the logits once more, for the log form (see subtile_stage1_log)
+    auto logits = [&](uint32_t qa) __attribute__((always_inline)) {
+        f32x16 acc;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
+#pragma unroll
+        for (int s = 0; s < D / 16; ++s)
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[s], __builtin_bit_cast(bf16x8, lds_load16(qa ^ (s << 5))), acc, 0, 0, 0);
+        return acc;
+    };
     // this wave's subtile of a tile: logits, dO.v, element-wise path; A and dZ to the scratch
     // qtile: LDS address of the subtile's Q rows (its dO rows lie C::TILE further); sc: LDS
     // address of this strip's scratch for the tile
@@ -1013,13 +1073,10 @@ bwd_dkv_pair_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
             pacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[s], __builtin_bit_cast(bf16x8, gw[s]), pacc, 0, 0, 0);
         }
         SubtileOut so;
-        if constexpr (SLOW) {
-            subtile_math_log<false, MASK>(so, sacc, pacc, car, cbl, c2, n, hh);
-        } else {
-            Chain ch;
-            dirty |= !subtile_stage1<MASK, SIGMA_DKV>(ch, sacc, c2, n, hh);
-            subtile_stage2<false, true>(so, ch, pacc, car, cbl, hh);
-        }
+        Chain ch;
+        if (__builtin_amdgcn_ballot_w64(!subtile_stage1<MASK, SIGMA_DKV>(ch, sacc, c2, n, hh)) != 0)
+            subtile_stage1_log<MASK>(ch, logits(qa), c2, n, hh);
+        subtile_stage2<false, true>(so, ch, pacc, car, cbl, hh);
         const uint32_t w = sc + role * CK::W_BYTES + sw_off;
         lds_store16(w, so.pa[0]);
         lds_store16(w ^ 16, so.pa[1]);
@@ -1082,12 +1139,13 @@ bwd_dkv_pair_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
         __builtin_amdgcn_s_setprio(2);
         // part B: the chain of the logits (vector) beside dO.v and the back of subtile 0 (matrix)
         Chain ch;
-        dirty |= !subtile_stage1<false, SIGMA_DKV>(ch, sacc, c2, n, hh);
+        const bool fits = subtile_stage1<false, SIGMA_DKV>(ch, sacc, c2, n, hh);
 #pragma unroll
         for (int s = 0; s < D / 16; ++s)
             pacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[s], __builtin_bit_cast(bf16x8, gw[s]), pacc, 0, 0, 0);
         back(ptile, scp, 0);
         __builtin_amdgcn_sched_barrier(0);
+        if (__builtin_amdgcn_ballot_w64(!fits) != 0) subtile_stage1_log<false>(ch, logits(qa), c2, n, hh);
         __builtin_amdgcn_s_setprio(1);
         // part C: A, G, dZ (vector) beside the back of subtile 1 (matrix)
         SubtileOut so;
@@ -1102,15 +1160,13 @@ bwd_dkv_pair_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
         __builtin_amdgcn_sched_barrier(0);
     };
 
-    for (int part = 0; part < 2; ++part) {
+    for (int part = sh.part0; part < sh.part1; ++part) {
         const int kb = part == 0 ? pidx : nkb - 1 - pidx;    // small kb = most later queries = first
         if (part == 1 && 2 * pidx == nkb - 1) break;
-        if (SLOW && flags[bh * nkb_arg + kb] == 0) continue; // only the blocks the fast variant flagged
         const int K0 = kb * BKW;
         const int k0 = K0 + strip * 32;                      // the strip's 32 keys
         const int kt32 = k0 >> 5;
         const bool live = k0 < T;
-        dirty = false;
         barrier_lds();                                       // everyone is done with the LDS of the block before
         {
             const long kr = min(k0 + perm_row(n), T - 1);
@@ -1144,24 +1200,30 @@ bwd_dkv_pair_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
         // issued at its start, after the carries of that tile (vector memory operations
         // complete in order, so the carries must not queue behind the staging loads).
         const int jt0 = K0 / TK;
-        const int ntile = max((T + TK - 1) / TK - jt0, 0);
+        const int* const fg = first + (kh.qhead0 + g) * nkb_arg;
+        const Reach reach = reach_of(fg, kb, nkb, lane);
+        const int ntile = max(min((T + TK - 1) / TK, reach.end) - jt0, 0);
         const int ndiag = min(ntile, BKW / TK);              // tiles that touch the diagonal band
         float cn0 = INFINITY, cn1 = 0.0f;                    // ca, cb of this wave's subtile of the next tile
         auto load_carries = [&](int jt) __attribute__((always_inline)) {
+            const bool there = live && (jt < reach.sure || fg[jt >> 1] <= kt32 >> 1);
             const int j = jt * TK + 32 * role + n;
-            // rows past T: an infinite carry gives A = 0 and G = 0, and with cb = 0 also dZ = 0
-            cn0 = (j < T && live) ? cag[j] : INFINITY;       // a dead strip's rows lie outside the arrays
-            cn1 = (j < T && live) ? cbg[j] : 0.0f;
+            // rows past T, tiles that do not reach these keys: an infinite carry gives A = 0 and
+            // G = 0, and with cb = 0 also dZ = 0
+            cn0 = (j < T && there) ? cag[j] : INFINITY;      // a dead strip's rows lie outside the arrays
+            cn1 = (j < T && there) ? cbg[j] : 0.0f;
         };
         if (ntile > 0) {
             load_carries(jt0);
             stage(jt0, smem);
         }
         // steady state (the intervals hot_begin .. hot_end - 1): the strip is live, tile `it` is past
-        // the diagonal band and complete, and the next tile is complete or does not exist
-        const int nfull = max(T / TK - jt0, 0);
+        // the diagonal band and complete, and the next tile is complete and reaches the block's keys,
+        // or does not exist
+        const int nfull = min(max(T / TK - jt0, 0), ntile);
         const int hot_begin = ndiag + 1;
-        const int hot_end = (SLOW || !live) ? 0 : (nfull == ntile ? ntile : nfull - 1);
+        const int sure = reach.sure - jt0;
+        const int hot_end = !live ? 0 : min(nfull == ntile ? ntile : nfull - 1, sure < ntile ? sure - 1 : ntile);
         int it = 0;
         while (it <= ntile) {
             if (it == hot_begin && it < hot_end) {
@@ -1244,16 +1306,6 @@ bwd_dkv_pair_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
                 }
             }
         }
-        if constexpr (!SLOW) {
-            // the block's flag: any chain of any wave out of range.  The tile buffers are free by now.
-            int* s_dirty = reinterpret_cast<int*>(smem);
-            barrier_lds();
-            if (tid == 0) *s_dirty = 0;
-            __syncthreads();
-            if (__builtin_amdgcn_ballot_w64(dirty) != 0 && lane == 0) atomicOr(s_dirty, 1);
-            __syncthreads();
-            if (tid == 0) flags[bh * nkb_arg + kb] = *s_dirty;
-        }
     }
 }
 
@@ -1317,7 +1369,7 @@ bwd_drb_sum_kernel(const float* __restrict__ part, float* __restrict__ drb, int 
 }
 
 // workspace layout: ca[BH][nt32][T], cb[BH][nt32][T] (fp32; [H][nt32][Ttot] for a packed
-// batch), then the per-block flags of the two kernels (int): [BH][nqb], [BH][nkb], then the
+// batch), then the query blocks' start tiles (int): [BH][nqb], room for as many more, then the
 // partial sums of the remainder-bias gradient (fp32): [BH][nchunk][D].  B, T: batch size and
 // length, or for a packed batch (VL) the number of sequences and the longest length.
 template <int D, bool VL>
@@ -1335,34 +1387,34 @@ hipError_t launch_one(const uint16_t* q, const uint16_t* k, const uint16_t* v, c
     const long ncarry = VL ? (long)H * nt32 * Ttot : (long)BH * nt32 * T;
     float* ca = workspace;
     float* cb = ca + ncarry;
-    int* fq = reinterpret_cast<int*>(cb + ncarry);
-    int* fk = fq + (long)BH * nqb;
-    float* part = reinterpret_cast<float*>(fk + (long)BH * nkb);
+    int* first = reinterpret_cast<int*>(cb + ncarry);
+    float* part = reinterpret_cast<float*>(first + (long)BH * (nqb + nkb));
     const int nchunk = (T + DR_ROWS - 1) / DR_ROWS;
-    const long bq = 8L * ((BH + 7) / 8) * ((nqb + 1) / 2);
-    const long bk = 8L * ((BHkv + 7) / 8) * ((nkb + 1) / 2);
+    const ShareRule rq = share_rule(BH, nqb), rk = share_rule(BHkv, nkb);
     // checked before the first launch, so that an error leaves nothing enqueued
-    if (bq > 0x7fffffffL || bk > 0x7fffffffL || nchunk * (long)BH > 0x7fffffffL) return hipErrorInvalidValue;
-    if (bq == 0) return hipSuccess;
+    if (rq.grid > 0x7fffffffL || rk.grid > 0x7fffffffL || nchunk * (long)BH > 0x7fffffffL) return hipErrorInvalidValue;
     hipError_t e = hipSuccess;
-#define SB_DQ(SLOWV, RBV)                                                                                       \
-    hipLaunchKernelGGL((bwd_dq_kernel<D, SLOWV, RBV, VL>), dim3((unsigned)bq), dim3(NTHREADS), 0, stream,       \
-                       q, k, v, rb, m, dout, dq, ca, cb, fq, T, BH, H, G, nqb, nt32, cu, Ttot);                 \
+#define SB_DQ(RBV)                                                                                              \
+    hipLaunchKernelGGL((bwd_dq_kernel<D, RBV, VL>), dim3((unsigned)rq.grid), dim3(NTHREADS), 0, stream,         \
+                       q, k, v, rb, m, dout, dq, ca, cb, first, T, BH, H, G, nqb, nt32, cu, Ttot,               \
+                       rq.spread, rq.single);                                                                   \
     if ((e = hipGetLastError()) != hipSuccess) return e
 // d = 128 takes the paired-wave kernel (two waves per SIMD instead of one); smaller head
 // dimensions leave room for two workgroups of the one-wave-per-strip kernel per CU, which
 // is faster there (measured).
-#define SB_DKV(SLOWV, GQAV)                                                                                     \
+#define SB_DKV(GQAV)                                                                                            \
     if constexpr (D == 128)                                                                                     \
-        hipLaunchKernelGGL((bwd_dkv_pair_kernel<D, SLOWV, GQAV, VL>), dim3((unsigned)bk), dim3(NTHREADS2), 0,   \
-                           stream, q, k, v, dout, ca, cb, dk, dv, fk, T, BHkv, H, G, nkb, nt32, cu, Ttot);      \
+        hipLaunchKernelGGL((bwd_dkv_pair_kernel<D, GQAV, VL>), dim3((unsigned)rk.grid), dim3(NTHREADS2), 0,     \
+                           stream, q, k, v, dout, ca, cb, dk, dv, first, T, BHkv, H, G, nkb, nt32, cu, Ttot,    \
+                           rk.spread, rk.single);                                                               \
     else                                                                                                        \
-        hipLaunchKernelGGL((bwd_dkv_kernel<D, SLOWV, GQAV, VL>), dim3((unsigned)bk), dim3(NTHREADS), 0,         \
-                           stream, q, k, v, dout, ca, cb, dk, dv, fk, T, BHkv, H, G, nkb, nt32, cu, Ttot);      \
+        hipLaunchKernelGGL((bwd_dkv_kernel<D, GQAV, VL>), dim3((unsigned)rk.grid), dim3(NTHREADS), 0,           \
+                           stream, q, k, v, dout, ca, cb, dk, dv, first, T, BHkv, H, G, nkb, nt32, cu, Ttot,    \
+                           rk.spread, rk.single);                                                               \
     if ((e = hipGetLastError()) != hipSuccess) return e
     if (passes & 1) {
-        if (rb) { SB_DQ(false, true); SB_DQ(true, true); }
-        else    { SB_DQ(false, false); SB_DQ(true, false); }
+        if (rb) { SB_DQ(true); }
+        else    { SB_DQ(false); }
         if (drb) {
             hipLaunchKernelGGL((bwd_drb_partial_kernel<D, VL>), dim3((unsigned)(nchunk * (long)BH)), dim3(NTHREADS), 0,
                                stream, m, dout, part, T, nchunk, H, cu, Ttot);
@@ -1374,8 +1426,8 @@ hipError_t launch_one(const uint16_t* q, const uint16_t* k, const uint16_t* v, c
     }
     if (passes & 2) {
         // a packed batch always takes the grouped variant (a group of one included)
-        if (VL || G > 1) { SB_DKV(false, true); SB_DKV(true, true); }
-        else             { SB_DKV(false, false); SB_DKV(true, false); }
+        if (VL || G > 1) { SB_DKV(true); }
+        else             { SB_DKV(false); }
     }
 #undef SB_DQ
 #undef SB_DKV

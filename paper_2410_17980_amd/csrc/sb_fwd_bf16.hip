@@ -4,8 +4,9 @@
 // wavefronts of a workgroup owns 32 of them and keeps their Q fragments in
 // registers.  A workgroup processes TWO query blocks one after the other, block p
 // and block nqb-1-p of the same head: with causal skipping their costs add up to
-// the same total for every p, so all workgroups run equally long.  Two workgroups
-// share a CU (two wavefronts per SIMD).
+// the same total for every p, so all workgroups of a head run equally long (which
+// workgroup does what: share_of()).  Two workgroups share a CU at d = 128 (two
+// wavefronts per SIMD), three at d = 64, four at d = 32.
 //
 // Keys are swept in 64-row tiles (two 32-row subtiles each) from the diagonal
 // towards key 0, the order Algorithm 1 prescribes: the weight of key i needs the
@@ -35,10 +36,15 @@
 // log form of Eq. 2/3 needs three transcendentals.  Where the in-lane product could
 // overflow, the wave falls back to the log form for that subtile (see ew()).
 //
-// Early halt (HALT variant, inference forward without m; the paper's "conditional
-// computation", section 4.1): the carry of a row is -log2 of the stick it has left, and
-// no weight of a farther key can exceed that.  Once every row of a query block has less
-// than eps left, the block stops sweeping: the error of o_j is at most eps * max|v|.
+// Exhausted rows (the paper's "conditional computation", section 4.1): the carry of a row
+// is -log2 of the stick it has left, and no weight of a farther key can exceed 2^-carry.
+// From CARRY_EXHAUSTED = 160 on every farther weight IS zero in this arithmetic (the smallest
+// nonzero bf16 is 2^-133, the smallest nonzero fp32 2^-149), so once every row of a query
+// block is there, the rest of the sweep cannot change a bit of o.  Without m the block stops;
+// with m, which needs the softplus total over all keys, it goes on with the logits alone (no
+// V, no A V: sum_tail()).  Rows whose weights reach far never get there and pay two scalar
+// compares a tile.  sb_attn_fwd_halt is the same kernel with the caller's threshold -log2(eps)
+// in place of 160; its error is at most eps * max|v|.
 #include <type_traits>
 
 #include "sb_kernels.h"
@@ -61,7 +67,11 @@ template <int D> struct FwdCfg {
     static constexpr int NPW = KT_BYTES / 1024 / NW;    // such loads per wave per K (or V) tile
 };
 
+// workgroups that share a CU (waves per SIMD)
+constexpr int wgs_per_cu(int d) { return d == 128 ? 2 : (d == 64 ? 3 : 4); }
+
 template <bool B> using bc = std::integral_constant<bool, B>;
+template <int I> using ic = std::integral_constant<int, I>;
 
 // VL: packed variable-length batch.  The tensors are [H][Ttot][D] ([H/G][Ttot][D] for k, v),
 // sequence s occupies rows cu[s] .. cu[s+1]-1, BH counts (sequence, head) pairs and T_arg,
@@ -70,29 +80,28 @@ template <bool B> using bc = std::integral_constant<bool, B>;
 // TRI: measurement variant of the element-wise path.  The in-tile reverse cumulative sum of
 // Algorithm 1 is taken on the matrix pipe, as a product with a triangular matrix of ones,
 // instead of the in-lane chain (see ew_tri()); everything else is the same kernel.
-template <int D, bool WRITE_M, bool HALT, bool RB, bool VL, bool TRI = false>
-__global__ void __launch_bounds__(64 * NW, D == 128 ? 2 : (D == 64 ? 3 : 4))
+template <int D, bool WRITE_M, bool RB, bool VL, bool TRI = false>
+__global__ void __launch_bounds__(64 * NW, wgs_per_cu(D))
 fwd_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
                 const uint16_t* __restrict__ v, const uint16_t* __restrict__ rb,
                 uint16_t* __restrict__ o, float* __restrict__ m,
-                int T_arg, int BH, int H, int G, int nqb_arg, float halt_carry,
-                unsigned long long* __restrict__ tile_counts, const int* __restrict__ cu, int Ttot)
+                int T_arg, int BH, int H, int G, int nqb_arg, float enough,
+                unsigned long long* __restrict__ tile_counts, const int* __restrict__ cu, int Ttot,
+                int spread, int single)
 {
     using C = FwdCfg<D>;
     constexpr int NPW = C::NPW;
-    static_assert(!(HALT && WRITE_M), "a halted sweep does not know m");
     __shared__ __attribute__((aligned(1024))) char smem[NS * C::STAGE];
-    __shared__ int s_halt[2][NW];                       // per iteration parity and wave: all rows exhausted
+    __shared__ __attribute__((aligned(16))) int s_done[NW];         // per wave: all rows exhausted
     __shared__ __attribute__((aligned(16))) char s_tri[TRI ? 2 * 64 * 16 : 16];   // triangular operand, per lane
 
-    // workgroup -> (head, pair of query blocks).  Consecutive workgroup ids go round
-    // the 8 XCDs, so every XCD gets its own heads and K/V of a head stay in one L2.
+    // workgroup -> (head, pair of query blocks)
     const int wg = blockIdx.x;
-    const int xcd = wg & 7, slot = wg >> 3;
     const int npair = (nqb_arg + 1) >> 1;
-    const long bh = xcd + 8L * (slot / npair);
-    const int pidx = slot % npair;
-    if (bh >= BH) return;
+    Share sh;
+    if (!share_of(sh, wg, BH, npair, spread, single)) return;
+    const long bh = sh.bh;
+    const int pidx = sh.p;
     int T = T_arg, nqb = nqb_arg;
     long row0, kvrow0;                                  // first row of this head's q / k rows
     int head;
@@ -116,7 +125,7 @@ fwd_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    if constexpr (!HALT) {
+    if constexpr (WRITE_M) {
         // measurement aid: with a non-null tile_counts the first workgroup leaves the shader
         // clock counter and the 100 MHz reference counter at its start ([0], [1]) and at its end
         // ([2], [3]); their ratio is the clock the chip sustained while this kernel ran
@@ -184,10 +193,8 @@ fwd_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
         if ((jt + 1) * C::TK <= T) {                    // all 64 rows exist
             const uint16_t* kb = Kg + (long)jt * C::TK * D;
             const uint16_t* vb = Vg + (long)jt * C::TK * D;
-#pragma unroll
-            for (int i = 0; i < NPW; ++i) dma16_to_lds_saddr(kb, goff[i], sp + (wave * NPW + i) * 1024);
-#pragma unroll
-            for (int i = 0; i < NPW; ++i) dma16_to_lds_saddr(vb, goff[i], sp + C::KT_BYTES + (wave * NPW + i) * 1024);
+            dma16_to_lds_run(kb, goff, sp + wave * NPW * 1024);
+            dma16_to_lds_run(vb, goff, sp + C::KT_BYTES + wave * NPW * 1024);
         } else {                                        // rows past T are clamped (causality masks them)
 #pragma unroll
             for (int i = 0; i < NPW; ++i) {
@@ -366,13 +373,59 @@ fwd_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
         pv_mfma(vop, p);
     };
 
-    for (int part = 0; part < 2; ++part) {
+    // The rest of a sweep whose weights are all zero, for m alone: adds log2(1 + e) over the keys of
+    // tiles 0 .. ntail-1 to the carry.  Two K tiles fill a staging buffer (V is not needed), so a
+    // barrier covers 128 keys; per subtile D/16 MFMAs instead of D/8, three vector instructions
+    // per logit instead of seven and half the LDS reads and staged bytes.
+    auto sum_tail = [&](int ntail) __attribute__((always_inline)) {
+        float l = 0.0f;                                      // this lane's keys only: the halves are added at the end
+        auto stage_pair = [&](int i, int st) __attribute__((always_inline)) {
+            char* sp = smem + st * C::STAGE;
+#pragma unroll
+            for (int x = 0; x < 2; ++x) {
+                const uint16_t* kb = Kg + (long)min(2 * i + x, ntail - 1) * C::TK * D;
+                dma16_to_lds_run(kb, goff, sp + x * C::KT_BYTES + wave * NPW * 1024);
+            }
+        };
+        auto sum_subtile = [&](uint32_t kslot) __attribute__((always_inline)) {
+            u32x4 kop[D / 16];
+            k_fetch(kslot, kop);
+            const f32x16 s = s_mfma(kop);
+            l += sp2_total<false>(s, c2, n, hh);
+        };
+        const int npr = (ntail + 1) >> 1;
+        auto pair_tile = [&](int i, auto buf_c) __attribute__((always_inline)) {
+            constexpr int BUF = decltype(buf_c)::value;
+            constexpr uint32_t sp = BUF * C::STAGE;
+            dma_wait<0>();
+            barrier_nofence();
+            if (i + 1 < npr) stage_pair(i + 1, BUF ^ 1);
+            sum_subtile(sp);
+            sum_subtile(sp + 32 * C::ROW);
+            if (2 * i + 1 < ntail) {
+                sum_subtile(sp + C::KT_BYTES);
+                sum_subtile(sp + C::KT_BYTES + 32 * C::ROW);
+            }
+        };
+        dma_wait<0>();
+        barrier_lds();                                       // nobody reads the sweep's tiles any more
+        stage_pair(0, 0);
+        for (int i = 0; i < npr; i += 2) {
+            pair_tile(i, ic<0>{});
+            if (i + 1 < npr) pair_tile(i + 1, ic<1>{});
+        }
+        float l_lo, l_hi;
+        both_halves(l, l_lo, l_hi);
+        a += l_lo + l_hi;
+    };
+
+    for (int part = sh.part0; part < sh.part1; ++part) {
         const int qb = part == 0 ? nqb - 1 - pidx : pidx;
         if (part == 1 && 2 * pidx == nqb - 1) break;     // odd block count: the middle block is alone
         const int Q0 = qb * BQ;
         const int q0 = Q0 + wave * 32;                   // this wave's first query row
         const bool wave_live = q0 < T;
-        if (part == 1) barrier_nofence();                // everyone is done with the stages of the first block
+        if (part > sh.part0) barrier_nofence();             // everyone is done with the stages of the first block
         {
             const int jq = min(q0 + n, T - 1);
             const u32x4* src = reinterpret_cast<const u32x4*>(Qg + (long)jq * D + 8 * hh);
@@ -402,10 +455,10 @@ fwd_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
         stage_tile(max(ntile - 1, 0), 0);
         auto begin_iter = [&](int it) __attribute__((always_inline)) {
             dma_wait<0>();                                   // this wave's share of tile `it` has landed
-            // ... everyone's has, and tile it-1 is no longer read.  The halting variant also
-            // publishes its flags through LDS here: their writes must have completed first,
-            // or the waves of a workgroup could disagree about leaving the loop.
-            if constexpr (HALT) barrier_lds(); else barrier_nofence();
+            // ... everyone's has, and tile it-1 is no longer read.  The waves' exhaustion flags go
+            // through LDS here: their writes must have completed first, or the waves of a
+            // workgroup could disagree about leaving the loop.
+            barrier_lds();
             stage_tile(max(ntile - 2 - it, 0), (it + 1) % NS);
             return (uint32_t)((it % NS) * C::STAGE);
         };
@@ -422,38 +475,26 @@ fwd_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
                 }
             }
         }
-        if constexpr (HALT) {
-            if (lane == 0) { s_halt[0][wave] = 0; s_halt[1][wave] = 0; }   // read only after later barriers
+        // Tiles fully visible to every row, two per trip with the staging buffer a compile-time
+        // constant, so that every LDS read of the sweep is a precomputed register plus an
+        // immediate: no address arithmetic in the loop.  In the middle of a trip a wave leaves in
+        // s_done whether all its rows are exhausted (both half-waves hold the same carry; rows
+        // past T repeat row T-1); the flags are read after the barrier that follows, by all waves
+        // alike, and written again only after the next one.  The loop has this one exit: with a
+        // second one in the middle the compiler copies the accumulators, which spills.
+        static_assert(NS == 2, "the unrolled sweep alternates two buffers");
+        int stop = 0;
+        if ((it & 1) && it < ntile) { hot_tile(begin_iter(it)); ++it; }
+        for (; it + 1 < ntile && !stop; it += 2) {
+            begin_iter(it);
+            hot_tile(0u);
+            if (!TRI && lane == 0) s_done[wave] = !wave_live || __builtin_amdgcn_ballot_w64(!(a >= enough)) == 0;
+            begin_iter(it + 1);
+            if (!TRI) stop = waves_done(s_done);
+            hot_tile((uint32_t)C::STAGE);
         }
-        if constexpr (!HALT) {
-            // Tiles fully visible to every row, two per trip with the staging buffer a
-            // compile-time constant, so that every LDS read of the sweep is a precomputed
-            // register plus an immediate: no address arithmetic in the loop.
-            static_assert(NS == 2, "the unrolled sweep alternates two buffers");
-            if ((it & 1) && it < ntile) { hot_tile(begin_iter(it)); ++it; }
-            for (; it + 1 < ntile; it += 2) {
-                begin_iter(it);
-                hot_tile(0u);
-                begin_iter(it + 1);
-                hot_tile((uint32_t)C::STAGE);
-            }
-        }
-        for (; it < ntile; ++it) {                           // tiles fully visible to every row
-            const uint32_t sp = begin_iter(it);
-            if constexpr (HALT) {
-                // flags of the previous iteration, written before the barrier just passed; all
-                // waves read the same four words, so they leave the loop together
-                const int* f = s_halt[(it + 1) & 1];
-                if (it > ndiag && (f[0] & f[1] & f[2] & f[3])) break;
-            }
-            hot_tile(sp);
-            if constexpr (HALT) {
-                // both half-waves hold the same carry; rows past T repeat row T-1
-                const int done = __builtin_amdgcn_ballot_w64(a < halt_carry) == 0;
-                if (lane == 0) s_halt[it & 1][wave] = done;
-            }
-        }
-        if constexpr (HALT) {
+        if (it < ntile && !stop) { hot_tile(begin_iter(it)); ++it; }
+        if constexpr (!WRITE_M) {
             if (tile_counts && tid == 0) {
                 atomicAdd(&tile_counts[0], (unsigned long long)it);        // tiles swept
                 atomicAdd(&tile_counts[1], (unsigned long long)ntile);     // tiles of the full sweep
@@ -492,10 +533,13 @@ fwd_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
                     }
                 }
             }
-            if (WRITE_M && hh == 0 && q0 + n < T) m[row0 + q0 + n] = -a * SB_LN2;
+        }
+        if constexpr (WRITE_M) {
+            if (it < ntile) sum_tail(ntile - it);
+            if (wave_live && hh == 0 && q0 + n < T) m[row0 + q0 + n] = -a * SB_LN2;
         }
     }
-    if constexpr (!HALT) {
+    if constexpr (WRITE_M) {
         if (tile_counts && wg == 0 && tid == 0) {
             tile_counts[2] = (unsigned long long)clock64();
             tile_counts[3] = (unsigned long long)wall_clock64();
@@ -503,18 +547,17 @@ fwd_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     }
 }
 
-template <int D, bool WRITE_M, bool HALT, bool RB, bool VL = false, bool TRI = false>
+template <int D, bool WRITE_M, bool RB, bool VL = false, bool TRI = false>
 hipError_t launch_one(const uint16_t* q, const uint16_t* k, const uint16_t* v, const uint16_t* rb,
-                      uint16_t* o, float* m, int BH, int H, int G, int T, float halt_carry,
+                      uint16_t* o, float* m, int BH, int H, int G, int T, float enough,
                       unsigned long long* tile_counts, hipStream_t stream,
                       const int* cu = nullptr, int Ttot = 0)
 {
     const int nqb = (T + BQ - 1) / BQ;
-    const long blocks = 8L * ((BH + 7) / 8) * ((nqb + 1) / 2);
-    if (blocks > 0x7fffffffL) return hipErrorInvalidValue;
-    if (blocks == 0) return hipSuccess;
-    hipLaunchKernelGGL((fwd_bf16_kernel<D, WRITE_M, HALT, RB, VL, TRI>), dim3((unsigned)blocks), dim3(64 * NW), 0, stream,
-                       q, k, v, rb, o, m, T, BH, H, G, nqb, halt_carry, tile_counts, cu, Ttot);
+    const ShareRule sr = share_rule(BH, nqb);
+    if (sr.grid > 0x7fffffffL) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((fwd_bf16_kernel<D, WRITE_M, RB, VL, TRI>), dim3((unsigned)sr.grid), dim3(64 * NW), 0, stream,
+                       q, k, v, rb, o, m, T, BH, H, G, nqb, enough, tile_counts, cu, Ttot, sr.spread, sr.single);
     return hipGetLastError();
 }
 
@@ -526,7 +569,7 @@ hipError_t launch_fwd_bf16(const uint16_t* q, const uint16_t* k, const uint16_t*
 {
     const int BH = B * H;
     const int G = H / Hkv;
-#define SB_FWD(DD, WM, RBV) launch_one<DD, WM, false, RBV>(q, k, v, rb, o, m, BH, H, G, T, 0.0f, clocks, stream)
+#define SB_FWD(DD, WM, RBV) launch_one<DD, WM, RBV>(q, k, v, rb, o, m, BH, H, G, T, CARRY_EXHAUSTED, m ? clocks : nullptr, stream)
     if (d == 32) {
         if (rb) return m ? SB_FWD(32, true, true) : SB_FWD(32, false, true);
         return m ? SB_FWD(32, true, false) : SB_FWD(32, false, false);
@@ -543,7 +586,7 @@ hipError_t launch_fwd_bf16(const uint16_t* q, const uint16_t* k, const uint16_t*
 hipError_t launch_fwd_bf16_tri(const uint16_t* q, const uint16_t* k, const uint16_t* v, uint16_t* o, float* m,
                                int B, int H, int T, hipStream_t stream)
 {
-    return launch_one<128, true, false, false, false, true>(q, k, v, nullptr, o, m, B * H, H, 1, T, 0.0f, nullptr, stream);
+    return launch_one<128, true, false, false, true>(q, k, v, nullptr, o, m, B * H, H, 1, T, CARRY_EXHAUSTED, nullptr, stream);
 }
 
 hipError_t launch_fwd_bf16_varlen(const uint16_t* q, const uint16_t* k, const uint16_t* v, const uint16_t* rb,
@@ -553,7 +596,7 @@ hipError_t launch_fwd_bf16_varlen(const uint16_t* q, const uint16_t* k, const ui
     const int BH = nseq * H;
     const int G = H / Hkv;
 #define SB_FWD(DD, WM, RBV) \
-    launch_one<DD, WM, false, RBV, true>(q, k, v, rb, o, m, BH, H, G, max_T, 0.0f, nullptr, stream, cu, Ttot)
+    launch_one<DD, WM, RBV, true>(q, k, v, rb, o, m, BH, H, G, max_T, CARRY_EXHAUSTED, nullptr, stream, cu, Ttot)
     if (d == 32) {
         if (rb) return m ? SB_FWD(32, true, true) : SB_FWD(32, false, true);
         return m ? SB_FWD(32, true, false) : SB_FWD(32, false, false);
@@ -572,12 +615,12 @@ hipError_t launch_fwd_bf16_halt(const uint16_t* q, const uint16_t* k, const uint
                                 int B, int H, int T, int d, hipStream_t stream)
 {
     const int BH = B * H;
-    const float halt_carry = -log2f(eps);               // carry = -log2(stick left)
+    const float enough = fminf(-log2f(eps), CARRY_EXHAUSTED);   // carry = -log2(stick left)
     if (d == 32)
-        return launch_one<32, false, true, false>(q, k, v, nullptr, o, nullptr, BH, H, 1, T, halt_carry, tile_counts, stream);
+        return launch_one<32, false, false>(q, k, v, nullptr, o, nullptr, BH, H, 1, T, enough, tile_counts, stream);
     if (d == 64)
-        return launch_one<64, false, true, false>(q, k, v, nullptr, o, nullptr, BH, H, 1, T, halt_carry, tile_counts, stream);
-    return launch_one<128, false, true, false>(q, k, v, nullptr, o, nullptr, BH, H, 1, T, halt_carry, tile_counts, stream);
+        return launch_one<64, false, false>(q, k, v, nullptr, o, nullptr, BH, H, 1, T, enough, tile_counts, stream);
+    return launch_one<128, false, false>(q, k, v, nullptr, o, nullptr, BH, H, 1, T, enough, tile_counts, stream);
 }
 
 }  // namespace sb

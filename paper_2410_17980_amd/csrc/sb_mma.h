@@ -29,6 +29,81 @@ __device__ __forceinline__ float sp2(float x)
     return __builtin_amdgcn_fmed3f(fast_log2(1.0f + fast_exp2(x)), x, 128.0f);
 }
 
+// A row whose carry (sum of sp2 over the keys already swept, -log2 of the stick left) has got
+// this far gives every farther key a weight below 2^-160: zero in fp32 and in bf16.
+constexpr float CARRY_EXHAUSTED = 160.0f;
+
+// Which blocks a workgroup works on.  A head's n row blocks form (n+1)/2 pairs (p, n-1-p) of equal
+// causal cost.  Workgroup ids go round the 8 XCDs.  A head's pairs are cut into 2^spread runs of
+// neighbours, each run on one XCD: neighbours sweep the same tiles at about the same time and share
+// them in that XCD's L2, and how much work a head is (how far its weights reach) spreads over the
+// XCDs.  With `single` the two blocks of a pair are workgroups of their own, the longer ones first.
+struct Share {
+    long bh;                  // head
+    int p;                    // pair
+    int part0, part1;         // parts of it to do: 0 = the longer block, 1 = the shorter
+};
+__host__ __device__ __forceinline__ int share_run(int npair, int spread) { return (npair + (1 << spread) - 1) >> spread; }
+// Measured on heads of which a third reach far (bf16 forward, B1 H32 T16384 d128 / B1 H24 T16384 d64):
+// one XCD a head 1102 / 660 us, all eight 1001 / 526 us; where every head reaches far the shared
+// L2 is worth more, 2318 against 2371 us, and with many short heads too (B8 H16 T4096 d128: 367
+// against 376 us, all far 641 against 682 us).  So a head spreads over the XCDs where its runs
+// are still 4 pairs long, or where there are so few heads that one XCD more or less of the costly
+// ones decides (B1 H24 Hkv8 T4096 d64: 91 -> 73 us).  Blocks go single where every one of them
+// gets a CU to itself (B1 H32 T1024 d128: 33 -> 27 us); beyond that pairs are faster, since they
+// load the CUs evenly (B1 H24 Hkv8 T4096 d64: 73 us in pairs, 89 us single).
+struct ShareRule {
+    int spread, single;
+    long grid;
+};
+inline ShareRule share_rule(long heads, int nblk)
+{
+    const int npair = (nblk + 1) / 2;
+    ShareRule r;
+    r.spread = npair >= 32 || heads < 64 ? 3 : 0;
+    r.single = heads * nblk <= 256;
+    r.grid = 8L * (((heads << r.spread) + 7) / 8) * share_run(npair, r.spread) * (1 + r.single);
+    return r;
+}
+// false: nothing to do
+__device__ __forceinline__ bool share_of(Share& sh, int wg, long heads, int npair, int spread, int single)
+{
+    const int run = share_run(npair, spread), per = run << single;
+    const int slot = wg >> 3;
+    const int s = slot / per;
+    int i = slot - s * per;
+    sh.part0 = 0;
+    sh.part1 = 2;
+    if (single) {
+        sh.part0 = i >= run;
+        sh.part1 = sh.part0 + 1;
+        i -= sh.part0 ? run : 0;
+    }
+    const long u = 8L * s + ((wg + (((unsigned)s * 0x9E3779B1u) >> 29)) & 7);
+    sh.bh = u >> spread;
+    sh.p = (int)(u & ((1 << spread) - 1)) * run + i;
+    return sh.bh < heads && sh.p < npair;
+}
+
+// sum of log2(1 + 2^(c2 s_r)) over a lane's 16 logits: one product of the (1 + e_r) from 2^-60 on,
+// one logarithm; where the product overflows in any lane, the wave takes the sum of sp2
+template <bool MASK>
+__device__ __forceinline__ float sp2_total(const f32x16& s, float c2, int n, int hh)
+{
+    float W = 0x1p-60f;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        float e = fast_exp2(s[r] * c2);
+        if (MASK) e = (16 * hh + r < n) ? e : 0.0f;
+        W = __builtin_fmaf(W, e, W);
+    }
+    if (__builtin_amdgcn_ballot_w64(!(W < INFINITY)) == 0) return fast_log2(W) + 60.0f;
+    float l = 0.0f;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) l += !MASK || 16 * hh + r < n ? sp2(s[r] * c2) : 0.0f;
+    return l;
+}
+
 // MFMA 32x32 accumulator register r of lane (n, hh) is output row
 // 8*(r/4) + 4*hh + r%4.  Feeding MFMA row rho from tile row perm_row(rho)
 // makes lane (n, hh) own the 16 CONSECUTIVE tile rows 16*hh + r, r = 0..15.
@@ -122,9 +197,11 @@ __device__ __forceinline__ bf16x8 tr_pair_at(uint32_t a_lo, uint32_t a_hi)
 // that the compiler's wait-count pass does not see an LDS write it would guard
 // every later LDS read against; the caller orders it with dma_wait<N>() + barrier.
 // Completion is counted in vmcnt, in issue order.  The LDS base travels in M0, which
-// is handed over as a register operand: the compiler writes it and knows it is in use
-// (the s_nop covers the wait state between a scalar write of M0 and this instruction,
-// which the compiler cannot see into).
+// is handed over as a register operand: the compiler writes it and knows it is in use.
+// The compiler does not see a memory instruction in here, so the wait states it would put
+// in are written out: one between a scalar write of M0 and the load, five between a vector
+// instruction's write of a scalar register (v_readfirstlane, v_readlane of a spilled one)
+// and a memory instruction that takes its base from it.
 __device__ __forceinline__ void dma16_to_lds(const void* gptr, const char* lds_base)
 {
     const uint32_t lds = __builtin_amdgcn_readfirstlane(lds_offset(lds_base));
@@ -132,16 +209,50 @@ __device__ __forceinline__ void dma16_to_lds(const void* gptr, const char* lds_b
                  :: "{m0}"(lds), "v"(gptr) : "memory");
 }
 
+// the wave-uniform base of the forms below, in scalar registers
+__device__ __forceinline__ uint64_t scalar_base(const void* gbase)
+{
+    const uint64_t b = (uint64_t)(uintptr_t)gbase;
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)b);
+    const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(b >> 32));
+    return ((uint64_t)hi << 32) | lo;
+}
+
 // same, with the global address given as a wave-uniform base plus a per-lane byte offset
 __device__ __forceinline__ void dma16_to_lds_saddr(const void* gbase, int lane_off, const char* lds_base)
 {
     const uint32_t lds = __builtin_amdgcn_readfirstlane(lds_offset(lds_base));
-    const uint64_t b = (uint64_t)(uintptr_t)gbase;
-    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)b);
-    const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(b >> 32));
-    const uint64_t sb = ((uint64_t)hi << 32) | lo;
-    asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
-                 :: "{m0}"(lds), "v"(lane_off), "s"(sb) : "memory");
+    asm volatile("s_nop 4\n\tglobal_load_lds_dwordx4 %1, %2"
+                 :: "{m0}"(lds), "v"(lane_off), "s"(scalar_base(gbase)) : "memory");
+}
+
+// N of them from one base, to N consecutive KB of LDS: the wait states for the base once
+template <int N>
+__device__ __forceinline__ void dma16_to_lds_run(const void* gbase, const int (&off)[N], const char* lds_base)
+{
+    static_assert(N == 1 || N == 2 || N == 4, "loads per wave and matrix");
+    uint32_t lds = __builtin_amdgcn_readfirstlane(lds_offset(lds_base));
+    const uint64_t sb = scalar_base(gbase);
+    if constexpr (N == 1) {
+        dma16_to_lds_saddr(gbase, off[0], lds_base);
+    } else if constexpr (N == 2) {
+        asm volatile("s_nop 4\n\tglobal_load_lds_dwordx4 %1, %3\n\t"
+                     "s_add_u32 m0, m0, 0x400\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %3"
+                     : "+{m0}"(lds) : "v"(off[0]), "v"(off[1]), "s"(sb) : "memory", "scc");
+    } else {
+        asm volatile("s_nop 4\n\tglobal_load_lds_dwordx4 %1, %5\n\t"
+                     "s_add_u32 m0, m0, 0x400\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %5\n\t"
+                     "s_add_u32 m0, m0, 0x400\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %3, %5\n\t"
+                     "s_add_u32 m0, m0, 0x400\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %4, %5"
+                     : "+{m0}"(lds) : "v"(off[0]), "v"(off[1]), "v"(off[2]), "v"(off[3]), "s"(sb) : "memory", "scc");
+    }
+}
+
+// are all four flags (16-byte aligned, in LDS) set
+__device__ __forceinline__ int waves_done(const int* flags)
+{
+    const u32x4 f = lds_load16(lds_offset(reinterpret_cast<const char*>(flags)));
+    return __builtin_amdgcn_readfirstlane((int)(f[0] & f[1] & f[2] & f[3]));
 }
 
 // wait until at most N of this wave's vector-memory operations are outstanding

@@ -1,0 +1,104 @@
+"""GPU parity where the stick is used up long before key 0: the kernels stop forming weights once
+every row of a block is exhausted (they are zero from there on), so these sizes put the end of the
+sweep at every place it can fall relative to the unrolled loop and the last tile."""
+import numpy as np
+import pytest
+import torch
+
+from helpers import check_grad, check_m, dev, fwd_bound, nan_bytes, to64
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def sb():
+    assert torch.cuda.is_available(), "these tests need the MI355X"
+    from paper_2410_17980_amd import binding
+    binding.load(build_if_missing=False)      # the built library must be there
+    return binding
+
+
+@pytest.fixture(scope="module")
+def gen():
+    from paper_2410_17980_amd import inputs
+    return inputs
+
+
+def mixed(gen, B, H, T, d, seed):
+    """Heads by turns: exhausted within ~130 keys, within a few (sharp, chains out of range), never."""
+    q, k, v = gen.gaussian(B, H, T, d, seed=seed, dtype="bf16")
+    _, k30, _ = gen.scaled_gaussian(B, H, T, d, seed, gain=30.0)
+    qb, kb, _ = gen.biased_gaussian(B, H, T, d, seed=seed, shift=-6.0, dtype="bf16")
+    q, k = q.clone(), k.clone()
+    k[:, 1::3] = k30[:, 1::3]
+    q[:, 2::3], k[:, 2::3] = qb[:, 2::3], kb[:, 2::3]
+    return q, k, v
+
+
+@pytest.mark.parametrize("T", [257, 383, 449, 511, 640, 705, 1025, 1300])
+@pytest.mark.parametrize("d", [32, 64, 128])
+def test_forward(sb, oracle, gen, T, d):
+    q, k, v = mixed(gen, 1, 3, T, d, seed=500 + T)
+    qd, kd, vd = dev(q, k, v)
+    o, m = sb.sb_attn_fwd_train(qd, kd, vd)
+    o2 = sb.sb_attn_fwd(qd, kd, vd)
+    torch.cuda.synchronize()
+    ref, rem = oracle.fwd(to64(q), to64(k), to64(v))
+    assert torch.equal(o, o2)
+    assert np.all(np.abs(to64(o) - ref) <= fwd_bound(ref, to64(v)))
+    check_m(to64(m), rem)
+
+
+def test_m_without_underflow(sb, gen):
+    """m beyond float64's range of the remainder itself: the softplus sum in float64."""
+    q, k, v = mixed(gen, 1, 3, 1500, 64, seed=9)
+    _, m = sb.sb_attn_fwd_train(*dev(q, k, v))
+    z = to64(q) @ np.swapaxes(to64(k), -1, -2) / 8.0
+    sp = np.tril(np.logaddexp(0.0, z), -1)
+    ref = -sp.sum(-1)
+    assert np.all(np.abs(to64(m) - ref) <= 2e-3 + 1e-4 * np.abs(ref))
+
+
+@pytest.mark.parametrize("H,T", [(1, 130), (9, 300), (65, 300), (3, 8200)])
+def test_every_block_once(sb, gen, H, T):
+    """The shares of the launch (heads over XCDs, single blocks or pairs) cover every row: equal to
+    one launch per head, which takes another share."""
+    q, k, v = dev(*mixed(gen, 1, H, T, 32, seed=77))
+    o, m = sb.sb_attn_fwd_train(q, k, v)
+    for h in {0, H // 2, H - 1}:
+        oh, mh = sb.sb_attn_fwd_train(*(t[:, h:h + 1].contiguous() for t in (q, k, v)))
+        assert torch.equal(o[:, h:h + 1], oh) and torch.equal(m[:, h:h + 1], mh)
+
+
+@pytest.mark.parametrize("T", [511, 512, 577, 705, 1025, 1300])
+@pytest.mark.parametrize("d", [32, 64, 128])
+def test_backward(sb, oracle, gen, T, d):
+    q, k, v = mixed(gen, 1, 3, T, d, seed=600 + T)
+    g = gen.gaussian(1, 3, T, d, seed=601 + T, dtype="bf16")[0]
+    qd, kd, vd, gd = dev(q, k, v, g)
+    _, m = sb.sb_attn_fwd_train(qd, kd, vd)
+    ws = nan_bytes(sb.sb_attn_bwd_workspace_bytes(1, 3, T, d))
+    got = sb.sb_attn_bwd(qd, kd, vd, m, gd, workspace=ws)
+    torch.cuda.synchronize()
+    for name, a, r in zip(("dq", "dk", "dv"), got, oracle.bwd(*(to64(t) for t in (q, k, v, g)))):
+        for h in range(3):
+            check_grad(f"{name} head {h}", to64(a)[:, h], r[:, h])
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_backward_far_queries_come_back(sb, oracle, gen, d):
+    """Rows 1024..1151 reach all keys, the rows before them only near ones: the query blocks that
+    reach a key block are not contiguous."""
+    T = 1300
+    q, k, v, g = gen.gaussian(1, 1, T, d, seed=8, dtype="bf16", with_dout=True)
+    q, k = q.clone(), k.clone()
+    q[..., 0], k[..., 0] = 0.0, -4.0
+    q[..., 1024:1152, :] *= 0.25
+    q[..., 1024:1152, 0] = 2.0 * d ** 0.5
+    qd, kd, vd, gd = dev(q, k, v, g)
+    _, m = sb.sb_attn_fwd_train(qd, kd, vd)
+    ws = nan_bytes(sb.sb_attn_bwd_workspace_bytes(1, 1, T, d))
+    got = sb.sb_attn_bwd(qd, kd, vd, m, gd, workspace=ws)
+    torch.cuda.synchronize()
+    for name, a, r in zip(("dq", "dk", "dv"), got, oracle.bwd(*(to64(t) for t in (q, k, v, g)))):
+        check_grad(name, to64(a), r)
