@@ -1,20 +1,33 @@
 // Single-token decode: one new query per (batch entry, head) against a cache of T keys
 // and values, all of them visible (the last row of Eq. 1 on the extended sequence).
 //
-// The work is one pass over K and V (2*T*d*2 bytes per kv head) with ~1 FLOP per byte:
-// bound by HBM bandwidth, so it runs on the vector ALU with coalesced 16-byte loads and
-// is split over the keys to fill the chip ("split-KV").  Stick-breaking partial results
+// The work is one pass over K and V (2*T*d*2 bytes per kv head), a few FLOP per byte: bound by
+// HBM bandwidth as long as the vector ALU stays out of the way.  Both contractions are matrix
+// instructions with the query heads of a group as the 16 columns (see decode_kernel), split over
+// the keys to fill the chip ("split-KV").  Stick-breaking partial results
 // combine without any rescaling by a maximum: a chunk of keys processed on its own gives
 //     O_s = sum_i A_s[i] v_i   with the chunk-local weights A_s (Eq. 2 inside the chunk),
 //     a_s = sum_i softplus(z_i)                      (minus the log of what the chunk leaves),
 // and the exact output is  sum_s exp(-sum_{s' nearer than s} a_s') O_s  (the farther
 // chunk's log-weights are shifted by what the nearer chunks took; Eq. 2).
 //
-//   decode_partial_kernel  grid (chunk, kv head, block of query heads).  Logits for the
-//       chunk (a row of K is read once for all query heads of the group), base-2
-//       softplus, suffix sums over the chunk, weights, weighted sum of the V rows.
-//   decode_combine_kernel  one workgroup per (batch entry, query head): suffix sums of the
-//       a_s over the chunks, O = sum_s 2^-A_s O_s, optional remainder bias, store.
+// The nearest keys come first, in a launch of their own: they take most of the stick, and
+// where they take all of it (CARRY_EXHAUSTED: every farther weight is zero in fp32) the
+// rest of the cache is not read at all.
+//   decode_kernel<.., false>  grid (kv head, block of query heads): the nearest keys, all of a
+//       short cache.  Finishes the heads that are exhausted, or all if that was all.
+//   decode_kernel<.., true>   grid (chunk, kv head, block of query heads): the keys before
+//       those.  Returns at once where the heads are finished.
+//   decode_combine_kernel     one workgroup per query head that is not finished: adds the
+//       chunks up, in a fixed order.  (Done by the last workgroup of the second launch to arrive
+//       instead, it cost more: 14 % of B8 H16 T16384 d128 in stores and counters each workgroup
+//       waits for, 10 us at B1 H8 Hkv1 T30000 d64 for one workgroup to add what eight can.)
+// Exhaustion does not end a pass that has to return m, the log of the stick left over all keys.
+//
+// Measured with a third of the kv heads reaching far / all of them (before this split: 180, 55, 41, 54
+// us either way): B8 H16 T16384 d128 69 / 168 us (all keys at 6.4 TB/s), B1 H32 Hkv8 T65000 d128
+// 30 / 55, B32 H16 T1500 d64 25 / 35, B16 H32 Hkv8 T4096 d128 28 / 56.
+#include <algorithm>
 #include <mutex>
 #include <type_traits>
 
@@ -25,285 +38,327 @@
 namespace sb {
 namespace {
 
-constexpr int DEC_THREADS = 256;
-constexpr int DEC_MAXCHUNKS = 256;     // chunks per head: the combine kernel gives each a thread
-constexpr int DEC_CMAX = 2048;         // keys per chunk at most (logits of a chunk live in LDS)
-constexpr int DEC_GT = 4;              // query heads of a group handled by one workgroup
+constexpr int NEAR_NW = 8;             // waves of a workgroup, first launch
+constexpr int FAR_NW = 4;              // and second: smaller, so that three share a CU
+constexpr int KW = 32;                 // keys per wave and pass
+constexpr int NEAR = KW * NEAR_NW;     // keys of a first launch that has a second one behind it
+constexpr int GMAX = 16;               // query heads of a group per workgroup: the columns of the MFMA
+constexpr int ALONE = 6 * NEAR;        // caches up to here take the first launch only (6 us + 1.3 us a pass; two launches 15 us)
+constexpr int COMBINE_THREADS = 256;
+constexpr int MAXFAR = 127;            // chunks beyond the nearest keys: with those, two per lane of a wave
+constexpr long FAR_WGS = 2048;      // workgroups of the second launch, all heads together
 
-__device__ __forceinline__ float bf_lo(uint32_t u) { return __builtin_bit_cast(float, u << 16); }
-__device__ __forceinline__ float bf_hi(uint32_t u) { return __builtin_bit_cast(float, u & 0xffff0000u); }
+typedef __attribute__((ext_vector_type(4))) float f32x4;
 
-// sum of v over the aligned group of N lanes (N = 4, 8 or 16) this lane belongs to, in every
-// lane of the group, with data-parallel-primitive adds (no LDS traffic): neighbours inside
-// quads, then the mirrored half row and the mirrored row (all lanes of a quad already hold
-// the same value then, so mirroring reaches the other quads' sum)
-template <int N> __device__ __forceinline__ float group_sum(float v)
+// sum of v over the lanes above this one, and over all lanes in `total`
+__device__ __forceinline__ float wave_suffix_excl(float v, float& total)
 {
-    auto dpp = [](float x, auto ctrl) {
-        return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x),
-                                                                     decltype(ctrl)::value, 0xf, 0xf, false));
-    };
-    v += dpp(v, std::integral_constant<int, 0xB1>{});              // quad_perm [1,0,3,2]
-    v += dpp(v, std::integral_constant<int, 0x4E>{});              // quad_perm [2,3,0,1]
-    if (N >= 8) v += dpp(v, std::integral_constant<int, 0x141>{}); // row_half_mirror
-    if (N >= 16) v += dpp(v, std::integral_constant<int, 0x140>{}); // row_mirror
-    return v;
-}
-
-// sum over the 256 threads' values v of all threads with a HIGHER thread index (exclusive
-// suffix sum), and the total in `total`.  red: 4 floats of LDS; contains a barrier.
-__device__ __forceinline__ float block_suffix_excl(float v, float* red, float& total)
-{
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63;
     float inc = v;
 #pragma unroll
     for (int off = 1; off < 64; off <<= 1) {
         const float y = __shfl_down(inc, off);
         if (lane + off < 64) inc += y;
     }
-    __syncthreads();                       // red may still be read from the call before
-    if (lane == 0) red[wave] = inc;        // the wave's total
-    __syncthreads();
-    float above = 0.0f, tot = 0.0f;
-#pragma unroll
-    for (int w = 0; w < DEC_THREADS / 64; ++w) {
-        const float t = red[w];
-        tot += t;
-        if (w > wave) above += t;
-    }
-    total = tot;
-    return inc - v + above;
+    total = __shfl(inc, 0);
+    return inc - v;
 }
 
-template <int D, int GT>
-__global__ void __launch_bounds__(DEC_THREADS)
-decode_partial_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
-                      const uint16_t* __restrict__ v, float* __restrict__ part_o, float* __restrict__ part_a,
-                      int T, int Tcap, int H, int G, int C, int nchunk)
+// The far keys are read once and by one workgroup: kept out of the way of the caches (B8 H16 T16384
+// d128, every chunk read: 191 -> 168 us; the first launch, whose reads are few, is faster without).
+template <bool NT, typename V> __device__ __forceinline__ V stream_load(const V* p)
 {
-    constexpr int LPR = D / 8;             // lanes per row (16 B each)
-    constexpr int RPI = 64 / LPR;          // rows per wave-wide load
-    constexpr int RSTEP = RPI * (DEC_THREADS / 64);
-    constexpr int U = 4;                   // rows in flight per lane
-    extern __shared__ float zs[];          // [GT][C]: logits (base 2), then weights
-    __shared__ float red[DEC_THREADS / 64];
-    __shared__ float ored[DEC_THREADS / 64][GT][D];
+    if constexpr (NT) return __builtin_nontemporal_load(p);
+    return *p;
+}
 
-    const int chunk = blockIdx.x;
-    const int bkv = blockIdx.y;            // batch entry * Hkv + kv head
-    const int g0 = blockIdx.z * GT;        // first query head (inside the group) of this workgroup
+// element c of a head's output r and, with c = 0, its m; total: sp2 over all keys.  Remainder bias
+// (Appendix C): what no key took goes to the head's embedding.
+__device__ __forceinline__ void store_out(const uint16_t* rb, uint16_t* o, float* m, int c, float r, float total)
+{
+    if (rb) r += fast_exp2(-total) * __builtin_bit_cast(float, (uint32_t)rb[c] << 16);
+    const __bf16 val = (__bf16)r;
+    o[c] = __builtin_bit_cast(uint16_t, val);
+    if (m && c == 0) *m = -total * SB_LN2;
+}
+
+// A workgroup takes its keys from the nearest down in passes of KEYS, 32 keys per wave.
+//   logits   z[key][head] = K q: 16x16x32 bf16 MFMA, A = 16 rows of K as they lie in memory (lane:
+//            row lane%16, 16-byte chunk 4s + lane/16), B = the query heads of the group.  A lane
+//            gets four consecutive keys of one head.
+//   weights  through LDS: wave g takes head g (and g + NW), NW/2 consecutive keys per lane.
+//   output   O^T[c][head] += V^T w: a lane loads D/16 columns of the 8 rows 8*(lane/16) + i, and an
+//            in-register transposition (one v_perm per packed pair) makes them the A operand of
+//            D/16 MFMAs, rows = columns of V, 32 keys deep.  B = the weights, each split exactly
+//            into three bf16 (8 + 8 + 8 bits of mantissa), so that nothing of the fp32 weight is lost.
+// On the vector ALU the same two products cost 35 instructions per 16-byte word and head, which
+// bound groups of 4 heads (B1 H32 Hkv8 T65000 d128: 78 us against 48 us of memory time; this way 55).
+// The K registers of a pass are free after its logits and the V registers after its output, and are
+// refilled there and then with the next pass's rows: loads stay in flight across the barriers.
+template <int D, bool FAR>
+__global__ void __launch_bounds__(64 * (FAR ? FAR_NW : NEAR_NW), FAR ? 3 : 2)
+decode_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
+              const uint16_t* __restrict__ rb, uint16_t* __restrict__ o, float* __restrict__ m,
+              float* __restrict__ part_o, float* __restrict__ part_a,
+              int T, int Tcap, int H, int G, int near, int C, int nfar)
+{
+    constexpr int NW = FAR ? FAR_NW : NEAR_NW;
+    constexpr int NTHR = 64 * NW;
+    constexpr int KEYS = KW * NW;          // keys per pass
+    constexpr int ZS = KEYS + 4;           // row stride of the logits in LDS (heads apart by 4 banks)
+    constexpr int CW = D / 16;             // columns of V per lane
+    typedef __attribute__((ext_vector_type(CW / 2))) unsigned int vword;
+    constexpr int HB = 4;                  // heads per round of the reduction over the waves
+    __shared__ __attribute__((aligned(16))) float zs[2][GMAX][ZS];   // per pass parity: logits (base 2), then weights
+    __shared__ __attribute__((aligned(16))) float ored[NW * HB * D];
+    __shared__ float s_carry[GMAX];
+    __shared__ int s_left[2];              // per pass parity: heads not exhausted
+
+    const int bkv = FAR ? blockIdx.y : blockIdx.x;     // batch entry * Hkv + kv head
+    const int g0 = blockIdx.z * GMAX;      // first query head (inside the group) of this workgroup
     const int Hkv = H / G;
     const int b = bkv / Hkv, hkv = bkv % Hkv;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int sub = lane % LPR, rw = lane / LPR;
-    const int k0 = chunk * C, k1 = min(T, k0 + C), n = k1 - k0;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l16 = lane & 15, lq = lane >> 4;
+    const int nch = nfar + 1;              // chunk nfar: the nearest keys
+    const int chunk = FAR ? blockIdx.x : nfar;
+    const int kend = FAR ? min(T - near, (chunk + 1) * C) : T;
+    const int k0 = FAR ? chunk * C : T - near;
     const long kvbase = (long)bkv * Tcap * D;
+    const long hq0 = (long)b * H + hkv * G + g0;       // first query head of this workgroup
+    const int live = min(GMAX, G - g0);                // and how many there are
     const float c2 = SB_LOG2E / sqrtf((float)D);
 
-    // ---- logits: z[g][key] = q_g . k_key * log2(e) / sqrt(d)
-    float qf[GT][8];
-#pragma unroll
-    for (int g = 0; g < GT; ++g) {
-        const bool live = g0 + g < G;
-        const long hq = (long)b * H + hkv * G + min(g0 + g, G - 1);
-        const u32x4 w = *reinterpret_cast<const u32x4*>(q + hq * D + 8 * sub);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            qf[g][2 * e] = live ? bf_lo(w[e]) * c2 : 0.0f;
-            qf[g][2 * e + 1] = live ? bf_hi(w[e]) * c2 : 0.0f;
+    if constexpr (FAR) {
+        if (!m) {
+            const float a = part_a[(hq0 + min(lane, live - 1)) * nch + nfar];
+            if (__builtin_amdgcn_ballot_w64(!(a >= CARRY_EXHAUSTED)) == 0) return;
         }
     }
-    for (int r0 = wave * RPI + rw; r0 < n; r0 += U * RSTEP) {
-        u32x4 kw[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int row = k0 + min(r0 + u * RSTEP, n - 1);
-            kw[u] = *reinterpret_cast<const u32x4*>(k + kvbase + (long)row * D + 8 * sub);
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            float kf[8];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) { kf[2 * e] = bf_lo(kw[u][e]); kf[2 * e + 1] = bf_hi(kw[u][e]); }
-#pragma unroll
-            for (int g = 0; g < GT; ++g) {
-                float s = 0.0f;
-#pragma unroll
-                for (int e = 0; e < 8; ++e) s += qf[g][e] * kf[e];
-                s = group_sum<LPR>(s);
-                if (sub == 0 && r0 + u * RSTEP < n) zs[g * C + r0 + u * RSTEP] = s;
-            }
-        }
-    }
-    __syncthreads();
 
-    // ---- weights inside the chunk: w[i] = 2^(x_i - sum_{i' >= i} sp2(x_i'))  (Eq. 2).
-    // Two sweeps over consecutive keys per thread: totals, a suffix scan of the totals over
-    // the threads, then the weights (the softplus is evaluated again rather than kept).
-    // With one query head the whole workgroup scans; with GT = 4 each wave takes one head
-    // and no barrier is needed in between.
+    // rows hi - KEYS + 32 wave .. + 31; those before k0 are loaded as k0 and masked
+    u32x4 kw[2][D / 32];
+    vword vw[8];
+    const int r0 = wave * KW - KEYS;
+    auto fetch_k = [&](int hi) __attribute__((always_inline)) {
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            const uint16_t* row = k + kvbase + (long)max(hi + r0 + 16 * t + l16, k0) * D + 8 * lq;
+#pragma unroll
+            for (int s = 0; s < D / 32; ++s) kw[t][s] = stream_load<FAR>(reinterpret_cast<const u32x4*>(row + 32 * s));
+        }
+    };
+    auto fetch_v = [&](int hi) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+            vw[i] = stream_load<FAR>(reinterpret_cast<const vword*>(v + kvbase + (long)max(hi + r0 + 8 * lq + i, k0) * D + CW * l16));
+    };
+    bf16x8 qw[D / 32];                     // B operand: head l16 (columns past `live` repeat the last one)
     {
-        const int nthr = GT == 1 ? DEC_THREADS : 64;           // threads that share one head's scan
-        const int g = GT == 1 ? 0 : wave;
-        const int t = GT == 1 ? tid : lane;
-        const int E = (C + nthr - 1) / nthr;                   // consecutive keys per thread
-        float* z = zs + g * C;
-        float mine = 0.0f;
-        for (int e = 0; e < E; ++e) {
-            const int i = t * E + e;
-            if (i < n) mine += sp2(z[i]);
-        }
-        float total, run;
-        if constexpr (GT == 1) {
-            run = block_suffix_excl(mine, red, total);         // sp2 of all keys after this thread's
-        } else {
-            float inc = mine;
+        const uint16_t* row = q + (hq0 + min(l16, live - 1)) * D + 8 * lq;
 #pragma unroll
-            for (int off = 1; off < 64; off <<= 1) {
-                const float y = __shfl_down(inc, off);
-                if (lane + off < 64) inc += y;
-            }
-            total = __shfl(inc, 0);
-            run = inc - mine;
-        }
-        for (int e = E - 1; e >= 0; --e) {
-            const int i = t * E + e;
-            if (i < n) {
-                const float x = z[i];
-                run += sp2(x);
-                z[i] = fast_exp2(x - run);
-            }
-        }
-        if (t == 0 && g0 + g < G) {
-            const long hq = (long)b * H + hkv * G + g0 + g;
-            part_a[hq * nchunk + chunk] = total;
-        }
+        for (int s = 0; s < D / 32; ++s) qw[s] = *reinterpret_cast<const bf16x8*>(row + 32 * s);
     }
-    __syncthreads();
+    fetch_k(kend);
+    fetch_v(kend);
+    f32x4 acc[CW];                         // O^T: row 4 lq + r of MFMA e is column CW * (4 lq + r) + e, head l16
+#pragma unroll
+    for (int e = 0; e < CW; ++e) acc[e] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    if (tid < GMAX) s_carry[tid] = 0.0f;   // sp2 of the keys already passed, per head
+    if (tid == 0) s_left[0] = 0;
+    barrier_lds();
+    int par = 0;
+    for (int hi = kend;; hi -= KEYS, par ^= 1) {
+        const bool more = hi - KEYS > k0;
+        // ---- logits
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            f32x4 z = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+            for (int s = 0; s < D / 32; ++s)
+                z = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kw[t][s]), qw[s], z, 0, 0, 0);
+            const int i = wave * KW + 16 * t + 4 * lq;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) z[r] = hi - KEYS + i + r >= k0 ? z[r] * c2 : -INFINITY;
+            if (l16 < live) *reinterpret_cast<f32x4*>(&zs[par][l16][i]) = z;
+        }
+        if (more) fetch_k(hi - KEYS);
+        barrier_lds();
+        if (tid == 0) s_left[par ^ 1] = 0;                   // everyone has read it, in the pass before
+        // ---- weights: w[i] = 2^(x_i - carry - sum_{i' >= i} sp2(x_i'))  (Eq. 2)
+        for (int g = wave; g < live; g += NW) {
+            constexpr int EPL = KEYS / 64;
+            typedef __attribute__((ext_vector_type(EPL))) float zvec;
+            zvec* z = reinterpret_cast<zvec*>(&zs[par][g][EPL * lane]);
+            zvec x = *z;
+            float sp[EPL], mine = 0.0f;
+#pragma unroll
+            for (int e = 0; e < EPL; ++e) { sp[e] = sp2(x[e]); mine += sp[e]; }
+            float total;
+            const float carry = s_carry[g];
+            float run = wave_suffix_excl(mine, total) + carry;
+#pragma unroll
+            for (int e = EPL - 1; e >= 0; --e) {
+                run += sp[e];
+                x[e] = fast_exp2(x[e] - run);
+            }
+            *z = x;
+            if (lane == 0) {
+                s_carry[g] = carry + total;
+                if (!(carry + total >= CARRY_EXHAUSTED)) atomicAdd(&s_left[par], 1);
+            }
+        }
+        barrier_lds();
+        // ---- output
+        {
+            float w[8];
+            const float* wrow = &zs[par][min(l16, live - 1)][wave * KW + 8 * lq];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) w[i] = wrow[i];
+            bf16x8 w0, w1, w2;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                w0[i] = (__bf16)w[i];
+                const float r1 = w[i] - (float)w0[i];
+                w1[i] = (__bf16)r1;
+                w2[i] = (__bf16)(r1 - (float)w1[i]);
+            }
+#pragma unroll
+            for (int e = 0; e < CW; ++e) {
+                // column e of the 8 rows: bytes 0,1 (e even) or 2,3 (e odd) of word e/2 of each
+                u32x4 x;
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    x[i] = __builtin_amdgcn_perm(vw[2 * i + 1][e >> 1], vw[2 * i][e >> 1], (e & 1) ? 0x07060302u : 0x05040100u);
+                const bf16x8 a = __builtin_bit_cast(bf16x8, x);
+                acc[e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, w2, acc[e], 0, 0, 0);
+                acc[e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, w1, acc[e], 0, 0, 0);
+                acc[e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, w0, acc[e], 0, 0, 0);
+            }
+        }
+        if (!more || (!m && s_left[par] == 0)) break;
+        fetch_v(hi - KEYS);
+    }
 
-    // ---- O_s[g][c] = sum_key w[g][key] V[key][c]
-    float acc[GT][8];
+    // ---- the waves' shares, HB heads at a time
+    for (int gb = 0; gb < live; gb += HB) {
+        if (gb > 0) barrier_lds();
+        if (l16 >= gb && l16 < gb + HB) {
+            float* r = ored + (wave * HB + l16 - gb) * D + CW * 4 * lq;
 #pragma unroll
-    for (int g = 0; g < GT; ++g)
+            for (int rr = 0; rr < 4; ++rr)
 #pragma unroll
-        for (int e = 0; e < 8; ++e) acc[g][e] = 0.0f;
-    for (int r0 = wave * RPI + rw; r0 < n; r0 += U * RSTEP) {
-        u32x4 vw[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int row = k0 + min(r0 + u * RSTEP, n - 1);
-            vw[u] = *reinterpret_cast<const u32x4*>(v + kvbase + (long)row * D + 8 * sub);
+                for (int e = 0; e < CW; ++e) r[CW * rr + e] = acc[e][rr];
         }
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int i = r0 + u * RSTEP;
-            float vf[8];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) { vf[2 * e] = bf_lo(vw[u][e]); vf[2 * e + 1] = bf_hi(vw[u][e]); }
-#pragma unroll
-            for (int g = 0; g < GT; ++g) {
-                const float w = i < n ? zs[g * C + i] : 0.0f;
-#pragma unroll
-                for (int e = 0; e < 8; ++e) acc[g][e] += w * vf[e];
-            }
-        }
-    }
-    // the lanes of a wave that hold the same columns, then the four waves
-#pragma unroll
-    for (int g = 0; g < GT; ++g)
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            float s = acc[g][e];
-#pragma unroll
-            for (int off = LPR; off < 64; off <<= 1) s += __shfl_xor(s, off);
-            if (rw == 0) ored[wave][g][8 * sub + e] = s;
-        }
-    __syncthreads();
-    for (int idx = tid; idx < GT * D; idx += DEC_THREADS) {
-        const int g = idx / D, c = idx % D;
-        if (g0 + g < G) {
+        barrier_lds();
+        for (int i = tid; i < min(HB, live - gb) * D; i += NTHR) {
+            const int g = gb + i / D, c = i % D;
             float s = 0.0f;
 #pragma unroll
-            for (int w = 0; w < DEC_THREADS / 64; ++w) s += ored[w][g][c];
-            const long hq = (long)b * H + hkv * G + g0 + g;
-            part_o[(hq * nchunk + chunk) * D + c] = s;
+            for (int w = 0; w < NW; ++w) s += ored[(w * HB) * D + i];
+            const float a = s_carry[g];
+            if (!FAR && (nfar == 0 || (!m && a >= CARRY_EXHAUSTED))) store_out(rb ? rb + (hkv * G + g0 + g) * D : nullptr, o + (hq0 + g) * D, m ? m + hq0 + g : nullptr, c, s, a);
+            if (nfar > 0) {
+                part_o[((hq0 + g) * nch + chunk) * D + c] = s;
+                if (c == 0) part_a[(hq0 + g) * nch + chunk] = a;
+            }
         }
     }
 }
 
 template <int D>
-__global__ void __launch_bounds__(DEC_THREADS)
+__global__ void __launch_bounds__(COMBINE_THREADS)
 decode_combine_kernel(const float* __restrict__ part_o, const float* __restrict__ part_a,
-                      const uint16_t* __restrict__ rb, uint16_t* __restrict__ o, float* __restrict__ m,
-                      int H, int nchunk)
+                      const uint16_t* __restrict__ rb, uint16_t* __restrict__ o, float* __restrict__ m, int H, int nch)
 {
     constexpr int NV = D / 4;              // a thread adds four columns of every NG-th chunk
-    constexpr int NG = DEC_THREADS / NV;
-    __shared__ float red[DEC_THREADS / 64];
-    __shared__ float ws[DEC_MAXCHUNKS];
-    __shared__ float ored[NG][D];
+    constexpr int NG = COMBINE_THREADS / NV;
+    __shared__ __attribute__((aligned(16))) float ored[NG][D];
+    __shared__ float ws[MAXFAR + 1];
     const long bh = blockIdx.x;
-    const int tid = threadIdx.x;
-    // chunk `tid` is shifted by everything the nearer (higher) chunks took
-    const float a = tid < nchunk ? part_a[bh * nchunk + tid] : 0.0f;
-    float total;
-    const float above = block_suffix_excl(a, red, total);
-    ws[tid] = fast_exp2(-above);
-    __syncthreads();
+    const int tid = threadIdx.x, lane = tid & 63;
     const int c4 = tid % NV, grp = tid / NV;
-    float s0 = 0.0f, s1 = 0.0f, s2 = 0.0f, s3 = 0.0f;
-    const float4* po = reinterpret_cast<const float4*>(part_o + bh * (long)nchunk * D) + c4;
-#pragma unroll 4
-    for (int ch = grp; ch < nchunk; ch += NG) {
-        const float4 p = po[(long)ch * NV];
-        const float w = ws[ch];
-        s0 += w * p.x; s1 += w * p.y; s2 += w * p.z; s3 += w * p.w;
-    }
-    ored[grp][4 * c4] = s0; ored[grp][4 * c4 + 1] = s1; ored[grp][4 * c4 + 2] = s2; ored[grp][4 * c4 + 3] = s3;
+    const float* pa = part_a + bh * nch;
+    if (!m && pa[nch - 1] >= CARRY_EXHAUSTED) return;      // finished by the first launch
+    // chunk i is shifted by everything the nearer (higher) chunks took; lane l holds chunks 2l, 2l + 1
+    float a[2];
+#pragma unroll
+    for (int e = 0; e < 2; ++e) a[e] = 2 * lane + e < nch ? pa[2 * lane + e] : 0.0f;
+    const f32x4* po = reinterpret_cast<const f32x4*>(part_o + bh * (long)nch * D) + c4;
+    // all of a thread's share is in flight at once
+    constexpr int N = (MAXFAR + NG) / NG;
+    f32x4 x[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) x[i] = po[(long)min(grp + i * NG, nch - 1) * NV];
+    float total;
+    float above = wave_suffix_excl(a[0] + a[1], total);
+    if (tid < 64)
+#pragma unroll
+        for (int e = 1; e >= 0; --e) {
+            ws[2 * lane + e] = 2 * lane + e < nch ? fast_exp2(-above) : 0.0f;
+            above += a[e];
+        }
+    __syncthreads();
+    f32x4 s = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int i = 0; i < N; ++i) s += ws[grp + i * NG] * x[i];
+    *reinterpret_cast<f32x4*>(&ored[grp][4 * c4]) = s;
     __syncthreads();
     if (tid < D) {
         float r = 0.0f;
 #pragma unroll
         for (int g = 0; g < NG; ++g) r += ored[g][tid];
-        // remainder bias (Appendix C): what no key took goes to the head's embedding
-        if (rb) r += fast_exp2(-total) * bf_lo((uint32_t)rb[(bh % H) * D + tid]);
-        const __bf16 val = (__bf16)r;
-        o[bh * D + tid] = __builtin_bit_cast(uint16_t, val);
+        store_out(rb ? rb + (bh % H) * D : nullptr, o + bh * D, m ? m + bh : nullptr, tid, r, total);
     }
-    if (m && tid == 0) m[bh] = -total * SB_LN2;
+}
+
+// Partial results there is room for in decode_workspace_bytes: one per 64 keys, or per 64 * 2^i where
+// those would be more than 256.
+int room(int T)
+{
+    int C = 64;
+    while ((T + C - 1) / C > 256) C *= 2;
+    return (T + C - 1) / C;
+}
+
+// How the keys are split: the nearest in the first launch, the rest in nfar chunks of C.
+struct Split {
+    int near, C, nfar;
+};
+Split split_of(long wgs, int T)
+{
+    Split s = {T, NEAR, 0};
+    if (T <= ALONE) return s;
+    s.near = NEAR;
+    const int far = T - s.near;
+    const long want = std::min((long)std::min(MAXFAR, room(T) - 1), std::max(1L, FAR_WGS / wgs));
+    s.C = (int)((far + want - 1) / want + NEAR - 1) / NEAR * NEAR;         // whole passes of either kernel
+    s.nfar = (far + s.C - 1) / s.C;
+    return s;
 }
 
 template <int D>
 hipError_t launch_d(const uint16_t* q, const uint16_t* k, const uint16_t* v, const uint16_t* rb,
-                    uint16_t* o, float* m, float* workspace, int B, int H, int Hkv, int T, int Tcap,
-                    int C, int nchunk, hipStream_t stream)
+                    uint16_t* o, float* m, float* workspace, int B, int H, int Hkv, int T, int Tcap, hipStream_t stream)
 {
     const int G = H / Hkv;
-    float* part_a = workspace;
-    float* part_o = workspace + (((long)B * H * nchunk + 3) & ~3L);
-    const dim3 grid((unsigned)nchunk, (unsigned)(B * Hkv), (unsigned)((G + DEC_GT - 1) / DEC_GT));
-    if (G == 1)
-        hipLaunchKernelGGL((decode_partial_kernel<D, 1>), dim3((unsigned)nchunk, (unsigned)(B * Hkv), 1u),
-                           dim3(DEC_THREADS), sizeof(float) * C, stream, q, k, v, part_o, part_a, T, Tcap, H, G, C, nchunk);
-    else
-        hipLaunchKernelGGL((decode_partial_kernel<D, DEC_GT>), grid, dim3(DEC_THREADS), sizeof(float) * DEC_GT * C, stream,
-                           q, k, v, part_o, part_a, T, Tcap, H, G, C, nchunk);
+    const int nz = (G + GMAX - 1) / GMAX;
+    const Split s = split_of((long)B * Hkv * nz, T);
+    const long heads = (long)B * H;
+    float* part_o = workspace;                                            // [heads][nfar + 1][D]
+    float* part_a = part_o + heads * (s.nfar + 1) * D;                    // [heads][nfar + 1]
+    hipLaunchKernelGGL((decode_kernel<D, false>), dim3((unsigned)(B * Hkv), 1u, (unsigned)nz), dim3(64 * NEAR_NW), 0, stream,
+                       q, k, v, rb, o, m, part_o, part_a, T, Tcap, H, G, s.near, s.C, s.nfar);
     hipError_t e = hipGetLastError();
+    if (e != hipSuccess || s.nfar == 0) return e;
+    hipLaunchKernelGGL((decode_kernel<D, true>), dim3((unsigned)s.nfar, (unsigned)(B * Hkv), (unsigned)nz), dim3(64 * FAR_NW), 0, stream,
+                       q, k, v, rb, o, m, part_o, part_a, T, Tcap, H, G, s.near, s.C, s.nfar);
+    e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((decode_combine_kernel<D>), dim3((unsigned)(B * H)), dim3(DEC_THREADS), 0, stream,
-                       part_o, part_a, rb, o, m, H, nchunk);
+    hipLaunchKernelGGL((decode_combine_kernel<D>), dim3((unsigned)heads), dim3(COMBINE_THREADS), 0, stream,
+                       part_o, part_a, rb, o, m, H, s.nfar + 1);
     return hipGetLastError();
-}
-
-// keys per chunk: as few as keep the chunk count within the combine kernel's reach; larger
-// while the launch would still have more than a thousand workgroups (measured: the fixed
-// cost per workgroup outweighs finer balance beyond that)
-int chunk_keys(int BHkv, int T)
-{
-    int C = 64;
-    while ((T + C - 1) / C > DEC_MAXCHUNKS) C *= 2;
-    while ((long)((T + C - 1) / C) * BHkv > 1024 && C < 1024) C *= 2;
-    return C;
 }
 
 // Scratch of the entry point that allocates nothing: every GPU the library runs on holds its
@@ -318,7 +373,7 @@ void* scratch_ptr[DEC_MAX_DEVICES];        // device address of `scratch`, per d
 
 }  // namespace
 
-int decode_max_T() { return DEC_MAXCHUNKS * DEC_CMAX; }
+int decode_max_T() { return 524288; }
 
 size_t decode_static_bytes() { return DEC_STATIC_BYTES; }
 
@@ -342,10 +397,7 @@ hipError_t decode_static_scratch(float** out)
 
 size_t decode_workspace_bytes(int B, int H, int T, int d)
 {
-    // the chunk count depends on the kv head count only through chunk_keys' second loop,
-    // which can only lower it: size for the largest
-    const int C = chunk_keys(1, T);
-    const size_t nchunk = (size_t)(T + C - 1) / C;
+    const size_t nchunk = room(T);
     return sizeof(float) * ((((size_t)B * H * nchunk + 3) & ~(size_t)3) + (size_t)B * H * nchunk * d);
 }
 
@@ -354,12 +406,9 @@ hipError_t launch_decode(const uint16_t* q, const uint16_t* k, const uint16_t* v
                          int B, int H, int Hkv, int T, int Tcap, int d, hipStream_t stream)
 {
     if (B * Hkv > 65535) return hipErrorInvalidValue;
-    const int C = chunk_keys(B * Hkv, T);
-    if (C > DEC_CMAX) return hipErrorInvalidValue;
-    const int nchunk = (T + C - 1) / C;
-    if (d == 32) return launch_d<32>(q, k, v, rb, o, m, workspace, B, H, Hkv, T, Tcap, C, nchunk, stream);
-    if (d == 64) return launch_d<64>(q, k, v, rb, o, m, workspace, B, H, Hkv, T, Tcap, C, nchunk, stream);
-    return launch_d<128>(q, k, v, rb, o, m, workspace, B, H, Hkv, T, Tcap, C, nchunk, stream);
+    if (d == 32) return launch_d<32>(q, k, v, rb, o, m, workspace, B, H, Hkv, T, Tcap, stream);
+    if (d == 64) return launch_d<64>(q, k, v, rb, o, m, workspace, B, H, Hkv, T, Tcap, stream);
+    return launch_d<128>(q, k, v, rb, o, m, workspace, B, H, Hkv, T, Tcap, stream);
 }
 
 }  // namespace sb

@@ -102,3 +102,25 @@ def test_backward_far_queries_come_back(sb, oracle, gen, d):
     torch.cuda.synchronize()
     for name, a, r in zip(("dq", "dk", "dv"), got, oracle.bwd(*(to64(t) for t in (q, k, v, g)))):
         check_grad(name, to64(a), r)
+
+
+@pytest.mark.parametrize("H,Hkv,T,d", [(6, 3, 256, 128), (6, 3, 257, 64), (34, 2, 600, 32), (12, 3, 1536, 128), (12, 3, 1537, 128),
+                                       (6, 3, 1793, 64), (3, 3, 2048, 32), (51, 3, 3000, 64), (3, 3, 33025, 128)])
+def test_decode(sb, oracle, gen, H, Hkv, T, d):
+    """Caches at the edges of the passes and of the two launches, groups of 1 to 17 heads; without m
+    (exhausted heads finish early) and with it (no head does)."""
+    q = gen.gaussian(1, H, 1, d, seed=T)[0][:, :, 0].clone()
+    qk, k, v = mixed(gen, 1, Hkv, T, d, seed=T + 1)
+    G = H // Hkv
+    for h in range(2, Hkv, 3):
+        q[:, h * G:(h + 1) * G] = qk[:, h, -1:].expand(-1, G, -1)
+    r = gen.remainder_embedding(H, d, seed=3)
+    ref, rem = oracle.decode(*(to64(t) for t in (q, k, v)), r=to64(r))
+    ws = nan_bytes(sb.load().sb_attn_decode_workspace_bytes(1, H, T, d))
+    qd, kd, vd, rd = dev(q, k, v, r)
+    o = sb.sb_attn_decode(qd, kd, vd, r=rd, workspace=ws)
+    o2, m = sb.sb_attn_decode(qd, kd, vd, r=rd, workspace=ws, want_m=True)
+    torch.cuda.synchronize()
+    for x in (o, o2):
+        assert np.all(np.abs(to64(x) - ref) <= fwd_bound(ref, to64(v)))
+    check_m(to64(m), rem)
