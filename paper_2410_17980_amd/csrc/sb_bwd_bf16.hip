@@ -227,17 +227,11 @@ __device__ __forceinline__ void stage_one(const uint16_t* X, int jt, int T, char
                                           const int (&goff)[StageCfg<D>::NPW], int wave, int lane)
 {
     using C = StageCfg<D>;
-    if ((jt + 1) * TK <= T) {                           // all 64 rows exist
-        dma16_to_lds_run(X + (long)jt * TK * D, goff, sp + wave * C::NPW * 1024);
-    } else {                                            // rows past T are clamped (their results are masked)
-#pragma unroll
-        for (int i = 0; i < C::NPW; ++i) {
-            const int row = (wave * C::NPW + i) * C::BLK_ROWS + lane / C::CPR;
-            const int c = (lane % C::CPR) ^ (PERM ? swz_perm<D>(row) : swz_nat<D>(row));
-            const long gr = min(jt * TK + row, T - 1);
-            dma16_to_lds(X + gr * D + c * 8, sp + (wave * C::NPW + i) * 1024);
-        }
-    }
+    const uint16_t* xb = X + (long)jt * TK * D;
+    char* dst = sp + wave * C::NPW * 1024;
+    if ((jt + 1) * TK <= T) dma16_to_lds_run(xb, goff, dst);
+    else                                                // rows past T are clamped (their results are masked)
+        dma16_to_lds_run_clamped<C::ROW, C::BLK_ROWS>(xb, goff, wave * C::NPW * C::BLK_ROWS + lane / C::CPR, T - 1 - jt * TK, dst);
 }
 
 // and of X, then Y
@@ -264,7 +258,7 @@ bwd_dq_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
               const uint16_t* __restrict__ dout, float* __restrict__ dq,
               float* __restrict__ ca, float* __restrict__ cb, int* __restrict__ first,
               int T_arg, int BH, int H, int G, int nqb_arg, int nt32, const int* __restrict__ cu, int Ttot,
-              int spread, int single)
+              int mode, int single)
 {
     using C = StageCfg<D>;
     __shared__ __attribute__((aligned(1024))) char smem[2 * C::STAGE];
@@ -272,15 +266,15 @@ bwd_dq_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
 
     const int wg = blockIdx.x;
     Share sh;
-    if (!share_of(sh, wg, BH, (nqb_arg + 1) >> 1, spread, single)) return;
-    const long bh = sh.bh;
+    if (!share_of(sh, wg, BH, (nqb_arg + 1) >> 1, mode, single)) return;
+    const int bh = sh.bh;
     const int pidx = sh.p;
     int T = T_arg, nqb = nqb_arg;
     long row0, kvrow0, cbase, cstride;      // first q / k row of this head; carries: base and strip stride
     int head;
     if constexpr (VL) {
-        const int seq = (int)(bh / H);
-        head = (int)(bh % H);
+        const int seq = bh / H;
+        head = bh % H;
         const int c0 = cu[seq];
         T = min(min(cu[seq + 1], Ttot) - c0, T_arg);      // never past the packed rows or the stated maximum
         if (c0 < 0) return;
@@ -292,10 +286,10 @@ bwd_dq_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
         cstride = Ttot;
     } else {
         // grouped kv heads: G consecutive query heads read the same K and V
-        head = (int)(bh % H);
+        head = bh % H;
         row0 = bh * (long)T;
         kvrow0 = (G == 1 ? bh : (bh / H) * (H / G) + (bh % H) / G) * (long)T;
-        cbase = bh * (long)nt32 * T;
+        cbase = (long)bh * nt32 * T;
         cstride = T;
     }
 
@@ -372,7 +366,7 @@ bwd_dq_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
         SubtileOut so;
         Chain ch;
         const bool fits = subtile_stage1<MASK, SIGMA_DQ>(ch, s_mfma(), c2, n, hh);
-        if (__builtin_amdgcn_ballot_w64(!fits) != 0) subtile_stage1_log<MASK>(ch, s_mfma(), c2, n, hh);
+        if (__builtin_expect(__builtin_amdgcn_ballot_w64(!fits) != 0, 0)) subtile_stage1_log<MASK>(ch, s_mfma(), c2, n, hh);
         const f32x16 pacc = p_mfma();
         subtile_stage2<true, false>(so, ch, pacc, a2, bsum, hh);
         // carries of this (subtile, query) for the key-stationary kernel
@@ -407,19 +401,20 @@ bwd_dq_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     // which also spares the start a sum over all keys that is then subtracted again.
     // Tried only where m says that the rows have at least twice what exhausts them, so that the
     // point is expected in the nearer half, and given up after that half: at worst a sixth more.
-    auto find_start = [&](const uint16_t* Kg, int T, int ntile, int nclean, bool wave_live) __attribute__((always_inline)) {
+    auto stage_pair = [&](const uint16_t* Kg, int T, int ntile, int i) __attribute__((always_inline)) {
+        char* sp = smem + (i & 1) * C::STAGE;
+        const int t = ntile - 1 - 2 * i;                     // the upper tile of the pair
+        stage_one<D, true>(Kg, t, T, sp, goff, wave, lane);
+        stage_one<D, true>(Kg, t - 1, T, sp + C::TILE, goff, wave, lane);
+    };
+    // (pair 0 has been staged)
+    auto find_start = [&](const uint16_t* Kg, int T, int ntile, bool wave_live) __attribute__((always_inline)) {
         const int limit = ntile >> 2;                        // pairs of tiles
         if (wave_live ? __builtin_amdgcn_ballot_w64(!(a2 >= 2.0f * CARRY_EXHAUSTED)) == 0 : true) {
             if (lane == 0) s_done[1][wave] = 1;
         } else if (lane == 0) s_done[1][wave] = 0;
         barrier_lds();
-        if (nclean < 6 || !waves_done(s_done[1])) return 0;
-        auto stage_pair = [&](int i) __attribute__((always_inline)) {
-            char* sp = smem + (i & 1) * C::STAGE;
-            const int t = ntile - 1 - 2 * i;                 // the upper tile of the pair; 2 * limit <= ntile
-            stage_one<D, true>(Kg, t, T, sp, goff, wave, lane);
-            stage_one<D, true>(Kg, t - 1, T, sp + C::TILE, goff, wave, lane);
-        };
+        if (!waves_done(s_done[1])) return 0;
         float l = 0.0f, left = 0.0f;                         // this lane's keys only; both halves'
         auto sum_subtile = [&](auto mask_c, uint32_t ktile) __attribute__((always_inline)) {
             constexpr bool MASK = decltype(mask_c)::value;
@@ -435,7 +430,6 @@ bwd_dq_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
                 acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kw[s]), qf[s], acc, 0, 0, 0);
             l += sp2_total<MASK>(acc, c2, n, hh);
         };
-        stage_pair(0);
         for (int i = 0;; ++i) {
             dma_wait<0>();
             barrier_lds();
@@ -445,7 +439,7 @@ bwd_dq_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
                 return ntile - 2 * i;
             }
             if (i == limit) return 0;
-            if (i + 1 < limit) stage_pair(i + 1);
+            if (i + 1 < limit) stage_pair(Kg, T, ntile, i + 1);
             if (wave_live) {
 #pragma unroll
                 for (int x = 0; x < 4; ++x) {
@@ -470,7 +464,14 @@ bwd_dq_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
         q0 = Q0 + wave * 32;
         const bool wave_live = q0 < T;
         const int jq = min(q0 + n, T - 1);
-        barrier_nofence();                               // everyone is done with the stages of the block before
+        const int kmax = min(T, Q0 + BQ) - 1;            // keys 0 .. kmax-1 are visible to some row
+        const int ntile = (kmax + TK - 1) / TK;
+        const int nclean = min(ntile, Q0 / TK);          // tiles entirely left of the block's rows
+        const bool far = nclean >= 6;                    // long enough to look for a start
+        if (part > sh.part0) barrier_nofence();          // everyone is done with the stages of the block before
+        // what the block needs first, tiles and rows alike, is fetched together: one memory latency
+        if (far) stage_pair(Kg, T, ntile, 0);
+        else if (ntile > 0) stage_tile<D, true>(Kg, Vg, 0, T, smem, goff, wave, lane);
         {
             const u32x4* qs = reinterpret_cast<const u32x4*>(q + base + (long)jq * D + 8 * hh);
             const u32x4* gs = reinterpret_cast<const u32x4*>(dout + base + (long)jq * D + 8 * hh);
@@ -500,8 +501,8 @@ bwd_dq_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
             both_halves(dot, d_lo, d_hi);
             bsum = fast_exp2(-a2) * (d_lo + d_hi);
         }
-        // wait for these loads (and the first block's stores) once, before the staging
-        // loads, which are counted in the same counter behind the compiler's back
+        // wait for these loads (and the first block's stores) once: the staging loads of the sweep
+        // are counted in the same counter behind the compiler's back
 #pragma unroll
         for (int s = 0; s < D / 16; ++s) { asm volatile("" :: "v"(qf[s])); asm volatile("" :: "v"(gf[s])); }
         asm volatile("" :: "v"(a2));
@@ -513,17 +514,17 @@ bwd_dq_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
             for (int r = 0; r < 16; ++r) dqacc[b][r] = 0.0f;
 
         // ---- sweep over 64-key tiles, left to right; iteration it handles tile it in buffer it & 1
-        const int kmax = min(T, Q0 + BQ) - 1;            // keys 0 .. kmax-1 are visible to some row
-        const int ntile = (kmax + TK - 1) / TK;
-        const int nclean = min(ntile, Q0 / TK);          // tiles entirely left of the block's rows
-        const int t0 = find_start(Kg, T, ntile, nclean, wave_live);
-        if (tid == 0) first[bh * nqb_arg + qb] = t0;
-        stage_tile<D, true>(Kg, Vg, t0, T, smem + (t0 & 1) * C::STAGE, goff, wave, lane);
+        int t0 = 0;
+        if (far) {
+            t0 = find_start(Kg, T, ntile, wave_live);
+            stage_tile<D, true>(Kg, Vg, t0, T, smem + (t0 & 1) * C::STAGE, goff, wave, lane);
+        }
+        if (tid == 0) first[(long)bh * nqb_arg + qb] = t0;
         auto begin_iter = [&](int it) __attribute__((always_inline)) {
             dma_wait<0>();                               // this wave's share of tile `it` has landed
             barrier_nofence();                           // ... everyone's has, and tile it-1 is no longer read
-            // past the end tile 0 is loaded once more into the buffer nobody reads
-            stage_tile<D, true>(Kg, Vg, it + 1 < ntile ? it + 1 : 0, T, smem + ((it + 1) & 1) * C::STAGE, goff, wave, lane);
+            if (it + 1 < ntile)
+                stage_tile<D, true>(Kg, Vg, it + 1, T, smem + ((it + 1) & 1) * C::STAGE, goff, wave, lane);
             return smem0 + (it & 1) * C::STAGE;
         };
         int it = t0;
@@ -543,7 +544,6 @@ bwd_dq_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
                 }
             }
         }
-        dma_wait<0>();
 
         // ---- dQ store: dqacc[b][r] is query row 8*(r/4) + 4*hh + r%4, column 32b + n
         if (wave_live) {
@@ -572,13 +572,13 @@ struct KvHead {
 };
 
 template <int D, bool VL>
-__device__ __forceinline__ bool kv_head(KvHead& kh, long bh, int pidx, int T_arg, int nkb_arg, int H, int G,
+__device__ __forceinline__ bool kv_head(KvHead& kh, int bh, int pidx, int T_arg, int nkb_arg, int H, int G,
                                         int nt32, const int* __restrict__ cu, int Ttot)
 {
     const int Hkv = H / G;
     if constexpr (VL) {
-        const int seq = (int)(bh / Hkv);
-        const int hkv = (int)(bh % Hkv);
+        const int seq = bh / Hkv;
+        const int hkv = bh % Hkv;
         const int c0 = cu[seq];
         kh.T = min(min(cu[seq + 1], Ttot) - c0, T_arg);   // never past the packed rows or the stated maximum
         if (c0 < 0) return false;
@@ -595,7 +595,7 @@ __device__ __forceinline__ bool kv_head(KvHead& kh, long bh, int pidx, int T_arg
         const long qh0 = G == 1 ? bh : (bh / Hkv) * H + (bh % Hkv) * G;
         kh.T = T_arg;
         kh.nkb = nkb_arg;
-        kh.base = bh * (long)T_arg * D;
+        kh.base = (long)bh * T_arg * D;
         kh.qrow0 = qh0 * (long)T_arg;
         kh.qhead0 = qh0;
         kh.qrow_step = T_arg;
@@ -640,7 +640,7 @@ bwd_dkv_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
                const float* __restrict__ ca, const float* __restrict__ cb,
                float* __restrict__ dk, float* __restrict__ dv, const int* __restrict__ first,
                int T_arg, int BH, int H, int G_arg, int nkb_arg, int nt32, const int* __restrict__ cu, int Ttot,
-               int spread, int single)
+               int mode, int single)
 {
     using C = StageCfg<D>;
     using CK = DkvCfg<D>;
@@ -649,8 +649,8 @@ bwd_dkv_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
 
     const int wg = blockIdx.x;
     Share sh;
-    if (!share_of(sh, wg, BH, (nkb_arg + 1) >> 1, spread, single)) return;
-    const long bh = sh.bh;
+    if (!share_of(sh, wg, BH, (nkb_arg + 1) >> 1, mode, single)) return;
+    const int bh = sh.bh;
     const int pidx = sh.p;
 
     const int tid = threadIdx.x;
@@ -698,6 +698,17 @@ bwd_dkv_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     f32x16 dkacc[D / 32], dvacc[D / 32];
     const float* cag = nullptr;
     const float* cbg = nullptr;
+    // ca, cb of query tile jt for this wave's keys.  Rows past T, tiles that do not reach the keys: an
+    // infinite carry gives A = 0 and G = 0, and with cb = 0 also dZ = 0.  (A dead wave's rows lie
+    // outside the arrays.)
+    auto load_carries = [&](float (&cn)[2][2], int jt, bool there) __attribute__((always_inline)) {
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const int j = jt * TK + 32 * u + n;
+            cn[u][0] = (j < T && there) ? cag[j] : INFINITY;
+            cn[u][1] = (j < T && there) ? cbg[j] : 0.0f;
+        }
+    };
 
     // one 32-query subtile at query rows j0 .. j0+31
     // the steps of one 32-query subtile (Q rows at qtile, dO rows C::TILE further).  All
@@ -775,7 +786,7 @@ bwd_dkv_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
         bf16x8 gop[D / 16], qop[D / 16];
         mm2_fetch(qtile, gop, qop);                          // lands during the element-wise work
         Chain ch;
-        if (__builtin_amdgcn_ballot_w64(!subtile_stage1<MASK, SIGMA_DKV>(ch, sacc, c2, n, hh)) != 0) {
+        if (__builtin_expect(__builtin_amdgcn_ballot_w64(!subtile_stage1<MASK, SIGMA_DKV>(ch, sacc, c2, n, hh)) != 0, 0)) {
             f32x16 again;
 #pragma unroll
             for (int r = 0; r < 16; ++r) again[r] = 0.0f;
@@ -797,7 +808,19 @@ bwd_dkv_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
         const int k0 = K0 + wave * 32;                       // this wave's 32 keys
         const int kt32 = k0 >> 5;
         const bool wave_live = k0 < T;
-        barrier_nofence();                                   // everyone is done with the stages of the block before
+        const int jt0 = K0 / TK;
+        float cn[2][2];                                      // [subtile][ca, cb] of the next tile
+        // the block's first tile of a head and its carries, which always reach these keys
+        auto first_tile = [&](int g) __attribute__((always_inline)) {
+            Qg = q + (qrow0 + g * qrow_step) * D;
+            Gg = dout + (qrow0 + g * qrow_step) * D;
+            cag = ca + cbase + g * cbase_step + kt32 * cstride;
+            cbg = cb + cbase + g * cbase_step + kt32 * cstride;
+            load_carries(cn, jt0, wave_live);
+            stage_tile<D, false>(Qg, Gg, jt0, T, smem, goff, wave, lane);
+        };
+        if (part > sh.part0) barrier_nofence();              // everyone is done with the stages of the block before
+        first_tile(0);                                       // fetched together with the stationary rows
         {
             const long kr = min(k0 + perm_row(n), T - 1);
             const u32x4* ks = reinterpret_cast<const u32x4*>(k + base + kr * D + 8 * hh);
@@ -817,46 +840,31 @@ bwd_dkv_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
             for (int r = 0; r < 16; ++r) { dkacc[b][r] = 0.0f; dvacc[b][r] = 0.0f; }
         // the query heads of the group one after the other, into the same accumulators
         for (int g = 0; g < G; ++g) {
-        Qg = q + (qrow0 + g * qrow_step) * D;
-        Gg = dout + (qrow0 + g * qrow_step) * D;
-        cag = ca + cbase + g * cbase_step + kt32 * cstride;
-        cbg = cb + cbase + g * cbase_step + kt32 * cstride;
-        if (g > 0) barrier_nofence();                        // everyone is done with the stages of the head before
+        if (g > 0) {
+            barrier_nofence();                               // everyone is done with the stages of the head before
+            first_tile(g);
+        }
 
         // ---- sweep over 64-row query tiles, from the block's diagonal to the end;
         // iteration it handles tile jt0 + it in buffer it & 1.  The carries of a tile are
         // fetched one iteration ahead, and BEFORE the staging loads of that iteration are
         // issued: vector memory operations complete in order, so a wait for a carry
         // issued after the staging loads would wait for those as well.
-        const int jt0 = K0 / TK;
         const int* const fg = first + (kh.qhead0 + g) * nkb_arg;
         const Reach reach = reach_of(fg, kb, nkb, lane);
-        const int ntile = max(min((T + TK - 1) / TK, reach.end) - jt0, 0);
+        const int ntile = min((T + TK - 1) / TK, reach.end) - jt0;
         const int ndiag = min(ntile, BKW / TK);              // tiles that touch the diagonal band
-        float cn[2][2];                                      // [subtile][ca, cb] of the next tile
-        auto load_carries = [&](int jt) __attribute__((always_inline)) {
-            const bool there = wave_live && (jt < reach.sure || fg[jt >> 1] <= kt32 >> 1);
-#pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                const int j = jt * TK + 32 * u + n;
-                // rows past T, tiles that do not reach these keys: an infinite carry gives A = 0 and
-                // G = 0, and with cb = 0 also dZ = 0
-                cn[u][0] = (j < T && there) ? cag[j] : INFINITY;   // a dead wave's rows lie outside the arrays
-                cn[u][1] = (j < T && there) ? cbg[j] : 0.0f;
-            }
-        };
-        if (ntile > 0) {
-            load_carries(jt0);
-            stage_tile<D, false>(Qg, Gg, jt0, T, smem, goff, wave, lane);
-        }
         float cc[2][2];
         auto begin_iter = [&](int it) __attribute__((always_inline)) {
             dma_wait<0>();
             barrier_nofence();
 #pragma unroll
             for (int u = 0; u < 2; ++u) { cc[u][0] = cn[u][0]; cc[u][1] = cn[u][1]; }
-            if (it + 1 < ntile) load_carries(jt0 + it + 1);
-            stage_tile<D, false>(Qg, Gg, it + 1 < ntile ? jt0 + it + 1 : jt0, T, smem + ((it + 1) & 1) * C::STAGE, goff, wave, lane);
+            if (it + 1 < ntile) {
+                const int jt = jt0 + it + 1;
+                load_carries(cn, jt, wave_live && (jt < reach.sure || fg[jt >> 1] <= kt32 >> 1));
+                stage_tile<D, false>(Qg, Gg, jt, T, smem + ((it + 1) & 1) * C::STAGE, goff, wave, lane);
+            }
             return (const char*)(smem + (it & 1) * C::STAGE);
         };
         int it = 0;
@@ -879,7 +887,6 @@ bwd_dkv_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
                 if (j0 + 32 < T) subtile(bc<false>{}, sp + 32 * C::ROW, cc[1][0], cc[1][1]);
             }
         }
-        dma_wait<0>();
         }
 
         // ---- store: acc[b][r] is key row k0 + 8*(r/4) + 4*hh + r%4, column 32b + n
@@ -948,7 +955,7 @@ bwd_dkv_pair_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
                     const float* __restrict__ ca, const float* __restrict__ cb,
                     float* __restrict__ dk, float* __restrict__ dv, const int* __restrict__ first,
                     int T_arg, int BH, int H, int G_arg, int nkb_arg, int nt32, const int* __restrict__ cu, int Ttot,
-               int spread, int single)
+               int mode, int single)
 {
     using C = StageCfg<D>;
     using CK = Dkv3Cfg<D>;
@@ -958,8 +965,8 @@ bwd_dkv_pair_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
 
     const int wg = blockIdx.x;
     Share sh;
-    if (!share_of(sh, wg, BH, (nkb_arg + 1) >> 1, spread, single)) return;
-    const long bh = sh.bh;
+    if (!share_of(sh, wg, BH, (nkb_arg + 1) >> 1, mode, single)) return;
+    const int bh = sh.bh;
     const int pidx = sh.p;
 
     const int tid = threadIdx.x;
@@ -999,9 +1006,9 @@ bwd_dkv_pair_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
     }
     const uint32_t smem0 = lds_offset(smem);
     auto stage = [&](int jt, char* sp) __attribute__((always_inline)) {
+        const uint16_t* xb = Qg + (long)jt * TK * D;
+        const uint16_t* yb = Gg + (long)jt * TK * D;
         if ((jt + 1) * TK <= T) {                           // all 64 rows exist
-            const uint16_t* xb = Qg + (long)jt * TK * D;
-            const uint16_t* yb = Gg + (long)jt * TK * D;
 #pragma unroll
             for (int i = 0; i < CK::NPW; ++i)
                 if (wave + NW2 * i < CK::LOADS) {
@@ -1009,14 +1016,13 @@ bwd_dkv_pair_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
                     dma16_to_lds_saddr(yb, goff[i], sp + C::TILE + (wave + NW2 * i) * 1024);
                 }
         } else {                                            // rows past T are clamped (their results are masked)
+            const int last = T - 1 - jt * TK;
 #pragma unroll
             for (int i = 0; i < CK::NPW; ++i)
                 if (wave + NW2 * i < CK::LOADS) {
-                    const int row = (wave + NW2 * i) * C::BLK_ROWS + lane / C::CPR;
-                    const int c = (lane % C::CPR) ^ swz_nat<D>(row);
-                    const long gr = min(jt * TK + row, T - 1);
-                    dma16_to_lds(Qg + gr * D + c * 8, sp + (wave + NW2 * i) * 1024);
-                    dma16_to_lds(Gg + gr * D + c * 8, sp + C::TILE + (wave + NW2 * i) * 1024);
+                    const int o = goff[i] - max((wave + NW2 * i) * C::BLK_ROWS + lane / C::CPR - last, 0) * C::ROW;
+                    dma16_to_lds_saddr(xb, o, sp + (wave + NW2 * i) * 1024);
+                    dma16_to_lds_saddr(yb, o, sp + C::TILE + (wave + NW2 * i) * 1024);
                 }
         }
     };
@@ -1074,7 +1080,7 @@ bwd_dkv_pair_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
         }
         SubtileOut so;
         Chain ch;
-        if (__builtin_amdgcn_ballot_w64(!subtile_stage1<MASK, SIGMA_DKV>(ch, sacc, c2, n, hh)) != 0)
+        if (__builtin_expect(__builtin_amdgcn_ballot_w64(!subtile_stage1<MASK, SIGMA_DKV>(ch, sacc, c2, n, hh)) != 0, 0))
             subtile_stage1_log<MASK>(ch, logits(qa), c2, n, hh);
         subtile_stage2<false, true>(so, ch, pacc, car, cbl, hh);
         const uint32_t w = sc + role * CK::W_BYTES + sw_off;
@@ -1145,7 +1151,7 @@ bwd_dkv_pair_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
             pacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[s], __builtin_bit_cast(bf16x8, gw[s]), pacc, 0, 0, 0);
         back(ptile, scp, 0);
         __builtin_amdgcn_sched_barrier(0);
-        if (__builtin_amdgcn_ballot_w64(!fits) != 0) subtile_stage1_log<false>(ch, logits(qa), c2, n, hh);
+        if (__builtin_expect(__builtin_amdgcn_ballot_w64(!fits) != 0, 0)) subtile_stage1_log<false>(ch, logits(qa), c2, n, hh);
         __builtin_amdgcn_s_setprio(1);
         // part C: A, G, dZ (vector) beside the back of subtile 1 (matrix)
         SubtileOut so;
@@ -1167,7 +1173,26 @@ bwd_dkv_pair_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
         const int k0 = K0 + strip * 32;                      // the strip's 32 keys
         const int kt32 = k0 >> 5;
         const bool live = k0 < T;
-        barrier_lds();                                       // everyone is done with the LDS of the block before
+        const int jt0 = K0 / TK;
+        float cn0, cn1;                                      // ca, cb of this wave's subtile of the next tile
+        // rows past T, tiles that do not reach the keys: an infinite carry gives A = 0 and G = 0, and
+        // with cb = 0 also dZ = 0 (a dead strip's rows lie outside the arrays)
+        auto load_carries = [&](int jt, bool there) __attribute__((always_inline)) {
+            const int j = jt * TK + 32 * role + n;
+            cn0 = (j < T && there) ? cag[j] : INFINITY;
+            cn1 = (j < T && there) ? cbg[j] : 0.0f;
+        };
+        // the block's first tile of a head and its carries, which always reach these keys
+        auto first_tile = [&](int g) __attribute__((always_inline)) {
+            Qg = q + (qrow0 + g * qrow_step) * D;
+            Gg = dout + (qrow0 + g * qrow_step) * D;
+            cag = ca + cbase + g * cbase_step + kt32 * cstride;
+            cbg = cb + cbase + g * cbase_step + kt32 * cstride;
+            load_carries(jt0, live);
+            stage(jt0, smem);
+        };
+        if (part > sh.part0) barrier_lds();                  // everyone is done with the LDS of the block before
+        first_tile(0);                                       // fetched together with the stationary rows
         {
             const long kr = min(k0 + perm_row(n), T - 1);
             const u32x4* ks = reinterpret_cast<const u32x4*>(k + base + kr * D + 8 * hh);
@@ -1188,35 +1213,21 @@ bwd_dkv_pair_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
 
         // the query heads of the group one after the other, into the same accumulators
         for (int g = 0; g < G; ++g) {
-        Qg = q + (qrow0 + g * qrow_step) * D;
-        Gg = dout + (qrow0 + g * qrow_step) * D;
-        cag = ca + cbase + g * cbase_step + kt32 * cstride;
-        cbg = cb + cbase + g * cbase_step + kt32 * cstride;
-        if (g > 0) barrier_lds();                            // everyone is done with the LDS of the head before
+        if (g > 0) {
+            dma_wait<0>();                                   // the steady state's last staging, read by nobody
+            barrier_lds();                                   // everyone is done with the LDS of the head before
+            first_tile(g);
+        }
 
         // ---- sweep over 64-row query tiles, from the block's diagonal to the end.  Interval
         // `it` (between two barriers) holds the front of tile jt0 + it (buffer it % 3, scratch
         // it & 1) and the back of tile jt0 + it - 1; the staging loads of tile jt0 + it + 1 are
         // issued at its start, after the carries of that tile (vector memory operations
         // complete in order, so the carries must not queue behind the staging loads).
-        const int jt0 = K0 / TK;
         const int* const fg = first + (kh.qhead0 + g) * nkb_arg;
         const Reach reach = reach_of(fg, kb, nkb, lane);
-        const int ntile = max(min((T + TK - 1) / TK, reach.end) - jt0, 0);
+        const int ntile = min((T + TK - 1) / TK, reach.end) - jt0;
         const int ndiag = min(ntile, BKW / TK);              // tiles that touch the diagonal band
-        float cn0 = INFINITY, cn1 = 0.0f;                    // ca, cb of this wave's subtile of the next tile
-        auto load_carries = [&](int jt) __attribute__((always_inline)) {
-            const bool there = live && (jt < reach.sure || fg[jt >> 1] <= kt32 >> 1);
-            const int j = jt * TK + 32 * role + n;
-            // rows past T, tiles that do not reach these keys: an infinite carry gives A = 0 and
-            // G = 0, and with cb = 0 also dZ = 0
-            cn0 = (j < T && there) ? cag[j] : INFINITY;      // a dead strip's rows lie outside the arrays
-            cn1 = (j < T && there) ? cbg[j] : 0.0f;
-        };
-        if (ntile > 0) {
-            load_carries(jt0);
-            stage(jt0, smem);
-        }
         // steady state (the intervals hot_begin .. hot_end - 1): the strip is live, tile `it` is past
         // the diagonal band and complete, and the next tile is complete and reaches the block's keys,
         // or does not exist
@@ -1265,8 +1276,9 @@ bwd_dkv_pair_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
             barrier_lds();        // tile `it` has landed, the scratch of tile it-1 is complete, tile it-2 is free
             const float car = cn0, cbl = cn1;
             if (it + 1 < ntile) {
-                load_carries(jt0 + it + 1);
-                stage(jt0 + it + 1, smem + bnext * C::STAGE);
+                const int jt = jt0 + it + 1;
+                load_carries(jt, live && (jt < reach.sure || fg[jt >> 1] <= kt32 >> 1));
+                stage(jt, smem + bnext * C::STAGE);
             }
             const int jbase = (jt0 + it) * TK;
             const uint32_t qt = smem0 + bcur * C::STAGE + role * 32 * C::ROW;
@@ -1397,7 +1409,7 @@ hipError_t launch_one(const uint16_t* q, const uint16_t* k, const uint16_t* v, c
 #define SB_DQ(RBV)                                                                                              \
     hipLaunchKernelGGL((bwd_dq_kernel<D, RBV, VL>), dim3((unsigned)rq.grid), dim3(NTHREADS), 0, stream,         \
                        q, k, v, rb, m, dout, dq, ca, cb, first, T, BH, H, G, nqb, nt32, cu, Ttot,               \
-                       rq.spread, rq.single);                                                                   \
+                       rq.mode, rq.single);                                                                   \
     if ((e = hipGetLastError()) != hipSuccess) return e
 // d = 128 takes the paired-wave kernel (two waves per SIMD instead of one); smaller head
 // dimensions leave room for two workgroups of the one-wave-per-strip kernel per CU, which
@@ -1406,11 +1418,11 @@ hipError_t launch_one(const uint16_t* q, const uint16_t* k, const uint16_t* v, c
     if constexpr (D == 128)                                                                                     \
         hipLaunchKernelGGL((bwd_dkv_pair_kernel<D, GQAV, VL>), dim3((unsigned)rk.grid), dim3(NTHREADS2), 0,     \
                            stream, q, k, v, dout, ca, cb, dk, dv, first, T, BHkv, H, G, nkb, nt32, cu, Ttot,    \
-                           rk.spread, rk.single);                                                               \
+                           rk.mode, rk.single);                                                               \
     else                                                                                                        \
         hipLaunchKernelGGL((bwd_dkv_kernel<D, GQAV, VL>), dim3((unsigned)rk.grid), dim3(NTHREADS), 0,           \
                            stream, q, k, v, dout, ca, cb, dk, dv, first, T, BHkv, H, G, nkb, nt32, cu, Ttot,    \
-                           rk.spread, rk.single);                                                               \
+                           rk.mode, rk.single);                                                               \
     if ((e = hipGetLastError()) != hipSuccess) return e
     if (passes & 1) {
         if (rb) { SB_DQ(true); }

@@ -87,7 +87,7 @@ fwd_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
                 uint16_t* __restrict__ o, float* __restrict__ m,
                 int T_arg, int BH, int H, int G, int nqb_arg, float enough,
                 unsigned long long* __restrict__ tile_counts, const int* __restrict__ cu, int Ttot,
-                int spread, int single)
+                int mode, int single)
 {
     using C = FwdCfg<D>;
     constexpr int NPW = C::NPW;
@@ -99,15 +99,15 @@ fwd_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     const int wg = blockIdx.x;
     const int npair = (nqb_arg + 1) >> 1;
     Share sh;
-    if (!share_of(sh, wg, BH, npair, spread, single)) return;
-    const long bh = sh.bh;
+    if (!share_of(sh, wg, BH, npair, mode, single)) return;
+    const int bh = sh.bh;
     const int pidx = sh.p;
     int T = T_arg, nqb = nqb_arg;
     long row0, kvrow0;                                  // first row of this head's q / k rows
     int head;
     if constexpr (VL) {
-        const int seq = (int)(bh / H);
-        head = (int)(bh % H);
+        const int seq = bh / H;
+        head = bh % H;
         const int c0 = cu[seq];
         T = min(min(cu[seq + 1], Ttot) - c0, T_arg);      // never past the packed rows or the stated maximum
         if (c0 < 0) return;
@@ -117,7 +117,7 @@ fwd_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
         kvrow0 = (long)(head / G) * Ttot + c0;
     } else {
         // grouped kv heads: G consecutive query heads read the same K and V
-        head = (int)(bh % H);
+        head = bh % H;
         row0 = bh * (long)T;
         kvrow0 = (G == 1 ? bh : (bh / H) * (H / G) + (bh % H) / G) * (long)T;
     }
@@ -190,26 +190,15 @@ fwd_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     }
     auto stage_tile = [&](int jt, int st) __attribute__((always_inline)) {
         char* sp = smem + st * C::STAGE;
+        const uint16_t* kb = Kg + (long)jt * C::TK * D;
+        const uint16_t* vb = Vg + (long)jt * C::TK * D;
         if ((jt + 1) * C::TK <= T) {                    // all 64 rows exist
-            const uint16_t* kb = Kg + (long)jt * C::TK * D;
-            const uint16_t* vb = Vg + (long)jt * C::TK * D;
             dma16_to_lds_run(kb, goff, sp + wave * NPW * 1024);
             dma16_to_lds_run(vb, goff, sp + C::KT_BYTES + wave * NPW * 1024);
         } else {                                        // rows past T are clamped (causality masks them)
-#pragma unroll
-            for (int i = 0; i < NPW; ++i) {
-                const int row = (wave * NPW + i) * C::BLK_ROWS + lane / C::CPR;
-                const int c = (lane % C::CPR) ^ swz_perm<D>(row);
-                const long gr = min(jt * C::TK + row, T - 1);
-                dma16_to_lds(Kg + gr * D + c * 8, sp + (wave * NPW + i) * 1024);
-            }
-#pragma unroll
-            for (int i = 0; i < NPW; ++i) {
-                const int row = (wave * NPW + i) * C::BLK_ROWS + lane / C::CPR;
-                const int c = (lane % C::CPR) ^ swz_perm<D>(row);
-                const long gr = min(jt * C::TK + row, T - 1);
-                dma16_to_lds(Vg + gr * D + c * 8, sp + C::KT_BYTES + (wave * NPW + i) * 1024);
-            }
+            const int row0 = wave * NPW * C::BLK_ROWS + lane / C::CPR, last = T - 1 - jt * C::TK;
+            dma16_to_lds_run_clamped<C::ROW, C::BLK_ROWS>(kb, goff, row0, last, sp + wave * NPW * 1024);
+            dma16_to_lds_run_clamped<C::ROW, C::BLK_ROWS>(vb, goff, row0, last, sp + C::KT_BYTES + wave * NPW * 1024);
         }
     };
 
@@ -278,7 +267,7 @@ fwd_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
             W += g[r];
         }
         const bool bad = !(W < 0x1p80f);
-        if (__builtin_amdgcn_ballot_w64(bad) == 0) {
+        if (__builtin_expect(__builtin_amdgcn_ballot_w64(bad) == 0, 1)) {
             const float l = fast_log2(W) + 60.0f;        // log2 of the lane's prod (1 + e)
             float l_lo, l_hi;
             both_halves(l, l_lo, l_hi);
@@ -425,7 +414,13 @@ fwd_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
         const int Q0 = qb * BQ;
         const int q0 = Q0 + wave * 32;                   // this wave's first query row
         const bool wave_live = q0 < T;
+        const int kmax = min(T, Q0 + BQ) - 1;                // keys 0 .. kmax-1 are visible to some row
+        const int ntile = (kmax + C::TK - 1) / C::TK;
+        const int ndiag = min(ntile, ntile - Q0 / C::TK);    // leading tiles that touch the diagonal band
         if (part > sh.part0) barrier_nofence();             // everyone is done with the stages of the first block
+        // iteration `it` handles tile ntile-1-it, staged in buffer it % NS.  The first tile and Q are
+        // fetched together: one memory latency in front of a block, not two.
+        if (ntile > 0) stage_tile(ntile - 1, 0);
         {
             const int jq = min(q0 + n, T - 1);
             const u32x4* src = reinterpret_cast<const u32x4*>(Qg + (long)jq * D + 8 * hh);
@@ -433,7 +428,7 @@ fwd_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
             for (int s = 0; s < D / 16; ++s) qf[s] = __builtin_bit_cast(bf16x8, src[2 * s]);
         }
         // Wait for the Q loads (and the first block's stores) here, once: the staging
-        // loads below are issued behind the compiler's back, and a wait for "all my
+        // loads are issued behind the compiler's back, and a wait for "all my
         // loads" placed inside the loop would also wait for those.
 #pragma unroll
         for (int s = 0; s < D / 16; ++s) asm volatile("" :: "v"(qf[s]));
@@ -445,21 +440,13 @@ fwd_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
         a = 0.0f;
 
         // ---- the sweep over 64-key tiles, from the diagonal down to key 0
-        const int kmax = min(T, Q0 + BQ) - 1;                // keys 0 .. kmax-1 are visible to some row
-        const int ntile = (kmax + C::TK - 1) / C::TK;
-        const int ndiag = min(ntile, ntile - Q0 / C::TK);    // leading tiles that touch the diagonal band
-
-        // iteration `it` handles tile ntile-1-it, staged in buffer it % NS.  Past the end
-        // tile 0 is loaded again into a buffer nobody reads, which keeps the number of
-        // outstanding loads per iteration constant.
-        stage_tile(max(ntile - 1, 0), 0);
         auto begin_iter = [&](int it) __attribute__((always_inline)) {
             dma_wait<0>();                                   // this wave's share of tile `it` has landed
             // ... everyone's has, and tile it-1 is no longer read.  The waves' exhaustion flags go
             // through LDS here: their writes must have completed first, or the waves of a
             // workgroup could disagree about leaving the loop.
             barrier_lds();
-            stage_tile(max(ntile - 2 - it, 0), (it + 1) % NS);
+            if (it + 1 < ntile) stage_tile(ntile - 2 - it, (it + 1) % NS);
             return (uint32_t)((it % NS) * C::STAGE);
         };
         int it = 0;
@@ -500,7 +487,7 @@ fwd_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
                 atomicAdd(&tile_counts[1], (unsigned long long)ntile);     // tiles of the full sweep
             }
         }
-        dma_wait<0>();                                       // the trailing re-load
+        dma_wait<0>();                                       // a tile staged before the sweep stopped
 
         // ---- store.  oacc[b][r] is query row 8*(r/4) + 4*hh + r%4, column 32b + n.
         if (wave_live) {
@@ -557,7 +544,7 @@ hipError_t launch_one(const uint16_t* q, const uint16_t* k, const uint16_t* v, c
     const ShareRule sr = share_rule(BH, nqb);
     if (sr.grid > 0x7fffffffL) return hipErrorInvalidValue;
     hipLaunchKernelGGL((fwd_bf16_kernel<D, WRITE_M, RB, VL, TRI>), dim3((unsigned)sr.grid), dim3(64 * NW), 0, stream,
-                       q, k, v, rb, o, m, T, BH, H, G, nqb, enough, tile_counts, cu, Ttot, sr.spread, sr.single);
+                       q, k, v, rb, o, m, T, BH, H, G, nqb, enough, tile_counts, cu, Ttot, sr.mode, sr.single);
     return hipGetLastError();
 }
 

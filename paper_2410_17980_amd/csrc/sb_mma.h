@@ -34,42 +34,45 @@ __device__ __forceinline__ float sp2(float x)
 constexpr float CARRY_EXHAUSTED = 160.0f;
 
 // Which blocks a workgroup works on.  A head's n row blocks form (n+1)/2 pairs (p, n-1-p) of equal
-// causal cost.  Workgroup ids go round the 8 XCDs.  A head's pairs are cut into 2^spread runs of
-// neighbours, each run on one XCD: neighbours sweep the same tiles at about the same time and share
-// them in that XCD's L2, and how much work a head is (how far its weights reach) spreads over the
-// XCDs.  With `single` the two blocks of a pair are workgroups of their own, the longer ones first.
+// causal cost; how much work a head is depends on how far its weights reach.  Workgroup ids go
+// round the 8 XCDs, each with an L2 of its own, in which neighbouring pairs of a head, which sweep
+// the same tiles at about the same time, can share them.
 struct Share {
-    long bh;                  // head
+    int bh;                   // head
     int p;                    // pair
     int part0, part1;         // parts of it to do: 0 = the longer block, 1 = the shorter
 };
-__host__ __device__ __forceinline__ int share_run(int npair, int spread) { return (npair + (1 << spread) - 1) >> spread; }
-// Measured on heads of which a third reach far (bf16 forward, B1 H32 T16384 d128 / B1 H24 T16384 d64):
-// one XCD a head 1102 / 660 us, all eight 1001 / 526 us; where every head reaches far the shared
-// L2 is worth more, 2318 against 2371 us, and with many short heads too (B8 H16 T4096 d128: 367
-// against 376 us, all far 641 against 682 us).  So a head spreads over the XCDs where its runs
-// are still 4 pairs long, or where there are so few heads that one XCD more or less of the costly
-// ones decides (B1 H24 Hkv8 T4096 d64: 91 -> 73 us).  Blocks go single where every one of them
-// gets a CU to itself (B1 H32 T1024 d128: 33 -> 27 us); beyond that pairs are faster, since they
+enum ShareMode { HEAD_PER_XCD, RUNS, ROUND_ROBIN };
+// RUNS: a head's pairs in 8 runs of neighbours, one per XCD.  Measured on heads of which a third
+// reach far (bf16 forward, B1 H32 T16384 d128 / B1 H24 T16384 d64): one XCD a head 1102 / 660 us,
+// runs 1001 / 526 us, since no XCD gets more of the costly heads than another.  Where every head
+// reaches far the shared L2 is worth more, 2318 against 2371 us, and with many shorter heads too
+// (B8 H16 T4096 d128: 367 against 376 us, all far 641 against 682 us): so runs from 4 pairs up.
+// ROUND_ROBIN: few heads of few pairs, pair after pair; an even load is all that counts (B1 H24 Hkv8
+// T4096 d64, one XCD a head: 91 us, pairs spread: 73 us).
+// single: the two blocks of a pair are workgroups of their own, the longer ones first, where every
+// block gets a CU to itself (B1 H32 T1024 d128: 33 -> 27 us).  Beyond that pairs are faster: they
 // load the CUs evenly (B1 H24 Hkv8 T4096 d64: 73 us in pairs, 89 us single).
 struct ShareRule {
-    int spread, single;
+    int mode, single;
     long grid;
 };
 inline ShareRule share_rule(long heads, int nblk)
 {
     const int npair = (nblk + 1) / 2;
     ShareRule r;
-    r.spread = npair >= 32 || heads < 64 ? 3 : 0;
+    r.mode = npair >= 32 ? RUNS : heads < 64 ? ROUND_ROBIN : HEAD_PER_XCD;
     r.single = heads * nblk <= 256;
-    r.grid = 8L * (((heads << r.spread) + 7) / 8) * share_run(npair, r.spread) * (1 + r.single);
+    r.grid = (r.mode == RUNS ? 8L * heads * ((npair + 7) / 8) : r.mode == ROUND_ROBIN ? heads * npair
+              : 8L * ((heads + 7) / 8) * npair) * (1 + r.single);
     return r;
 }
 // false: nothing to do
-__device__ __forceinline__ bool share_of(Share& sh, int wg, long heads, int npair, int spread, int single)
+__device__ __forceinline__ bool share_of(Share& sh, int wg, int heads, int npair, int mode, int single)
 {
-    const int run = share_run(npair, spread), per = run << single;
-    const int slot = wg >> 3;
+    const int run = mode == RUNS ? (npair + 7) >> 3 : npair;
+    const int per = run << single;
+    const int slot = mode == ROUND_ROBIN ? wg : wg >> 3;
     const int s = slot / per;
     int i = slot - s * per;
     sh.part0 = 0;
@@ -79,10 +82,15 @@ __device__ __forceinline__ bool share_of(Share& sh, int wg, long heads, int npai
         sh.part1 = sh.part0 + 1;
         i -= sh.part0 ? run : 0;
     }
-    const long u = 8L * s + ((wg + (((unsigned)s * 0x9E3779B1u) >> 29)) & 7);
-    sh.bh = u >> spread;
-    sh.p = (int)(u & ((1 << spread) - 1)) * run + i;
-    return sh.bh < heads && sh.p < npair;
+    const int x = (wg + (((unsigned)s * 0x9E3779B1u) >> 29)) & 7;     // XCDs in another order for every s
+    sh.bh = mode == HEAD_PER_XCD ? 8 * s + x : s;
+    sh.p = i;
+    if (mode == RUNS) {
+        const int start = (x * npair) >> 3;
+        if (i >= (((x + 1) * npair) >> 3) - start) return false;
+        sh.p += start;
+    }
+    return sh.bh < heads;
 }
 
 // sum of log2(1 + 2^(c2 s_r)) over a lane's 16 logits: one product of the (1 + e_r) from 2^-60 on,
@@ -97,7 +105,7 @@ __device__ __forceinline__ float sp2_total(const f32x16& s, float c2, int n, int
         if (MASK) e = (16 * hh + r < n) ? e : 0.0f;
         W = __builtin_fmaf(W, e, W);
     }
-    if (__builtin_amdgcn_ballot_w64(!(W < INFINITY)) == 0) return fast_log2(W) + 60.0f;
+    if (__builtin_expect(__builtin_amdgcn_ballot_w64(!(W < INFINITY)) == 0, 1)) return fast_log2(W) + 60.0f;
     float l = 0.0f;
 #pragma unroll
     for (int r = 0; r < 16; ++r) l += !MASK || 16 * hh + r < n ? sp2(s[r] * c2) : 0.0f;
@@ -191,25 +199,7 @@ __device__ __forceinline__ bf16x8 tr_pair_at(uint32_t a_lo, uint32_t a_hi)
     return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
 }
 
-// Direct global -> LDS copy of 16 bytes per lane (global_load_lds_dwordx4): lane l
-// of the wave writes LDS bytes [lds_base + 16 l, +16) with the 16 bytes at its own
-// global address; lds_base must be wave-uniform.  Issued through inline assembly so
-// that the compiler's wait-count pass does not see an LDS write it would guard
-// every later LDS read against; the caller orders it with dma_wait<N>() + barrier.
-// Completion is counted in vmcnt, in issue order.  The LDS base travels in M0, which
-// is handed over as a register operand: the compiler writes it and knows it is in use.
-// The compiler does not see a memory instruction in here, so the wait states it would put
-// in are written out: one between a scalar write of M0 and the load, five between a vector
-// instruction's write of a scalar register (v_readfirstlane, v_readlane of a spilled one)
-// and a memory instruction that takes its base from it.
-__device__ __forceinline__ void dma16_to_lds(const void* gptr, const char* lds_base)
-{
-    const uint32_t lds = __builtin_amdgcn_readfirstlane(lds_offset(lds_base));
-    asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %1, off"
-                 :: "{m0}"(lds), "v"(gptr) : "memory");
-}
-
-// the wave-uniform base of the forms below, in scalar registers
+// a wave-uniform base in scalar registers
 __device__ __forceinline__ uint64_t scalar_base(const void* gbase)
 {
     const uint64_t b = (uint64_t)(uintptr_t)gbase;
@@ -218,7 +208,17 @@ __device__ __forceinline__ uint64_t scalar_base(const void* gbase)
     return ((uint64_t)hi << 32) | lo;
 }
 
-// same, with the global address given as a wave-uniform base plus a per-lane byte offset
+// Direct global -> LDS copy of 16 bytes per lane (global_load_lds_dwordx4): lane l
+// of the wave writes LDS bytes [lds_base + 16 l, +16) with the 16 bytes at its own
+// global address, a wave-uniform base plus a byte offset per lane; lds_base must be
+// wave-uniform.  Issued through inline assembly so that the compiler's wait-count pass
+// does not see an LDS write it would guard every later LDS read against; the caller orders it with dma_wait<N>() + barrier.
+// Completion is counted in vmcnt, in issue order.  The LDS base travels in M0, which
+// is handed over as a register operand: the compiler writes it and knows it is in use.
+// The compiler does not see a memory instruction in here, so the wait states it would put
+// in are written out: one between a scalar write of M0 and the load, five between a vector
+// instruction's write of a scalar register (v_readfirstlane, v_readlane of a spilled one)
+// and a memory instruction that takes its base from it.
 __device__ __forceinline__ void dma16_to_lds_saddr(const void* gbase, int lane_off, const char* lds_base)
 {
     const uint32_t lds = __builtin_amdgcn_readfirstlane(lds_offset(lds_base));
@@ -253,6 +253,17 @@ __device__ __forceinline__ int waves_done(const int* flags)
 {
     const u32x4 f = lds_load16(lds_offset(reinterpret_cast<const char*>(flags)));
     return __builtin_amdgcn_readfirstlane((int)(f[0] & f[1] & f[2] & f[3]));
+}
+
+// The same where the source has fewer rows than a tile: lanes whose tile row row0 + i*STEP lies beyond
+// `last` fetch row `last` instead.
+template <int ROW, int STEP, int N>
+__device__ __forceinline__ void dma16_to_lds_run_clamped(const void* gbase, const int (&off)[N], int row0, int last, const char* lds_base)
+{
+    int o[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) o[i] = off[i] - max(row0 + i * STEP - last, 0) * ROW;
+    dma16_to_lds_run(gbase, o, lds_base);
 }
 
 // wait until at most N of this wave's vector-memory operations are outstanding
