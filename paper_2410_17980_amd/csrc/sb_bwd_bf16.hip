@@ -31,9 +31,8 @@
 // pass first looks for that point from the diagonal, with the logits alone (find_start()),
 // starts its sweep there and leaves the tile in `first`, one per query block; the
 // key-stationary pass visits only the query blocks that reach its keys.
-// Both kernels give a workgroup two blocks, p and n-1-p, whose causal costs add up
-// to the same total for every p (or one, see share_of()), and stage their streamed tiles
-// with direct global->LDS loads, double buffered, one barrier per 64-row tile.  The 1/sqrt(d)
+// Which blocks a workgroup takes: share_of().  Streamed tiles are staged with direct
+// global->LDS loads, double buffered, one barrier per 64-row tile.  The 1/sqrt(d)
 // of dQ and dK is applied once, to the accumulators, on store.
 //
 // Register layout is the forward's: S^T = K Q^T and P^T = V dO^T with the
@@ -257,18 +256,15 @@ bwd_dq_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
               const float* __restrict__ m,
               const uint16_t* __restrict__ dout, float* __restrict__ dq,
               float* __restrict__ ca, float* __restrict__ cb, int* __restrict__ first,
-              int T_arg, int BH, int H, int G, int nqb_arg, int nt32, const int* __restrict__ cu, int Ttot,
-              int mode, int single)
+              int T_arg, int BH, int H, int G, int nqb_arg, int nt32, const int* __restrict__ cu, int Ttot)
 {
     using C = StageCfg<D>;
     __shared__ __attribute__((aligned(1024))) char smem[2 * C::STAGE];
     __shared__ __attribute__((aligned(16))) int s_done[2][NW];   // find_start(): per parity and wave
 
     const int wg = blockIdx.x;
-    Share sh;
-    if (!share_of(sh, wg, BH, (nqb_arg + 1) >> 1, mode, single)) return;
+    const Share sh = share_of(wg, BH, nqb_arg, false);
     const int bh = sh.bh;
-    const int pidx = sh.p;
     int T = T_arg, nqb = nqb_arg;
     long row0, kvrow0, cbase, cstride;      // first q / k row of this head; carries: base and strip stride
     int head;
@@ -279,7 +275,7 @@ bwd_dq_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
         T = min(min(cu[seq + 1], Ttot) - c0, T_arg);      // never past the packed rows or the stated maximum
         if (c0 < 0) return;
         nqb = (T + BQ - 1) / BQ;
-        if (pidx >= ((nqb + 1) >> 1)) return;
+        if (sh.i >= nqb) return;
         row0 = (long)head * Ttot + c0;
         kvrow0 = (long)(head / G) * Ttot + c0;
         cbase = (long)head * nt32 * Ttot + c0;
@@ -457,104 +453,100 @@ bwd_dq_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
         }
     };
 
-    for (int part = sh.part0; part < sh.part1; ++part) {
-        const int qb = part == 0 ? nqb - 1 - pidx : pidx;
-        if (part == 1 && 2 * pidx == nqb - 1) break;     // odd block count: the middle block is alone
-        const int Q0 = qb * BQ;
-        q0 = Q0 + wave * 32;
-        const bool wave_live = q0 < T;
-        const int jq = min(q0 + n, T - 1);
-        const int kmax = min(T, Q0 + BQ) - 1;            // keys 0 .. kmax-1 are visible to some row
-        const int ntile = (kmax + TK - 1) / TK;
-        const int nclean = min(ntile, Q0 / TK);          // tiles entirely left of the block's rows
-        const bool far = nclean >= 6;                    // long enough to look for a start
-        if (part > sh.part0) barrier_nofence();          // everyone is done with the stages of the block before
-        // what the block needs first, tiles and rows alike, is fetched together: one memory latency
-        if (far) stage_pair(Kg, T, ntile, 0);
-        else if (ntile > 0) stage_tile<D, true>(Kg, Vg, 0, T, smem, goff, wave, lane);
-        {
-            const u32x4* qs = reinterpret_cast<const u32x4*>(q + base + (long)jq * D + 8 * hh);
-            const u32x4* gs = reinterpret_cast<const u32x4*>(dout + base + (long)jq * D + 8 * hh);
+    const int qb = nqb - 1 - sh.i;
+    const int Q0 = qb * BQ;
+    q0 = Q0 + wave * 32;
+    const bool wave_live = q0 < T;
+    const int jq = min(q0 + n, T - 1);
+    const int kmax = min(T, Q0 + BQ) - 1;            // keys 0 .. kmax-1 are visible to some row
+    const int ntile = (kmax + TK - 1) / TK;
+    const int nclean = min(ntile, Q0 / TK);          // tiles entirely left of the block's rows
+    const bool far = nclean >= 6;                    // long enough to look for a start
+    // what the block needs first, tiles and rows alike, is fetched together: one memory latency
+    if (far) stage_pair(Kg, T, ntile, 0);
+    else if (ntile > 0) stage_tile<D, true>(Kg, Vg, 0, T, smem, goff, wave, lane);
+    {
+        const u32x4* qs = reinterpret_cast<const u32x4*>(q + base + (long)jq * D + 8 * hh);
+        const u32x4* gs = reinterpret_cast<const u32x4*>(dout + base + (long)jq * D + 8 * hh);
 #pragma unroll
-            for (int s = 0; s < D / 16; ++s) {
-                u32x4 a = qs[2 * s], g = gs[2 * s];
-                if (q0 + n >= T) g = u32x4{0u, 0u, 0u, 0u};   // rows past T contribute nothing
-                qf[s] = __builtin_bit_cast(bf16x8, a);
-                gf[s] = __builtin_bit_cast(bf16x8, g);
-            }
+        for (int s = 0; s < D / 16; ++s) {
+            u32x4 a = qs[2 * s], g = gs[2 * s];
+            if (q0 + n >= T) g = u32x4{0u, 0u, 0u, 0u};   // rows past T contribute nothing
+            qf[s] = __builtin_bit_cast(bf16x8, a);
+            gf[s] = __builtin_bit_cast(bf16x8, g);
         }
-        a2 = -m[row0 + jq] * SB_LOG2E;
-        bsum = 0.0f;
-        if constexpr (RB) {
-            // remainder bias (Appendix C): the unused stick exp(m) acts like one more weight
-            // in front of key 0, with "value" r_head: the cumulative sum of G starts at
-            // exp(m_j) (dO_j . r_head)
-            const u32x4* rs = reinterpret_cast<const u32x4*>(rb + head * D + 8 * hh);
-            float dot = 0.0f;
+    }
+    a2 = -m[row0 + jq] * SB_LOG2E;
+    bsum = 0.0f;
+    if constexpr (RB) {
+        // remainder bias (Appendix C): the unused stick exp(m) acts like one more weight
+        // in front of key 0, with "value" r_head: the cumulative sum of G starts at
+        // exp(m_j) (dO_j . r_head)
+        const u32x4* rs = reinterpret_cast<const u32x4*>(rb + head * D + 8 * hh);
+        float dot = 0.0f;
 #pragma unroll
-            for (int s = 0; s < D / 16; ++s) {
-                const bf16x8 rr = __builtin_bit_cast(bf16x8, rs[2 * s]);
+        for (int s = 0; s < D / 16; ++s) {
+            const bf16x8 rr = __builtin_bit_cast(bf16x8, rs[2 * s]);
 #pragma unroll
-                for (int e = 0; e < 8; ++e) dot += (float)gf[s][e] * (float)rr[e];
-            }
-            float d_lo, d_hi;
-            both_halves(dot, d_lo, d_hi);
-            bsum = fast_exp2(-a2) * (d_lo + d_hi);
+            for (int e = 0; e < 8; ++e) dot += (float)gf[s][e] * (float)rr[e];
         }
-        // wait for these loads (and the first block's stores) once: the staging loads of the sweep
-        // are counted in the same counter behind the compiler's back
+        float d_lo, d_hi;
+        both_halves(dot, d_lo, d_hi);
+        bsum = fast_exp2(-a2) * (d_lo + d_hi);
+    }
+    // wait for these loads once: the staging loads of the sweep
+    // are counted in the same counter behind the compiler's back
 #pragma unroll
-        for (int s = 0; s < D / 16; ++s) { asm volatile("" :: "v"(qf[s])); asm volatile("" :: "v"(gf[s])); }
-        asm volatile("" :: "v"(a2));
-        asm volatile("" :: "v"(bsum));
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    for (int s = 0; s < D / 16; ++s) { asm volatile("" :: "v"(qf[s])); asm volatile("" :: "v"(gf[s])); }
+    asm volatile("" :: "v"(a2));
+    asm volatile("" :: "v"(bsum));
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 #pragma unroll
-        for (int b = 0; b < D / 32; ++b)
+    for (int b = 0; b < D / 32; ++b)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) dqacc[b][r] = 0.0f;
+        for (int r = 0; r < 16; ++r) dqacc[b][r] = 0.0f;
 
-        // ---- sweep over 64-key tiles, left to right; iteration it handles tile it in buffer it & 1
-        int t0 = 0;
-        if (far) {
-            t0 = find_start(Kg, T, ntile, wave_live);
-            stage_tile<D, true>(Kg, Vg, t0, T, smem + (t0 & 1) * C::STAGE, goff, wave, lane);
-        }
-        if (tid == 0) first[(long)bh * nqb_arg + qb] = t0;
-        auto begin_iter = [&](int it) __attribute__((always_inline)) {
-            dma_wait<0>();                               // this wave's share of tile `it` has landed
-            barrier_nofence();                           // ... everyone's has, and tile it-1 is no longer read
-            if (it + 1 < ntile)
-                stage_tile<D, true>(Kg, Vg, it + 1, T, smem + ((it + 1) & 1) * C::STAGE, goff, wave, lane);
-            return smem0 + (it & 1) * C::STAGE;
-        };
-        int it = t0;
-        for (; it < nclean; ++it) {                      // fully visible tiles
-            const uint32_t sp = begin_iter(it);
-            subtile(bc<false>{}, sp, it * TK);
-            subtile(bc<false>{}, sp + 32 * C::ROW, it * TK + 32);
-        }
-        for (; it < ntile; ++it) {                       // tiles that touch the diagonal band
-            const uint32_t sp = begin_iter(it);
-            if (wave_live) {
-#pragma unroll
-                for (int u = 0; u < 2; ++u) {
-                    const int key0 = it * TK + 32 * u;
-                    if (key0 == q0) subtile(bc<true>{}, sp + u * 32 * C::ROW, key0);
-                    else if (key0 < q0) subtile(bc<false>{}, sp + u * 32 * C::ROW, key0);
-                }
-            }
-        }
-
-        // ---- dQ store: dqacc[b][r] is query row 8*(r/4) + 4*hh + r%4, column 32b + n
+    // ---- sweep over 64-key tiles, left to right; iteration it handles tile it in buffer it & 1
+    int t0 = 0;
+    if (far) {
+        t0 = find_start(Kg, T, ntile, wave_live);
+        stage_tile<D, true>(Kg, Vg, t0, T, smem + (t0 & 1) * C::STAGE, goff, wave, lane);
+    }
+    if (tid == 0) first[(long)bh * nqb_arg + qb] = t0;
+    auto begin_iter = [&](int it) __attribute__((always_inline)) {
+        dma_wait<0>();                               // this wave's share of tile `it` has landed
+        barrier_nofence();                           // ... everyone's has, and tile it-1 is no longer read
+        if (it + 1 < ntile)
+            stage_tile<D, true>(Kg, Vg, it + 1, T, smem + ((it + 1) & 1) * C::STAGE, goff, wave, lane);
+        return smem0 + (it & 1) * C::STAGE;
+    };
+    int it = t0;
+    for (; it < nclean; ++it) {                      // fully visible tiles
+        const uint32_t sp = begin_iter(it);
+        subtile(bc<false>{}, sp, it * TK);
+        subtile(bc<false>{}, sp + 32 * C::ROW, it * TK + 32);
+    }
+    for (; it < ntile; ++it) {                       // tiles that touch the diagonal band
+        const uint32_t sp = begin_iter(it);
         if (wave_live) {
-            float* dQg = dq + base;
 #pragma unroll
-            for (int b = 0; b < D / 32; ++b) {
+            for (int u = 0; u < 2; ++u) {
+                const int key0 = it * TK + 32 * u;
+                if (key0 == q0) subtile(bc<true>{}, sp + u * 32 * C::ROW, key0);
+                else if (key0 < q0) subtile(bc<false>{}, sp + u * 32 * C::ROW, key0);
+            }
+        }
+    }
+
+    // ---- dQ store: dqacc[b][r] is query row 8*(r/4) + 4*hh + r%4, column 32b + n
+    if (wave_live) {
+        float* dQg = dq + base;
 #pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int row = q0 + 8 * (r >> 2) + 4 * hh + (r & 3);
-                    if (row < T) dQg[(long)row * D + 32 * b + n] = dqacc[b][r] * scale;
-                }
+        for (int b = 0; b < D / 32; ++b) {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int row = q0 + 8 * (r >> 2) + 4 * hh + (r & 3);
+                if (row < T) dQg[(long)row * D + 32 * b + n] = dqacc[b][r] * scale;
             }
         }
     }
@@ -572,7 +564,7 @@ struct KvHead {
 };
 
 template <int D, bool VL>
-__device__ __forceinline__ bool kv_head(KvHead& kh, int bh, int pidx, int T_arg, int nkb_arg, int H, int G,
+__device__ __forceinline__ bool kv_head(KvHead& kh, int bh, int T_arg, int nkb_arg, int H, int G,
                                         int nt32, const int* __restrict__ cu, int Ttot)
 {
     const int Hkv = H / G;
@@ -583,7 +575,6 @@ __device__ __forceinline__ bool kv_head(KvHead& kh, int bh, int pidx, int T_arg,
         kh.T = min(min(cu[seq + 1], Ttot) - c0, T_arg);   // never past the packed rows or the stated maximum
         if (c0 < 0) return false;
         kh.nkb = (kh.T + BKW - 1) / BKW;
-        if (pidx >= ((kh.nkb + 1) >> 1)) return false;
         kh.base = ((long)hkv * Ttot + c0) * D;
         kh.qrow0 = (long)hkv * G * Ttot + c0;
         kh.qrow_step = Ttot;
@@ -639,8 +630,7 @@ bwd_dkv_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
                const uint16_t* __restrict__ v, const uint16_t* __restrict__ dout,
                const float* __restrict__ ca, const float* __restrict__ cb,
                float* __restrict__ dk, float* __restrict__ dv, const int* __restrict__ first,
-               int T_arg, int BH, int H, int G_arg, int nkb_arg, int nt32, const int* __restrict__ cu, int Ttot,
-               int mode, int single)
+               int T_arg, int BH, int H, int G_arg, int nkb_arg, int nt32, const int* __restrict__ cu, int Ttot)
 {
     using C = StageCfg<D>;
     using CK = DkvCfg<D>;
@@ -648,10 +638,8 @@ bwd_dkv_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     __shared__ __attribute__((aligned(1024))) char smem[CK::LDS_BYTES];
 
     const int wg = blockIdx.x;
-    Share sh;
-    if (!share_of(sh, wg, BH, (nkb_arg + 1) >> 1, mode, single)) return;
+    const Share sh = share_of(wg, BH, nkb_arg, false);
     const int bh = sh.bh;
-    const int pidx = sh.p;
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -661,7 +649,7 @@ bwd_dkv_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
 
     // bh counts kv heads here (BH = B * H / G of them)
     KvHead kh;
-    if (!kv_head<D, VL>(kh, bh, pidx, T_arg, nkb_arg, H, G, nt32, cu, Ttot)) return;
+    if (!kv_head<D, VL>(kh, bh, T_arg, nkb_arg, H, G, nt32, cu, Ttot) || sh.i >= kh.nkb) return;
     const int T = kh.T, nkb = kh.nkb;
     const long base = kh.base, qrow0 = kh.qrow0, qrow_step = kh.qrow_step;
     const long cbase = kh.cbase, cbase_step = kh.cbase_step, cstride = kh.cstride;
@@ -801,107 +789,103 @@ bwd_dkv_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
         mm2(gop, qop, at, zt);
     };
 
-    for (int part = sh.part0; part < sh.part1; ++part) {
-        const int kb = part == 0 ? pidx : nkb - 1 - pidx;    // small kb = most later queries = first
-        if (part == 1 && 2 * pidx == nkb - 1) break;
-        const int K0 = kb * BKW;
-        const int k0 = K0 + wave * 32;                       // this wave's 32 keys
-        const int kt32 = k0 >> 5;
-        const bool wave_live = k0 < T;
-        const int jt0 = K0 / TK;
-        float cn[2][2];                                      // [subtile][ca, cb] of the next tile
-        // the block's first tile of a head and its carries, which always reach these keys
-        auto first_tile = [&](int g) __attribute__((always_inline)) {
-            Qg = q + (qrow0 + g * qrow_step) * D;
-            Gg = dout + (qrow0 + g * qrow_step) * D;
-            cag = ca + cbase + g * cbase_step + kt32 * cstride;
-            cbg = cb + cbase + g * cbase_step + kt32 * cstride;
-            load_carries(cn, jt0, wave_live);
-            stage_tile<D, false>(Qg, Gg, jt0, T, smem, goff, wave, lane);
-        };
-        if (part > sh.part0) barrier_nofence();              // everyone is done with the stages of the block before
-        first_tile(0);                                       // fetched together with the stationary rows
-        {
-            const long kr = min(k0 + perm_row(n), T - 1);
-            const u32x4* ks = reinterpret_cast<const u32x4*>(k + base + kr * D + 8 * hh);
-            const u32x4* vs = reinterpret_cast<const u32x4*>(v + base + kr * D + 8 * hh);
+    const int kb = sh.i;                                 // small kb = most later queries = first
+    const int K0 = kb * BKW;
+    const int k0 = K0 + wave * 32;                       // this wave's 32 keys
+    const int kt32 = k0 >> 5;
+    const bool wave_live = k0 < T;
+    const int jt0 = K0 / TK;
+    float cn[2][2];                                      // [subtile][ca, cb] of the next tile
+    // the block's first tile of a head and its carries, which always reach these keys
+    auto first_tile = [&](int g) __attribute__((always_inline)) {
+        Qg = q + (qrow0 + g * qrow_step) * D;
+        Gg = dout + (qrow0 + g * qrow_step) * D;
+        cag = ca + cbase + g * cbase_step + kt32 * cstride;
+        cbg = cb + cbase + g * cbase_step + kt32 * cstride;
+        load_carries(cn, jt0, wave_live);
+        stage_tile<D, false>(Qg, Gg, jt0, T, smem, goff, wave, lane);
+    };
+    first_tile(0);                                       // fetched together with the stationary rows
+    {
+        const long kr = min(k0 + perm_row(n), T - 1);
+        const u32x4* ks = reinterpret_cast<const u32x4*>(k + base + kr * D + 8 * hh);
+        const u32x4* vs = reinterpret_cast<const u32x4*>(v + base + kr * D + 8 * hh);
 #pragma unroll
-            for (int s = 0; s < D / 16; ++s) {
-                kf[s] = __builtin_bit_cast(bf16x8, ks[2 * s]);
-                vf[s] = __builtin_bit_cast(bf16x8, vs[2 * s]);
-            }
+        for (int s = 0; s < D / 16; ++s) {
+            kf[s] = __builtin_bit_cast(bf16x8, ks[2 * s]);
+            vf[s] = __builtin_bit_cast(bf16x8, vs[2 * s]);
         }
+    }
 #pragma unroll
-        for (int s = 0; s < D / 16; ++s) { asm volatile("" :: "v"(kf[s])); asm volatile("" :: "v"(vf[s])); }
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    for (int s = 0; s < D / 16; ++s) { asm volatile("" :: "v"(kf[s])); asm volatile("" :: "v"(vf[s])); }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 #pragma unroll
-        for (int b = 0; b < D / 32; ++b)
+    for (int b = 0; b < D / 32; ++b)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) { dkacc[b][r] = 0.0f; dvacc[b][r] = 0.0f; }
-        // the query heads of the group one after the other, into the same accumulators
-        for (int g = 0; g < G; ++g) {
-        if (g > 0) {
-            barrier_nofence();                               // everyone is done with the stages of the head before
-            first_tile(g);
-        }
+        for (int r = 0; r < 16; ++r) { dkacc[b][r] = 0.0f; dvacc[b][r] = 0.0f; }
+    // the query heads of the group one after the other, into the same accumulators
+    for (int g = 0; g < G; ++g) {
+    if (g > 0) {
+        barrier_nofence();                               // everyone is done with the stages of the head before
+        first_tile(g);
+    }
 
-        // ---- sweep over 64-row query tiles, from the block's diagonal to the end;
-        // iteration it handles tile jt0 + it in buffer it & 1.  The carries of a tile are
-        // fetched one iteration ahead, and BEFORE the staging loads of that iteration are
-        // issued: vector memory operations complete in order, so a wait for a carry
-        // issued after the staging loads would wait for those as well.
-        const int* const fg = first + (kh.qhead0 + g) * nkb_arg;
-        const Reach reach = reach_of(fg, kb, nkb, lane);
-        const int ntile = min((T + TK - 1) / TK, reach.end) - jt0;
-        const int ndiag = min(ntile, BKW / TK);              // tiles that touch the diagonal band
-        float cc[2][2];
-        auto begin_iter = [&](int it) __attribute__((always_inline)) {
-            dma_wait<0>();
-            barrier_nofence();
+    // ---- sweep over 64-row query tiles, from the block's diagonal to the end;
+    // iteration it handles tile jt0 + it in buffer it & 1.  The carries of a tile are
+    // fetched one iteration ahead, and BEFORE the staging loads of that iteration are
+    // issued: vector memory operations complete in order, so a wait for a carry
+    // issued after the staging loads would wait for those as well.
+    const int* const fg = first + (kh.qhead0 + g) * nkb_arg;
+    const Reach reach = reach_of(fg, kb, nkb, lane);
+    const int ntile = min((T + TK - 1) / TK, reach.end) - jt0;
+    const int ndiag = min(ntile, BKW / TK);              // tiles that touch the diagonal band
+    float cc[2][2];
+    auto begin_iter = [&](int it) __attribute__((always_inline)) {
+        dma_wait<0>();
+        barrier_nofence();
 #pragma unroll
-            for (int u = 0; u < 2; ++u) { cc[u][0] = cn[u][0]; cc[u][1] = cn[u][1]; }
-            if (it + 1 < ntile) {
-                const int jt = jt0 + it + 1;
-                load_carries(cn, jt, wave_live && (jt < reach.sure || fg[jt >> 1] <= kt32 >> 1));
-                stage_tile<D, false>(Qg, Gg, jt, T, smem + ((it + 1) & 1) * C::STAGE, goff, wave, lane);
-            }
-            return (const char*)(smem + (it & 1) * C::STAGE);
-        };
-        int it = 0;
-        for (; it < ndiag; ++it) {
-            const char* sp = begin_iter(it);
-            if (wave_live) {
-#pragma unroll
-                for (int u = 0; u < 2; ++u) {
-                    const int j0 = (jt0 + it) * TK + 32 * u;
-                    if (j0 == k0) subtile(bc<true>{}, sp + u * 32 * C::ROW, cc[u][0], cc[u][1]);
-                    else if (j0 > k0 && j0 < T) subtile(bc<false>{}, sp + u * 32 * C::ROW, cc[u][0], cc[u][1]);
-                }
-            }
+        for (int u = 0; u < 2; ++u) { cc[u][0] = cn[u][0]; cc[u][1] = cn[u][1]; }
+        if (it + 1 < ntile) {
+            const int jt = jt0 + it + 1;
+            load_carries(cn, jt, wave_live && (jt < reach.sure || fg[jt >> 1] <= kt32 >> 1));
+            stage_tile<D, false>(Qg, Gg, jt, T, smem + ((it + 1) & 1) * C::STAGE, goff, wave, lane);
         }
-        for (; it < ntile; ++it) {
-            const char* sp = begin_iter(it);
-            if (wave_live) {
-                const int j0 = (jt0 + it) * TK;
-                subtile(bc<false>{}, sp, cc[0][0], cc[0][1]);
-                if (j0 + 32 < T) subtile(bc<false>{}, sp + 32 * C::ROW, cc[1][0], cc[1][1]);
-            }
-        }
-        }
-
-        // ---- store: acc[b][r] is key row k0 + 8*(r/4) + 4*hh + r%4, column 32b + n
+        return (const char*)(smem + (it & 1) * C::STAGE);
+    };
+    int it = 0;
+    for (; it < ndiag; ++it) {
+        const char* sp = begin_iter(it);
         if (wave_live) {
-            float* dKg = dk + base;
-            float* dVg = dv + base;
 #pragma unroll
-            for (int b = 0; b < D / 32; ++b) {
+            for (int u = 0; u < 2; ++u) {
+                const int j0 = (jt0 + it) * TK + 32 * u;
+                if (j0 == k0) subtile(bc<true>{}, sp + u * 32 * C::ROW, cc[u][0], cc[u][1]);
+                else if (j0 > k0 && j0 < T) subtile(bc<false>{}, sp + u * 32 * C::ROW, cc[u][0], cc[u][1]);
+            }
+        }
+    }
+    for (; it < ntile; ++it) {
+        const char* sp = begin_iter(it);
+        if (wave_live) {
+            const int j0 = (jt0 + it) * TK;
+            subtile(bc<false>{}, sp, cc[0][0], cc[0][1]);
+            if (j0 + 32 < T) subtile(bc<false>{}, sp + 32 * C::ROW, cc[1][0], cc[1][1]);
+        }
+    }
+    }
+
+    // ---- store: acc[b][r] is key row k0 + 8*(r/4) + 4*hh + r%4, column 32b + n
+    if (wave_live) {
+        float* dKg = dk + base;
+        float* dVg = dv + base;
 #pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int key = k0 + 8 * (r >> 2) + 4 * hh + (r & 3);
-                    if (key < T) {
-                        dKg[(long)key * D + 32 * b + n] = dkacc[b][r] * scale;
-                        dVg[(long)key * D + 32 * b + n] = dvacc[b][r];
-                    }
+        for (int b = 0; b < D / 32; ++b) {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int key = k0 + 8 * (r >> 2) + 4 * hh + (r & 3);
+                if (key < T) {
+                    dKg[(long)key * D + 32 * b + n] = dkacc[b][r] * scale;
+                    dVg[(long)key * D + 32 * b + n] = dvacc[b][r];
                 }
             }
         }
@@ -954,8 +938,7 @@ bwd_dkv_pair_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
                     const uint16_t* __restrict__ v, const uint16_t* __restrict__ dout,
                     const float* __restrict__ ca, const float* __restrict__ cb,
                     float* __restrict__ dk, float* __restrict__ dv, const int* __restrict__ first,
-                    int T_arg, int BH, int H, int G_arg, int nkb_arg, int nt32, const int* __restrict__ cu, int Ttot,
-               int mode, int single)
+                    int T_arg, int BH, int H, int G_arg, int nkb_arg, int nt32, const int* __restrict__ cu, int Ttot, int pairs)
 {
     using C = StageCfg<D>;
     using CK = Dkv3Cfg<D>;
@@ -964,10 +947,9 @@ bwd_dkv_pair_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
     __shared__ __attribute__((aligned(1024))) char smem[CK::LDS_BYTES];
 
     const int wg = blockIdx.x;
-    Share sh;
-    if (!share_of(sh, wg, BH, (nkb_arg + 1) >> 1, mode, single)) return;
+    const Share sh = share_of(wg, BH, nkb_arg, pairs);
     const int bh = sh.bh;
-    const int pidx = sh.p;
+    if (bh >= BH) return;
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -978,7 +960,7 @@ bwd_dkv_pair_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
     const int gg = lane >> 4, li = lane & 15;
 
     KvHead kh;
-    if (!kv_head<D, VL>(kh, bh, pidx, T_arg, nkb_arg, H, G, nt32, cu, Ttot)) return;
+    if (!kv_head<D, VL>(kh, bh, T_arg, nkb_arg, H, G, nt32, cu, Ttot) || sh.i >= (pairs ? (kh.nkb + 1) >> 1 : kh.nkb)) return;
     const int T = kh.T, nkb = kh.nkb;
     const long base = kh.base, qrow0 = kh.qrow0, qrow_step = kh.qrow_step;
     const long cbase = kh.cbase, cbase_step = kh.cbase_step, cstride = kh.cstride;
@@ -1166,9 +1148,9 @@ bwd_dkv_pair_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
         __builtin_amdgcn_sched_barrier(0);
     };
 
-    for (int part = sh.part0; part < sh.part1; ++part) {
-        const int kb = part == 0 ? pidx : nkb - 1 - pidx;    // small kb = most later queries = first
-        if (part == 1 && 2 * pidx == nkb - 1) break;
+    for (int part = 0; part <= pairs; ++part) {
+        const int kb = part == 0 ? sh.i : nkb - 1 - sh.i;    // small kb = most later queries = first
+        if (part == 1 && 2 * sh.i == nkb - 1) break;         // odd block count: the middle block is alone
         const int K0 = kb * BKW;
         const int k0 = K0 + strip * 32;                      // the strip's 32 keys
         const int kt32 = k0 >> 5;
@@ -1191,7 +1173,7 @@ bwd_dkv_pair_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
             load_carries(jt0, live);
             stage(jt0, smem);
         };
-        if (part > sh.part0) barrier_lds();                  // everyone is done with the LDS of the block before
+        if (part > 0) barrier_lds();                  // everyone is done with the LDS of the block before
         first_tile(0);                                       // fetched together with the stationary rows
         {
             const long kr = min(k0 + perm_row(n), T - 1);
@@ -1402,27 +1384,25 @@ hipError_t launch_one(const uint16_t* q, const uint16_t* k, const uint16_t* v, c
     int* first = reinterpret_cast<int*>(cb + ncarry);
     float* part = reinterpret_cast<float*>(first + (long)BH * (nqb + nkb));
     const int nchunk = (T + DR_ROWS - 1) / DR_ROWS;
-    const ShareRule rq = share_rule(BH, nqb), rk = share_rule(BHkv, nkb);
+    const bool pairs = D == 128 && BHkv >= 64;              // see share_of()
+    const long gq = share_grid(BH, nqb, false), gk = share_grid(BHkv, nkb, pairs);
     // checked before the first launch, so that an error leaves nothing enqueued
-    if (rq.grid > 0x7fffffffL || rk.grid > 0x7fffffffL || nchunk * (long)BH > 0x7fffffffL) return hipErrorInvalidValue;
+    if (gq > 0x7fffffffL || gk > 0x7fffffffL || nchunk * (long)BH > 0x7fffffffL) return hipErrorInvalidValue;
     hipError_t e = hipSuccess;
-#define SB_DQ(RBV)                                                                                              \
-    hipLaunchKernelGGL((bwd_dq_kernel<D, RBV, VL>), dim3((unsigned)rq.grid), dim3(NTHREADS), 0, stream,         \
-                       q, k, v, rb, m, dout, dq, ca, cb, first, T, BH, H, G, nqb, nt32, cu, Ttot,               \
-                       rq.mode, rq.single);                                                                   \
+#define SB_DQ(RBV)                                                                                             \
+    hipLaunchKernelGGL((bwd_dq_kernel<D, RBV, VL>), dim3((unsigned)gq), dim3(NTHREADS), 0, stream,             \
+                       q, k, v, rb, m, dout, dq, ca, cb, first, T, BH, H, G, nqb, nt32, cu, Ttot);             \
     if ((e = hipGetLastError()) != hipSuccess) return e
 // d = 128 takes the paired-wave kernel (two waves per SIMD instead of one); smaller head
 // dimensions leave room for two workgroups of the one-wave-per-strip kernel per CU, which
 // is faster there (measured).
-#define SB_DKV(GQAV)                                                                                            \
-    if constexpr (D == 128)                                                                                     \
-        hipLaunchKernelGGL((bwd_dkv_pair_kernel<D, GQAV, VL>), dim3((unsigned)rk.grid), dim3(NTHREADS2), 0,     \
-                           stream, q, k, v, dout, ca, cb, dk, dv, first, T, BHkv, H, G, nkb, nt32, cu, Ttot,    \
-                           rk.mode, rk.single);                                                               \
-    else                                                                                                        \
-        hipLaunchKernelGGL((bwd_dkv_kernel<D, GQAV, VL>), dim3((unsigned)rk.grid), dim3(NTHREADS), 0,           \
-                           stream, q, k, v, dout, ca, cb, dk, dv, first, T, BHkv, H, G, nkb, nt32, cu, Ttot,    \
-                           rk.mode, rk.single);                                                               \
+#define SB_DKV(GQAV)                                                                                           \
+    if constexpr (D == 128)                                                                                    \
+        hipLaunchKernelGGL((bwd_dkv_pair_kernel<D, GQAV, VL>), dim3((unsigned)gk), dim3(NTHREADS2), 0,         \
+                           stream, q, k, v, dout, ca, cb, dk, dv, first, T, BHkv, H, G, nkb, nt32, cu, Ttot, pairs); \
+    else                                                                                                       \
+        hipLaunchKernelGGL((bwd_dkv_kernel<D, GQAV, VL>), dim3((unsigned)gk), dim3(NTHREADS), 0,               \
+                           stream, q, k, v, dout, ca, cb, dk, dv, first, T, BHkv, H, G, nkb, nt32, cu, Ttot);  \
     if ((e = hipGetLastError()) != hipSuccess) return e
     if (passes & 1) {
         if (rb) { SB_DQ(true); }

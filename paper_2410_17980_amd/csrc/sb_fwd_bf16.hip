@@ -2,11 +2,9 @@
 //
 // Work split.  A query block is 128 rows of one (batch, head); each of the 4
 // wavefronts of a workgroup owns 32 of them and keeps their Q fragments in
-// registers.  A workgroup processes TWO query blocks one after the other, block p
-// and block nqb-1-p of the same head: with causal skipping their costs add up to
-// the same total for every p, so all workgroups of a head run equally long (which
-// workgroup does what: share_of()).  Two workgroups share a CU at d = 128 (two
-// wavefronts per SIMD), three at d = 64, four at d = 32.
+// registers.  Every workgroup one block, the longest first (share_of()).  Two
+// workgroups share a CU at d = 128 (two wavefronts per SIMD), three at d = 64, four
+// at d = 32.
 //
 // Keys are swept in 64-row tiles (two 32-row subtiles each) from the diagonal
 // towards key 0, the order Algorithm 1 prescribes: the weight of key i needs the
@@ -75,7 +73,7 @@ template <int I> using ic = std::integral_constant<int, I>;
 
 // VL: packed variable-length batch.  The tensors are [H][Ttot][D] ([H/G][Ttot][D] for k, v),
 // sequence s occupies rows cu[s] .. cu[s+1]-1, BH counts (sequence, head) pairs and T_arg,
-// nqb_arg describe the longest sequence (they size the grid); a workgroup whose pair of
+// nqb_arg describe the longest sequence (they size the grid); a workgroup whose
 // blocks lies beyond its own sequence's end returns at once.
 // TRI: measurement variant of the element-wise path.  The in-tile reverse cumulative sum of
 // Algorithm 1 is taken on the matrix pipe, as a product with a triangular matrix of ones,
@@ -86,8 +84,7 @@ fwd_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
                 const uint16_t* __restrict__ v, const uint16_t* __restrict__ rb,
                 uint16_t* __restrict__ o, float* __restrict__ m,
                 int T_arg, int BH, int H, int G, int nqb_arg, float enough,
-                unsigned long long* __restrict__ tile_counts, const int* __restrict__ cu, int Ttot,
-                int mode, int single)
+                unsigned long long* __restrict__ tile_counts, const int* __restrict__ cu, int Ttot)
 {
     using C = FwdCfg<D>;
     constexpr int NPW = C::NPW;
@@ -95,13 +92,10 @@ fwd_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     __shared__ __attribute__((aligned(16))) int s_done[NW];         // per wave: all rows exhausted
     __shared__ __attribute__((aligned(16))) char s_tri[TRI ? 2 * 64 * 16 : 16];   // triangular operand, per lane
 
-    // workgroup -> (head, pair of query blocks)
+    // workgroup -> (head, query block)
     const int wg = blockIdx.x;
-    const int npair = (nqb_arg + 1) >> 1;
-    Share sh;
-    if (!share_of(sh, wg, BH, npair, mode, single)) return;
+    const Share sh = share_of(wg, BH, nqb_arg, false);
     const int bh = sh.bh;
-    const int pidx = sh.p;
     int T = T_arg, nqb = nqb_arg;
     long row0, kvrow0;                                  // first row of this head's q / k rows
     int head;
@@ -112,7 +106,7 @@ fwd_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
         T = min(min(cu[seq + 1], Ttot) - c0, T_arg);      // never past the packed rows or the stated maximum
         if (c0 < 0) return;
         nqb = (T + BQ - 1) / BQ;
-        if (pidx >= ((nqb + 1) >> 1)) return;
+        if (sh.i >= nqb) return;
         row0 = (long)head * Ttot + c0;
         kvrow0 = (long)(head / G) * Ttot + c0;
     } else {
@@ -408,123 +402,118 @@ fwd_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
         a += l_lo + l_hi;
     };
 
-    for (int part = sh.part0; part < sh.part1; ++part) {
-        const int qb = part == 0 ? nqb - 1 - pidx : pidx;
-        if (part == 1 && 2 * pidx == nqb - 1) break;     // odd block count: the middle block is alone
-        const int Q0 = qb * BQ;
-        const int q0 = Q0 + wave * 32;                   // this wave's first query row
-        const bool wave_live = q0 < T;
-        const int kmax = min(T, Q0 + BQ) - 1;                // keys 0 .. kmax-1 are visible to some row
-        const int ntile = (kmax + C::TK - 1) / C::TK;
-        const int ndiag = min(ntile, ntile - Q0 / C::TK);    // leading tiles that touch the diagonal band
-        if (part > sh.part0) barrier_nofence();             // everyone is done with the stages of the first block
-        // iteration `it` handles tile ntile-1-it, staged in buffer it % NS.  The first tile and Q are
-        // fetched together: one memory latency in front of a block, not two.
-        if (ntile > 0) stage_tile(ntile - 1, 0);
-        {
-            const int jq = min(q0 + n, T - 1);
-            const u32x4* src = reinterpret_cast<const u32x4*>(Qg + (long)jq * D + 8 * hh);
+    const int Q0 = (nqb - 1 - sh.i) * BQ;
+    const int q0 = Q0 + wave * 32;                   // this wave's first query row
+    const bool wave_live = q0 < T;
+    const int kmax = min(T, Q0 + BQ) - 1;                // keys 0 .. kmax-1 are visible to some row
+    const int ntile = (kmax + C::TK - 1) / C::TK;
+    const int ndiag = min(ntile, ntile - Q0 / C::TK);    // leading tiles that touch the diagonal band
+    // iteration `it` handles tile ntile-1-it, staged in buffer it % NS.  The first tile and Q are
+    // fetched together: one memory latency in front of a block, not two.
+    if (ntile > 0) stage_tile(ntile - 1, 0);
+    {
+        const int jq = min(q0 + n, T - 1);
+        const u32x4* src = reinterpret_cast<const u32x4*>(Qg + (long)jq * D + 8 * hh);
 #pragma unroll
-            for (int s = 0; s < D / 16; ++s) qf[s] = __builtin_bit_cast(bf16x8, src[2 * s]);
-        }
-        // Wait for the Q loads (and the first block's stores) here, once: the staging
-        // loads are issued behind the compiler's back, and a wait for "all my
-        // loads" placed inside the loop would also wait for those.
+        for (int s = 0; s < D / 16; ++s) qf[s] = __builtin_bit_cast(bf16x8, src[2 * s]);
+    }
+    // Wait for the Q loads here, once: the staging
+    // loads are issued behind the compiler's back, and a wait for "all my
+    // loads" placed inside the loop would also wait for those.
 #pragma unroll
-        for (int s = 0; s < D / 16; ++s) asm volatile("" :: "v"(qf[s]));
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    for (int s = 0; s < D / 16; ++s) asm volatile("" :: "v"(qf[s]));
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 #pragma unroll
-        for (int b = 0; b < D / 32; ++b)
+    for (int b = 0; b < D / 32; ++b)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) oacc[b][r] = 0.0f;
-        a = 0.0f;
+        for (int r = 0; r < 16; ++r) oacc[b][r] = 0.0f;
+    a = 0.0f;
 
-        // ---- the sweep over 64-key tiles, from the diagonal down to key 0
-        auto begin_iter = [&](int it) __attribute__((always_inline)) {
-            dma_wait<0>();                                   // this wave's share of tile `it` has landed
-            // ... everyone's has, and tile it-1 is no longer read.  The waves' exhaustion flags go
-            // through LDS here: their writes must have completed first, or the waves of a
-            // workgroup could disagree about leaving the loop.
-            barrier_lds();
-            if (it + 1 < ntile) stage_tile(ntile - 2 - it, (it + 1) % NS);
-            return (uint32_t)((it % NS) * C::STAGE);
-        };
-        int it = 0;
-        for (; it < ndiag; ++it) {                           // tiles that touch the diagonal band
-            const uint32_t sp = begin_iter(it);
-            const int jt = ntile - 1 - it;
-            if (wave_live) {
-#pragma unroll
-                for (int sub = 1; sub >= 0; --sub) {
-                    const int k0 = jt * C::TK + 32 * sub;    // subtiles and wave rows are both 32-aligned
-                    if (k0 == q0) subtile(bc<true>{}, sp, sub);
-                    else if (k0 < q0) subtile(bc<false>{}, sp, sub);
-                }
-            }
-        }
-        // Tiles fully visible to every row, two per trip with the staging buffer a compile-time
-        // constant, so that every LDS read of the sweep is a precomputed register plus an
-        // immediate: no address arithmetic in the loop.  In the middle of a trip a wave leaves in
-        // s_done whether all its rows are exhausted (both half-waves hold the same carry; rows
-        // past T repeat row T-1); the flags are read after the barrier that follows, by all waves
-        // alike, and written again only after the next one.  The loop has this one exit: with a
-        // second one in the middle the compiler copies the accumulators, which spills.
-        static_assert(NS == 2, "the unrolled sweep alternates two buffers");
-        int stop = 0;
-        if ((it & 1) && it < ntile) { hot_tile(begin_iter(it)); ++it; }
-        for (; it + 1 < ntile && !stop; it += 2) {
-            begin_iter(it);
-            hot_tile(0u);
-            if (!TRI && lane == 0) s_done[wave] = !wave_live || __builtin_amdgcn_ballot_w64(!(a >= enough)) == 0;
-            begin_iter(it + 1);
-            if (!TRI) stop = waves_done(s_done);
-            hot_tile((uint32_t)C::STAGE);
-        }
-        if (it < ntile && !stop) { hot_tile(begin_iter(it)); ++it; }
-        if constexpr (!WRITE_M) {
-            if (tile_counts && tid == 0) {
-                atomicAdd(&tile_counts[0], (unsigned long long)it);        // tiles swept
-                atomicAdd(&tile_counts[1], (unsigned long long)ntile);     // tiles of the full sweep
-            }
-        }
-        dma_wait<0>();                                       // a tile staged before the sweep stopped
-
-        // ---- store.  oacc[b][r] is query row 8*(r/4) + 4*hh + r%4, column 32b + n.
+    // ---- the sweep over 64-key tiles, from the diagonal down to key 0
+    auto begin_iter = [&](int it) __attribute__((always_inline)) {
+        dma_wait<0>();                                   // this wave's share of tile `it` has landed
+        // ... everyone's has, and tile it-1 is no longer read.  The waves' exhaustion flags go
+        // through LDS here: their writes must have completed first, or the waves of a
+        // workgroup could disagree about leaving the loop.
+        barrier_lds();
+        if (it + 1 < ntile) stage_tile(ntile - 2 - it, (it + 1) % NS);
+        return (uint32_t)((it % NS) * C::STAGE);
+    };
+    int it = 0;
+    for (; it < ndiag; ++it) {                           // tiles that touch the diagonal band
+        const uint32_t sp = begin_iter(it);
+        const int jt = ntile - 1 - it;
         if (wave_live) {
-            if constexpr (RB) {
-                // remainder bias (Appendix C): o_j += (stick left of row j) * r_head.  The
-                // lanes n of both half-waves hold the carry of row q0 + n.
-                const float rem = fast_exp2(-a);
-                const uint16_t* rh = rb + head * D;
-                float rc[D / 32];
 #pragma unroll
-                for (int b = 0; b < D / 32; ++b)
-                    rc[b] = __builtin_bit_cast(float, (uint32_t)rh[32 * b + n] << 16);
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const float rr = __shfl(rem, 8 * (r >> 2) + 4 * hh + (r & 3));
-#pragma unroll
-                    for (int b = 0; b < D / 32; ++b) oacc[b][r] += rr * rc[b];
-                }
+            for (int sub = 1; sub >= 0; --sub) {
+                const int k0 = jt * C::TK + 32 * sub;    // subtiles and wave rows are both 32-aligned
+                if (k0 == q0) subtile(bc<true>{}, sp, sub);
+                else if (k0 < q0) subtile(bc<false>{}, sp, sub);
             }
-            uint16_t* Og = o + row0 * D;
-            const bool full = q0 + 32 <= T;
+        }
+    }
+    // Tiles fully visible to every row, two per trip with the staging buffer a compile-time
+    // constant, so that every LDS read of the sweep is a precomputed register plus an
+    // immediate: no address arithmetic in the loop.  In the middle of a trip a wave leaves in
+    // s_done whether all its rows are exhausted (both half-waves hold the same carry; rows
+    // past T repeat row T-1); the flags are read after the barrier that follows, by all waves
+    // alike, and written again only after the next one.  The loop has this one exit: with a
+    // second one in the middle the compiler copies the accumulators, which spills.
+    static_assert(NS == 2, "the unrolled sweep alternates two buffers");
+    int stop = 0;
+    if ((it & 1) && it < ntile) { hot_tile(begin_iter(it)); ++it; }
+    for (; it + 1 < ntile && !stop; it += 2) {
+        begin_iter(it);
+        hot_tile(0u);
+        if (!TRI && lane == 0) s_done[wave] = !wave_live || __builtin_amdgcn_ballot_w64(!(a >= enough)) == 0;
+        begin_iter(it + 1);
+        if (!TRI) stop = waves_done(s_done);
+        hot_tile((uint32_t)C::STAGE);
+    }
+    if (it < ntile && !stop) { hot_tile(begin_iter(it)); ++it; }
+    if constexpr (!WRITE_M) {
+        if (tile_counts && tid == 0) {
+            atomicAdd(&tile_counts[0], (unsigned long long)it);        // tiles swept
+            atomicAdd(&tile_counts[1], (unsigned long long)ntile);     // tiles of the full sweep
+        }
+    }
+    dma_wait<0>();                                       // a tile staged before the sweep stopped
+
+    // ---- store.  oacc[b][r] is query row 8*(r/4) + 4*hh + r%4, column 32b + n.
+    if (wave_live) {
+        if constexpr (RB) {
+            // remainder bias (Appendix C): o_j += (stick left of row j) * r_head.  The
+            // lanes n of both half-waves hold the carry of row q0 + n.
+            const float rem = fast_exp2(-a);
+            const uint16_t* rh = rb + head * D;
+            float rc[D / 32];
 #pragma unroll
-            for (int b = 0; b < D / 32; ++b) {
+            for (int b = 0; b < D / 32; ++b)
+                rc[b] = __builtin_bit_cast(float, (uint32_t)rh[32 * b + n] << 16);
 #pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int row = q0 + 8 * (r >> 2) + 4 * hh + (r & 3);
-                    if (full || row < T) {
-                        const __bf16 val = (__bf16)oacc[b][r];
-                        Og[(long)row * D + 32 * b + n] = __builtin_bit_cast(uint16_t, val);
-                    }
+            for (int r = 0; r < 16; ++r) {
+                const float rr = __shfl(rem, 8 * (r >> 2) + 4 * hh + (r & 3));
+#pragma unroll
+                for (int b = 0; b < D / 32; ++b) oacc[b][r] += rr * rc[b];
+            }
+        }
+        uint16_t* Og = o + row0 * D;
+        const bool full = q0 + 32 <= T;
+#pragma unroll
+        for (int b = 0; b < D / 32; ++b) {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int row = q0 + 8 * (r >> 2) + 4 * hh + (r & 3);
+                if (full || row < T) {
+                    const __bf16 val = (__bf16)oacc[b][r];
+                    Og[(long)row * D + 32 * b + n] = __builtin_bit_cast(uint16_t, val);
                 }
             }
         }
-        if constexpr (WRITE_M) {
-            if (it < ntile) sum_tail(ntile - it);
-            if (wave_live && hh == 0 && q0 + n < T) m[row0 + q0 + n] = -a * SB_LN2;
-        }
+    }
+    if constexpr (WRITE_M) {
+        if (it < ntile) sum_tail(ntile - it);
+        if (wave_live && hh == 0 && q0 + n < T) m[row0 + q0 + n] = -a * SB_LN2;
     }
     if constexpr (WRITE_M) {
         if (tile_counts && wg == 0 && tid == 0) {
@@ -541,10 +530,10 @@ hipError_t launch_one(const uint16_t* q, const uint16_t* k, const uint16_t* v, c
                       const int* cu = nullptr, int Ttot = 0)
 {
     const int nqb = (T + BQ - 1) / BQ;
-    const ShareRule sr = share_rule(BH, nqb);
-    if (sr.grid > 0x7fffffffL) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((fwd_bf16_kernel<D, WRITE_M, RB, VL, TRI>), dim3((unsigned)sr.grid), dim3(64 * NW), 0, stream,
-                       q, k, v, rb, o, m, T, BH, H, G, nqb, enough, tile_counts, cu, Ttot, sr.mode, sr.single);
+    const long grid = share_grid(BH, nqb, false);
+    if (grid > 0x7fffffffL) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((fwd_bf16_kernel<D, WRITE_M, RB, VL, TRI>), dim3((unsigned)grid), dim3(64 * NW), 0, stream,
+                       q, k, v, rb, o, m, T, BH, H, G, nqb, enough, tile_counts, cu, Ttot);
     return hipGetLastError();
 }
 

@@ -33,64 +33,42 @@ __device__ __forceinline__ float sp2(float x)
 // this far gives every farther key a weight below 2^-160: zero in fp32 and in bf16.
 constexpr float CARRY_EXHAUSTED = 160.0f;
 
-// Which blocks a workgroup works on.  A head's n row blocks form (n+1)/2 pairs (p, n-1-p) of equal
-// causal cost; how much work a head is depends on how far its weights reach.  Workgroup ids go
-// round the 8 XCDs, each with an L2 of its own, in which neighbouring pairs of a head, which sweep
-// the same tiles at about the same time, can share them.
+// Which blocks a workgroup works on.  Block i of a head (i = 0 the longest) and block n-1-i form pair i,
+// of the same causal cost for every i; but how much of that cost a block is depends on how far its
+// head's weights reach.  Workgroup ids go round the 8 XCDs and start in order as places come free.
+//
+// Longest first: every workgroup one block, block 0 of all heads, then block 1, ...; the heads turn
+// with i where their number is even, so that a head's blocks do not all go to the same XCDs.  What
+// runs last is short, and no XCD gets more of the costly heads than another.
+// In pairs: every workgroup a pair, every head on one XCD, slot s of the XCDs takes heads 8s .. 8s+7,
+// turned by s(s+1)/2 (over any 8 even or 8 odd s these are all 8 turns, so that also where the heads
+// of a layer are a multiple of 8 no XCD gets the same ones from every batch entry).  A head's tiles
+// then stay in one L2.
+//
+// Measured, a third of the heads reaching far, pairs / longest first, us: forward B1 H32 T16384 d128
+// 1217 / 940, B1 H24 T16384 d64 470 / 319, B4 H12 Hkv4 T2048 d128 82 / 64, packed H24 d64 200 / 153;
+// query-stationary backward B8 H16 T4096 d128 591 / 519, B8 H16 T2048 d64 170 / 142.  All heads far:
+// 2384 / 2467, 760 / 711, 91 / 80, 232 / 178, 1034 / 1027, 215 / 208.  The key-stationary kernel of
+// d = 128, one workgroup per CU and nothing else to hide a tile's latency, is better in pairs while
+// there are heads enough to even out (B8 H16 T4096: 712 / 773, all far 1388 / 1457; B1 H16 T6000 with
+// the dq pass: 668 / 392).
 struct Share {
     int bh;                   // head
-    int p;                    // pair
-    int part0, part1;         // parts of it to do: 0 = the longer block, 1 = the shorter
+    int i;                    // block, or with pairs pair
 };
-enum ShareMode { HEAD_PER_XCD, RUNS, ROUND_ROBIN };
-// RUNS: a head's pairs in 8 runs of neighbours, one per XCD.  Measured on heads of which a third
-// reach far (bf16 forward, B1 H32 T16384 d128 / B1 H24 T16384 d64): one XCD a head 1102 / 660 us,
-// runs 1001 / 526 us, since no XCD gets more of the costly heads than another.  Where every head
-// reaches far the shared L2 is worth more, 2318 against 2371 us, and with many shorter heads too
-// (B8 H16 T4096 d128: 367 against 376 us, all far 641 against 682 us): so runs from 4 pairs up.
-// ROUND_ROBIN: few heads of few pairs, pair after pair; an even load is all that counts (B1 H24 Hkv8
-// T4096 d64, one XCD a head: 91 us, pairs spread: 73 us).
-// single: the two blocks of a pair are workgroups of their own, the longer ones first, where every
-// block gets a CU to itself (B1 H32 T1024 d128: 33 -> 27 us).  Beyond that pairs are faster: they
-// load the CUs evenly (B1 H24 Hkv8 T4096 d64: 73 us in pairs, 89 us single).
-struct ShareRule {
-    int mode, single;
-    long grid;
-};
-inline ShareRule share_rule(long heads, int nblk)
+inline long share_grid(long heads, int nblk, bool pairs)
 {
-    const int npair = (nblk + 1) / 2;
-    ShareRule r;
-    r.mode = npair >= 32 ? RUNS : heads < 64 ? ROUND_ROBIN : HEAD_PER_XCD;
-    r.single = heads * nblk <= 256;
-    r.grid = (r.mode == RUNS ? 8L * heads * ((npair + 7) / 8) : r.mode == ROUND_ROBIN ? heads * npair
-              : 8L * ((heads + 7) / 8) * npair) * (1 + r.single);
-    return r;
+    return pairs ? 8L * ((heads + 7) / 8) * ((nblk + 1) / 2) : heads * nblk;
 }
-// false: nothing to do
-__device__ __forceinline__ bool share_of(Share& sh, int wg, int heads, int npair, int mode, int single)
+__device__ __forceinline__ Share share_of(int wg, int heads, int nblk, bool pairs)
 {
-    const int run = mode == RUNS ? (npair + 7) >> 3 : npair;
-    const int per = run << single;
-    const int slot = mode == ROUND_ROBIN ? wg : wg >> 3;
-    const int s = slot / per;
-    int i = slot - s * per;
-    sh.part0 = 0;
-    sh.part1 = 2;
-    if (single) {
-        sh.part0 = i >= run;
-        sh.part1 = sh.part0 + 1;
-        i -= sh.part0 ? run : 0;
+    if (pairs) {              // bh >= heads: nothing to do
+        const int npair = (nblk + 1) >> 1;
+        const int slot = wg >> 3, s = slot / npair;
+        return {8 * s + ((wg + ((s * (s + 1)) >> 1)) & 7), slot - s * npair};
     }
-    const int x = (wg + (((unsigned)s * 0x9E3779B1u) >> 29)) & 7;     // XCDs in another order for every s
-    sh.bh = mode == HEAD_PER_XCD ? 8 * s + x : s;
-    sh.p = i;
-    if (mode == RUNS) {
-        const int start = (x * npair) >> 3;
-        if (i >= (((x + 1) * npair) >> 3) - start) return false;
-        sh.p += start;
-    }
-    return sh.bh < heads;
+    const int i = wg / heads, w = wg - i * heads;
+    return {(heads & 1) ? w : (w + i) % heads, i};
 }
 
 // sum of log2(1 + 2^(c2 s_r)) over a lane's 16 logits: one product of the (1 + e_r) from 2^-60 on,
