@@ -618,14 +618,19 @@ __device__ __forceinline__ Reach reach_of(const int* __restrict__ f, int kb, int
 }
 
 // ------------------------------------------------------------------ dK / dV kernel
-template <int D> struct DkvCfg {
-    static constexpr int T_OFF = 2 * StageCfg<D>::STAGE;   // after the double buffer
+// SP groups of four waves take the block's query tiles in turn (tile t: group t % SP), each into
+// accumulators of its own, added up at the end in LDS.  Two groups where a block has a CU to itself
+// anyway: one wave per SIMD issues an instruction every five clocks at best, two keep it busy
+// (B2 H4 T777 d32: 24 -> 19 us).
+template <int D, int SP> struct DkvCfg {
+    static constexpr int T_OFF = SP * 2 * StageCfg<D>::STAGE;   // after the double buffers
     static constexpr int T_WAVE = 2 * SCR_MAT;             // A and dZ scratch of one wave
-    static constexpr int LDS_BYTES = T_OFF + NW * T_WAVE;
+    static constexpr int LDS_BYTES = T_OFF + SP * NW * T_WAVE;
+    static_assert(SP == 1 || NW * 2 * 32 * D * 4 <= LDS_BYTES, "the second group's accumulators fit");
 };
 
-template <int D, bool GQA, bool VL>
-__global__ void __launch_bounds__(NTHREADS, 2)
+template <int D, bool GQA, bool VL, int SP>
+__global__ void __launch_bounds__(SP * NTHREADS, 2)
 bwd_dkv_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
                const uint16_t* __restrict__ v, const uint16_t* __restrict__ dout,
                const float* __restrict__ ca, const float* __restrict__ cb,
@@ -633,7 +638,7 @@ bwd_dkv_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
                int T_arg, int BH, int H, int G_arg, int nkb_arg, int nt32, const int* __restrict__ cu, int Ttot)
 {
     using C = StageCfg<D>;
-    using CK = DkvCfg<D>;
+    using CK = DkvCfg<D, SP>;
     const int G = GQA ? G_arg : 1;                      // query heads per kv head
     __shared__ __attribute__((aligned(1024))) char smem[CK::LDS_BYTES];
 
@@ -643,7 +648,9 @@ bwd_dkv_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6) & (NW - 1);
+    const int grp = SP == 1 ? 0 : __builtin_amdgcn_readfirstlane(tid / NTHREADS);
+    char* const tiles = smem + grp * 2 * C::STAGE;      // the group's double buffer
     const int n = lane & 31, hh = lane >> 5;
     const int gg = lane >> 4, li = lane & 15;
 
@@ -672,7 +679,7 @@ bwd_dkv_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     }
     int goff[C::NPW];
     stage_offsets<D, false>(goff, wave, lane);
-    char* const scr = smem + CK::T_OFF + wave * CK::T_WAVE;               // [A, dZ][32 rows of 64 B]
+    char* const scr = smem + CK::T_OFF + (grp * NW + wave) * CK::T_WAVE;               // [A, dZ][32 rows of 64 B]
     const int sw_off = scr_off(n, 2 * hh);                                // scratch write: row = query n; second chunk: ^ 16
     int st_off[2];                                                        // transposing reads, rows 8h + li/4 (+ 4t)
 #pragma unroll
@@ -796,14 +803,15 @@ bwd_dkv_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     const bool wave_live = k0 < T;
     const int jt0 = K0 / TK;
     float cn[2][2];                                      // [subtile][ca, cb] of the next tile
-    // the block's first tile of a head and its carries, which always reach these keys
+    // the group's first tile of a head and its carries, which always reach these keys (the block's own
+    // queries are two tiles)
     auto first_tile = [&](int g) __attribute__((always_inline)) {
         Qg = q + (qrow0 + g * qrow_step) * D;
         Gg = dout + (qrow0 + g * qrow_step) * D;
         cag = ca + cbase + g * cbase_step + kt32 * cstride;
         cbg = cb + cbase + g * cbase_step + kt32 * cstride;
-        load_carries(cn, jt0, wave_live);
-        stage_tile<D, false>(Qg, Gg, jt0, T, smem, goff, wave, lane);
+        load_carries(cn, jt0 + grp, wave_live);
+        if (SP == 1 || (jt0 + grp) * TK < T) stage_tile<D, false>(Qg, Gg, jt0 + grp, T, tiles, goff, wave, lane);
     };
     first_tile(0);                                       // fetched together with the stationary rows
     {
@@ -838,19 +846,20 @@ bwd_dkv_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     const int* const fg = first + (kh.qhead0 + g) * nkb_arg;
     const Reach reach = reach_of(fg, kb, nkb, lane);
     const int ntile = min((T + TK - 1) / TK, reach.end) - jt0;
-    const int ndiag = min(ntile, BKW / TK);              // tiles that touch the diagonal band
+    const int niter = (ntile + SP - 1) / SP;
+    const int ndiag = min(niter, BKW / TK / SP);         // iterations on tiles that touch the diagonal band
     float cc[2][2];
     auto begin_iter = [&](int it) __attribute__((always_inline)) {
         dma_wait<0>();
         barrier_nofence();
 #pragma unroll
         for (int u = 0; u < 2; ++u) { cc[u][0] = cn[u][0]; cc[u][1] = cn[u][1]; }
-        if (it + 1 < ntile) {
-            const int jt = jt0 + it + 1;
+        const int jt = jt0 + (it + 1) * SP + grp;
+        if (jt < jt0 + ntile) {
             load_carries(cn, jt, wave_live && (jt < reach.sure || fg[jt >> 1] <= kt32 >> 1));
-            stage_tile<D, false>(Qg, Gg, jt, T, smem + ((it + 1) & 1) * C::STAGE, goff, wave, lane);
+            stage_tile<D, false>(Qg, Gg, jt, T, tiles + ((it + 1) & 1) * C::STAGE, goff, wave, lane);
         }
-        return (const char*)(smem + (it & 1) * C::STAGE);
+        return (const char*)(tiles + (it & 1) * C::STAGE);
     };
     int it = 0;
     for (; it < ndiag; ++it) {
@@ -858,20 +867,40 @@ bwd_dkv_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
         if (wave_live) {
 #pragma unroll
             for (int u = 0; u < 2; ++u) {
-                const int j0 = (jt0 + it) * TK + 32 * u;
+                const int j0 = (jt0 + it * SP + grp) * TK + 32 * u;
                 if (j0 == k0) subtile(bc<true>{}, sp + u * 32 * C::ROW, cc[u][0], cc[u][1]);
                 else if (j0 > k0 && j0 < T) subtile(bc<false>{}, sp + u * 32 * C::ROW, cc[u][0], cc[u][1]);
             }
         }
     }
-    for (; it < ntile; ++it) {
+    for (; it < niter; ++it) {
         const char* sp = begin_iter(it);
-        if (wave_live) {
-            const int j0 = (jt0 + it) * TK;
+        if (wave_live && (SP == 1 || it * SP + grp < ntile)) {
+            const int j0 = (jt0 + it * SP + grp) * TK;
             subtile(bc<false>{}, sp, cc[0][0], cc[0][1]);
             if (j0 + 32 < T) subtile(bc<false>{}, sp + 32 * C::ROW, cc[1][0], cc[1][1]);
         }
     }
+    }
+
+    if constexpr (SP == 2) {
+        barrier_lds();                                   // everyone is done with tiles and scratch
+        f32x4* const red = reinterpret_cast<f32x4*>(smem) + wave * (D / 32 * 2 * 4) * 64 + lane;
+#pragma unroll
+        for (int i = 0; i < D / 32 * 2 * 4; ++i) {
+            f32x16& acc = (i >> 2) & 1 ? dvacc[i >> 3] : dkacc[i >> 3];
+            const int r = 4 * (i & 3);
+            if (grp == 1) red[i * 64] = f32x4{acc[r], acc[r + 1], acc[r + 2], acc[r + 3]};
+        }
+        barrier_lds();
+        if (grp == 1) return;
+#pragma unroll
+        for (int i = 0; i < D / 32 * 2 * 4; ++i) {
+            f32x16& acc = (i >> 2) & 1 ? dvacc[i >> 3] : dkacc[i >> 3];
+            const f32x4 o = red[i * 64];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[4 * (i & 3) + e] += o[e];
+        }
     }
 
     // ---- store: acc[b][r] is key row k0 + 8*(r/4) + 4*hh + r%4, column 32b + n
@@ -1427,8 +1456,11 @@ hipError_t launch_one(const uint16_t* q, const uint16_t* k, const uint16_t* v, c
     if constexpr (D == 128)                                                                                    \
         hipLaunchKernelGGL((bwd_dkv_pair_kernel<D, GQAV, VL>), dim3((unsigned)gk), dim3(NTHREADS2), 0,         \
                            stream, q, k, v, dout, ca, cb, dk, dv, first, T, BHkv, H, G, nkb, nt32, cu, Ttot, pairs); \
+    else if (gk <= ONE_PER_CU)                                                                                 \
+        hipLaunchKernelGGL((bwd_dkv_kernel<D, GQAV, VL, 2>), dim3((unsigned)gk), dim3(2 * NTHREADS), 0,        \
+                           stream, q, k, v, dout, ca, cb, dk, dv, first, T, BHkv, H, G, nkb, nt32, cu, Ttot);  \
     else                                                                                                       \
-        hipLaunchKernelGGL((bwd_dkv_kernel<D, GQAV, VL>), dim3((unsigned)gk), dim3(NTHREADS), 0,               \
+        hipLaunchKernelGGL((bwd_dkv_kernel<D, GQAV, VL, 1>), dim3((unsigned)gk), dim3(NTHREADS), 0,            \
                            stream, q, k, v, dout, ca, cb, dk, dv, first, T, BHkv, H, G, nkb, nt32, cu, Ttot);  \
     if ((e = hipGetLastError()) != hipSuccess) return e
     if (passes & 1) {

@@ -48,7 +48,6 @@ constexpr int COMBINE_THREADS = 256;
 constexpr int MAXFAR = 127;            // chunks beyond the nearest keys: with those, two per lane of a wave
 constexpr long FAR_WGS = 2048;      // workgroups of the second launch, all heads together
 
-typedef __attribute__((ext_vector_type(4))) float f32x4;
 
 // sum of v over the lanes above this one, and over all lanes in `total`
 __device__ __forceinline__ float wave_suffix_excl(float v, float& total)
