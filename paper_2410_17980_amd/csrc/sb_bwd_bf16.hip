@@ -556,7 +556,7 @@ bwd_dq_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
 // bh counts kv heads (B * H / G of them); its G query heads are qh0 .. qh0+G-1.  Returns
 // false when the workgroup has nothing to do (packed batch: blocks beyond its sequence).
 struct KvHead {
-    int T, nkb;                             // rows and 128-key blocks of this head's sequence
+    int T, nkb;                             // rows and key blocks (of `keys` keys) of this head's sequence
     long base;                              // first element of the kv head's K / V / dK / dV rows
     long qrow0, qrow_step;                  // first Q / dO row of query head qh0, step to the next head
     long cbase, cbase_step, cstride;        // carries: start for head qh0, step per head, strip stride
@@ -564,7 +564,7 @@ struct KvHead {
 };
 
 template <int D, bool VL>
-__device__ __forceinline__ bool kv_head(KvHead& kh, int bh, int T_arg, int nkb_arg, int H, int G,
+__device__ __forceinline__ bool kv_head(KvHead& kh, int bh, int T_arg, int nkb_arg, int keys, int H, int G,
                                         int nt32, const int* __restrict__ cu, int Ttot)
 {
     const int Hkv = H / G;
@@ -574,7 +574,7 @@ __device__ __forceinline__ bool kv_head(KvHead& kh, int bh, int T_arg, int nkb_a
         const int c0 = cu[seq];
         kh.T = min(min(cu[seq + 1], Ttot) - c0, T_arg);   // never past the packed rows or the stated maximum
         if (c0 < 0) return false;
-        kh.nkb = (kh.T + BKW - 1) / BKW;
+        kh.nkb = (kh.T + keys - 1) / keys;
         kh.base = ((long)hkv * Ttot + c0) * D;
         kh.qrow0 = (long)hkv * G * Ttot + c0;
         kh.qrow_step = Ttot;
@@ -597,20 +597,22 @@ __device__ __forceinline__ bool kv_head(KvHead& kh, int bh, int T_arg, int nkb_a
     return true;
 }
 
-// Which query tiles reach key block kb, from the query blocks' start tiles f[0 .. nqb-1]: none
-// from tile `end` on; all tiles before `sure` reach every key of it.  In between a tile reaches
-// a strip's keys iff f[tile / 2] <= the strip's 64-key tile.  The block's own queries always do.
+// Which query tiles reach the keys of tiles lo .. hi (of the 128-key block kb), from the query blocks'
+// start tiles f[0 .. nqb-1]: none from tile `end` on; all tiles before `sure` reach every one of
+// them.  In between a tile reaches a key tile iff f[tile / 2] is not beyond it.  The block's own
+// queries always count.
 struct Reach {
     int sure, end;
 };
-__device__ __forceinline__ Reach reach_of(const int* __restrict__ f, int kb, int nqb, int lane)
+__device__ __forceinline__ Reach reach_of(const int* __restrict__ f, int lo, int hi, int nqb, int lane)
 {
-    static_assert(BQ == 2 * TK && BKW == 2 * TK, "two tiles per block on either side");
+    static_assert(BQ == 2 * TK, "two tiles per query block");
+    const int kb = lo >> 1;
     int last = kb, cut = nqb;
     for (int b = kb + 1; b < nqb; b += 64) {
         const int t = b + lane < nqb ? f[b + lane] : 0x7fffffff;
-        const unsigned long long some = __builtin_amdgcn_ballot_w64(t <= 2 * kb + 1);
-        const unsigned long long not_all = __builtin_amdgcn_ballot_w64(t > 2 * kb);
+        const unsigned long long some = __builtin_amdgcn_ballot_w64(t <= hi);
+        const unsigned long long not_all = __builtin_amdgcn_ballot_w64(t > lo);
         if (some) last = b + 63 - __builtin_clzll(some);
         if (not_all && cut == nqb) cut = min(nqb, b + __builtin_ctzll(not_all));
     }
@@ -656,7 +658,7 @@ bwd_dkv_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
 
     // bh counts kv heads here (BH = B * H / G of them)
     KvHead kh;
-    if (!kv_head<D, VL>(kh, bh, T_arg, nkb_arg, H, G, nt32, cu, Ttot) || sh.i >= kh.nkb) return;
+    if (!kv_head<D, VL>(kh, bh, T_arg, nkb_arg, BKW, H, G, nt32, cu, Ttot) || sh.i >= kh.nkb) return;
     const int T = kh.T, nkb = kh.nkb;
     const long base = kh.base, qrow0 = kh.qrow0, qrow_step = kh.qrow_step;
     const long cbase = kh.cbase, cbase_step = kh.cbase_step, cstride = kh.cstride;
@@ -844,7 +846,7 @@ bwd_dkv_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     // issued: vector memory operations complete in order, so a wait for a carry
     // issued after the staging loads would wait for those as well.
     const int* const fg = first + (kh.qhead0 + g) * nkb_arg;
-    const Reach reach = reach_of(fg, kb, nkb, lane);
+    const Reach reach = reach_of(fg, 2 * kb, 2 * kb + 1, nkb, lane);
     const int ntile = min((T + TK - 1) / TK, reach.end) - jt0;
     const int niter = (ntile + SP - 1) / SP;
     const int ndiag = min(niter, BKW / TK / SP);         // iterations on tiles that touch the diagonal band
@@ -947,30 +949,36 @@ bwd_dkv_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
 // the two roles taking front and back in opposite order within an interval (so that one
 // wave of a SIMD is in its vector phase while the other is in its matrix phase) is slower,
 // 1.47 ms: the compiler then copies the accumulator (64 registers) on every switch.
-constexpr int NW2 = 8;
-constexpr int NTHREADS2 = 64 * NW2;
-
-template <int D> struct Dkv3Cfg {
+// KS: strips per block, 4 or, in small grids, 2: what bounds a launch there is one block's chain of
+// intervals, and with one wave per SIMD in place of two an interval is shorter.  Backward with 128 /
+// 64 keys a block, us: B4 H12 Hkv4 T2048 (256 blocks of 128) 267 / 217, B2 H16 Hkv8 T3000 (384) 289 / 240,
+// B1 H16 T4096 (512) 268 / 262, B8 H16 Hkv4 T2048 (512) 426 / 438, B2 H16 T4096 (1024) 313 / 366.
+constexpr long SMALL_KV_GRID = 384;
+template <int D, int KS> struct Dkv3Cfg {
+    static constexpr int NW2 = 2 * KS;
+    static constexpr int KEYS = 32 * KS;
     static constexpr int NBUF = 3;
     static constexpr int T_OFF = NBUF * StageCfg<D>::STAGE;  // after the tile buffers
     static constexpr int M_BYTES = 32 * 64;                  // one 32x32 bf16 matrix
     static constexpr int W_BYTES = 2 * M_BYTES;              // A and dZ of one wave's subtile
-    static constexpr int SCR_BUF = NW2 * W_BYTES;            // the eight waves' subtiles of one tile
+    static constexpr int SCR_BUF = NW2 * W_BYTES;            // the waves' subtiles of one tile
     static constexpr int LDS_BYTES = T_OFF + 2 * SCR_BUF;
     static constexpr int LOADS = StageCfg<D>::TILE / 1024;
     static constexpr int NPW = (LOADS + NW2 - 1) / NW2;
 };
 
-template <int D, bool GQA, bool VL>
-__global__ void __launch_bounds__(NTHREADS2, 1)
+template <int D, int KS, bool GQA, bool VL>
+__global__ void __launch_bounds__(128 * KS, 1)
 bwd_dkv_pair_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
                     const uint16_t* __restrict__ v, const uint16_t* __restrict__ dout,
                     const float* __restrict__ ca, const float* __restrict__ cb,
                     float* __restrict__ dk, float* __restrict__ dv, const int* __restrict__ first,
-                    int T_arg, int BH, int H, int G_arg, int nkb_arg, int nt32, const int* __restrict__ cu, int Ttot, int pairs)
+                    int T_arg, int BH, int H, int G_arg, int nkb_arg, int nqb_arg, int nt32,
+                    const int* __restrict__ cu, int Ttot, int pairs)
 {
     using C = StageCfg<D>;
-    using CK = Dkv3Cfg<D>;
+    using CK = Dkv3Cfg<D, KS>;
+    constexpr int NW2 = CK::NW2;
     static_assert(CK::LDS_BYTES <= 160 * 1024, "LDS budget");
     const int G = GQA ? G_arg : 1;                      // query heads per kv head
     __shared__ __attribute__((aligned(1024))) char smem[CK::LDS_BYTES];
@@ -983,13 +991,13 @@ bwd_dkv_pair_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int strip = wave & 3;             // which 32 keys of the block
-    const int role = wave >> 2;             // the subtile of every tile this wave fronts; 0 accumulates dV, 1 dK
+    const int strip = wave & (KS - 1);           // which 32 keys of the block
+    const int role = wave / KS;             // the subtile of every tile this wave fronts; 0 accumulates dV, 1 dK
     const int n = lane & 31, hh = lane >> 5;
     const int gg = lane >> 4, li = lane & 15;
 
     KvHead kh;
-    if (!kv_head<D, VL>(kh, bh, T_arg, nkb_arg, H, G, nt32, cu, Ttot) || sh.i >= (pairs ? (kh.nkb + 1) >> 1 : kh.nkb)) return;
+    if (!kv_head<D, VL>(kh, bh, T_arg, nkb_arg, CK::KEYS, H, G, nt32, cu, Ttot) || sh.i >= (pairs ? (kh.nkb + 1) >> 1 : kh.nkb)) return;
     const int T = kh.T, nkb = kh.nkb;
     const long base = kh.base, qrow0 = kh.qrow0, qrow_step = kh.qrow_step;
     const long cbase = kh.cbase, cbase_step = kh.cbase_step, cstride = kh.cstride;
@@ -1141,14 +1149,14 @@ bwd_dkv_pair_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
 #pragma unroll
         for (int r = 0; r < 16; ++r) { sacc[r] = 0.0f; pacc[r] = 0.0f; }
         // the staging loads go out between the matrix instructions
-        static_assert(CK::LOADS == 2 * NW2, "two staging loads per wave and matrix");
+        static_assert(2 * CK::NPW <= D / 16 && CK::LOADS == CK::NPW * NW2, "whole staging loads");
 #pragma unroll
         for (int s = 0; s < D / 16; ++s) {
             sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[s], __builtin_bit_cast(bf16x8, qw[s]), sacc, 0, 0, 0);
-            if (s == 0) dma16_to_lds_saddr(xn, goff[0], spn + wave * 1024);
-            if (s == 2) dma16_to_lds_saddr(yn, goff[0], spn + C::TILE + wave * 1024);
-            if (s == 4) dma16_to_lds_saddr(xn, goff[1], spn + (wave + NW2) * 1024);
-            if (s == 6) dma16_to_lds_saddr(yn, goff[1], spn + C::TILE + (wave + NW2) * 1024);
+            constexpr int EVERY = D / 16 / (2 * CK::NPW);
+            const int i = s / EVERY / 2;
+            if (s % EVERY == 0)
+                dma16_to_lds_saddr(s / EVERY % 2 ? yn : xn, goff[i], spn + (s / EVERY % 2 ? C::TILE : 0) + (wave + NW2 * i) * 1024);
         }
 #pragma unroll
         for (int s = 0; s < D / 16; ++s) gw[s] = lds_load16((qa ^ (s << 5)) + C::TILE);
@@ -1180,7 +1188,7 @@ bwd_dkv_pair_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
     for (int part = 0; part <= pairs; ++part) {
         const int kb = part == 0 ? sh.i : nkb - 1 - sh.i;    // small kb = most later queries = first
         if (part == 1 && 2 * sh.i == nkb - 1) break;         // odd block count: the middle block is alone
-        const int K0 = kb * BKW;
+        const int K0 = kb * CK::KEYS;
         const int k0 = K0 + strip * 32;                      // the strip's 32 keys
         const int kt32 = k0 >> 5;
         const bool live = k0 < T;
@@ -1235,10 +1243,10 @@ bwd_dkv_pair_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
         // it & 1) and the back of tile jt0 + it - 1; the staging loads of tile jt0 + it + 1 are
         // issued at its start, after the carries of that tile (vector memory operations
         // complete in order, so the carries must not queue behind the staging loads).
-        const int* const fg = first + (kh.qhead0 + g) * nkb_arg;
-        const Reach reach = reach_of(fg, kb, nkb, lane);
+        const int* const fg = first + (kh.qhead0 + g) * nqb_arg;
+        const Reach reach = reach_of(fg, jt0, jt0 + CK::KEYS / TK - 1, (T + BQ - 1) / BQ, lane);
         const int ntile = min((T + TK - 1) / TK, reach.end) - jt0;
-        const int ndiag = min(ntile, BKW / TK);              // tiles that touch the diagonal band
+        const int ndiag = min(ntile, CK::KEYS / TK);              // tiles that touch the diagonal band
         // steady state (the intervals hot_begin .. hot_end - 1): the strip is live, tile `it` is past
         // the diagonal band and complete, and the next tile is complete and reaches the block's keys,
         // or does not exist
@@ -1434,13 +1442,14 @@ hipError_t launch_one(const uint16_t* q, const uint16_t* k, const uint16_t* v, c
     const int nt32 = (T + 31) / 32;
     const int nqb = (T + BQ - 1) / BQ;
     const int nkb = (T + BKW - 1) / BKW;
+    const int nkb64 = (T + 63) / 64;
     const long ncarry = VL ? (long)H * nt32 * Ttot : (long)BH * nt32 * T;
     float* ca = workspace;
     float* cb = ca + ncarry;
     int* first = reinterpret_cast<int*>(cb + ncarry);
     float* part = reinterpret_cast<float*>(first + (long)BH * (nqb + nkb));
     const int nchunk = (T + DR_ROWS - 1) / DR_ROWS;
-    const bool pairs = D == 128 && BHkv >= 64;              // see share_of()
+    const bool pairs = D == 128 && BHkv >= 128;             // see share_of()
     const long gq = share_grid(BH, nqb, false), gk = share_grid(BHkv, nkb, pairs);
     // checked before the first launch, so that an error leaves nothing enqueued
     if (gq > 0x7fffffffL || gk > 0x7fffffffL || nchunk * (long)BH > 0x7fffffffL) return hipErrorInvalidValue;
@@ -1454,8 +1463,12 @@ hipError_t launch_one(const uint16_t* q, const uint16_t* k, const uint16_t* v, c
 // is faster there (measured).
 #define SB_DKV(GQAV)                                                                                           \
     if constexpr (D == 128)                                                                                    \
-        hipLaunchKernelGGL((bwd_dkv_pair_kernel<D, GQAV, VL>), dim3((unsigned)gk), dim3(NTHREADS2), 0,         \
-                           stream, q, k, v, dout, ca, cb, dk, dv, first, T, BHkv, H, G, nkb, nt32, cu, Ttot, pairs); \
+        if (BHkv * (long)nkb <= SMALL_KV_GRID)                                                                 \
+            hipLaunchKernelGGL((bwd_dkv_pair_kernel<D, 2, GQAV, VL>), dim3((unsigned)share_grid(BHkv, nkb64, false)), dim3(256), 0, \
+                               stream, q, k, v, dout, ca, cb, dk, dv, first, T, BHkv, H, G, nkb64, nqb, nt32, cu, Ttot, 0); \
+        else                                                                                                   \
+            hipLaunchKernelGGL((bwd_dkv_pair_kernel<D, 4, GQAV, VL>), dim3((unsigned)gk), dim3(512), 0,        \
+                               stream, q, k, v, dout, ca, cb, dk, dv, first, T, BHkv, H, G, nkb, nqb, nt32, cu, Ttot, pairs); \
     else if (gk <= ONE_PER_CU)                                                                                 \
         hipLaunchKernelGGL((bwd_dkv_kernel<D, GQAV, VL, 2>), dim3((unsigned)gk), dim3(2 * NTHREADS), 0,        \
                            stream, q, k, v, dout, ca, cb, dk, dv, first, T, BHkv, H, G, nkb, nt32, cu, Ttot);  \

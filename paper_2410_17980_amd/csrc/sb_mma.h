@@ -53,8 +53,8 @@ constexpr float CARRY_EXHAUSTED = 160.0f;
 // query-stationary backward B8 H16 T4096 d128 591 / 519, B8 H16 T2048 d64 170 / 142.  All heads far:
 // 2384 / 2467, 760 / 711, 91 / 80, 232 / 178, 1034 / 1027, 215 / 208.  The key-stationary kernel of
 // d = 128, one workgroup per CU and nothing else to hide a tile's latency, is better in pairs while
-// there are heads enough to even out (B8 H16 T4096: 712 / 773, all far 1388 / 1457; B1 H16 T6000 with
-// the dq pass: 668 / 392).
+// there are heads enough to even out (B8 H16 T4096: 712 / 773, all far 1388 / 1457; with the
+// query-stationary pass B4 H16 T4096 681 / 591, B4 H16 T1500 183 / 154).
 struct Share {
     int bh;                   // head
     int i;                    // block, or with pairs pair

@@ -124,3 +124,20 @@ def test_decode(sb, oracle, gen, H, Hkv, T, d):
     for x in (o, o2):
         assert np.all(np.abs(to64(x) - ref) <= fwd_bound(ref, to64(v)))
     check_m(to64(m), rem)
+
+
+@pytest.mark.parametrize("T", [449, 512, 577])
+@pytest.mark.parametrize("d", [32, 64, 128])
+def test_backward_of_more_blocks_than_cus(sb, oracle, gen, T, d):
+    """Grids beyond the small ones take other key-stationary kernels: 97 heads of 4 or 5 key blocks."""
+    H = 97
+    q, k, v = mixed(gen, 1, H, T, d, seed=700 + T)
+    g = gen.gaussian(1, H, T, d, seed=701 + T, dtype="bf16")[0]
+    qd, kd, vd, gd = dev(q, k, v, g)
+    _, m = sb.sb_attn_fwd_train(qd, kd, vd)
+    got = sb.sb_attn_bwd(qd, kd, vd, m, gd, workspace=nan_bytes(sb.sb_attn_bwd_workspace_bytes(1, H, T, d)))
+    torch.cuda.synchronize()
+    for h in (0, 1, 2, 95, 96):
+        one = (to64(t[:, h:h + 1]) for t in (q, k, v, g))
+        for name, a, r in zip(("dq", "dk", "dv"), got, oracle.bwd(*one)):
+            check_grad(f"{name} head {h}", to64(a)[:, h], r[:, 0])
