@@ -61,12 +61,24 @@ const at::Tensor& tensor(PyObject* o, const char* name)
     return THPVariable_Unpack(o);
 }
 
+// what int(o) gives: integers, floats, one-element tensors
 int to_int(PyObject* o)
 {
-    const long v = PyLong_AsLong(o);
-    if (v == -1 && PyErr_Occurred()) throw Raised{};
+    PyObject* i = PyNumber_Long(o);
+    if (!i) throw Raised{};
+    int overflow = 0;
+    const long v = PyLong_AsLongAndOverflow(i, &overflow);
+    Py_DECREF(i);
+    if (overflow) throw Failed("integer argument out of range");
     if (v > INT32_MAX || v < INT32_MIN) throw Failed("integer argument out of range");
     return (int)v;
+}
+
+bool truth(PyObject* o)
+{
+    const int v = PyObject_IsTrue(o);
+    if (v < 0) throw Raised{};
+    return v != 0;
 }
 
 int dim(const at::Tensor& t, int i)
@@ -234,7 +246,7 @@ PyObject* forward(PyObject* const* a)
     auto go = [&](float* m) {
         call(what, [&] { return sb_attn_fwd_gqa(q, k, v, r, o.p(), m, s.B, s.H, s.Hkv, s.T, s.d, st); });
     };
-    if (none(a[7]) && !PyObject_IsTrue(a[8])) {
+    if (none(a[7]) && !truth(a[8])) {
         go(nullptr);
         return o.take();
     }
@@ -275,7 +287,7 @@ PyObject* forward_f32(PyObject* const* a)
     auto go = [&](float* m) {
         call("sb_attn_fwd_f32", [&] { return sb_attn_fwd_f32(q, k, v, o.p<float>(), m, s.B, s.H, s.T, s.d, st); });
     };
-    if (none(a[4]) && !PyObject_IsTrue(a[5])) {
+    if (none(a[4]) && !truth(a[5])) {
         go(nullptr);
         return o.take();
     }
@@ -369,7 +381,7 @@ PyObject* varlen_forward(PyObject* const* a)
         call("sb_attn_varlen_fwd",
              [&] { return sb_attn_varlen_fwd(q, k, v, r, o.p(), m, cu, nseq, s.H, s.Hkv, s.T, max_T, s.d, st); });
     };
-    if (none(a[7]) && !PyObject_IsTrue(a[8])) {
+    if (none(a[7]) && !truth(a[8])) {
         go(nullptr);
         return o.take();
     }
@@ -425,7 +437,7 @@ PyObject* decode(PyObject* const* a)
     void* v = ptr(a[2], BF, skv, "v");
     void* r = ptr(a[4], BF, sr, "r");
     void* st = stream_of(a[9]);
-    const bool in_static = PyObject_IsTrue(a[10]);
+    const bool in_static = truth(a[10]);
     if (in_static && none(a[5])) throw Failed("sb_attn_decode_static allocates nothing: o is required");
     Out o(a[5], BF, sq, tq, "o");
     auto go = [&](float* m) {
@@ -438,7 +450,7 @@ PyObject* decode(PyObject* const* a)
         call("sb_attn_decode",
              [&] { return sb_attn_decode(q, k, v, r, o.p(), m, ws.p(), ws.bytes(), B, H, Hkv, T, Tcap, d, st); });
     };
-    if (none(a[6]) && !PyObject_IsTrue(a[7])) {
+    if (none(a[6]) && !truth(a[7])) {
         go(nullptr);
         return o.take();
     }

@@ -112,3 +112,23 @@ def test_binding_fails_loudly_on_cpu_tensors():
     x = torch.zeros(1, 1, 4, 64, dtype=torch.bfloat16)
     with pytest.raises(binding.SbAttnError):
         binding.sb_attn_fwd(x, x, x, x)
+
+
+def test_integer_arguments_take_what_int_takes():
+    """T of decode and max_T of the packed calls go through int(): floats and one-element tensors
+    are accepted, so each of these calls gets as far as the check of its tensors' device."""
+    import numpy as np
+    import torch
+    from paper_2410_17980_amd import binding
+    bf = lambda *shape: torch.zeros(*shape, dtype=torch.bfloat16)
+    q, c = bf(1, 1, 64), bf(1, 1, 8, 64)
+    p, cu, m = bf(1, 8, 64), torch.tensor([0, 8], dtype=torch.int32), torch.zeros(1, 8)
+    for n in (5, np.int64(5), 5.0, np.float32(5.0), torch.tensor(5), torch.tensor(5.0), torch.tensor([5])):
+        for call in (lambda: binding.sb_attn_decode(q, c, c, T=n), lambda: binding.sb_attn_decode_static(q, c, c, q, T=n),
+                     lambda: binding.sb_attn_varlen_fwd(p, p, p, cu, n), lambda: binding.sb_attn_varlen_bwd(p, p, p, m, p, cu, n)):
+            with pytest.raises(binding.SbAttnError, match="must live on the GPU"):
+                call()
+    for n, error in ((float("nan"), ValueError), (torch.tensor([1, 2]), (ValueError, RuntimeError)), ([], TypeError),
+                     (2 ** 40, binding.SbAttnError), (2 ** 80, binding.SbAttnError)):
+        with pytest.raises(error):
+            binding.sb_attn_decode(q, c, c, T=n)
