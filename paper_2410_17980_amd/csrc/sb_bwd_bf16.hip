@@ -256,13 +256,14 @@ bwd_dq_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
               const float* __restrict__ m,
               const uint16_t* __restrict__ dout, float* __restrict__ dq,
               float* __restrict__ ca, float* __restrict__ cb, int* __restrict__ first,
-              int T_arg, int BH, int H, int G, int nqb_arg, int nt32, const int* __restrict__ cu, int Ttot)
+              int T_arg, int BH, int H, int G, int nqb_arg, int nt32, const int* __restrict__ cu, int Ttot,
+              int first_wg)
 {
     using C = StageCfg<D>;
     __shared__ __attribute__((aligned(1024))) char smem[2 * C::STAGE];
     __shared__ __attribute__((aligned(16))) int s_done[2][NW];   // find_start(): per parity and wave
 
-    const int wg = blockIdx.x;
+    const int wg = first_wg + blockIdx.x;
     const Share sh = share_of(wg, BH, nqb_arg, false);
     const int bh = sh.bh;
     int T = T_arg, nqb = nqb_arg;
@@ -637,14 +638,15 @@ bwd_dkv_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
                const uint16_t* __restrict__ v, const uint16_t* __restrict__ dout,
                const float* __restrict__ ca, const float* __restrict__ cb,
                float* __restrict__ dk, float* __restrict__ dv, const int* __restrict__ first,
-               int T_arg, int BH, int H, int G_arg, int nkb_arg, int nt32, const int* __restrict__ cu, int Ttot)
+               int T_arg, int BH, int H, int G_arg, int nkb_arg, int nt32, const int* __restrict__ cu, int Ttot,
+               int first_wg)
 {
     using C = StageCfg<D>;
     using CK = DkvCfg<D, SP>;
     const int G = GQA ? G_arg : 1;                      // query heads per kv head
     __shared__ __attribute__((aligned(1024))) char smem[CK::LDS_BYTES];
 
-    const int wg = blockIdx.x;
+    const int wg = first_wg + blockIdx.x;
     const Share sh = share_of(wg, BH, nkb_arg, false);
     const int bh = sh.bh;
 
@@ -974,7 +976,7 @@ bwd_dkv_pair_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
                     const float* __restrict__ ca, const float* __restrict__ cb,
                     float* __restrict__ dk, float* __restrict__ dv, const int* __restrict__ first,
                     int T_arg, int BH, int H, int G_arg, int nkb_arg, int nqb_arg, int nt32,
-                    const int* __restrict__ cu, int Ttot, int pairs)
+                    const int* __restrict__ cu, int Ttot, int pairs, int first_wg)
 {
     using C = StageCfg<D>;
     using CK = Dkv3Cfg<D, KS>;
@@ -983,7 +985,7 @@ bwd_dkv_pair_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
     const int G = GQA ? G_arg : 1;                      // query heads per kv head
     __shared__ __attribute__((aligned(1024))) char smem[CK::LDS_BYTES];
 
-    const int wg = blockIdx.x;
+    const int wg = first_wg + blockIdx.x;
     const Share sh = share_of(wg, BH, nkb_arg, pairs);
     const int bh = sh.bh;
     if (bh >= BH) return;
@@ -1353,14 +1355,15 @@ template <int D, bool VL>
 __global__ void __launch_bounds__(NTHREADS)
 bwd_drb_partial_kernel(const float* __restrict__ m, const uint16_t* __restrict__ dout,
                        float* __restrict__ part, int T_arg, int nchunk, int H,
-                       const int* __restrict__ cu, int Ttot)
+                       const int* __restrict__ cu, int Ttot, int first_wg)
 {
     constexpr int CG = D / 8;                 // lanes per row, eight columns each
     constexpr int RG = NTHREADS / CG;         // rows per pass
     constexpr int NP = DR_ROWS / RG;
     __shared__ float red[RG][D + 4];
-    const int bh = blockIdx.x / nchunk;       // one grid dimension: no 65535 limit on the heads
-    const int chunk = blockIdx.x % nchunk;
+    const int wg = first_wg + blockIdx.x;     // one grid dimension: no 65535 limit on the heads
+    const int bh = wg / nchunk;
+    const int chunk = wg % nchunk;
     const int cg = threadIdx.x % CG, rg = threadIdx.x / CG;
     int T = T_arg;
     long row0 = (long)bh * T;
@@ -1454,35 +1457,39 @@ hipError_t launch_one(const uint16_t* q, const uint16_t* k, const uint16_t* v, c
     // checked before the first launch, so that an error leaves nothing enqueued
     if (gq > 0x7fffffffL || gk > 0x7fffffffL || nchunk * (long)BH > 0x7fffffffL) return hipErrorInvalidValue;
     hipError_t e = hipSuccess;
-#define SB_DQ(RBV)                                                                                             \
-    hipLaunchKernelGGL((bwd_dq_kernel<D, RBV, VL>), dim3((unsigned)gq), dim3(NTHREADS), 0, stream,             \
-                       q, k, v, rb, m, dout, dq, ca, cb, first, T, BH, H, G, nqb, nt32, cu, Ttot);             \
-    if ((e = hipGetLastError()) != hipSuccess) return e
+#define SB_LAUNCH(WGS, THREADS, KERNEL, ...)                                                                    \
+    e = launch_workgroups(WGS, THREADS, [&](unsigned n, int first_wg) {                                         \
+        hipLaunchKernelGGL(KERNEL, dim3(n), dim3(THREADS), 0, stream, __VA_ARGS__, first_wg);                   \
+    });                                                                                                         \
+    if (e != hipSuccess) return e
+#define SB_DQ(RBV)                                                                                              \
+    SB_LAUNCH(gq, NTHREADS, (bwd_dq_kernel<D, RBV, VL>),                                                        \
+              q, k, v, rb, m, dout, dq, ca, cb, first, T, BH, H, G, nqb, nt32, cu, Ttot)
 // d = 128 takes the paired-wave kernel (two waves per SIMD instead of one); smaller head
 // dimensions leave room for two workgroups of the one-wave-per-strip kernel per CU, which
 // is faster there (measured).
-#define SB_DKV(GQAV)                                                                                           \
-    if constexpr (D == 128)                                                                                    \
-        if (BHkv * (long)nkb <= SMALL_KV_GRID)                                                                 \
-            hipLaunchKernelGGL((bwd_dkv_pair_kernel<D, 2, GQAV, VL>), dim3((unsigned)share_grid(BHkv, nkb64, false)), dim3(256), 0, \
-                               stream, q, k, v, dout, ca, cb, dk, dv, first, T, BHkv, H, G, nkb64, nqb, nt32, cu, Ttot, 0); \
-        else                                                                                                   \
-            hipLaunchKernelGGL((bwd_dkv_pair_kernel<D, 4, GQAV, VL>), dim3((unsigned)gk), dim3(512), 0,        \
-                               stream, q, k, v, dout, ca, cb, dk, dv, first, T, BHkv, H, G, nkb, nqb, nt32, cu, Ttot, pairs); \
-    else if (gk <= ONE_PER_CU)                                                                                 \
-        hipLaunchKernelGGL((bwd_dkv_kernel<D, GQAV, VL, 2>), dim3((unsigned)gk), dim3(2 * NTHREADS), 0,        \
-                           stream, q, k, v, dout, ca, cb, dk, dv, first, T, BHkv, H, G, nkb, nt32, cu, Ttot);  \
-    else                                                                                                       \
-        hipLaunchKernelGGL((bwd_dkv_kernel<D, GQAV, VL, 1>), dim3((unsigned)gk), dim3(NTHREADS), 0,            \
-                           stream, q, k, v, dout, ca, cb, dk, dv, first, T, BHkv, H, G, nkb, nt32, cu, Ttot);  \
-    if ((e = hipGetLastError()) != hipSuccess) return e
+#define SB_DKV(GQAV)                                                                                            \
+    if constexpr (D == 128) {                                                                                   \
+        if (BHkv * (long)nkb <= SMALL_KV_GRID) {                                                                \
+            SB_LAUNCH(share_grid(BHkv, nkb64, false), 256, (bwd_dkv_pair_kernel<D, 2, GQAV, VL>),               \
+                      q, k, v, dout, ca, cb, dk, dv, first, T, BHkv, H, G, nkb64, nqb, nt32, cu, Ttot, 0);      \
+        } else {                                                                                                \
+            SB_LAUNCH(gk, 512, (bwd_dkv_pair_kernel<D, 4, GQAV, VL>),                                           \
+                      q, k, v, dout, ca, cb, dk, dv, first, T, BHkv, H, G, nkb, nqb, nt32, cu, Ttot, pairs);    \
+        }                                                                                                       \
+    } else if (gk <= ONE_PER_CU) {                                                                              \
+        SB_LAUNCH(gk, 2 * NTHREADS, (bwd_dkv_kernel<D, GQAV, VL, 2>),                                           \
+                  q, k, v, dout, ca, cb, dk, dv, first, T, BHkv, H, G, nkb, nt32, cu, Ttot);                    \
+    } else {                                                                                                    \
+        SB_LAUNCH(gk, NTHREADS, (bwd_dkv_kernel<D, GQAV, VL, 1>),                                               \
+                  q, k, v, dout, ca, cb, dk, dv, first, T, BHkv, H, G, nkb, nt32, cu, Ttot);                    \
+    }
     if (passes & 1) {
         if (rb) { SB_DQ(true); }
         else    { SB_DQ(false); }
         if (drb) {
-            hipLaunchKernelGGL((bwd_drb_partial_kernel<D, VL>), dim3((unsigned)(nchunk * (long)BH)), dim3(NTHREADS), 0,
-                               stream, m, dout, part, T, nchunk, H, cu, Ttot);
-            if ((e = hipGetLastError()) != hipSuccess) return e;
+            SB_LAUNCH(nchunk * (long)BH, NTHREADS, (bwd_drb_partial_kernel<D, VL>),
+                      m, dout, part, T, nchunk, H, cu, Ttot);
             hipLaunchKernelGGL((bwd_drb_sum_kernel<D>), dim3((unsigned)H), dim3(DR_SUM), 0, stream,
                                part, drb, B, H, nchunk);
             if ((e = hipGetLastError()) != hipSuccess) return e;
@@ -1490,9 +1497,10 @@ hipError_t launch_one(const uint16_t* q, const uint16_t* k, const uint16_t* v, c
     }
     if (passes & 2) {
         // a packed batch always takes the grouped variant (a group of one included)
-        if (VL || G > 1) { SB_DKV(true); }
-        else             { SB_DKV(false); }
+        if (VL || G > 1) { SB_DKV(true) }
+        else             { SB_DKV(false) }
     }
+#undef SB_LAUNCH
 #undef SB_DQ
 #undef SB_DKV
     return e;

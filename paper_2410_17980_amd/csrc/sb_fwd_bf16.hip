@@ -84,7 +84,7 @@ fwd_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
                 const uint16_t* __restrict__ v, const uint16_t* __restrict__ rb,
                 uint16_t* __restrict__ o, float* __restrict__ m,
                 int T_arg, int BH, int H, int G, int nqb_arg, float enough,
-                unsigned long long* __restrict__ tile_counts, const int* __restrict__ cu, int Ttot)
+                unsigned long long* __restrict__ tile_counts, const int* __restrict__ cu, int Ttot, int first_wg)
 {
     using C = FwdCfg<D>;
     constexpr int NPW = C::NPW;
@@ -93,7 +93,7 @@ fwd_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     __shared__ __attribute__((aligned(16))) char s_tri[TRI ? 2 * 64 * 16 : 16];   // triangular operand, per lane
 
     // workgroup -> (head, query block)
-    const int wg = blockIdx.x;
+    const int wg = first_wg + blockIdx.x;
     const Share sh = share_of(wg, BH, nqb_arg, false);
     const int bh = sh.bh;
     int T = T_arg, nqb = nqb_arg;
@@ -532,9 +532,10 @@ hipError_t launch_one(const uint16_t* q, const uint16_t* k, const uint16_t* v, c
     const int nqb = (T + BQ - 1) / BQ;
     const long grid = share_grid(BH, nqb, false);
     if (grid > 0x7fffffffL) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((fwd_bf16_kernel<D, WRITE_M, RB, VL, TRI>), dim3((unsigned)grid), dim3(64 * NW), 0, stream,
-                       q, k, v, rb, o, m, T, BH, H, G, nqb, enough, tile_counts, cu, Ttot);
-    return hipGetLastError();
+    return launch_workgroups(grid, 64 * NW, [&](unsigned n, int first_wg) {
+        hipLaunchKernelGGL((fwd_bf16_kernel<D, WRITE_M, RB, VL, TRI>), dim3(n), dim3(64 * NW), 0, stream,
+                           q, k, v, rb, o, m, T, BH, H, G, nqb, enough, tile_counts, cu, Ttot, first_wg);
+    });
 }
 
 }  // namespace

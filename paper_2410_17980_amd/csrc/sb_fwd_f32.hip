@@ -40,7 +40,7 @@ __device__ __forceinline__ float softplus_f32(float z)
 template <int D>
 __global__ void __launch_bounds__(F32_THREADS)
 fwd_f32_kernel(const float* __restrict__ q, const float* __restrict__ k, const float* __restrict__ v,
-               float* __restrict__ o, float* __restrict__ m, int T, int nqb, long nblocks)
+               float* __restrict__ o, float* __restrict__ m, int T, int nqb, long nblocks, int first_wg)
 {
     constexpr int VEC = D >= 64 ? 4 : 2;
     constexpr int NV = D / (16 * VEC);
@@ -51,7 +51,8 @@ fwd_f32_kernel(const float* __restrict__ q, const float* __restrict__ k, const f
     // consecutive workgroup ids go round the 8 XCDs: give each XCD one contiguous eighth of the
     // (head, query block) list, so that a head's K and V are read into one or two L2s only
     const long per_xcd = (nblocks + 7) >> 3;
-    const long lin = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+    const long wg = (long)first_wg + blockIdx.x;
+    const long lin = (wg & 7) * per_xcd + (wg >> 3);
     if (lin >= nblocks) return;
     const long bh = lin / nqb;
     const int q0 = (nqb - 1 - (int)(lin % nqb)) * F32_BQ;      // longest rows first
@@ -170,14 +171,15 @@ hipError_t launch_fwd_f32(const float* q, const float* k, const float* v, float*
     const long nblocks = (long)B * H * nqb;
     const long grid = (nblocks + 7) / 8 * 8;
     if (grid > 0x7fffffffL) return hipErrorInvalidValue;
-    const dim3 g((unsigned)grid), block(F32_THREADS);
-    if (d == 32)
-        hipLaunchKernelGGL(fwd_f32_kernel<32>, g, block, 0, stream, q, k, v, o, m, T, nqb, nblocks);
-    else if (d == 64)
-        hipLaunchKernelGGL(fwd_f32_kernel<64>, g, block, 0, stream, q, k, v, o, m, T, nqb, nblocks);
-    else
-        hipLaunchKernelGGL(fwd_f32_kernel<128>, g, block, 0, stream, q, k, v, o, m, T, nqb, nblocks);
-    return hipGetLastError();
+    return launch_workgroups(grid, F32_THREADS, [&](unsigned wgs, int first_wg) {
+        const dim3 g(wgs), block(F32_THREADS);
+        if (d == 32)
+            hipLaunchKernelGGL(fwd_f32_kernel<32>, g, block, 0, stream, q, k, v, o, m, T, nqb, nblocks, first_wg);
+        else if (d == 64)
+            hipLaunchKernelGGL(fwd_f32_kernel<64>, g, block, 0, stream, q, k, v, o, m, T, nqb, nblocks, first_wg);
+        else
+            hipLaunchKernelGGL(fwd_f32_kernel<128>, g, block, 0, stream, q, k, v, o, m, T, nqb, nblocks, first_wg);
+    });
 }
 
 }  // namespace sb

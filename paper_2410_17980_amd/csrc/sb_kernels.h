@@ -5,7 +5,23 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include <algorithm>
+
 namespace sb {
+
+// A HIP launch takes fewer than 2^32 threads.  Workgroups 0 .. grid-1 in as few launches as that allows:
+// launch(n, first) is to enqueue n of them, starting at workgroup `first`, which the kernel adds to its
+// block index.  All but the last launch hold a multiple of 8, so that a workgroup's XCD stays its index mod 8.
+template <class F> hipError_t launch_workgroups(long grid, int threads, F launch)
+{
+    const long most = (0xffffffffL / threads) & ~7L;
+    for (long first = 0; first < grid; first += most) {
+        launch((unsigned)std::min(most, grid - first), (int)first);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
 
 // Each launcher validates nothing (the C-ABI layer did) and returns the HIP
 // error of the launch.
