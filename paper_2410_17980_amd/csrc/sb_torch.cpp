@@ -10,6 +10,7 @@
 #include <Python.h>
 
 #include <initializer_list>
+#include <optional>
 #include <stdexcept>
 #include <string>
 
@@ -131,17 +132,34 @@ private:
     PyObject* o_ = nullptr;
 };
 
+// `stream` as torch's current stream of `device`, for one scope
+class OnStream {
+public:
+    OnStream(void* stream, c10::DeviceIndex device) : before_(c10::hip::getCurrentHIPStream(device))
+    {
+        c10::hip::setCurrentHIPStream(c10::hip::getStreamFromExternal(static_cast<hipStream_t>(stream), device));
+    }
+    OnStream(const OnStream&) = delete;
+    ~OnStream() { c10::hip::setCurrentHIPStream(before_); }
+
+private:
+    c10::hip::HIPStream before_;
+};
+
 // the caller's workspace, or one of `need` bytes that goes back to torch's caching allocator when
-// the call returns (which keeps it for later work of the same stream)
+// the call returns, before the kernels have run.  The allocator hands it to later work of the stream
+// that it was allocated on, so that has to be the stream of the launch (`so`, None for the current one).
 class Workspace {
 public:
-    Workspace(PyObject* given, size_t need, const at::Tensor& like)
+    Workspace(PyObject* given, size_t need, const at::Tensor& like, PyObject* so, void* stream)
     {
         if (!none(given)) {
             const at::Tensor& t = tensor(given, "workspace");
             p_ = t.data_ptr();
             bytes_ = t.nbytes();
         } else if (need > 0 && like.is_cuda()) {
+            std::optional<OnStream> on;
+            if (!none(so)) on.emplace(stream, like.device().index());
             own_ = at::detail::empty_cuda({(int64_t)need}, at::kByte, like.device(), c10::nullopt);
             p_ = own_.data_ptr();
             bytes_ = need;
@@ -310,8 +328,8 @@ PyObject* backward(PyObject* const* a)
     auto* m = static_cast<float*>(ptr(a[6], F32, s.m, "m"));
     void* g = ptr(a[7], BF, s.q, "dout");
     Out dq(a[8], F32, s.q, like, "dq"), dk(a[9], F32, s.kv, like, "dk"), dv(a[10], F32, s.kv, like, "dv");
-    Workspace ws(a[12], sb_attn_bwd_workspace_bytes(s.B, s.H, s.T, s.d), like);
     void* st = stream_of(a[13]);
+    Workspace ws(a[12], sb_attn_bwd_workspace_bytes(s.B, s.H, s.T, s.d), like, a[13], st);
     auto go = [&](float* dr) {
         call(what, [&] {
             return sb_attn_bwd_gqa(q, k, v, r, m, g, dq.p<float>(), dk.p<float>(), dv.p<float>(), dr, ws.p(), ws.bytes(),
@@ -338,8 +356,8 @@ PyObject* backward_dq(PyObject* const* a)
     auto* m = static_cast<float*>(ptr(a[3], F32, s.m, "m"));
     void* g = ptr(a[4], BF, s.q, "dout");
     Out dq(a[5], F32, s.q, like, "dq");
-    Workspace ws(a[6], 0, like);
     void* st = stream_of(a[7]);
+    Workspace ws(a[6], 0, like, a[7], st);
     call("sb_attn_bwd_dq",
          [&] { return sb_attn_bwd_dq(q, k, v, m, g, dq.p<float>(), ws.p(), ws.bytes(), s.B, s.H, s.T, s.d, st); });
     return dq.take();
@@ -354,9 +372,9 @@ PyObject* backward_dkdv(PyObject* const* a)
     void* k = ptr(a[1], BF, s.q, "k");
     void* v = ptr(a[2], BF, s.q, "v");
     void* g = ptr(a[3], BF, s.q, "dout");
-    Workspace ws(a[4], sb_attn_bwd_workspace_bytes(s.B, s.H, s.T, s.d), like);
-    Out dk(a[5], F32, s.q, like, "dk"), dv(a[6], F32, s.q, like, "dv");
     void* st = stream_of(a[7]);
+    Workspace ws(a[4], sb_attn_bwd_workspace_bytes(s.B, s.H, s.T, s.d), like, a[7], st);
+    Out dk(a[5], F32, s.q, like, "dk"), dv(a[6], F32, s.q, like, "dv");
     call("sb_attn_bwd_dkdv", [&] {
         return sb_attn_bwd_dkdv(q, k, v, g, dk.p<float>(), dv.p<float>(), ws.p(), ws.bytes(), s.B, s.H, s.T, s.d, st);
     });
@@ -405,8 +423,8 @@ PyObject* varlen_backward(PyObject* const* a)
     auto* cu = static_cast<const int*>(any_shape(a[5], at::kInt, "cu_seqlens"));
     void* r = ptr(a[7], BF, s.hd, "r");
     Out dq(a[8], F32, s.q, like, "dq"), dk(a[9], F32, s.kv, like, "dk"), dv(a[10], F32, s.kv, like, "dv");
-    Workspace ws(a[12], sb_attn_varlen_bwd_workspace_bytes(nseq, s.H, s.T, max_T, s.d), like);
     void* st = stream_of(a[13]);
+    Workspace ws(a[12], sb_attn_varlen_bwd_workspace_bytes(nseq, s.H, s.T, max_T, s.d), like, a[13], st);
     auto go = [&](float* dr) {
         call("sb_attn_varlen_bwd", [&] {
             return sb_attn_varlen_bwd(q, k, v, r, m, g, dq.p<float>(), dk.p<float>(), dv.p<float>(), dr, cu, nseq,
@@ -446,7 +464,7 @@ PyObject* decode(PyObject* const* a)
                  [&] { return sb_attn_decode_static(q, k, v, r, o.p(), m, B, H, Hkv, T, Tcap, d, st); });
             return;
         }
-        Workspace ws(a[8], sb_attn_decode_workspace_bytes(B, H, T, d), tq);
+        Workspace ws(a[8], sb_attn_decode_workspace_bytes(B, H, T, d), tq, a[9], st);
         call("sb_attn_decode",
              [&] { return sb_attn_decode(q, k, v, r, o.p(), m, ws.p(), ws.bytes(), B, H, Hkv, T, Tcap, d, st); });
     };

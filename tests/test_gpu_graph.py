@@ -87,3 +87,36 @@ def test_decode_in_a_graph(sb, gen):
         graph.replay()
         torch.cuda.synchronize()
         assert torch.equal(o, want), f"replay {rep}"
+
+
+def test_workspace_lives_as_long_as_the_stream_needs_it(sb, gen):
+    """A call on a stream of its own returns before its kernels have run, and gives its workspace back to
+    torch's allocator: what the current stream allocates and writes meanwhile must be other memory."""
+    B, H, T, d = 1, 4, 700, 64
+    q, k, v, g = dev(*gen.gaussian(B, H, T, d, seed=5, with_dout=True))
+    qd, _, _ = dev(*gen.gaussian(B, H, 1, d, seed=6))
+    kd, vd = (t.expand(4, H, T, d).transpose(0, 1).reshape(B, H, 4 * T, d).contiguous() for t in (k, v))
+    qd = qd[:, :, 0].contiguous()
+    cu = torch.tensor([0, 300, T], dtype=torch.int32, device="cuda")
+    one = [t[0].contiguous() for t in (q, k, v, g)]
+    o, m = sb.sb_attn_fwd_train(q, k, v)
+    _, mp = sb.sb_attn_varlen_fwd(*one[:3], cu, 400)
+    side = torch.cuda.Stream()
+    calls = ((sb.sb_attn_bwd_workspace_bytes(B, H, T, d), lambda **kw: sb.sb_attn_bwd(q, k, v, m, g, **kw)),
+             (sb.sb_attn_varlen_bwd_workspace_bytes(2, H, T, 400, d),
+              lambda **kw: sb.sb_attn_varlen_bwd(*one[:3], mp, one[3], cu, 400, **kw)),
+             (sb.load().sb_attn_decode_workspace_bytes(B, H, 4 * T, d),
+              lambda **kw: (sb.sb_attn_decode(qd, kd, vd, **kw),)))
+    for need, call in calls:
+        want = call()
+        torch.cuda.synchronize()
+        with torch.cuda.stream(side):
+            torch.cuda._sleep(200_000_000)       # about 0.1 s: the call's kernels wait behind it
+        got = call(stream=side)
+        for _ in range(4):
+            torch.empty(need, dtype=torch.uint8, device="cuda").fill_(0xFF)
+        torch.cuda.synchronize()
+        segment = [s for s in torch.cuda.memory_snapshot() if s["stream"] == side.cuda_stream]
+        assert sum(s["total_size"] for s in segment) >= need
+        for a, b in zip(got, want):
+            assert torch.equal(a, b)
