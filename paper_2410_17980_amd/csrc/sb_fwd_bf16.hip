@@ -452,20 +452,31 @@ fwd_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
             }
         }
     }
-    // Tiles fully visible to every row, two per trip with the staging buffer a compile-time
-    // constant, so that every LDS read of the sweep is a precomputed register plus an
-    // immediate: no address arithmetic in the loop.  In the middle of a trip a wave leaves in
-    // s_done whether all its rows are exhausted (both half-waves hold the same carry; rows
-    // past T repeat row T-1); the flags are read after the barrier that follows, by all waves
-    // alike, and written again only after the next one.  The loop has this one exit: with a
-    // second one in the middle the compiler copies the accumulators, which spills.
+    // A wave leaves in s_done whether all its rows are exhausted (both half-waves hold the same carry;
+    // rows past T repeat row T-1).  The flags are read after the next barrier, by all waves alike, and
+    // written again only after the one behind that.
+    auto publish = [&]() __attribute__((always_inline)) {
+        if (!TRI && lane == 0) s_done[wave] = !wave_live || __builtin_amdgcn_ballot_w64(!(a >= enough)) == 0;
+    };
+    // Tiles fully visible to every row.  The first row of a block has no key in the diagonal band, so the
+    // tile behind the band is the first after which a block can stop, and a block of near keys or a halting
+    // one usually does: it is looked at by itself.
     static_assert(NS == 2, "the unrolled sweep alternates two buffers");
     int stop = 0;
-    if ((it & 1) && it < ntile) { hot_tile(begin_iter(it)); ++it; }
+    if (it < ntile) { hot_tile(begin_iter(it)); publish(); ++it; }
+    if ((it & 1) && it < ntile) {
+        const uint32_t sp = begin_iter(it);
+        if (!TRI) stop = waves_done(s_done);
+        if (!stop) { hot_tile(sp); ++it; }
+    }
+    // From there on two per trip with the staging buffer a compile-time constant, so that every LDS
+    // read of the sweep is a precomputed register plus an immediate: no address arithmetic in the
+    // loop.  The flags are those of the middle of a trip.  The loop has this one exit: with a
+    // second one in the middle the compiler copies the accumulators, which spills.
     for (; it + 1 < ntile && !stop; it += 2) {
         begin_iter(it);
         hot_tile(0u);
-        if (!TRI && lane == 0) s_done[wave] = !wave_live || __builtin_amdgcn_ballot_w64(!(a >= enough)) == 0;
+        publish();
         begin_iter(it + 1);
         if (!TRI) stop = waves_done(s_done);
         hot_tile((uint32_t)C::STAGE);

@@ -141,3 +141,25 @@ def test_backward_of_more_blocks_than_cus(sb, oracle, gen, T, d):
         one = (to64(t[:, h:h + 1]) for t in (q, k, v, g))
         for name, a, r in zip(("dq", "dk", "dv"), got, oracle.bwd(*one)):
             check_grad(f"{name} head {h}", to64(a)[:, h], r[:, 0])
+
+
+@pytest.mark.parametrize("T", [129, 193, 1024, 1025, 1153, 1216])
+@pytest.mark.parametrize("d", [32, 64, 128])
+def test_halt_after_the_first_tile_behind_the_band(sb, gen, T, d):
+    """N(0,1) logits leave less than 2^-20 after 64 keys (about 74 bits are used up; the sum of 64 terms
+    of mean 1.16 and deviation 0.9 stays above 20 in every row).  So a block takes its diagonal band and
+    the one tile behind it, and no more."""
+    H, eps = 4, 2.0 ** -20
+    q, k, v = dev(*gen.gaussian(1, H, T, d, seed=800 + T, dtype="bf16"))
+    tc = torch.zeros(2, dtype=torch.int64, device="cuda")
+    sb.sb_attn_fwd_halt(q, k, v, eps, tile_counts=tc)
+    full = want = 0
+    for Q0 in range(0, T, 128):
+        ntile = (min(T, Q0 + 128) - 1 + 63) // 64
+        ndiag = max(0, ntile - Q0 // 64)
+        full += ntile
+        want += min(ntile, ndiag + 1)
+    swept, of = tc.tolist()
+    assert of == H * full
+    ragged = T % 128 != 0                        # the last block, whose band may be one tile: a trip more
+    assert H * want <= swept <= H * (want + 2 * ragged), (swept, H * want)
