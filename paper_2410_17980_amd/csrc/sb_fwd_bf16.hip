@@ -148,8 +148,10 @@ fwd_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     }
 
     const uint16_t* Qg = q + row0 * D;
-    const uint16_t* Kg = k + kvrow0 * D;
-    const uint16_t* Vg = v + kvrow0 * D;
+    // in scalar registers: the compiler keeps them in vector ones otherwise, which costs the unrolled
+    // sweep 22 of its 964 vector instructions
+    const uint16_t* Kg = reinterpret_cast<const uint16_t*>(scalar_base(k + kvrow0 * D));
+    const uint16_t* Vg = reinterpret_cast<const uint16_t*>(scalar_base(v + kvrow0 * D));
 
     // ---- per-lane LDS byte addresses inside the first 32-row subtile of the first staging
     // buffer; every other subtile, matrix and buffer is a compile-time constant further on
@@ -459,29 +461,34 @@ fwd_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
         if (!TRI && lane == 0) s_done[wave] = !wave_live || __builtin_amdgcn_ballot_w64(!(a >= enough)) == 0;
     };
     // Tiles fully visible to every row.  The first row of a block has no key in the diagonal band, so the
-    // tile behind the band is the first after which a block can stop, and a block of near keys or a halting
-    // one usually does: it is looked at by itself.
+    // tile behind the band is the first after which a block can stop, and a halting one usually does.
+    // From there on two tiles per trip with the staging buffer a compile-time constant, so that every LDS
+    // read of the sweep is a precomputed register plus an immediate: no address arithmetic in the
+    // loop.  The barrier in front of a trip is taken at the end of the one before, where the flags
+    // decide whether there is another: the loop has this one exit.  (With a second one in its middle the
+    // compiler copies the accumulators, which spills.  The band is two tiles, or one or none in a ragged
+    // last block.)
     static_assert(NS == 2, "the unrolled sweep alternates two buffers");
     int stop = 0;
-    if (it < ntile) { hot_tile(begin_iter(it)); publish(); ++it; }
-    if ((it & 1) && it < ntile) {
-        const uint32_t sp = begin_iter(it);
-        if (!TRI) stop = waves_done(s_done);
-        if (!stop) { hot_tile(sp); ++it; }
-    }
-    // From there on two per trip with the staging buffer a compile-time constant, so that every LDS
-    // read of the sweep is a precomputed register plus an immediate: no address arithmetic in the
-    // loop.  The flags are those of the middle of a trip.  The loop has this one exit: with a
-    // second one in the middle the compiler copies the accumulators, which spills.
-    for (; it + 1 < ntile && !stop; it += 2) {
+    const bool lead = !(it & 1) && it < ntile;
+    if (lead) {
         begin_iter(it);
         hot_tile(0u);
+        ++it;
         publish();
-        begin_iter(it + 1);
-        if (!TRI) stop = waves_done(s_done);
-        hot_tile((uint32_t)C::STAGE);
     }
-    if (it < ntile && !stop) { hot_tile(begin_iter(it)); ++it; }
+    if (it < ntile) begin_iter(it);
+    if (!TRI && lead && it < ntile) stop = waves_done(s_done);
+    while (it + 1 < ntile && !stop) {
+        hot_tile((uint32_t)C::STAGE);
+        begin_iter(it + 1);
+        hot_tile(0u);
+        it += 2;
+        publish();
+        begin_iter(it);
+        if (!TRI) stop = waves_done(s_done);
+    }
+    if (it < ntile && !stop) { hot_tile((uint32_t)C::STAGE); ++it; }
     if constexpr (!WRITE_M) {
         if (tile_counts && tid == 0) {
             atomicAdd(&tile_counts[0], (unsigned long long)it);        // tiles swept
