@@ -45,6 +45,7 @@
 
 #include "sb_kernels.h"
 #include "sb_mma.h"
+#include "sb_share.h"
 
 namespace sb {
 namespace {
@@ -257,14 +258,16 @@ bwd_dq_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
               const uint16_t* __restrict__ dout, float* __restrict__ dq,
               float* __restrict__ ca, float* __restrict__ cb, int* __restrict__ first,
               int T_arg, int BH, int H, int G, int nqb_arg, int nt32, const int* __restrict__ cu, int Ttot,
-              int first_wg)
+              int run, int first_wg)
 {
     using C = StageCfg<D>;
     __shared__ __attribute__((aligned(1024))) char smem[2 * C::STAGE];
     __shared__ __attribute__((aligned(16))) int s_done[2][NW];   // find_start(): per parity and wave
 
+    // what the first loads need is fetched together with the share, not behind the branches of share_of()
+    asm volatile("" :: "s"(q), "s"(k), "s"(v), "s"(m), "s"(dout), "s"(T_arg), "s"(G));
     const int wg = first_wg + blockIdx.x;
-    const Share sh = share_of(wg, BH, nqb_arg, false);
+    const Share sh = in_scalars(share_of(wg, BH, run));
     const int bh = sh.bh;
     int T = T_arg, nqb = nqb_arg;
     long row0, kvrow0, cbase, cstride;      // first q / k row of this head; carries: base and strip stride
@@ -285,7 +288,7 @@ bwd_dq_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
         // grouped kv heads: G consecutive query heads read the same K and V
         head = bh % H;
         row0 = bh * (long)T;
-        kvrow0 = (G == 1 ? bh : (bh / H) * (H / G) + (bh % H) / G) * (long)T;
+        kvrow0 = (long)(G == 1 ? bh : (int)((unsigned)bh / (unsigned)G)) * T;
         cbase = (long)bh * nt32 * T;
         cstride = T;
     }
@@ -568,8 +571,8 @@ template <int D, bool VL>
 __device__ __forceinline__ bool kv_head(KvHead& kh, int bh, int T_arg, int nkb_arg, int keys, int H, int G,
                                         int nt32, const int* __restrict__ cu, int Ttot)
 {
-    const int Hkv = H / G;
     if constexpr (VL) {
+        const int Hkv = H / G;
         const int seq = bh / Hkv;
         const int hkv = bh % Hkv;
         const int c0 = cu[seq];
@@ -584,7 +587,7 @@ __device__ __forceinline__ bool kv_head(KvHead& kh, int bh, int T_arg, int nkb_a
         kh.cbase_step = (long)nt32 * Ttot;
         kh.cstride = Ttot;
     } else {
-        const long qh0 = G == 1 ? bh : (bh / Hkv) * H + (bh % Hkv) * G;
+        const long qh0 = (long)bh * G;
         kh.T = T_arg;
         kh.nkb = nkb_arg;
         kh.base = (long)bh * T_arg * D;
@@ -639,15 +642,16 @@ bwd_dkv_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
                const float* __restrict__ ca, const float* __restrict__ cb,
                float* __restrict__ dk, float* __restrict__ dv, const int* __restrict__ first,
                int T_arg, int BH, int H, int G_arg, int nkb_arg, int nt32, const int* __restrict__ cu, int Ttot,
-               int first_wg)
+               int run, int first_wg)
 {
     using C = StageCfg<D>;
     using CK = DkvCfg<D, SP>;
     const int G = GQA ? G_arg : 1;                      // query heads per kv head
     __shared__ __attribute__((aligned(1024))) char smem[CK::LDS_BYTES];
 
+    asm volatile("" :: "s"(q), "s"(k), "s"(v), "s"(dout), "s"(ca), "s"(cb), "s"(first), "s"(T_arg));   // as in bwd_dq_kernel
     const int wg = first_wg + blockIdx.x;
-    const Share sh = share_of(wg, BH, nkb_arg, false);
+    const Share sh = in_scalars(share_of(wg, BH, run));
     const int bh = sh.bh;
 
     const int tid = threadIdx.x;
@@ -986,7 +990,7 @@ bwd_dkv_pair_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
     __shared__ __attribute__((aligned(1024))) char smem[CK::LDS_BYTES];
 
     const int wg = first_wg + blockIdx.x;
-    const Share sh = share_of(wg, BH, nkb_arg, pairs);
+    const Share sh = in_scalars(pairs ? share_in_pairs(wg, nkb_arg) : share_of(wg, BH, -1));
     const int bh = sh.bh;
     if (bh >= BH) return;
 
@@ -1454,6 +1458,7 @@ hipError_t launch_one(const uint16_t* q, const uint16_t* k, const uint16_t* v, c
     const int nchunk = (T + DR_ROWS - 1) / DR_ROWS;
     const bool pairs = D == 128 && BHkv >= 128;             // see share_of()
     const long gq = share_grid(BH, nqb, false), gk = share_grid(BHkv, nkb, pairs);
+    const int run_q = VL || G > 1 ? -1 : share_run(BH, nqb), run_k = VL || G > 1 ? -1 : share_run(BHkv, nkb);
     // checked before the first launch, so that an error leaves nothing enqueued
     if (gq > 0x7fffffffL || gk > 0x7fffffffL || nchunk * (long)BH > 0x7fffffffL) return hipErrorInvalidValue;
     hipError_t e = hipSuccess;
@@ -1464,7 +1469,7 @@ hipError_t launch_one(const uint16_t* q, const uint16_t* k, const uint16_t* v, c
     if (e != hipSuccess) return e
 #define SB_DQ(RBV)                                                                                              \
     SB_LAUNCH(gq, NTHREADS, (bwd_dq_kernel<D, RBV, VL>),                                                        \
-              q, k, v, rb, m, dout, dq, ca, cb, first, T, BH, H, G, nqb, nt32, cu, Ttot)
+              q, k, v, rb, m, dout, dq, ca, cb, first, T, BH, H, G, nqb, nt32, cu, Ttot, run_q)
 // d = 128 takes the paired-wave kernel (two waves per SIMD instead of one); smaller head
 // dimensions leave room for two workgroups of the one-wave-per-strip kernel per CU, which
 // is faster there (measured).
@@ -1479,10 +1484,10 @@ hipError_t launch_one(const uint16_t* q, const uint16_t* k, const uint16_t* v, c
         }                                                                                                       \
     } else if (gk <= ONE_PER_CU) {                                                                              \
         SB_LAUNCH(gk, 2 * NTHREADS, (bwd_dkv_kernel<D, GQAV, VL, 2>),                                           \
-                  q, k, v, dout, ca, cb, dk, dv, first, T, BHkv, H, G, nkb, nt32, cu, Ttot);                    \
+                  q, k, v, dout, ca, cb, dk, dv, first, T, BHkv, H, G, nkb, nt32, cu, Ttot, run_k);             \
     } else {                                                                                                    \
         SB_LAUNCH(gk, NTHREADS, (bwd_dkv_kernel<D, GQAV, VL, 1>),                                               \
-                  q, k, v, dout, ca, cb, dk, dv, first, T, BHkv, H, G, nkb, nt32, cu, Ttot);                    \
+                  q, k, v, dout, ca, cb, dk, dv, first, T, BHkv, H, G, nkb, nt32, cu, Ttot, run_k);             \
     }
     if (passes & 1) {
         if (rb) { SB_DQ(true); }

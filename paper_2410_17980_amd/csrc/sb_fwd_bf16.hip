@@ -47,6 +47,7 @@
 
 #include "sb_kernels.h"
 #include "sb_mma.h"
+#include "sb_share.h"
 
 namespace sb {
 namespace {
@@ -84,7 +85,7 @@ fwd_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
                 const uint16_t* __restrict__ v, const uint16_t* __restrict__ rb,
                 uint16_t* __restrict__ o, float* __restrict__ m,
                 int T_arg, int BH, int H, int G, int nqb_arg, float enough,
-                unsigned long long* __restrict__ tile_counts, const int* __restrict__ cu, int Ttot, int first_wg)
+                unsigned long long* __restrict__ tile_counts, const int* __restrict__ cu, int Ttot, int run, int first_wg)
 {
     using C = FwdCfg<D>;
     constexpr int NPW = C::NPW;
@@ -92,9 +93,11 @@ fwd_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     __shared__ __attribute__((aligned(16))) int s_done[NW];         // per wave: all rows exhausted
     __shared__ __attribute__((aligned(16))) char s_tri[TRI ? 2 * 64 * 16 : 16];   // triangular operand, per lane
 
-    // workgroup -> (head, query block)
+    // workgroup -> (head, query block).  What the first loads need is fetched together with it, not behind
+    // the branches of share_of(): a short prompt is a chain of such latencies.
+    asm volatile("" :: "s"(q), "s"(k), "s"(v), "s"(T_arg), "s"(G));
     const int wg = first_wg + blockIdx.x;
-    const Share sh = share_of(wg, BH, nqb_arg, false);
+    const Share sh = in_scalars(share_of(wg, BH, run));
     const int bh = sh.bh;
     int T = T_arg, nqb = nqb_arg;
     long row0, kvrow0;                                  // first row of this head's q / k rows
@@ -113,7 +116,7 @@ fwd_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
         // grouped kv heads: G consecutive query heads read the same K and V
         head = bh % H;
         row0 = bh * (long)T;
-        kvrow0 = (G == 1 ? bh : (bh / H) * (H / G) + (bh % H) / G) * (long)T;
+        kvrow0 = (long)(G == 1 ? bh : (int)((unsigned)bh / (unsigned)G)) * T;
     }
 
     const int tid = threadIdx.x;
@@ -552,7 +555,7 @@ hipError_t launch_one(const uint16_t* q, const uint16_t* k, const uint16_t* v, c
     if (grid > 0x7fffffffL) return hipErrorInvalidValue;
     return launch_workgroups(grid, 64 * NW, [&](unsigned n, int first_wg) {
         hipLaunchKernelGGL((fwd_bf16_kernel<D, WRITE_M, RB, VL, TRI>), dim3(n), dim3(64 * NW), 0, stream,
-                           q, k, v, rb, o, m, T, BH, H, G, nqb, enough, tile_counts, cu, Ttot, first_wg);
+                           q, k, v, rb, o, m, T, BH, H, G, nqb, enough, tile_counts, cu, Ttot, VL || G > 1 ? -1 : share_run(BH, nqb), first_wg);
     });
 }
 

@@ -36,44 +36,6 @@ __device__ __forceinline__ float sp2(float x)
 // this far gives every farther key a weight below 2^-160: zero in fp32 and in bf16.
 constexpr float CARRY_EXHAUSTED = 160.0f;
 
-// Which blocks a workgroup works on.  Block i of a head (i = 0 the longest) and block n-1-i form pair i,
-// of the same causal cost for every i; but how much of that cost a block is depends on how far its
-// head's weights reach.  Workgroup ids go round the 8 XCDs and start in order as places come free.
-//
-// Longest first: every workgroup one block, block 0 of all heads, then block 1, ...; the heads turn
-// with i where their number is even, so that a head's blocks do not all go to the same XCDs.  What
-// runs last is short, and no XCD gets more of the costly heads than another.
-// In pairs: every workgroup a pair, every head on one XCD, slot s of the XCDs takes heads 8s .. 8s+7,
-// turned by s(s+1)/2 (over any 8 even or 8 odd s these are all 8 turns, so that also where the heads
-// of a layer are a multiple of 8 no XCD gets the same ones from every batch entry).  A head's tiles
-// then stay in one L2.
-//
-// Measured, a third of the heads reaching far, pairs / longest first, us: forward B1 H32 T16384 d128
-// 1217 / 940, B1 H24 T16384 d64 470 / 319, B4 H12 Hkv4 T2048 d128 82 / 64, packed H24 d64 200 / 153;
-// query-stationary backward B8 H16 T4096 d128 591 / 519, B8 H16 T2048 d64 170 / 142.  All heads far:
-// 2384 / 2467, 760 / 711, 91 / 80, 232 / 178, 1034 / 1027, 215 / 208.  The key-stationary kernel of
-// d = 128, one workgroup per CU and nothing else to hide a tile's latency, is better in pairs while
-// there are heads enough to even out (B8 H16 T4096: 712 / 773, all far 1388 / 1457; with the
-// query-stationary pass B4 H16 T4096 681 / 591, B4 H16 T1500 183 / 154).
-struct Share {
-    int bh;                   // head
-    int i;                    // block, or with pairs pair
-};
-inline long share_grid(long heads, int nblk, bool pairs)
-{
-    return pairs ? 8L * ((heads + 7) / 8) * ((nblk + 1) / 2) : heads * nblk;
-}
-__device__ __forceinline__ Share share_of(int wg, int heads, int nblk, bool pairs)
-{
-    if (pairs) {              // bh >= heads: nothing to do
-        const int npair = (nblk + 1) >> 1;
-        const int slot = wg >> 3, s = slot / npair;
-        return {8 * s + ((wg + ((s * (s + 1)) >> 1)) & 7), slot - s * npair};
-    }
-    const int i = wg / heads, w = wg - i * heads;
-    return {(heads & 1) ? w : (w + i) % heads, i};
-}
-
 // sum of log2(1 + 2^(c2 s_r)) over a lane's 16 logits: one product of the (1 + e_r) from 2^-60 on,
 // one logarithm; where the product overflows in any lane, the wave takes the sum of sp2
 template <bool MASK>

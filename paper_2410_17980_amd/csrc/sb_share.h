@@ -1,0 +1,80 @@
+// Which blocks a workgroup works on.
+#pragma once
+#include <hip/hip_runtime.h>
+
+namespace sb {
+
+// Block i of a head (i = 0 the longest) and block n-1-i form pair i, of the same causal cost for
+// every i; but how much of that cost a block is depends on how far its head's weights reach.
+// Workgroup ids go round the 8 XCDs and start in order as places come free.
+//
+// Longest first: every workgroup one block, block 0 of all heads, then block 1, ...  What runs last is
+// short.  The heads turn with i, so that no XCD is left with more of the costly heads than another: with
+// every block, or with every run of 2^run blocks.  Inside a run a head stays on one XCD, and its
+// blocks, which sweep the same tiles at the same time, find them in that XCD's L2.
+// Longest first against pairs (below), a third of the heads reaching far, us: forward B1 H32 T16384 d128
+// 940 / 1217, B8 H16 T4096 d128 331 / 615, query-stationary backward B8 H16 T2048 d64 142 / 170.
+//
+// In pairs: every workgroup a pair, every head on one XCD, slot s of the XCDs takes heads 8s .. 8s+7,
+// turned by s(s+1)/2.  Only the key-stationary kernel of d = 128, one workgroup per CU and nothing else
+// to hide a tile's latency, still takes it, from 128 kv heads on.  Pairs / longest first there, us, all
+// heads far, then a third: B8 H16 T4096 1309 / 1392, 660 / 715; B4 H32 T6144 2809 / 3024, 1242 / 1374;
+// B8 H20 T4096 1629 / 1763, 878 / 845; B8 H24 T2048 570 / 599, 415 / 384.  With fewer heads it still
+// wins where all reach far, but too little evens out where a third does: B7 H16 T4096 1153 / 1214,
+// 603 / 622; B4 H24 T4096 993 / 1033, 640 / 528; B2 H32 T8192 2398 / 2557, 1195 / 1082; B2 H24 T2048
+// 169 / 151, 123 / 96.
+struct Share {
+    int bh;                   // head
+    int i;                    // block, or with pairs pair
+};
+inline long share_grid(long heads, int nblk, bool pairs)
+{
+    return pairs ? 8L * ((heads + 7) / 8) * ((nblk + 1) / 2) : heads * nblk;
+}
+
+// log2 of the run, -1: turn with every block.  A run pays where the launch is several rounds deep and
+// there are enough runs to even the XCDs out: 32 of them, or 16 where 64 heads and more can be turned
+// among each other as well, by o(o+1)/2 inside each octet o of heads (over any 8 octets these are all 8
+// turns, so that heads which are costly in every batch entry do not meet on one XCD).  Query heads that
+// share a kv head have its tiles in every L2 already; in a packed batch a run is cut short by the
+// sequences' ends: both turn with every block.
+// Every block / runs, us, all heads far, then a third, then none: forward B8 H16 T4096 d128 698 / 669,
+// 331 / 329, 160 / 150; B1 H32 T16384 d128 2422 / 2266, 883 / 880, 165 / 154; B1 H24 T16384 d64 1078 / 1032,
+// 460 / 422, 65 / 56; query-stationary backward of the same three 1049 / 1032, 524 / 530, 309 / 304;
+// 3849 / 3762, 1410 / 1433, 319 / 312; 1828 / 1780, 774 / 725, 139 / 134.  Runs twice as long are
+// another 1 % faster where all heads reach far and up to 20 % slower where a third does (B8 H16 T4096: 393 us).
+// Smaller launches and odd head counts lose up to 20 % (B1 H27 T8192 d128: 224 / 284 with a third far).
+inline int share_run(long heads, int nblk)
+{
+    if (heads % 8 != 0 || heads * nblk < 1536 || nblk < (heads < 64 ? 64 : 32)) return -1;
+    int run = 1;
+    while (nblk >> (run + 1) >= 32) ++run;
+    return run;
+}
+
+// (unsigned: a division is half as long)
+__host__ __device__ __forceinline__ Share share_in_pairs(unsigned wg, int nblk)     // bh >= heads: nothing to do
+{
+    const unsigned npair = (unsigned)(nblk + 1) >> 1;
+    const unsigned slot = wg >> 3, s = slot / npair;
+    return {(int)(8 * s + ((wg + ((s * (s + 1)) >> 1)) & 7)), (int)(slot - s * npair)};
+}
+
+__host__ __device__ __forceinline__ Share share_of(unsigned wg, unsigned heads, int run)
+{
+    const unsigned i = wg / heads, w = wg - i * heads;
+    if (run < 0) return {(int)((heads & 1) ? w : w + i < heads ? w + i : (w + i) % heads), (int)i};
+    const unsigned turn = i >> run;                           // heads a multiple of 8 from here on
+    if (heads < 64) return {(int)(w + turn < heads ? w + turn : (w + turn) % heads), (int)i};
+    const unsigned o = w >> 3;
+    return {(int)(8 * o + ((w + turn + ((o * (o + 1)) >> 1)) & 7)), (int)i};
+}
+
+// the divisions above pass through vector registers: back into scalar ones, and with it everything
+// that a kernel derives from its share
+__device__ __forceinline__ Share in_scalars(Share s)
+{
+    return {__builtin_amdgcn_readfirstlane(s.bh), __builtin_amdgcn_readfirstlane(s.i)};
+}
+
+}  // namespace sb

@@ -1,0 +1,101 @@
+"""The order in which a launch hands its blocks to workgroups (csrc/sb_share.h), compiled for the host:
+every block once, neighbouring blocks of a head on one XCD, costly heads spread over the XCDs."""
+import itertools
+import os
+import random
+import shutil
+import subprocess
+
+import numpy as np
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2410_17980_amd", "csrc")
+HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+
+MAIN = r"""
+#include <stdio.h>
+#include "sb_share.h"
+int main(int argc, char** argv)
+{
+    int heads, nblk, pairs;
+    while (scanf("%d %d %d", &heads, &nblk, &pairs) == 3) {
+        const int grid = (int)sb::share_grid(heads, nblk, pairs), run = sb::share_run(heads, nblk);
+        printf("%d %d\n", grid, run);
+        for (int wg = 0; wg < grid; ++wg) {
+            const sb::Share s = pairs ? sb::share_in_pairs(wg, nblk) : sb::share_of(wg, heads, run);
+            printf("%d %d\n", s.bh, s.i);
+        }
+    }
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def order(tmp_path_factory):
+    if not shutil.which(HIPCC):
+        pytest.skip("no hipcc")
+    tmp = tmp_path_factory.mktemp("order")
+    (tmp / "main.hip").write_text(MAIN)
+    subprocess.run([HIPCC, "-std=c++17", "-O1", "--offload-host-only", f"-I{CSRC}", "main.hip", "-o", "main"],
+                   cwd=tmp, check=True, stdout=subprocess.DEVNULL, stderr=subprocess.DEVNULL)
+
+    def get(heads, nblk, pairs=False):
+        out = subprocess.run([str(tmp / "main")], input=f"{heads} {nblk} {int(pairs)}\n", text=True, check=True,
+                             stdout=subprocess.PIPE).stdout.split()
+        grid, run = int(out[0]), int(out[1])
+        return np.array(out[2:], dtype=np.int64).reshape(grid, 2), 1 << run if run >= 0 else 0
+    return get
+
+
+SHAPES = [(h, n) for h, n in itertools.product((1, 2, 3, 5, 7, 8, 9, 12, 24, 30, 32, 40, 63, 64, 65, 67, 72, 96, 128, 130, 512),
+                                               (1, 2, 3, 4, 12, 16, 31, 32, 33, 64, 128)) if h * n <= 16384]
+
+
+def test_every_block_once(order):
+    for heads, nblk in SHAPES:
+        got, _ = order(heads, nblk)
+        assert sorted(map(tuple, got)) == [(h, i) for h in range(heads) for i in range(nblk)], (heads, nblk)
+        assert np.all(np.diff(got[:, 1]) >= 0), "the longest blocks first"
+        pairs, _ = order(heads, nblk, True)
+        pairs = pairs[pairs[:, 0] < heads]
+        assert sorted(map(tuple, pairs)) == [(h, i) for h in range(heads) for i in range((nblk + 1) // 2)], (heads, nblk)
+
+
+def xcds(order, heads, nblk):
+    got, run = order(heads, nblk)
+    x = np.empty((heads, nblk), dtype=np.int64)
+    x[got[:, 0], got[:, 1]] = np.arange(len(got)) % 8
+    return x, run
+
+
+@pytest.mark.parametrize("heads,nblk,run", [(128, 32, 2), (64, 32, 2), (256, 64, 2), (64, 128, 4), (32, 128, 4), (24, 128, 4), (40, 64, 2)])
+def test_neighbouring_blocks_share_an_xcd(order, heads, nblk, run):
+    """Launches several rounds deep: a head moves to another XCD after a run of blocks only."""
+    x, got = xcds(order, heads, nblk)
+    assert got == run
+    assert (x[:, 1:] == x[:, :-1])[:, np.arange(1, nblk) % run != 0].all()
+
+
+@pytest.mark.parametrize("heads,nblk", [(9, 83), (8, 128), (12, 128), (30, 64), (95, 25), (96, 31), (65, 64), (512, 8), (40, 63)])
+def test_small_or_short_launches_turn_with_every_block(order, heads, nblk):
+    x, got = xcds(order, heads, nblk)
+    assert got == 0
+    assert (x[:, 1:] != x[:, :-1]).mean() >= 0.8
+
+
+def test_costly_heads_are_spread(order):
+    """Half of the heads of a layer reach far, the same ones in every batch entry (as in a real model),
+    the rest costs next to nothing: no XCD gets more than 1.35 times its share of the causal cost."""
+    rng = random.Random(1)
+    for B, H, nblk in ((8, 16, 32), (1, 32, 128), (8, 16, 16), (2, 32, 64), (4, 32, 32), (16, 32, 8)):
+        worst = []
+        for _ in range(40):
+            far = np.array([rng.random() < 0.5 for _ in range(H)])
+            if far.sum() < 8:
+                continue
+            x, _ = xcds(order, B * H, nblk)
+            cost = np.repeat(np.tile(far, B)[:, None], nblk, 1) * np.arange(nblk, 0, -1)
+            load = np.array([cost[x == c].sum() for c in range(8)])
+            worst.append(load.max() / load.mean())
+        assert np.mean(worst) <= 1.35, (B, H, nblk, np.mean(worst))
