@@ -41,6 +41,7 @@
 // the half-waves.  dZ feeds the "query-major" product (dQ) straight from
 // registers; for the "key-major" products (dK, dV) A and dZ are written to a small
 // per-wave LDS scratch row-wise and read back with the transposing load.
+#include <algorithm>
 #include <type_traits>
 
 #include "sb_kernels.h"
@@ -956,10 +957,17 @@ bwd_dkv_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
 // wave of a SIMD is in its vector phase while the other is in its matrix phase) is slower,
 // 1.47 ms: the compiler then copies the accumulator (64 registers) on every switch.
 // KS: strips per block, 4 or, in small grids, 2: what bounds a launch there is one block's chain of
-// intervals, and with one wave per SIMD in place of two an interval is shorter.  Backward with 128 /
-// 64 keys a block, us: B4 H12 Hkv4 T2048 (256 blocks of 128) 267 / 217, B2 H16 Hkv8 T3000 (384) 289 / 240,
-// B1 H16 T4096 (512) 268 / 262, B8 H16 Hkv4 T2048 (512) 426 / 438, B2 H16 T4096 (1024) 313 / 366.
-constexpr long SMALL_KV_GRID = 384;
+// intervals, and with one wave per SIMD in place of two an interval is shorter.  Where the 128-key blocks
+// outnumber the CUs this costs more rounds than it saves, except with long chains and heads of mixed
+// reach.  Key-stationary pass with 128 / 64 keys a block, us, all heads far, then a third:
+//   up to 256 blocks   B1 H20 T1024 (160) 40 / 31, 40 / 31; B1 H16 T2048 (256) 69 / 64, 67 / 50;
+//                      B8 H16 T256 (256) 33 / 28, 33 / 27; B1 H8 T4096 (256) 123 / 108, 120 / 88
+//   more, short heads  B2 H20 T1024 (320) 44 / 56, 42 / 46; B2 H16 T1280 (320) 50 / 62, 48 / 47;
+//                      B3 H32 T512 (384) 39 / 48, 39 / 47; B1 H24 T2048 (384) 78 / 97, 68 / 70
+//   more, long heads   B1 H20 T2048 (320) 71 / 83, 68 / 58; B1 H16 T3072 (384) 105 / 128, 94 / 79;
+//                      B1 H12 T4096 (384) 138 / 164, 121 / 89; B1 H3 T16384 (384) 499 / 579, 439 / 318
+//   beyond             B1 H14 T4096 (448) 152 / 185, 121 / 105; B1 H16 T4096 (512) 172 / 209, 121 / 116
+constexpr long small_kv_grid(int nkb) { return std::clamp(64L + 16L * nkb, 256L, 384L); }
 template <int D, int KS> struct Dkv3Cfg {
     static constexpr int NW2 = 2 * KS;
     static constexpr int KEYS = 32 * KS;
@@ -1475,7 +1483,7 @@ hipError_t launch_one(const uint16_t* q, const uint16_t* k, const uint16_t* v, c
 // is faster there (measured).
 #define SB_DKV(GQAV)                                                                                            \
     if constexpr (D == 128) {                                                                                   \
-        if (BHkv * (long)nkb <= SMALL_KV_GRID) {                                                                \
+        if (BHkv * (long)nkb <= small_kv_grid(nkb)) {                                                           \
             SB_LAUNCH(share_grid(BHkv, nkb64, false), 256, (bwd_dkv_pair_kernel<D, 2, GQAV, VL>),               \
                       q, k, v, dout, ca, cb, dk, dv, first, T, BHkv, H, G, nkb64, nqb, nt32, cu, Ttot, 0);      \
         } else {                                                                                                \
