@@ -22,11 +22,13 @@
 //       chunks up, in a fixed order.  (Done by the last workgroup of the second launch to arrive
 //       instead, it cost more: 14 % of B8 H16 T16384 d128 in stores and counters each workgroup
 //       waits for, 10 us at B1 H8 Hkv1 T30000 d64 for one workgroup to add what eight can.)
-// Exhaustion does not end a pass that has to return m, the log of the stick left over all keys.
+// Exhaustion does not end a pass that has to return m, the log of the stick left over all keys: the second
+// launch then takes the nearest keys as well.
 //
-// Measured with a third of the kv heads reaching far / all of them (before this split: 180, 55, 41, 54
-// us either way): B8 H16 T16384 d128 69 / 168 us (all keys at 6.4 TB/s), B1 H32 Hkv8 T65000 d128
-// 30 / 55, B32 H16 T1500 d64 25 / 35, B16 H32 Hkv8 T4096 d128 28 / 56.
+// Measured without m, a third of the kv heads reaching far / all of them / all keys in one pass over the
+// chip, whatever they take (this kernel's predecessor), us: B8 H16 T16384 d128 68 / 167 / 180 (all keys at
+// 6.4 TB/s), B1 H32 Hkv8 T65000 d128 29 / 54 / 47, B32 H16 T1800 d64 34 / 50 / 37, B16 H32 Hkv8 T4096 d128
+// 28 / 55 / 45: where every head reaches far the launch in front is 5 to 13 us lost.
 #include <algorithm>
 #include <mutex>
 #include <type_traits>
@@ -46,7 +48,9 @@ constexpr int GMAX = 16;               // query heads of a group per workgroup: 
 constexpr int ALONE = 6 * NEAR;        // caches up to here take the first launch only (6 us + 1.3 us a pass; two launches 15 us)
 constexpr int COMBINE_THREADS = 256;
 constexpr int MAXFAR = 127;            // chunks beyond the nearest keys: with those, two per lane of a wave
-constexpr long FAR_WGS = 2048;      // workgroups of the second launch, all heads together
+constexpr int FAR_KEYS = KW * FAR_NW;  // keys of a pass of the second launch
+constexpr long FAR_WGS = 2048;         // workgroups of the second launch, all heads together
+constexpr long ALL_WGS = 8192;         // the same where it takes all keys (see split_of())
 
 
 // sum of v over the lanes above this one, and over all lanes in `total`
@@ -120,7 +124,7 @@ decode_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, co
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l16 = lane & 15, lq = lane >> 4;
-    const int nch = nfar + 1;              // chunk nfar: the nearest keys
+    const int nch = nfar + (near > 0);     // chunk nfar: the nearest keys, where they have a launch of their own
     const int chunk = FAR ? blockIdx.x : nfar;
     const int kend = FAR ? min(T - near, (chunk + 1) * C) : T;
     const int k0 = FAR ? chunk * C : T - near;
@@ -321,18 +325,24 @@ int room(int T)
     return (T + C - 1) / C;
 }
 
-// How the keys are split: the nearest in the first launch, the rest in nfar chunks of C.
+// How the keys are split: the nearest in the first launch, the rest in nfar chunks of C, whole passes of
+// either kernel.  With m wanted every key is read whatever the nearest ones take: they need no launch of
+// their own, and as no workgroup is let off, more and smaller chunks even the CUs out.  With m, us: three
+// launches / two with the same chunks / two with these: B16 H32 Hkv8 T4096 d128 55 / 49 / 48, B32 H16 T1800 d64
+// 49 / 43 / 39, B1 H32 Hkv8 T65000 d128 53 / 46 / 46, B8 H16 T16384 d128 167 / 161 / 162, B1 H8 T2000 d64
+// 12.8 / 9.4 / 6.7.
 struct Split {
     int near, C, nfar;
+    int chunks() const { return nfar + (near > 0); }
 };
-Split split_of(long wgs, int T)
+Split split_of(long wgs, int T, bool want_m)
 {
     Split s = {T, NEAR, 0};
     if (T <= ALONE) return s;
-    s.near = NEAR;
-    const int far = T - s.near;
-    const long want = std::min((long)std::min(MAXFAR, room(T) - 1), std::max(1L, FAR_WGS / wgs));
-    s.C = (int)((far + want - 1) / want + NEAR - 1) / NEAR * NEAR;         // whole passes of either kernel
+    s.near = want_m ? 0 : NEAR;
+    const int far = T - s.near, unit = want_m ? FAR_KEYS : NEAR;
+    const long want = std::min((long)std::min(MAXFAR, room(T) - 1), std::max(1L, (want_m ? ALL_WGS : FAR_WGS) / wgs));
+    s.C = (int)((far + want - 1) / want + unit - 1) / unit * unit;
     s.nfar = (far + s.C - 1) / s.C;
     return s;
 }
@@ -343,20 +353,23 @@ hipError_t launch_d(const uint16_t* q, const uint16_t* k, const uint16_t* v, con
 {
     const int G = H / Hkv;
     const int nz = (G + GMAX - 1) / GMAX;
-    const Split s = split_of((long)B * Hkv * nz, T);
+    const Split s = split_of((long)B * Hkv * nz, T, m != nullptr);
     const long heads = (long)B * H;
-    float* part_o = workspace;                                            // [heads][nfar + 1][D]
-    float* part_a = part_o + heads * (s.nfar + 1) * D;                    // [heads][nfar + 1]
-    hipLaunchKernelGGL((decode_kernel<D, false>), dim3((unsigned)(B * Hkv), 1u, (unsigned)nz), dim3(64 * NEAR_NW), 0, stream,
-                       q, k, v, rb, o, m, part_o, part_a, T, Tcap, H, G, s.near, s.C, s.nfar);
-    hipError_t e = hipGetLastError();
+    float* part_o = workspace;                                            // [heads][chunks][D]
+    float* part_a = part_o + heads * s.chunks() * D;                      // [heads][chunks]
+    hipError_t e = hipSuccess;
+    if (s.near > 0) {
+        hipLaunchKernelGGL((decode_kernel<D, false>), dim3((unsigned)(B * Hkv), 1u, (unsigned)nz), dim3(64 * NEAR_NW), 0, stream,
+                           q, k, v, rb, o, m, part_o, part_a, T, Tcap, H, G, s.near, s.C, s.nfar);
+        e = hipGetLastError();
+    }
     if (e != hipSuccess || s.nfar == 0) return e;
     hipLaunchKernelGGL((decode_kernel<D, true>), dim3((unsigned)s.nfar, (unsigned)(B * Hkv), (unsigned)nz), dim3(64 * FAR_NW), 0, stream,
                        q, k, v, rb, o, m, part_o, part_a, T, Tcap, H, G, s.near, s.C, s.nfar);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL((decode_combine_kernel<D>), dim3((unsigned)heads), dim3(COMBINE_THREADS), 0, stream,
-                       part_o, part_a, rb, o, m, H, s.nfar + 1);
+                       part_o, part_a, rb, o, m, H, s.chunks());
     return hipGetLastError();
 }
 
