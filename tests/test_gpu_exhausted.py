@@ -163,3 +163,84 @@ def test_halt_after_the_first_tile_behind_the_band(sb, gen, T, d):
     assert of == H * full
     ragged = T % 128 != 0                        # the last block, whose band may be one tile: a trip more
     assert H * want <= swept <= H * (want + 2 * ragged), (swept, H * want)
+
+
+def mixed_grouped(gen, B, H, Hkv, T, d, seed):
+    """kv heads by turns as in mixed(); of the query heads on a far one every second is near all the same."""
+    qk, k, v = mixed(gen, B, Hkv, T, d, seed)
+    q, _, _, g = gen.gaussian(B, H, T, d, seed=seed + 5, dtype="bf16", with_dout=True)
+    q, G = q.clone(), H // Hkv
+    for h in range(2, Hkv, 3):
+        q[:, h * G:(h + 1) * G] = qk[:, h:h + 1]
+        q[:, h * G + 1:(h + 1) * G:2, :, d - 1] = 0.0
+    return q, k, v, g
+
+
+def check_heads(got, refs):
+    for name, a, r in zip(("dq", "dk", "dv", "dr"), got, refs):
+        a, heads = to64(a), r.shape[-3] if name != "dr" else 1
+        for h in range(heads):
+            check_grad(f"{name} head {h}", a[..., h, :, :] if name != "dr" else a, r[..., h, :, :] if name != "dr" else r)
+
+
+def test_mixed_grouped_reaches(gen):
+    """The inputs do what the tests below need: of two query heads on one far kv head one is exhausted
+    within 400 keys, the other keeps most of its stick."""
+    q, k, _, _ = mixed_grouped(gen, 1, 6, 3, 600, 64, seed=1)
+    sp = lambda h: np.logaddexp(0.0, to64(q[0, h, -1]) @ to64(k[0, 2]).T / 8.0)
+    assert sp(4)[200:].sum() < 10.0 and sp(5)[200:].sum() > 112.0
+
+
+@pytest.mark.parametrize("T", [1025, 1300])
+@pytest.mark.parametrize("d", [32, 64, 128])
+def test_backward_grouped_with_bias(sb, oracle, gen, T, d):
+    """Every query head of a group has a start tile of its own."""
+    q, k, v, g = mixed_grouped(gen, 1, 6, 3, T, d, seed=900 + T)
+    r = gen.remainder_embedding(6, d, seed=3)
+    qd, kd, vd, gd, rd = dev(q, k, v, g, r)
+    o, m = sb.sb_attn_fwd_gqa(qd, kd, vd, r=rd)
+    got = sb.sb_attn_bwd_gqa(qd, kd, vd, m, gd, r=rd, workspace=nan_bytes(sb.sb_attn_bwd_workspace_bytes(1, 6, T, d)))
+    torch.cuda.synchronize()
+    q64, k64, v64, g64, r64 = (to64(t) for t in (q, k, v, g, r))
+    ref, rem = oracle.fwd_gqa(q64, k64, v64, r=r64)
+    assert np.all(np.abs(to64(o) - ref) <= fwd_bound(ref, v64))
+    check_m(to64(m), rem)
+    check_heads(got, oracle.bwd_gqa(q64, k64, v64, g64, r=r64))
+
+
+@pytest.mark.parametrize("lens,max_T", [([1100, 40, 0, 1300, 513], 1300), ([700, 1025], 1725)])
+@pytest.mark.parametrize("d", [32, 64, 128])
+def test_backward_packed(sb, oracle, gen, lens, max_T, d):
+    """Start tiles of sequences that lie one behind the other, also with a bound that is too long."""
+    H, Hkv, Ttot = 6, 3, sum(lens)
+    q, k, v, g = (t[0] for t in mixed_grouped(gen, 1, H, Hkv, Ttot, d, seed=950 + d))
+    r = gen.remainder_embedding(H, d, seed=4)
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    qd, kd, vd, gd, rd = dev(q, k, v, g, r)
+    cud = torch.from_numpy(cu).cuda()
+    o, m = sb.sb_attn_varlen_fwd(qd, kd, vd, cud, max_T, r=rd)
+    ws = nan_bytes(sb.sb_attn_varlen_bwd_workspace_bytes(len(lens), H, Ttot, max_T, d))
+    got = sb.sb_attn_varlen_bwd(qd, kd, vd, m, gd, cud, max_T, r=rd, workspace=ws)
+    torch.cuda.synchronize()
+    q64, k64, v64, g64, r64 = (to64(t) for t in (q, k, v, g, r))
+    ref, rem = oracle.fwd_varlen(q64, k64, v64, cu, r=r64)
+    assert np.all(np.abs(to64(o) - ref) <= fwd_bound(ref, v64))
+    check_m(to64(m), rem)
+    check_heads(got, oracle.bwd_varlen(q64, k64, v64, g64, cu, r=r64))
+
+
+@pytest.mark.parametrize("B,H,Hkv,T", [(8, 16, 16, 640), (8, 16, 16, 1025), (16, 16, 8, 700), (2, 20, 20, 1000), (1, 32, 32, 1100)])
+def test_backward_of_many_heads(sb, oracle, gen, B, H, Hkv, T):
+    """d = 128: from 128 kv heads on blocks in pairs; 320 and 288 blocks of 128 keys, more than CUs but
+    short heads; heads of all reaches at both ends of the grid."""
+    d = 128
+    q, k, v, g = mixed_grouped(gen, B, H, Hkv, T, d, seed=1000 + T)
+    qd, kd, vd, gd = dev(q, k, v, g)
+    _, m = sb.sb_attn_fwd_gqa(qd, kd, vd)
+    got = sb.sb_attn_bwd_gqa(qd, kd, vd, m, gd, workspace=nan_bytes(sb.sb_attn_bwd_workspace_bytes(B, H, T, d)))
+    torch.cuda.synchronize()
+    G = H // Hkv
+    for b, h in ((0, 0), (0, 1), (0, 2), (B // 2, 2), (B - 1, Hkv - 2), (B - 1, Hkv - 1)):
+        qs, ks = slice(h * G, (h + 1) * G), slice(h, h + 1)
+        one = oracle.bwd_gqa(*(to64(t) for t in (q[b:b + 1, qs], k[b:b + 1, ks], v[b:b + 1, ks], g[b:b + 1, qs])))
+        check_heads((got[0][b:b + 1, qs], got[1][b:b + 1, ks], got[2][b:b + 1, ks]), one)
