@@ -23,6 +23,12 @@
  *     synchronisation.  The return value is an sb_status (0 = ok, negative =
  *     error, nothing was enqueued).  Nothing is thrown across the boundary.
  *   - Outputs are written for every row, including the all-zero row j = 0.
+ *   - NaN and infinities reach every result that gives them a weight other than zero (in m a NaN
+ *     logit counts as one of 128 log 2).  Through a zero weight they may or may not: inside the
+ *     32 x 32 strip on the diagonal a masked weight is a zero that v and dout are multiplied with,
+ *     and once a row has less than 2^-160 of its stick left every farther weight is zero in fp32
+ *     and its terms (v, k where m is not asked for, dout in dk, dv and dr) are left out from
+ *     wherever the row's block stopped.  With finite inputs no bit of a result depends on that.
  */
 #ifndef SB_ATTN_H
 #define SB_ATTN_H
@@ -60,7 +66,7 @@ int sb_attn_fwd(const void* q, const void* k, const void* v, void* o,
  * than what is left, so |o_j - exact o_j| <= eps * max_i |v_i| per component.
  * 0 < eps < 1 (SB_ERR_SHAPE otherwise).  How much is skipped depends on the data.
  * tile_counts: optional (may be NULL) device pointer to 2 x u64, 16-byte aligned;
- * the call ADDS to [0] the 64-key tiles swept beyond the diagonal band and to [1]
+ * the call ADDS to [0] the 64-key tiles swept (the diagonal band among them) and to [1]
  * the tiles a full sweep would take (per 128-row block), for reporting.
  */
 int sb_attn_fwd_halt(const void* q, const void* k, const void* v, void* o,
@@ -76,8 +82,8 @@ int sb_attn_fwd_train(const void* q, const void* k, const void* v, void* o, floa
                       int B, int H, int T, int d, void* stream);
 
 /*
- * fp32 forward (fp32 q, k, v, o, optional m; all arithmetic fp32 on the vector
- * ALU).  m may be NULL.
+ * fp32 forward (fp32 q, k, v, o, optional m; all arithmetic fp32, both products on the
+ * fp32 matrix instructions).  m may be NULL.
  */
 int sb_attn_fwd_f32(const float* q, const float* k, const float* v, float* o, float* m,
                     int B, int H, int T, int d, void* stream);
@@ -90,8 +96,8 @@ int sb_attn_fwd_f32(const float* q, const float* k, const float* v, float* o, fl
  * workspace: caller-owned device scratch of at least
  * sb_attn_bwd_workspace_bytes(B,H,T,d) bytes, 16-byte aligned; its contents on
  * entry do not matter and are garbage afterwards.  It holds two floats per
- * (query row, 32-key strip), one int per 128-row block of queries and of keys and
- * d floats per 128-row block (partial sums of sb_attn_bwd_rb's dr):
+ * (query row, 32-key strip), two ints per 128-row block (the first is where the block's sweep
+ * starts, the second is unused) and d floats per 128-row block (partial sums of sb_attn_bwd_rb's dr):
  * B*H*(8*T*ceil(T/32) + (8 + 4*d)*ceil(T/128)) bytes.  SB_ERR_WORKSPACE if it is NULL or
  * too small.  sb_attn_bwd_workspace_bytes returns 0 for a bad shape.
  * The carried sums make the workspace grow with T^2 (T^2/4 bytes per head: 4 MiB at

@@ -1358,7 +1358,7 @@ bwd_dkv_pair_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
 // dr[h][c] = sum over the batch and the rows j of exp(m_j) dO[j][c] (Appendix C: the
 // output holds (stick left of row j) * r_h).  Two deterministic steps: per (batch entry,
 // head, 128-row chunk) partial sums, then one workgroup per head adds them in a fixed order.
-// Rows that used up their stick (exp(m) = 0 in fp32) are not read.  Both steps are a few memory
+// Rows that used up their stick (exp(m) = 0 in fp32) are not read (nor is a NaN in them).  Both steps are a few memory
 // latencies long, all loads of a thread in flight at once (B4 H12 T2048 d128: 31 -> 11 us; with a
 // thread per column walking over the chunks one by one the second step alone took 18).
 constexpr int DR_ROWS = 128;

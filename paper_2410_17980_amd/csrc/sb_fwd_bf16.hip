@@ -38,11 +38,13 @@
 // is -log2 of the stick it has left, and no weight of a farther key can exceed 2^-carry.
 // From CARRY_EXHAUSTED = 160 on every farther weight IS zero in this arithmetic (the smallest
 // nonzero bf16 is 2^-133, the smallest nonzero fp32 2^-149), so once every row of a query
-// block is there, the rest of the sweep cannot change a bit of o.  Without m the block stops;
-// with m, which needs the softplus total over all keys, it goes on with the logits alone (no
-// V, no A V: sum_tail()).  Rows whose weights reach far never get there and pay two scalar
-// compares a tile.  sb_attn_fwd_halt is the same kernel with the caller's threshold -log2(eps)
-// in place of 160; its error is at most eps * max|v|.
+// block is there, the rest of the sweep cannot change a bit of o (for finite inputs: a NaN in V
+// would come through a zero weight, and does not where its tile is left out).  Without m the
+// block stops; with m, which needs the softplus total over all keys, it goes on with the logits
+// alone (no V, no A V: sum_tail()).  Rows whose weights reach far never get there and pay, every
+// two tiles, a ballot, an LDS write per wave and a read of four flags behind the barrier.
+// sb_attn_fwd_halt is the same kernel with the caller's threshold -log2(eps) in place of 160;
+// its error is at most eps * max|v|.
 #include <type_traits>
 
 #include "sb_kernels.h"
