@@ -8,7 +8,8 @@ workload (bf16, B=8, H=16, T=4096, d_head=128; half the heads with k*3): the
 training forward (o and m) followed by the backward (dq, dk, dv).  Inputs are
 resident in HBM before the timed region starts.  One JSON line is printed:
 whole-step TFLOP/s as `value`, the forward and the two backward passes separately,
-a roofline object for the dominant kernel, every one of the five stated
+the same on inputs where no work can be left out, a roofline object for that
+run's dominant kernel, every one of the five stated
 workloads with its own timing and its error against the CPU oracle (`configs`),
 the rate the matrix cores sustain on such data with no other work (the practical
 ceiling under the power limit), the vendor GEMM at a large square shape and the
@@ -20,6 +21,12 @@ FLOP convention (algorithmic, strictly causal pairs only): one contraction is
 backward = 5 (query-stationary pass: logits, dO.v, dQ = 3; key-stationary pass:
 dK, dV = 2, its recomputation of the first two is not counted).  Nothing else
 (masked halves of diagonal tiles, recomputation, element-wise work) is counted.
+The kernels leave out terms whose weight is zero in fp32, and on the workload's
+data (every stick is used up within tens of keys) those are most of them: `value`
+and the rates of `fwd`, `bwd`, `configs` are EFFECTIVE rates, all pairs' operations
+over the time, and may exceed what the hardware can execute.  `full_sweep` times the
+same step on long-range inputs, where no term can be left out, and `roofline`
+is of that run: these are achieved rates.
 
 `roofline.traffic` (HBM bytes per launch of the dominant kernel) comes from
 rocprofv3 counter runs that cannot be made from inside this script; it is read
@@ -84,7 +91,7 @@ def spread(ts):
 
 
 TRAFFIC_FILE = os.path.join("profiles", "hbm_traffic_B8_H16_T4096_d128.txt")
-KERNEL_SOURCES = ("sb_fwd_bf16.hip", "sb_bwd_bf16.hip", "sb_decode.hip", "sb_mma.h")
+KERNEL_SOURCES = ("sb_fwd_bf16.hip", "sb_bwd_bf16.hip", "sb_decode.hip", "sb_mma.h", "sb_share.h")
 
 
 def source_fingerprint(name):
@@ -248,32 +255,32 @@ def config_entries(sb, inputs, iters, headline):
             e["max_abs_err"], e["tol"] = max(errs.values()), 2e-2
             e["max_abs_err_by_tensor"], e["max_err_over_max_ref"] = errs, rels
         tf = flop / (st["ms"] * 1e-3) / 1e12
-        e.update({"flop": flop, **st, "tflops": tf, "frac_bf16_peak": tf / PEAK_BF16_TFLOPS,
+        e.update({"flop": flop, **st, "effective_tflops": tf, "effective_frac_bf16_peak": tf / PEAK_BF16_TFLOPS,
                   "ok": bool(e["max_abs_err"] <= e["tol"])})
         if w.dtype == "f32":
-            e["note"] = "vector-ALU fp32 check path, latency-bound at this size: not a matrix-core rate"
-        if w.dtype == "bf16" and w.direction == "fwd" and d == 64:
-            # At d = 64 the element-wise path outweighs the matrix work of a subtile: per MFMA 14.3
-            # vector instructions, 2.25 of them transcendental (profiles/counters_fwd_B8_H16_T2048_d64.md).
-            # At the published vector rate (157.3 TFLOP/s fp32 = one 64-lane instruction per 2 clocks per
-            # SIMD, transcendentals a quarter of that) a 32x32 subtile (8 MFMAs = 256 matrix clocks) needs
-            # 8 * (12.05 * 2 + 2.25 * 8) = 337 vector clocks: the vector ALU is the binding roof.
-            alu_clk, pairs = 8 * ((14.3 - 2.25) * 2.0 + 2.25 * 8.0), 1024
-            alu_roof = 4.0 * d * pairs / alu_clk * 1024 * 2.4e9 / 1e12
-            e["alu_roof"] = {"bound": "alu", "peak": alu_roof, "unit": "TFLOP/s", "frac": tf / alu_roof,
-                             "what": "vector-ALU clocks of a 32x32 subtile at the published fp32 vector rate, "
-                                     "instruction counts from the rocprofv3 counters of this kernel"}
+            e["note"] = "full-precision check path, latency-bound at this size: not a matrix-core rate"
         out.append(e)
     return out
 
 
-def run_one_config(sb, inputs, n, iters, calibrate_copy=False):
+def long_range(inputs, w):
+    """q, k, v, dout of a workload's shape with logits about N(-6,1): the stick lasts for hundreds to
+    thousands of keys and no term of the sweep is zero."""
+    return [t.cuda() for t in inputs.biased_gaussian(w.B, w.H, w.T, w.d, seed=w.seed, shift=-6.0, with_dout=True)]
+
+
+def run_one_config(sb, inputs, n, iters, calibrate_copy=False, far=False, with_bwd=False):
     """One stated workload on its own (training forward, plus the backward for the backward
-    workload), launched `iters` times: the command a rocprofv3 run of that shape wraps."""
+    workload or on request), launched `iters` times: the command a rocprofv3 run of that shape wraps."""
     import torch
     w = inputs.WORKLOADS[n - 1]
     B, H, T, d = w.B, w.H, w.T, w.d
-    ts = [t.cuda() for t in inputs.workload_tensors(w)]
+    if far:
+        ts = long_range(inputs, w)
+    elif with_bwd and w.direction == "fwd":
+        ts = [t.cuda() for t in inputs.gaussian(B, H, T, d, w.seed, w.dtype, w.sharp_half, with_dout=True)]
+    else:
+        ts = [t.cuda() for t in inputs.workload_tensors(w)]
     q, k, v = ts[:3]
     if calibrate_copy:
         src = torch.empty(1 << 30, dtype=torch.uint8, device="cuda").fill_(1)
@@ -287,7 +294,7 @@ def run_one_config(sb, inputs, n, iters, calibrate_copy=False):
         fn = lambda: sb.sb_attn_fwd_f32(q, k, v, o)
     else:
         m = torch.empty((B, H, T), dtype=torch.float32, device="cuda")
-        if w.direction == "fwd":
+        if w.direction == "fwd" and not with_bwd:
             fn = lambda: sb.sb_attn_fwd_train(q, k, v, o, m)
         else:
             dq = torch.empty((B, H, T, d), dtype=torch.float32, device="cuda")
@@ -314,6 +321,8 @@ def main():
     ap.add_argument("--only-config", type=int, default=0, metavar="N",
                     help="profiling aid: run only stated workload N (1-5) --kernel-iters times, print its timing "
                          "and exit (what a rocprofv3 run of one of the other shapes wraps)")
+    ap.add_argument("--long-range", action="store_true", help="with --only-config: long-range inputs of that shape")
+    ap.add_argument("--with-bwd", action="store_true", help="with --only-config: forward and backward")
     ap.add_argument("--calibrate-copy", action="store_true",
                     help="also run a plain 1 GiB element-wise copy kernel (3 times): the known traffic the "
                          "FETCH_SIZE / WRITE_SIZE counters of a rocprofv3 --pmc run are scaled by")
@@ -332,7 +341,8 @@ def main():
     torch.cuda.set_device(0)
 
     if args.only_config:
-        print(json.dumps(run_one_config(sb, inputs, args.only_config, args.kernel_iters, args.calibrate_copy)))
+        print(json.dumps(run_one_config(sb, inputs, args.only_config, args.kernel_iters, args.calibrate_copy,
+                                        args.long_range, args.with_bwd)))
         return
 
     w = inputs.WORKLOADS[2]
@@ -401,14 +411,21 @@ def main():
     ms_inf = event_time_ms(lambda: sb.sb_attn_fwd(qd, kd, vd, o), args.kernel_iters)
     ms_halt = event_time_ms(lambda: sb.sb_attn_fwd_halt(qd, kd, vd, 1e-9, o), args.kernel_iters)
 
-    # the same on long-range inputs (logits around -6: the stick lasts for hundreds of keys)
-    ql, kl, vl = (t.cuda() for t in inputs.biased_gaussian(B, H, T, d, seed=w.seed, shift=-6.0))
+    # the same, and the step's kernels, on long-range inputs: no term can be left out
+    ql, kl, vl, gl = long_range(inputs, w)
+    full_kernels = {"fwd_bf16_kernel": (event_time_ms(lambda: sb.sb_attn_fwd_train(ql, kl, vl, o, m), args.kernel_iters), f_fwd)}
+    if with_bwd:
+        full_kernels["bwd_dq_kernel"] = (
+            event_time_ms(lambda: sb.sb_attn_bwd_dq(ql, kl, vl, m, gl, dq, ws), args.kernel_iters), 0.6 * f_bwd)
+        full_kernels["bwd_dkv_pair_kernel" if d == 128 else "bwd_dkv_kernel"] = (
+            event_time_ms(lambda: sb.sb_attn_bwd_dkdv(ql, kl, vl, gl, ws, dk, dv), args.kernel_iters), 0.4 * f_bwd)
     counts.zero_()
     sb.sb_attn_fwd_halt(ql, kl, vl, 1e-9, o, counts)
     swept_l, full_l = counts.cpu().tolist()
     ms_inf_l = event_time_ms(lambda: sb.sb_attn_fwd(ql, kl, vl, o), args.kernel_iters)
     ms_halt_l = event_time_ms(lambda: sb.sb_attn_fwd_halt(ql, kl, vl, 1e-9, o), args.kernel_iters)
-    del ql, kl, vl
+    del ql, kl, vl, gl
+    fwd()                                  # o and m of the workload again
 
     # single-token decode (NOT part of the step or of `value`): one query per head against a
     # cache of 16384 tokens; bound by HBM bandwidth, K and V are read once
@@ -421,6 +438,9 @@ def main():
     o1 = torch.empty_like(q1)
     wsd = torch.empty(sb.load().sb_attn_decode_workspace_bytes(B, H, Td, d), dtype=torch.uint8, device="cuda")
     ms_dec = event_time_ms(lambda: sb.sb_attn_decode(q1, kc, vc, o=o1, workspace=wsd), 3 * args.kernel_iters)
+    # with m wanted every key is read, whatever the nearest ones take
+    m1 = torch.empty((B, H), dtype=torch.float32, device="cuda")
+    ms_dec_all = event_time_ms(lambda: sb.sb_attn_decode(q1, kc, vc, o=o1, m=m1, workspace=wsd), 3 * args.kernel_iters)
     dec_bytes = 2.0 * B * H * Td * d * 2
     # what a kernel that only reads the same number of bytes reaches (K and V together)
     kv_all = torch.cat([kc.reshape(-1), vc.reshape(-1)])
@@ -451,9 +471,9 @@ def main():
     gemm_tf = 2.0 * n_g ** 3 / (ms_gemm * 1e-3) / 1e12
     del ga, gb, gc
 
-    # dominant kernel = the one with the largest share of the step
-    dom = max(kernels, key=lambda n: kernels[n][0])
-    dom_ms, dom_flop = kernels[dom]
+    # dominant kernel = the one with the largest share of the full sweep's step
+    dom = max(full_kernels, key=lambda n: full_kernels[n][0])
+    dom_ms, dom_flop = full_kernels[dom]
     dom_tf = dom_flop / (dom_ms * 1e-3) / 1e12
 
     out = {
@@ -471,27 +491,41 @@ def main():
         "data": "synthetic",
         "config": {"workload": "train_step_bf16_B8_H16_T4096_d128", "B": B, "H": H, "T": T, "d_head": d,
                    "inputs": "iid N(0,1) bf16, heads h>=H/2 with k*3, seed 2",
-                   "step": "fwd_train + bwd" if with_bwd else "fwd_train", "early_halt": "off"},
-        "fwd": {"ms": ms_fwd, "tflops": tf_fwd, "frac_bf16_peak": tf_fwd / PEAK_BF16_TFLOPS, **sp_fwd},
-        "bwd": {"ms": ms_bwd, "tflops": tf_bwd, "frac_bf16_peak": tf_bwd / PEAK_BF16_TFLOPS,
+                   "step": "fwd_train + bwd" if with_bwd else "fwd_train",
+                   "zero_weights": "terms whose weight is zero in fp32 are left out (exact); no halting threshold"},
+        "rates": "value, fwd, bwd and configs: effective (all causal pairs' operations / time); full_sweep and "
+                 "roofline: achieved (inputs on which no term is left out)",
+        "fwd": {"ms": ms_fwd, "effective_tflops": tf_fwd, "effective_frac_bf16_peak": tf_fwd / PEAK_BF16_TFLOPS, **sp_fwd},
+        "bwd": {"ms": ms_bwd, "effective_tflops": tf_bwd, "effective_frac_bf16_peak": tf_bwd / PEAK_BF16_TFLOPS,
                 "dq_pass_ms": ms_dq, "dkdv_pass_ms": ms_dkdv, **sp_bwd} if with_bwd else None,
         "roofline": {"bound": "mfma", "kernel": dom, "achieved": dom_tf, "peak": PEAK_BF16_TFLOPS,
                      "unit": "TFLOP/s", "frac": dom_tf / PEAK_BF16_TFLOPS, "avg_launch_ms": dom_ms,
-                     "flop_per_launch": dom_flop, "traffic": hbm_traffic(dom)},
-        "early_halt": {"eps": 1e-9, "ms_full_sweep": ms_inf, "ms_halted": ms_halt, "speedup": ms_inf / ms_halt,
+                     "flop_per_launch": dom_flop, "inputs": "long range: every term of the sweep counts",
+                     "avg_launch_ms_on_workload": kernels[dom][0], "traffic": hbm_traffic(dom + "/full_sweep"),
+                     "traffic_on_workload": hbm_traffic(dom)},
+        "full_sweep": {"inputs": "N(0,1) q, k, v with a bias coordinate: logits about N(-6,1)",
+                       "ms": sum(t for t, _ in full_kernels.values()),
+                       "tflops": sum(f for _, f in full_kernels.values()) / sum(t for t, _ in full_kernels.values()) / 1e9,
+                       "kernels": {n: {"ms": t, "tflops": f / t / 1e9, "frac_bf16_peak": f / t / 1e9 / PEAK_BF16_TFLOPS,
+                                       "frac_mfma_only_ceiling": f / t / 1e9 / mfma_tf}
+                                   for n, (t, f) in full_kernels.items()}},
+        "early_halt": {"eps": 1e-9, "ms_no_threshold": ms_inf, "ms_halted": ms_halt, "speedup": ms_inf / ms_halt,
                        "tiles_swept_frac": swept / max(full, 1),
-                       "note": "sb_attn_fwd_halt vs sb_attn_fwd (forward without m); depends on the data: "
-                               "N(0,1) logits exhaust the stick within a few dozen keys"},
-        "early_halt_long_range": {"eps": 1e-9, "ms_full_sweep": ms_inf_l, "ms_halted": ms_halt_l,
+                       "note": "sb_attn_fwd_halt vs sb_attn_fwd (forward without m, which stops where every farther "
+                               "weight is zero); depends on the data: N(0,1) logits exhaust the stick within a "
+                               "few dozen keys"},
+        "early_halt_long_range": {"eps": 1e-9, "ms_no_threshold": ms_inf_l, "ms_halted": ms_halt_l,
                                   "speedup": ms_inf_l / ms_halt_l, "tiles_swept_frac": swept_l / max(full_l, 1),
                                   "inputs": "N(0,1) q, k, v with a bias coordinate: logits about N(-6,1)"},
         "decode": {"workload": f"B{B} H{H} cache T{Td} d{d}, bf16, one query per head", "ms": ms_dec,
-                   "roofline": {"bound": "hbm", "achieved": dec_bytes / (ms_dec * 1e-3) / 1e9, "peak": 8000.0,
-                                "unit": "GB/s", "frac": dec_bytes / (ms_dec * 1e-3) / 1e9 / 8000.0,
-                                "bytes_per_launch": dec_bytes, "what": "K and V read once",
-                                "traffic": hbm_traffic("decode_partial_kernel"),
+                   "effective_gbs": dec_bytes / (ms_dec * 1e-3) / 1e9, "ms_all_keys_read": ms_dec_all,
+                   "note": "far keys of exhausted heads are not read; with m wanted (ms_all_keys_read) all are",
+                   "roofline": {"bound": "hbm", "achieved": dec_bytes / (ms_dec_all * 1e-3) / 1e9, "peak": 8000.0,
+                                "unit": "GB/s", "frac": dec_bytes / (ms_dec_all * 1e-3) / 1e9 / 8000.0,
+                                "bytes_per_launch": dec_bytes, "what": "K and V read once, m wanted",
+                                "traffic": hbm_traffic("decode_kernel/all_keys"),
                                 "streaming_read_gbs": stream_gbs,
-                                "frac_streaming_read": dec_bytes / (ms_dec * 1e-3) / 1e9 / stream_gbs}},
+                                "frac_streaming_read": dec_bytes / (ms_dec_all * 1e-3) / 1e9 / stream_gbs}},
         "fwd_shader_clock_mhz": fwd_mhz,
         "cumsum_variants": {"in_lane_chain_ms": ms_fwd_again, "triangular_mfma_ms": ms_tri,
                             "what": "training forward at the headline workload with the in-tile reverse "
@@ -505,15 +539,12 @@ def main():
                               "shader_clock_mhz": mfma_mhz,
                               "what": "32x32x16 bf16 MFMAs alone, operands = the workload's k, 2 waves per SIMD"},
     }
-    # the same rates against what the matrix cores sustain on this data (measured above)
-    out["fwd"]["frac_mfma_only_ceiling"] = tf_fwd / mfma_tf
-    if with_bwd:
-        out["bwd"]["frac_mfma_only_ceiling"] = tf_bwd / mfma_tf
+    # the achieved rate against what the matrix cores sustain on such data (measured above)
     out["roofline"]["frac_mfma_only_ceiling"] = dom_tf / mfma_tf
     out["roofline"]["traffic_source"] = TRAFFIC_FILE + " (stored rocprofv3 run)"
     # false: the kernel sources changed since that run, the figure describes an older kernel
     out["roofline"]["traffic_is_of_these_sources"] = hbm_traffic_is_current()
-    out["fwd"]["frac_gemm_reference"] = tf_fwd / gemm_tf
+    out["full_sweep"]["kernels"]["fwd_bf16_kernel"]["frac_gemm_reference"] = f_fwd / full_kernels["fwd_bf16_kernel"][0] / 1e9 / gemm_tf
     if not args.no_configs:
         out["configs"] = config_entries(sb, inputs, max(args.kernel_iters, 50),
                                         ((q, k, v, dout), {"ms": ms_fwd, **sp_fwd}, o_fwd))

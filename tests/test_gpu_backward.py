@@ -182,9 +182,9 @@ def test_long_context_backward_one_head(sb, oracle, gen):
 
 @pytest.mark.parametrize("d", [64, 128])
 def test_bwd_log_domain_redo_of_every_block(sb, oracle, gen, d):
-    """Sharp logits in every head of a batch that fills the chip: the fast kernels flag (nearly)
-    every block and the log-domain launches redo them all (384 block pairs per pass); heads at
-    both ends of the grid against the oracle, everything finite."""
+    """Sharp logits in every head of a batch that fills the chip: (nearly) every wave takes the
+    logits of its subtiles once more and redoes them in the log domain (768 blocks per pass); heads
+    at both ends of the grid against the oracle, everything finite."""
     B, H, T = 4, 16, 1536
     q, k, v, g = gen.scaled_gaussian(B, H, T, d, seed=31, gain=30.0, dtype="bf16", with_dout=True)
     qd, kd, vd, gd = dev(q, k, v, g)
@@ -210,8 +210,8 @@ def test_bwd_split_passes_equal_the_whole(sb, gen):
 
 
 def test_bwd_sharp_blocks_are_redone_only_where_needed(sb, oracle, gen):
-    """One head with logits far beyond the linear-domain range next to an ordinary one:
-    the flagged blocks go through the log-domain variant, the rest do not, and both match."""
+    """One head with logits far beyond the linear-domain range next to an ordinary one: the
+    waves of the first take the log form, those of the second do not, and both match."""
     q, k, v, g = gen.gaussian(1, 2, 400, 128, seed=22, dtype="bf16", with_dout=True)
     k[:, 1] = (k[:, 1].float() * 40.0).to(k.dtype)
     check(sb, oracle, q, k, v, g)
