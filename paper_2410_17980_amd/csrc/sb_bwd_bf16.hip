@@ -72,15 +72,6 @@ __device__ __forceinline__ int scr_off(int row, int c)
 
 template <bool B> using bc = std::integral_constant<bool, B>;
 
-#ifndef SB_SIGMA_DQ
-#define SB_SIGMA_DQ 2
-#endif
-#ifndef SB_SIGMA_DKV
-#define SB_SIGMA_DKV 2
-#endif
-constexpr int SIGMA_DQ = SB_SIGMA_DQ;     // how each pass forms sigma (see subtile_stage1)
-constexpr int SIGMA_DKV = SB_SIGMA_DKV;
-
 // ------------------------------------------------------------------ element-wise core
 // One 32x32 subtile in the lane layout (query n; keys 16hh + r).
 struct SubtileOut {
@@ -111,13 +102,10 @@ struct Chain {
     float norm;      // log2 of what t is still to be divided by
 };
 
-// How sigma = e / (1 + e) is formed (SIGMA):
-//   0  e * rcp(1 + e): independent of the chain, an add and a reciprocal per element;
-//   1  t_r * rcp(W_{r+1}): one add fewer, but the reciprocal waits for the chain;
-//   2  t_r * (1 / W_{r+1}) with the 16 reciprocals from ONE reciprocal and a second chain run
-//      backwards, 1/W_r = 1/W_{r+1} * (1 + e_r): a fused multiply-add per element in place of
-//      the reciprocal (a transcendental, about twice the cost of a plain instruction here).
-template <bool MASK, int SIGMA = 0>
+// sigma = e / (1 + e) = t_r / W_{r+1}, with the 16 reciprocals from ONE reciprocal and a second chain run
+// backwards, 1/W_r = 1/W_{r+1} * (1 + e_r): a fused multiply-add per element in place of a reciprocal
+// (a transcendental, about twice the cost of a plain instruction here).
+template <bool MASK>
 __device__ __forceinline__ bool subtile_stage1(Chain& ch, const f32x16& sacc, float c2, int n, int hh)
 {
     float W = 0x1p-60f;
@@ -127,20 +115,16 @@ __device__ __forceinline__ bool subtile_stage1(Chain& ch, const f32x16& sacc, fl
         if (MASK) e = (16 * hh + r < n) ? e : 0.0f;
         ch.t[r] = W * e;
         W += ch.t[r];
-        if (SIGMA == 0) ch.be[r] = e * __builtin_amdgcn_rcpf(1.0f + e);
-        else if (SIGMA == 1) ch.be[r] = ch.t[r] * __builtin_amdgcn_rcpf(W);
-        else ch.be[r] = e;                                 // kept for the backward chain below
+        ch.be[r] = e;                                      // kept for the backward chain below
     }
     ch.norm = fast_log2(W);                                // W_16 = 2^(l - 60)
     ch.l = ch.norm + 60.0f;
-    if (SIGMA == 2) {
-        float inv = __builtin_amdgcn_rcpf(W);              // 1 / W_16; 0 where the chain overflowed
+    float inv = __builtin_amdgcn_rcpf(W);                  // 1 / W_16; 0 where the chain overflowed
 #pragma unroll
-        for (int r = 15; r >= 0; --r) {
-            const float e = ch.be[r];
-            ch.be[r] = ch.t[r] * inv;                      // t_r / W_{r+1}
-            inv = __builtin_fmaf(inv, e, inv);             // 1 / W_r
-        }
+    for (int r = 15; r >= 0; --r) {
+        const float e = ch.be[r];
+        ch.be[r] = ch.t[r] * inv;                          // t_r / W_{r+1}
+        inv = __builtin_fmaf(inv, e, inv);                 // 1 / W_r
     }
     return W < 0x1p80f;                                    // false: this lane's chain left its range
 }
@@ -366,7 +350,7 @@ bwd_dq_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
         };
         SubtileOut so;
         Chain ch;
-        const bool fits = subtile_stage1<MASK, SIGMA_DQ>(ch, s_mfma(), c2, n, hh);
+        const bool fits = subtile_stage1<MASK>(ch, s_mfma(), c2, n, hh);
         if (__builtin_expect(__builtin_amdgcn_ballot_w64(!fits) != 0, 0)) subtile_stage1_log<MASK>(ch, s_mfma(), c2, n, hh);
         const f32x16 pacc = p_mfma();
         subtile_stage2<true, false>(so, ch, pacc, a2, bsum, hh);
@@ -790,7 +774,7 @@ bwd_dkv_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
         bf16x8 gop[D / 16], qop[D / 16];
         mm2_fetch(qtile, gop, qop);                          // lands during the element-wise work
         Chain ch;
-        if (__builtin_expect(__builtin_amdgcn_ballot_w64(!subtile_stage1<MASK, SIGMA_DKV>(ch, sacc, c2, n, hh)) != 0, 0)) {
+        if (__builtin_expect(__builtin_amdgcn_ballot_w64(!subtile_stage1<MASK>(ch, sacc, c2, n, hh)) != 0, 0)) {
             f32x16 again;
 #pragma unroll
             for (int r = 0; r < 16; ++r) again[r] = 0.0f;
@@ -1113,7 +1097,7 @@ bwd_dkv_pair_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
         }
         SubtileOut so;
         Chain ch;
-        if (__builtin_expect(__builtin_amdgcn_ballot_w64(!subtile_stage1<MASK, SIGMA_DKV>(ch, sacc, c2, n, hh)) != 0, 0))
+        if (__builtin_expect(__builtin_amdgcn_ballot_w64(!subtile_stage1<MASK>(ch, sacc, c2, n, hh)) != 0, 0))
             subtile_stage1_log<MASK>(ch, logits(qa), c2, n, hh);
         subtile_stage2<false, true>(so, ch, pacc, car, cbl, hh);
         const uint32_t w = sc + role * CK::W_BYTES + sw_off;
@@ -1178,7 +1162,7 @@ bwd_dkv_pair_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
         __builtin_amdgcn_s_setprio(2);
         // part B: the chain of the logits (vector) beside dO.v and the back of subtile 0 (matrix)
         Chain ch;
-        const bool fits = subtile_stage1<false, SIGMA_DKV>(ch, sacc, c2, n, hh);
+        const bool fits = subtile_stage1<false>(ch, sacc, c2, n, hh);
 #pragma unroll
         for (int s = 0; s < D / 16; ++s)
             pacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[s], __builtin_bit_cast(bf16x8, gw[s]), pacc, 0, 0, 0);
@@ -1442,7 +1426,8 @@ bwd_drb_sum_kernel(const float* __restrict__ part, float* __restrict__ drb, int 
 }
 
 // workspace layout: ca[BH][nt32][T], cb[BH][nt32][T] (fp32; [H][nt32][Ttot] for a packed
-// batch), then the query blocks' start tiles (int): [BH][nqb], room for as many more, then the
+// batch), then the query blocks' start tiles (int): [BH][nqb], as many unused ones (the size that
+// the header states), then the
 // partial sums of the remainder-bias gradient (fp32): [BH][nchunk][D].  B, T: batch size and
 // length, or for a packed batch (VL) the number of sequences and the longest length.
 template <int D, bool VL>

@@ -174,15 +174,17 @@ template <int N>
 __device__ __forceinline__ void dma16_to_lds_run(const void* gbase, const int (&off)[N], const char* lds_base)
 {
     static_assert(N == 1 || N == 2 || N == 4, "loads per wave and matrix");
-    uint32_t lds = __builtin_amdgcn_readfirstlane(lds_offset(lds_base));
-    const uint64_t sb = scalar_base(gbase);
     if constexpr (N == 1) {
         dma16_to_lds_saddr(gbase, off[0], lds_base);
-    } else if constexpr (N == 2) {
+        return;
+    }
+    uint32_t lds = __builtin_amdgcn_readfirstlane(lds_offset(lds_base));
+    const uint64_t sb = scalar_base(gbase);
+    if constexpr (N == 2) {
         asm volatile("s_nop 4\n\tglobal_load_lds_dwordx4 %1, %3\n\t"
                      "s_add_u32 m0, m0, 0x400\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %3"
                      : "+{m0}"(lds) : "v"(off[0]), "v"(off[1]), "s"(sb) : "memory", "scc");
-    } else {
+    } else if constexpr (N == 4) {
         asm volatile("s_nop 4\n\tglobal_load_lds_dwordx4 %1, %5\n\t"
                      "s_add_u32 m0, m0, 0x400\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %5\n\t"
                      "s_add_u32 m0, m0, 0x400\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %3, %5\n\t"
