@@ -346,12 +346,11 @@ fwd_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
         pv_mfma(vop, p);
     };
     // a full tile, upper subtile first, written so that the operand fetches of a phase
-    // can be issued during the phase before it
-    auto hot_tile = [&](uint32_t sp) __attribute__((always_inline)) {
-        u32x4 kop[D / 16];
+    // can be issued during the phase before it; kop: the K rows of the upper subtile, fetched by first_k()
+    auto first_k = [&](uint32_t sp, u32x4 (&kop)[D / 16]) __attribute__((always_inline)) { k_fetch(sp + 32 * C::ROW, kop); };
+    auto hot_tile = [&](uint32_t sp, u32x4 (&kop)[D / 16]) __attribute__((always_inline)) {
         bf16x8 vop[D / 16];
         bf16x8 p[2];
-        k_fetch(sp + 32 * C::ROW, kop);
         f32x16 s = s_mfma(kop);
         v_fetch(sp + C::KT_BYTES + 32 * C::ROW, vop);
         if constexpr (TRI) ew_tri(s, p); else ew(bc<false>{}, s, p);
@@ -474,26 +473,34 @@ fwd_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     // compiler copies the accumulators, which spills.  The band is two tiles, or one or none in a ragged
     // last block.)
     static_assert(NS == 2, "the unrolled sweep alternates two buffers");
+    // The K rows of the next tile are asked for together with the flags: their latency is one.
     int stop = 0;
+    u32x4 kop[D / 16];
     const bool lead = !(it & 1) && it < ntile;
     if (lead) {
         begin_iter(it);
-        hot_tile(0u);
+        first_k(0u, kop);
+        hot_tile(0u, kop);
         ++it;
         publish();
     }
-    if (it < ntile) begin_iter(it);
-    if (!TRI && lead && it < ntile) stop = waves_done(s_done);
+    if (it < ntile) {
+        begin_iter(it);
+        if (!TRI && lead) stop = waves_done(s_done);
+        first_k((uint32_t)C::STAGE, kop);
+    }
     while (it + 1 < ntile && !stop) {
-        hot_tile((uint32_t)C::STAGE);
+        hot_tile((uint32_t)C::STAGE, kop);
         begin_iter(it + 1);
-        hot_tile(0u);
+        first_k(0u, kop);
+        hot_tile(0u, kop);
         it += 2;
         publish();
         begin_iter(it);
         if (!TRI) stop = waves_done(s_done);
+        first_k((uint32_t)C::STAGE, kop);                    // past the last tile: read and not used
     }
-    if (it < ntile && !stop) { hot_tile((uint32_t)C::STAGE); ++it; }
+    if (it < ntile && !stop) { hot_tile((uint32_t)C::STAGE, kop); ++it; }
     if constexpr (!WRITE_M) {
         if (tile_counts && tid == 0) {
             atomicAdd(&tile_counts[0], (unsigned long long)it);        // tiles swept
