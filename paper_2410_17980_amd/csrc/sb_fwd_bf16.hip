@@ -472,8 +472,11 @@ fwd_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     // decide whether there is another: the loop has this one exit.  (With a second one in its middle the
     // compiler copies the accumulators, which spills.  The band is two tiles, or one or none in a ragged
     // last block.)
-    static_assert(NS == 2, "the unrolled sweep alternates two buffers");
     // The K rows of the next tile are asked for together with the flags: their latency is one.
+    // Against flags read in the middle of a trip and acted on at its end, us: B8 H16 T4096 d128 near heads
+    // 168 -> 149, with halt 134 -> 122; B1 H24 T16384 d64 66 -> 55, 52 -> 42; one block's chain, all far,
+    // B1 H9 T4096 d128 89 -> 87, B2 H5 T3490 d64 52.1 -> 52.7 (with the runs of sb_share.h in the first two).
+    static_assert(NS == 2, "the unrolled sweep alternates two buffers");
     int stop = 0;
     u32x4 kop[D / 16];
     const bool lead = !(it & 1) && it < ntile;
