@@ -121,6 +121,9 @@ fwd_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
         kvrow0 = (long)(G == 1 ? bh : (int)((unsigned)bh / (unsigned)G)) * T;
     }
 
+    // a sweep's instructions go before those of another block's sum_tail(): a sweep waits for memory and
+    // for its own chain, the tail only for the pipes (1-2 % of a launch where heads are near)
+    if constexpr (WRITE_M) __builtin_amdgcn_s_setprio(1);
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -362,12 +365,23 @@ fwd_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
         pv_mfma(vop, p);
     };
 
+    const int Q0 = (nqb - 1 - sh.i) * BQ;
+    const int q0 = Q0 + wave * 32;                   // this wave's first query row
+    const bool wave_live = q0 < T;
     // The rest of a sweep whose weights are all zero, for m alone: adds log2(1 + e) over the keys of
     // tiles 0 .. ntail-1 to the carry.  Two K tiles fill a staging buffer (V is not needed), so a
-    // barrier covers 128 keys; per subtile D/16 MFMAs instead of D/8, three vector instructions
-    // per logit instead of seven and half the LDS reads and staged bytes.
+    // barrier covers 128 keys.  The accumulators of the output are free by now: a wave takes one of
+    // the two subtiles of every tile for its own rows and for those of its neighbour (wave ^ 1), which
+    // halves the LDS reads of a product, and the exponentials of a subtile stand beside the products of
+    // the next one in one block of code.  Bound by the matrix pipe and its power at d = 128 (1.1 PFLOP/s of
+    // products at T = 16384, what a library GEMM reaches on this data is 1.2), by the three vector
+    // instructions a logit below.  Against a wave's own rows alone, product and exponentials in turn, all
+    // heads near, the whole forward, us: B8 H16 T4096 d128 409 -> 378, B1 H32 T16384 d128 1279 -> 1130, one
+    // block's chain B1 H16 T4096 d128 73 -> 57, B1 H24 T16384 d64 565 -> 537, B8 H16 T2048 d64 76.6 -> 75.8.
     auto sum_tail = [&](int ntail) __attribute__((always_inline)) {
-        float l = 0.0f;                                      // this lane's keys only: the halves are added at the end
+        __builtin_amdgcn_s_setprio(0);
+        const uint32_t khalf = (wave & 1) * 32 * C::ROW;     // the wave's subtile of a tile
+        const int npr = (ntail + 1) >> 1;
         auto stage_pair = [&](int i, int st) __attribute__((always_inline)) {
             char* sp = smem + st * C::STAGE;
 #pragma unroll
@@ -376,41 +390,64 @@ fwd_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
                 dma16_to_lds_run(kb, goff, sp + x * C::KT_BYTES + wave * NPW * 1024);
             }
         };
-        auto sum_subtile = [&](uint32_t kslot) __attribute__((always_inline)) {
+        dma_wait<0>();
+        barrier_lds();                                       // nobody reads the sweep's tiles any more
+        stage_pair(0, 0);
+        // the neighbour's rows, through the other buffer (read again from memory they cost a fifth of the
+        // traffic of a block whose weights end early)
+        static_assert(NW * (D / 16) * 1024 <= C::STAGE, "the rows of all waves fit a buffer");
+        bf16x8 qn[D / 16];
+        const uint32_t qswap = smem0 + C::STAGE + lane * 16;
+#pragma unroll
+        for (int s = 0; s < D / 16; ++s) lds_store16(qswap + (wave * (D / 16) + s) * 1024, qf[s]);
+        barrier_lds();
+#pragma unroll
+        for (int s = 0; s < D / 16; ++s)
+            qn[s] = __builtin_bit_cast(bf16x8, lds_load16(qswap + ((wave ^ 1) * (D / 16) + s) * 1024));
+        float l = 0.0f, ln = 0.0f;                           // this lane's keys only: the halves are added at the end
+        struct Logits { f32x16 own, nbr; };
+        // logits of the subtile in `slot`, beside the totals of the one before
+        auto logits = [&](uint32_t slot, Logits& x) __attribute__((always_inline)) {
             u32x4 kop[D / 16];
-            k_fetch(kslot, kop);
-            const f32x16 s = s_mfma(kop);
-            l += sp2_total<false>(s, c2, n, hh);
+            k_fetch(khalf + slot, kop);
+#pragma unroll
+            for (int r = 0; r < 16; ++r) { x.own[r] = 0.0f; x.nbr[r] = 0.0f; }
+#pragma unroll
+            for (int s = 0; s < D / 16; ++s) {
+                x.own = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kop[s]), qf[s], x.own, 0, 0, 0);
+                x.nbr = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kop[s]), qn[s], x.nbr, 0, 0, 0);
+            }
         };
-        const int npr = (ntail + 1) >> 1;
+        auto add = [&](const Logits& x) __attribute__((always_inline)) { sp2_total_of_two(x.own, x.nbr, c2, l, ln); };
+        Logits x0, x1;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) { x1.own[r] = -INFINITY; x1.nbr[r] = -INFINITY; }     // adds nothing
         auto pair_tile = [&](int i, auto buf_c) __attribute__((always_inline)) {
             constexpr int BUF = decltype(buf_c)::value;
             constexpr uint32_t sp = BUF * C::STAGE;
             dma_wait<0>();
-            barrier_nofence();
+            barrier_lds();
             if (i + 1 < npr) stage_pair(i + 1, BUF ^ 1);
-            sum_subtile(sp);
-            sum_subtile(sp + 32 * C::ROW);
-            if (2 * i + 1 < ntail) {
-                sum_subtile(sp + C::KT_BYTES);
-                sum_subtile(sp + C::KT_BYTES + 32 * C::ROW);
-            }
+            logits(sp, x0);
+            add(x1);
+            logits(sp + C::KT_BYTES, x1);
+            add(x0);
         };
-        dma_wait<0>();
-        barrier_lds();                                       // nobody reads the sweep's tiles any more
-        stage_pair(0, 0);
         for (int i = 0; i < npr; i += 2) {
             pair_tile(i, ic<0>{});
             if (i + 1 < npr) pair_tile(i + 1, ic<1>{});
         }
-        float l_lo, l_hi;
-        both_halves(l, l_lo, l_hi);
-        a += l_lo + l_hi;
+        if (!(ntail & 1)) add(x1);                           // else the last tile was staged twice
+        float lo, hi;
+        both_halves(ln, lo, hi);
+        barrier_lds();                                       // the tiles have been read
+        float* const swap = reinterpret_cast<float*>(smem);
+        if (hh == 0) swap[(wave ^ 1) * 32 + n] = lo + hi;
+        barrier_lds();
+        both_halves(l, lo, hi);
+        a += (lo + hi) + swap[wave * 32 + n];
     };
 
-    const int Q0 = (nqb - 1 - sh.i) * BQ;
-    const int q0 = Q0 + wave * 32;                   // this wave's first query row
-    const bool wave_live = q0 < T;
     const int kmax = min(T, Q0 + BQ) - 1;                // keys 0 .. kmax-1 are visible to some row
     const int ntile = (kmax + C::TK - 1) / C::TK;
     const int ndiag = min(ntile, ntile - Q0 / C::TK);    // leading tiles that touch the diagonal band

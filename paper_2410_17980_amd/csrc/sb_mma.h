@@ -55,6 +55,25 @@ __device__ __forceinline__ float sp2_total(const f32x16& s, float c2, int n, int
     return l;
 }
 
+// l0 and l1 += the same of two accumulators, as one block of code up to the check
+__device__ __forceinline__ void sp2_total_of_two(const f32x16& s0, const f32x16& s1, float c2, float& l0, float& l1)
+{
+    float W0 = 0x1p-60f, W1 = 0x1p-60f;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        W0 = __builtin_fmaf(W0, fast_exp2(s0[r] * c2), W0);
+        W1 = __builtin_fmaf(W1, fast_exp2(s1[r] * c2), W1);
+    }
+    float t0 = fast_log2(W0) + 60.0f, t1 = fast_log2(W1) + 60.0f;
+    if (__builtin_expect(__builtin_amdgcn_ballot_w64(!(W0 + W1 < INFINITY)) != 0, 0)) {
+        t0 = t1 = 0.0f;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) { t0 += sp2(s0[r] * c2); t1 += sp2(s1[r] * c2); }
+    }
+    l0 += t0;
+    l1 += t1;
+}
+
 // MFMA 32x32 accumulator register r of lane (n, hh) is output row
 // 8*(r/4) + 4*hh + r%4.  Feeding MFMA row rho from tile row perm_row(rho)
 // makes lane (n, hh) own the 16 CONSECUTIVE tile rows 16*hh + r, r = 0..15.

@@ -59,6 +59,19 @@ def test_m_without_underflow(sb, gen):
     assert np.all(np.abs(to64(m) - ref) <= 2e-3 + 1e-4 * np.abs(ref))
 
 
+@pytest.mark.parametrize("T", [257, 320, 353, 385, 449, 577, 641, 1283])
+@pytest.mark.parametrize("d", [32, 64, 128])
+def test_m_of_short_tails(sb, gen, T, d):
+    """m over 0 to 18 tiles behind the end of the weights, odd and even, whose keys the waves of a block
+    share, with one to four waves' rows in the last block.  A logit is a sum of d products in fp32, a
+    softplus total one of T logits' worth: both a few 2^-24 of their terms, 1e-5 in all."""
+    q, k, v = mixed(gen, 2, 3, T, d, seed=900 + T)
+    _, m = sb.sb_attn_fwd_train(*dev(q, k, v))
+    z = to64(q) @ np.swapaxes(to64(k), -1, -2) / np.sqrt(d)
+    ref = -np.tril(np.logaddexp(0.0, z), -1).sum(-1)
+    assert np.all(np.abs(to64(m) - ref) <= 1e-4 + 1e-5 * np.abs(ref))
+
+
 @pytest.mark.parametrize("H,T", [(1, 130), (9, 300), (65, 300), (3, 8200)])
 def test_every_block_once(sb, gen, H, T):
     """The shares of the launch (heads over XCDs, single blocks or pairs) cover every row: equal to
