@@ -26,11 +26,12 @@
 // Recomputing them there, instead of keeping the accumulator for the case, is what keeps
 // the kernels within their register budget; a second launch of a log-domain variant for
 // flagged blocks, which this replaces, cost 7 us a pass with nothing flagged.
-// Far keys: once every row of a query block has less than 2^-160 of its stick left, all
-// weights and logit gradients beyond are zero (CARRY_EXHAUSTED).  The query-stationary
-// pass first looks for that point from the diagonal, with the logits alone (find_start()),
-// starts its sweep there and leaves the tile in `first`, one per query block; the
-// key-stationary pass visits only the query blocks that reach its keys.
+// Far keys: once every row of a 32-row strip of queries has less than 2^-160 of its stick
+// left, all weights and logit gradients beyond are zero (CARRY_EXHAUSTED).  The
+// query-stationary pass first looks for that point from the diagonal, with the logits alone
+// (find_start()), starts each wave's sweep there and leaves the 32-key strip in `first`, one
+// 16-bit number per strip of queries; the key-stationary pass visits only the query tiles that
+// reach its keys, and in those only the pairs of strips that reach each other.
 // Which blocks a workgroup takes: share_of().  Streamed tiles are staged with direct
 // global->LDS loads, double buffered, one barrier per 64-row tile.  The 1/sqrt(d)
 // of dQ and dK is applied once, to the accumulators, on store.
@@ -241,7 +242,7 @@ bwd_dq_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
               const uint16_t* __restrict__ v, const uint16_t* __restrict__ rb,
               const float* __restrict__ m,
               const uint16_t* __restrict__ dout, float* __restrict__ dq,
-              float* __restrict__ ca, float* __restrict__ cb, int* __restrict__ first,
+              float* __restrict__ ca, float* __restrict__ cb, uint16_t* __restrict__ first,
               int T_arg, int BH, int H, int G, int nqb_arg, int nt32, const int* __restrict__ cu, int Ttot,
               int run, int first_wg)
 {
@@ -379,11 +380,12 @@ bwd_dq_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
                 dqacc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(so.pz[s], kt[2 * b + s], dqacc[b], 0, 0, 0);
     };
 
-    // Where the sweep of the block at Q0 has to start: the tile beyond which every row is exhausted,
-    // 0 if there is none or if looking for it would not pay.  From the diagonal towards key 0, two K
-    // tiles per staging buffer and barrier, logits and softplus totals only (a third of the sweep's
-    // matrix work, a quarter of its vector work).  Sets a2 to the carry at that tile's left edge,
-    // which also spares the start a sum over all keys that is then subtracted again.
+    // Where the sweep of the block at Q0 has to start.  Every wave looks for the 32-key strip beyond which
+    // its own rows are exhausted, from the diagonal towards key 0, two K tiles per staging buffer and
+    // barrier, logits and softplus totals only (a third of the sweep's matrix work, a quarter of its
+    // vector work), and sets `start` to it and a2 to the carry at its left edge, which also spares the sweep
+    // a sum over all keys that is then subtracted again; 0 and a2 as it is if there is none.  Returns the
+    // tile at which the first of the waves has to start.
     // Tried only where m says that the rows have at least twice what exhausts them, so that the
     // point is expected in the nearer half, and given up after that half: at worst a sixth more.
     auto stage_pair = [&](const uint16_t* Kg, int T, int ntile, int i) __attribute__((always_inline)) {
@@ -393,14 +395,14 @@ bwd_dq_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
         stage_one<D, true>(Kg, t - 1, T, sp + C::TILE, goff, wave, lane);
     };
     // (pair 0 has been staged)
-    auto find_start = [&](const uint16_t* Kg, int T, int ntile, bool wave_live) __attribute__((always_inline)) {
+    auto find_start = [&](const uint16_t* Kg, int T, int ntile, bool wave_live, int& start) __attribute__((always_inline)) {
         const int limit = ntile >> 2;                        // pairs of tiles
-        if (wave_live ? __builtin_amdgcn_ballot_w64(!(a2 >= 2.0f * CARRY_EXHAUSTED)) == 0 : true) {
-            if (lane == 0) s_done[1][wave] = 1;
-        } else if (lane == 0) s_done[1][wave] = 0;
+        const int likely = !wave_live || __builtin_amdgcn_ballot_w64(!(a2 >= 2.0f * CARRY_EXHAUSTED)) == 0;
+        if (lane == 0) s_done[1][wave] = likely;
         barrier_lds();
         if (!waves_done(s_done[1])) return 0;
-        float l = 0.0f, left = 0.0f;                         // this lane's keys only; both halves'
+        float l = 0.0f;                                      // this lane's keys only
+        int found = wave_live ? 0 : 0x7fffffff;              // the strip, plus one
         auto sum_subtile = [&](auto mask_c, uint32_t ktile) __attribute__((always_inline)) {
             constexpr bool MASK = decltype(mask_c)::value;
             const uint32_t ka = ktile + aoff0;
@@ -418,27 +420,31 @@ bwd_dq_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
         for (int i = 0;; ++i) {
             dma_wait<0>();
             barrier_lds();
-            // the flags of pair i - 1; all waves read the same words and leave together
-            if (i > 0 && waves_done(s_done[(i + 1) & 1])) {
-                a2 = left;
-                return ntile - 2 * i;
+            if (i > 0) {
+                // what the waves found up to pair i - 1; all read the same words and leave together
+                const u32x4 f = lds_load16(lds_offset(reinterpret_cast<const char*>(s_done[(i + 1) & 1])));
+                const int least = __builtin_amdgcn_readfirstlane((int)min(min(f[0], f[1]), min(f[2], f[3])));
+                if (least > 0) return (least - 1) >> 1;
+                if (i == limit) return 0;
             }
-            if (i == limit) return 0;
             if (i + 1 < limit) stage_pair(Kg, T, ntile, i + 1);
-            if (wave_live) {
 #pragma unroll
-                for (int x = 0; x < 4; ++x) {
-                    const int key0 = (ntile - 2 * i) * TK - 32 * (x + 1);
-                    const uint32_t kt = smem0 + (i & 1) * C::STAGE + (x >> 1) * C::TILE + (1 - (x & 1)) * 32 * C::ROW;
-                    if (key0 == q0) sum_subtile(bc<true>{}, kt);
-                    else if (key0 < q0) sum_subtile(bc<false>{}, kt);
+            for (int x = 0; x < 4; ++x) {
+                const int key0 = (ntile - 2 * i) * TK - 32 * (x + 1);
+                const uint32_t kt = smem0 + (i & 1) * C::STAGE + (x >> 1) * C::TILE + (1 - (x & 1)) * 32 * C::ROW;
+                if (!found && key0 == q0) sum_subtile(bc<true>{}, kt);       // the strip's first row sees none of these
+                else if (!found && key0 < q0) {
+                    sum_subtile(bc<false>{}, kt);
+                    float l_lo, l_hi;
+                    both_halves(l, l_lo, l_hi);
+                    if (__builtin_amdgcn_ballot_w64(!(l_lo + l_hi >= CARRY_EXHAUSTED)) == 0) {
+                        a2 = l_lo + l_hi;
+                        start = key0 >> 5;
+                        found = start + 1;
+                    }
                 }
             }
-            float l_lo, l_hi;
-            both_halves(l, l_lo, l_hi);
-            left = l_lo + l_hi;
-            const int d = !wave_live || __builtin_amdgcn_ballot_w64(!(left >= CARRY_EXHAUSTED)) == 0;
-            if (lane == 0) s_done[i & 1][wave] = d;
+            if (lane == 0) s_done[i & 1][wave] = found;
         }
     };
 
@@ -450,7 +456,7 @@ bwd_dq_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     const int kmax = min(T, Q0 + BQ) - 1;            // keys 0 .. kmax-1 are visible to some row
     const int ntile = (kmax + TK - 1) / TK;
     const int nclean = min(ntile, Q0 / TK);          // tiles entirely left of the block's rows
-    const bool far = nclean >= 6;                    // long enough to look for a start
+    const bool far = nclean >= 6 && ntile <= 32768;  // long enough to look for a start, and `first` can hold it
     // what the block needs first, tiles and rows alike, is fetched together: one memory latency
     if (far) stage_pair(Kg, T, ntile, 0);
     else if (ntile > 0) stage_tile<D, true>(Kg, Vg, 0, T, smem, goff, wave, lane);
@@ -496,12 +502,12 @@ bwd_dq_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
         for (int r = 0; r < 16; ++r) dqacc[b][r] = 0.0f;
 
     // ---- sweep over 64-key tiles, left to right; iteration it handles tile it in buffer it & 1
-    int t0 = 0;
+    int t0 = 0, start = 0;
     if (far) {
-        t0 = find_start(Kg, T, ntile, wave_live);
+        t0 = find_start(Kg, T, ntile, wave_live, start);
         stage_tile<D, true>(Kg, Vg, t0, T, smem + (t0 & 1) * C::STAGE, goff, wave, lane);
     }
-    if (tid == 0) first[(long)bh * nqb_arg + qb] = t0;
+    if (lane == 0) first[((long)bh * nqb_arg + qb) * 4 + wave] = (uint16_t)(wave_live ? start : 2 * t0);
     auto begin_iter = [&](int it) __attribute__((always_inline)) {
         dma_wait<0>();                               // this wave's share of tile `it` has landed
         barrier_nofence();                           // ... everyone's has, and tile it-1 is no longer read
@@ -512,8 +518,8 @@ bwd_dq_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     int it = t0;
     for (; it < nclean; ++it) {                      // fully visible tiles
         const uint32_t sp = begin_iter(it);
-        subtile(bc<false>{}, sp, it * TK);
-        subtile(bc<false>{}, sp + 32 * C::ROW, it * TK + 32);
+        if (2 * it >= start) subtile(bc<false>{}, sp, it * TK);
+        if (2 * it + 1 >= start) subtile(bc<false>{}, sp + 32 * C::ROW, it * TK + 32);
     }
     for (; it < ntile; ++it) {                       // tiles that touch the diagonal band
         const uint32_t sp = begin_iter(it);
@@ -522,7 +528,7 @@ bwd_dq_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
             for (int u = 0; u < 2; ++u) {
                 const int key0 = it * TK + 32 * u;
                 if (key0 == q0) subtile(bc<true>{}, sp + u * 32 * C::ROW, key0);
-                else if (key0 < q0) subtile(bc<false>{}, sp + u * 32 * C::ROW, key0);
+                else if (key0 < q0 && 2 * it + u >= start) subtile(bc<false>{}, sp + u * 32 * C::ROW, key0);
             }
         }
     }
@@ -586,26 +592,36 @@ __device__ __forceinline__ bool kv_head(KvHead& kh, int bh, int T_arg, int nkb_a
     return true;
 }
 
-// Which query tiles reach the keys of tiles lo .. hi (of the 128-key block kb), from the query blocks'
-// start tiles f[0 .. nqb-1]: none from tile `end` on; all tiles before `sure` reach every one of
-// them.  In between a tile reaches a key tile iff f[tile / 2] is not beyond it.  The block's own
-// queries always count.
+// Which query tiles reach the 32-key strips lo .. hi, a block's, from the start strips that the
+// query-stationary pass left: f[jt] holds those of tile jt's two strips of queries.  None from tile `end` on;
+// in all tiles before `sure` both strips reach every one of the keys.  In between strip u of a tile
+// reaches key strip ks iff its start is not beyond it (reaching()).
 struct Reach {
     int sure, end;
 };
-__device__ __forceinline__ Reach reach_of(const int* __restrict__ f, int lo, int hi, int nqb, int lane)
+__device__ __forceinline__ Reach reach_of(const uint32_t* __restrict__ f, int lo, int hi, int nqb, int lane)
 {
     static_assert(BQ == 2 * TK, "two tiles per query block");
-    const int kb = lo >> 1;
-    int last = kb, cut = nqb;
-    for (int b = kb + 1; b < nqb; b += 64) {
-        const int t = b + lane < nqb ? f[b + lane] : 0x7fffffff;
-        const unsigned long long some = __builtin_amdgcn_ballot_w64(t <= hi);
-        const unsigned long long not_all = __builtin_amdgcn_ballot_w64(t > lo);
-        if (some) last = b + 63 - __builtin_clzll(some);
+    int last = lo >> 1, cut = nqb;
+    for (int b = lo >> 2; b < nqb; b += 64) {
+        const bool in = b + lane < nqb;
+        const uint32_t f0 = in ? f[2 * (b + lane)] : ~0u, f1 = in ? f[2 * (b + lane) + 1] : ~0u;
+        const int lo0 = f0 & 0xffff, hi0 = f0 >> 16, lo1 = f1 & 0xffff, hi1 = f1 >> 16;
+        const unsigned long long some0 = __builtin_amdgcn_ballot_w64(in && min(lo0, hi0) <= hi);
+        const unsigned long long some1 = __builtin_amdgcn_ballot_w64(in && min(lo1, hi1) <= hi);
+        const unsigned long long not_all = __builtin_amdgcn_ballot_w64(max(max(lo0, hi0), max(lo1, hi1)) > lo);
+        if (some0) last = max(last, 2 * (b + 63 - __builtin_clzll(some0)));
+        if (some1) last = max(last, 2 * (b + 63 - __builtin_clzll(some1)) + 1);
         if (not_all && cut == nqb) cut = min(nqb, b + __builtin_ctzll(not_all));
     }
-    return {2 * cut, 2 * (last + 1)};
+    return {2 * cut, last + 1};
+}
+// bit u: strip u of query tile jt reaches key strip ks
+__device__ __forceinline__ int reaching(const uint32_t* __restrict__ f, int jt, int sure, int ks)
+{
+    if (jt < sure) return 3;
+    const uint32_t w = f[jt];
+    return ((int)(w & 0xffff) <= ks ? 1 : 0) | ((int)(w >> 16) <= ks ? 2 : 0);
 }
 
 // ------------------------------------------------------------------ dK / dV kernel
@@ -625,7 +641,7 @@ __global__ void __launch_bounds__(SP * NTHREADS, 2)
 bwd_dkv_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
                const uint16_t* __restrict__ v, const uint16_t* __restrict__ dout,
                const float* __restrict__ ca, const float* __restrict__ cb,
-               float* __restrict__ dk, float* __restrict__ dv, const int* __restrict__ first,
+               float* __restrict__ dk, float* __restrict__ dv, const uint32_t* __restrict__ first,
                int T_arg, int BH, int H, int G_arg, int nkb_arg, int nt32, const int* __restrict__ cu, int Ttot,
                int run, int first_wg)
 {
@@ -686,15 +702,15 @@ bwd_dkv_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     f32x16 dkacc[D / 32], dvacc[D / 32];
     const float* cag = nullptr;
     const float* cbg = nullptr;
-    // ca, cb of query tile jt for this wave's keys.  Rows past T, tiles that do not reach the keys: an
-    // infinite carry gives A = 0 and G = 0, and with cb = 0 also dZ = 0.  (A dead wave's rows lie
-    // outside the arrays.)
-    auto load_carries = [&](float (&cn)[2][2], int jt, bool there) __attribute__((always_inline)) {
+    // ca, cb of query tile jt for this wave's keys (of a strip that does not reach them: unwritten
+    // memory, and not used).  Rows past T: an infinite carry gives A = 0 and G = 0, and with cb = 0 also
+    // dZ = 0.  (A dead wave's rows lie outside the arrays.)
+    auto load_carries = [&](float (&cn)[2][2], int jt, bool live) __attribute__((always_inline)) {
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
             const int j = jt * TK + 32 * u + n;
-            cn[u][0] = (j < T && there) ? cag[j] : INFINITY;
-            cn[u][1] = (j < T && there) ? cbg[j] : 0.0f;
+            cn[u][0] = (j < T && live) ? cag[j] : INFINITY;
+            cn[u][1] = (j < T && live) ? cbg[j] : 0.0f;
         }
     };
 
@@ -796,8 +812,7 @@ bwd_dkv_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     const bool wave_live = k0 < T;
     const int jt0 = K0 / TK;
     float cn[2][2];                                      // [subtile][ca, cb] of the next tile
-    // the group's first tile of a head and its carries, which always reach these keys (the block's own
-    // queries are two tiles)
+    // the group's first tile of a head and its carries
     auto first_tile = [&](int g) __attribute__((always_inline)) {
         Qg = q + (qrow0 + g * qrow_step) * D;
         Gg = dout + (qrow0 + g * qrow_step) * D;
@@ -836,20 +851,23 @@ bwd_dkv_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     // fetched one iteration ahead, and BEFORE the staging loads of that iteration are
     // issued: vector memory operations complete in order, so a wait for a carry
     // issued after the staging loads would wait for those as well.
-    const int* const fg = first + (kh.qhead0 + g) * nkb_arg;
-    const Reach reach = reach_of(fg, 2 * kb, 2 * kb + 1, nkb, lane);
+    const uint32_t* const fg = first + (kh.qhead0 + g) * 2 * nkb_arg;
+    const Reach reach = reach_of(fg, 4 * kb, 4 * kb + 3, nkb, lane);
     const int ntile = min((T + TK - 1) / TK, reach.end) - jt0;
     const int niter = (ntile + SP - 1) / SP;
     const int ndiag = min(niter, BKW / TK / SP);         // iterations on tiles that touch the diagonal band
     float cc[2][2];
+    int there = 0, there_next = grp < ntile ? reaching(fg, jt0 + grp, reach.sure, kt32) : 0;
     auto begin_iter = [&](int it) __attribute__((always_inline)) {
         dma_wait<0>();
         barrier_nofence();
 #pragma unroll
         for (int u = 0; u < 2; ++u) { cc[u][0] = cn[u][0]; cc[u][1] = cn[u][1]; }
+        there = there_next;
         const int jt = jt0 + (it + 1) * SP + grp;
         if (jt < jt0 + ntile) {
-            load_carries(cn, jt, wave_live && (jt < reach.sure || fg[jt >> 1] <= kt32 >> 1));
+            load_carries(cn, jt, wave_live);
+            there_next = reaching(fg, jt, reach.sure, kt32);
             stage_tile<D, false>(Qg, Gg, jt, T, tiles + ((it + 1) & 1) * C::STAGE, goff, wave, lane);
         }
         return (const char*)(tiles + (it & 1) * C::STAGE);
@@ -862,7 +880,7 @@ bwd_dkv_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
             for (int u = 0; u < 2; ++u) {
                 const int j0 = (jt0 + it * SP + grp) * TK + 32 * u;
                 if (j0 == k0) subtile(bc<true>{}, sp + u * 32 * C::ROW, cc[u][0], cc[u][1]);
-                else if (j0 > k0 && j0 < T) subtile(bc<false>{}, sp + u * 32 * C::ROW, cc[u][0], cc[u][1]);
+                else if (j0 > k0 && j0 < T && (there >> u & 1)) subtile(bc<false>{}, sp + u * 32 * C::ROW, cc[u][0], cc[u][1]);
             }
         }
     }
@@ -870,8 +888,8 @@ bwd_dkv_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
         const char* sp = begin_iter(it);
         if (wave_live && (SP == 1 || it * SP + grp < ntile)) {
             const int j0 = (jt0 + it * SP + grp) * TK;
-            subtile(bc<false>{}, sp, cc[0][0], cc[0][1]);
-            if (j0 + 32 < T) subtile(bc<false>{}, sp + 32 * C::ROW, cc[1][0], cc[1][1]);
+            if (there & 1) subtile(bc<false>{}, sp, cc[0][0], cc[0][1]);
+            if (j0 + 32 < T && (there & 2)) subtile(bc<false>{}, sp + 32 * C::ROW, cc[1][0], cc[1][1]);
         }
     }
     }
@@ -970,7 +988,7 @@ __global__ void __launch_bounds__(128 * KS, 1)
 bwd_dkv_pair_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
                     const uint16_t* __restrict__ v, const uint16_t* __restrict__ dout,
                     const float* __restrict__ ca, const float* __restrict__ cb,
-                    float* __restrict__ dk, float* __restrict__ dv, const int* __restrict__ first,
+                    float* __restrict__ dk, float* __restrict__ dv, const uint32_t* __restrict__ first,
                     int T_arg, int BH, int H, int G_arg, int nkb_arg, int nqb_arg, int nt32,
                     const int* __restrict__ cu, int Ttot, int pairs, int first_wg)
 {
@@ -1192,20 +1210,20 @@ bwd_dkv_pair_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
         const bool live = k0 < T;
         const int jt0 = K0 / TK;
         float cn0, cn1;                                      // ca, cb of this wave's subtile of the next tile
-        // rows past T, tiles that do not reach the keys: an infinite carry gives A = 0 and G = 0, and
-        // with cb = 0 also dZ = 0 (a dead strip's rows lie outside the arrays)
-        auto load_carries = [&](int jt, bool there) __attribute__((always_inline)) {
+        // rows past T: an infinite carry gives A = 0 and G = 0, and with cb = 0 also dZ = 0 (a dead
+        // strip's rows lie outside the arrays; those of queries that do not reach the keys are not used)
+        auto load_carries = [&](int jt) __attribute__((always_inline)) {
             const int j = jt * TK + 32 * role + n;
-            cn0 = (j < T && there) ? cag[j] : INFINITY;
-            cn1 = (j < T && there) ? cbg[j] : 0.0f;
+            cn0 = (j < T && live) ? cag[j] : INFINITY;
+            cn1 = (j < T && live) ? cbg[j] : 0.0f;
         };
-        // the block's first tile of a head and its carries, which always reach these keys
+        // the block's first tile of a head and its carries
         auto first_tile = [&](int g) __attribute__((always_inline)) {
             Qg = q + (qrow0 + g * qrow_step) * D;
             Gg = dout + (qrow0 + g * qrow_step) * D;
             cag = ca + cbase + g * cbase_step + kt32 * cstride;
             cbg = cb + cbase + g * cbase_step + kt32 * cstride;
-            load_carries(jt0, live);
+            load_carries(jt0);
             stage(jt0, smem);
         };
         if (part > 0) barrier_lds();                  // everyone is done with the LDS of the block before
@@ -1241,8 +1259,8 @@ bwd_dkv_pair_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
         // it & 1) and the back of tile jt0 + it - 1; the staging loads of tile jt0 + it + 1 are
         // issued at its start, after the carries of that tile (vector memory operations
         // complete in order, so the carries must not queue behind the staging loads).
-        const int* const fg = first + (kh.qhead0 + g) * nqb_arg;
-        const Reach reach = reach_of(fg, jt0, jt0 + CK::KEYS / TK - 1, (T + BQ - 1) / BQ, lane);
+        const uint32_t* const fg = first + (kh.qhead0 + g) * 2 * nqb_arg;
+        const Reach reach = reach_of(fg, K0 >> 5, (K0 >> 5) + KS - 1, (T + BQ - 1) / BQ, lane);
         const int ntile = min((T + TK - 1) / TK, reach.end) - jt0;
         const int ndiag = min(ntile, CK::KEYS / TK);              // tiles that touch the diagonal band
         // steady state (the intervals hot_begin .. hot_end - 1): the strip is live, tile `it` is past
@@ -1252,6 +1270,8 @@ bwd_dkv_pair_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
         const int hot_begin = ndiag + 1;
         const int sure = reach.sure - jt0;
         const int hot_end = !live ? 0 : min(nfull == ntile ? ntile : nfull - 1, sure < ntile ? sure - 1 : ntile);
+        // which strips of the queries reach this wave's keys: of tile it - 1, it, it + 1
+        int there_prev = 0, there = 0, there_next = reaching(fg, jt0, reach.sure, kt32);
         int it = 0;
         while (it <= ntile) {
             if (it == hot_begin && it < hot_end) {
@@ -1286,15 +1306,19 @@ bwd_dkv_pair_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
                     s_prev = s_cur;
                     s_cur = u;
                 }
+                there = there_next = 3;                  // the tile before and, if there is one, this one
                 continue;
             }
             const int bcur = it % 3, bprev = (it + 2) % 3, bnext = (it + 1) % 3;   // buffers of tiles it, it - 1, it + 1
             dma_wait<0>();
             barrier_lds();        // tile `it` has landed, the scratch of tile it-1 is complete, tile it-2 is free
             const float car = cn0, cbl = cn1;
+            there_prev = there;
+            there = there_next;
             if (it + 1 < ntile) {
                 const int jt = jt0 + it + 1;
-                load_carries(jt, live && (jt < reach.sure || fg[jt >> 1] <= kt32 >> 1));
+                load_carries(jt);
+                there_next = reaching(fg, jt, reach.sure, kt32);
                 stage(jt, smem + bnext * C::STAGE);
             }
             const int jbase = (jt0 + it) * TK;
@@ -1303,7 +1327,7 @@ bwd_dkv_pair_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
             const uint32_t spp = smem0 + bprev * C::STAGE;
             const uint32_t scp = scr + ((it + 1) & 1) * CK::SCR_BUF;
             const int j0 = jbase + 32 * role;
-            if (it < ntile && live && j0 < T) {
+            if (it < ntile && live && j0 < T && (there >> role & 1)) {
                 if (it < ndiag) {
                     if (j0 == k0) front(bc<true>{}, qt, sc, car, cbl);
                     else if (j0 > k0) front(bc<false>{}, qt, sc, car, cbl);
@@ -1315,7 +1339,7 @@ bwd_dkv_pair_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
 #pragma unroll
                 for (int u = 0; u < 2; ++u) {
                     const int ju = jbase - TK + 32 * u;
-                    if (ju >= k0 && ju < T) back(spp, scp, u);
+                    if (ju >= k0 && ju < T && (there_prev >> u & 1)) back(spp, scp, u);
                 }
             }
             ++it;
@@ -1426,8 +1450,7 @@ bwd_drb_sum_kernel(const float* __restrict__ part, float* __restrict__ drb, int 
 }
 
 // workspace layout: ca[BH][nt32][T], cb[BH][nt32][T] (fp32; [H][nt32][Ttot] for a packed
-// batch), then the query blocks' start tiles (int): [BH][nqb], as many unused ones (the size that
-// the header states), then the
+// batch), then the start strips of the queries' 32-row strips (16 bits): [BH][nqb][4], then the
 // partial sums of the remainder-bias gradient (fp32): [BH][nchunk][D].  B, T: batch size and
 // length, or for a packed batch (VL) the number of sequences and the longest length.
 template <int D, bool VL>
@@ -1446,8 +1469,9 @@ hipError_t launch_one(const uint16_t* q, const uint16_t* k, const uint16_t* v, c
     const long ncarry = VL ? (long)H * nt32 * Ttot : (long)BH * nt32 * T;
     float* ca = workspace;
     float* cb = ca + ncarry;
-    int* first = reinterpret_cast<int*>(cb + ncarry);
-    float* part = reinterpret_cast<float*>(first + (long)BH * (nqb + nkb));
+    uint16_t* first = reinterpret_cast<uint16_t*>(cb + ncarry);
+    const uint32_t* first2 = reinterpret_cast<const uint32_t*>(first);     // of a tile's two strips
+    float* part = reinterpret_cast<float*>(first + (long)BH * nqb * 4);
     const int nchunk = (T + DR_ROWS - 1) / DR_ROWS;
     const bool pairs = D == 128 && BHkv >= 128;             // see share_of()
     const long gq = share_grid(BH, nqb, false), gk = share_grid(BHkv, nkb, pairs);
@@ -1470,17 +1494,17 @@ hipError_t launch_one(const uint16_t* q, const uint16_t* k, const uint16_t* v, c
     if constexpr (D == 128) {                                                                                   \
         if (BHkv * (long)nkb <= small_kv_grid(nkb)) {                                                           \
             SB_LAUNCH(share_grid(BHkv, nkb64, false), 256, (bwd_dkv_pair_kernel<D, 2, GQAV, VL>),               \
-                      q, k, v, dout, ca, cb, dk, dv, first, T, BHkv, H, G, nkb64, nqb, nt32, cu, Ttot, 0);      \
+                      q, k, v, dout, ca, cb, dk, dv, first2, T, BHkv, H, G, nkb64, nqb, nt32, cu, Ttot, 0);      \
         } else {                                                                                                \
             SB_LAUNCH(gk, 512, (bwd_dkv_pair_kernel<D, 4, GQAV, VL>),                                           \
-                      q, k, v, dout, ca, cb, dk, dv, first, T, BHkv, H, G, nkb, nqb, nt32, cu, Ttot, pairs);    \
+                      q, k, v, dout, ca, cb, dk, dv, first2, T, BHkv, H, G, nkb, nqb, nt32, cu, Ttot, pairs);    \
         }                                                                                                       \
     } else if (gk <= ONE_PER_CU) {                                                                              \
         SB_LAUNCH(gk, 2 * NTHREADS, (bwd_dkv_kernel<D, GQAV, VL, 2>),                                           \
-                  q, k, v, dout, ca, cb, dk, dv, first, T, BHkv, H, G, nkb, nt32, cu, Ttot, run_k);             \
+                  q, k, v, dout, ca, cb, dk, dv, first2, T, BHkv, H, G, nkb, nt32, cu, Ttot, run_k);             \
     } else {                                                                                                    \
         SB_LAUNCH(gk, NTHREADS, (bwd_dkv_kernel<D, GQAV, VL, 1>),                                               \
-                  q, k, v, dout, ca, cb, dk, dv, first, T, BHkv, H, G, nkb, nt32, cu, Ttot, run_k);             \
+                  q, k, v, dout, ca, cb, dk, dv, first2, T, BHkv, H, G, nkb, nt32, cu, Ttot, run_k);             \
     }
     if (passes & 1) {
         if (rb) { SB_DQ(true); }
@@ -1509,18 +1533,18 @@ hipError_t launch_one(const uint16_t* q, const uint16_t* k, const uint16_t* v, c
 size_t bwd_workspace_bytes(int B, int H, int T, int d)
 {
     const size_t nt32 = (size_t)(T + 31) / 32;
-    const size_t nblk = (size_t)(T + BQ - 1) / BQ + (size_t)(T + BKW - 1) / BKW;
+    const size_t nblk = (size_t)(T + BQ - 1) / BQ;
     const size_t nchunk = (size_t)(T + DR_ROWS - 1) / DR_ROWS;
-    return (2 * sizeof(float) * nt32 * T + sizeof(int) * nblk + sizeof(float) * nchunk * d) * (size_t)B * H;
+    return (2 * sizeof(float) * nt32 * T + 4 * sizeof(uint16_t) * nblk + sizeof(float) * nchunk * d) * (size_t)B * H;
 }
 
 size_t bwd_varlen_workspace_bytes(int nseq, int H, int Ttot, int max_T, int d)
 {
     const size_t nt32 = (size_t)(max_T + 31) / 32;
-    const size_t nblk = (size_t)(max_T + BQ - 1) / BQ + (size_t)(max_T + BKW - 1) / BKW;
+    const size_t nblk = (size_t)(max_T + BQ - 1) / BQ;
     const size_t nchunk = (size_t)(max_T + DR_ROWS - 1) / DR_ROWS;
     return 2 * sizeof(float) * nt32 * (size_t)Ttot * H +
-           (sizeof(int) * nblk + sizeof(float) * nchunk * d) * (size_t)nseq * H;
+           (4 * sizeof(uint16_t) * nblk + sizeof(float) * nchunk * d) * (size_t)nseq * H;
 }
 
 hipError_t launch_bwd_bf16(const uint16_t* q, const uint16_t* k, const uint16_t* v, const uint16_t* rb,
