@@ -599,13 +599,25 @@ __device__ __forceinline__ bool kv_head(KvHead& kh, int bh, int T_arg, int nkb_a
 struct Reach {
     int sure, end;
 };
-__device__ __forceinline__ Reach reach_of(const uint32_t* __restrict__ f, int lo, int hi, int nqb, int lane)
+// The words of the first 64 blocks come from the caller (start_words()): bwd_dkv_kernel asks for them
+// together with what else a block needs first, one memory latency less (1 to 3 % where heads are near); the
+// paired kernel gains nothing that way.
+struct StartWords {
+    uint32_t f0, f1;
+};
+__device__ __forceinline__ StartWords start_words(const uint32_t* __restrict__ f, int b, int nqb, int lane)
+{
+    if (b + lane >= nqb) return {~0u, ~0u};
+    return {f[2 * (b + lane)], f[2 * (b + lane) + 1]};
+}
+__device__ __forceinline__ Reach reach_of(const uint32_t* __restrict__ f, StartWords w, int lo, int hi, int nqb, int lane)
 {
     static_assert(BQ == 2 * TK, "two tiles per query block");
     int last = lo >> 1, cut = nqb;
     for (int b = lo >> 2; b < nqb; b += 64) {
         const bool in = b + lane < nqb;
-        const uint32_t f0 = in ? f[2 * (b + lane)] : ~0u, f1 = in ? f[2 * (b + lane) + 1] : ~0u;
+        if (b != lo >> 2) w = start_words(f, b, nqb, lane);
+        const uint32_t f0 = w.f0, f1 = w.f1;
         const int lo0 = f0 & 0xffff, hi0 = f0 >> 16, lo1 = f1 & 0xffff, hi1 = f1 >> 16;
         const unsigned long long some0 = __builtin_amdgcn_ballot_w64(in && min(lo0, hi0) <= hi);
         const unsigned long long some1 = __builtin_amdgcn_ballot_w64(in && min(lo1, hi1) <= hi);
@@ -616,11 +628,14 @@ __device__ __forceinline__ Reach reach_of(const uint32_t* __restrict__ f, int lo
     }
     return {2 * cut, last + 1};
 }
-// bit u: strip u of query tile jt reaches key strip ks
-__device__ __forceinline__ int reaching(const uint32_t* __restrict__ f, int jt, int sure, int ks)
+// The word of tile jt, asked for one tile ahead and looked at a tile later by reaching(), whose bit u says
+// that strip u of the tile reaches key strip ks.
+__device__ __forceinline__ uint32_t start_word(const uint32_t* __restrict__ f, int jt, int sure)
 {
-    if (jt < sure) return 3;
-    const uint32_t w = f[jt];
+    return jt < sure ? 0u : f[jt];
+}
+__device__ __forceinline__ int reaching(uint32_t w, int ks)
+{
     return ((int)(w & 0xffff) <= ks ? 1 : 0) | ((int)(w >> 16) <= ks ? 2 : 0);
 }
 
@@ -812,12 +827,16 @@ bwd_dkv_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     const bool wave_live = k0 < T;
     const int jt0 = K0 / TK;
     float cn[2][2];                                      // [subtile][ca, cb] of the next tile
+    const uint32_t* fg = nullptr;
+    StartWords sw;
     // the group's first tile of a head and its carries
     auto first_tile = [&](int g) __attribute__((always_inline)) {
         Qg = q + (qrow0 + g * qrow_step) * D;
         Gg = dout + (qrow0 + g * qrow_step) * D;
         cag = ca + cbase + g * cbase_step + kt32 * cstride;
         cbg = cb + cbase + g * cbase_step + kt32 * cstride;
+        fg = first + (kh.qhead0 + g) * 2 * nkb_arg;
+        sw = start_words(fg, kb, nkb, lane);
         load_carries(cn, jt0 + grp, wave_live);
         if (SP == 1 || (jt0 + grp) * TK < T) stage_tile<D, false>(Qg, Gg, jt0 + grp, T, tiles, goff, wave, lane);
     };
@@ -851,23 +870,23 @@ bwd_dkv_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     // fetched one iteration ahead, and BEFORE the staging loads of that iteration are
     // issued: vector memory operations complete in order, so a wait for a carry
     // issued after the staging loads would wait for those as well.
-    const uint32_t* const fg = first + (kh.qhead0 + g) * 2 * nkb_arg;
-    const Reach reach = reach_of(fg, 4 * kb, 4 * kb + 3, nkb, lane);
+    const Reach reach = reach_of(fg, sw, 4 * kb, 4 * kb + 3, nkb, lane);
     const int ntile = min((T + TK - 1) / TK, reach.end) - jt0;
     const int niter = (ntile + SP - 1) / SP;
     const int ndiag = min(niter, BKW / TK / SP);         // iterations on tiles that touch the diagonal band
     float cc[2][2];
-    int there = 0, there_next = grp < ntile ? reaching(fg, jt0 + grp, reach.sure, kt32) : 0;
+    int there = 0;
+    uint32_t word_next = grp < ntile ? start_word(fg, jt0 + grp, reach.sure) : ~0u;
     auto begin_iter = [&](int it) __attribute__((always_inline)) {
         dma_wait<0>();
         barrier_nofence();
 #pragma unroll
         for (int u = 0; u < 2; ++u) { cc[u][0] = cn[u][0]; cc[u][1] = cn[u][1]; }
-        there = there_next;
+        there = reaching(word_next, kt32);
         const int jt = jt0 + (it + 1) * SP + grp;
         if (jt < jt0 + ntile) {
             load_carries(cn, jt, wave_live);
-            there_next = reaching(fg, jt, reach.sure, kt32);
+            word_next = start_word(fg, jt, reach.sure);
             stage_tile<D, false>(Qg, Gg, jt, T, tiles + ((it + 1) & 1) * C::STAGE, goff, wave, lane);
         }
         return (const char*)(tiles + (it & 1) * C::STAGE);
@@ -1218,29 +1237,41 @@ bwd_dkv_pair_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
             cn1 = (j < T && live) ? cbg[j] : 0.0f;
         };
         // the block's first tile of a head and its carries
+        const uint32_t* fg = nullptr;
+        const int nqb = (T + BQ - 1) / BQ;
         auto first_tile = [&](int g) __attribute__((always_inline)) {
             Qg = q + (qrow0 + g * qrow_step) * D;
             Gg = dout + (qrow0 + g * qrow_step) * D;
             cag = ca + cbase + g * cbase_step + kt32 * cstride;
             cbg = cb + cbase + g * cbase_step + kt32 * cstride;
+            fg = first + (kh.qhead0 + g) * 2 * nqb_arg;
             load_carries(jt0);
             stage(jt0, smem);
         };
         if (part > 0) barrier_lds();                  // everyone is done with the LDS of the block before
         first_tile(0);                                       // fetched together with the stationary rows
+        // K and V of the block into the other two tile buffers and from there into registers: as whole rows
+        // and once, not as 32 bytes of 32 rows an instruction and by both waves of a strip (B8 H16 T4096 all
+        // near 374 -> 353 us, a third far 636 -> 627)
+        static_assert(CK::KEYS * C::ROW <= C::STAGE, "the block's rows fit a tile buffer");
+        constexpr int KLOADS = CK::KEYS * C::ROW / 1024 / NW2;
+#pragma unroll
+        for (int i = 0; i < KLOADS; ++i) {
+            const int row = (wave + NW2 * i) * C::BLK_ROWS + lane / C::CPR;
+            const int off = (min(row, T - 1 - K0) * D + (((lane % C::CPR) ^ swz_perm<D>(row)) << 3)) * 2;
+            dma16_to_lds_saddr(k + base + (long)K0 * D, off, smem + C::STAGE + (wave + NW2 * i) * 1024);
+            dma16_to_lds_saddr(v + base + (long)K0 * D, off, smem + 2 * C::STAGE + (wave + NW2 * i) * 1024);
+        }
+        dma_wait<0>();
+        barrier_lds();
         {
-            const long kr = min(k0 + perm_row(n), T - 1);
-            const u32x4* ks = reinterpret_cast<const u32x4*>(k + base + kr * D + 8 * hh);
-            const u32x4* vs = reinterpret_cast<const u32x4*>(v + base + kr * D + 8 * hh);
+            const uint32_t ka = smem0 + C::STAGE + strip * 32 * C::ROW + tile_off_perm<D>(perm_row(n), hh);
 #pragma unroll
             for (int s = 0; s < D / 16; ++s) {
-                kf[s] = __builtin_bit_cast(bf16x8, ks[2 * s]);
-                vf[s] = __builtin_bit_cast(bf16x8, vs[2 * s]);
+                kf[s] = __builtin_bit_cast(bf16x8, lds_load16(ka ^ (s << 5)));
+                vf[s] = __builtin_bit_cast(bf16x8, lds_load16((ka ^ (s << 5)) + C::STAGE));
             }
         }
-#pragma unroll
-        for (int s = 0; s < D / 16; ++s) { asm volatile("" :: "v"(kf[s])); asm volatile("" :: "v"(vf[s])); }
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 #pragma unroll
         for (int b = 0; b < D / 32; ++b)
 #pragma unroll
@@ -1259,8 +1290,7 @@ bwd_dkv_pair_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
         // it & 1) and the back of tile jt0 + it - 1; the staging loads of tile jt0 + it + 1 are
         // issued at its start, after the carries of that tile (vector memory operations
         // complete in order, so the carries must not queue behind the staging loads).
-        const uint32_t* const fg = first + (kh.qhead0 + g) * 2 * nqb_arg;
-        const Reach reach = reach_of(fg, K0 >> 5, (K0 >> 5) + KS - 1, (T + BQ - 1) / BQ, lane);
+        const Reach reach = reach_of(fg, start_words(fg, K0 / BQ, nqb, lane), K0 >> 5, (K0 >> 5) + KS - 1, nqb, lane);
         const int ntile = min((T + TK - 1) / TK, reach.end) - jt0;
         const int ndiag = min(ntile, CK::KEYS / TK);              // tiles that touch the diagonal band
         // steady state (the intervals hot_begin .. hot_end - 1): the strip is live, tile `it` is past
@@ -1271,7 +1301,8 @@ bwd_dkv_pair_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
         const int sure = reach.sure - jt0;
         const int hot_end = !live ? 0 : min(nfull == ntile ? ntile : nfull - 1, sure < ntile ? sure - 1 : ntile);
         // which strips of the queries reach this wave's keys: of tile it - 1, it, it + 1
-        int there_prev = 0, there = 0, there_next = reaching(fg, jt0, reach.sure, kt32);
+        int there_prev = 0, there = 0;
+        uint32_t word_next = start_word(fg, jt0, reach.sure);
         int it = 0;
         while (it <= ntile) {
             if (it == hot_begin && it < hot_end) {
@@ -1306,7 +1337,8 @@ bwd_dkv_pair_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
                     s_prev = s_cur;
                     s_cur = u;
                 }
-                there = there_next = 3;                  // the tile before and, if there is one, this one
+                there = 3;                               // the tile before and, if there is one, this one
+                word_next = 0;
                 continue;
             }
             const int bcur = it % 3, bprev = (it + 2) % 3, bnext = (it + 1) % 3;   // buffers of tiles it, it - 1, it + 1
@@ -1314,11 +1346,11 @@ bwd_dkv_pair_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
             barrier_lds();        // tile `it` has landed, the scratch of tile it-1 is complete, tile it-2 is free
             const float car = cn0, cbl = cn1;
             there_prev = there;
-            there = there_next;
+            there = reaching(word_next, kt32);
             if (it + 1 < ntile) {
                 const int jt = jt0 + it + 1;
                 load_carries(jt);
-                there_next = reaching(fg, jt, reach.sure, kt32);
+                word_next = start_word(fg, jt, reach.sure);
                 stage(jt, smem + bnext * C::STAGE);
             }
             const int jbase = (jt0 + it) * TK;
