@@ -516,10 +516,14 @@ bwd_dq_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
         return smem0 + (it & 1) * C::STAGE;
     };
     int it = t0;
+    for (; it < nclean && 2 * it < start; ++it) {    // tiles in front of this wave's start
+        const uint32_t sp = begin_iter(it);
+        if (2 * it + 1 >= start) subtile(bc<false>{}, sp + 32 * C::ROW, it * TK + 32);
+    }
     for (; it < nclean; ++it) {                      // fully visible tiles
         const uint32_t sp = begin_iter(it);
-        if (2 * it >= start) subtile(bc<false>{}, sp, it * TK);
-        if (2 * it + 1 >= start) subtile(bc<false>{}, sp + 32 * C::ROW, it * TK + 32);
+        subtile(bc<false>{}, sp, it * TK);
+        subtile(bc<false>{}, sp + 32 * C::ROW, it * TK + 32);
     }
     for (; it < ntile; ++it) {                       // tiles that touch the diagonal band
         const uint32_t sp = begin_iter(it);
@@ -874,6 +878,7 @@ bwd_dkv_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     const int ntile = min((T + TK - 1) / TK, reach.end) - jt0;
     const int niter = (ntile + SP - 1) / SP;
     const int ndiag = min(niter, BKW / TK / SP);         // iterations on tiles that touch the diagonal band
+    const int nsure = min(niter, (reach.sure - jt0) / SP);
     float cc[2][2];
     int there = 0;
     uint32_t word_next = grp < ntile ? start_word(fg, jt0 + grp, reach.sure) : ~0u;
@@ -903,12 +908,21 @@ bwd_dkv_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
             }
         }
     }
-    for (; it < niter; ++it) {
+    for (; it < nsure; ++it) {                           // tiles that reach all keys
         const char* sp = begin_iter(it);
         if (wave_live && (SP == 1 || it * SP + grp < ntile)) {
             const int j0 = (jt0 + it * SP + grp) * TK;
-            if (there & 1) subtile(bc<false>{}, sp, cc[0][0], cc[0][1]);
-            if (j0 + 32 < T && (there & 2)) subtile(bc<false>{}, sp + 32 * C::ROW, cc[1][0], cc[1][1]);
+            subtile(bc<false>{}, sp, cc[0][0], cc[0][1]);
+            if (j0 + 32 < T) subtile(bc<false>{}, sp + 32 * C::ROW, cc[1][0], cc[1][1]);
+        }
+    }
+    for (; it < niter; ++it) {
+        const char* sp = begin_iter(it);
+#pragma unroll 1
+        for (int u = 0; u < 2; ++u) {
+            const int j0 = (jt0 + it * SP + grp) * TK + 32 * u;
+            if (wave_live && (SP == 1 || it * SP + grp < ntile) && j0 < T && (there >> u & 1))
+                subtile(bc<false>{}, sp + u * 32 * C::ROW, u ? cc[1][0] : cc[0][0], u ? cc[1][1] : cc[0][1]);
         }
     }
     }
