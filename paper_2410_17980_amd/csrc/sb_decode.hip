@@ -11,9 +11,9 @@
 // and the exact output is  sum_s exp(-sum_{s' nearer than s} a_s') O_s  (the farther
 // chunk's log-weights are shifted by what the nearer chunks took; Eq. 2).
 //
-// The nearest keys come first, in a launch of their own: they take most of the stick, and
-// where they take all of it (CARRY_EXHAUSTED: every farther weight is zero in fp32) the
-// rest of the cache is not read at all.
+// In a large cache the nearest keys come first, in a launch of their own: they take most of the stick,
+// and where they take all of it (CARRY_EXHAUSTED: every farther weight is zero in fp32) the
+// rest of the cache is not read at all.  A small one is read whole by the second launch (split_of()).
 //   decode_kernel<.., false>  grid (kv head, block of query heads): the nearest keys, all of a
 //       short cache.  Finishes the heads that are exhausted, or all if that was all.
 //   decode_kernel<.., true>   grid (chunk, kv head, block of query heads): the keys before
@@ -134,7 +134,7 @@ decode_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, co
     const float c2 = SB_LOG2E / sqrtf((float)D);
 
     if constexpr (FAR) {
-        if (!m) {
+        if (!m && near > 0) {
             const float a = part_a[(hq0 + min(lane, live - 1)) * nch + nfar];
             if (__builtin_amdgcn_ballot_w64(!(a >= CARRY_EXHAUSTED)) == 0) return;
         }
@@ -273,7 +273,7 @@ decode_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, co
 template <int D>
 __global__ void __launch_bounds__(COMBINE_THREADS)
 decode_combine_kernel(const float* __restrict__ part_o, const float* __restrict__ part_a,
-                      const uint16_t* __restrict__ rb, uint16_t* __restrict__ o, float* __restrict__ m, int H, int nch)
+                      const uint16_t* __restrict__ rb, uint16_t* __restrict__ o, float* __restrict__ m, int H, int nch, bool near)
 {
     constexpr int NV = D / 4;              // a thread adds four columns of every NG-th chunk
     constexpr int NG = COMBINE_THREADS / NV;
@@ -283,7 +283,7 @@ decode_combine_kernel(const float* __restrict__ part_o, const float* __restrict_
     const int tid = threadIdx.x, lane = tid & 63;
     const int c4 = tid % NV, grp = tid / NV;
     const float* pa = part_a + bh * nch;
-    if (!m && pa[nch - 1] >= CARRY_EXHAUSTED) return;      // finished by the first launch
+    if (!m && near && pa[nch - 1] >= CARRY_EXHAUSTED) return;      // finished by the first launch
     // chunk i is shifted by everything the nearer (higher) chunks took; lane l holds chunks 2l, 2l + 1
     float a[2];
 #pragma unroll
@@ -331,17 +331,30 @@ int room(int T)
 // launches / two with the same chunks / two with these: B16 H32 Hkv8 T4096 d128 55 / 49 / 48, B32 H16 T1800 d64
 // 49 / 43 / 39, B1 H32 Hkv8 T65000 d128 53 / 46 / 46, B8 H16 T16384 d128 167 / 161 / 162, B1 H8 T2000 d64
 // 12.8 / 9.4 / 6.7.
+//
+// A small cache is spread over the chip as well: one workgroup a head is bound by what one CU can load (2 us
+// per 128 KB of a head's K and V), three launches by their latencies.  That reads every key, so it is
+// limited by the size of the whole cache, and it pays unless all heads end within their nearest keys.  Without m, us, as
+// before / spread, a third of the kv heads far, then none:
+//   B1 H12 Hkv4 d128 T600 10.2 / 7.5, 6.8 / 7.5; T1500 18.0 / 7.6, 6.7 / 7.5
+//   B2 H8 T1000 d64 9.0 / 6.3, 4.6 / 6.2; B4 H8 T1200 d128 (20 MB) 15.2 / 9.3, 6.7 / 9.3
+//   B1 H8 T2000 d64 12.5 / 6.4, 11 / 6.4; B1 H8 T6000 d128 (25 MB) 15.2 / 9.4, 10.0 / 9.3
+//   B2 H16 T2000 d128 (33 MB) 16.1 / 9.9, 10.0 / 9.8
+// and not where B1 H12 Hkv4 T333 d128 7.8 / 7.6, 6.4 / 7.4; B4 H8 T400 d128 7.7 / 7.7, 6.4 / 7.7;
+// B8 H16 T1000 d128 (66 MB) 14.0 / 14.7, 7.0 / 14.8; B2 H16 T4000 d128 (66 MB) 16.4 / 14.9, 9.9 / 15.1.
 struct Split {
     int near, C, nfar;
     int chunks() const { return nfar + (near > 0); }
 };
-Split split_of(long wgs, int T, bool want_m)
+Split split_of(long wgs, double cache_bytes, int T, bool want_m)
 {
     Split s = {T, NEAR, 0};
-    if (T <= ALONE) return s;
-    s.near = want_m ? 0 : NEAR;
-    const int far = T - s.near, unit = want_m ? FAR_KEYS : NEAR;
-    const long want = std::min((long)std::min(MAXFAR, room(T) - 1), std::max(1L, (want_m ? ALL_WGS : FAR_WGS) / wgs));
+    const bool spread = T > 2 * NEAR && cache_bytes <= (T > ALONE ? 34e6 : 24e6);
+    if (T <= ALONE && !spread) return s;
+    const bool all = want_m || spread;
+    s.near = all ? 0 : NEAR;
+    const int far = T - s.near, unit = all ? FAR_KEYS : NEAR;
+    const long want = std::min((long)std::min(MAXFAR, room(T) - 1), std::max(1L, (all ? ALL_WGS : FAR_WGS) / wgs));
     s.C = (int)((far + want - 1) / want + unit - 1) / unit * unit;
     s.nfar = (far + s.C - 1) / s.C;
     return s;
@@ -353,7 +366,7 @@ hipError_t launch_d(const uint16_t* q, const uint16_t* k, const uint16_t* v, con
 {
     const int G = H / Hkv;
     const int nz = (G + GMAX - 1) / GMAX;
-    const Split s = split_of((long)B * Hkv * nz, T, m != nullptr);
+    const Split s = split_of((long)B * Hkv * nz, 4.0 * B * Hkv * T * D, T, m != nullptr);
     const long heads = (long)B * H;
     float* part_o = workspace;                                            // [heads][chunks][D]
     float* part_a = part_o + heads * s.chunks() * D;                      // [heads][chunks]
@@ -369,7 +382,7 @@ hipError_t launch_d(const uint16_t* q, const uint16_t* k, const uint16_t* v, con
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL((decode_combine_kernel<D>), dim3((unsigned)heads), dim3(COMBINE_THREADS), 0, stream,
-                       part_o, part_a, rb, o, m, H, s.chunks());
+                       part_o, part_a, rb, o, m, H, s.chunks(), s.near > 0);
     return hipGetLastError();
 }
 

@@ -118,10 +118,13 @@ def test_backward_far_queries_come_back(sb, oracle, gen, d):
 
 
 @pytest.mark.parametrize("H,Hkv,T,d", [(6, 3, 256, 128), (6, 3, 257, 64), (34, 2, 600, 32), (12, 3, 1536, 128), (12, 3, 1537, 128),
-                                       (6, 3, 1793, 64), (3, 3, 2048, 32), (51, 3, 3000, 64), (3, 3, 33025, 128)])
+                                       (6, 3, 1793, 64), (3, 3, 2048, 32), (51, 3, 3000, 64), (3, 3, 33025, 128),
+                                       # spread over the chip beyond 512 keys and up to 34 MB in all
+                                       (6, 3, 512, 128), (34, 2, 513, 64), (6, 3, 513, 128), (51, 3, 1025, 32),
+                                       (6, 3, 24001, 128), (51, 3, 46000, 64), (6, 6, 47000, 32)])
 def test_decode(sb, oracle, gen, H, Hkv, T, d):
-    """Caches at the edges of the passes and of the two launches, groups of 1 to 17 heads; without m
-    (exhausted heads finish early) and with it (no head does)."""
+    """Caches at the edges of the passes and of the ways to split them, groups of 1 to 17 heads; without m
+    (exhausted heads may finish early) and with it (no head does)."""
     q = gen.gaussian(1, H, 1, d, seed=T)[0][:, :, 0].clone()
     qk, k, v = mixed(gen, 1, Hkv, T, d, seed=T + 1)
     G = H // Hkv
