@@ -80,6 +80,7 @@ struct SubtileOut {
     bf16x8 pz[2];    // dZ (without the 1/sqrt(d)), same layout
     float ca_right;  // sum of sp2 over the keys right of the subtile
     float g_tot;     // sum of G over the subtile's 32 keys
+    float g_lo;      // and over its first 16
 };
 
 // In the linear domain inside the lane, as in the forward: with e_r = 2^{x_r}
@@ -149,9 +150,9 @@ __device__ __forceinline__ void subtile_stage1_log(Chain& ch, const f32x16& sacc
     ch.norm = 0.0f;
 }
 
+// subtile_g() up to the sums of G, subtile_dz() with cb in hand.
 template <bool CA_INCLUDES_SUBTILE, bool NEED_A>
-__device__ __forceinline__ void subtile_stage2(SubtileOut& out, Chain& ch, const f32x16& pacc,
-                                               float ca, float cb, int hh)
+__device__ __forceinline__ void subtile_g(SubtileOut& out, Chain& ch, const f32x16& pacc, float ca, int hh)
 {
     float l_lo, l_hi;
     both_halves(ch.l, l_lo, l_hi);
@@ -170,15 +171,25 @@ __device__ __forceinline__ void subtile_stage2(SubtileOut& out, Chain& ch, const
         grun += g;                                         // inclusive prefix inside the lane
         ch.t[r] = g - ch.be[r] * grun;
     }
-    float g_lo, g_hi;
-    both_halves(grun, g_lo, g_hi);
-    out.g_tot = g_lo + g_hi;
-    const float boff = cb + (hh == 1 ? g_lo : 0.0f);
+    float g_hi;
+    both_halves(grun, out.g_lo, g_hi);
+    out.g_tot = out.g_lo + g_hi;
+}
+__device__ __forceinline__ void subtile_dz(SubtileOut& out, const Chain& ch, float cb, int hh)
+{
+    const float boff = cb + (hh == 1 ? out.g_lo : 0.0f);
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
         const float dz = ch.t[r] - ch.be[r] * boff;        // Eq. 4
         out.pz[r >> 3][r & 7] = (__bf16)dz;
     }
+}
+template <bool CA_INCLUDES_SUBTILE, bool NEED_A>
+__device__ __forceinline__ void subtile_stage2(SubtileOut& out, Chain& ch, const f32x16& pacc,
+                                               float ca, float cb, int hh)
+{
+    subtile_g<CA_INCLUDES_SUBTILE, NEED_A>(out, ch, pacc, ca, hh);
+    subtile_dz(out, ch, cb, hh);
 }
 
 // ------------------------------------------------------------------ staging
@@ -1408,6 +1419,431 @@ bwd_dkv_pair_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
     }
 }
 
+// ------------------------------------------------------------------ small grids
+// Where the 128-row blocks leave most of the chip idle, what counts is the length of one row's chain of
+// subtiles.  Here a workgroup takes one strip of 32 rows, and its waves share the other side's subtiles, each
+// staging its own, without a barrier for the tiles.  Still bound by the chain: B2 H4 T777 d32 takes 11 + 8 us,
+// of which 4 to 5 each are a launch and its first loads.  Which grids: small_grid().
+template <int D> struct SmallCfg {
+    static constexpr int NWS = D == 128 ? 4 : 8;        // waves
+    static constexpr int ROW = D * 2;
+    static constexpr int SUB = 32 * ROW;                // one 32-row subtile of one matrix
+    static constexpr int WAVE = 4 * SUB;                // two matrices, double buffered
+    static constexpr int MAXSUB = SMALL_T / 32;         // subtiles of a strip
+};
+
+// one 32-row subtile of X (rows 32*sub ..), by one wave; rows past `last` are clamped
+template <int D, bool PERM>
+__device__ __forceinline__ void stage_subtile(const uint16_t* X, int sub, int T, char* dst, int lane)
+{
+    using C = SmallCfg<D>;
+    constexpr int CPR = C::ROW / 16;
+    const uint16_t* xb = X + (long)sub * 32 * D;
+    const int last = T - 1 - sub * 32;
+#pragma unroll
+    for (int i = 0; i < C::SUB / 1024; ++i) {
+        const int row = i * (1024 / C::ROW) + lane / CPR;
+        const int swz = PERM ? swz_perm<D>(row) : swz_nat<D>(row);
+        dma16_to_lds_saddr(xb, (min(row, last) * D + (((lane % CPR) ^ swz) << 3)) * 2, dst + i * 1024);
+    }
+}
+
+// what a wave has staged has landed, and its reads of the buffer to be refilled have returned
+__device__ __forceinline__ void own_landed() { asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory"); }
+
+// Query-stationary pass.  First the softplus totals of all subtiles, from the logits alone, every wave its
+// share; their sums from the diagonal on are every subtile's carry, and say where the rows are exhausted.
+// Then the sweep from there to the diagonal, a round of one subtile per wave at a time: A and G of the round, one barrier
+// to add up the G of the subtiles further left, dZ.
+template <int D>
+__global__ void __launch_bounds__(64 * SmallCfg<D>::NWS)
+bwd_dq_small_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
+                    const uint16_t* __restrict__ v, const uint16_t* __restrict__ rb,
+                    const float* __restrict__ m,
+                    const uint16_t* __restrict__ dout, float* __restrict__ dq,
+                    float* __restrict__ ca, float* __restrict__ cb, uint16_t* __restrict__ first,
+                    int T_arg, int BH, int H, int G, int nstrip_arg, int nqb_arg, int nt32, const int* __restrict__ cu, int Ttot)
+{
+    using C = SmallCfg<D>;
+    constexpr int NWS = C::NWS, NTHR = 64 * NWS;
+    __shared__ __attribute__((aligned(1024))) char smem[NWS * C::WAVE];
+    __shared__ float s_car[C::MAXSUB][32];              // totals, then carries, per subtile and row
+    __shared__ float s_g[2][NWS][32];                   // a round's sums of G
+    __shared__ int s_start;
+    static_assert(NWS * 32 * D * 4 <= NWS * C::WAVE, "the partial gradients fit");
+
+    asm volatile("" :: "s"(q), "s"(k), "s"(v), "s"(m), "s"(dout), "s"(T_arg), "s"(G));
+    const Share sh = in_scalars(share_of(blockIdx.x, BH, -1));
+    const int bh = sh.bh, head = bh % H;
+    int T = T_arg, nstrip = nstrip_arg;
+    long row0 = bh * (long)T, kvrow0 = (long)(G == 1 ? bh : (int)((unsigned)bh / (unsigned)G)) * T;
+    long cbase = (long)bh * nt32 * T, cstride = T;
+    if (cu) {                                           // packed batch, as in bwd_dq_kernel
+        const int seq = bh / H;
+        const int c0 = cu[seq];
+        T = min(min(cu[seq + 1], Ttot) - c0, T_arg);
+        if (c0 < 0) return;
+        nstrip = (T + 31) / 32;
+        if (sh.i >= nstrip) return;
+        row0 = (long)head * Ttot + c0;
+        kvrow0 = (long)(head / G) * Ttot + c0;
+        cbase = (long)head * nt32 * Ttot + c0;
+        cstride = Ttot;
+    }
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int n = lane & 31, hh = lane >> 5, gg = lane >> 4, li = lane & 15;
+    const int strip = nstrip - 1 - sh.i;
+    const int q0 = strip * 32;
+    const uint16_t* Kg = k + kvrow0 * D;
+    const uint16_t* Vg = v + kvrow0 * D;
+    char* const mine = smem + wave * C::WAVE;
+    const uint32_t base = lds_offset(mine);
+    const uint32_t ka = base + tile_off_perm<D>(perm_row(n), hh);       // A operands, ^ (s << 5)
+    uint32_t ktr[2];                                                    // transposing reads, ^ (b << 6)
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+        ktr[t] = base + tile_off_perm<D>(16 * (gg >> 1) + (li >> 2) + 4 * t, 2 * (gg & 1) + ((li & 3) >> 1)) + 8 * (li & 1);
+    const float scale = 1.0f / sqrtf((float)D);
+    const float c2 = SB_LOG2E * scale;
+
+    if (wave <= strip) stage_subtile<D, true>(Kg, wave, T, mine, lane);
+    bf16x8 qf[D / 16], gf[D / 16];
+    const int jq = min(q0 + n, T - 1);
+    {
+        const u32x4* qs = reinterpret_cast<const u32x4*>(q + (row0 + jq) * D + 8 * hh);
+        const u32x4* gs = reinterpret_cast<const u32x4*>(dout + (row0 + jq) * D + 8 * hh);
+#pragma unroll
+        for (int s = 0; s < D / 16; ++s) {
+            u32x4 a = qs[2 * s], g = gs[2 * s];
+            if (q0 + n >= T) g = u32x4{0u, 0u, 0u, 0u};   // rows past T contribute nothing
+            qf[s] = __builtin_bit_cast(bf16x8, a);
+            gf[s] = __builtin_bit_cast(bf16x8, g);
+        }
+    }
+    float bsum = 0.0f;                      // sum of G over the keys left of the round
+    if (rb) {                               // remainder bias, as in bwd_dq_kernel
+        const u32x4* rs = reinterpret_cast<const u32x4*>(rb + head * D + 8 * hh);
+        float dot = 0.0f;
+#pragma unroll
+        for (int s = 0; s < D / 16; ++s) {
+            const bf16x8 rr = __builtin_bit_cast(bf16x8, rs[2 * s]);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) dot += (float)gf[s][e] * (float)rr[e];
+        }
+        float d_lo, d_hi;
+        both_halves(dot, d_lo, d_hi);
+        bsum = fast_exp2(m[row0 + jq] * SB_LOG2E) * (d_lo + d_hi);
+    }
+#pragma unroll
+    for (int s = 0; s < D / 16; ++s) { asm volatile("" :: "v"(qf[s])); asm volatile("" :: "v"(gf[s])); }
+    asm volatile("" :: "v"(bsum));
+
+    auto rows_by = [&](uint32_t rows, const bf16x8 (&f)[D / 16]) __attribute__((always_inline)) {
+        u32x4 w[D / 16];
+#pragma unroll
+        for (int s = 0; s < D / 16; ++s) w[s] = lds_load16(rows ^ (s << 5));
+        f32x16 acc;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
+#pragma unroll
+        for (int s = 0; s < D / 16; ++s)
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, w[s]), f[s], acc, 0, 0, 0);
+        return acc;
+    };
+
+    // ---- totals
+    for (int sub = wave, st = 0; sub <= strip; sub += NWS, st ^= 1) {
+        own_landed();
+        if (sub + NWS <= strip) stage_subtile<D, true>(Kg, sub + NWS, T, mine + (st ^ 1) * 2 * C::SUB, lane);
+        const f32x16 s = rows_by(ka + st * 2 * C::SUB, qf);
+        const float l = sub == strip ? sp2_total<true>(s, c2, n, hh) : sp2_total<false>(s, c2, n, hh);
+        float l_lo, l_hi;
+        both_halves(l, l_lo, l_hi);
+        if (hh == 0) s_car[sub][n] = l_lo + l_hi;
+    }
+    barrier_lds();
+    if (wave == 0) {                                     // both halves alike
+        float right = 0.0f;
+        int start = strip;
+        for (int sub = strip; sub >= 0; --sub) {
+            const float t = s_car[sub][n];
+            if (hh == 0) s_car[sub][n] = right;
+            if (__builtin_amdgcn_ballot_w64(!(right >= CARRY_EXHAUSTED)) == 0) break;
+            start = sub;
+            right += t;
+        }
+        if (lane == 0) s_start = start;
+    }
+    barrier_lds();
+    const int start = __builtin_amdgcn_readfirstlane(s_start);
+    if (wave == 0 && lane < 4) {
+        // the strips of the last block that do not exist share the last one's
+        const int s4 = lane, at = strip & ~3;
+        if (at + s4 == strip || (strip == nstrip - 1 && at + s4 > strip)) first[(long)bh * nqb_arg * 4 + at + s4] = (uint16_t)start;
+    }
+
+    // ---- the sweep
+    f32x16 dqacc[D / 32];
+#pragma unroll
+    for (int b = 0; b < D / 32; ++b)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) dqacc[b][r] = 0.0f;
+    float* const cag = ca + cbase;
+    float* const cbg = cb + cbase;
+    auto stage = [&](int sub, int st) __attribute__((always_inline)) {
+        stage_subtile<D, true>(Kg, sub, T, mine + st * 2 * C::SUB, lane);
+        stage_subtile<D, true>(Vg, sub, T, mine + st * 2 * C::SUB + C::SUB, lane);
+    };
+    if (start + wave <= strip) stage(start + wave, 0);
+    for (int sub0 = start, st = 0; sub0 <= strip; sub0 += NWS, st ^= 1) {
+        const int sub = sub0 + wave;
+        const bool there = sub <= strip;
+        Chain ch;
+        SubtileOut so;
+        so.g_tot = 0.0f;
+        float car = 0.0f;
+        const uint32_t buf = st * 2 * C::SUB;
+        if (there) {
+            own_landed();
+            if (sub + NWS <= strip) stage(sub + NWS, st ^ 1);
+            car = s_car[sub][n];
+            const f32x16 s = rows_by(ka + buf, qf);
+            const bool fits = sub == strip ? subtile_stage1<true>(ch, s, c2, n, hh) : subtile_stage1<false>(ch, s, c2, n, hh);
+            if (__builtin_expect(__builtin_amdgcn_ballot_w64(!fits) != 0, 0)) {
+                const f32x16 again = rows_by(ka + buf, qf);
+                if (sub == strip) subtile_stage1_log<true>(ch, again, c2, n, hh);
+                else subtile_stage1_log<false>(ch, again, c2, n, hh);
+            }
+            subtile_g<false, false>(so, ch, rows_by(ka + buf + C::SUB, gf), car, hh);
+        }
+        if (hh == 0) s_g[st][wave][n] = so.g_tot;
+        barrier_lds();
+        float left = bsum;
+        for (int w = 0; w < NWS; ++w) {
+            if (w == wave) left = bsum;
+            bsum += s_g[st][w][n];
+        }
+        if (there) {
+            if (hh == 0 && q0 + n < T) {
+                const long ci = (long)sub * cstride + q0 + n;
+                cag[ci] = car;
+                cbg[ci] = left;
+            }
+            subtile_dz(so, ch, left, hh);
+            bf16x8 kt[D / 16];
+#pragma unroll
+            for (int b = 0; b < D / 32; ++b)
+#pragma unroll
+                for (int s = 0; s < 2; ++s)
+                    kt[2 * b + s] = tr_pair_at(((ktr[0] + buf) ^ (b << 6)) + 8 * s * C::ROW, ((ktr[1] + buf) ^ (b << 6)) + 8 * s * C::ROW);
+#pragma unroll
+            for (int b = 0; b < D / 32; ++b)
+#pragma unroll
+                for (int s = 0; s < 2; ++s)
+                    dqacc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(so.pz[s], kt[2 * b + s], dqacc[b], 0, 0, 0);
+        }
+    }
+
+    // ---- the waves' shares added up, in a fixed order.  dqacc[b][r] is query row 8*(r/4) + 4*hh + r%4, column 32b + n
+    barrier_lds();                                       // everyone is done with the tiles
+    float* const red = reinterpret_cast<float*>(smem);
+#pragma unroll
+    for (int b = 0; b < D / 32; ++b)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) red[(wave * 32 + 8 * (r >> 2) + 4 * hh + (r & 3)) * D + 32 * b + n] = dqacc[b][r];
+    barrier_lds();
+    for (int i = tid; i < 32 * D / 4; i += NTHR) {
+        const int row = i / (D / 4), c = 4 * (i % (D / 4));
+        f32x4 x = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int w = 0; w < NWS; ++w) x += *reinterpret_cast<const f32x4*>(&red[(w * 32 + row) * D + c]);
+        if (q0 + row < T) *reinterpret_cast<f32x4*>(dq + (row0 + q0 + row) * D + c) = x * scale;
+    }
+}
+
+// Key-stationary pass at d <= 64: a strip of 32 keys a workgroup, whose waves take its query subtiles (of all
+// query heads of the group) in turn and add their accumulators up at the end.
+template <int D>
+__global__ void __launch_bounds__(64 * SmallCfg<D>::NWS)
+bwd_dkv_small_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
+                     const uint16_t* __restrict__ v, const uint16_t* __restrict__ dout,
+                     const float* __restrict__ ca, const float* __restrict__ cb,
+                     float* __restrict__ dk, float* __restrict__ dv, const uint16_t* __restrict__ first,
+                     int T_arg, int BH, int H, int G, int nstrip_arg, int nqb_arg, int nt32, const int* __restrict__ cu, int Ttot)
+{
+    using C = SmallCfg<D>;
+    constexpr int NWS = C::NWS, NTHR = 64 * NWS;
+    constexpr int WAVE = C::WAVE + 2 * SCR_MAT;          // Q and dO subtiles, double buffered; A and dZ scratch
+    __shared__ __attribute__((aligned(1024))) char smem[NWS * WAVE];
+    static_assert(NWS * WAVE <= 160 * 1024 && NWS * 32 * D * 4 <= NWS * WAVE, "LDS budget; the partial gradients fit");
+
+    asm volatile("" :: "s"(q), "s"(k), "s"(v), "s"(dout), "s"(ca), "s"(cb), "s"(first), "s"(T_arg));
+    const Share sh = in_scalars(share_of(blockIdx.x, BH, -1));
+    KvHead kh;
+    const bool some = cu ? kv_head<D, true>(kh, sh.bh, T_arg, nstrip_arg, 32, H, G, nt32, cu, Ttot)
+                         : kv_head<D, false>(kh, sh.bh, T_arg, nstrip_arg, 32, H, G, nt32, cu, Ttot);
+    if (!some || sh.i >= kh.nkb) return;
+    const int T = kh.T, nstrip = kh.nkb;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int n = lane & 31, hh = lane >> 5, gg = lane >> 4, li = lane & 15;
+    const int ks = sh.i, k0 = ks * 32;                   // the strip; small ones have the most queries
+    char* const mine = smem + wave * WAVE;
+
+    // the query strips of head g that reach the keys, as bits; wave w takes strips ks + w, ks + w + NWS, ... of
+    // all heads in turn
+    const int nq = nstrip - ks;
+    struct Item {
+        int g, r;                                        // head, strip - ks
+    };
+    int mask_g = -1;
+    unsigned long long mask[2];
+    static_assert(C::MAXSUB <= 128, "two masks");
+    auto next_item = [&](Item i) __attribute__((always_inline)) {
+        for (;; i.r += NWS) {
+            while (i.r >= nq) { i.r -= nq; ++i.g; }
+            if (i.g >= G) return i;
+            if (i.g != mask_g) {
+                mask_g = i.g;
+                const uint16_t* f = first + (kh.qhead0 + i.g) * nqb_arg * 4 + ks;
+#pragma unroll
+                for (int x = 0; x < 2; ++x) {
+                    const int r = 64 * x + lane;
+                    mask[x] = __builtin_amdgcn_ballot_w64(r < nq && f[min(r, nq - 1)] <= ks);
+                }
+            }
+            if (mask[i.r >> 6] >> (i.r & 63) & 1) return i;
+        }
+    };
+    float cn0 = 0.0f, cn1 = 0.0f;
+    auto fetch = [&](Item it, int st) __attribute__((always_inline)) {
+        const float* cag = ca + kh.cbase + it.g * kh.cbase_step + ks * kh.cstride;
+        const float* cbg = cb + kh.cbase + it.g * kh.cbase_step + ks * kh.cstride;
+        const int j = (ks + it.r) * 32 + n;
+        cn0 = j < T ? cag[j] : INFINITY;                 // rows past T: A, G and dZ are zero
+        cn1 = j < T ? cbg[j] : 0.0f;
+        const long r0 = kh.qrow0 + it.g * kh.qrow_step;
+        stage_subtile<D, false>(q + r0 * D, ks + it.r, T, mine + st * 2 * C::SUB, lane);
+        stage_subtile<D, false>(dout + r0 * D, ks + it.r, T, mine + st * 2 * C::SUB + C::SUB, lane);
+    };
+    Item it = next_item(Item{0, wave});
+    if (it.g < G) fetch(it, 0);
+    bf16x8 kf[D / 16], vf[D / 16];
+    {
+        const long kr = min(k0 + perm_row(n), T - 1);
+        const u32x4* kp = reinterpret_cast<const u32x4*>(k + kh.base + kr * D + 8 * hh);
+        const u32x4* vp = reinterpret_cast<const u32x4*>(v + kh.base + kr * D + 8 * hh);
+#pragma unroll
+        for (int s = 0; s < D / 16; ++s) {
+            kf[s] = __builtin_bit_cast(bf16x8, kp[2 * s]);
+            vf[s] = __builtin_bit_cast(bf16x8, vp[2 * s]);
+        }
+    }
+#pragma unroll
+    for (int s = 0; s < D / 16; ++s) { asm volatile("" :: "v"(kf[s])); asm volatile("" :: "v"(vf[s])); }
+    const uint32_t base = lds_offset(mine);
+    const uint32_t qb = base + tile_off_nat<D>(n, hh);                  // B operands, ^ (s << 5)
+    uint32_t qtr[2];                                                    // transposing reads, ^ (b << 6)
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+        qtr[t] = base + tile_off_nat<D>(8 * (gg >> 1) + (li >> 2) + 4 * t, 2 * (gg & 1) + ((li & 3) >> 1)) + 8 * (li & 1);
+    const uint32_t scr = base + C::WAVE;
+    const uint32_t sw_off = scr + scr_off(n, 2 * hh);
+    uint32_t st_off[2];
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+        st_off[t] = scr + scr_off(8 * (gg >> 1) + (li >> 2) + 4 * t, 2 * (gg & 1) + ((li & 3) >> 1)) + 8 * (li & 1);
+    const float scale = 1.0f / sqrtf((float)D);
+    const float c2 = SB_LOG2E * scale;
+    f32x16 dkacc[D / 32], dvacc[D / 32];
+#pragma unroll
+    for (int b = 0; b < D / 32; ++b)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) { dkacc[b][r] = 0.0f; dvacc[b][r] = 0.0f; }
+
+    for (int st = 0; it.g < G; st ^= 1) {
+        own_landed();
+        float car = cn0, cbl = cn1;
+        asm volatile("" : "+v"(car), "+v"(cbl));
+        const Item nx = next_item(Item{it.g, it.r + NWS});
+        if (nx.g < G) fetch(nx, st ^ 1);
+        const uint32_t buf = st * 2 * C::SUB;
+        const bool diag = it.r == 0;
+        if (diag && n == 0) car = cbl = 0.0f;            // as in bwd_dkv_kernel
+        u32x4 qw[D / 16], gw[D / 16];
+#pragma unroll
+        for (int s = 0; s < D / 16; ++s) {
+            qw[s] = lds_load16((qb + buf) ^ (s << 5));
+            gw[s] = lds_load16(((qb + buf) ^ (s << 5)) + C::SUB);
+        }
+        f32x16 sacc, pacc;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) { sacc[r] = 0.0f; pacc[r] = 0.0f; }
+#pragma unroll
+        for (int s = 0; s < D / 16; ++s) {
+            sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[s], __builtin_bit_cast(bf16x8, qw[s]), sacc, 0, 0, 0);
+            pacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[s], __builtin_bit_cast(bf16x8, gw[s]), pacc, 0, 0, 0);
+        }
+        Chain ch;
+        const bool fits = diag ? subtile_stage1<true>(ch, sacc, c2, n, hh) : subtile_stage1<false>(ch, sacc, c2, n, hh);
+        if (__builtin_expect(__builtin_amdgcn_ballot_w64(!fits) != 0, 0)) {
+            f32x16 again;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) again[r] = 0.0f;
+#pragma unroll
+            for (int s = 0; s < D / 16; ++s)
+                again = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[s], __builtin_bit_cast(bf16x8, lds_load16((qb + buf) ^ (s << 5))), again, 0, 0, 0);
+            if (diag) subtile_stage1_log<true>(ch, again, c2, n, hh);
+            else subtile_stage1_log<false>(ch, again, c2, n, hh);
+        }
+        SubtileOut so;
+        subtile_stage2<false, true>(so, ch, pacc, car, cbl, hh);
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        lds_store16(sw_off, so.pa[0]);
+        lds_store16(sw_off ^ 16, so.pa[1]);
+        lds_store16(sw_off + SCR_MAT, so.pz[0]);
+        lds_store16((sw_off ^ 16) + SCR_MAT, so.pz[1]);
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        bf16x8 at[2], zt[2];
+#pragma unroll
+        for (int s2 = 0; s2 < 2; ++s2) {
+            at[s2] = tr_pair_at(st_off[0] + 16 * s2 * 64, st_off[1] + 16 * s2 * 64);
+            zt[s2] = tr_pair_at(st_off[0] + 16 * s2 * 64 + SCR_MAT, st_off[1] + 16 * s2 * 64 + SCR_MAT);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+#pragma unroll
+        for (int b = 0; b < D / 32; ++b)
+#pragma unroll
+            for (int s2 = 0; s2 < 2; ++s2) {
+                const uint32_t x0 = ((qtr[0] + buf) ^ (b << 6)) + 16 * s2 * C::ROW, x1 = ((qtr[1] + buf) ^ (b << 6)) + 16 * s2 * C::ROW;
+                dvacc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(at[s2], tr_pair_at(x0 + C::SUB, x1 + C::SUB), dvacc[b], 0, 0, 0);
+                dkacc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(zt[s2], tr_pair_at(x0, x1), dkacc[b], 0, 0, 0);
+            }
+        it = nx;
+    }
+
+    // ---- the waves' shares added up, in a fixed order: dV, then dK
+    float* const red = reinterpret_cast<float*>(smem);
+#pragma unroll
+    for (int mat = 0; mat < 2; ++mat) {
+        barrier_lds();                                   // everyone is done with the tiles, or with dV
+#pragma unroll
+        for (int b = 0; b < D / 32; ++b)
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+                red[(wave * 32 + 8 * (r >> 2) + 4 * hh + (r & 3)) * D + 32 * b + n] = mat == 0 ? dvacc[b][r] : dkacc[b][r];
+        barrier_lds();
+        for (int i = tid; i < 32 * D / 4; i += NTHR) {
+            const int row = i / (D / 4), c = 4 * (i % (D / 4));
+            f32x4 x = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+            for (int w = 0; w < NWS; ++w) x += *reinterpret_cast<const f32x4*>(&red[(w * 32 + row) * D + c]);
+            if (k0 + row < T) *reinterpret_cast<f32x4*>((mat == 0 ? dv : dk) + kh.base + (long)(k0 + row) * D + c) = mat == 0 ? x : x * scale;
+        }
+    }
+}
+
 // ------------------------------------------------------------------ gradient of the remainder bias
 // dr[h][c] = sum over the batch and the rows j of exp(m_j) dO[j][c] (Appendix C: the
 // output holds (stick left of row j) * r_h).  Two deterministic steps: per (batch entry,
@@ -1526,18 +1962,28 @@ hipError_t launch_one(const uint16_t* q, const uint16_t* k, const uint16_t* v, c
     if (gq > 0x7fffffffL || gk > 0x7fffffffL || nchunk * (long)BH > 0x7fffffffL) return hipErrorInvalidValue;
     hipError_t e = hipSuccess;
 #define SB_LAUNCH(WGS, THREADS, KERNEL, ...)                                                                    \
+    {                                                                                                           \
     e = launch_workgroups(WGS, THREADS, [&](unsigned n, int first_wg) {                                         \
         hipLaunchKernelGGL(KERNEL, dim3(n), dim3(THREADS), 0, stream, __VA_ARGS__, first_wg);                   \
     });                                                                                                         \
-    if (e != hipSuccess) return e
+    if (e != hipSuccess) return e;                                                                              \
+    }
 #define SB_DQ(RBV)                                                                                              \
-    SB_LAUNCH(gq, NTHREADS, (bwd_dq_kernel<D, RBV, VL>),                                                        \
+    if (small_grid(BH, T, D)) {                                                                                  \
+        hipLaunchKernelGGL((bwd_dq_small_kernel<D>), dim3((unsigned)(BH * nt32)), dim3(64 * SmallCfg<D>::NWS), 0, stream, \
+                           q, k, v, rb, m, dout, dq, ca, cb, first, T, BH, H, G, nt32, nqb, nt32, cu, Ttot);    \
+        if ((e = hipGetLastError()) != hipSuccess) return e;                                                    \
+    } else SB_LAUNCH(gq, NTHREADS, (bwd_dq_kernel<D, RBV, VL>),                                                        \
               q, k, v, rb, m, dout, dq, ca, cb, first, T, BH, H, G, nqb, nt32, cu, Ttot, run_q)
 // d = 128 takes the paired-wave kernel (two waves per SIMD instead of one); smaller head
 // dimensions leave room for two workgroups of the one-wave-per-strip kernel per CU, which
 // is faster there (measured).
 #define SB_DKV(GQAV)                                                                                            \
-    if constexpr (D == 128) {                                                                                   \
+    if (small_grid(BHkv, T, D)) {                                                                               \
+            hipLaunchKernelGGL((bwd_dkv_small_kernel<D>), dim3((unsigned)(BHkv * nt32)), dim3(64 * SmallCfg<D>::NWS), 0, stream, \
+                               q, k, v, dout, ca, cb, dk, dv, first, T, BHkv, H, G, nt32, nqb, nt32, cu, Ttot); \
+        if ((e = hipGetLastError()) != hipSuccess) return e;                                                    \
+    } else if constexpr (D == 128) {                                                                            \
         if (BHkv * (long)nkb <= small_kv_grid(nkb)) {                                                           \
             SB_LAUNCH(share_grid(BHkv, nkb64, false), 256, (bwd_dkv_pair_kernel<D, 2, GQAV, VL>),               \
                       q, k, v, dout, ca, cb, dk, dv, first2, T, BHkv, H, G, nkb64, nqb, nt32, cu, Ttot, 0);      \

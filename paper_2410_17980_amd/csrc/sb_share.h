@@ -32,6 +32,24 @@ inline long share_grid(long heads, int nblk, bool pairs)
     return pairs ? 8L * ((heads + 7) / 8) * ((nblk + 1) / 2) : heads * nblk;
 }
 
+// Grids of the backward that take one strip of 32 rows a workgroup, its waves sharing the strip's other side
+// (bwd_dq_small_kernel, bwd_dkv_small_kernel), in place of 128-row blocks whose every wave has the
+// whole other side to itself.  What bounds the blocks there is one chain, what bounds the strips from a round or two of the
+// chip on is their tiles, which no other wave shares.  Blocks / strips, us, query-stationary, then key-stationary:
+//   B2 H4 T777 d32 (200 strips) 19.1 / 10.9, 19.2 / 7.7; B1 H4 T4000 d64 (500) 98 / 52, 96 / 38;
+//   B1 H12 T2000 d64 (756) 52 / 48, 52 / 37; B2 H12 T1000 d32 (768) 24.7 / 24.2, 24.2 / 18.0;
+//   B1 H8 T700 d128 (176) 28 / 21.5, 24.4 / 17.9; B1 H16 T500 d128 (256) 23 / 16.7, 21 / 15.2;
+//   B1 H16 T100 d64 (64) 6.9 / 6.3, 8.2 / 6.5; both B1 H6 Hkv2 T4000 d32 320 / 125
+// and not B4 H8 T700 d64 (704) 21.5 / 25.9, 23.2 / 23.2; B4 H16 T300 d64 (640) 11.6 / 19.9, 14.4 / 19.2;
+// B1 H24 T1000 d128 (768) 40 / 55; B1 H4 T64 d64 5.0 / 6.1, 6.4 / 6.3.  (All heads far; where they are near the
+// strips gain more.)  4096: the kernels' arrays hold 128 strips.
+constexpr int SMALL_T = 4096;
+inline bool small_grid(long heads, int T, int d)
+{
+    const long limit = d == 128 ? 256 : T >= 1024 ? 768 : T > 341 ? 3L * T / 4 : 256;
+    return T > 64 && T <= SMALL_T && heads * ((T + 31) / 32) <= limit;
+}
+
 // log2 of the run, -1: turn with every block.  A run pays where the launch is several rounds deep and
 // there are enough runs to even the XCDs out: 32 of them, or 16 where 64 heads and more can be turned
 // among each other as well, by o(o+1)/2 inside each octet o of heads (over any 8 octets these are all 8

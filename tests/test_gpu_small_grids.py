@@ -1,0 +1,84 @@
+"""The backward of grids that leave most of the chip idle: one strip of 32 rows a workgroup, whose waves share
+the other side's subtiles.  And, at the same lengths with more heads, the 128-row blocks that larger grids take."""
+import numpy as np
+import pytest
+import torch
+
+from helpers import check_grad, dev, nan_bytes, to64
+from test_gpu_exhausted import gen, mixed, sb  # noqa: F401  (fixtures)
+
+pytestmark = pytest.mark.gpu
+
+
+def run(sb, oracle, gen, H, Hkv, T, d, kv_heads, seed):
+    """kv heads by turns near, sharp and far (a group's first query head sees them so); every gradient of the
+    stated ones against the oracle, with a workspace that reads as NaN where nothing was written."""
+    G = H // Hkv
+    q0, k, v = mixed(gen, 1, Hkv, T, d, seed=seed + T)
+    g, q, _ = gen.gaussian(1, H, T, d, seed=seed + T + 1, dtype="bf16")
+    q = q.clone()
+    q[:, ::G] = q0
+    r = gen.remainder_embedding(H, d, seed=seed + 2)
+    qd, kd, vd, gd, rd = dev(q, k, v, g, r)
+    _, m = sb.sb_attn_fwd_gqa(qd, kd, vd, r=rd)
+    ws = nan_bytes(sb.sb_attn_bwd_workspace_bytes(1, H, T, d))
+    got = sb.sb_attn_bwd_gqa(qd, kd, vd, m, gd, r=rd, workspace=ws)
+    torch.cuda.synchronize()
+    for h in kv_heads:
+        s, h = slice(h * G, (h + 1) * G), slice(h, h + 1)
+        ref = oracle.bwd_gqa(to64(q[:, s]), to64(k[:, h]), to64(v[:, h]), to64(g[:, s]), r=to64(r[s]))
+        for name, a, x in zip(("dq", "dk", "dv", "dr"), (got[0][:, s], got[1][:, h], got[2][:, h], got[3][s]), ref):
+            check_grad(f"{name} kv head {h.start}", to64(a), x)
+
+
+@pytest.mark.parametrize("T", [65, 96, 97, 128, 255, 257, 1000])
+@pytest.mark.parametrize("d", [32, 64, 128])
+def test_strips(sb, oracle, gen, T, d):
+    run(sb, oracle, gen, 3, 3, T, d, range(3), seed=0)
+
+
+@pytest.mark.parametrize("H,Hkv,T", [(6, 3, 200), (16, 2, 97), (15, 3, 321)])
+@pytest.mark.parametrize("d", [32, 64, 128])
+def test_strips_of_groups(sb, oracle, gen, H, Hkv, T, d):
+    run(sb, oracle, gen, H, Hkv, T, d, range(Hkv), seed=40)
+
+
+@pytest.mark.parametrize("d", [32, 64, 128])
+def test_longest_strips(sb, oracle, gen, d):
+    """128 subtiles a row, the most the kernels' arrays hold; one more row takes the 128-row blocks."""
+    for T in (4096, 4097):
+        q, k, v = mixed(gen, 1, 3, T, d, seed=T)
+        g = gen.gaussian(1, 3, T, d, seed=T + 1, dtype="bf16")[0]
+        h = slice(2, 3)                                    # the far one
+        qd, kd, vd, gd = dev(q[:, h], k[:, h], v[:, h], g[:, h])
+        _, m = sb.sb_attn_fwd_train(qd, kd, vd)
+        ws = nan_bytes(sb.sb_attn_bwd_workspace_bytes(1, 1, T, d))
+        got = sb.sb_attn_bwd(qd, kd, vd, m, gd, workspace=ws)
+        torch.cuda.synchronize()
+        for name, a, r in zip(("dq", "dk", "dv"), got, oracle.bwd(*(to64(t[:, h]) for t in (q, k, v, g)))):
+            check_grad(f"{name} T {T}", to64(a), r)
+
+
+@pytest.mark.parametrize("H,Hkv,T,d", [(66, 66, 129, 64), (66, 66, 257, 32), (42, 42, 193, 128), (42, 42, 255, 128), (90, 45, 200, 128),
+                                       (132, 66, 130, 64), (150, 150, 129, 128), (150, 150, 65, 32)])
+def test_blocks_of_larger_grids(sb, oracle, gen, H, Hkv, T, d):
+    run(sb, oracle, gen, H, Hkv, T, d, (0, 1, 2, Hkv - 1), seed=80)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_packed(sb, oracle, gen, d):
+    """Sequences of all kinds of lengths in one small grid: none, one row, one strip, a strip and a row, many."""
+    lens = [1, 0, 32, 33, 64, 65, 96, 300]
+    q, k, v = mixed(gen, 1, 3, sum(lens), d, seed=7)
+    g = gen.gaussian(1, 3, sum(lens), d, seed=8, dtype="bf16")[0]
+    q, k, v, g = (t[0] for t in (q, k, v, g))
+    cu = torch.tensor(np.cumsum([0] + lens), dtype=torch.int32)
+    qd, kd, vd, gd = dev(q, k, v, g)
+    _, m = sb.sb_attn_varlen_fwd(qd, kd, vd, cu.cuda(), max(lens))
+    got = sb.sb_attn_varlen_bwd(qd, kd, vd, m, gd, cu.cuda(), max(lens))
+    torch.cuda.synchronize()
+    for i, n in enumerate(lens):
+        s = slice(int(cu[i]), int(cu[i]) + n)
+        if n:
+            for name, a, r in zip(("dq", "dk", "dv"), got, oracle.bwd(*(to64(t[:, s]) for t in (q, k, v, g)))):
+                check_grad(f"{name} of {n}", to64(a[:, s]), r)
