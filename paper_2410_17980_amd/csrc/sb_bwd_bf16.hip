@@ -241,6 +241,29 @@ __device__ __forceinline__ void stage_tile(const uint16_t* X, const uint16_t* Y,
     stage_one<D, PERM>(Y, jt, T, sp + C::TILE, goff, wave, lane);
 }
 
+// A strip's accumulators, times f, to its 32 rows from `out` on (wave-uniform), of which `rows` exist: acc[b][r] is
+// row 8*(r/4) + 4*hh + r%4, column 32b + n.  Whole strips without a test per element: 64 tests with their
+// addresses, reloaded from scratch each, took as long as the stores (bwd_dkv_pair_kernel, see there).
+template <int D>
+__device__ __forceinline__ void store_strip(float* out, int rows, const f32x16 (&acc)[D / 32], float f, int n, int hh)
+{
+    float* const o = reinterpret_cast<float*>(scalar_base(out));
+    const int at = 4 * hh * D + n;
+    if (rows >= 32) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+#pragma unroll
+            for (int b = 0; b < D / 32; ++b) o[(8 * (r >> 2) + (r & 3)) * D + 32 * b + at] = acc[b][r] * f;
+        return;
+    }
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        if (8 * (r >> 2) + 4 * hh + (r & 3) < rows)
+#pragma unroll
+            for (int b = 0; b < D / 32; ++b) o[(8 * (r >> 2) + (r & 3)) * D + 32 * b + at] = acc[b][r] * f;
+    }
+}
+
 // ------------------------------------------------------------------ dQ kernel
 // VL (both kernels): packed variable-length batch, tensors [H][Ttot][D] ([H/G][Ttot][D] for
 // k, v, dk, dv) with sequence s at rows cu[s] .. cu[s+1]-1.  BH counts (sequence, head)
@@ -548,18 +571,7 @@ bwd_dq_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
         }
     }
 
-    // ---- dQ store: dqacc[b][r] is query row 8*(r/4) + 4*hh + r%4, column 32b + n
-    if (wave_live) {
-        float* dQg = dq + base;
-#pragma unroll
-        for (int b = 0; b < D / 32; ++b) {
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int row = q0 + 8 * (r >> 2) + 4 * hh + (r & 3);
-                if (row < T) dQg[(long)row * D + 32 * b + n] = dqacc[b][r] * scale;
-            }
-        }
-    }
+    if (wave_live) store_strip<D>(dq + base + (long)q0 * D, T - q0, dqacc, scale, n, hh);
 }
 
 // Where a kv head's rows and its query heads' rows and carries live (key-stationary kernels).
@@ -958,21 +970,9 @@ bwd_dkv_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
         }
     }
 
-    // ---- store: acc[b][r] is key row k0 + 8*(r/4) + 4*hh + r%4, column 32b + n
     if (wave_live) {
-        float* dKg = dk + base;
-        float* dVg = dv + base;
-#pragma unroll
-        for (int b = 0; b < D / 32; ++b) {
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int key = k0 + 8 * (r >> 2) + 4 * hh + (r & 3);
-                if (key < T) {
-                    dKg[(long)key * D + 32 * b + n] = dkacc[b][r] * scale;
-                    dVg[(long)key * D + 32 * b + n] = dvacc[b][r];
-                }
-            }
-        }
+        store_strip<D>(dk + base + (long)k0 * D, T - k0, dkacc, scale, n, hh);
+        store_strip<D>(dv + base + (long)k0 * D, T - k0, dvacc, 1.0f, n, hh);
     }
 }
 
@@ -1403,19 +1403,7 @@ bwd_dkv_pair_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
         }
         }
 
-        // ---- store: acc[b][r] is key row k0 + 8*(r/4) + 4*hh + r%4, column 32b + n
-        if (live) {
-            float* out = (role == 0 ? dv : dk) + base;
-            const float f = role == 0 ? 1.0f : scale;
-#pragma unroll
-            for (int b = 0; b < D / 32; ++b) {
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int key = k0 + 8 * (r >> 2) + 4 * hh + (r & 3);
-                    if (key < T) out[(long)key * D + 32 * b + n] = acc[b][r] * f;
-                }
-            }
-        }
+        if (live) store_strip<D>((role == 0 ? dv : dk) + base + (long)k0 * D, T - k0, acc, role == 0 ? 1.0f : scale, n, hh);
     }
 }
 
