@@ -567,17 +567,32 @@ fwd_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
                 for (int b = 0; b < D / 32; ++b) oacc[b][r] += rr * rc[b];
             }
         }
-        uint16_t* Og = o + row0 * D;
-        const bool full = q0 + 32 <= T;
+        uint16_t* const Og = reinterpret_cast<uint16_t*>(scalar_base(o + (row0 + q0) * D));
+        if (q0 + 32 <= T) {
+            // whole strips: without a test per element, and two columns a store.  A lane holds one column
+            // of rows r and r + 1; with its neighbour's it makes two columns of row r (n even) or r + 1.
+            const uint32_t pick = (n & 1) ? 0x03020706u : 0x05040100u;
+            const int at = (4 * hh + (n & 1)) * D + (n & ~1);
 #pragma unroll
-        for (int b = 0; b < D / 32; ++b) {
+            for (int r = 0; r < 16; r += 2)
+#pragma unroll
+                for (int b = 0; b < D / 32; ++b) {
+                    typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
+                    const bf16x2 two = {(__bf16)oacc[b][r], (__bf16)oacc[b][r + 1]};
+                    const uint32_t x = __builtin_bit_cast(uint32_t, two);
+                    const uint32_t y = __builtin_amdgcn_mov_dpp(x, 0xB1, 0xF, 0xF, true);      // of lane n ^ 1
+                    *reinterpret_cast<uint32_t*>(Og + (8 * (r >> 2) + (r & 3)) * D + 32 * b + at) = __builtin_amdgcn_perm(y, x, pick);
+                }
+        } else {
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
-                const int row = q0 + 8 * (r >> 2) + 4 * hh + (r & 3);
-                if (full || row < T) {
-                    const __bf16 val = (__bf16)oacc[b][r];
-                    Og[(long)row * D + 32 * b + n] = __builtin_bit_cast(uint16_t, val);
-                }
+                const int row = 8 * (r >> 2) + 4 * hh + (r & 3);
+                if (q0 + row < T)
+#pragma unroll
+                    for (int b = 0; b < D / 32; ++b) {
+                        const __bf16 val = (__bf16)oacc[b][r];
+                        Og[row * D + 32 * b + n] = __builtin_bit_cast(uint16_t, val);
+                    }
             }
         }
     }
