@@ -74,6 +74,64 @@ constexpr int wgs_per_cu(int d) { return d == 128 ? 2 : (d == 64 ? 3 : 4); }
 template <bool B> using bc = std::integral_constant<bool, B>;
 template <int I> using ic = std::integral_constant<int, I>;
 
+// Element-wise path of one 32x32 subtile: logits -> weights (as MFMA operands).
+// Inside the lane the chain  t_r = W_r e_r,  W_{r+1} = W_r + t_r  runs over the 16
+// keys in ascending order, so W_r = W_0 prod_{r' < r} (1 + e_r') and the weight of
+// key r is t_r / W_16 * 2^-(carry from all nearer keys).  log2(W_16 / W_0) is this
+// lane's contribution to the carry.  W_0 = 2^-60 keeps the chain inside fp32 for
+// in-lane products up to 2^140; weights below 2^-66 are flushed to zero.  If a chain
+// still gets beyond 2^80 (sharp logits: softplus summing to more than 97 nats over
+// 16 keys) or overflows, the wave redoes the subtile in the log form of Eq. 2 with
+// the overflow-proof base-2 softplus.
+// With MASK (the subtile on the diagonal) key 16hh + r is visible to query n iff
+// 16hh + r < n.
+// chain_of(): what needs no carry.  g: the t_r, or in the log form x - (sum of sp2 over this lane's keys
+// from r on); t_lo, t_hi: both halves' softplus totals.  False: log form.
+template <bool MASK>
+__device__ __forceinline__ bool chain_of(const f32x16& sin, float (&g)[16], float& t_lo, float& t_hi, float c2, int n, int hh)
+{
+    float W = 0x1p-60f;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        float e = fast_exp2(sin[r] * c2);
+        if constexpr (MASK) e = (16 * hh + r < n) ? e : 0.0f;
+        g[r] = W * e;
+        W += g[r];
+    }
+    const bool bad = !(W < 0x1p80f);
+    if (__builtin_expect(__builtin_amdgcn_ballot_w64(bad) == 0, 1)) {
+        both_halves(fast_log2(W) + 60.0f, t_lo, t_hi);   // log2 of the lane's prod (1 + e)
+        return true;
+    }
+    float run = 0.0f;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        g[r] = sin[r] * c2;
+        if constexpr (MASK) g[r] = (16 * hh + r < n) ? g[r] : -INFINITY;
+    }
+#pragma unroll
+    for (int r = 15; r >= 0; --r) {
+        run += sp2(g[r]);
+        g[r] -= run;
+    }
+    both_halves(run, t_lo, t_hi);
+    return false;
+}
+// keys 16..31 (hh = 1) are nearer to the query than keys 0..15
+template <bool LINEAR>
+__device__ __forceinline__ void weights_of(const float (&g)[16], float t_lo, float t_hi, float a, int hh, bf16x8 (&pout)[2])
+{
+    if constexpr (LINEAR) {
+        const float kf = fast_exp2(60.0f - (a + t_hi + (hh == 0 ? t_lo : 0.0f)));
+#pragma unroll
+        for (int r = 0; r < 16; ++r) pout[r >> 3][r & 7] = (__bf16)(g[r] * kf);
+    } else {
+        const float off = a + (hh == 0 ? t_hi : 0.0f);
+#pragma unroll
+        for (int r = 0; r < 16; ++r) pout[r >> 3][r & 7] = (__bf16)fast_exp2(g[r] - off);
+    }
+}
+
 // VL: packed variable-length batch.  The tensors are [H][Ttot][D] ([H/G][Ttot][D] for k, v),
 // sequence s occupies rows cu[s] .. cu[s+1]-1, BH counts (sequence, head) pairs and T_arg,
 // nqb_arg describe the longest sequence (they size the grid); a workgroup whose
@@ -248,58 +306,11 @@ fwd_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
                 oacc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(p[s], vop[2 * b + s], oacc[b], 0, 0, 0);
     };
 
-    // Element-wise path of one 32x32 subtile: logits -> weights (as MFMA operands).
-    // Inside the lane the chain  t_r = W_r e_r,  W_{r+1} = W_r + t_r  runs over the 16
-    // keys in ascending order, so W_r = W_0 prod_{r' < r} (1 + e_r') and the weight of
-    // key r is t_r / W_16 * 2^-(carry from all nearer keys).  log2(W_16 / W_0) is this
-    // lane's contribution to the carry.  W_0 = 2^-60 keeps the chain inside fp32 for
-    // in-lane products up to 2^140; weights below 2^-66 are flushed to zero.  If a chain
-    // still gets beyond 2^80 (sharp logits: softplus summing to more than 97 nats over
-    // 16 keys) or overflows, the wave redoes the subtile in the log form of Eq. 2 with
-    // the overflow-proof base-2 softplus.
-    // With MASK (the subtile on the diagonal) key 16hh + r is visible to query n iff
-    // 16hh + r < n.
     auto ew = [&](auto mask_c, const f32x16& sin, bf16x8 (&pout)[2]) __attribute__((always_inline)) {
-        constexpr bool MASK = decltype(mask_c)::value;
-        float g[16];
-        float W = 0x1p-60f;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            float e = fast_exp2(sin[r] * c2);
-            if constexpr (MASK) e = (16 * hh + r < n) ? e : 0.0f;
-            g[r] = W * e;
-            W += g[r];
-        }
-        const bool bad = !(W < 0x1p80f);
-        if (__builtin_expect(__builtin_amdgcn_ballot_w64(bad) == 0, 1)) {
-            const float l = fast_log2(W) + 60.0f;        // log2 of the lane's prod (1 + e)
-            float l_lo, l_hi;
-            both_halves(l, l_lo, l_hi);
-            // keys 16..31 (hh = 1) are nearer to the query than keys 0..15
-            const float kf = fast_exp2(60.0f - (a + l_hi + (hh == 0 ? l_lo : 0.0f)));
-            a += l_lo + l_hi;
-#pragma unroll
-            for (int r = 0; r < 16; ++r) pout[r >> 3][r & 7] = (__bf16)(g[r] * kf);
-        } else {
-            float y[16];
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                y[r] = sin[r] * c2;
-                if constexpr (MASK) y[r] = (16 * hh + r < n) ? y[r] : -INFINITY;
-            }
-            float run = 0.0f;
-#pragma unroll
-            for (int r = 15; r >= 0; --r) {
-                run += sp2(y[r]);
-                y[r] -= run;                           // x - (sum of sp2 over this lane's keys r..15)
-            }
-            float t_lo, t_hi;
-            both_halves(run, t_lo, t_hi);
-            const float off = a + (hh == 0 ? t_hi : 0.0f);
-            a += t_lo + t_hi;
-#pragma unroll
-            for (int r = 0; r < 16; ++r) pout[r >> 3][r & 7] = (__bf16)fast_exp2(y[r] - off);
-        }
+        float g[16], t_lo, t_hi;
+        if (__builtin_expect(chain_of<decltype(mask_c)::value>(sin, g, t_lo, t_hi, c2, n, hh), 1)) weights_of<true>(g, t_lo, t_hi, a, hh, pout);
+        else weights_of<false>(g, t_lo, t_hi, a, hh, pout);
+        a += t_lo + t_hi;
     };
 
     // The same step in the log form of Eq. 2 with Algorithm 1's in-tile cumulative sum on the
@@ -608,12 +619,188 @@ fwd_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     }
 }
 
+// ------------------------------------------------------------------ small grids
+// Where the 128-row blocks leave most of the chip idle, what counts is the length of one row's chain of
+// subtiles.  Here a workgroup takes one strip of 32 query rows, and its waves take the strip's subtiles from
+// the diagonal on in rounds of one each: logits and chains, which need no carry, side by side; one barrier
+// for the carries; weights, into LDS; one barrier; then O += A V, a wave per 32 columns, over the round's subtiles
+// in order.  Every sum is taken in the order of fwd_bf16_kernel: o is the same, bit for bit (m too,
+// unless that takes its sum_tail()).  Which grids: small_fwd_grid().
+template <int D> struct FwdSmallCfg {
+    static constexpr int NWS = D == 128 ? 4 : 8;        // waves
+    static constexpr int ROW = D * 2;
+    static constexpr int SUB = 32 * ROW;                // one 32-row subtile of K (or V)
+    static constexpr int W_OFF = NWS * 4 * SUB;         // after the waves' K and V, double buffered: weights
+    static constexpr int W_SUB = 2 * 1024;              // of a subtile: two operands of 16 bytes a lane
+};
+
+template <int D>
+__global__ void __launch_bounds__(64 * FwdSmallCfg<D>::NWS)
+fwd_small_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
+                 const uint16_t* __restrict__ v, const uint16_t* __restrict__ rb,
+                 uint16_t* __restrict__ o, float* __restrict__ m,
+                 int T_arg, int BH, int H, int G, int nstrip_arg,
+                 unsigned long long* __restrict__ clocks, const int* __restrict__ cu, int Ttot)
+{
+    using C = FwdSmallCfg<D>;
+    constexpr int NWS = C::NWS;
+    static_assert(D / 32 <= NWS, "a wave per 32 columns");
+    __shared__ __attribute__((aligned(1024))) char smem[C::W_OFF + NWS * C::W_SUB];
+    __shared__ float s_tot[2][NWS][32];                 // per round parity: softplus totals of its subtiles (base 2), per row
+
+    asm volatile("" :: "s"(q), "s"(k), "s"(v), "s"(T_arg), "s"(G));
+    const Share sh = in_scalars(share_of(blockIdx.x, BH, -1));
+    const int bh = sh.bh, head = bh % H;
+    int T = T_arg, nstrip = nstrip_arg;
+    long row0 = bh * (long)T, kvrow0 = (long)(G == 1 ? bh : (int)((unsigned)bh / (unsigned)G)) * T;
+    if (cu) {                                           // packed batch, as in fwd_bf16_kernel
+        const int seq = bh / H;
+        const int c0 = cu[seq];
+        T = min(min(cu[seq + 1], Ttot) - c0, T_arg);
+        if (c0 < 0) return;
+        nstrip = (T + 31) / 32;
+        if (sh.i >= nstrip) return;
+        row0 = (long)head * Ttot + c0;
+        kvrow0 = (long)(head / G) * Ttot + c0;
+    }
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const bool clock = clocks && blockIdx.x == 0 && tid == 0;
+    if (clock) {                                        // as in fwd_bf16_kernel
+        clocks[0] = (unsigned long long)clock64();
+        clocks[1] = (unsigned long long)wall_clock64();
+    }
+    const int n = lane & 31, hh = lane >> 5, gg = lane >> 4, li = lane & 15;
+    const int strip = nstrip - 1 - sh.i;
+    const int q0 = strip * 32;
+    const uint16_t* Qg = q + row0 * D;
+    const uint16_t* Kg = reinterpret_cast<const uint16_t*>(scalar_base(k + kvrow0 * D));
+    const uint16_t* Vg = reinterpret_cast<const uint16_t*>(scalar_base(v + kvrow0 * D));
+
+    // a wave's buffers: K, K, V, V
+    char* const mine = smem + wave * 4 * C::SUB;
+    auto stage = [&](const uint16_t* X, int sub, char* dst) __attribute__((always_inline)) {
+        const int last = T - 1 - sub * 32;              // rows past T are clamped (causality masks them)
+        const uint16_t* xb = X + (long)sub * 32 * D;
+        constexpr int CPR = C::ROW / 16;
+#pragma unroll
+        for (int i = 0; i < C::SUB / 1024; ++i) {
+            const int row = i * (1024 / C::ROW) + lane / CPR;
+            dma16_to_lds_saddr(xb, (min(row, last) * D + (((lane % CPR) ^ swz_perm<D>(row)) << 3)) * 2, dst + i * 1024);
+        }
+    };
+    if (strip - wave >= 0) {
+        stage(Kg, strip - wave, mine);
+        stage(Vg, strip - wave, mine + 2 * C::SUB);
+    }
+    bf16x8 qf[D / 16];
+    {
+        const u32x4* src = reinterpret_cast<const u32x4*>(Qg + (long)min(q0 + n, T - 1) * D + 8 * hh);
+#pragma unroll
+        for (int s = 0; s < D / 16; ++s) qf[s] = __builtin_bit_cast(bf16x8, src[2 * s]);
+    }
+#pragma unroll
+    for (int s = 0; s < D / 16; ++s) asm volatile("" :: "v"(qf[s]));
+    const uint32_t smem0 = lds_offset(smem);
+    const uint32_t ka = lds_offset(mine) + tile_off_perm<D>(perm_row(n), hh);       // K as A operand, ^ (s << 5)
+    uint32_t vtr[2];                                    // V of wave 0, this wave's columns, through the transposing load
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+        vtr[t] = smem0 + 2 * C::SUB + tile_off_perm<D>(16 * (gg >> 1) + (li >> 2) + 4 * t, (4 * wave & (D / 8 - 1)) + 2 * (gg & 1) + ((li & 3) >> 1)) + 8 * (li & 1);
+    const uint32_t wts = smem0 + C::W_OFF + lane * 16;
+    const float c2 = SB_LOG2E / sqrtf((float)D);
+    f32x16 oacc;                                        // columns 32 wave .. (the first D / 32 waves)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) oacc[r] = 0.0f;
+    float a = 0.0f;                                     // carry of the round
+    bool done = false;                                  // every row exhausted: the weights are zero from here on
+
+    int st = 0;
+    for (int top = strip; top >= 0; top -= NWS, st ^= 1) {
+        const int sub = top - wave;
+        float g[16], t_lo = 0.0f, t_hi = 0.0f;
+        bool linear = true;
+        if (sub >= 0) {
+            // this subtile has landed; the K buffer to be refilled was read a round ago, by this wave
+            asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+            if (sub - NWS >= 0) stage(Kg, sub - NWS, mine + (st ^ 1) * C::SUB);
+            u32x4 kop[D / 16];
+#pragma unroll
+            for (int s = 0; s < D / 16; ++s) kop[s] = lds_load16((ka + st * C::SUB) ^ (s << 5));
+            f32x16 acc;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
+#pragma unroll
+            for (int s = 0; s < D / 16; ++s)
+                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kop[s]), qf[s], acc, 0, 0, 0);
+            linear = sub == strip ? chain_of<true>(acc, g, t_lo, t_hi, c2, n, hh) : chain_of<false>(acc, g, t_lo, t_hi, c2, n, hh);
+        }
+        if (hh == 0) s_tot[st][wave][n] = t_lo + t_hi;
+        barrier_lds();                                   // totals and V have landed, the weights before have been used
+        float mine_a = a;
+        for (int w = 0; w < NWS; ++w) {
+            if (w == wave) mine_a = a;
+            a += s_tot[st][w][n];
+        }
+        if (done) continue;                              // alike in all waves
+        if (sub - NWS >= 0) stage(Vg, sub - NWS, mine + (2 + (st ^ 1)) * C::SUB);
+        bf16x8 p[2] = {};
+        if (sub >= 0) {
+            if (linear) weights_of<true>(g, t_lo, t_hi, mine_a, hh, p);
+            else weights_of<false>(g, t_lo, t_hi, mine_a, hh, p);
+            lds_store16(wts + wave * C::W_SUB, p[0]);
+            lds_store16(wts + wave * C::W_SUB + 1024, p[1]);
+        }
+        barrier_lds();
+        if (wave < D / 32) {
+            for (int w = 0; w < min(NWS, top + 1); ++w) {
+#pragma unroll
+                for (int s = 0; s < 2; ++s) {
+                    const uint32_t vs = w * 4 * C::SUB + st * C::SUB + 8 * s * C::ROW;
+                    oacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, lds_load16(wts + w * C::W_SUB + s * 1024)),
+                                                                   tr_pair_at(vtr[0] + vs, vtr[1] + vs), oacc, 0, 0, 0);
+                }
+            }
+        }
+        done = __builtin_amdgcn_ballot_w64(!(a >= CARRY_EXHAUSTED)) == 0;
+        if (done && !m) break;
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // subtiles staged before the sweep stopped
+
+    // ---- store.  oacc[r] is query row 8*(r/4) + 4*hh + r%4, column 32 wave + n.
+    if (wave < D / 32) {
+        if (rb) {                                        // remainder bias, as in fwd_bf16_kernel
+            const float rem = fast_exp2(-a);
+            const float rc = __builtin_bit_cast(float, (uint32_t)rb[head * D + 32 * wave + n] << 16);
+#pragma unroll
+            for (int r = 0; r < 16; ++r) oacc[r] += __shfl(rem, 8 * (r >> 2) + 4 * hh + (r & 3)) * rc;
+        }
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const int row = q0 + 8 * (r >> 2) + 4 * hh + (r & 3);
+            const __bf16 val = (__bf16)oacc[r];
+            if (row < T) o[(row0 + row) * D + 32 * wave + n] = __builtin_bit_cast(uint16_t, val);
+        }
+    }
+    if (m && tid < 32 && q0 + n < T) m[row0 + q0 + n] = -a * SB_LN2;
+    if (clock) {
+        clocks[2] = (unsigned long long)clock64();
+        clocks[3] = (unsigned long long)wall_clock64();
+    }
+}
+
 template <int D, bool WRITE_M, bool RB, bool VL = false, bool TRI = false>
 hipError_t launch_one(const uint16_t* q, const uint16_t* k, const uint16_t* v, const uint16_t* rb,
                       uint16_t* o, float* m, int BH, int H, int G, int T, float enough,
                       unsigned long long* tile_counts, hipStream_t stream,
                       const int* cu = nullptr, int Ttot = 0)
 {
+    if (!TRI && enough == CARRY_EXHAUSTED && (WRITE_M || !tile_counts) && small_fwd_grid(BH, T, D)) {     // halting sweeps stop by blocks
+        const int nstrip = (T + 31) / 32;
+        hipLaunchKernelGGL((fwd_small_kernel<D>), dim3((unsigned)(BH * nstrip)), dim3(64 * FwdSmallCfg<D>::NWS), 0, stream,
+                           q, k, v, rb, o, m, T, BH, H, G, nstrip, tile_counts, cu, Ttot);
+        return hipGetLastError();
+    }
     const int nqb = (T + BQ - 1) / BQ;
     const long grid = share_grid(BH, nqb, false);
     if (grid > 0x7fffffffL) return hipErrorInvalidValue;

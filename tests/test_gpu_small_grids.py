@@ -1,10 +1,10 @@
-"""The backward of grids that leave most of the chip idle: one strip of 32 rows a workgroup, whose waves share
+"""Grids that leave most of the chip idle: one strip of 32 rows a workgroup, whose waves share
 the other side's subtiles.  And, at the same lengths with more heads, the 128-row blocks that larger grids take."""
 import numpy as np
 import pytest
 import torch
 
-from helpers import check_grad, dev, nan_bytes, to64
+from helpers import check_grad, check_m, dev, fwd_bound, nan_bytes, to64
 from test_gpu_exhausted import gen, mixed, sb  # noqa: F401  (fixtures)
 
 pytestmark = pytest.mark.gpu
@@ -82,3 +82,41 @@ def test_packed(sb, oracle, gen, d):
         if n:
             for name, a, r in zip(("dq", "dk", "dv"), got, oracle.bwd(*(to64(t[:, s]) for t in (q, k, v, g)))):
                 check_grad(f"{name} of {n}", to64(a[:, s]), r)
+
+
+@pytest.mark.parametrize("T", [65, 96, 97, 128, 129, 255, 257, 321, 500, 1000, 4096])
+@pytest.mark.parametrize("d", [32, 64, 128])
+def test_forward_strips(sb, oracle, gen, T, d):
+    """o of a small grid is what the 128-row blocks of a large one give, bit for bit; o and m against the oracle."""
+    q, k, v = mixed(gen, 1, 3, T, d, seed=300 + T)
+    r = gen.remainder_embedding(3, d, seed=9)
+    qd, kd, vd, rd = dev(q, k, v, r)
+    o, m = sb.sb_attn_fwd_gqa(qd, kd, vd, r=rd)
+    o2 = sb.sb_attn_fwd(qd, kd, vd)
+    times = 520 // (3 * ((T + 31) // 32)) + 1                 # beyond the largest of the small grids
+    many = [torch.cat([t] * times) for t in (qd, kd, vd)]
+    om, mm = sb.sb_attn_fwd_gqa(*many, r=rd)
+    torch.cuda.synchronize()
+    for i in (0, times - 1):
+        assert torch.equal(o, om[i:i + 1])
+        assert torch.allclose(m, mm[i:i + 1], rtol=1e-5, atol=1e-4)      # sums in another order behind exhausted rows
+    assert torch.equal(o2, sb.sb_attn_fwd(*many)[:1])
+    if T <= 1000:
+        ref, rem = oracle.fwd(to64(q), to64(k), to64(v), r=to64(r))
+        assert np.all(np.abs(to64(o) - ref) <= fwd_bound(ref, to64(v)))
+        check_m(to64(m), rem)
+
+
+@pytest.mark.parametrize("d", [32, 64, 128])
+def test_forward_packed(sb, gen, d):
+    """Sequences of all kinds of lengths in one small grid: each as it is alone."""
+    lens = [1, 0, 32, 33, 64, 65, 96, 400]
+    q, k, v = (t[0] for t in mixed(gen, 1, 3, sum(lens), d, seed=17))
+    cu = torch.tensor(np.cumsum([0] + lens), dtype=torch.int32)
+    qd, kd, vd = dev(q, k, v)
+    o, m = sb.sb_attn_varlen_fwd(qd, kd, vd, cu.cuda(), max(lens))
+    for i, n in enumerate(lens):
+        s = slice(int(cu[i]), int(cu[i]) + n)
+        if n:
+            o1, m1 = sb.sb_attn_fwd_train(*(t[None, :, s].contiguous() for t in (qd, kd, vd)))
+            assert torch.equal(o[:, s], o1[0]) and torch.allclose(m[:, s], m1[0], rtol=1e-5, atol=1e-4)
