@@ -332,15 +332,16 @@ int room(int T)
 // 49 / 43 / 39, B1 H32 Hkv8 T65000 d128 53 / 46 / 46, B8 H16 T16384 d128 167 / 161 / 162, B1 H8 T2000 d64
 // 12.8 / 9.4 / 6.7.
 //
-// A small cache is spread over the chip as well: one workgroup a head is bound by what one CU can load (2 us
-// per 128 KB of a head's K and V), three launches by their latencies.  That reads every key, so it is
-// limited by the size of the whole cache, and it pays unless all heads end within their nearest keys.  Without m, us, as
-// before / spread, a third of the kv heads far, then none:
+// A small cache is spread over the chip as well: one workgroup a head is bound by what one CU can load (per pass
+// of 256 keys 2.2 us at d = 128, 1.3 at d = 64), three launches by their latencies.  That reads every key (0.1 us per MB of
+// cache on top of 6 to 7.4), so it is limited by the size of the whole cache, and it pays unless all heads end within
+// their nearest keys.  Without m, us, as before / spread, a third of the kv heads far, then none:
 //   B1 H12 Hkv4 d128 T600 10.2 / 7.5, 6.8 / 7.5; T1500 18.0 / 7.6, 6.7 / 7.5
 //   B2 H8 T1000 d64 9.0 / 6.3, 4.6 / 6.2; B4 H8 T1200 d128 (20 MB) 15.2 / 9.3, 6.7 / 9.3
 //   B1 H8 T2000 d64 12.5 / 6.4, 11 / 6.4; B1 H8 T6000 d128 (25 MB) 15.2 / 9.4, 10.0 / 9.3
 //   B2 H16 T2000 d128 (33 MB) 16.1 / 9.9, 10.0 / 9.8
-// and not where B1 H12 Hkv4 T333 d128 7.8 / 7.6, 6.4 / 7.4; B4 H8 T400 d128 7.7 / 7.7, 6.4 / 7.7;
+//   B5 H30 Hkv10 T588 d64 (8 MB) 7.8 / 6.3, 4.7 / 6.4
+// and not where B8 H16 T600 d64 (20 MB) 7.6 / 8.2, 4.7 / 8.2; B1 H12 Hkv4 T333 d128 7.8 / 7.6, 6.4 / 7.4; B4 H8 T400 d128 7.7 / 7.7, 6.4 / 7.7;
 // B8 H16 T1000 d128 (66 MB) 14.0 / 14.7, 7.0 / 14.8; B2 H16 T4000 d128 (66 MB) 16.4 / 14.9, 9.9 / 15.1.
 struct Split {
     int near, C, nfar;
@@ -349,7 +350,8 @@ struct Split {
 Split split_of(long wgs, double cache_bytes, int T, bool want_m)
 {
     Split s = {T, NEAR, 0};
-    const bool spread = T > 2 * NEAR && cache_bytes <= (T > ALONE ? 34e6 : 24e6);
+    const int passes = (T + NEAR - 1) / NEAR;
+    const bool spread = passes > 2 && cache_bytes <= std::min(34e6, 12e6 * (passes - 2));
     if (T <= ALONE && !spread) return s;
     const bool all = want_m || spread;
     s.near = all ? 0 : NEAR;

@@ -85,11 +85,12 @@ template <int I> using ic = std::integral_constant<int, I>;
 // the overflow-proof base-2 softplus.
 // With MASK (the subtile on the diagonal) key 16hh + r is visible to query n iff
 // 16hh + r < n.
-// chain_of(): what needs no carry.  g: the t_r, or in the log form x - (sum of sp2 over this lane's keys
-// from r on); t_lo, t_hi: both halves' softplus totals.  False: log form.
-template <bool MASK>
-__device__ __forceinline__ bool chain_of(const f32x16& sin, float (&g)[16], float& t_lo, float& t_hi, float c2, int n, int hh)
+// chain_of(): what needs no carry, handed to then(linear, g, t_lo, t_hi).  g: the t_r, or in the log form
+// x - (sum of sp2 over this lane's keys from r on); t_lo, t_hi: both halves' softplus totals.
+template <bool MASK, class F>
+__device__ __forceinline__ void chain_of(const f32x16& sin, float c2, int n, int hh, F then)
 {
+    float g[16], t_lo, t_hi;
     float W = 0x1p-60f;
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
@@ -101,7 +102,8 @@ __device__ __forceinline__ bool chain_of(const f32x16& sin, float (&g)[16], floa
     const bool bad = !(W < 0x1p80f);
     if (__builtin_expect(__builtin_amdgcn_ballot_w64(bad) == 0, 1)) {
         both_halves(fast_log2(W) + 60.0f, t_lo, t_hi);   // log2 of the lane's prod (1 + e)
-        return true;
+        then(bc<true>{}, g, t_lo, t_hi);
+        return;
     }
     float run = 0.0f;
 #pragma unroll
@@ -115,7 +117,7 @@ __device__ __forceinline__ bool chain_of(const f32x16& sin, float (&g)[16], floa
         g[r] -= run;
     }
     both_halves(run, t_lo, t_hi);
-    return false;
+    then(bc<false>{}, g, t_lo, t_hi);
 }
 // keys 16..31 (hh = 1) are nearer to the query than keys 0..15
 template <bool LINEAR>
@@ -307,10 +309,10 @@ fwd_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     };
 
     auto ew = [&](auto mask_c, const f32x16& sin, bf16x8 (&pout)[2]) __attribute__((always_inline)) {
-        float g[16], t_lo, t_hi;
-        if (__builtin_expect(chain_of<decltype(mask_c)::value>(sin, g, t_lo, t_hi, c2, n, hh), 1)) weights_of<true>(g, t_lo, t_hi, a, hh, pout);
-        else weights_of<false>(g, t_lo, t_hi, a, hh, pout);
-        a += t_lo + t_hi;
+        chain_of<decltype(mask_c)::value>(sin, c2, n, hh, [&](auto linear, const float (&g)[16], float t_lo, float t_hi) __attribute__((always_inline)) {
+            weights_of<decltype(linear)::value>(g, t_lo, t_hi, a, hh, pout);
+            a += t_lo + t_hi;
+        });
     };
 
     // The same step in the log form of Eq. 2 with Algorithm 1's in-tile cumulative sum on the
@@ -733,7 +735,15 @@ fwd_small_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
 #pragma unroll
             for (int s = 0; s < D / 16; ++s)
                 acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kop[s]), qf[s], acc, 0, 0, 0);
-            linear = sub == strip ? chain_of<true>(acc, g, t_lo, t_hi, c2, n, hh) : chain_of<false>(acc, g, t_lo, t_hi, c2, n, hh);
+            auto keep = [&](auto lin, const float (&x)[16], float x_lo, float x_hi) __attribute__((always_inline)) {
+                linear = decltype(lin)::value;
+                t_lo = x_lo;
+                t_hi = x_hi;
+#pragma unroll
+                for (int r = 0; r < 16; ++r) g[r] = x[r];
+            };
+            if (sub == strip) chain_of<true>(acc, c2, n, hh, keep);
+            else chain_of<false>(acc, c2, n, hh, keep);
         }
         if (hh == 0) s_tot[st][wave][n] = t_lo + t_hi;
         barrier_lds();                                   // totals and V have landed, the weights before have been used
