@@ -451,6 +451,9 @@ fwd_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
             if (i + 1 < npr) pair_tile(i + 1, ic<1>{});
         }
         if (!(ntail & 1)) add(x1);                           // else the last tile was staged twice
+        // (the lane index once more, so that it is not kept across the loop: d = 32 has no register to spare)
+        const int at = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+        const int n = at & 31, hh = at >> 5;
         float lo, hi;
         both_halves(ln, lo, hi);
         barrier_lds();                                       // the tiles have been read
@@ -611,7 +614,8 @@ fwd_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     }
     if constexpr (WRITE_M) {
         if (it < ntile) sum_tail(ntile - it);
-        if (wave_live && hh == 0 && q0 + n < T) m[row0 + q0 + n] = -a * SB_LN2;
+        const int at = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+        if (wave_live && at < 32 && q0 + at < T) m[row0 + q0 + at] = -a * SB_LN2;
     }
     if constexpr (WRITE_M) {
         if (tile_counts && wg == 0 && tid == 0) {
