@@ -669,8 +669,14 @@ __device__ __forceinline__ int reaching(uint32_t w, int ks)
 // ------------------------------------------------------------------ dK / dV kernel
 // SP groups of four waves take the block's query tiles in turn (tile t: group t % SP), each into
 // accumulators of its own, added up at the end in LDS.  Two groups where a block has a CU to itself
-// anyway: one wave per SIMD issues an instruction every five clocks at best, two keep it busy
-// (B2 H4 T777 d32: 24 -> 19 us).
+// anyway (one wave per SIMD issues an instruction every five clocks at best, two keep it busy), and where
+// few enough blocks are left once some heads turn out near: what counts then is the longest block's
+// chain.  One group / two, us, all heads far, then a third, then none:
+//   B1 H16 T4096 d32 (512 blocks, 32 a head) 115 / 92, 115 / 84, 18 / 22; B1 H24 T4096 d64 (768, 32) 171 / 179, 143 / 101,
+//   37 / 42; B2 H24 T1024 d64 (384, 8) 39 / 33, 39 / 32, 24 / 27; B1 H40 T2048 d64 (640, 16) 78 / 86, 73 / 55, 32 / 39
+// and not B8 H16 T512 d64 (512, 4) 25 / 29, 24 / 29, 23 / 28; B8 H8 T2000 d32 (1024, 16) 78 / 94, 60 / 52, 28 / 36;
+// B2 H20 T4096 d64 (1280, 32) 275 / 291, 158 / 143, 52 / 65; B8 H16 T2048 d64 (2048, 16) 236 / 259, 126 / 164, 80 / 108.
+constexpr long in_turn_grid(int nkb) { return std::clamp(48L * nkb, ONE_PER_CU, 1024L); }
 template <int D, int SP> struct DkvCfg {
     static constexpr int T_OFF = SP * 2 * StageCfg<D>::STAGE;   // after the double buffers
     static constexpr int T_WAVE = 2 * SCR_MAT;             // A and dZ scratch of one wave
@@ -1945,6 +1951,7 @@ hipError_t launch_one(const uint16_t* q, const uint16_t* k, const uint16_t* v, c
     const int nchunk = (T + DR_ROWS - 1) / DR_ROWS;
     const bool pairs = D == 128 && BHkv >= 128;             // see share_of()
     const long gq = share_grid(BH, nqb, false), gk = share_grid(BHkv, nkb, pairs);
+    const long blocks_k = VL ? Hkv * ((long)Ttot / BKW + B) : gk;      // that have something to do
     const int run_q = VL || G > 1 ? -1 : share_run(BH, nqb), run_k = VL || G > 1 ? -1 : share_run(BHkv, nkb);
     // checked before the first launch, so that an error leaves nothing enqueued
     if (gq > 0x7fffffffL || gk > 0x7fffffffL || nchunk * (long)BH > 0x7fffffffL) return hipErrorInvalidValue;
@@ -1979,7 +1986,7 @@ hipError_t launch_one(const uint16_t* q, const uint16_t* k, const uint16_t* v, c
             SB_LAUNCH(gk, 512, (bwd_dkv_pair_kernel<D, 4, GQAV, VL>),                                           \
                       q, k, v, dout, ca, cb, dk, dv, first2, T, BHkv, H, G, nkb, nqb, nt32, cu, Ttot, pairs);    \
         }                                                                                                       \
-    } else if (gk <= ONE_PER_CU) {                                                                              \
+    } else if (blocks_k <= in_turn_grid(nkb)) {                                                                            \
         SB_LAUNCH(gk, 2 * NTHREADS, (bwd_dkv_kernel<D, GQAV, VL, 2>),                                           \
                   q, k, v, dout, ca, cb, dk, dv, first2, T, BHkv, H, G, nkb, nt32, cu, Ttot, run_k);             \
     } else {                                                                                                    \
