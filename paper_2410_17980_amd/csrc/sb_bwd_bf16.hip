@@ -1951,7 +1951,8 @@ hipError_t launch_one(const uint16_t* q, const uint16_t* k, const uint16_t* v, c
     const int nchunk = (T + DR_ROWS - 1) / DR_ROWS;
     const bool pairs = D == 128 && BHkv >= 128;             // see share_of()
     const long gq = share_grid(BH, nqb, false), gk = share_grid(BHkv, nkb, pairs);
-    const long blocks_k = VL ? Hkv * ((long)Ttot / BKW + B) : gk;      // that have something to do
+    const long strips_q = pieces(B, H, T, 32, VL, Ttot), strips_k = pieces(B, Hkv, T, 32, VL, Ttot);
+    const long blocks_k = pieces(B, Hkv, T, BKW, VL, Ttot);
     const int run_q = VL || G > 1 ? -1 : share_run(BH, nqb), run_k = VL || G > 1 ? -1 : share_run(BHkv, nkb);
     // checked before the first launch, so that an error leaves nothing enqueued
     if (gq > 0x7fffffffL || gk > 0x7fffffffL || nchunk * (long)BH > 0x7fffffffL) return hipErrorInvalidValue;
@@ -1964,7 +1965,7 @@ hipError_t launch_one(const uint16_t* q, const uint16_t* k, const uint16_t* v, c
     if (e != hipSuccess) return e;                                                                              \
     }
 #define SB_DQ(RBV)                                                                                              \
-    if (small_grid(BH, T, D)) {                                                                                  \
+    if (small_grid(strips_q, T, D)) {                                                                                  \
         hipLaunchKernelGGL((bwd_dq_small_kernel<D>), dim3((unsigned)(BH * nt32)), dim3(64 * SmallCfg<D>::NWS), 0, stream, \
                            q, k, v, rb, m, dout, dq, ca, cb, first, T, BH, H, G, nt32, nqb, nt32, cu, Ttot);    \
         if ((e = hipGetLastError()) != hipSuccess) return e;                                                    \
@@ -1974,12 +1975,12 @@ hipError_t launch_one(const uint16_t* q, const uint16_t* k, const uint16_t* v, c
 // dimensions leave room for two workgroups of the one-wave-per-strip kernel per CU, which
 // is faster there (measured).
 #define SB_DKV(GQAV)                                                                                            \
-    if (small_grid(BHkv, T, D)) {                                                                               \
+    if (small_grid(strips_k, T, D)) {                                                                               \
             hipLaunchKernelGGL((bwd_dkv_small_kernel<D>), dim3((unsigned)(BHkv * nt32)), dim3(64 * SmallCfg<D>::NWS), 0, stream, \
                                q, k, v, dout, ca, cb, dk, dv, first, T, BHkv, H, G, nt32, nqb, nt32, cu, Ttot); \
         if ((e = hipGetLastError()) != hipSuccess) return e;                                                    \
     } else if constexpr (D == 128) {                                                                            \
-        if (BHkv * (long)nkb <= small_kv_grid(nkb)) {                                                           \
+        if (blocks_k <= small_kv_grid(nkb)) {                                                         \
             SB_LAUNCH(share_grid(BHkv, nkb64, false), 256, (bwd_dkv_pair_kernel<D, 2, GQAV, VL>),               \
                       q, k, v, dout, ca, cb, dk, dv, first2, T, BHkv, H, G, nkb64, nqb, nt32, cu, Ttot, 0);      \
         } else {                                                                                                \

@@ -809,7 +809,7 @@ hipError_t launch_one(const uint16_t* q, const uint16_t* k, const uint16_t* v, c
                       unsigned long long* tile_counts, hipStream_t stream,
                       const int* cu = nullptr, int Ttot = 0)
 {
-    if (!TRI && enough == CARRY_EXHAUSTED && (WRITE_M || !tile_counts) && small_fwd_grid(BH, T, D)) {     // halting sweeps stop by blocks
+    if (!TRI && enough == CARRY_EXHAUSTED && (WRITE_M || !tile_counts) && small_fwd_grid(pieces(BH / H, H, T, 32, VL, Ttot), T, D)) {     // halting sweeps stop by blocks
         const int nstrip = (T + 31) / 32;
         hipLaunchKernelGGL((fwd_small_kernel<D>), dim3((unsigned)(BH * nstrip)), dim3(64 * FwdSmallCfg<D>::NWS), 0, stream,
                            q, k, v, rb, o, m, T, BH, H, G, nstrip, tile_counts, cu, Ttot);

@@ -2,6 +2,8 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 namespace sb {
 
 // Block i of a head (i = 0 the longest) and block n-1-i form pair i, of the same causal cost for
@@ -44,10 +46,18 @@ inline long share_grid(long heads, int nblk, bool pairs)
 // B1 H24 T1000 d128 (768) 40 / 55; B1 H4 T64 d64 5.0 / 6.1, 6.4 / 6.3.  (All heads far; where they are near the
 // strips gain more.)  4096: the kernels' arrays hold 128 strips.
 constexpr int SMALL_T = 4096;
-inline bool small_grid(long heads, int T, int d)
+inline bool small_grid(long strips, int T, int d)
 {
     const long limit = d == 128 ? 256 : T >= 1024 ? 768 : T > 341 ? 3L * T / 4 : 256;
-    return T > 64 && T <= SMALL_T && heads * ((T + 31) / 32) <= limit;
+    return T > 64 && T <= SMALL_T && strips <= limit;
+}
+
+// How many strips or blocks of `rows` rows there are: exactly, or in a packed batch of nseq sequences, whose
+// lengths the host does not know, at most (and as many as in the batched call where they are all equal).
+inline long pieces(int B, int H, int T, int rows, bool packed, int Ttot)
+{
+    const long all = (long)B * H * ((T + rows - 1) / rows);
+    return packed ? std::min(all, (long)H * (Ttot / rows + B)) : all;
 }
 
 // Grids of the forward that take one strip of 32 rows a workgroup, its waves taking the strip's subtiles in rounds
@@ -59,10 +69,10 @@ inline bool small_grid(long heads, int T, int d)
 //   none far        12.2 / 7.3 and 17.2 / 10.4 for B1 H8 T700 d128, 8.9 / 10.4 and 41 / 22 for B1 H4 T4000 d64
 // and not, a third far, B4 H8 T700 d64 (704) 13.5 / 16.2, 13.6 / 17.6; B1 H24 T1000 d128 (768) 26.4 / 28.1, 26.5 / 31.8;
 // B4 H16 T300 d32 (640) 6.9 / 9.8, 7.0 / 10.1.  At d = 32 a chain of 10 subtiles is not worth the rounds' barriers.
-inline bool small_fwd_grid(long heads, int T, int d)
+inline bool small_fwd_grid(long strips, int T, int d)
 {
     const long limit = T < 256 ? 256 : T < 512 || d == 128 ? 384 : 512;
-    return T > (d == 32 ? 320 : 64) && T <= SMALL_T && heads * ((T + 31) / 32) <= limit;
+    return T > (d == 32 ? 320 : 64) && T <= SMALL_T && strips <= limit;
 }
 
 // log2 of the run, -1: turn with every block.  A run pays where the launch is several rounds deep and
