@@ -1033,14 +1033,14 @@ template <int D, int KS> struct Dkv3Cfg {
     static constexpr int NPW = (LOADS + NW2 - 1) / NW2;
 };
 
-template <int D, int KS, bool GQA, bool VL>
+template <int D, int KS, bool GQA, bool VL, bool PAIRS>
 __global__ void __launch_bounds__(128 * KS, 1)
 bwd_dkv_pair_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
                     const uint16_t* __restrict__ v, const uint16_t* __restrict__ dout,
                     const float* __restrict__ ca, const float* __restrict__ cb,
                     float* __restrict__ dk, float* __restrict__ dv, const uint32_t* __restrict__ first,
                     int T_arg, int BH, int H, int G_arg, int nkb_arg, int nqb_arg, int nt32,
-                    const int* __restrict__ cu, int Ttot, int pairs, int first_wg)
+                    const int* __restrict__ cu, int Ttot, int first_wg)
 {
     using C = StageCfg<D>;
     using CK = Dkv3Cfg<D, KS>;
@@ -1050,7 +1050,7 @@ bwd_dkv_pair_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
     __shared__ __attribute__((aligned(1024))) char smem[CK::LDS_BYTES];
 
     const int wg = first_wg + blockIdx.x;
-    const Share sh = in_scalars(pairs ? share_in_pairs(wg, nkb_arg) : share_of(wg, BH, -1));
+    const Share sh = in_scalars(PAIRS ? share_in_pairs(wg, nkb_arg) : share_of(wg, BH, -1));
     const int bh = sh.bh;
     if (bh >= BH) return;
 
@@ -1063,7 +1063,7 @@ bwd_dkv_pair_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
     const int gg = lane >> 4, li = lane & 15;
 
     KvHead kh;
-    if (!kv_head<D, VL>(kh, bh, T_arg, nkb_arg, CK::KEYS, H, G, nt32, cu, Ttot) || sh.i >= (pairs ? (kh.nkb + 1) >> 1 : kh.nkb)) return;
+    if (!kv_head<D, VL>(kh, bh, T_arg, nkb_arg, CK::KEYS, H, G, nt32, cu, Ttot) || sh.i >= (PAIRS ? (kh.nkb + 1) >> 1 : kh.nkb)) return;
     const int T = kh.T, nkb = kh.nkb;
     const long base = kh.base, qrow0 = kh.qrow0, qrow_step = kh.qrow_step;
     const long cbase = kh.cbase, cbase_step = kh.cbase_step, cstride = kh.cstride;
@@ -1251,56 +1251,70 @@ bwd_dkv_pair_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
         __builtin_amdgcn_sched_barrier(0);
     };
 
-    for (int part = 0; part <= pairs; ++part) {
+    float cn0, cn1;                                          // ca, cb of this wave's subtile of the next tile
+    const uint32_t* fg = nullptr;
+    // rows past T: an infinite carry gives A = 0 and G = 0, and with cb = 0 also dZ = 0 (a dead
+    // strip's rows lie outside the arrays; those of queries that do not reach the keys are not used)
+    auto load_carries = [&](int jt, bool live) __attribute__((always_inline)) {
+        const int j = jt * TK + 32 * role + n;
+        cn0 = (j < T && live) ? cag[j] : INFINITY;
+        cn1 = (j < T && live) ? cbg[j] : 0.0f;
+    };
+    // a head's first tile for block kb, into buffer b, and its carries
+    auto first_tile = [&](int g, int kb, int b) __attribute__((always_inline)) {
+        const int k0 = kb * CK::KEYS + strip * 32, jt0 = kb * CK::KEYS / TK;
+        Qg = q + (qrow0 + g * qrow_step) * D;
+        Gg = dout + (qrow0 + g * qrow_step) * D;
+        cag = ca + cbase + g * cbase_step + (k0 >> 5) * cstride;
+        cbg = cb + cbase + g * cbase_step + (k0 >> 5) * cstride;
+        fg = first + (kh.qhead0 + g) * 2 * nqb_arg;
+        load_carries(jt0, k0 < T);
+        stage(jt0, smem + b * C::STAGE);
+    };
+    // All that block kb starts from: the first tile into buffer b, K into the one after it, V into half p of the
+    // scratch; from there into registers: as whole rows and once, not as 32 bytes of 32 rows an instruction and by
+    // both waves of a strip.  These 96 KB take a CU 6 us, a third of a short block's time.  A pair's second
+    // block asks for them in the last interval of the first, which reads none of these three places, so that they
+    // arrive under its back and its stores: B8 H16 T4096 all near 347 -> 318 us, a third far 634 -> 614, all far
+    // 1290 -> 1268.
+    static_assert(CK::KEYS * C::ROW <= C::STAGE && CK::KEYS * C::ROW <= CK::SCR_BUF, "the block's rows fit");
+    int buf0 = 0, vhalf = 0;
+    auto begin = [&](int kb, int b, int p) __attribute__((always_inline)) {
+        buf0 = b;
+        vhalf = p;
+        first_tile(0, kb, b);
+        constexpr int KLOADS = CK::KEYS * C::ROW / 1024 / NW2;
+        const int K0 = kb * CK::KEYS;
+        char* const kp = smem + (b == 2 ? 0 : b + 1) * C::STAGE;
+        char* const vp = smem + CK::T_OFF + p * CK::SCR_BUF;
+#pragma unroll
+        for (int i = 0; i < KLOADS; ++i) {
+            const int row = (wave + NW2 * i) * C::BLK_ROWS + lane / C::CPR;
+            const int off = (min(row, T - 1 - K0) * D + (((lane % C::CPR) ^ swz_perm<D>(row)) << 3)) * 2;
+            dma16_to_lds_saddr(k + base + (long)K0 * D, off, kp + (wave + NW2 * i) * 1024);
+            dma16_to_lds_saddr(v + base + (long)K0 * D, off, vp + (wave + NW2 * i) * 1024);
+        }
+    };
+    begin(sh.i, 0, 0);
+    for (int part = 0;; ++part) {
         const int kb = part == 0 ? sh.i : nkb - 1 - sh.i;    // small kb = most later queries = first
-        if (part == 1 && 2 * sh.i == nkb - 1) break;         // odd block count: the middle block is alone
+        const bool more = PAIRS && part == 0 && 2 * sh.i != nkb - 1;   // odd block count: the middle block is alone
         const int K0 = kb * CK::KEYS;
         const int k0 = K0 + strip * 32;                      // the strip's 32 keys
         const int kt32 = k0 >> 5;
         const bool live = k0 < T;
         const int jt0 = K0 / TK;
-        float cn0, cn1;                                      // ca, cb of this wave's subtile of the next tile
-        // rows past T: an infinite carry gives A = 0 and G = 0, and with cb = 0 also dZ = 0 (a dead
-        // strip's rows lie outside the arrays; those of queries that do not reach the keys are not used)
-        auto load_carries = [&](int jt) __attribute__((always_inline)) {
-            const int j = jt * TK + 32 * role + n;
-            cn0 = (j < T && live) ? cag[j] : INFINITY;
-            cn1 = (j < T && live) ? cbg[j] : 0.0f;
-        };
-        // the block's first tile of a head and its carries
-        const uint32_t* fg = nullptr;
         const int nqb = (T + BQ - 1) / BQ;
-        auto first_tile = [&](int g) __attribute__((always_inline)) {
-            Qg = q + (qrow0 + g * qrow_step) * D;
-            Gg = dout + (qrow0 + g * qrow_step) * D;
-            cag = ca + cbase + g * cbase_step + kt32 * cstride;
-            cbg = cb + cbase + g * cbase_step + kt32 * cstride;
-            fg = first + (kh.qhead0 + g) * 2 * nqb_arg;
-            load_carries(jt0);
-            stage(jt0, smem);
-        };
-        if (part > 0) barrier_lds();                  // everyone is done with the LDS of the block before
-        first_tile(0);                                       // fetched together with the stationary rows
-        // K and V of the block into the other two tile buffers and from there into registers: as whole rows
-        // and once, not as 32 bytes of 32 rows an instruction and by both waves of a strip (B8 H16 T4096 all
-        // near 374 -> 353 us, a third far 636 -> 627)
-        static_assert(CK::KEYS * C::ROW <= C::STAGE, "the block's rows fit a tile buffer");
-        constexpr int KLOADS = CK::KEYS * C::ROW / 1024 / NW2;
-#pragma unroll
-        for (int i = 0; i < KLOADS; ++i) {
-            const int row = (wave + NW2 * i) * C::BLK_ROWS + lane / C::CPR;
-            const int off = (min(row, T - 1 - K0) * D + (((lane % C::CPR) ^ swz_perm<D>(row)) << 3)) * 2;
-            dma16_to_lds_saddr(k + base + (long)K0 * D, off, smem + C::STAGE + (wave + NW2 * i) * 1024);
-            dma16_to_lds_saddr(v + base + (long)K0 * D, off, smem + 2 * C::STAGE + (wave + NW2 * i) * 1024);
-        }
         dma_wait<0>();
         barrier_lds();
         {
-            const uint32_t ka = smem0 + C::STAGE + strip * 32 * C::ROW + tile_off_perm<D>(perm_row(n), hh);
+            const uint32_t at = strip * 32 * C::ROW + tile_off_perm<D>(perm_row(n), hh);
+            const uint32_t ka = smem0 + (buf0 == 2 ? 0 : buf0 + 1) * C::STAGE + at;
+            const uint32_t va = smem0 + CK::T_OFF + vhalf * CK::SCR_BUF + at;
 #pragma unroll
             for (int s = 0; s < D / 16; ++s) {
                 kf[s] = __builtin_bit_cast(bf16x8, lds_load16(ka ^ (s << 5)));
-                vf[s] = __builtin_bit_cast(bf16x8, lds_load16((ka ^ (s << 5)) + C::STAGE));
+                vf[s] = __builtin_bit_cast(bf16x8, lds_load16(va ^ (s << 5)));
             }
         }
 #pragma unroll
@@ -1313,11 +1327,11 @@ bwd_dkv_pair_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
         if (g > 0) {
             dma_wait<0>();                                   // the steady state's last staging, read by nobody
             barrier_lds();                                   // everyone is done with the LDS of the head before
-            first_tile(g);
+            first_tile(g, kb, buf0);
         }
 
         // ---- sweep over 64-row query tiles, from the block's diagonal to the end.  Interval
-        // `it` (between two barriers) holds the front of tile jt0 + it (buffer it % 3, scratch
+        // `it` (between two barriers) holds the front of tile jt0 + it (buffer (buf0 + it) % 3, scratch
         // it & 1) and the back of tile jt0 + it - 1; the staging loads of tile jt0 + it + 1 are
         // issued at its start, after the carries of that tile (vector memory operations
         // complete in order, so the carries must not queue behind the staging loads).
@@ -1340,8 +1354,8 @@ bwd_dkv_pair_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
                 // LDS addresses of the tile buffers of tiles it, it - 1, it + 1 and of the scratch
                 // of tiles it, it - 1; they rotate, nothing is recomputed.  The tile staged in an
                 // interval is tile it + 1, or, after the last one, that tile once more (never read).
-                uint32_t a_cur = smem0 + (it % 3) * C::STAGE, a_prev = smem0 + ((it + 2) % 3) * C::STAGE;
-                uint32_t a_next = smem0 + ((it + 1) % 3) * C::STAGE;
+                uint32_t a_cur = smem0 + ((buf0 + it) % 3) * C::STAGE, a_prev = smem0 + ((buf0 + it + 2) % 3) * C::STAGE;
+                uint32_t a_next = smem0 + ((buf0 + it + 1) % 3) * C::STAGE;
                 uint32_t s_cur = scr + (it & 1) * CK::SCR_BUF, s_prev = scr + ((it + 1) & 1) * CK::SCR_BUF;
                 const int tn = min(it + 1, ntile - 1);
                 const uint16_t* xn = Qg + (long)(jt0 + tn) * TK * D;
@@ -1372,7 +1386,7 @@ bwd_dkv_pair_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
                 word_next = 0;
                 continue;
             }
-            const int bcur = it % 3, bprev = (it + 2) % 3, bnext = (it + 1) % 3;   // buffers of tiles it, it - 1, it + 1
+            const int bcur = (buf0 + it) % 3, bprev = (buf0 + it + 2) % 3, bnext = (buf0 + it + 1) % 3;   // buffers of tiles it, it - 1, it + 1
             dma_wait<0>();
             barrier_lds();        // tile `it` has landed, the scratch of tile it-1 is complete, tile it-2 is free
             const float car = cn0, cbl = cn1;
@@ -1380,9 +1394,11 @@ bwd_dkv_pair_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
             there = reaching(word_next, kt32);
             if (it + 1 < ntile) {
                 const int jt = jt0 + it + 1;
-                load_carries(jt);
+                load_carries(jt, live);
                 word_next = start_word(fg, jt, reach.sure);
                 stage(jt, smem + bnext * C::STAGE);
+            } else if (it == ntile && more && g == G - 1) {
+                begin(nkb - 1 - kb, bcur, it & 1);
             }
             const int jbase = (jt0 + it) * TK;
             const uint32_t qt = smem0 + bcur * C::STAGE + role * 32 * C::ROW;
@@ -1410,6 +1426,7 @@ bwd_dkv_pair_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
         }
 
         if (live) store_strip<D>((role == 0 ? dv : dk) + base + (long)k0 * D, T - k0, acc, role == 0 ? 1.0f : scale, n, hh);
+        if (!more) break;
     }
 }
 
@@ -1949,7 +1966,7 @@ hipError_t launch_one(const uint16_t* q, const uint16_t* k, const uint16_t* v, c
     const uint32_t* first2 = reinterpret_cast<const uint32_t*>(first);     // of a tile's two strips
     float* part = reinterpret_cast<float*>(first + (long)BH * nqb * 4);
     const int nchunk = (T + DR_ROWS - 1) / DR_ROWS;
-    const bool pairs = D == 128 && BHkv >= 128;             // see share_of()
+    const bool pairs = D == 128 && !VL && G == 1 && BHkv >= 128;   // see Share
     const long gq = share_grid(BH, nqb, false), gk = share_grid(BHkv, nkb, pairs);
     const long strips_q = pieces(B, H, T, 32, VL, Ttot), strips_k = pieces(B, Hkv, T, 32, VL, Ttot);
     const long blocks_k = pieces(B, Hkv, T, BKW, VL, Ttot);
@@ -1981,11 +1998,16 @@ hipError_t launch_one(const uint16_t* q, const uint16_t* k, const uint16_t* v, c
         if ((e = hipGetLastError()) != hipSuccess) return e;                                                    \
     } else if constexpr (D == 128) {                                                                            \
         if (blocks_k <= small_kv_grid(nkb)) {                                                         \
-            SB_LAUNCH(share_grid(BHkv, nkb64, false), 256, (bwd_dkv_pair_kernel<D, 2, GQAV, VL>),               \
-                      q, k, v, dout, ca, cb, dk, dv, first2, T, BHkv, H, G, nkb64, nqb, nt32, cu, Ttot, 0);      \
+            SB_LAUNCH(share_grid(BHkv, nkb64, false), 256, (bwd_dkv_pair_kernel<D, 2, GQAV, VL, false>),               \
+                      q, k, v, dout, ca, cb, dk, dv, first2, T, BHkv, H, G, nkb64, nqb, nt32, cu, Ttot);      \
         } else {                                                                                                \
-            SB_LAUNCH(gk, 512, (bwd_dkv_pair_kernel<D, 4, GQAV, VL>),                                           \
-                      q, k, v, dout, ca, cb, dk, dv, first2, T, BHkv, H, G, nkb, nqb, nt32, cu, Ttot, pairs);    \
+            constexpr bool CAN = !VL && !GQAV;                                                                  \
+            if (CAN && pairs)                                                                                   \
+                SB_LAUNCH(gk, 512, (bwd_dkv_pair_kernel<D, 4, GQAV, VL, CAN>),                                  \
+                          q, k, v, dout, ca, cb, dk, dv, first2, T, BHkv, H, G, nkb, nqb, nt32, cu, Ttot)       \
+            else                                                                                                \
+                SB_LAUNCH(gk, 512, (bwd_dkv_pair_kernel<D, 4, GQAV, VL, false>),                                \
+                          q, k, v, dout, ca, cb, dk, dv, first2, T, BHkv, H, G, nkb, nqb, nt32, cu, Ttot)       \
         }                                                                                                       \
     } else if (blocks_k <= in_turn_grid(nkb)) {                                                                            \
         SB_LAUNCH(gk, 2 * NTHREADS, (bwd_dkv_kernel<D, GQAV, VL, 2>),                                           \
@@ -2007,8 +2029,9 @@ hipError_t launch_one(const uint16_t* q, const uint16_t* k, const uint16_t* v, c
     }
     if (passes & 2) {
         // a packed batch always takes the grouped variant (a group of one included)
-        if (VL || G > 1) { SB_DKV(true) }
-        else             { SB_DKV(false) }
+        if constexpr (VL) { SB_DKV(true) }
+        else if (G > 1)   { SB_DKV(true) }
+        else              { SB_DKV(false) }
     }
 #undef SB_LAUNCH
 #undef SB_DQ

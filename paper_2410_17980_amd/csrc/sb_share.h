@@ -19,12 +19,14 @@ namespace sb {
 //
 // In pairs: every workgroup a pair, every head on one XCD, slot s of the XCDs takes heads 8s .. 8s+7,
 // turned by s(s+1)/2.  Only the key-stationary kernel of d = 128, one workgroup per CU and nothing else
-// to hide a tile's latency, still takes it, from 128 kv heads on.  Pairs / longest first there, us, all
-// heads far, then a third: B8 H16 T4096 1309 / 1392, 660 / 715; B4 H32 T6144 2809 / 3024, 1242 / 1374;
-// B8 H20 T4096 1629 / 1763, 878 / 845; B8 H24 T2048 570 / 599, 415 / 384.  With fewer heads it still
-// wins where all reach far, but too little evens out where a third does: B7 H16 T4096 1153 / 1214,
-// 603 / 622; B4 H24 T4096 993 / 1033, 640 / 528; B2 H32 T8192 2398 / 2557, 1195 / 1082; B2 H24 T2048
-// 169 / 151, 123 / 96.
+// to hide a tile's latency, still takes it, from 128 heads on: its second block is fetched under the end of the
+// first.  Pairs / longest first there, us, all heads far, then a third: B8 H16 T4096 1270 / 1345, 612 / 650;
+// B4 H32 T6144 2700 / 2930, 1155 / 1260; B16 H16 T1024 240 / 245, 191 / 198; B8 H20 T4096 1592 / 1753, 818 / 771;
+// B8 H24 T2048 549 / 578, 372 / 340.  With fewer heads it still wins where all reach far, but too little evens
+// out where a third does: B7 H16 T4096 1112 / 1184, 557 / 564; B4 H24 T4096 955 / 990, 607 / 500; B2 H32 T8192
+// 2355 / 2470, 1130 / 1035.  Not for heads that share a kv head or a packed batch, whose pairs keep more than the
+// registers hold: whole backward B16 H32 Hkv8 T4096 9430 / 9620, 5130 / 4945; B32 H32 Hkv4 T1024 1500 / 1455,
+// 1290 / 1095; B6 H48 Hkv24 T3000 3130 / 3050, 1708 / 1564.
 struct Share {
     int bh;                   // head
     int i;                    // block, or with pairs pair

@@ -260,3 +260,19 @@ def test_backward_of_many_heads(sb, oracle, gen, B, H, Hkv, T):
         qs, ks = slice(h * G, (h + 1) * G), slice(h, h + 1)
         one = oracle.bwd_gqa(*(to64(t) for t in (q[b:b + 1, qs], k[b:b + 1, ks], v[b:b + 1, ks], g[b:b + 1, qs])))
         check_heads((got[0][b:b + 1, qs], got[1][b:b + 1, ks], got[2][b:b + 1, ks]), one)
+
+
+@pytest.mark.parametrize("T", [129, 300, 385, 768])
+def test_second_block_of_a_pair(sb, oracle, gen, T):
+    """d = 128, 128 heads: the second block of a pair is fetched while the first ends, after 12, 10, 8, ... tiles
+    of 64 rows; with a block of one row, with rows past the end, with a middle block alone."""
+    B, H, d = 8, 16, 128
+    q, k, v = mixed(gen, B, H, T, d, seed=2000 + T)
+    g = gen.gaussian(B, H, T, d, seed=2001 + T, dtype="bf16")[0]
+    qd, kd, vd, gd = dev(q, k, v, g)
+    _, m = sb.sb_attn_fwd_train(qd, kd, vd)
+    got = sb.sb_attn_bwd(qd, kd, vd, m, gd, workspace=nan_bytes(sb.sb_attn_bwd_workspace_bytes(B, H, T, d)))
+    torch.cuda.synchronize()
+    for b, h in ((0, 0), (0, 1), (0, 2), (3, 5), (7, 15)):
+        one = oracle.bwd(*(to64(t[b:b + 1, h:h + 1]) for t in (q, k, v, g)))
+        check_heads([t[b:b + 1, h:h + 1] for t in got], one)
