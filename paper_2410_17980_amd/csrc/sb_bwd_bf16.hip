@@ -415,67 +415,76 @@ bwd_dq_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     };
 
     // Where the sweep of the block at Q0 has to start.  Every wave looks for the 32-key strip beyond which
-    // its own rows are exhausted, from the diagonal towards key 0, two K tiles per staging buffer and
-    // barrier, logits and softplus totals only (a third of the sweep's matrix work, a quarter of its
-    // vector work), and sets `start` to it and a2 to the carry at its left edge, which also spares the sweep
-    // a sum over all keys that is then subtracted again; 0 and a2 as it is if there is none.  Returns the
-    // tile at which the first of the waves has to start.
+    // its own rows are exhausted, from its diagonal towards key 0, logits and softplus totals only (a third of
+    // the sweep's matrix work, a quarter of its vector work), and sets `start` to it and a2 to the carry at its
+    // left edge, which also spares the sweep a sum over all keys that is then subtracted again; 0 and a2 as it
+    // is if there is none.  Returns the tile at which the first of the waves has to start.
+    // Bound by its steps' latencies: 9 of the 29 us of a short-reaching block at d = 128.  Two strips a wave and
+    // barrier, out of a ring of eight in the staging buffers, each wave its own distance from its diagonal, not
+    // all of them the same tile pairs (of which the first wave sees only the masked subtile of the first); and
+    // whether to look at all is known from m before the first tiles are asked for.  All heads near, us:
+    // B8 H16 T4096 d128 242 -> 230, B4 H12 T2048 d128 60 -> 47, B8 H16 T2048 d64 68 -> 61, T1024 36 -> 32.6;
+    // a third far 493 -> 481, 84 -> 83, 95.5 -> 93, 40 -> 37; all far within 1 %.
     // Tried only where m says that the rows have at least twice what exhausts them, so that the
     // point is expected in the nearer half, and given up after that half: at worst a sixth more.
-    auto stage_pair = [&](const uint16_t* Kg, int T, int ntile, int i) __attribute__((always_inline)) {
-        char* sp = smem + (i & 1) * C::STAGE;
-        const int t = ntile - 1 - 2 * i;                     // the upper tile of the pair
-        stage_one<D, true>(Kg, t, T, sp, goff, wave, lane);
-        stage_one<D, true>(Kg, t - 1, T, sp + C::TILE, goff, wave, lane);
+    auto ring = [&](int s) __attribute__((always_inline)) { return ((s + 1) & 7) * 32 * C::ROW; };
+    auto stage_strips = [&](const uint16_t* Kg, int T, int s) __attribute__((always_inline)) {    // s and s + 1; s is odd
+        stage_one<D, true>(Kg + (long)s * 32 * D, 0, T - s * 32, smem + ring(s), goff, wave, lane);
     };
-    // (pair 0 has been staged)
-    auto find_start = [&](const uint16_t* Kg, int T, int ntile, bool wave_live, int& start) __attribute__((always_inline)) {
-        const int limit = ntile >> 2;                        // pairs of tiles
-        const int likely = !wave_live || __builtin_amdgcn_ballot_w64(!(a2 >= 2.0f * CARRY_EXHAUSTED)) == 0;
-        if (lane == 0) s_done[1][wave] = likely;
-        barrier_lds();
-        if (!waves_done(s_done[1])) return 0;
+    // what the first step takes: the block's strips sb .. sb + 3 and the one in front
+    auto stage_first = [&](const uint16_t* Kg, int T, int sb) __attribute__((always_inline)) {
+        stage_strips(Kg, T, sb - 1);
+        if ((sb + 1) * 32 < T) stage_strips(Kg, T, sb + 1);
+        if ((sb + 3) * 32 < T && wave < NW / 2) stage_strips(Kg, T, sb + 3);
+    };
+    auto find_start = [&](const uint16_t* Kg, int T, int ntile, int sb, bool wave_live, int& start) __attribute__((always_inline)) {
+        const int limit = ntile >> 1;                        // steps
         float l = 0.0f;                                      // this lane's keys only
         int found = wave_live ? 0 : 0x7fffffff;              // the strip, plus one
-        auto sum_subtile = [&](auto mask_c, uint32_t ktile) __attribute__((always_inline)) {
-            constexpr bool MASK = decltype(mask_c)::value;
-            const uint32_t ka = ktile + aoff0;
+        auto logits = [&](int s) __attribute__((always_inline)) {
+            const uint32_t ka = smem0 + ring(s) + aoff0;
             u32x4 kw[D / 16];
 #pragma unroll
-            for (int s = 0; s < D / 16; ++s) kw[s] = lds_load16(ka ^ (s << 5));
+            for (int x = 0; x < D / 16; ++x) kw[x] = lds_load16(ka ^ (x << 5));
             f32x16 acc;
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
 #pragma unroll
-            for (int s = 0; s < D / 16; ++s)
-                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kw[s]), qf[s], acc, 0, 0, 0);
-            l += sp2_total<MASK>(acc, c2, n, hh);
+            for (int x = 0; x < D / 16; ++x)
+                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kw[x]), qf[x], acc, 0, 0, 0);
+            return acc;
+        };
+        auto look = [&](int s) __attribute__((always_inline)) {
+            float l_lo, l_hi;
+            both_halves(l, l_lo, l_hi);
+            if (__builtin_amdgcn_ballot_w64(!(l_lo + l_hi >= CARRY_EXHAUSTED)) == 0) {
+                a2 = l_lo + l_hi;
+                start = s;
+                found = s + 1;
+            }
         };
         for (int i = 0;; ++i) {
             dma_wait<0>();
             barrier_lds();
             if (i > 0) {
-                // what the waves found up to pair i - 1; all read the same words and leave together
+                // what the waves found up to step i - 1; all read the same words and leave together
                 const u32x4 f = lds_load16(lds_offset(reinterpret_cast<const char*>(s_done[(i + 1) & 1])));
                 const int least = __builtin_amdgcn_readfirstlane((int)min(min(f[0], f[1]), min(f[2], f[3])));
                 if (least > 0) return (least - 1) >> 1;
                 if (i == limit) return 0;
             }
-            if (i + 1 < limit) stage_pair(Kg, T, ntile, i + 1);
-#pragma unroll
-            for (int x = 0; x < 4; ++x) {
-                const int key0 = (ntile - 2 * i) * TK - 32 * (x + 1);
-                const uint32_t kt = smem0 + (i & 1) * C::STAGE + (x >> 1) * C::TILE + (1 - (x & 1)) * 32 * C::ROW;
-                if (!found && key0 == q0) sum_subtile(bc<true>{}, kt);       // the strip's first row sees none of these
-                else if (!found && key0 < q0) {
-                    sum_subtile(bc<false>{}, kt);
-                    float l_lo, l_hi;
-                    both_halves(l, l_lo, l_hi);
-                    if (__builtin_amdgcn_ballot_w64(!(l_lo + l_hi >= CARRY_EXHAUSTED)) == 0) {
-                        a2 = l_lo + l_hi;
-                        start = key0 >> 5;
-                        found = start + 1;
-                    }
+            if (i + 1 < limit) stage_strips(Kg, T, sb - 2 * i - 3);
+            if (!found) {
+                const int s = sb + wave - 2 * i;
+                const f32x16 s0 = logits(s), s1 = logits(s - 1);
+                if (i == 0) l += sp2_total<true>(s0, c2, n, hh);             // the strip's first row sees none of these
+                else {
+                    l += sp2_total<false>(s0, c2, n, hh);
+                    look(s);
+                }
+                if (!found) {
+                    l += sp2_total<false>(s1, c2, n, hh);
+                    look(s - 1);
                 }
             }
             if (lane == 0) s_done[i & 1][wave] = found;
@@ -491,21 +500,37 @@ bwd_dq_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     const int ntile = (kmax + TK - 1) / TK;
     const int nclean = min(ntile, Q0 / TK);          // tiles entirely left of the block's rows
     const bool far = nclean >= 6 && ntile <= 32768;  // long enough to look for a start, and `first` can hold it
-    // what the block needs first, tiles and rows alike, is fetched together: one memory latency
-    if (far) stage_pair(Kg, T, ntile, 0);
-    else if (ntile > 0) stage_tile<D, true>(Kg, Vg, 0, T, smem, goff, wave, lane);
+    // what the block needs first, tiles and rows alike, is fetched together: one memory latency.  (m ahead of the
+    // rows, so that which tiles it is to be is known by then.)
+    bool seek = false;                               // look for a start
     {
+        const float mj = m[row0 + jq];
         const u32x4* qs = reinterpret_cast<const u32x4*>(q + base + (long)jq * D + 8 * hh);
         const u32x4* gs = reinterpret_cast<const u32x4*>(dout + base + (long)jq * D + 8 * hh);
+        u32x4 a[D / 16], g[D / 16];
+        asm volatile("" ::: "memory");
 #pragma unroll
         for (int s = 0; s < D / 16; ++s) {
-            u32x4 a = qs[2 * s], g = gs[2 * s];
-            if (q0 + n >= T) g = u32x4{0u, 0u, 0u, 0u};   // rows past T contribute nothing
-            qf[s] = __builtin_bit_cast(bf16x8, a);
-            gf[s] = __builtin_bit_cast(bf16x8, g);
+            a[s] = qs[2 * s];
+            g[s] = gs[2 * s];
+        }
+        asm volatile("" ::: "memory");
+        a2 = -mj * SB_LOG2E;
+        if (far) {
+            const int likely = !wave_live || __builtin_amdgcn_ballot_w64(!(a2 >= 2.0f * CARRY_EXHAUSTED)) == 0;
+            if (lane == 0) s_done[1][wave] = likely;
+            barrier_lds();
+            seek = waves_done(s_done[1]);
+        }
+        if (seek) stage_first(Kg, T, Q0 / 32);
+        else if (ntile > 0) stage_tile<D, true>(Kg, Vg, 0, T, smem, goff, wave, lane);
+#pragma unroll
+        for (int s = 0; s < D / 16; ++s) {
+            if (q0 + n >= T) g[s] = u32x4{0u, 0u, 0u, 0u};   // rows past T contribute nothing
+            qf[s] = __builtin_bit_cast(bf16x8, a[s]);
+            gf[s] = __builtin_bit_cast(bf16x8, g[s]);
         }
     }
-    a2 = -m[row0 + jq] * SB_LOG2E;
     bsum = 0.0f;
     if constexpr (RB) {
         // remainder bias (Appendix C): the unused stick exp(m) acts like one more weight
@@ -537,8 +562,8 @@ bwd_dq_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
 
     // ---- sweep over 64-key tiles, left to right; iteration it handles tile it in buffer it & 1
     int t0 = 0, start = 0;
-    if (far) {
-        t0 = find_start(Kg, T, ntile, wave_live, start);
+    if (seek) {
+        t0 = find_start(Kg, T, ntile, Q0 / 32, wave_live, start);
         stage_tile<D, true>(Kg, Vg, t0, T, smem + (t0 & 1) * C::STAGE, goff, wave, lane);
     }
     if (lane == 0) first[((long)bh * nqb_arg + qb) * 4 + wave] = (uint16_t)(wave_live ? start : 2 * t0);

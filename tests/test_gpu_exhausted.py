@@ -276,3 +276,22 @@ def test_second_block_of_a_pair(sb, oracle, gen, T):
     for b, h in ((0, 0), (0, 1), (0, 2), (3, 5), (7, 15)):
         one = oracle.bwd(*(to64(t[b:b + 1, h:h + 1]) for t in (q, k, v, g)))
         check_heads([t[b:b + 1, h:h + 1] for t in got], one)
+
+
+@pytest.mark.parametrize("T", [449, 513, 700, 1057])
+@pytest.mark.parametrize("d", [32, 64, 128])
+def test_starts_of_all_distances(sb, oracle, gen, T, d):
+    """Heads whose rows are exhausted after 4 strips of 32 keys, 5, ... up to more than there are: the search for
+    the backward's start finds it in each of its steps, at its limit, and not at all."""
+    B, H = 1, 64
+    q, k, v, g = (gen.gaussian(B, H, T, d, seed=3000 + T + i, dtype="bf16")[0].clone() for i in range(4))
+    for h in range(H):
+        f = (4.0 * h / H * d ** 0.5) ** 0.5                 # logits shifted by 0 ... -4
+        q[:, h, :, d - 1], k[:, h, :, d - 1] = f, -f
+    qd, kd, vd, gd = dev(q, k, v, g)
+    _, m = sb.sb_attn_fwd_train(qd, kd, vd)
+    got = sb.sb_attn_bwd(qd, kd, vd, m, gd, workspace=nan_bytes(sb.sb_attn_bwd_workspace_bytes(B, H, T, d)))
+    torch.cuda.synchronize()
+    for h in range(0, H, 6):
+        one = oracle.bwd(*(to64(t[:, h:h + 1]) for t in (q, k, v, g)))
+        check_heads([t[:, h:h + 1] for t in got], one)
