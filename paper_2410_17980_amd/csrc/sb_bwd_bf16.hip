@@ -1991,7 +1991,7 @@ hipError_t launch_one(const uint16_t* q, const uint16_t* k, const uint16_t* v, c
     const uint32_t* first2 = reinterpret_cast<const uint32_t*>(first);     // of a tile's two strips
     float* part = reinterpret_cast<float*>(first + (long)BH * nqb * 4);
     const int nchunk = (T + DR_ROWS - 1) / DR_ROWS;
-    const bool pairs = D == 128 && !VL && G == 1 && BHkv >= 128;   // see Share
+    const bool pairs = D == 128 && !VL && G == 1 && take_pairs(BHkv, nkb);
     const long gq = share_grid(BH, nqb, false), gk = share_grid(BHkv, nkb, pairs);
     const long strips_q = pieces(B, H, T, 32, VL, Ttot), strips_k = pieces(B, Hkv, T, 32, VL, Ttot);
     const long blocks_k = pieces(B, Hkv, T, BKW, VL, Ttot);

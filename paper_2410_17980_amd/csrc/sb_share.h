@@ -19,14 +19,17 @@ namespace sb {
 //
 // In pairs: every workgroup a pair, every head on one XCD, slot s of the XCDs takes heads 8s .. 8s+7,
 // turned by s(s+1)/2.  Only the key-stationary kernel of d = 128, one workgroup per CU and nothing else
-// to hide a tile's latency, still takes it, from 128 heads on: its second block is fetched under the end of the
-// first.  Pairs / longest first there, us, all heads far, then a third: B8 H16 T4096 1270 / 1345, 612 / 650;
-// B4 H32 T6144 2700 / 2930, 1155 / 1260; B16 H16 T1024 240 / 245, 191 / 198; B8 H20 T4096 1592 / 1753, 818 / 771;
-// B8 H24 T2048 549 / 578, 372 / 340.  With fewer heads it still wins where all reach far, but too little evens
-// out where a third does: B7 H16 T4096 1112 / 1184, 557 / 564; B4 H24 T4096 955 / 990, 607 / 500; B2 H32 T8192
-// 2355 / 2470, 1130 / 1035.  Not for heads that share a kv head or a packed batch, whose pairs keep more than the
-// registers hold: whole backward B16 H32 Hkv8 T4096 9430 / 9620, 5130 / 4945; B32 H32 Hkv4 T1024 1500 / 1455,
-// 1290 / 1095; B6 H48 Hkv24 T3000 3130 / 3050, 1708 / 1564.
+// to hide a tile's latency, still takes it (take_pairs()): its second block is fetched under the end of the first.
+// Pairs / longest first there, us, all heads far, then a third: B8 H16 T4096 1270 / 1345, 612 / 650; T8000 4706 / 5219,
+// 1849 / 2035; B4 H32 T6144 2700 / 2930, 1155 / 1260; B16 H32 T512 171 / 177, 157 / 172; B8 H20 T4096 1592 / 1753,
+// 818 / 771; B8 H24 T2048 549 / 578, 372 / 340.  From 128 heads on: with fewer it still wins where all reach far, but
+// too little evens out where a third does: B7 H16 T4096 1112 / 1184, 557 / 564; B4 H24 T4096 955 / 990, 607 / 500;
+// B2 H32 T8192 2355 / 2470, 1130 / 1035.  And where whole octets of heads fill whole rounds of the chip, as pairs cost all
+// the same: B10 H20 T1000 (3.1 rounds) 227 / 199, 168 / 146; B3 H48 T2048 (4.5) 449 / 440, 271 / 259; B8 H22
+// T2048 (5.5) 544 / 540, 328 / 319; B10 H13 T3000 834 / 810, 507 / 406; B8 H17 T4096 1434 / 1500, 746 / 663.
+// Not for heads that share a kv head or a packed batch, whose pairs keep more than the registers hold: whole
+// backward B16 H32 Hkv8 T4096 9430 / 9620, 5130 / 4945; B32 H32 Hkv4 T1024 1500 / 1455, 1290 / 1095; B6 H48 Hkv24 T3000
+// 3130 / 3050, 1708 / 1564.
 struct Share {
     int bh;                   // head
     int i;                    // block, or with pairs pair
@@ -34,6 +37,12 @@ struct Share {
 inline long share_grid(long heads, int nblk, bool pairs)
 {
     return pairs ? 8L * ((heads + 7) / 8) * ((nblk + 1) / 2) : heads * nblk;
+}
+inline bool take_pairs(long heads, int nblk)
+{
+    if (heads < 128 || heads % 8 != 0) return false;
+    const long n = share_grid(heads, nblk, true), idle = (256 - n % 256) % 256;      // places in the last round
+    return 32 * idle <= n;
 }
 
 // Grids of the backward that take one strip of 32 rows a workgroup, its waves sharing the strip's other side
