@@ -96,8 +96,8 @@ int sb_attn_fwd_f32(const float* q, const float* k, const float* v, float* o, fl
  * workspace: caller-owned device scratch of at least
  * sb_attn_bwd_workspace_bytes(B,H,T,d) bytes, 16-byte aligned; its contents on
  * entry do not matter and are garbage afterwards.  It holds two floats per
- * (query row, 32-key strip), two ints per 128-row block (the first is where the block's sweep
- * starts, the second is unused) and d floats per 128-row block (partial sums of sb_attn_bwd_rb's dr):
+ * (query row, 32-key strip), four 16-bit integers per 128-row block (where the sweeps of its 32-row
+ * strips start) and d floats per 128-row block (partial sums of sb_attn_bwd_rb's dr):
  * B*H*(8*T*ceil(T/32) + (8 + 4*d)*ceil(T/128)) bytes.  SB_ERR_WORKSPACE if it is NULL or
  * too small.  sb_attn_bwd_workspace_bytes returns 0 for a bad shape.
  * The carried sums make the workspace grow with T^2 (T^2/4 bytes per head: 4 MiB at
