@@ -1602,12 +1602,25 @@ bwd_dq_small_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
     if (wave == 0) {                                     // both halves alike
         float right = 0.0f;
         int start = strip;
-        for (int sub = strip; sub >= 0; --sub) {
-            const float t = s_car[sub][n];
-            if (hh == 0) s_car[sub][n] = right;
-            if (__builtin_amdgcn_ballot_w64(!(right >= CARRY_EXHAUSTED)) == 0) break;
-            start = sub;
-            right += t;
+        // four totals are fetched at a time: one LDS latency for them, not one for each (B1 H4 T4000 d64 52.0 -> 49.9 us)
+        bool more = true;
+        for (int top = strip; more && top >= 0; top -= 4) {
+            float t[4];
+#pragma unroll
+            for (int x = 0; x < 4; ++x) t[x] = s_car[max(top - x, 0)][n];
+#pragma unroll
+            for (int x = 0; x < 4; ++x) {
+                const int sub = top - x;
+                more = more && sub >= 0;
+                if (more) {
+                    if (hh == 0) s_car[sub][n] = right;
+                    more = __builtin_amdgcn_ballot_w64(!(right >= CARRY_EXHAUSTED)) != 0;
+                }
+                if (more) {
+                    start = sub;
+                    right += t[x];
+                }
+            }
         }
         if (lane == 0) s_start = start;
     }

@@ -49,7 +49,7 @@ inline bool take_pairs(long heads, int nblk)
 // (bwd_dq_small_kernel, bwd_dkv_small_kernel), in place of 128-row blocks whose every wave has the
 // whole other side to itself.  What bounds the blocks there is one chain, what bounds the strips from a round or two of the
 // chip on is their tiles, which no other wave shares.  Blocks / strips, us, query-stationary, then key-stationary:
-//   B2 H4 T777 d32 (200 strips) 19.1 / 10.9, 19.2 / 7.7; B1 H4 T4000 d64 (500) 98 / 52, 96 / 38;
+//   B2 H4 T777 d32 (200 strips) 19.1 / 10.9, 19.2 / 7.7; B1 H4 T4000 d64 (500) 98 / 50, 96 / 38;
 //   B1 H12 T2000 d64 (756) 52 / 48, 52 / 37; B2 H12 T1000 d32 (768) 24.7 / 24.2, 24.2 / 18.0;
 //   B1 H8 T700 d128 (176) 28 / 21.5, 24.4 / 17.9; B1 H16 T500 d128 (256) 23 / 16.7, 21 / 15.2;
 //   B1 H16 T100 d64 (64) 6.9 / 6.3, 8.2 / 6.5; both B1 H6 Hkv2 T4000 d32 320 / 125
