@@ -631,7 +631,7 @@ fwd_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
 // the diagonal on in rounds of one each: logits and chains, which need no carry, side by side; one barrier
 // for the carries; weights, into LDS; one barrier; then O += A V, a wave per 32 columns, over the round's subtiles
 // in order.  Every sum is taken in the order of fwd_bf16_kernel: o is the same, bit for bit (m too,
-// unless that takes its sum_tail()).  Which grids: small_fwd_grid().
+// unless the rows are exhausted on the way).  Which grids: small_fwd_grid().
 template <int D> struct FwdSmallCfg {
     static constexpr int NWS = D == 128 ? 4 : 8;        // waves
     static constexpr int ROW = D * 2;
@@ -721,8 +721,20 @@ fwd_small_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     float a = 0.0f;                                     // carry of the round
     bool done = false;                                  // every row exhausted: the weights are zero from here on
 
-    int st = 0;
-    for (int top = strip; top >= 0; top -= NWS, st ^= 1) {
+    auto logits = [&](int st) __attribute__((always_inline)) {
+        u32x4 kop[D / 16];
+#pragma unroll
+        for (int s = 0; s < D / 16; ++s) kop[s] = lds_load16((ka + st * C::SUB) ^ (s << 5));
+        f32x16 acc;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
+#pragma unroll
+        for (int s = 0; s < D / 16; ++s)
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kop[s]), qf[s], acc, 0, 0, 0);
+        return acc;
+    };
+    int st = 0, top = strip;
+    for (; top >= 0; top -= NWS, st ^= 1) {
         const int sub = top - wave;
         float g[16], t_lo = 0.0f, t_hi = 0.0f;
         bool linear = true;
@@ -730,15 +742,7 @@ fwd_small_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
             // this subtile has landed; the K buffer to be refilled was read a round ago, by this wave
             asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
             if (sub - NWS >= 0) stage(Kg, sub - NWS, mine + (st ^ 1) * C::SUB);
-            u32x4 kop[D / 16];
-#pragma unroll
-            for (int s = 0; s < D / 16; ++s) kop[s] = lds_load16((ka + st * C::SUB) ^ (s << 5));
-            f32x16 acc;
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
-#pragma unroll
-            for (int s = 0; s < D / 16; ++s)
-                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kop[s]), qf[s], acc, 0, 0, 0);
+            const f32x16 acc = logits(st);
             auto keep = [&](auto lin, const float (&x)[16], float x_lo, float x_hi) __attribute__((always_inline)) {
                 linear = decltype(lin)::value;
                 t_lo = x_lo;
@@ -756,7 +760,6 @@ fwd_small_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
             if (w == wave) mine_a = a;
             a += s_tot[st][w][n];
         }
-        if (done) continue;                              // alike in all waves
         if (sub - NWS >= 0) stage(Vg, sub - NWS, mine + (2 + (st ^ 1)) * C::SUB);
         bf16x8 p[2] = {};
         if (sub >= 0) {
@@ -776,8 +779,27 @@ fwd_small_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
                 }
             }
         }
-        done = __builtin_amdgcn_ballot_w64(!(a >= CARRY_EXHAUSTED)) == 0;
-        if (done && !m) break;
+        done = __builtin_amdgcn_ballot_w64(!(a >= CARRY_EXHAUSTED)) == 0;      // alike in all waves
+        if (done) break;
+    }
+    if (m && done) {
+        // the logits alone, as in sum_tail(), every wave on its own (in rounds with the others, us: B1 H4 T4000 d64 near
+        // 21.7 -> 16.7, B2 H4 T777 d32 near 6.2 -> 5.4, all far 8.0 -> 7.8, with no test for it in the rounds)
+        float l = 0.0f;
+        int b = st ^ 1;
+        for (int sub = top - NWS - wave; sub >= 0; sub -= NWS, b ^= 1) {
+            asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+            if (sub - NWS >= 0) stage(Kg, sub - NWS, mine + (b ^ 1) * C::SUB);
+            l += sp2_total<false>(logits(b), c2, n, hh);
+        }
+        float l_lo, l_hi;
+        both_halves(l, l_lo, l_hi);
+        if (hh == 0) s_tot[st][wave][n] = l_lo + l_hi;   // this round's totals have been read
+        barrier_lds();
+        float rest = 0.0f;
+#pragma unroll
+        for (int w = 0; w < NWS; ++w) rest += s_tot[st][w][n];
+        a += rest;
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // subtiles staged before the sweep stopped
 

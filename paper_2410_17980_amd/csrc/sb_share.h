@@ -74,10 +74,10 @@ inline long pieces(int B, int H, int T, int rows, bool packed, int Ttot)
 // Grids of the forward that take one strip of 32 rows a workgroup, its waves taking the strip's subtiles in rounds
 // (fwd_small_kernel), in place of 128-row blocks whose every wave has its rows' chain to itself.  Blocks / strips, us,
 // without m, then with it:
-//   all heads far   B1 H16 T100 d64 (64 strips) 5.2 / 4.6, 5.2 / 4.7; B2 H4 T777 d32 (200) 12.2 / 8.1, 12.4 / 8.1;
-//                   B1 H8 T700 d128 (176) 18.9 / 12.7, 19.1 / 12.8; B2 H12 T500 d128 (384) 15.8 / 12.5, 15.9 / 12.6;
-//                   B1 H4 T4000 d64 (500) 58 / 34, 58 / 34
-//   none far        12.2 / 7.3 and 17.2 / 10.4 for B1 H8 T700 d128, 8.9 / 10.4 and 41 / 22 for B1 H4 T4000 d64
+//   all heads far   B1 H16 T100 d64 (64 strips) 5.2 / 4.6, 5.2 / 4.7; B2 H4 T777 d32 (200) 12.2 / 7.7, 12.4 / 7.8;
+//                   B1 H8 T700 d128 (176) 18.9 / 11.9, 19.1 / 12.2; B2 H12 T500 d128 (384) 15.8 / 12.5, 15.9 / 12.6;
+//                   B1 H4 T4000 d64 (500) 58 / 33, 58 / 33
+//   none far        12.2 / 7.0 and 17.2 / 9.4 for B1 H8 T700 d128, 8.9 / 10.2 and 41 / 17 for B1 H4 T4000 d64
 // and not, a third far, B4 H8 T700 d64 (704) 13.5 / 16.2, 13.6 / 17.6; B1 H24 T1000 d128 (768) 26.4 / 28.1, 26.5 / 31.8;
 // B4 H16 T300 d32 (640) 6.9 / 9.8, 7.0 / 10.1.  At d = 32 a chain of 10 subtiles is not worth the rounds' barriers.
 inline bool small_fwd_grid(long strips, int T, int d)
