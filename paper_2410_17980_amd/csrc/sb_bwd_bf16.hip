@@ -700,7 +700,7 @@ __device__ __forceinline__ int reaching(uint32_t w, int ks)
 //   B1 H16 T4096 d32 (512 blocks, 32 a head) 115 / 92, 115 / 84, 18 / 22; B1 H24 T4096 d64 (768, 32) 171 / 179, 143 / 101,
 //   37 / 42; B2 H24 T1024 d64 (384, 8) 39 / 33, 39 / 32, 24 / 27; B1 H40 T2048 d64 (640, 16) 78 / 86, 73 / 55, 32 / 39
 //   B1 H32 T4096 d64 (1024, 32) 225 / 232, 154 / 113, 42 / 57; B5 H5 T4500 d32 (900, 36) 156 / 177, 122 / 92, 27 / 36; but
-//   B1 H30 T3500 d64 (840, 28) 163 / 170, 129 / 158, 38 / 52, where that third comes round to the same shader engines
+//   B1 H30 T3500 d64 (840, 28) 163 / 170, 129 / 158, 38 / 52 (every third head far; why that count differs was not found)
 // and not B8 H16 T512 d64 (512, 4) 25 / 29, 24 / 29, 23 / 28; B8 H8 T2000 d32 (1024, 16) 78 / 94, 60 / 52, 28 / 36;
 // B2 H20 T4096 d64 (1280, 32) 275 / 291, 158 / 143, 52 / 65; B8 H16 T2048 d64 (2048, 16) 236 / 259, 126 / 164, 80 / 108.
 constexpr long in_turn_grid(int nkb) { return std::clamp(48L * nkb, ONE_PER_CU, 1024L); }
