@@ -150,13 +150,21 @@ def _ptr(t, dtype, shape=None, name="tensor"):
     return ctypes.c_void_p(t.data_ptr())
 
 
-def _stream(stream=None):
-    s = torch.cuda.current_stream() if stream is None else stream
-    return ctypes.c_void_p(s.cuda_stream)
+def _on(stream):
+    """`stream` as the current one, for what a measurement allocates, fills and reads back."""
+    if stream is not None and not isinstance(stream, torch.cuda.Stream):
+        stream = torch.cuda.ExternalStream(stream.cuda_stream)
+    return torch.cuda.stream(stream)
+
+
+def _stream():
+    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
 
 
 # The calls of the method go through the native module: it checks the tensors, allocates what was
-# not passed in, takes the stream and calls the C ABI (csrc/sb_torch.cpp).
+# not passed in, takes the stream and calls the C ABI (csrc/sb_torch.cpp).  With stream= a call launches and
+# allocates as under `with torch.cuda.stream(stream)`, and what it returns may be dropped while work of the stream that was
+# current still uses it.
 
 
 def sb_attn_fwd(q, k, v, o=None, stream=None):
@@ -248,10 +256,7 @@ def sb_attn_decode_static(q, k, v, o, T=None, r=None, m=None, stream=None):
 
 def sb_attn_bwd_dq(q, k, v, m, dout, dq=None, workspace=None, stream=None):
     """Query-stationary pass of the backward.  Returns (dq, workspace)."""
-    if workspace is None:
-        need = sb_attn_bwd_workspace_bytes(*_dims(q))
-        workspace = torch.empty(need, dtype=torch.uint8, device=q.device) if need > 0 else None
-    return (_ext or _load_ext()).backward_dq(q, k, v, m, dout, dq, workspace, stream), workspace
+    return (_ext or _load_ext()).backward_dq(q, k, v, m, dout, dq, workspace, stream)
 
 
 def sb_attn_bwd_dkdv(q, k, v, dout, workspace, dk=None, dv=None, stream=None):
@@ -263,21 +268,21 @@ def sb_diag_mfma_rate(operands, iters=2000, stream=None):
     """MFMA-only rate on the given bf16 operand data.  Returns (TFLOP/s, shader clock in MHz)."""
     if not operands.is_cuda or operands.dtype != torch.bfloat16 or not operands.is_contiguous():
         raise SbAttnError("operands must be a contiguous bf16 tensor on the GPU")
-    ticks = torch.zeros(4, dtype=torch.int64, device=operands.device)
     flop = ctypes.c_double(0.0)
     nbytes = operands.numel() * 2
-    run = lambda: _check(load().sb_diag_mfma_rate(ctypes.c_void_p(operands.data_ptr()), nbytes, int(iters),
-                                                  ctypes.c_void_p(ticks.data_ptr()), ctypes.byref(flop),
-                                                  _stream(stream)), "sb_diag_mfma_rate")
-    run()
-    s = torch.cuda.current_stream() if stream is None else stream
-    e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
-    e0.record(s)
-    run()
-    e1.record(s)
-    e1.synchronize()
-    ms = e0.elapsed_time(e1)
-    t = ticks.cpu().tolist()
+    with _on(stream):
+        ticks = torch.zeros(4, dtype=torch.int64, device=operands.device)
+        run = lambda: _check(load().sb_diag_mfma_rate(ctypes.c_void_p(operands.data_ptr()), nbytes, int(iters),
+                                                      ctypes.c_void_p(ticks.data_ptr()), ctypes.byref(flop),
+                                                      _stream()), "sb_diag_mfma_rate")
+        run()
+        e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        e0.record()
+        run()
+        e1.record()
+        e1.synchronize()
+        ms = e0.elapsed_time(e1)
+        t = ticks.cpu().tolist()
     mhz = t[0] / (t[1] / 100e6) / 1e6 if t[1] > 0 else float("nan")
     return flop.value / (ms * 1e-3) / 1e12, mhz
 
@@ -287,32 +292,33 @@ def sb_diag_stream_read(data, iters=10, stream=None):
     if not data.is_cuda or not data.is_contiguous():
         raise SbAttnError("data must be a contiguous tensor on the GPU")
     nbytes = (data.numel() * data.element_size()) // 16 * 16
-    sink = torch.zeros(4, dtype=torch.int32, device=data.device)
-    run = lambda: _check(load().sb_diag_stream_read(ctypes.c_void_p(data.data_ptr()), nbytes,
-                                                    ctypes.c_void_p(sink.data_ptr()), _stream(stream)),
-                         "sb_diag_stream_read")
-    for _ in range(2):
-        run()
-    s = torch.cuda.current_stream() if stream is None else stream
-    e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
-    e0.record(s)
-    for _ in range(iters):
-        run()
-    e1.record(s)
-    e1.synchronize()
+    with _on(stream):
+        sink = torch.zeros(4, dtype=torch.int32, device=data.device)
+        run = lambda: _check(load().sb_diag_stream_read(ctypes.c_void_p(data.data_ptr()), nbytes,
+                                                        ctypes.c_void_p(sink.data_ptr()), _stream()),
+                             "sb_diag_stream_read")
+        for _ in range(2):
+            run()
+        e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        e0.record()
+        for _ in range(iters):
+            run()
+        e1.record()
+        e1.synchronize()
     return nbytes * iters / (e0.elapsed_time(e1) * 1e-3) / 1e9
 
 
 def sb_diag_fwd_clock(q, k, v, o, m, stream=None):
     """sb_attn_fwd_train that also returns the shader clock (MHz) its first workgroup saw."""
     B, H, T, d = _dims(q)
-    clocks = torch.zeros(4, dtype=torch.int64, device=q.device)
-    rc = load().sb_diag_fwd_clock(_ptr(q, torch.bfloat16, None, "q"), _ptr(k, torch.bfloat16, q.shape, "k"),
-                                  _ptr(v, torch.bfloat16, q.shape, "v"), _ptr(o, torch.bfloat16, q.shape, "o"),
-                                  _ptr(m, torch.float32, (B, H, T), "m"), B, H, T, d,
-                                  ctypes.c_void_p(clocks.data_ptr()), _stream(stream))
-    _check(rc, "sb_diag_fwd_clock")
-    c = clocks.cpu().tolist()
+    with _on(stream):
+        clocks = torch.zeros(4, dtype=torch.int64, device=q.device)
+        rc = load().sb_diag_fwd_clock(_ptr(q, torch.bfloat16, None, "q"), _ptr(k, torch.bfloat16, q.shape, "k"),
+                                      _ptr(v, torch.bfloat16, q.shape, "v"), _ptr(o, torch.bfloat16, q.shape, "o"),
+                                      _ptr(m, torch.float32, (B, H, T), "m"), B, H, T, d,
+                                      ctypes.c_void_p(clocks.data_ptr()), _stream())
+        _check(rc, "sb_diag_fwd_clock")
+        c = clocks.cpu().tolist()
     ref = c[3] - c[1]
     return (c[2] - c[0]) / (ref / 100e6) / 1e6 if ref > 0 else float("nan")
 
@@ -320,12 +326,16 @@ def sb_diag_fwd_clock(q, k, v, o, m, stream=None):
 def sb_diag_fwd_tri(q, k, v, o=None, m=None, stream=None):
     """Training forward with the in-tile cumulative sum taken by triangular MFMA (d = 128)."""
     B, H, T, d = _dims(q)
-    if o is None:
-        o = torch.empty_like(q)
-    if m is None:
-        m = torch.empty((B, H, T), dtype=torch.float32, device=q.device)
-    rc = load().sb_diag_fwd_tri(_ptr(q, torch.bfloat16, None, "q"), _ptr(k, torch.bfloat16, q.shape, "k"),
-                                _ptr(v, torch.bfloat16, q.shape, "v"), _ptr(o, torch.bfloat16, q.shape, "o"),
-                                _ptr(m, torch.float32, (B, H, T), "m"), B, H, T, d, _stream(stream))
+    inputs = [_ptr(t, torch.bfloat16, q.shape, name) for t, name in ((q, "q"), (k, "k"), (v, "v"))]
+    current = torch.cuda.current_stream()
+    with _on(stream):
+        if o is None:
+            o = torch.empty_like(q)
+            o.record_stream(current)
+        if m is None:
+            m = torch.empty((B, H, T), dtype=torch.float32, device=q.device)
+            m.record_stream(current)
+        rc = load().sb_diag_fwd_tri(*inputs, _ptr(o, torch.bfloat16, q.shape, "o"),
+                                    _ptr(m, torch.float32, (B, H, T), "m"), B, H, T, d, _stream())
     _check(rc, "sb_diag_fwd_tri")
     return o, m

@@ -10,12 +10,12 @@
 #include <Python.h>
 
 #include <initializer_list>
-#include <optional>
 #include <stdexcept>
 #include <string>
 
 #include <ATen/ATen.h>
 #include <ATen/hip/EmptyTensor.h>
+#include <c10/hip/HIPCachingAllocator.h>
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/autograd/python_variable.h>
 
@@ -105,14 +105,61 @@ void* ptr(PyObject* o, at::ScalarType dtype, at::IntArrayRef shape, const char* 
 
 void* any_shape(PyObject* o, at::ScalarType dtype, const char* name) { return ptr(o, dtype, at::IntArrayRef(), name); }
 
+// where a call launches: stream=, or the current stream where that is None
+struct Launch {
+    void* stream;
+    bool given;
+};
+Launch launch_on(PyObject* o)
+{
+    if (none(o)) return {c10::hip::getCurrentHIPStream().stream(), false};
+    PyObject* h = PyObject_GetAttrString(o, "cuda_stream");
+    if (!h) throw Raised{};
+    void* s = PyLong_AsVoidPtr(h);
+    Py_DECREF(h);
+    if (!s && PyErr_Occurred()) throw Raised{};
+    return {s, true};
+}
+
+// `stream` as torch's current stream of `device`, for one scope
+class OnStream {
+public:
+    OnStream(void* stream, c10::DeviceIndex device) : before_(c10::hip::getCurrentHIPStream(device))
+    {
+        c10::hip::setCurrentHIPStream(c10::hip::getStreamFromExternal(static_cast<hipStream_t>(stream), device));
+    }
+    OnStream(const OnStream&) = delete;
+    ~OnStream() { c10::hip::setCurrentHIPStream(before_); }
+    const c10::hip::HIPStream& before() const { return before_; }
+
+private:
+    c10::hip::HIPStream before_;
+};
+
+// Memory for a launch.  torch's caching allocator hands freed memory on in the order of the stream that it was
+// allocated on, so that has to be the stream of the launch: memory of the current stream may still be in use by
+// earlier work there, which a launch on stream= does not wait for.  What the caller gets back (`shared`) the current
+// stream will use as well: dropped, it is not handed on before the work that the current stream then holds is done.
+at::Tensor allocate(at::IntArrayRef shape, at::ScalarType dtype, const at::Tensor& like, const Launch& on, bool shared)
+{
+    const c10::Device dev = like.device();
+    if (!on.given) return at::detail::empty_cuda(shape, dtype, dev, c10::nullopt);
+    OnStream here(on.stream, dev.index());
+    at::Tensor t = at::detail::empty_cuda(shape, dtype, dev, c10::nullopt);
+    if (shared && here.before().stream() != on.stream)
+        c10::hip::HIPCachingAllocator::recordStream(t.storage().data_ptr(), here.before());
+    return t;
+}
+
 // a new reference to the caller's tensor, or a fresh one where it is None; released unless taken
 class Out {
 public:
-    Out(PyObject* given, at::ScalarType dtype, at::IntArrayRef shape, const at::Tensor& like, const char* name)
+    Out(PyObject* given, at::ScalarType dtype, at::IntArrayRef shape, const at::Tensor& like, const char* name,
+        const Launch& on)
     {
         if (none(given)) {
             if (!like.is_cuda()) throw Failed("q must live on the GPU");
-            at::Tensor t = at::detail::empty_cuda(shape, dtype, like.device(), c10::nullopt);
+            at::Tensor t = allocate(shape, dtype, like, on, true);
             p_ = t.data_ptr();
             o_ = THPVariable_Wrap(std::move(t));
             if (!o_) throw Raised{};
@@ -132,58 +179,31 @@ private:
     PyObject* o_ = nullptr;
 };
 
-// `stream` as torch's current stream of `device`, for one scope
-class OnStream {
-public:
-    OnStream(void* stream, c10::DeviceIndex device) : before_(c10::hip::getCurrentHIPStream(device))
-    {
-        c10::hip::setCurrentHIPStream(c10::hip::getStreamFromExternal(static_cast<hipStream_t>(stream), device));
-    }
-    OnStream(const OnStream&) = delete;
-    ~OnStream() { c10::hip::setCurrentHIPStream(before_); }
-
-private:
-    c10::hip::HIPStream before_;
-};
-
 // the caller's workspace, or one of `need` bytes that goes back to torch's caching allocator when
-// the call returns, before the kernels have run.  The allocator hands it to later work of the stream
-// that it was allocated on, so that has to be the stream of the launch (`so`, None for the current one).
+// the call returns, before the kernels have run, unless it is taken
 class Workspace {
 public:
-    Workspace(PyObject* given, size_t need, const at::Tensor& like, PyObject* so, void* stream)
+    Workspace(PyObject* given, size_t need, const at::Tensor& like, const Launch& on, bool shared = false)
     {
         if (!none(given)) {
-            const at::Tensor& t = tensor(given, "workspace");
-            p_ = t.data_ptr();
-            bytes_ = t.nbytes();
+            t_ = tensor(given, "workspace");
         } else if (need > 0 && like.is_cuda()) {
-            std::optional<OnStream> on;
-            if (!none(so)) on.emplace(stream, like.device().index());
-            own_ = at::detail::empty_cuda({(int64_t)need}, at::kByte, like.device(), c10::nullopt);
-            p_ = own_.data_ptr();
-            bytes_ = need;
+            t_ = allocate({(int64_t)need}, at::kByte, like, on, shared);
+        } else {
+            return;
         }
+        p_ = t_.data_ptr();
+        bytes_ = t_.nbytes();
     }
     void* p() const { return p_; }
     size_t bytes() const { return bytes_; }
+    PyObject* take() { return THPVariable_Wrap(std::move(t_)); }      // (None where there is none)
 
 private:
-    at::Tensor own_;
+    at::Tensor t_;
     void* p_ = nullptr;
     size_t bytes_ = 0;
 };
-
-void* stream_of(PyObject* o)
-{
-    if (none(o)) return c10::hip::getCurrentHIPStream().stream();
-    PyObject* h = PyObject_GetAttrString(o, "cuda_stream");
-    if (!h) throw Raised{};
-    void* s = PyLong_AsVoidPtr(h);
-    Py_DECREF(h);
-    if (!s && PyErr_Occurred()) throw Raised{};
-    return s;
-}
 
 template <class F> void call(const char* what, F f)
 {
@@ -259,16 +279,16 @@ PyObject* forward(PyObject* const* a)
     void* k = ptr(a[3], BF, s.kv, "k");
     void* v = ptr(a[4], BF, s.kv, "v");
     void* r = ptr(a[5], BF, s.hd, "r");
-    Out o(a[6], BF, s.q, like, "o");
-    void* st = stream_of(a[9]);
+    const Launch on = launch_on(a[9]);
+    Out o(a[6], BF, s.q, like, "o", on);
     auto go = [&](float* m) {
-        call(what, [&] { return sb_attn_fwd_gqa(q, k, v, r, o.p(), m, s.B, s.H, s.Hkv, s.T, s.d, st); });
+        call(what, [&] { return sb_attn_fwd_gqa(q, k, v, r, o.p(), m, s.B, s.H, s.Hkv, s.T, s.d, on.stream); });
     };
     if (none(a[7]) && !truth(a[8])) {
         go(nullptr);
         return o.take();
     }
-    Out m(a[7], F32, s.m, like, "m");
+    Out m(a[7], F32, s.m, like, "m", on);
     go(m.p<float>());
     return tuple({&o, &m});
 }
@@ -283,12 +303,12 @@ PyObject* halt(PyObject* const* a)
     void* v = ptr(a[2], BF, s.q, "v");
     const double eps = PyFloat_AsDouble(a[3]);
     if (eps == -1.0 && PyErr_Occurred()) throw Raised{};
-    Out o(a[4], BF, s.q, like, "o");
+    const Launch on = launch_on(a[6]);
+    Out o(a[4], BF, s.q, like, "o", on);
     const int64_t two[1] = {2};
     auto* tc = static_cast<unsigned long long*>(ptr(a[5], at::kLong, two, "tile_counts"));
-    void* st = stream_of(a[6]);
     call("sb_attn_fwd_halt",
-         [&] { return sb_attn_fwd_halt(q, k, v, o.p(), (float)eps, tc, s.B, s.H, s.T, s.d, st); });
+         [&] { return sb_attn_fwd_halt(q, k, v, o.p(), (float)eps, tc, s.B, s.H, s.T, s.d, on.stream); });
     return o.take();
 }
 
@@ -300,16 +320,16 @@ PyObject* forward_f32(PyObject* const* a)
     auto* q = static_cast<float*>(any_shape(a[0], F32, "q"));
     auto* k = static_cast<float*>(ptr(a[1], F32, s.q, "k"));
     auto* v = static_cast<float*>(ptr(a[2], F32, s.q, "v"));
-    Out o(a[3], F32, s.q, like, "o");
-    void* st = stream_of(a[6]);
+    const Launch on = launch_on(a[6]);
+    Out o(a[3], F32, s.q, like, "o", on);
     auto go = [&](float* m) {
-        call("sb_attn_fwd_f32", [&] { return sb_attn_fwd_f32(q, k, v, o.p<float>(), m, s.B, s.H, s.T, s.d, st); });
+        call("sb_attn_fwd_f32", [&] { return sb_attn_fwd_f32(q, k, v, o.p<float>(), m, s.B, s.H, s.T, s.d, on.stream); });
     };
     if (none(a[4]) && !truth(a[5])) {
         go(nullptr);
         return o.take();
     }
-    Out m(a[4], F32, s.m, like, "m");
+    Out m(a[4], F32, s.m, like, "m", on);
     go(m.p<float>());
     return tuple({&o, &m});
 }
@@ -327,25 +347,25 @@ PyObject* backward(PyObject* const* a)
     void* r = ptr(a[5], BF, s.hd, "r");
     auto* m = static_cast<float*>(ptr(a[6], F32, s.m, "m"));
     void* g = ptr(a[7], BF, s.q, "dout");
-    Out dq(a[8], F32, s.q, like, "dq"), dk(a[9], F32, s.kv, like, "dk"), dv(a[10], F32, s.kv, like, "dv");
-    void* st = stream_of(a[13]);
-    Workspace ws(a[12], sb_attn_bwd_workspace_bytes(s.B, s.H, s.T, s.d), like, a[13], st);
+    const Launch on = launch_on(a[13]);
+    Out dq(a[8], F32, s.q, like, "dq", on), dk(a[9], F32, s.kv, like, "dk", on), dv(a[10], F32, s.kv, like, "dv", on);
+    Workspace ws(a[12], sb_attn_bwd_workspace_bytes(s.B, s.H, s.T, s.d), like, on);
     auto go = [&](float* dr) {
         call(what, [&] {
             return sb_attn_bwd_gqa(q, k, v, r, m, g, dq.p<float>(), dk.p<float>(), dv.p<float>(), dr, ws.p(), ws.bytes(),
-                                   s.B, s.H, s.Hkv, s.T, s.d, st);
+                                   s.B, s.H, s.Hkv, s.T, s.d, on.stream);
         });
     };
     if (!r) {
         go(static_cast<float*>(ptr(a[11], F32, s.hd, "dr")));
         return tuple({&dq, &dk, &dv});
     }
-    Out dr(a[11], F32, s.hd, like, "dr");
+    Out dr(a[11], F32, s.hd, like, "dr", on);
     go(dr.p<float>());
     return tuple({&dq, &dk, &dv, &dr});
 }
 
-// backward_dq(q, k, v, m, dout, dq, workspace, stream) on a workspace that the caller keeps
+// backward_dq(q, k, v, m, dout, dq, workspace, stream): (dq, workspace), the workspace for backward_dkdv
 PyObject* backward_dq(PyObject* const* a)
 {
     const Dims s = dims(a[0], nullptr);
@@ -355,12 +375,12 @@ PyObject* backward_dq(PyObject* const* a)
     void* v = ptr(a[2], BF, s.q, "v");
     auto* m = static_cast<float*>(ptr(a[3], F32, s.m, "m"));
     void* g = ptr(a[4], BF, s.q, "dout");
-    Out dq(a[5], F32, s.q, like, "dq");
-    void* st = stream_of(a[7]);
-    Workspace ws(a[6], 0, like, a[7], st);
+    const Launch on = launch_on(a[7]);
+    Out dq(a[5], F32, s.q, like, "dq", on);
+    Workspace ws(a[6], sb_attn_bwd_workspace_bytes(s.B, s.H, s.T, s.d), like, on, true);
     call("sb_attn_bwd_dq",
-         [&] { return sb_attn_bwd_dq(q, k, v, m, g, dq.p<float>(), ws.p(), ws.bytes(), s.B, s.H, s.T, s.d, st); });
-    return dq.take();
+         [&] { return sb_attn_bwd_dq(q, k, v, m, g, dq.p<float>(), ws.p(), ws.bytes(), s.B, s.H, s.T, s.d, on.stream); });
+    return Py_BuildValue("(NN)", dq.take(), ws.take());
 }
 
 // backward_dkdv(q, k, v, dout, workspace, dk, dv, stream)
@@ -372,11 +392,11 @@ PyObject* backward_dkdv(PyObject* const* a)
     void* k = ptr(a[1], BF, s.q, "k");
     void* v = ptr(a[2], BF, s.q, "v");
     void* g = ptr(a[3], BF, s.q, "dout");
-    void* st = stream_of(a[7]);
-    Workspace ws(a[4], sb_attn_bwd_workspace_bytes(s.B, s.H, s.T, s.d), like, a[7], st);
-    Out dk(a[5], F32, s.q, like, "dk"), dv(a[6], F32, s.q, like, "dv");
+    const Launch on = launch_on(a[7]);
+    Workspace ws(a[4], sb_attn_bwd_workspace_bytes(s.B, s.H, s.T, s.d), like, on);
+    Out dk(a[5], F32, s.q, like, "dk", on), dv(a[6], F32, s.q, like, "dv", on);
     call("sb_attn_bwd_dkdv", [&] {
-        return sb_attn_bwd_dkdv(q, k, v, g, dk.p<float>(), dv.p<float>(), ws.p(), ws.bytes(), s.B, s.H, s.T, s.d, st);
+        return sb_attn_bwd_dkdv(q, k, v, g, dk.p<float>(), dv.p<float>(), ws.p(), ws.bytes(), s.B, s.H, s.T, s.d, on.stream);
     });
     return tuple({&dk, &dv});
 }
@@ -393,17 +413,17 @@ PyObject* varlen_forward(PyObject* const* a)
     void* v = ptr(a[2], BF, s.kv, "v");
     auto* cu = static_cast<const int*>(any_shape(a[3], at::kInt, "cu_seqlens"));
     void* r = ptr(a[5], BF, s.hd, "r");
-    Out o(a[6], BF, s.q, like, "o");
-    void* st = stream_of(a[9]);
+    const Launch on = launch_on(a[9]);
+    Out o(a[6], BF, s.q, like, "o", on);
     auto go = [&](float* m) {
         call("sb_attn_varlen_fwd",
-             [&] { return sb_attn_varlen_fwd(q, k, v, r, o.p(), m, cu, nseq, s.H, s.Hkv, s.T, max_T, s.d, st); });
+             [&] { return sb_attn_varlen_fwd(q, k, v, r, o.p(), m, cu, nseq, s.H, s.Hkv, s.T, max_T, s.d, on.stream); });
     };
     if (none(a[7]) && !truth(a[8])) {
         go(nullptr);
         return o.take();
     }
-    Out m(a[7], F32, s.m, like, "m");
+    Out m(a[7], F32, s.m, like, "m", on);
     go(m.p<float>());
     return tuple({&o, &m});
 }
@@ -422,20 +442,20 @@ PyObject* varlen_backward(PyObject* const* a)
     void* g = ptr(a[4], BF, s.q, "dout");
     auto* cu = static_cast<const int*>(any_shape(a[5], at::kInt, "cu_seqlens"));
     void* r = ptr(a[7], BF, s.hd, "r");
-    Out dq(a[8], F32, s.q, like, "dq"), dk(a[9], F32, s.kv, like, "dk"), dv(a[10], F32, s.kv, like, "dv");
-    void* st = stream_of(a[13]);
-    Workspace ws(a[12], sb_attn_varlen_bwd_workspace_bytes(nseq, s.H, s.T, max_T, s.d), like, a[13], st);
+    const Launch on = launch_on(a[13]);
+    Out dq(a[8], F32, s.q, like, "dq", on), dk(a[9], F32, s.kv, like, "dk", on), dv(a[10], F32, s.kv, like, "dv", on);
+    Workspace ws(a[12], sb_attn_varlen_bwd_workspace_bytes(nseq, s.H, s.T, max_T, s.d), like, on);
     auto go = [&](float* dr) {
         call("sb_attn_varlen_bwd", [&] {
             return sb_attn_varlen_bwd(q, k, v, r, m, g, dq.p<float>(), dk.p<float>(), dv.p<float>(), dr, cu, nseq,
-                                      s.H, s.Hkv, s.T, max_T, s.d, ws.p(), ws.bytes(), st);
+                                      s.H, s.Hkv, s.T, max_T, s.d, ws.p(), ws.bytes(), on.stream);
         });
     };
     if (!r) {
         go(static_cast<float*>(ptr(a[11], F32, s.hd, "dr")));
         return tuple({&dq, &dk, &dv});
     }
-    Out dr(a[11], F32, s.hd, like, "dr");
+    Out dr(a[11], F32, s.hd, like, "dr", on);
     go(dr.p<float>());
     return tuple({&dq, &dk, &dv, &dr});
 }
@@ -454,25 +474,25 @@ PyObject* decode(PyObject* const* a)
     void* k = ptr(a[1], BF, skv, "k");
     void* v = ptr(a[2], BF, skv, "v");
     void* r = ptr(a[4], BF, sr, "r");
-    void* st = stream_of(a[9]);
+    const Launch on = launch_on(a[9]);
     const bool in_static = truth(a[10]);
     if (in_static && none(a[5])) throw Failed("sb_attn_decode_static allocates nothing: o is required");
-    Out o(a[5], BF, sq, tq, "o");
+    Out o(a[5], BF, sq, tq, "o", on);
     auto go = [&](float* m) {
         if (in_static) {
             call("sb_attn_decode_static",
-                 [&] { return sb_attn_decode_static(q, k, v, r, o.p(), m, B, H, Hkv, T, Tcap, d, st); });
+                 [&] { return sb_attn_decode_static(q, k, v, r, o.p(), m, B, H, Hkv, T, Tcap, d, on.stream); });
             return;
         }
-        Workspace ws(a[8], sb_attn_decode_workspace_bytes(B, H, T, d), tq, a[9], st);
+        Workspace ws(a[8], sb_attn_decode_workspace_bytes(B, H, T, d), tq, on);
         call("sb_attn_decode",
-             [&] { return sb_attn_decode(q, k, v, r, o.p(), m, ws.p(), ws.bytes(), B, H, Hkv, T, Tcap, d, st); });
+             [&] { return sb_attn_decode(q, k, v, r, o.p(), m, ws.p(), ws.bytes(), B, H, Hkv, T, Tcap, d, on.stream); });
     };
     if (none(a[6]) && !truth(a[7])) {
         go(nullptr);
         return o.take();
     }
-    Out m(a[6], F32, sm, tq, "m");
+    Out m(a[6], F32, sm, tq, "m", on);
     go(m.p<float>());
     return tuple({&o, &m});
 }
