@@ -610,25 +610,31 @@ struct KvHead {
     long qhead0;                            // index of head qh0 in `first`
 };
 
+// rows c0 .. c1 of a packed batch
+template <int D>
+__device__ __forceinline__ bool packed_kv_head(KvHead& kh, int seq, int hkv, int c0, int c1, int T_arg, int keys, int H, int G,
+                                               int nt32, int Ttot)
+{
+    kh.T = min(min(c1, Ttot) - c0, T_arg);                // never past the packed rows or the stated maximum
+    if (c0 < 0) return false;
+    kh.nkb = (kh.T + keys - 1) / keys;
+    kh.base = ((long)hkv * Ttot + c0) * D;
+    kh.qrow0 = (long)hkv * G * Ttot + c0;
+    kh.qrow_step = Ttot;
+    kh.qhead0 = (long)seq * H + hkv * G;
+    kh.cbase = (long)hkv * G * nt32 * Ttot + c0;
+    kh.cbase_step = (long)nt32 * Ttot;
+    kh.cstride = Ttot;
+    return true;
+}
+
 template <int D, bool VL>
 __device__ __forceinline__ bool kv_head(KvHead& kh, int bh, int T_arg, int nkb_arg, int keys, int H, int G,
                                         int nt32, const int* __restrict__ cu, int Ttot)
 {
     if constexpr (VL) {
-        const int Hkv = H / G;
-        const int seq = bh / Hkv;
-        const int hkv = bh % Hkv;
-        const int c0 = cu[seq];
-        kh.T = min(min(cu[seq + 1], Ttot) - c0, T_arg);   // never past the packed rows or the stated maximum
-        if (c0 < 0) return false;
-        kh.nkb = (kh.T + keys - 1) / keys;
-        kh.base = ((long)hkv * Ttot + c0) * D;
-        kh.qrow0 = (long)hkv * G * Ttot + c0;
-        kh.qrow_step = Ttot;
-        kh.qhead0 = (long)seq * H + hkv * G;
-        kh.cbase = (long)hkv * G * nt32 * Ttot + c0;
-        kh.cbase_step = (long)nt32 * Ttot;
-        kh.cstride = Ttot;
+        const int seq = bh / (H / G);
+        return packed_kv_head<D>(kh, seq, bh % (H / G), cu[seq], cu[seq + 1], T_arg, keys, H, G, nt32, Ttot);
     } else {
         const long qh0 = (long)bh * G;
         kh.T = T_arg;
@@ -1500,7 +1506,8 @@ bwd_dq_small_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
                     const float* __restrict__ m,
                     const uint16_t* __restrict__ dout, float* __restrict__ dq,
                     float* __restrict__ ca, float* __restrict__ cb, uint16_t* __restrict__ first,
-                    int T_arg, int BH, int H, int G, int nstrip_arg, int nqb_arg, int nt32, const int* __restrict__ cu, int Ttot)
+                    int T_arg, int BH, int H, int G, int n_arg, int nqb_arg, int nt32,       // n_arg: strips a head; packed batch: sequences
+                    const int* __restrict__ cu, int Ttot)
 {
     using C = SmallCfg<D>;
     constexpr int NWS = C::NWS, NTHR = 64 * NWS;
@@ -1511,27 +1518,28 @@ bwd_dq_small_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
     static_assert(NWS * 32 * D * 4 <= NWS * C::WAVE, "the partial gradients fit");
 
     asm volatile("" :: "s"(q), "s"(k), "s"(v), "s"(m), "s"(dout), "s"(T_arg), "s"(G));
+    const int tid = threadIdx.x, lane = tid & 63;
     const Share sh = in_scalars(share_of(blockIdx.x, BH, -1));
-    const int bh = sh.bh, head = bh % H;
-    int T = T_arg, nstrip = nstrip_arg;
+    const int head = sh.bh % H;
+    int bh = sh.bh, T = T_arg, nstrip = n_arg, i = sh.i;
     long row0 = bh * (long)T, kvrow0 = (long)(G == 1 ? bh : (int)((unsigned)bh / (unsigned)G)) * T;
     long cbase = (long)bh * nt32 * T, cstride = T;
-    if (cu) {                                           // packed batch, as in bwd_dq_kernel
-        const int seq = bh / H;
-        const int c0 = cu[seq];
-        T = min(min(cu[seq + 1], Ttot) - c0, T_arg);
-        if (c0 < 0) return;
+    if (cu) {                                           // packed batch: sh.bh is the head alone, sh.i its place
+        const Place at = place_of(sh.i, cu, n_arg, lane);
+        T = min(min(at.c1, Ttot) - at.c0, T_arg);
+        if (at.c0 < 0) return;
         nstrip = (T + 31) / 32;
-        if (sh.i >= nstrip) return;
-        row0 = (long)head * Ttot + c0;
-        kvrow0 = (long)(head / G) * Ttot + c0;
-        cbase = (long)head * nt32 * Ttot + c0;
+        i = at.i;
+        if (i < 0 || i >= nstrip) return;
+        bh = at.seq * H + head;
+        row0 = (long)head * Ttot + at.c0;
+        kvrow0 = (long)(head / G) * Ttot + at.c0;
+        cbase = (long)head * nt32 * Ttot + at.c0;
         cstride = Ttot;
     }
-    const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n = lane & 31, hh = lane >> 5, gg = lane >> 4, li = lane & 15;
-    const int strip = nstrip - 1 - sh.i;
+    const int strip = nstrip - 1 - i;
     const int q0 = strip * 32;
     const uint16_t* Kg = k + kvrow0 * D;
     const uint16_t* Vg = v + kvrow0 * D;
@@ -1721,7 +1729,8 @@ bwd_dkv_small_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict_
                      const uint16_t* __restrict__ v, const uint16_t* __restrict__ dout,
                      const float* __restrict__ ca, const float* __restrict__ cb,
                      float* __restrict__ dk, float* __restrict__ dv, const uint16_t* __restrict__ first,
-                     int T_arg, int BH, int H, int G, int nstrip_arg, int nqb_arg, int nt32, const int* __restrict__ cu, int Ttot)
+                     int T_arg, int BH, int H, int G, int n_arg, int nqb_arg, int nt32,       // n_arg: strips a head; packed batch: sequences
+                     const int* __restrict__ cu, int Ttot)
 {
     using C = SmallCfg<D>;
     constexpr int NWS = C::NWS, NTHR = 64 * NWS;
@@ -1731,15 +1740,22 @@ bwd_dkv_small_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict_
 
     asm volatile("" :: "s"(q), "s"(k), "s"(v), "s"(dout), "s"(ca), "s"(cb), "s"(first), "s"(T_arg));
     const Share sh = in_scalars(share_of(blockIdx.x, BH, -1));
-    KvHead kh;
-    const bool some = cu ? kv_head<D, true>(kh, sh.bh, T_arg, nstrip_arg, 32, H, G, nt32, cu, Ttot)
-                         : kv_head<D, false>(kh, sh.bh, T_arg, nstrip_arg, 32, H, G, nt32, cu, Ttot);
-    if (!some || sh.i >= kh.nkb) return;
-    const int T = kh.T, nstrip = kh.nkb;
     const int tid = threadIdx.x, lane = tid & 63;
+    KvHead kh;
+    int ks = sh.i;                                       // the strip; small ones have the most queries
+    if (cu) {                                            // packed batch: sh.bh is the head alone, sh.i its place
+        const Place at = place_of(sh.i, cu, n_arg, lane);
+        if (!packed_kv_head<D>(kh, at.seq, sh.bh, at.c0, at.c1, T_arg, 32, H, G, nt32, Ttot)) return;
+        ks = at.i;
+        if (ks < 0) return;
+    } else {
+        kv_head<D, false>(kh, sh.bh, T_arg, n_arg, 32, H, G, nt32, cu, Ttot);
+    }
+    if (ks >= kh.nkb) return;
+    const int T = kh.T, nstrip = kh.nkb;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n = lane & 31, hh = lane >> 5, gg = lane >> 4, li = lane & 15;
-    const int ks = sh.i, k0 = ks * 32;                   // the strip; small ones have the most queries
+    const int k0 = ks * 32;
     char* const mine = smem + wave * WAVE;
 
     // the query strips of head g that reach the keys, as bits; wave w takes strips ks + w, ks + w + NWS, ... of
@@ -2010,6 +2026,7 @@ hipError_t launch_one(const uint16_t* q, const uint16_t* k, const uint16_t* v, c
     const long gq = share_grid(BH, nqb, false), gk = share_grid(BHkv, nkb, pairs);
     const long strips_q = pieces(B, H, T, 32, VL, Ttot), strips_k = pieces(B, Hkv, T, 32, VL, Ttot);
     const long blocks_k = pieces(B, Hkv, T, BKW, VL, Ttot);
+    const long mean_T = mean_length(B, T, VL, Ttot), places = VL ? packed_places(B, Ttot) : nt32;
     const int run_q = VL || G > 1 ? -1 : share_run(BH, nqb), run_k = VL || G > 1 ? -1 : share_run(BHkv, nkb);
     // checked before the first launch, so that an error leaves nothing enqueued
     if (gq > 0x7fffffffL || gk > 0x7fffffffL || nchunk * (long)BH > 0x7fffffffL) return hipErrorInvalidValue;
@@ -2022,9 +2039,9 @@ hipError_t launch_one(const uint16_t* q, const uint16_t* k, const uint16_t* v, c
     if (e != hipSuccess) return e;                                                                              \
     }
 #define SB_DQ(RBV)                                                                                              \
-    if (small_grid(strips_q, T, D)) {                                                                                  \
-        hipLaunchKernelGGL((bwd_dq_small_kernel<D>), dim3((unsigned)(BH * nt32)), dim3(64 * SmallCfg<D>::NWS), 0, stream, \
-                           q, k, v, rb, m, dout, dq, ca, cb, first, T, BH, H, G, nt32, nqb, nt32, cu, Ttot);    \
+    if (small_grid(strips_q, T, mean_T, D)) {                                                                   \
+        hipLaunchKernelGGL((bwd_dq_small_kernel<D>), dim3((unsigned)((VL ? H : BH) * places)), dim3(64 * SmallCfg<D>::NWS), 0, stream, \
+                           q, k, v, rb, m, dout, dq, ca, cb, first, T, VL ? H : BH, H, G, VL ? B : nt32, nqb, nt32, cu, Ttot); \
         if ((e = hipGetLastError()) != hipSuccess) return e;                                                    \
     } else SB_LAUNCH(gq, NTHREADS, (bwd_dq_kernel<D, RBV, VL>),                                                        \
               q, k, v, rb, m, dout, dq, ca, cb, first, T, BH, H, G, nqb, nt32, cu, Ttot, run_q)
@@ -2032,9 +2049,9 @@ hipError_t launch_one(const uint16_t* q, const uint16_t* k, const uint16_t* v, c
 // dimensions leave room for two workgroups of the one-wave-per-strip kernel per CU, which
 // is faster there (measured).
 #define SB_DKV(GQAV)                                                                                            \
-    if (small_grid(strips_k, T, D)) {                                                                               \
-            hipLaunchKernelGGL((bwd_dkv_small_kernel<D>), dim3((unsigned)(BHkv * nt32)), dim3(64 * SmallCfg<D>::NWS), 0, stream, \
-                               q, k, v, dout, ca, cb, dk, dv, first, T, BHkv, H, G, nt32, nqb, nt32, cu, Ttot); \
+    if (small_grid(strips_k, T, mean_T, D)) {                                                                   \
+        hipLaunchKernelGGL((bwd_dkv_small_kernel<D>), dim3((unsigned)((VL ? Hkv : BHkv) * places)), dim3(64 * SmallCfg<D>::NWS), 0, stream, \
+                           q, k, v, dout, ca, cb, dk, dv, first, T, VL ? Hkv : BHkv, H, G, VL ? B : nt32, nqb, nt32, cu, Ttot); \
         if ((e = hipGetLastError()) != hipSuccess) return e;                                                    \
     } else if constexpr (D == 128) {                                                                            \
         if (blocks_k <= small_kv_grid(nkb)) {                                                         \

@@ -645,7 +645,7 @@ __global__ void __launch_bounds__(64 * FwdSmallCfg<D>::NWS)
 fwd_small_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
                  const uint16_t* __restrict__ v, const uint16_t* __restrict__ rb,
                  uint16_t* __restrict__ o, float* __restrict__ m,
-                 int T_arg, int BH, int H, int G, int nstrip_arg,
+                 int T_arg, int BH, int H, int G, int n_arg,       // n_arg: strips a head; packed batch: sequences
                  unsigned long long* __restrict__ clocks, const int* __restrict__ cu, int Ttot)
 {
     using C = FwdSmallCfg<D>;
@@ -655,21 +655,21 @@ fwd_small_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     __shared__ float s_tot[2][NWS][32];                 // per round parity: softplus totals of its subtiles (base 2), per row
 
     asm volatile("" :: "s"(q), "s"(k), "s"(v), "s"(T_arg), "s"(G));
+    const int tid = threadIdx.x, lane = tid & 63;
     const Share sh = in_scalars(share_of(blockIdx.x, BH, -1));
     const int bh = sh.bh, head = bh % H;
-    int T = T_arg, nstrip = nstrip_arg;
+    int T = T_arg, nstrip = n_arg, i = sh.i;
     long row0 = bh * (long)T, kvrow0 = (long)(G == 1 ? bh : (int)((unsigned)bh / (unsigned)G)) * T;
-    if (cu) {                                           // packed batch, as in fwd_bf16_kernel
-        const int seq = bh / H;
-        const int c0 = cu[seq];
-        T = min(min(cu[seq + 1], Ttot) - c0, T_arg);
-        if (c0 < 0) return;
+    if (cu) {                                           // packed batch: bh is the head alone, sh.i its place
+        const Place at = place_of(sh.i, cu, n_arg, lane);
+        T = min(min(at.c1, Ttot) - at.c0, T_arg);
+        if (at.c0 < 0) return;
         nstrip = (T + 31) / 32;
-        if (sh.i >= nstrip) return;
-        row0 = (long)head * Ttot + c0;
-        kvrow0 = (long)(head / G) * Ttot + c0;
+        i = at.i;
+        if (i < 0 || i >= nstrip) return;
+        row0 = (long)head * Ttot + at.c0;
+        kvrow0 = (long)(head / G) * Ttot + at.c0;
     }
-    const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const bool clock = clocks && blockIdx.x == 0 && tid == 0;
     if (clock) {                                        // as in fwd_bf16_kernel
@@ -677,7 +677,7 @@ fwd_small_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
         clocks[1] = (unsigned long long)wall_clock64();
     }
     const int n = lane & 31, hh = lane >> 5, gg = lane >> 4, li = lane & 15;
-    const int strip = nstrip - 1 - sh.i;
+    const int strip = nstrip - 1 - i;
     const int q0 = strip * 32;
     const uint16_t* Qg = q + row0 * D;
     const uint16_t* Kg = reinterpret_cast<const uint16_t*>(scalar_base(k + kvrow0 * D));
@@ -831,10 +831,11 @@ hipError_t launch_one(const uint16_t* q, const uint16_t* k, const uint16_t* v, c
                       unsigned long long* tile_counts, hipStream_t stream,
                       const int* cu = nullptr, int Ttot = 0)
 {
-    if (!TRI && enough == CARRY_EXHAUSTED && (WRITE_M || !tile_counts) && small_fwd_grid(pieces(BH / H, H, T, 32, VL, Ttot), T, D)) {     // halting sweeps stop by blocks
-        const int nstrip = (T + 31) / 32;
-        hipLaunchKernelGGL((fwd_small_kernel<D>), dim3((unsigned)(BH * nstrip)), dim3(64 * FwdSmallCfg<D>::NWS), 0, stream,
-                           q, k, v, rb, o, m, T, BH, H, G, nstrip, tile_counts, cu, Ttot);
+    const bool small = small_fwd_grid(pieces(BH / H, H, T, 32, VL, Ttot), T, mean_length(BH / H, T, VL, Ttot), D);
+    if (!TRI && enough == CARRY_EXHAUSTED && (WRITE_M || !tile_counts) && small) {     // halting sweeps stop by blocks
+        const int heads = VL ? H : BH, n = VL ? BH / H : (T + 31) / 32;
+        hipLaunchKernelGGL((fwd_small_kernel<D>), dim3((unsigned)(heads * (VL ? packed_places(n, Ttot) : n))), dim3(64 * FwdSmallCfg<D>::NWS), 0, stream,
+                           q, k, v, rb, o, m, T, heads, H, G, n, tile_counts, cu, Ttot);
         return hipGetLastError();
     }
     const int nqb = (T + BQ - 1) / BQ;

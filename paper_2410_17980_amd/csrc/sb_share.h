@@ -45,6 +45,19 @@ inline bool take_pairs(long heads, int nblk)
     return 32 * idle <= n;
 }
 
+// Of a packed batch the host knows how many sequences of how many rows in all, and T, at least the longest one's length and
+// perhaps far more.  mean_T: the sequences' mean length (T itself in a batched call).  Strips are for chains that count:
+//   not where the mean is 64 rows or less, unless there is a place on the chip for every strip and T leaves room for
+//   a long one.  Blocks / strips, us, forward, then backward: 64 sequences of 32 rows, H4 d64 (512 places), T 128 to 512
+//   3.8 / 8.2, 10 / 26; H2 d128 (256) 4.5 / 5.3, 12.5 / 17.8; but one of 600 and 30 of 20 rows, H2 d128 (136) 14.3 / 9.1, 32 / 24;
+//   below 512 with the limit of three times the mean: 100 of 70 rows, H1 d64 (318), T 400 5.2 / 8.3, 14.9 / 25.
+inline long mean_length(int B, int T, bool packed, int Ttot) { return packed ? ((long)Ttot + B - 1) / B : T; }
+inline bool long_enough(long strips, int T, long mean_T)
+{
+    return mean_T <= T && (mean_T > 64 || (T >= 256 && strips <= 256));
+}
+inline long chain_length(int T, long mean_T) { return T < 512 ? std::min((long)T, 3 * mean_T) : T; }
+
 // Grids of the backward that take one strip of 32 rows a workgroup, its waves sharing the strip's other side
 // (bwd_dq_small_kernel, bwd_dkv_small_kernel), in place of 128-row blocks whose every wave has the
 // whole other side to itself.  What bounds the blocks there is one chain, what bounds the strips from a round or two of the
@@ -57,10 +70,11 @@ inline bool take_pairs(long heads, int nblk)
 // B1 H24 T1000 d128 (768) 40 / 55; B1 H4 T64 d64 5.0 / 6.1, 6.4 / 6.3.  (All heads far; where they are near the
 // strips gain more.)  4096: the kernels' arrays hold 128 strips.
 constexpr int SMALL_T = 4096;
-inline bool small_grid(long strips, int T, int d)
+inline bool small_grid(long strips, int T, long mean_T, int d)
 {
-    const long limit = d == 128 ? 256 : T >= 1024 ? 768 : T > 341 ? 3L * T / 4 : 256;
-    return T > 64 && T <= SMALL_T && strips <= limit;
+    const long t = chain_length(T, mean_T);
+    const long limit = d == 128 ? 256 : t >= 1024 ? 768 : t > 341 ? 3 * t / 4 : 256;
+    return long_enough(strips, T, mean_T) && T <= SMALL_T && strips <= limit;
 }
 
 // How many strips or blocks of `rows` rows there are: exactly, or in a packed batch of nseq sequences, whose
@@ -69,6 +83,32 @@ inline long pieces(int B, int H, int T, int rows, bool packed, int Ttot)
 {
     const long all = (long)B * H * ((T + rows - 1) / rows);
     return packed ? std::min(all, (long)H * (Ttot / rows + B)) : all;
+}
+
+// Workgroups of a packed batch's strips, per head: sequence s has the places (cu[s] >> 5) + s up to the next one's,
+// as many as it has strips, or one more.  (A place for every strip that max_T leaves room for costs 2 us a thousand in each
+// launch: 64 sequences of 32 rows, H4 d64, max_T 2048, forward 34.6 us with 16384 of them.)
+inline long packed_places(int nseq, int Ttot) { return Ttot / 32 + nseq; }
+struct Place {
+    int seq, i;               // sequence, strip
+    int c0, c1;               // the sequence's offsets; c0 < 0: none
+};
+__device__ __forceinline__ Place place_of(int place, const int* __restrict__ cu, int nseq, int lane)
+{
+    Place at = {0, 0, -1, -1};
+    for (int b = 0; b < nseq; b += 64) {
+        const int s = min(b + lane, nseq - 1);
+        const int c0 = cu[s], c1 = cu[s + 1];
+        const int n = __builtin_popcountll(__builtin_amdgcn_ballot_w64(b + lane < nseq && (c0 >> 5) + s <= place));
+        if (n > 0) {
+            at.seq = b + n - 1;
+            at.c0 = __builtin_amdgcn_readlane(c0, n - 1);
+            at.c1 = __builtin_amdgcn_readlane(c1, n - 1);
+        }
+        if (n < 64) break;
+    }
+    at.i = place - (at.c0 >> 5) - at.seq;
+    return at;
 }
 
 // Grids of the forward that take one strip of 32 rows a workgroup, its waves taking the strip's subtiles in rounds
@@ -80,10 +120,11 @@ inline long pieces(int B, int H, int T, int rows, bool packed, int Ttot)
 //   none far        12.2 / 7.0 and 17.2 / 9.4 for B1 H8 T700 d128, 8.9 / 10.2 and 41 / 17 for B1 H4 T4000 d64
 // and not, a third far, B4 H8 T700 d64 (704) 13.5 / 16.2, 13.6 / 17.6; B1 H24 T1000 d128 (768) 26.4 / 28.1, 26.5 / 31.8;
 // B4 H16 T300 d32 (640) 6.9 / 9.8, 7.0 / 10.1.  At d = 32 a chain of 10 subtiles is not worth the rounds' barriers.
-inline bool small_fwd_grid(long strips, int T, int d)
+inline bool small_fwd_grid(long strips, int T, long mean_T, int d)
 {
-    const long limit = T < 256 ? 256 : T < 512 || d == 128 ? 384 : 512;
-    return T > (d == 32 ? 320 : 64) && T <= SMALL_T && strips <= limit;
+    const long t = chain_length(T, mean_T);
+    const long limit = t < 256 ? 256 : t < 512 || d == 128 ? 384 : 512;
+    return T > (d == 32 ? 320 : 64) && long_enough(strips, T, mean_T) && T <= SMALL_T && strips <= limit;
 }
 
 // log2 of the run, -1: turn with every block.  A run pays where the launch is several rounds deep and

@@ -120,3 +120,33 @@ def test_forward_packed(sb, gen, d):
         if n:
             o1, m1 = sb.sb_attn_fwd_train(*(t[None, :, s].contiguous() for t in (qd, kd, vd)))
             assert torch.equal(o[:, s], o1[0]) and torch.allclose(m[:, s], m1[0], rtol=1e-5, atol=1e-4)
+
+
+@pytest.mark.parametrize("lens,H,Hkv,max_T", [
+    ([0] * 3 + [1, 33] * 32 + [0, 300, 31], 2, 2, 300),                # 70 sequences: more than a wave looks at at a time
+    ([2, 0, 34] * 21 + [1, 400] + [0] * 70, 1, 1, 400),                # the 64th and the 65th of 135; nothing behind them
+    ([100] * 13, 4, 2, 1300),                                          # a maximum that no sequence comes near
+])
+@pytest.mark.parametrize("d", [32, 64, 128])
+def test_packed_places(sb, oracle, gen, lens, H, Hkv, max_T, d):
+    """A workgroup finds its sequence and strip among many, and among empty ones: o is every sequence's alone,
+    bit for bit, and every gradient the oracle's."""
+    q0, k, v = mixed(gen, 1, Hkv, sum(lens), d, seed=27)
+    g, q, _ = gen.gaussian(1, H, sum(lens), d, seed=28, dtype="bf16")
+    q = q.clone()
+    q[:, ::H // Hkv] = q0
+    q, k, v, g = (t[0] for t in (q, k, v, g))
+    r = gen.remainder_embedding(H, d, seed=29)
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    qd, kd, vd, gd, rd, cud = dev(q, k, v, g, r, torch.from_numpy(cu))
+    o, m = sb.sb_attn_varlen_fwd(qd, kd, vd, cud, max_T, r=rd)
+    ws = nan_bytes(sb.sb_attn_varlen_bwd_workspace_bytes(len(lens), H, sum(lens), max_T, d))
+    got = sb.sb_attn_varlen_bwd(qd, kd, vd, m, gd, cud, max_T, r=rd, workspace=ws)
+    for a, n in zip(cu, lens):
+        s = slice(int(a), int(a) + n)
+        if n:
+            o1, m1 = sb.sb_attn_fwd_gqa(*(t[None, :, s].contiguous() for t in (qd, kd, vd)), r=rd)
+            assert torch.equal(o[:, s], o1[0]) and torch.allclose(m[:, s], m1[0], rtol=1e-5, atol=1e-4)
+    ref = oracle.bwd_varlen(to64(q), to64(k), to64(v), to64(g), cu, r=to64(r))
+    for name, a, x in zip(("dq", "dk", "dv", "dr"), got, ref):
+        check_grad(name, to64(a), x)
