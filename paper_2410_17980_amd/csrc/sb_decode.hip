@@ -29,28 +29,19 @@
 // chip, whatever they take (this kernel's predecessor), us: B8 H16 T16384 d128 68 / 167 / 180 (all keys at
 // 6.4 TB/s), B1 H32 Hkv8 T65000 d128 29 / 54 / 47, B32 H16 T1800 d64 34 / 50 / 37, B16 H32 Hkv8 T4096 d128
 // 28 / 55 / 45: where every head reaches far the launch in front is 5 to 13 us lost.
-#include <algorithm>
 #include <mutex>
 #include <type_traits>
 
 #include "../../include/sb_attn.h"
 #include "sb_kernels.h"
 #include "sb_mma.h"
+#include "sb_split.h"
 
 namespace sb {
 namespace {
 
-constexpr int NEAR_NW = 8;             // waves of a workgroup, first launch
-constexpr int FAR_NW = 4;              // and second: smaller, so that three share a CU
-constexpr int KW = 32;                 // keys per wave and pass
-constexpr int NEAR = KW * NEAR_NW;     // keys of a first launch that has a second one behind it
 constexpr int GMAX = 16;               // query heads of a group per workgroup: the columns of the MFMA
-constexpr int ALONE = 6 * NEAR;        // caches up to here take the first launch only (6 us + 1.3 us a pass; two launches 15 us)
 constexpr int COMBINE_THREADS = 256;
-constexpr int MAXFAR = 127;            // chunks beyond the nearest keys: with those, two per lane of a wave
-constexpr int FAR_KEYS = KW * FAR_NW;  // keys of a pass of the second launch
-constexpr long FAR_WGS = 2048;         // workgroups of the second launch, all heads together
-constexpr long ALL_WGS = 8192;         // the same where it takes all keys (see split_of())
 
 
 // sum of v over the lanes above this one, and over all lanes in `total`
@@ -316,59 +307,13 @@ decode_combine_kernel(const float* __restrict__ part_o, const float* __restrict_
     }
 }
 
-// Partial results there is room for in decode_workspace_bytes: one per 64 keys, or per 64 * 2^i where
-// those would be more than 256.
-int room(int T)
-{
-    int C = 64;
-    while ((T + C - 1) / C > 256) C *= 2;
-    return (T + C - 1) / C;
-}
-
-// How the keys are split: the nearest in the first launch, the rest in nfar chunks of C, whole passes of
-// either kernel.  With m wanted every key is read whatever the nearest ones take: they need no launch of
-// their own, and as no workgroup is let off, more and smaller chunks even the CUs out.  With m, us: three
-// launches / two with the same chunks / two with these: B16 H32 Hkv8 T4096 d128 55 / 49 / 48, B32 H16 T1800 d64
-// 49 / 43 / 39, B1 H32 Hkv8 T65000 d128 53 / 46 / 46, B8 H16 T16384 d128 167 / 161 / 162, B1 H8 T2000 d64
-// 12.8 / 9.4 / 6.7.
-//
-// A small cache is spread over the chip as well: one workgroup a head is bound by what one CU can load (per pass
-// of 256 keys 2.2 us at d = 128, 1.3 at d = 64), three launches by their latencies.  That reads every key (0.1 us per MB of
-// cache on top of 6 to 7.4), so it is limited by the size of the whole cache, and it pays unless all heads end within
-// their nearest keys.  Without m, us, as before / spread, a third of the kv heads far, then none:
-//   B1 H12 Hkv4 d128 T600 10.2 / 7.5, 6.8 / 7.5; T1500 18.0 / 7.6, 6.7 / 7.5
-//   B2 H8 T1000 d64 9.0 / 6.3, 4.6 / 6.2; B4 H8 T1200 d128 (20 MB) 15.2 / 9.3, 6.7 / 9.3
-//   B1 H8 T2000 d64 12.5 / 6.4, 11 / 6.4; B1 H8 T6000 d128 (25 MB) 15.2 / 9.4, 10.0 / 9.3
-//   B2 H16 T2000 d128 (33 MB) 16.1 / 9.9, 10.0 / 9.8
-//   B5 H30 Hkv10 T588 d64 (8 MB) 7.8 / 6.3, 4.7 / 6.4
-// and not where B8 H16 T600 d64 (20 MB) 7.6 / 8.2, 4.7 / 8.2; B1 H12 Hkv4 T333 d128 7.8 / 7.6, 6.4 / 7.4; B4 H8 T400 d128 7.7 / 7.7, 6.4 / 7.7;
-// B8 H16 T1000 d128 (66 MB) 14.0 / 14.7, 7.0 / 14.8; B2 H16 T4000 d128 (66 MB) 16.4 / 14.9, 9.9 / 15.1.
-struct Split {
-    int near, C, nfar;
-    int chunks() const { return nfar + (near > 0); }
-};
-Split split_of(long wgs, double cache_bytes, int T, bool want_m)
-{
-    Split s = {T, NEAR, 0};
-    const int passes = (T + NEAR - 1) / NEAR;
-    const bool spread = passes > 2 && cache_bytes <= std::min(34e6, 12e6 * (passes - 2));
-    if (T <= ALONE && !spread) return s;
-    const bool all = want_m || spread;
-    s.near = all ? 0 : NEAR;
-    const int far = T - s.near, unit = all ? FAR_KEYS : NEAR;
-    const long want = std::min((long)std::min(MAXFAR, room(T) - 1), std::max(1L, (all ? ALL_WGS : FAR_WGS) / wgs));
-    s.C = (int)((far + want - 1) / want + unit - 1) / unit * unit;
-    s.nfar = (far + s.C - 1) / s.C;
-    return s;
-}
-
 template <int D>
 hipError_t launch_d(const uint16_t* q, const uint16_t* k, const uint16_t* v, const uint16_t* rb,
                     uint16_t* o, float* m, float* workspace, int B, int H, int Hkv, int T, int Tcap, hipStream_t stream)
 {
     const int G = H / Hkv;
     const int nz = (G + GMAX - 1) / GMAX;
-    const Split s = split_of((long)B * Hkv * nz, 4.0 * B * Hkv * T * D, T, m != nullptr);
+    const Split s = split_of((long)B * Hkv * nz, 4.0 * B * Hkv * T * D, T, D, m != nullptr);
     const long heads = (long)B * H;
     float* part_o = workspace;                                            // [heads][chunks][D]
     float* part_a = part_o + heads * s.chunks() * D;                      // [heads][chunks]

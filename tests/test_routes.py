@@ -1,4 +1,4 @@
-"""Which kernels a call takes (csrc/sb_share.h), compiled for the host: the rules' edges, and the routes that the GPU
+"""Which kernels a call takes (csrc/sb_share.h, csrc/sb_split.h), compiled for the host: the rules' edges, and the routes that the GPU
 tests name for their shapes."""
 import os
 import random
@@ -14,11 +14,17 @@ HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 MAIN = r"""
 #include <stdio.h>
 #include "sb_share.h"
+#include "sb_split.h"
 using namespace sb;
 int main()
 {
     int B, H, Hkv, T, d, packed, Ttot;
     while (scanf("%d %d %d %d %d %d %d", &B, &H, &Hkv, &T, &d, &packed, &Ttot) == 7) {
+        if (packed == 2) {                              // decode; Ttot: m wanted
+            const Split s = split_of((long)B * Hkv * ((H / Hkv + 15) / 16), 4.0 * B * Hkv * T * d, T, d, Ttot);
+            printf("%d %d %d %d\n", s.near, s.C, s.nfar, room(T));
+            continue;
+        }
         const long mean = mean_length(B, T, packed, Ttot);
         printf("%d %d %d %ld\n", small_fwd_grid(pieces(B, H, T, 32, packed, Ttot), T, mean, d),
                small_grid(pieces(B, H, T, 32, packed, Ttot), T, mean, d),
@@ -88,3 +94,42 @@ def test_shapes_of_the_gpu_tests(ask):
                                 ([100] * 13, 4, 2, 1300)):
         for d in (32, 64, 128):
             assert ask([packed(lens, H, d, max_T, Hkv)])[0][:3] == (d > 32 or max_T > 320, 1, 1), (lens, d)
+
+
+def decode(B, H, Hkv, T, d, want_m=False):
+    return (B, H, Hkv, T, d, 2, want_m)
+
+
+ONE, SPREAD, FAR_AND_NEAR = "one workgroup a head", "spread", "nearest keys first"
+
+
+def kind(row, got):
+    near, _, nfar, _ = got
+    return SPREAD if near == 0 else ONE if nfar == 0 else FAR_AND_NEAR
+
+
+def test_decode_routes(ask):
+    """A small cache is spread over the chip only where heads that end within their nearest keys lose less by it than
+    far ones gain; always with m, which takes every key."""
+    want = {ONE: [(1, 12, 4, 333, 128), (5, 30, 10, 588, 64), (5, 30, 10, 1000, 64), (2, 8, 8, 1000, 64), (5, 30, 10, 1000, 32), (2, 8, 8, 1280, 32),
+                  (8, 16, 16, 1000, 128), (5, 30, 10, 1000, 128), (1, 1, 1, 512, 128), (4, 8, 8, 1500, 64)],
+            SPREAD: [(1, 12, 4, 600, 128), (4, 8, 8, 1000, 128), (4, 8, 8, 1200, 128), (1, 12, 4, 1500, 128), (2, 8, 8, 1280, 64), (2, 8, 8, 1500, 64),
+                     (2, 8, 8, 1500, 32), (1, 4, 4, 1600, 32), (2, 16, 16, 2000, 128), (1, 8, 8, 6000, 128)],
+            FAR_AND_NEAR: [(8, 16, 16, 16384, 128), (1, 32, 8, 65000, 128), (8, 8, 8, 3000, 64), (2, 16, 16, 4000, 128)]}
+    for name, shapes in want.items():
+        rows = [decode(*s) for s in shapes]
+        assert [kind(r, g) for r, g in zip(rows, ask(rows))] == [name] * len(rows), name
+    rows = [decode(B, H, Hkv, T, d, True) for B, H, Hkv, T, d in ((5, 30, 10, 588, 64), (5, 30, 10, 1000, 64), (2, 8, 8, 1000, 32), (2, 16, 16, 4000, 128))]
+    assert all(kind(r, g) == SPREAD for r, g in zip(rows, ask(rows)))
+
+
+def test_decode_chunks_cover_the_keys_and_fit(ask):
+    rng = random.Random(5)
+    rows = []
+    for _ in range(2000):
+        Hkv, T = rng.randrange(1, 33), round(2 ** rng.uniform(0, 19))
+        rows.append(decode(rng.randrange(1, 33), Hkv * rng.choice((1, 2, 3, 17)), Hkv, T, rng.choice((32, 64, 128)), rng.random() < 0.5))
+    for row, (near, C, nfar, room) in zip(rows, ask(rows)):
+        T = row[3]
+        assert near + C * nfar >= T and near + C * (nfar - 1) < T and nfar <= 127, row
+        assert nfar == 0 or nfar + (near > 0) <= room, row
