@@ -699,17 +699,7 @@ __device__ __forceinline__ int reaching(uint32_t w, int ks)
 
 // ------------------------------------------------------------------ dK / dV kernel
 // SP groups of four waves take the block's query tiles in turn (tile t: group t % SP), each into
-// accumulators of its own, added up at the end in LDS.  Two groups where a block has a CU to itself
-// anyway (one wave per SIMD issues an instruction every five clocks at best, two keep it busy), and where
-// few enough blocks are left once some heads turn out near: what counts then is the longest block's
-// chain.  One group / two, us, all heads far, then a third, then none:
-//   B1 H16 T4096 d32 (512 blocks, 32 a head) 115 / 92, 115 / 84, 18 / 22; B1 H24 T4096 d64 (768, 32) 171 / 179, 143 / 101,
-//   37 / 42; B2 H24 T1024 d64 (384, 8) 39 / 33, 39 / 32, 24 / 27; B1 H40 T2048 d64 (640, 16) 78 / 86, 73 / 55, 32 / 39
-//   B1 H32 T4096 d64 (1024, 32) 225 / 232, 154 / 113, 42 / 57; B5 H5 T4500 d32 (900, 36) 156 / 177, 122 / 92, 27 / 36; but
-//   B1 H30 T3500 d64 (840, 28) 163 / 170, 129 / 158, 38 / 52 (every third head far; why that count differs was not found)
-// and not B8 H16 T512 d64 (512, 4) 25 / 29, 24 / 29, 23 / 28; B8 H8 T2000 d32 (1024, 16) 78 / 94, 60 / 52, 28 / 36;
-// B2 H20 T4096 d64 (1280, 32) 275 / 291, 158 / 143, 52 / 65; B8 H16 T2048 d64 (2048, 16) 236 / 259, 126 / 164, 80 / 108.
-constexpr long in_turn_grid(int nkb) { return std::clamp(48L * nkb, ONE_PER_CU, 1024L); }
+// accumulators of its own, added up at the end in LDS.  Which grids take two: take_in_turn().
 template <int D, int SP> struct DkvCfg {
     static constexpr int T_OFF = SP * 2 * StageCfg<D>::STAGE;   // after the double buffers
     static constexpr int T_WAVE = 2 * SCR_MAT;             // A and dZ scratch of one wave
@@ -1041,18 +1031,7 @@ bwd_dkv_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
 // the two roles taking front and back in opposite order within an interval (so that one
 // wave of a SIMD is in its vector phase while the other is in its matrix phase) is slower,
 // 1.47 ms: the compiler then copies the accumulator (64 registers) on every switch.
-// KS: strips per block, 4 or, in small grids, 2: what bounds a launch there is one block's chain of
-// intervals, and with one wave per SIMD in place of two an interval is shorter.  Where the 128-key blocks
-// outnumber the CUs this costs more rounds than it saves, except with long chains and heads of mixed
-// reach.  Key-stationary pass with 128 / 64 keys a block, us, all heads far, then a third:
-//   up to 256 blocks   B1 H20 T1024 (160) 40 / 31, 40 / 31; B1 H16 T2048 (256) 69 / 64, 67 / 50;
-//                      B8 H16 T256 (256) 33 / 28, 33 / 27; B1 H8 T4096 (256) 123 / 108, 120 / 88
-//   more, short heads  B2 H20 T1024 (320) 44 / 56, 42 / 46; B2 H16 T1280 (320) 50 / 62, 48 / 47;
-//                      B3 H32 T512 (384) 39 / 48, 39 / 47; B1 H24 T2048 (384) 78 / 97, 68 / 70
-//   more, long heads   B1 H20 T2048 (320) 71 / 83, 68 / 58; B1 H16 T3072 (384) 105 / 128, 94 / 79;
-//                      B1 H12 T4096 (384) 138 / 164, 121 / 89; B1 H3 T16384 (384) 499 / 579, 439 / 318
-//   beyond             B1 H14 T4096 (448) 152 / 185, 121 / 105; B1 H16 T4096 (512) 172 / 209, 121 / 116
-constexpr long small_kv_grid(int nkb) { return std::clamp(64L + 16L * nkb, 256L, 384L); }
+// KS: strips per block, 4 or, in small grids, 2 (small_kv_grid()).
 template <int D, int KS> struct Dkv3Cfg {
     static constexpr int NW2 = 2 * KS;
     static constexpr int KEYS = 32 * KS;
@@ -2066,7 +2045,7 @@ hipError_t launch_one(const uint16_t* q, const uint16_t* k, const uint16_t* v, c
                 SB_LAUNCH(gk, 512, (bwd_dkv_pair_kernel<D, 4, GQAV, VL, false>),                                \
                           q, k, v, dout, ca, cb, dk, dv, first2, T, BHkv, H, G, nkb, nqb, nt32, cu, Ttot)       \
         }                                                                                                       \
-    } else if (blocks_k <= in_turn_grid(nkb)) {                                                                            \
+    } else if (take_in_turn(blocks_k, nkb, VL, mean_T, gk)) {                                                                            \
         SB_LAUNCH(gk, 2 * NTHREADS, (bwd_dkv_kernel<D, GQAV, VL, 2>),                                           \
                   q, k, v, dout, ca, cb, dk, dv, first2, T, BHkv, H, G, nkb, nt32, cu, Ttot, run_k);             \
     } else {                                                                                                    \

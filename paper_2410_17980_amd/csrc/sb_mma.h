@@ -14,7 +14,6 @@ typedef __attribute__((ext_vector_type(4))) unsigned int u32x4;
 
 #define SB_LDS(T, p) ((__attribute__((address_space(3))) T*)(p))
 
-constexpr long ONE_PER_CU = 256;          // workgroups of a launch that leaves none waiting for a CU
 
 constexpr float SB_LOG2E = 1.4426950408889634f;
 constexpr float SB_LN2 = 0.6931471805599453f;

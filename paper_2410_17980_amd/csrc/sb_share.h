@@ -127,6 +127,40 @@ inline bool small_fwd_grid(long strips, int T, long mean_T, int d)
     return T > (d == 32 ? 320 : 64) && long_enough(strips, T, mean_T) && T <= SMALL_T && strips <= limit;
 }
 
+// Grids of the key-stationary pass at d <= 64 whose blocks are taken by two groups of four waves (bwd_dkv_kernel<.., 2>): where a
+// block has a CU to itself anyway (one wave per SIMD issues an instruction every five clocks at best, two keep it busy), and
+// for some more blocks, of which few are left once some heads turn out near: what counts then is the longest block's chain.
+// One group / two, us, all heads far, then a third, then none:
+//   d = 64  B2 H24 T1024 (384 blocks, 8 a head) 39 / 33, 38 / 31, 23 / 27; B1 H32 T2011 (512, 16) 70 / 60, 68 / 53, 24 / 30;
+//           B1 H12 T4059 (384, 32) 131 / 98, 127 / 99, 23 / 27; B1 H16 T4096 (512, 32) 135 / 111, 134 / 100, 24 / 30
+//     not   B1 H48 T1499 (576, 12) 56 / 60, 54 / 44, 29 / 38; B1 H36 T2011 (576, 16) 72 / 74, 69 / 65, 29 / 38; B1 H24 T4096 (768, 32) 165 / 173,
+//           143 / 101, 33 / 42; B1 H30 T3500 (840, 28) 158 / 160, 129 / 158, 38 / 52; B1 H32 T4096 (1024, 32) 210 / 217, 153 / 112, 41 / 56;
+//           B8 H16 T512 (512, 4) 25 / 29, 24 / 29, 23 / 28
+//   d = 32  B1 H16 T4096 (512, 32) 115 / 92, 114 / 84, 17 / 20; B1 H32 T2011 (512, 16) 59 / 49, 58 / 44, 18 / 20
+//     not   B1 H24 T4096 (768, 32) 128 / 146, 122 / 84, 22 / 29; B1 H43 T3035 (1032, 24) 113 / 139, 86 / 75, 27 / 37
+// Up to 512 what near heads lose is half of what the others gain at most; beyond, where all heads reach far, it is slower as well.
+// In a packed batch (blocks: those that the sequences can hold; launched: with those that only max_T leaves room for) up to 384: four
+// of 800 to 4200 rows, H8 d64 (440) 247 / 304, 244 / 210, 50 / 69; 11 of 300 to 5000, H4 d64 (292) 362 / 284, 287 / 246, 47 / 53; 8 of 1000, H6 d64
+// (384) 71 / 67, 71 / 64, 44 / 49.  And not for many short ones: 64 of 32 rows, H4 d64, max_T 512 (320) 9.9 / 12.9, 2048 12.9 / 22.
+constexpr long ONE_PER_CU = 256;          // workgroups of a launch that leaves none waiting for a CU
+inline bool take_in_turn(long blocks, int nkb, bool packed, long mean_T, long launched)
+{
+    if (packed && (mean_T <= 64 || launched > 16 * ONE_PER_CU)) return launched <= ONE_PER_CU;
+    return blocks <= std::clamp(48L * nkb, ONE_PER_CU, packed ? 384L : 512L);
+}
+
+// Grids of the key-stationary pass at d = 128 that take 64 keys a block in place of 128: what bounds a launch there is one
+// block's chain of intervals, and with one wave per SIMD in place of two an interval is shorter.  Where the 128-key blocks
+// outnumber the CUs this costs more rounds than it saves, except with long chains and heads of mixed
+// reach.  Key-stationary pass with 128 / 64 keys a block, us, all heads far, then a third:
+//   up to 256 blocks   B1 H20 T1024 (160) 40 / 31, 40 / 31; B1 H16 T2048 (256) 69 / 64, 67 / 50;
+//                      B8 H16 T256 (256) 33 / 28, 33 / 27; B1 H8 T4096 (256) 123 / 108, 120 / 88
+//   more, short heads  B2 H20 T1024 (320) 44 / 56, 42 / 46; B2 H16 T1280 (320) 50 / 62, 48 / 47;
+//                      B3 H32 T512 (384) 39 / 48, 39 / 47; B1 H24 T2048 (384) 78 / 97, 68 / 70
+//   more, long heads   B1 H20 T2048 (320) 71 / 83, 68 / 58; B1 H16 T3072 (384) 105 / 128, 94 / 79;
+//                      B1 H12 T4096 (384) 138 / 164, 121 / 89; B1 H3 T16384 (384) 499 / 579, 439 / 318
+//   beyond             B1 H14 T4096 (448) 152 / 185, 121 / 105; B1 H16 T4096 (512) 172 / 209, 121 / 116
+constexpr long small_kv_grid(int nkb) { return std::clamp(64L + 16L * nkb, 256L, 384L); }
 // log2 of the run, -1: turn with every block.  A run pays where the launch is several rounds deep and
 // there are enough runs to even the XCDs out: 32 of them, or 16 where 64 heads and more can be turned
 // among each other as well, by o(o+1)/2 inside each octet o of heads (over any 8 octets these are all 8

@@ -26,10 +26,12 @@ int main()
             continue;
         }
         const long mean = mean_length(B, T, packed, Ttot);
-        printf("%d %d %d %ld\n", small_fwd_grid(pieces(B, H, T, 32, packed, Ttot), T, mean, d),
+        printf("%d %d %d %ld %d %d\n", small_fwd_grid(pieces(B, H, T, 32, packed, Ttot), T, mean, d),
                small_grid(pieces(B, H, T, 32, packed, Ttot), T, mean, d),
                small_grid(pieces(B, Hkv, T, 32, packed, Ttot), T, mean, d),
-               packed ? H * packed_places(B, Ttot) : (long)B * H * ((T + 31) / 32));
+               packed ? H * packed_places(B, Ttot) : (long)B * H * ((T + 31) / 32),
+               take_in_turn(pieces(B, Hkv, T, 128, packed, Ttot), (T + 127) / 128, packed, mean, (long)B * Hkv * ((T + 127) / 128)),
+               pieces(B, Hkv, T, 128, packed, Ttot) <= small_kv_grid((T + 127) / 128));
     }
 }
 """
@@ -94,6 +96,15 @@ def test_shapes_of_the_gpu_tests(ask):
                                 ([100] * 13, 4, 2, 1300)):
         for d in (32, 64, 128):
             assert ask([packed(lens, H, d, max_T, Hkv)])[0][:3] == (d > 32 or max_T > 320, 1, 1), (lens, d)
+
+
+def test_two_wave_groups(ask):
+    """Key-stationary pass at d <= 64: two groups only where neither near heads nor far ones lose more than a mix gains."""
+    for B, H, T, two in ((1, 8, 4096, 1), (2, 24, 1024, 1), (1, 16, 4096, 1), (1, 32, 2011, 1), (8, 16, 512, 0), (1, 40, 2048, 0), (1, 24, 4096, 0),
+                         (1, 30, 3500, 0), (1, 32, 4096, 0), (8, 16, 2048, 0)):
+        assert ask([(B, H, H, T, 64, 0, 0)])[0][4] == two, (B, H, T)
+    for lens, H, max_T, two in (([5000] + [300] * 10, 4, None, 1), ([4200] + [800] * 3, 8, None, 0), ([32] * 64, 4, 2048, 0), ([32] * 64, 4, 512, 0)):
+        assert ask([packed(lens, H, 64, max_T)])[0][4] == two, (H, max_T)
 
 
 def decode(B, H, Hkv, T, d, want_m=False):
