@@ -2001,11 +2001,9 @@ hipError_t launch_one(const uint16_t* q, const uint16_t* k, const uint16_t* v, c
     const uint32_t* first2 = reinterpret_cast<const uint32_t*>(first);     // of a tile's two strips
     float* part = reinterpret_cast<float*>(first + (long)BH * nqb * 4);
     const int nchunk = (T + DR_ROWS - 1) / DR_ROWS;
-    const bool pairs = D == 128 && !VL && G == 1 && take_pairs(BHkv, nkb);
-    const long gq = share_grid(BH, nqb, false), gk = share_grid(BHkv, nkb, pairs);
-    const long strips_q = pieces(B, H, T, 32, VL, Ttot), strips_k = pieces(B, Hkv, T, 32, VL, Ttot);
-    const long blocks_k = pieces(B, Hkv, T, BKW, VL, Ttot);
-    const long mean_T = mean_length(B, T, VL, Ttot), places = VL ? packed_places(B, Ttot) : nt32;
+    const Keys keys = keys_of(B, H, Hkv, T, D, VL, Ttot);
+    const long gq = share_grid(BH, nqb, false), gk = share_grid(BHkv, nkb, keys == Keys::PAIRS);
+    const long places = VL ? packed_places(B, Ttot) : nt32;
     const int run_q = VL || G > 1 ? -1 : share_run(BH, nqb), run_k = VL || G > 1 ? -1 : share_run(BHkv, nkb);
     // checked before the first launch, so that an error leaves nothing enqueued
     if (gq > 0x7fffffffL || gk > 0x7fffffffL || nchunk * (long)BH > 0x7fffffffL) return hipErrorInvalidValue;
@@ -2018,7 +2016,7 @@ hipError_t launch_one(const uint16_t* q, const uint16_t* k, const uint16_t* v, c
     if (e != hipSuccess) return e;                                                                              \
     }
 #define SB_DQ(RBV)                                                                                              \
-    if (small_grid(strips_q, T, mean_T, D)) {                                                                   \
+    if (query_strips(B, H, T, D, VL, Ttot)) {                                                                   \
         hipLaunchKernelGGL((bwd_dq_small_kernel<D>), dim3((unsigned)((VL ? H : BH) * places)), dim3(64 * SmallCfg<D>::NWS), 0, stream, \
                            q, k, v, rb, m, dout, dq, ca, cb, first, T, VL ? H : BH, H, G, VL ? B : nt32, nqb, nt32, cu, Ttot); \
         if ((e = hipGetLastError()) != hipSuccess) return e;                                                    \
@@ -2028,29 +2026,27 @@ hipError_t launch_one(const uint16_t* q, const uint16_t* k, const uint16_t* v, c
 // dimensions leave room for two workgroups of the one-wave-per-strip kernel per CU, which
 // is faster there (measured).
 #define SB_DKV(GQAV)                                                                                            \
-    if (small_grid(strips_k, T, mean_T, D)) {                                                                   \
+    if (keys == Keys::STRIPS) {                                                                                 \
         hipLaunchKernelGGL((bwd_dkv_small_kernel<D>), dim3((unsigned)((VL ? Hkv : BHkv) * places)), dim3(64 * SmallCfg<D>::NWS), 0, stream, \
                            q, k, v, dout, ca, cb, dk, dv, first, T, VL ? Hkv : BHkv, H, G, VL ? B : nt32, nqb, nt32, cu, Ttot); \
         if ((e = hipGetLastError()) != hipSuccess) return e;                                                    \
     } else if constexpr (D == 128) {                                                                            \
-        if (blocks_k <= small_kv_grid(nkb)) {                                                         \
-            SB_LAUNCH(share_grid(BHkv, nkb64, false), 256, (bwd_dkv_pair_kernel<D, 2, GQAV, VL, false>),               \
-                      q, k, v, dout, ca, cb, dk, dv, first2, T, BHkv, H, G, nkb64, nqb, nt32, cu, Ttot);      \
-        } else {                                                                                                \
-            constexpr bool CAN = !VL && !GQAV;                                                                  \
-            if (CAN && pairs)                                                                                   \
-                SB_LAUNCH(gk, 512, (bwd_dkv_pair_kernel<D, 4, GQAV, VL, CAN>),                                  \
-                          q, k, v, dout, ca, cb, dk, dv, first2, T, BHkv, H, G, nkb, nqb, nt32, cu, Ttot)       \
-            else                                                                                                \
-                SB_LAUNCH(gk, 512, (bwd_dkv_pair_kernel<D, 4, GQAV, VL, false>),                                \
-                          q, k, v, dout, ca, cb, dk, dv, first2, T, BHkv, H, G, nkb, nqb, nt32, cu, Ttot)       \
-        }                                                                                                       \
-    } else if (take_in_turn(blocks_k, nkb, VL, mean_T, gk)) {                                                                            \
+        constexpr bool CAN = !VL && !GQAV;                                                                      \
+        if (keys == Keys::KEYS_64)                                                                              \
+            SB_LAUNCH(share_grid(BHkv, nkb64, false), 256, (bwd_dkv_pair_kernel<D, 2, GQAV, VL, false>),        \
+                      q, k, v, dout, ca, cb, dk, dv, first2, T, BHkv, H, G, nkb64, nqb, nt32, cu, Ttot)         \
+        else if (CAN && keys == Keys::PAIRS)                                                                    \
+            SB_LAUNCH(gk, 512, (bwd_dkv_pair_kernel<D, 4, GQAV, VL, CAN>),                                      \
+                      q, k, v, dout, ca, cb, dk, dv, first2, T, BHkv, H, G, nkb, nqb, nt32, cu, Ttot)           \
+        else                                                                                                    \
+            SB_LAUNCH(gk, 512, (bwd_dkv_pair_kernel<D, 4, GQAV, VL, false>),                                    \
+                      q, k, v, dout, ca, cb, dk, dv, first2, T, BHkv, H, G, nkb, nqb, nt32, cu, Ttot)           \
+    } else if (keys == Keys::TWO_GROUPS) {                                                                      \
         SB_LAUNCH(gk, 2 * NTHREADS, (bwd_dkv_kernel<D, GQAV, VL, 2>),                                           \
-                  q, k, v, dout, ca, cb, dk, dv, first2, T, BHkv, H, G, nkb, nt32, cu, Ttot, run_k);             \
+                  q, k, v, dout, ca, cb, dk, dv, first2, T, BHkv, H, G, nkb, nt32, cu, Ttot, run_k);            \
     } else {                                                                                                    \
         SB_LAUNCH(gk, NTHREADS, (bwd_dkv_kernel<D, GQAV, VL, 1>),                                               \
-                  q, k, v, dout, ca, cb, dk, dv, first2, T, BHkv, H, G, nkb, nt32, cu, Ttot, run_k);             \
+                  q, k, v, dout, ca, cb, dk, dv, first2, T, BHkv, H, G, nkb, nt32, cu, Ttot, run_k);            \
     }
     if (passes & 1) {
         if (rb) { SB_DQ(true); }

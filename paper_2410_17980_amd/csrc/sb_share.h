@@ -161,6 +161,27 @@ inline bool take_in_turn(long blocks, int nkb, bool packed, long mean_T, long la
 //                      B1 H12 T4096 (384) 138 / 164, 121 / 89; B1 H3 T16384 (384) 499 / 579, 439 / 318
 //   beyond             B1 H14 T4096 (448) 152 / 185, 121 / 105; B1 H16 T4096 (512) 172 / 209, 121 / 116
 constexpr long small_kv_grid(int nkb) { return std::clamp(64L + 16L * nkb, 256L, 384L); }
+// The kernels of the backward's passes.
+inline bool query_strips(int B, int H, int T, int d, bool packed, int Ttot)
+{
+    return small_grid(pieces(B, H, T, 32, packed, Ttot), T, mean_length(B, T, packed, Ttot), d);
+}
+enum class Keys {
+    STRIPS,                               // bwd_dkv_small_kernel
+    ONE_GROUP, TWO_GROUPS,                // bwd_dkv_kernel, d <= 64
+    KEYS_64, KEYS_128, PAIRS,             // bwd_dkv_pair_kernel, d = 128
+};
+inline Keys keys_of(int B, int H, int Hkv, int T, int d, bool packed, int Ttot)
+{
+    const long mean_T = mean_length(B, T, packed, Ttot), heads = (long)B * Hkv;
+    const int nkb = (T + 127) / 128;
+    const long blocks = pieces(B, Hkv, T, 128, packed, Ttot);
+    if (small_grid(pieces(B, Hkv, T, 32, packed, Ttot), T, mean_T, d)) return Keys::STRIPS;
+    if (d < 128) return take_in_turn(blocks, nkb, packed, mean_T, heads * nkb) ? Keys::TWO_GROUPS : Keys::ONE_GROUP;
+    if (blocks <= small_kv_grid(nkb)) return Keys::KEYS_64;
+    return !packed && H == Hkv && take_pairs(heads, nkb) ? Keys::PAIRS : Keys::KEYS_128;
+}
+
 // log2 of the run, -1: turn with every block.  A run pays where the launch is several rounds deep and
 // there are enough runs to even the XCDs out: 32 of them, or 16 where 64 heads and more can be turned
 // among each other as well, by o(o+1)/2 inside each octet o of heads (over any 8 octets these are all 8

@@ -119,8 +119,10 @@ def test_backward_far_queries_come_back(sb, oracle, gen, d):
 
 @pytest.mark.parametrize("H,Hkv,T,d", [(6, 3, 256, 128), (6, 3, 257, 64), (34, 2, 600, 32), (12, 3, 1536, 128), (12, 3, 1537, 128),
                                        (6, 3, 1793, 64), (3, 3, 2048, 32), (51, 3, 3000, 64), (3, 3, 33025, 128),
-                                       # spread over the chip beyond 512 keys and up to 34 MB in all
+                                       # spread over the chip with m beyond 512 keys; without it from 513, 1025 or 1281 keys on at
+                                       # d = 128, 64, 32; both up to 34 MB in all
                                        (6, 3, 512, 128), (34, 2, 513, 64), (6, 3, 513, 128), (51, 3, 1025, 32),
+                                       (34, 2, 1024, 64), (6, 3, 1025, 64), (34, 2, 1280, 32), (51, 3, 1281, 32),
                                        (6, 3, 24001, 128), (51, 3, 46000, 64), (6, 6, 47000, 32)])
 def test_decode(sb, oracle, gen, H, Hkv, T, d):
     """Caches at the edges of the passes and of the ways to split them, groups of 1 to 17 heads; without m

@@ -7,6 +7,8 @@ import subprocess
 
 import pytest
 
+import block_shapes
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_2410_17980_amd", "csrc")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -25,13 +27,9 @@ int main()
             printf("%d %d %d %d\n", s.near, s.C, s.nfar, room(T));
             continue;
         }
-        const long mean = mean_length(B, T, packed, Ttot);
-        printf("%d %d %d %ld %d %d\n", small_fwd_grid(pieces(B, H, T, 32, packed, Ttot), T, mean, d),
-               small_grid(pieces(B, H, T, 32, packed, Ttot), T, mean, d),
-               small_grid(pieces(B, Hkv, T, 32, packed, Ttot), T, mean, d),
-               packed ? H * packed_places(B, Ttot) : (long)B * H * ((T + 31) / 32),
-               take_in_turn(pieces(B, Hkv, T, 128, packed, Ttot), (T + 127) / 128, packed, mean, (long)B * Hkv * ((T + 127) / 128)),
-               pieces(B, Hkv, T, 128, packed, Ttot) <= small_kv_grid((T + 127) / 128));
+        printf("%d %d %ld %d\n", small_fwd_grid(pieces(B, H, T, 32, packed, Ttot), T, mean_length(B, T, packed, Ttot), d),
+               query_strips(B, H, T, d, packed, Ttot), packed ? H * packed_places(B, Ttot) : (long)B * H * ((T + 31) / 32),
+               (int)keys_of(B, H, Hkv, T, d, packed, Ttot));
     }
 }
 """
@@ -57,6 +55,15 @@ def packed(lens, H, d, max_T=None, Hkv=None):
     return (len(lens), H, Hkv or H, max_T or max(lens), d, 1, sum(lens))
 
 
+KEYS = ("strips", "one group", "two groups", "64 keys", "128 keys", "pairs")
+
+
+def strips(ask, row):
+    """Whether the forward, the query-stationary and the key-stationary pass take a strip a workgroup."""
+    fwd, dq, _, keys = ask([row])[0]
+    return bool(fwd), bool(dq), KEYS[keys] == "strips"
+
+
 def test_packed_strips_are_counted_and_launched_as_they_exist(ask):
     """However loose max_T is: no more workgroups than strips and one per sequence and head."""
     rng = random.Random(3)
@@ -68,18 +75,18 @@ def test_packed_strips_are_counted_and_launched_as_they_exist(ask):
             rows.append(packed(lens, H, 64, max_T))
             least.append(H * sum((n + 31) // 32 for n in lens))
     for row, strips, got in zip(rows, least, ask(rows)):
-        assert strips <= got[3] <= strips + row[0] * row[1]
+        assert strips <= got[2] <= strips + row[0] * row[1]
 
 
 def test_short_sequences_keep_the_blocks(ask):
     """64 sequences of 32 rows: a strip a workgroup is slower, whatever max_T says."""
     for H, d, max_T in ((4, 64, 65), (4, 64, 512), (4, 64, 2048), (4, 32, 2048), (8, 128, 512)):
-        assert ask([packed([32] * 64, H, d, max_T)])[0][:3] == (0, 0, 0), (H, d, max_T)
-    assert ask([packed([70] * 100, 1, 64, 400)])[0][:3] == (0, 0, 0)
+        assert not any(strips(ask, packed([32] * 64, H, d, max_T))), (H, d, max_T)
+    assert not any(strips(ask, packed([70] * 100, 1, 64, 400)))
     # one of 600 rows among short ones, a place on the chip for every strip; and ordinary lengths, loose max_T
-    assert ask([packed([600] + [20] * 30, 2, 128)])[0][:3] == (1, 1, 1)
+    assert all(strips(ask, packed([600] + [20] * 30, 2, 128)))
     for max_T in (100, 300, 1300):
-        assert ask([packed([100] * 13, 4, 64, max_T)])[0][:3] == (1, 1, 1)
+        assert all(strips(ask, packed([100] * 13, 4, 64, max_T)))
 
 
 def test_equal_lengths_take_the_route_of_the_batched_call(ask):
@@ -87,7 +94,7 @@ def test_equal_lengths_take_the_route_of_the_batched_call(ask):
     shapes = [(rng.randrange(1, 9), rng.randrange(1, 25), rng.randrange(1, 4200), rng.choice((32, 64, 128))) for _ in range(400)]
     batched = ask([(B, H, H, T, d, 0, 0) for B, H, T, d in shapes])
     for shape, a, b in zip(shapes, batched, ask([(B, H, H, T, d, 1, B * T) for B, H, T, d in shapes])):
-        assert a[:3] == b[:3], shape
+        assert a[:2] == b[:2] and (KEYS[a[3]] == "strips") == (KEYS[b[3]] == "strips"), shape
 
 
 def test_shapes_of_the_gpu_tests(ask):
@@ -95,16 +102,29 @@ def test_shapes_of_the_gpu_tests(ask):
     for lens, H, Hkv, max_T in (([0] * 3 + [1, 33] * 32 + [0, 300, 31], 2, 2, 300), ([2, 0, 34] * 21 + [1, 400] + [0] * 70, 1, 1, 400),
                                 ([100] * 13, 4, 2, 1300)):
         for d in (32, 64, 128):
-            assert ask([packed(lens, H, d, max_T, Hkv)])[0][:3] == (d > 32 or max_T > 320, 1, 1), (lens, d)
+            assert strips(ask, packed(lens, H, d, max_T, Hkv)) == (d > 32 or max_T > 320, True, True), (lens, d)
+
+
+def test_block_shapes(ask):
+    """test_gpu_blocks.py: every shape takes the kernels that it names."""
+    rows = [packed(lens, H, d, T, Hkv) if lens else (B, H, Hkv, T, d, 0, 0) for B, H, Hkv, T, d, lens, _, _ in block_shapes.ALL]
+    for shape, (_, dq, _, keys) in zip(block_shapes.ALL, ask(rows)):
+        assert ("strips" if dq else "blocks", KEYS[keys]) == shape[6:], shape
+    import test_gpu_blocks
+    rest = [s[:5] + (0, 0) for s in test_gpu_blocks.random_shapes()] + \
+           [(1, H, H, T, d, 0, 0) for H, T, d in ((19, 1300, 64), (48, 1300, 64), (19, 1300, 32), (7, 1300, 128), (28, 1300, 128),
+                                                  (24, 333, 128), (66, 449, 64), (30, 1300, 32), (128, 449, 128))]
+    for row, (_, dq, _, keys) in zip(rest, ask(rest)):
+        assert not dq and KEYS[keys] != "strips", row
 
 
 def test_two_wave_groups(ask):
     """Key-stationary pass at d <= 64: two groups only where neither near heads nor far ones lose more than a mix gains."""
-    for B, H, T, two in ((1, 8, 4096, 1), (2, 24, 1024, 1), (1, 16, 4096, 1), (1, 32, 2011, 1), (8, 16, 512, 0), (1, 40, 2048, 0), (1, 24, 4096, 0),
-                         (1, 30, 3500, 0), (1, 32, 4096, 0), (8, 16, 2048, 0)):
-        assert ask([(B, H, H, T, 64, 0, 0)])[0][4] == two, (B, H, T)
-    for lens, H, max_T, two in (([5000] + [300] * 10, 4, None, 1), ([4200] + [800] * 3, 8, None, 0), ([32] * 64, 4, 2048, 0), ([32] * 64, 4, 512, 0)):
-        assert ask([packed(lens, H, 64, max_T)])[0][4] == two, (H, max_T)
+    for B, H, T, want in ((2, 24, 1024, 2), (1, 16, 4096, 2), (1, 32, 2011, 2), (8, 16, 512, 1), (1, 40, 2048, 1), (1, 24, 4096, 1),
+                          (1, 30, 3500, 1), (1, 32, 4096, 1), (8, 16, 2048, 1)):
+        assert ask([(B, H, H, T, 64, 0, 0)])[0][3] == want, (B, H, T)
+    for lens, H, max_T, want in (([5000] + [300] * 10, 4, None, 2), ([4200] + [800] * 3, 8, None, 1), ([32] * 64, 4, 2048, 1), ([32] * 64, 4, 512, 1)):
+        assert ask([packed(lens, H, 64, max_T)])[0][3] == want, (H, max_T)
 
 
 def decode(B, H, Hkv, T, d, want_m=False):
@@ -130,6 +150,9 @@ def test_decode_routes(ask):
     for name, shapes in want.items():
         rows = [decode(*s) for s in shapes]
         assert [kind(r, g) for r, g in zip(rows, ask(rows))] == [name] * len(rows), name
+    for T, d in ((513, 128), (1025, 64), (1281, 32)):                        # test_gpu_exhausted.py, test_decode
+        rows = [decode(1, 34, 2, T - 1, d), decode(1, 34, 2, T, d)]
+        assert [kind(r, g) for r, g in zip(rows, ask(rows))] == [ONE, SPREAD]
     rows = [decode(B, H, Hkv, T, d, True) for B, H, Hkv, T, d in ((5, 30, 10, 588, 64), (5, 30, 10, 1000, 64), (2, 8, 8, 1000, 32), (2, 16, 16, 4000, 128))]
     assert all(kind(r, g) == SPREAD for r, g in zip(rows, ask(rows)))
 
