@@ -1615,11 +1615,8 @@ bwd_dq_small_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
     }
     barrier_lds();
     const int start = __builtin_amdgcn_readfirstlane(s_start);
-    if (wave == 0 && lane < 4) {
-        // the strips of the last block that do not exist share the last one's
-        const int s4 = lane, at = strip & ~3;
-        if (at + s4 == strip || (strip == nstrip - 1 && at + s4 > strip)) first[(long)bh * nqb_arg * 4 + at + s4] = (uint16_t)start;
-    }
+    // (where this pass takes strips the key-stationary one does too, so that nobody reads the places of strips that do not exist)
+    if (tid == 0) first[(long)bh * nqb_arg * 4 + strip] = (uint16_t)start;
 
     // ---- the sweep
     f32x16 dqacc[D / 32];
@@ -1700,7 +1697,7 @@ bwd_dq_small_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
     }
 }
 
-// Key-stationary pass at d <= 64: a strip of 32 keys a workgroup, whose waves take its query subtiles (of all
+// Key-stationary pass: a strip of 32 keys a workgroup, whose waves take its query subtiles (of all
 // query heads of the group) in turn and add their accumulators up at the end.
 template <int D>
 __global__ void __launch_bounds__(64 * SmallCfg<D>::NWS)

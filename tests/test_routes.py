@@ -118,6 +118,21 @@ def test_block_shapes(ask):
         assert not dq and KEYS[keys] != "strips", row
 
 
+def test_strips_of_queries_come_with_strips_of_keys(ask):
+    """bwd_dq_small_kernel leaves starts for the strips that exist alone, which is what bwd_dkv_small_kernel reads;
+    the block kernels read whole blocks of four."""
+    rng = random.Random(6)
+    rows = []
+    for _ in range(4000):
+        Hkv, T, B = rng.randrange(1, 25), round(2 ** rng.uniform(0, 13)), rng.randrange(1, 40)
+        is_packed = rng.random() < 0.5
+        rows.append((B, Hkv * rng.randrange(1, 9), Hkv, T, rng.choice((32, 64, 128)), is_packed, rng.randrange(1, 1 + B * T) if is_packed else 0))
+    got = ask(rows)
+    assert any(dq for _, dq, _, _ in got)
+    for row, (_, dq, _, keys) in zip(rows, got):
+        assert not dq or KEYS[keys] == "strips", row
+
+
 def test_two_wave_groups(ask):
     """Key-stationary pass at d <= 64: two groups only where neither near heads nor far ones lose more than a mix gains."""
     for B, H, T, want in ((2, 24, 1024, 2), (1, 16, 4096, 2), (1, 32, 2011, 2), (8, 16, 512, 1), (1, 40, 2048, 1), (1, 24, 4096, 1),
