@@ -8,7 +8,7 @@ import torch
 
 import block_shapes
 from helpers import GRAD_REL, check_grad, check_m, dev, fwd_bound, nan_bytes, to64
-from test_gpu_exhausted import gen, mixed_grouped, sb  # noqa: F401  (fixtures)
+from test_gpu_exhausted import gen, mixed, mixed_grouped, sb  # noqa: F401  (fixtures)
 
 pytestmark = pytest.mark.gpu
 
@@ -161,3 +161,18 @@ def test_split_passes_equal_the_whole(sb, gen, H, T, d):
     dq, ws = sb.sb_attn_bwd_dq(q, k, v, m, g)
     for a, b in zip((dq, *sb.sb_attn_bwd_dkdv(q, k, v, g, ws)), want):
         assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("T", [257, 320, 353, 385, 449, 577, 641, 1283])
+@pytest.mark.parametrize("d", [32, 64, 128])
+def test_forward_and_m_of_short_tails(sb, oracle, gen, T, d):
+    """The lengths and the bound on m of test_gpu_exhausted.py, where the forward takes blocks of 128 rows."""
+    H = block_shapes.above(512, block_shapes.strips(T))
+    q, k, v = mixed(gen, 1, H, T, d, seed=900 + T)
+    o, m = sb.sb_attn_fwd_train(*dev(q, k, v))
+    for h in some(H):
+        q64, k64, v64 = (to64(t[0, h]) for t in (q, k, v))
+        ref = -np.tril(np.logaddexp(0.0, q64 @ k64.T / np.sqrt(d)), -1).sum(-1)
+        assert np.all(np.abs(to64(m[0, h]) - ref) <= 1e-4 + 1e-5 * np.abs(ref))
+        ref, _ = oracle.fwd(q64, k64, v64)
+        assert np.all(np.abs(to64(o[0, h]) - ref) <= fwd_bound(ref, v64))

@@ -104,3 +104,38 @@ def test_decode(sb, gen, want_m):
         for h in (0, 1):
             assert not torch.isfinite(b[0, h, 5]) or (h not in reach and torch.equal(a[0, h], b[0, h]))
             assert torch.equal(a[0, h, :5], b[0, h, :5]) and torch.equal(a[0, h, 6:], b[0, h, 6:])
+
+
+class Many:
+    """The library with every call's two heads `times` over, so that a call takes the kernels of larger grids: results of
+    the first two, those of the last two the same bit for bit."""
+    def __init__(self, sb, times):
+        self.sb, self.times = sb, times
+
+    def __getattr__(self, name):
+        def call(*tensors):
+            out = getattr(self.sb, name)(*(t.repeat(*((self.times, 1) if t.dim() == 2 else (1, self.times) + (1,) * (t.dim() - 2))) for t in tensors))
+            return tuple(map(self.two, out)) if isinstance(out, tuple) else self.two(out)
+        return call
+
+    def two(self, x):
+        heads = (lambda a, b: x[a:b]) if x.dim() == 2 else (lambda a, b: x[:, a:b].contiguous())
+        first, last = heads(None, 2), heads(-2, None)
+        assert torch.equal(first.isfinite(), last.isfinite()) and torch.equal(first.nan_to_num(), last.nan_to_num())
+        return first
+
+
+# (d, times over, key-stationary pass); the other passes take blocks of 128 rows.  test_routes.py asks the library's rules
+GRIDS = [(32, 9, "two groups"), (32, 22, "one group"), (64, 9, "two groups"), (64, 22, "one group"),
+         (128, 9, "64 keys"), (128, 17, "128 keys"), (128, 64, "pairs")]
+
+
+@pytest.mark.parametrize("value", [float("nan"), float("inf")])
+@pytest.mark.parametrize("d", [32, 64, 128])
+def test_forward_blocks(sb, gen, d, value):
+    test_forward(Many(sb, GRIDS[0][1]), gen, d, value)
+
+
+@pytest.mark.parametrize("d,times", [g[:2] for g in GRIDS])
+def test_backward_blocks(sb, gen, d, times):
+    test_backward(Many(sb, times), gen, d)

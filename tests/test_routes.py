@@ -116,6 +116,12 @@ def test_block_shapes(ask):
                                                   (24, 333, 128), (66, 449, 64), (30, 1300, 32), (128, 449, 128))]
     for row, (_, dq, _, keys) in zip(rest, ask(rest)):
         assert not dq and KEYS[keys] != "strips", row
+    import test_gpu_nonfinite as nonfinite
+    rows = [(1, 2 * n, 2 * n, nonfinite.T, d, 0, 0) for d, n, _ in nonfinite.GRIDS]
+    assert [(fwd, dq, KEYS[keys]) for fwd, dq, _, keys in ask(rows)] == [(0, 0, g[2]) for g in nonfinite.GRIDS]
+    rows = [(1, H, H, T, d, 0, 0) for T in (257, 320, 353, 385, 449, 577, 641, 1283) for d in (32, 64, 128)
+            for H in [block_shapes.above(512, block_shapes.strips(T))]]
+    assert not any(fwd for fwd, _, _, _ in ask(rows))
 
 
 def test_strips_of_queries_come_with_strips_of_keys(ask):
