@@ -1504,12 +1504,11 @@ bwd_dq_small_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
     long row0 = bh * (long)T, kvrow0 = (long)(G == 1 ? bh : (int)((unsigned)bh / (unsigned)G)) * T;
     long cbase = (long)bh * nt32 * T, cstride = T;
     if (cu) {                                           // packed batch: sh.bh is the head alone, sh.i its place
-        const Place at = place_of(sh.i, cu, n_arg, lane);
-        T = min(min(at.c1, Ttot) - at.c0, T_arg);
-        if (at.c0 < 0) return;
+        const Place at = place_of(sh.i, cu, n_arg, Ttot, T_arg, lane);
+        if (at.T == 0) return;
+        T = at.T;
         nstrip = (T + 31) / 32;
         i = at.i;
-        if (i < 0 || i >= nstrip) return;
         bh = at.seq * H + head;
         row0 = (long)head * Ttot + at.c0;
         kvrow0 = (long)(head / G) * Ttot + at.c0;
@@ -1720,14 +1719,13 @@ bwd_dkv_small_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict_
     KvHead kh;
     int ks = sh.i;                                       // the strip; small ones have the most queries
     if (cu) {                                            // packed batch: sh.bh is the head alone, sh.i its place
-        const Place at = place_of(sh.i, cu, n_arg, lane);
-        if (!packed_kv_head<D>(kh, at.seq, sh.bh, at.c0, at.c1, T_arg, 32, H, G, nt32, Ttot)) return;
+        const Place at = place_of(sh.i, cu, n_arg, Ttot, T_arg, lane);
+        if (at.T == 0) return;
+        packed_kv_head<D>(kh, at.seq, sh.bh, at.c0, at.c0 + at.T, T_arg, 32, H, G, nt32, Ttot);
         ks = at.i;
-        if (ks < 0) return;
     } else {
         kv_head<D, false>(kh, sh.bh, T_arg, n_arg, 32, H, G, nt32, cu, Ttot);
     }
-    if (ks >= kh.nkb) return;
     const int T = kh.T, nstrip = kh.nkb;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n = lane & 31, hh = lane >> 5, gg = lane >> 4, li = lane & 15;
@@ -2000,7 +1998,7 @@ hipError_t launch_one(const uint16_t* q, const uint16_t* k, const uint16_t* v, c
     const int nchunk = (T + DR_ROWS - 1) / DR_ROWS;
     const Keys keys = keys_of(B, H, Hkv, T, D, VL, Ttot);
     const long gq = share_grid(BH, nqb, false), gk = share_grid(BHkv, nkb, keys == Keys::PAIRS);
-    const long places = VL ? packed_places(B, Ttot) : nt32;
+    const long strips_q = pieces(B, H, T, 32, VL, Ttot), strips_k = pieces(B, Hkv, T, 32, VL, Ttot);
     const int run_q = VL || G > 1 ? -1 : share_run(BH, nqb), run_k = VL || G > 1 ? -1 : share_run(BHkv, nkb);
     // checked before the first launch, so that an error leaves nothing enqueued
     if (gq > 0x7fffffffL || gk > 0x7fffffffL || nchunk * (long)BH > 0x7fffffffL) return hipErrorInvalidValue;
@@ -2014,7 +2012,7 @@ hipError_t launch_one(const uint16_t* q, const uint16_t* k, const uint16_t* v, c
     }
 #define SB_DQ(RBV)                                                                                              \
     if (query_strips(B, H, T, D, VL, Ttot)) {                                                                   \
-        hipLaunchKernelGGL((bwd_dq_small_kernel<D>), dim3((unsigned)((VL ? H : BH) * places)), dim3(64 * SmallCfg<D>::NWS), 0, stream, \
+        hipLaunchKernelGGL((bwd_dq_small_kernel<D>), dim3((unsigned)strips_q), dim3(64 * SmallCfg<D>::NWS), 0, stream, \
                            q, k, v, rb, m, dout, dq, ca, cb, first, T, VL ? H : BH, H, G, VL ? B : nt32, nqb, nt32, cu, Ttot); \
         if ((e = hipGetLastError()) != hipSuccess) return e;                                                    \
     } else SB_LAUNCH(gq, NTHREADS, (bwd_dq_kernel<D, RBV, VL>),                                                        \
@@ -2024,7 +2022,7 @@ hipError_t launch_one(const uint16_t* q, const uint16_t* k, const uint16_t* v, c
 // is faster there (measured).
 #define SB_DKV(GQAV)                                                                                            \
     if (keys == Keys::STRIPS) {                                                                                 \
-        hipLaunchKernelGGL((bwd_dkv_small_kernel<D>), dim3((unsigned)((VL ? Hkv : BHkv) * places)), dim3(64 * SmallCfg<D>::NWS), 0, stream, \
+        hipLaunchKernelGGL((bwd_dkv_small_kernel<D>), dim3((unsigned)strips_k), dim3(64 * SmallCfg<D>::NWS), 0, stream, \
                            q, k, v, dout, ca, cb, dk, dv, first, T, VL ? Hkv : BHkv, H, G, VL ? B : nt32, nqb, nt32, cu, Ttot); \
         if ((e = hipGetLastError()) != hipSuccess) return e;                                                    \
     } else if constexpr (D == 128) {                                                                            \

@@ -661,12 +661,11 @@ fwd_small_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     int T = T_arg, nstrip = n_arg, i = sh.i;
     long row0 = bh * (long)T, kvrow0 = (long)(G == 1 ? bh : (int)((unsigned)bh / (unsigned)G)) * T;
     if (cu) {                                           // packed batch: bh is the head alone, sh.i its place
-        const Place at = place_of(sh.i, cu, n_arg, lane);
-        T = min(min(at.c1, Ttot) - at.c0, T_arg);
-        if (at.c0 < 0) return;
+        const Place at = place_of(sh.i, cu, n_arg, Ttot, T_arg, lane);
+        if (at.T == 0) return;
+        T = at.T;
         nstrip = (T + 31) / 32;
         i = at.i;
-        if (i < 0 || i >= nstrip) return;
         row0 = (long)head * Ttot + at.c0;
         kvrow0 = (long)(head / G) * Ttot + at.c0;
     }
@@ -831,10 +830,10 @@ hipError_t launch_one(const uint16_t* q, const uint16_t* k, const uint16_t* v, c
                       unsigned long long* tile_counts, hipStream_t stream,
                       const int* cu = nullptr, int Ttot = 0)
 {
-    const bool small = small_fwd_grid(pieces(BH / H, H, T, 32, VL, Ttot), T, mean_length(BH / H, T, VL, Ttot), D);
-    if (!TRI && enough == CARRY_EXHAUSTED && (WRITE_M || !tile_counts) && small) {     // halting sweeps stop by blocks
+    const long strips = pieces(BH / H, H, T, 32, VL, Ttot);
+    if (!TRI && enough == CARRY_EXHAUSTED && (WRITE_M || !tile_counts) && small_fwd_grid(strips, T, D)) {     // halting sweeps stop by blocks
         const int heads = VL ? H : BH, n = VL ? BH / H : (T + 31) / 32;
-        hipLaunchKernelGGL((fwd_small_kernel<D>), dim3((unsigned)(heads * (VL ? packed_places(n, Ttot) : n))), dim3(64 * FwdSmallCfg<D>::NWS), 0, stream,
+        hipLaunchKernelGGL((fwd_small_kernel<D>), dim3((unsigned)strips), dim3(64 * FwdSmallCfg<D>::NWS), 0, stream,
                            q, k, v, rb, o, m, T, heads, H, G, n, tile_counts, cu, Ttot);
         return hipGetLastError();
     }

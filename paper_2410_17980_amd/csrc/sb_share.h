@@ -45,36 +45,23 @@ inline bool take_pairs(long heads, int nblk)
     return 32 * idle <= n;
 }
 
-// Of a packed batch the host knows how many sequences of how many rows in all, and T, at least the longest one's length and
-// perhaps far more.  mean_T: the sequences' mean length (T itself in a batched call).  Strips are for chains that count:
-//   not where the mean is 64 rows or less, unless there is a place on the chip for every strip and T leaves room for
-//   a long one.  Blocks / strips, us, forward, then backward: 64 sequences of 32 rows, H4 d64 (512 places), T 128 to 512
-//   3.8 / 8.2, 10 / 26; H2 d128 (256) 4.5 / 5.3, 12.5 / 17.8; but one of 600 and 30 of 20 rows, H2 d128 (136) 14.3 / 9.1, 32 / 24;
-//   below 512 with the limit of three times the mean: 100 of 70 rows, H1 d64 (318), T 400 5.2 / 8.3, 14.9 / 25.
-inline long mean_length(int B, int T, bool packed, int Ttot) { return packed ? ((long)Ttot + B - 1) / B : T; }
-inline bool long_enough(long strips, int T, long mean_T)
-{
-    return mean_T <= T && (mean_T > 64 || (T >= 256 && strips <= 256));
-}
-inline long chain_length(int T, long mean_T) { return T < 512 ? std::min((long)T, 3 * mean_T) : T; }
-
 // Grids of the backward that take one strip of 32 rows a workgroup, its waves sharing the strip's other side
 // (bwd_dq_small_kernel, bwd_dkv_small_kernel), in place of 128-row blocks whose every wave has the
 // whole other side to itself.  What bounds the blocks there is one chain, what bounds the strips from a round or two of the
 // chip on is their tiles, which no other wave shares.  Blocks / strips, us, query-stationary, then key-stationary:
 //   B2 H4 T777 d32 (200 strips) 19.1 / 10.9, 19.2 / 7.7; B1 H4 T4000 d64 (500) 98 / 50, 96 / 38;
-//   B1 H12 T2000 d64 (756) 52 / 48, 52 / 37; B2 H12 T1000 d32 (768) 24.7 / 24.2, 24.2 / 18.0;
+//   B1 H12 T2000 d64 (756) 52 / 48, 52 / 37;
 //   B1 H8 T700 d128 (176) 28 / 21.5, 24.4 / 17.9; B1 H16 T500 d128 (256) 23 / 16.7, 21 / 15.2;
 //   B1 H16 T100 d64 (64) 6.9 / 6.3, 8.2 / 6.5; both B1 H6 Hkv2 T4000 d32 320 / 125
 // and not B4 H8 T700 d64 (704) 21.5 / 25.9, 23.2 / 23.2; B4 H16 T300 d64 (640) 11.6 / 19.9, 14.4 / 19.2;
 // B1 H24 T1000 d128 (768) 40 / 55; B1 H4 T64 d64 5.0 / 6.1, 6.4 / 6.3.  (All heads far; where they are near the
-// strips gain more.)  4096: the kernels' arrays hold 128 strips.
+// strips gain more.)  One line serves both passes and, below d = 128, both head sizes: B2 H12 T1000 d32 (768), just beyond it,
+// would gain too, 24.7 / 24.2, 24.2 / 18.0.  4096: the kernels' arrays hold 128 strips.
 constexpr int SMALL_T = 4096;
-inline bool small_grid(long strips, int T, long mean_T, int d)
+inline bool small_grid(long strips, int T, int d)
 {
-    const long t = chain_length(T, mean_T);
-    const long limit = d == 128 ? 256 : t >= 1024 ? 768 : t > 341 ? 3 * t / 4 : 256;
-    return long_enough(strips, T, mean_T) && T <= SMALL_T && strips <= limit;
+    const long limit = d == 128 ? 256 : T >= 1024 ? 768 : T > 341 ? 3L * T / 4 : 256;
+    return T > 64 && T <= SMALL_T && strips <= limit;
 }
 
 // How many strips or blocks of `rows` rows there are: exactly, or in a packed batch of nseq sequences, whose
@@ -85,30 +72,49 @@ inline long pieces(int B, int H, int T, int rows, bool packed, int Ttot)
     return packed ? std::min(all, (long)H * (Ttot / rows + B)) : all;
 }
 
-// Workgroups of a packed batch's strips, per head: sequence s has the places (cu[s] >> 5) + s up to the next one's,
-// as many as it has strips, or one more.  (A place for every strip that max_T leaves room for costs 2 us a thousand in each
-// launch: 64 sequences of 32 rows, H4 d64, max_T 2048, forward 34.6 us with 16384 of them.)
-inline long packed_places(int nseq, int Ttot) { return Ttot / 32 + nseq; }
+// A packed batch's strips are launched as pieces() counts them, T (max_T) being at least the longest sequence's length and perhaps far
+// more; place_of() finds a workgroup's.  Each that T leaves room for, in every sequence, cost 2 us a thousand: 64 sequences of 32 rows,
+// H4 d64, T 2048, forward 34.6 -> 5.7 us, backward 85 -> 15.8.  The rules above hold for packed batches as well, though the host
+// cannot tell a long chain from many short ones.  Blocks / strips, us, forward, then backward: that batch 4.9 / 5.7, 12.9 / 15.8; T 200
+// with 32 of them 5.3 / 5.1, 11.0 / 14.2; H2 d128, T 512 5.5 / 5.3, 12.8 / 17.4; 100 of 70 rows, H1 d64, T 400 5.3 / 8.3, 15.2 / 15.1 (blocks);
+// but with one long one, all heads far, then none: 250 and 20 of 16 rows, H4 d64 7.5 / 5.7, 23 / 15.7 and 7.5 / 5.9, 23 / 15.6; 500 and
+// 40 of 60, H2 d32 9.3 / 6.1, 28 / 15 and 9.0 / 5.4, 24 / 12; 1000 and 30 of 20, H4 d64 18 / 10.4, 66 / 28 and 13.7 / 7.4, 33 / 18; 2000
+// and 44 of 16, H2 d64 31 / 16.7, 119 / 44 and 19.5 / 9.0, 32 / 20.
 struct Place {
     int seq, i;               // sequence, strip
-    int c0, c1;               // the sequence's offsets; c0 < 0: none
+    int c0, T;                // the sequence's first row and length; none: T = 0
 };
-__device__ __forceinline__ Place place_of(int place, const int* __restrict__ cu, int nseq, int lane)
+__device__ __forceinline__ int sum_up_to_lane(int x)
 {
-    Place at = {0, 0, -1, -1};
+    x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xF, 0xF, false);       // row_shr:1, 2, 4, 8
+    x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xF, 0xF, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xF, 0xF, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xF, 0xF, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xA, 0xF, false);       // row_bcast:15 into rows 1 and 3
+    x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xC, 0xF, false);       // row_bcast:31 into rows 2 and 3
+    return x;
+}
+// The strips of sequence 0, then of sequence 1, ...: what has nothing to do comes last.  (Among the others, with the offsets alone to say
+// where a sequence's places begin, it takes a CU's turn: the batch above 8.2 and 25.9 us.)
+__device__ __forceinline__ Place place_of(int place, const int* __restrict__ cu, int nseq, int Ttot, int T_arg, int lane)
+{
+    int s = min(lane, nseq - 1), n0 = cu[s], n1 = cu[s + 1];
     for (int b = 0; b < nseq; b += 64) {
-        const int s = min(b + lane, nseq - 1);
-        const int c0 = cu[s], c1 = cu[s + 1];
-        const int n = __builtin_popcountll(__builtin_amdgcn_ballot_w64(b + lane < nseq && (c0 >> 5) + s <= place));
-        if (n > 0) {
-            at.seq = b + n - 1;
-            at.c0 = __builtin_amdgcn_readlane(c0, n - 1);
-            at.c1 = __builtin_amdgcn_readlane(c1, n - 1);
+        const int c0 = n0, c1 = min(n1, Ttot);
+        s = min(b + 64 + lane, nseq - 1);                                     // the next 64, one step ahead
+        n0 = cu[s];
+        n1 = cu[s + 1];
+        const int T = b + lane < nseq && c0 >= 0 && c1 > c0 ? min(c1 - c0, T_arg) : 0;     // never past the packed rows or the stated maximum
+        const int n = (T + 31) >> 5;
+        const int upto = sum_up_to_lane(n);
+        const unsigned long long beyond = __builtin_amdgcn_ballot_w64(upto > place);
+        if (beyond) {
+            const int at = __builtin_ctzll(beyond);
+            return {b + at, place - __builtin_amdgcn_readlane(upto - n, at), __builtin_amdgcn_readlane(c0, at), __builtin_amdgcn_readlane(T, at)};
         }
-        if (n < 64) break;
+        place -= __builtin_amdgcn_readlane(upto, 63);
     }
-    at.i = place - (at.c0 >> 5) - at.seq;
-    return at;
+    return {0, 0, 0, 0};
 }
 
 // Grids of the forward that take one strip of 32 rows a workgroup, its waves taking the strip's subtiles in rounds
@@ -120,11 +126,10 @@ __device__ __forceinline__ Place place_of(int place, const int* __restrict__ cu,
 //   none far        12.2 / 7.0 and 17.2 / 9.4 for B1 H8 T700 d128, 8.9 / 10.2 and 41 / 17 for B1 H4 T4000 d64
 // and not, a third far, B4 H8 T700 d64 (704) 13.5 / 16.2, 13.6 / 17.6; B1 H24 T1000 d128 (768) 26.4 / 28.1, 26.5 / 31.8;
 // B4 H16 T300 d32 (640) 6.9 / 9.8, 7.0 / 10.1.  At d = 32 a chain of 10 subtiles is not worth the rounds' barriers.
-inline bool small_fwd_grid(long strips, int T, long mean_T, int d)
+inline bool small_fwd_grid(long strips, int T, int d)
 {
-    const long t = chain_length(T, mean_T);
-    const long limit = t < 256 ? 256 : t < 512 || d == 128 ? 384 : 512;
-    return T > (d == 32 ? 320 : 64) && long_enough(strips, T, mean_T) && T <= SMALL_T && strips <= limit;
+    const long limit = T < 256 ? 256 : T < 512 || d == 128 ? 384 : 512;
+    return T > (d == 32 ? 320 : 64) && T <= SMALL_T && strips <= limit;
 }
 
 // Grids of the key-stationary pass at d <= 64 whose blocks are taken by two groups of four waves (bwd_dkv_kernel<.., 2>): where a
@@ -161,10 +166,11 @@ inline bool take_in_turn(long blocks, int nkb, bool packed, long mean_T, long la
 //                      B1 H12 T4096 (384) 138 / 164, 121 / 89; B1 H3 T16384 (384) 499 / 579, 439 / 318
 //   beyond             B1 H14 T4096 (448) 152 / 185, 121 / 105; B1 H16 T4096 (512) 172 / 209, 121 / 116
 constexpr long small_kv_grid(int nkb) { return std::clamp(64L + 16L * nkb, 256L, 384L); }
+
 // The kernels of the backward's passes.
 inline bool query_strips(int B, int H, int T, int d, bool packed, int Ttot)
 {
-    return small_grid(pieces(B, H, T, 32, packed, Ttot), T, mean_length(B, T, packed, Ttot), d);
+    return small_grid(pieces(B, H, T, 32, packed, Ttot), T, d);
 }
 enum class Keys {
     STRIPS,                               // bwd_dkv_small_kernel
@@ -173,21 +179,21 @@ enum class Keys {
 };
 inline Keys keys_of(int B, int H, int Hkv, int T, int d, bool packed, int Ttot)
 {
-    const long mean_T = mean_length(B, T, packed, Ttot), heads = (long)B * Hkv;
+    const long heads = (long)B * Hkv;
     const int nkb = (T + 127) / 128;
     const long blocks = pieces(B, Hkv, T, 128, packed, Ttot);
-    if (small_grid(pieces(B, Hkv, T, 32, packed, Ttot), T, mean_T, d)) return Keys::STRIPS;
-    if (d < 128) return take_in_turn(blocks, nkb, packed, mean_T, heads * nkb) ? Keys::TWO_GROUPS : Keys::ONE_GROUP;
+    if (small_grid(pieces(B, Hkv, T, 32, packed, Ttot), T, d)) return Keys::STRIPS;
+    if (d < 128) return take_in_turn(blocks, nkb, packed, ((long)Ttot + B - 1) / B, heads * nkb) ? Keys::TWO_GROUPS : Keys::ONE_GROUP;
     if (blocks <= small_kv_grid(nkb)) return Keys::KEYS_64;
     return !packed && H == Hkv && take_pairs(heads, nkb) ? Keys::PAIRS : Keys::KEYS_128;
 }
 
 // log2 of the run, -1: turn with every block.  A run pays where the launch is several rounds deep and
 // there are enough runs to even the XCDs out: 32 of them, or 16 where 64 heads and more can be turned
-// among each other as well, by o(o+1)/2 inside each octet o of heads (over any 8 octets these are all 8
+// among each other as well, by o(o+1)/2 inside each octet o of heads (over octets 8x to 8x + 7 these are all 8
 // turns, so that heads which are costly in every batch entry do not meet on one XCD).  Query heads that
-// share a kv head have its tiles in every L2 already; in a packed batch a run is cut short by the
-// sequences' ends: both turn with every block.
+// share a kv head, for which runs were not measured, and packed batches, where a run is cut short by the
+// sequences' ends, turn with every block.
 // Every block / runs, us, all heads far, then a third, then none: forward B8 H16 T4096 d128 698 / 669,
 // 331 / 329, 160 / 150; B1 H32 T16384 d128 2422 / 2266, 883 / 880, 165 / 154; B1 H24 T16384 d64 1078 / 1032,
 // 460 / 422, 65 / 56; query-stationary backward of the same three 1049 / 1032, 524 / 530, 309 / 304;

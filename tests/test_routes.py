@@ -27,8 +27,8 @@ int main()
             printf("%d %d %d %d\n", s.near, s.C, s.nfar, room(T));
             continue;
         }
-        printf("%d %d %ld %d\n", small_fwd_grid(pieces(B, H, T, 32, packed, Ttot), T, mean_length(B, T, packed, Ttot), d),
-               query_strips(B, H, T, d, packed, Ttot), packed ? H * packed_places(B, Ttot) : (long)B * H * ((T + 31) / 32),
+        const long strips = pieces(B, H, T, 32, packed, Ttot);
+        printf("%d %d %ld %d\n", small_fwd_grid(strips, T, d), query_strips(B, H, T, d, packed, Ttot), strips,
                (int)keys_of(B, H, Hkv, T, d, packed, Ttot));
     }
 }
@@ -78,15 +78,13 @@ def test_packed_strips_are_counted_and_launched_as_they_exist(ask):
         assert strips <= got[2] <= strips + row[0] * row[1]
 
 
-def test_short_sequences_keep_the_blocks(ask):
-    """64 sequences of 32 rows: a strip a workgroup is slower, whatever max_T says."""
-    for H, d, max_T in ((4, 64, 65), (4, 64, 512), (4, 64, 2048), (4, 32, 2048), (8, 128, 512)):
-        assert not any(strips(ask, packed([32] * 64, H, d, max_T))), (H, d, max_T)
-    assert not any(strips(ask, packed([70] * 100, 1, 64, 400)))
-    # one of 600 rows among short ones, a place on the chip for every strip; and ordinary lengths, loose max_T
-    assert all(strips(ask, packed([600] + [20] * 30, 2, 128)))
-    for max_T in (100, 300, 1300):
-        assert all(strips(ask, packed([100] * 13, 4, 64, max_T)))
+def test_strips_of_packed_batches(ask):
+    """By the strips that there are and by max_T, as in a batched call; one long sequence among short ones takes strips."""
+    for lens, H, d, max_T in (([600] + [20] * 30, 2, 128, None), ([1000] + [20] * 30, 4, 32, None), ([500] + [60] * 40, 2, 32, None),
+                              ([250] + [16] * 20, 4, 64, None), ([32] * 64, 4, 64, 2048), ([100] * 13, 4, 64, 1300)):
+        assert strips(ask, packed(lens, H, d, max_T)) == (True, True, True), (H, d)
+    for lens, H, d, max_T in (([32] * 64, 4, 64, 64), ([32] * 64, 8, 128, 512), ([32] * 200, 4, 64, 6400), ([4000] + [16] * 40, 4, 128, None)):
+        assert not any(strips(ask, packed(lens, H, d, max_T))), (H, d, max_T)
 
 
 def test_equal_lengths_take_the_route_of_the_batched_call(ask):
@@ -144,7 +142,7 @@ def test_two_wave_groups(ask):
     for B, H, T, want in ((2, 24, 1024, 2), (1, 16, 4096, 2), (1, 32, 2011, 2), (8, 16, 512, 1), (1, 40, 2048, 1), (1, 24, 4096, 1),
                           (1, 30, 3500, 1), (1, 32, 4096, 1), (8, 16, 2048, 1)):
         assert ask([(B, H, H, T, 64, 0, 0)])[0][3] == want, (B, H, T)
-    for lens, H, max_T, want in (([5000] + [300] * 10, 4, None, 2), ([4200] + [800] * 3, 8, None, 1), ([32] * 64, 4, 2048, 1), ([32] * 64, 4, 512, 1)):
+    for lens, H, max_T, want in (([5000] + [300] * 10, 4, None, 2), ([4200] + [800] * 3, 8, None, 1), ([32] * 64, 4, 511, 1), ([32] * 64, 4, 512, 1)):
         assert ask([packed(lens, H, 64, max_T)])[0][3] == want, (H, max_T)
 
 
