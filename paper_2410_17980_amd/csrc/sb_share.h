@@ -135,23 +135,41 @@ inline bool small_fwd_grid(long strips, int T, int d)
 // Grids of the key-stationary pass at d <= 64 whose blocks are taken by two groups of four waves (bwd_dkv_kernel<.., 2>): where a
 // block has a CU to itself anyway (one wave per SIMD issues an instruction every five clocks at best, two keep it busy), and
 // for some more blocks, of which few are left once some heads turn out near: what counts then is the longest block's chain.
-// One group / two, us, all heads far, then a third, then none:
-//   d = 64  B2 H24 T1024 (384 blocks, 8 a head) 39 / 33, 38 / 31, 23 / 27; B1 H32 T2011 (512, 16) 70 / 60, 68 / 53, 24 / 30;
-//           B1 H12 T4059 (384, 32) 131 / 98, 127 / 99, 23 / 27; B1 H16 T4096 (512, 32) 135 / 111, 134 / 100, 24 / 30
-//     not   B1 H48 T1499 (576, 12) 56 / 60, 54 / 44, 29 / 38; B1 H36 T2011 (576, 16) 72 / 74, 69 / 65, 29 / 38; B1 H24 T4096 (768, 32) 165 / 173,
-//           143 / 101, 33 / 42; B1 H30 T3500 (840, 28) 158 / 160, 129 / 158, 38 / 52; B1 H32 T4096 (1024, 32) 210 / 217, 153 / 112, 41 / 56;
-//           B8 H16 T512 (512, 4) 25 / 29, 24 / 29, 23 / 28
-//   d = 32  B1 H16 T4096 (512, 32) 115 / 92, 114 / 84, 17 / 20; B1 H32 T2011 (512, 16) 59 / 49, 58 / 44, 18 / 20
-//     not   B1 H24 T4096 (768, 32) 128 / 146, 122 / 84, 22 / 29; B1 H43 T3035 (1032, 24) 113 / 139, 86 / 75, 27 / 37
-// Up to 512 what near heads lose is half of what the others gain at most; beyond, where all heads reach far, it is slower as well.
-// In a packed batch (blocks: those that the sequences can hold; launched: with those that only max_T leaves room for) up to 384: four
-// of 800 to 4200 rows, H8 d64 (440) 247 / 304, 244 / 210, 50 / 69; 11 of 300 to 5000, H4 d64 (292) 362 / 284, 287 / 246, 47 / 53; 8 of 1000, H6 d64
-// (384) 71 / 67, 71 / 64, 44 / 49.  And not for many short ones: 64 of 32 rows, H4 d64, max_T 512 (320) 9.9 / 12.9, 2048 12.9 / 22.
+// The limits lie where neither far heads nor near ones lose more by it than a mix gains.  One group / two, the whole backward, us,
+// all heads far, then a third drawn at random (five times, mean), then none:
+//   d = 64  B2 H16 T2048 (512 blocks) 130 / 121, 125 / 111, 46 / 51; B1 H36 T2011 (576) 139 / 139, 127 / 111, 52 / 61; B4 H8 T2500 (640)
+//           169 / 176, 157 / 136, 59 / 67; B1 H24 T4096 (768) 331 / 345, 261 / 221, 63 / 71; B1 H27 T4096 (864) 338 / 347, 267 / 229, 74 / 87;
+//           B1 H20 T6000 (940) 520 / 523, 393 / 352, 75 / 88; B1 H16 T8000 (1008) 706 / 723, 548 / 463, 78 / 90; B1 H32 T4096 (1024)
+//           402 / 401, 289 / 270, 77 / 91; the least: B1 H30 T3500 (840) 284 / 308, 234 / 215, 71 / 85
+//     not   B8 H16 T512 (512, 4 a head) this pass 25 / 29, 24 / 29, 23 / 28; B1 H48 T1499 (576, 12) 106 / 111, 99 / 93, 52 / 60; B1 H50 T1600 (650, 13)
+//           116 / 124, 106 / 100, 56 / 64; B1 H40 T2048 (640, 16) 148 / 154, 131 / 120, 58 / 66
+//   d = 32  B1 H16 T4096 (512) this pass 115 / 92, 114 / 84, 17 / 20; B1 H24 T4096 (768) 236 / 253, 225 / 187, 45 / 51; B5 H5 T4500 (900)
+//           292 / 309, 240 / 207, 53 / 62; B1 H16 T8000 (1008) 523 / 563, 488 / 397, 55 / 64;  not B1 H43 T3035 (1032) 225 / 251, 194 / 175, 55 / 64
+// Grouped heads, whose blocks are G times as long, up to 512:
+//   d = 64  B1 H48 Hkv24 T2011 (384) 227 / 202, 195 / 164, 67 / 74; B8 H16 Hkv4 T1500 (384) 292 / 246, 264 / 211, 114 / 121; B12 H9 Hkv3
+//           T1500 (432) 233 / 205, 207 / 168, 95 / 102; B1 H32 Hkv8 T8000 (504) 1602 / 1407, 1242 / 951, 139 / 142; B16 H16 Hkv2 T1200 (320)
+//           442 / 362, 176 / 183, 177 / 185;  not B12 H9 Hkv3 T3256 (936) 832 / 832, 490 / 559, 177 / 200
+//   d = 32  B2 H24 Hkv12 T2048 (384) 168 / 144, 158 / 132, 54 / 56; B4 H12 Hkv4 T4000 (512) 487 / 430, 423 / 343, 83 / 86
+// A packed batch's blocks are counted by its rows (in brackets; every third head far):
+//   d = 64  4500 and 30 of 50 rows, H8 (375) 343 / 279, 261 / 226, 62 / 81; four of 2000, H8 (500) 128 / 119, 126 / 110, 46 / 53; 2500 to 100, H12
+//           (562) 192 / 172, 165 / 142, 60 / 72; 6000 and three of 200, H12 (618) 418 / 414, 386 / 330, 60 / 70; two of 4000, H12 (750) 282 / 301,
+//           248 / 212, 61 / 72; six of 100 to 3000, H24 Hkv6 (248) 500 / 401, 477 / 377, 110 / 115; the worst: 4200 and three of 800, H8 (412)
+//           246 / 304, 244 / 210, 51 / 69;  not four of 2000, H12 (750) 158 / 169, 138 / 129, 62 / 71; six of 1500, H9 (632) 110 / 122, 101 / 97, 59 / 69
+//   d = 32  4500 and 30 of 50 rows, H8 (375) 297 / 233, 218 / 190, 50 / 69; two of 4000, H12 (750) 227 / 244, 213 / 180, 45 / 54
+// and not for many short ones (64 of 32 rows, H4 d64, T 511, this pass 9.9 / 12.9) nor very many, whose empty places cost two groups
+// more (5000 and 300 of 16, H2 d64, 77 / 117 with none far).
 constexpr long ONE_PER_CU = 256;          // workgroups of a launch that leaves none waiting for a CU
-inline bool take_in_turn(long blocks, int nkb, bool packed, long mean_T, long launched)
+inline bool take_in_turn(int B, int H, int Hkv, int T, bool packed, int Ttot)
 {
-    if (packed && (mean_T <= 64 || launched > 16 * ONE_PER_CU)) return launched <= ONE_PER_CU;
-    return blocks <= std::clamp(48L * nkb, ONE_PER_CU, packed ? 384L : 512L);
+    const long heads = (long)B * Hkv, nkb = (T + 127) / 128;
+    if (packed) {
+        if (heads > 256) return false;
+        if (pieces(B, Hkv, T, 128, true, Ttot) <= ONE_PER_CU) return true;
+        if (Ttot <= 64L * B) return false;
+    }
+    const long blocks = packed ? ((long)Hkv * Ttot + 127) / 128 : heads * nkb;
+    const long limit = std::max(ONE_PER_CU, std::min(48 * nkb, 512L));
+    return blocks <= (H == Hkv ? std::max(limit, std::min(36 * nkb, 1024L)) : limit);
 }
 
 // Grids of the key-stationary pass at d = 128 that take 64 keys a block in place of 128: what bounds a launch there is one
@@ -183,7 +201,7 @@ inline Keys keys_of(int B, int H, int Hkv, int T, int d, bool packed, int Ttot)
     const int nkb = (T + 127) / 128;
     const long blocks = pieces(B, Hkv, T, 128, packed, Ttot);
     if (small_grid(pieces(B, Hkv, T, 32, packed, Ttot), T, d)) return Keys::STRIPS;
-    if (d < 128) return take_in_turn(blocks, nkb, packed, ((long)Ttot + B - 1) / B, heads * nkb) ? Keys::TWO_GROUPS : Keys::ONE_GROUP;
+    if (d < 128) return take_in_turn(B, H, Hkv, T, packed, Ttot) ? Keys::TWO_GROUPS : Keys::ONE_GROUP;
     if (blocks <= small_kv_grid(nkb)) return Keys::KEYS_64;
     return !packed && H == Hkv && take_pairs(heads, nkb) ? Keys::PAIRS : Keys::KEYS_128;
 }

@@ -31,7 +31,7 @@ LOOPS = [(1, above(256, strips(T)), None, T, 128, None, "blocks", "64 keys") for
 # the search for a start begins at row 384: beyond that, all kernels, with and without groups
 LONG = [(1, 24, None, 705, 64, None, "blocks", "two groups"), (1, 24, None, 705, 32, None, "blocks", "two groups"),
         (1, 30, None, 1300, 64, None, "blocks", "two groups"), (1, 40, None, 1025, 64, None, "blocks", "two groups"),
-        (1, 46, None, 1300, 64, None, "blocks", "two groups"), (1, 42, None, 1409, 32, None, "blocks", "two groups"),
+        (1, 46, None, 1300, 64, None, "blocks", "two groups"), (1, 18, None, 4097, 32, None, "blocks", "two groups"), (1, 42, None, 1409, 32, None, "blocks", "two groups"),
         (1, 48, None, 1300, 64, None, "blocks", "one group"), (1, 48, None, 1300, 32, None, "blocks", "one group"),
         (1, 66, None, 449, 64, None, "blocks", "one group"), (1, 8, None, 1300, 128, None, "blocks", "64 keys"),
         (1, 28, None, 1300, 128, None, "blocks", "128 keys")]
@@ -42,11 +42,11 @@ GROUPED = [(1, 24, 8, 1025, 64, None, "blocks", "strips"), (1, 24, 8, 1300, 32, 
            (1, 20, 10, 1025, 128, None, "blocks", "64 keys"), (1, 58, 29, 1025, 128, None, "blocks", "128 keys")]
 
 LENS, LONG_AND_SHORT = [1100, 40, 0, 1300, 513], [2, 700, 1025, 31, 129]
-PACKED = [(5, 8, 8, 1300, 64, LENS, "blocks", "two groups"), (5, 16, 16, 1300, 64, LENS, "blocks", "one group"),
-          (5, 16, 8, 1300, 32, LENS, "blocks", "two groups"), (5, 32, 16, 1300, 64, LENS, "blocks", "one group"),
+PACKED = [(5, 8, 8, 1300, 64, LENS, "blocks", "two groups"), (5, 24, 24, 1300, 64, LENS, "blocks", "one group"),
+          (5, 16, 8, 1300, 32, LENS, "blocks", "two groups"), (5, 48, 24, 1300, 64, LENS, "blocks", "one group"),
           (5, 16, 4, 1300, 64, LENS, "blocks", "strips"), (5, 3, 3, 1300, 128, LENS, "blocks", "64 keys"),
           (5, 20, 10, 1300, 128, LENS, "blocks", "128 keys"), (5, 6, 2, 1300, 128, LENS, "blocks", "strips"),
-          (5, 24, 24, 1887, 64, LONG_AND_SHORT, "blocks", "one group"), (5, 13, 13, 1887, 32, LONG_AND_SHORT, "blocks", "two groups"),
+          (5, 38, 38, 1887, 64, LONG_AND_SHORT, "blocks", "one group"), (5, 13, 13, 1887, 32, LONG_AND_SHORT, "blocks", "two groups"),
           (5, 5, 5, 1887, 128, LONG_AND_SHORT, "blocks", "64 keys")]
 
 ALL = [s[:2] + (s[2] or s[1],) + s[3:] for s in LOOPS + LONG + GROUPED + PACKED]

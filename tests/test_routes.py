@@ -139,11 +139,13 @@ def test_strips_of_queries_come_with_strips_of_keys(ask):
 
 def test_two_wave_groups(ask):
     """Key-stationary pass at d <= 64: two groups only where neither near heads nor far ones lose more than a mix gains."""
-    for B, H, T, want in ((2, 24, 1024, 2), (1, 16, 4096, 2), (1, 32, 2011, 2), (8, 16, 512, 1), (1, 40, 2048, 1), (1, 24, 4096, 1),
-                          (1, 30, 3500, 1), (1, 32, 4096, 1), (8, 16, 2048, 1)):
-        assert ask([(B, H, H, T, 64, 0, 0)])[0][3] == want, (B, H, T)
-    for lens, H, max_T, want in (([5000] + [300] * 10, 4, None, 2), ([4200] + [800] * 3, 8, None, 1), ([32] * 64, 4, 511, 1), ([32] * 64, 4, 512, 1)):
-        assert ask([packed(lens, H, 64, max_T)])[0][3] == want, (H, max_T)
+    for B, H, Hkv, T, want in ((2, 24, 24, 1024, 2), (1, 16, 16, 4096, 2), (1, 32, 32, 2011, 2), (1, 36, 36, 2011, 2), (1, 24, 24, 4096, 2), (1, 32, 32, 4096, 2),
+                               (1, 16, 16, 8000, 2), (8, 16, 16, 512, 1), (1, 40, 40, 2048, 1), (1, 48, 48, 1499, 1), (1, 43, 43, 3035, 1), (1, 33, 33, 4096, 1),
+                               (8, 16, 16, 2048, 1), (1, 32, 8, 8000, 2), (12, 9, 3, 1500, 2), (12, 9, 3, 3256, 1)):
+        assert KEYS[ask([(B, H, Hkv, T, 64, 0, 0)])[0][3]] == ("one group", "two groups")[want - 1], (B, H, Hkv, T)
+    for lens, H, max_T, want in (([5000] + [300] * 10, 4, None, 2), ([4500] + [50] * 30, 8, None, 2), ([4000] * 2, 12, None, 2), ([5000] + [16] * 60, 2, None, 2),
+                                 ([2000] * 4, 12, None, 1), ([1500] * 6, 9, None, 1), ([5000] + [16] * 300, 2, None, 1), ([32] * 64, 4, 511, 1), ([32] * 64, 4, 512, 1)):
+        assert KEYS[ask([packed(lens, H, 64, max_T)])[0][3]] == ("one group", "two groups")[want - 1], (lens[0], H, max_T)
 
 
 def decode(B, H, Hkv, T, d, want_m=False):
