@@ -91,7 +91,7 @@ def spread(ts):
 
 
 TRAFFIC_FILE = os.path.join("profiles", "hbm_traffic_B8_H16_T4096_d128.txt")
-KERNEL_SOURCES = ("sb_fwd_bf16.hip", "sb_bwd_bf16.hip", "sb_decode.hip", "sb_mma.h", "sb_share.h")
+KERNEL_SOURCES = ("sb_fwd_bf16.hip", "sb_bwd_bf16.hip", "sb_decode.hip", "sb_split.h", "sb_mma.h", "sb_share.h")
 
 
 def source_fingerprint(name):

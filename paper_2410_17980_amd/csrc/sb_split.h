@@ -8,7 +8,7 @@ constexpr int NEAR_NW = 8;             // waves of a workgroup, first launch
 constexpr int FAR_NW = 4;              // and second: smaller, so that three share a CU
 constexpr int KW = 32;                 // keys per wave and pass
 constexpr int NEAR = KW * NEAR_NW;     // keys of a first launch that has a second one behind it
-constexpr int ALONE = 6 * NEAR;        // the first launch alone takes up to here: longer, two more launches are faster than its passes
+constexpr int ALONE = 6 * NEAR;        // a cache that is not spread is the first launch's alone up to here: longer, two more are faster than its passes
 constexpr int MAXFAR = 127;            // chunks beyond the nearest keys: with those, two per lane of a wave
 constexpr int FAR_KEYS = KW * FAR_NW;  // keys of a pass of the second launch
 constexpr long FAR_WGS = 2048;         // workgroups of the second launch, all heads together
