@@ -629,19 +629,24 @@ fwd_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
 // Where the 128-row blocks leave most of the chip idle, what counts is the length of one row's chain of
 // subtiles.  Here a workgroup takes one strip of 32 query rows, and its waves take the strip's subtiles from
 // the diagonal on in rounds of one each: logits and chains, which need no carry, side by side; one barrier
-// for the carries; weights, into LDS; one barrier; then O += A V, a wave per 32 columns, over the round's subtiles
-// in order.  Every sum is taken in the order of fwd_bf16_kernel: o is the same, bit for bit (m too,
-// unless the rows are exhausted on the way).  Which grids: small_fwd_grid().
+// for the carries; weights, into LDS; one barrier; then O += A V, over the round's subtiles in order, by waves
+// of their own, one per 32 columns, beside the logits and chains of the next round.  Every sum is taken in the order of
+// fwd_bf16_kernel: o is the same, bit for bit (m too, unless the rows are exhausted on the way).  Which grids: small_fwd_grid().
+// Against O += A V by the first of the waves between two rounds, and Q read by all of them, all heads far, then none, us: B2 H4 T777 d32
+// 8.4 -> 7.3, 6.0 -> 5.2; B1 H4 T4000 d64 36 -> 30, 18.7 -> 16.1; B1 H8 T700 d128 13.0 -> 10.9, 10.1 -> 8.3; B1 H16 T100 d64 5.0 -> 4.5.
 template <int D> struct FwdSmallCfg {
-    static constexpr int NWS = D == 128 ? 4 : 8;        // waves
+    static constexpr int NWS = D == 128 ? 4 : 8;        // waves that take subtiles
+    static constexpr int NWO = D / 32;                  // and waves that take O += A V
+    static constexpr int NTHR = 64 * (NWS + NWO);
     static constexpr int ROW = D * 2;
     static constexpr int SUB = 32 * ROW;                // one 32-row subtile of K (or V)
+    static constexpr int LOADS = SUB / 1024;            // of 16 bytes a lane, for a subtile
     static constexpr int W_OFF = NWS * 4 * SUB;         // after the waves' K and V, double buffered: weights
     static constexpr int W_SUB = 2 * 1024;              // of a subtile: two operands of 16 bytes a lane
 };
 
 template <int D>
-__global__ void __launch_bounds__(64 * FwdSmallCfg<D>::NWS)
+__global__ void __launch_bounds__(FwdSmallCfg<D>::NTHR)
 fwd_small_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
                  const uint16_t* __restrict__ v, const uint16_t* __restrict__ rb,
                  uint16_t* __restrict__ o, float* __restrict__ m,
@@ -650,7 +655,6 @@ fwd_small_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
 {
     using C = FwdSmallCfg<D>;
     constexpr int NWS = C::NWS;
-    static_assert(D / 32 <= NWS, "a wave per 32 columns");
     __shared__ __attribute__((aligned(1024))) char smem[C::W_OFF + NWS * C::W_SUB];
     __shared__ float s_tot[2][NWS][32];                 // per round parity: softplus totals of its subtiles (base 2), per row
 
@@ -670,6 +674,8 @@ fwd_small_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
         kvrow0 = (long)(head / G) * Ttot + at.c0;
     }
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const bool sums = wave >= NWS;                      // one of the waves that take O += A V
+    const int cols = wave - NWS;                        // its columns, 32 cols ..
     const bool clock = clocks && blockIdx.x == 0 && tid == 0;
     if (clock) {                                        // as in fwd_bf16_kernel
         clocks[0] = (unsigned long long)clock64();
@@ -678,146 +684,217 @@ fwd_small_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     const int n = lane & 31, hh = lane >> 5, gg = lane >> 4, li = lane & 15;
     const int strip = nstrip - 1 - i;
     const int q0 = strip * 32;
-    const uint16_t* Qg = q + row0 * D;
+    const int nlast = min(T - q0, 32);                  // rows of the strip, and of the subtile on the diagonal
     const uint16_t* Kg = reinterpret_cast<const uint16_t*>(scalar_base(k + kvrow0 * D));
     const uint16_t* Vg = reinterpret_cast<const uint16_t*>(scalar_base(v + kvrow0 * D));
+    const uint32_t smem0 = lds_offset(smem);
 
     // a wave's buffers: K, K, V, V
-    char* const mine = smem + wave * 4 * C::SUB;
-    auto stage = [&](const uint16_t* X, int sub, char* dst) __attribute__((always_inline)) {
-        const int last = T - 1 - sub * 32;              // rows past T are clamped (causality masks them)
-        const uint16_t* xb = X + (long)sub * 32 * D;
-        constexpr int CPR = C::ROW / 16;
+    const uint32_t mine = smem0 + wave * 4 * C::SUB;
+    constexpr int CPR = C::ROW / 16;
+    int off[C::LOADS];
 #pragma unroll
-        for (int i = 0; i < C::SUB / 1024; ++i) {
-            const int row = i * (1024 / C::ROW) + lane / CPR;
-            dma16_to_lds_saddr(xb, (min(row, last) * D + (((lane % CPR) ^ swz_perm<D>(row)) << 3)) * 2, dst + i * 1024);
+    for (int i = 0; i < C::LOADS; ++i) off[i] = tile_off_perm<D>(i * (1024 / C::ROW) + lane / CPR, lane % CPR);
+    auto stage = [&](const uint16_t* X, int sub, uint32_t dst) __attribute__((always_inline)) {
+        const uint64_t xb = scalar_base(X + (long)sub * 32 * D);
+        if (sub < strip || nlast == 32) {
+            dma16_to_lds_run_at(xb, off, dst);
+        } else {                                        // rows past T are clamped (causality masks them)
+            int o[C::LOADS];
+#pragma unroll
+            for (int i = 0; i < C::LOADS; ++i) o[i] = off[i] - max(i * (1024 / C::ROW) + lane / CPR - (nlast - 1), 0) * C::ROW;
+            dma16_to_lds_run_at(xb, o, dst);
         }
     };
-    if (strip - wave >= 0) {
+    // Q passes through the place of the weights: whole rows and once, every wave its share.  (As operands from
+    // memory, 32 bytes of 32 rows an instruction, all of it by every wave: 1700, 2200 and 4500 clocks at d = 32, 64 and 128.)
+    static_assert(C::SUB <= NWS * C::W_SUB, "the rows fit");
+    for (int i = wave; i < C::LOADS; i += C::NTHR / 64) {
+        const int row = i * (1024 / C::ROW) + lane / CPR;
+        dma16_to_lds_at(scalar_base(q + (row0 + q0) * D), min(row, nlast - 1) * C::ROW + (((lane % CPR) ^ swz_perm<D>(row)) << 4),
+                        smem0 + C::W_OFF + i * 1024);
+    }
+    if (!sums && strip - wave >= 0) {
         stage(Kg, strip - wave, mine);
         stage(Vg, strip - wave, mine + 2 * C::SUB);
+        dma_wait<C::LOADS>();                           // all but V
+    } else {
+        dma_wait<0>();
     }
-    bf16x8 qf[D / 16];
-    {
-        const u32x4* src = reinterpret_cast<const u32x4*>(Qg + (long)min(q0 + n, T - 1) * D + 8 * hh);
-#pragma unroll
-        for (int s = 0; s < D / 16; ++s) qf[s] = __builtin_bit_cast(bf16x8, src[2 * s]);
-    }
-#pragma unroll
-    for (int s = 0; s < D / 16; ++s) asm volatile("" :: "v"(qf[s]));
-    const uint32_t smem0 = lds_offset(smem);
-    const uint32_t ka = lds_offset(mine) + tile_off_perm<D>(perm_row(n), hh);       // K as A operand, ^ (s << 5)
-    uint32_t vtr[2];                                    // V of wave 0, this wave's columns, through the transposing load
-#pragma unroll
-    for (int t = 0; t < 2; ++t)
-        vtr[t] = smem0 + 2 * C::SUB + tile_off_perm<D>(16 * (gg >> 1) + (li >> 2) + 4 * t, (4 * wave & (D / 8 - 1)) + 2 * (gg & 1) + ((li & 3) >> 1)) + 8 * (li & 1);
-    const uint32_t wts = smem0 + C::W_OFF + lane * 16;
+    barrier_nofence();
     const float c2 = SB_LOG2E / sqrtf((float)D);
-    f32x16 oacc;                                        // columns 32 wave .. (the first D / 32 waves)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) oacc[r] = 0.0f;
+    f32x16 oacc;                                        // columns 32 cols ..
     float a = 0.0f;                                     // carry of the round
     bool done = false;                                  // every row exhausted: the weights are zero from here on
-
-    auto logits = [&](int st) __attribute__((always_inline)) {
-        u32x4 kop[D / 16];
-#pragma unroll
-        for (int s = 0; s < D / 16; ++s) kop[s] = lds_load16((ka + st * C::SUB) ^ (s << 5));
-        f32x16 acc;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
-#pragma unroll
-        for (int s = 0; s < D / 16; ++s)
-            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kop[s]), qf[s], acc, 0, 0, 0);
-        return acc;
-    };
     int st = 0, top = strip;
-    for (; top >= 0; top -= NWS, st ^= 1) {
-        const int sub = top - wave;
-        float g[16], t_lo = 0.0f, t_hi = 0.0f;
-        bool linear = true;
-        if (sub >= 0) {
-            // this subtile has landed; the K buffer to be refilled was read a round ago, by this wave
-            asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
-            if (sub - NWS >= 0) stage(Kg, sub - NWS, mine + (st ^ 1) * C::SUB);
-            const f32x16 acc = logits(st);
-            auto keep = [&](auto lin, const float (&x)[16], float x_lo, float x_hi) __attribute__((always_inline)) {
-                linear = decltype(lin)::value;
-                t_lo = x_lo;
-                t_hi = x_hi;
+    auto totals = [&](float (&t)[NWS]) __attribute__((always_inline)) {
 #pragma unroll
-                for (int r = 0; r < 16; ++r) g[r] = x[r];
-            };
-            if (sub == strip) chain_of<true>(acc, c2, n, hh, keep);
-            else chain_of<false>(acc, c2, n, hh, keep);
-        }
-        if (hh == 0) s_tot[st][wave][n] = t_lo + t_hi;
-        barrier_lds();                                   // totals and V have landed, the weights before have been used
-        float mine_a = a;
-        for (int w = 0; w < NWS; ++w) {
-            if (w == wave) mine_a = a;
-            a += s_tot[st][w][n];
-        }
-        if (sub - NWS >= 0) stage(Vg, sub - NWS, mine + (2 + (st ^ 1)) * C::SUB);
-        bf16x8 p[2] = {};
-        if (sub >= 0) {
-            if (linear) weights_of<true>(g, t_lo, t_hi, mine_a, hh, p);
-            else weights_of<false>(g, t_lo, t_hi, mine_a, hh, p);
-            lds_store16(wts + wave * C::W_SUB, p[0]);
-            lds_store16(wts + wave * C::W_SUB + 1024, p[1]);
-        }
-        barrier_lds();
-        if (wave < D / 32) {
-            for (int w = 0; w < min(NWS, top + 1); ++w) {
+        for (int w = 0; w < NWS; ++w) t[w] = s_tot[st][w][n];
+    };
+    auto ended = [&]() __attribute__((always_inline)) {          // alike in all waves
+        done = __builtin_amdgcn_ballot_w64(!(a >= CARRY_EXHAUSTED)) == 0;
+        return done || top < NWS;
+    };
+    // Both kinds of waves pass the same barriers.
+    if (sums) {
+        uint32_t vtr[2];                                // V of wave 0, this wave's columns, through the transposing load
 #pragma unroll
-                for (int s = 0; s < 2; ++s) {
-                    const uint32_t vs = w * 4 * C::SUB + st * C::SUB + 8 * s * C::ROW;
-                    oacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, lds_load16(wts + w * C::W_SUB + s * 1024)),
-                                                                   tr_pair_at(vtr[0] + vs, vtr[1] + vs), oacc, 0, 0, 0);
-                }
+        for (int t = 0; t < 2; ++t)
+            vtr[t] = smem0 + 2 * C::SUB + tile_off_perm<D>(16 * (gg >> 1) + (li >> 2) + 4 * t, 4 * cols + 2 * (gg & 1) + ((li & 3) >> 1)) + 8 * (li & 1);
+        const uint32_t wts = smem0 + C::W_OFF + lane * 16;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) oacc[r] = 0.0f;
+        // operands of a round's subtiles, all asked for before the first product
+        bf16x8 p[2 * NWS], x[2 * NWS];
+        auto ask = [&](int st, int count) __attribute__((always_inline)) {
+#pragma unroll
+            for (int i = 0; i < 2 * NWS; ++i) {
+                const int w = min(i >> 1, count - 1), s = i & 1;
+                const uint32_t vs = w * 4 * C::SUB + st * C::SUB + 8 * s * C::ROW;
+                p[i] = __builtin_bit_cast(bf16x8, lds_load16(wts + w * C::W_SUB + s * 1024));
+                x[i] = tr_pair_at(vtr[0] + vs, vtr[1] + vs);
             }
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        auto multiply = [&](int from, int to) __attribute__((always_inline)) {
+#pragma unroll
+            for (int i = 0; i < 2 * NWS; ++i)
+                if (i >= from && i < to) oacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(p[i], x[i], oacc, 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        for (;; top -= NWS, st ^= 1) {
+            if (top != strip) {                         // the round before: half of it beside the logits of this one
+                ask(st ^ 1, NWS);
+                multiply(0, NWS);
+            }
+            barrier_lds();
+            if (top != strip) multiply(NWS, 2 * NWS);
+            float t[NWS];
+            totals(t);
+#pragma unroll
+            for (int w = 0; w < NWS; ++w) a += t[w];
+            barrier_lds();
+            if (ended()) break;
         }
-        done = __builtin_amdgcn_ballot_w64(!(a >= CARRY_EXHAUSTED)) == 0;      // alike in all waves
-        if (done) break;
+        const int count = min(NWS, top + 1);            // the last round
+        ask(st, count);
+        multiply(0, 2 * count);
+        if (m && done) barrier_lds();
+    } else {
+        bf16x8 qf[D / 16];
+        {
+            const uint32_t at = smem0 + C::W_OFF + tile_off_perm<D>(n, hh);
+#pragma unroll
+            for (int s = 0; s < D / 16; ++s) qf[s] = __builtin_bit_cast(bf16x8, lds_load16(at ^ (s << 5)));
+        }
+        const uint32_t ka = mine + tile_off_perm<D>(perm_row(n), hh);               // K as A operand, ^ (s << 5)
+        const uint32_t wts = smem0 + C::W_OFF + wave * C::W_SUB + lane * 16;
+        auto logits = [&](int st) __attribute__((always_inline)) {
+            u32x4 kop[D / 16];
+#pragma unroll
+            for (int s = 0; s < D / 16; ++s) kop[s] = lds_load16((ka + st * C::SUB) ^ (s << 5));
+            f32x16 acc;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
+#pragma unroll
+            for (int s = 0; s < D / 16; ++s)
+                acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kop[s]), qf[s], acc, 0, 0, 0);
+            return acc;
+        };
+        for (;; top -= NWS, st ^= 1) {
+            const int sub = top - wave;
+            float g[16], t_lo = 0.0f, t_hi = 0.0f;
+            bool linear = true;
+            if (sub >= 0) {
+                // this subtile's K has landed, V was asked for behind it; the K buffer to be refilled was read a round ago, by this wave
+                asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" :: "n"(C::LOADS) : "memory");
+                if (sub - NWS >= 0) stage(Kg, sub - NWS, mine + (st ^ 1) * C::SUB);
+                const f32x16 acc = logits(st);
+                auto keep = [&](auto lin, const float (&x)[16], float x_lo, float x_hi) __attribute__((always_inline)) {
+                    linear = decltype(lin)::value;
+                    t_lo = x_lo;
+                    t_hi = x_hi;
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) g[r] = x[r];
+                };
+                if (sub == strip) chain_of<true>(acc, c2, n, hh, keep);
+                else chain_of<false>(acc, c2, n, hh, keep);
+                if (sub - NWS >= 0) dma_wait<C::LOADS>();    // V has landed
+                else dma_wait<0>();
+            }
+            if (hh == 0) s_tot[st][wave][n] = t_lo + t_hi;
+            barrier_lds();                               // totals and V have landed, the weights before have been used
+            float mine_a = a, t[NWS];
+            totals(t);
+#pragma unroll
+            for (int w = 0; w < NWS; ++w) {
+                if (w == wave) mine_a = a;
+                a += t[w];
+            }
+            if (sub >= 0) {
+                if (sub - NWS >= 0) stage(Vg, sub - NWS, mine + (2 + (st ^ 1)) * C::SUB);
+                bf16x8 p[2];
+                if (linear) weights_of<true>(g, t_lo, t_hi, mine_a, hh, p);
+                else weights_of<false>(g, t_lo, t_hi, mine_a, hh, p);
+                lds_store16(wts, p[0]);
+                lds_store16(wts + 1024, p[1]);
+            }
+            barrier_lds();
+            if (ended()) break;
+        }
+        if (m && done) {
+            // the logits alone, as in sum_tail(), every wave on its own (in rounds with the others, us: B1 H4 T4000 d64 near
+            // 21.7 -> 16.7, B2 H4 T777 d32 near 6.2 -> 5.4, all far 8.0 -> 7.8, with no test for it in the rounds)
+            float l = 0.0f;
+            int b = st ^ 1;
+            for (int sub = top - NWS - wave; sub >= 0; sub -= NWS, b ^= 1) {
+                asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+                if (sub - NWS >= 0) stage(Kg, sub - NWS, mine + (b ^ 1) * C::SUB);
+                l += sp2_total<false>(logits(b), c2, n, hh);
+            }
+            float l_lo, l_hi;
+            both_halves(l, l_lo, l_hi);
+            if (hh == 0) s_tot[st][wave][n] = l_lo + l_hi;   // this round's totals have been read
+            barrier_lds();
+        }
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // subtiles staged before the sweep stopped
     }
     if (m && done) {
-        // the logits alone, as in sum_tail(), every wave on its own (in rounds with the others, us: B1 H4 T4000 d64 near
-        // 21.7 -> 16.7, B2 H4 T777 d32 near 6.2 -> 5.4, all far 8.0 -> 7.8, with no test for it in the rounds)
-        float l = 0.0f;
-        int b = st ^ 1;
-        for (int sub = top - NWS - wave; sub >= 0; sub -= NWS, b ^= 1) {
-            asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
-            if (sub - NWS >= 0) stage(Kg, sub - NWS, mine + (b ^ 1) * C::SUB);
-            l += sp2_total<false>(logits(b), c2, n, hh);
-        }
-        float l_lo, l_hi;
-        both_halves(l, l_lo, l_hi);
-        if (hh == 0) s_tot[st][wave][n] = l_lo + l_hi;   // this round's totals have been read
-        barrier_lds();
-        float rest = 0.0f;
+        float t[NWS], rest = 0.0f;
+        totals(t);
 #pragma unroll
-        for (int w = 0; w < NWS; ++w) rest += s_tot[st][w][n];
+        for (int w = 0; w < NWS; ++w) rest += t[w];
         a += rest;
     }
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");     // subtiles staged before the sweep stopped
 
-    // ---- store.  oacc[r] is query row 8*(r/4) + 4*hh + r%4, column 32 wave + n.
-    if (wave < D / 32) {
+    // ---- store.  oacc[r] is query row 8*(r/4) + 4*hh + r%4, column 32 cols + n.
+    if (sums) {
         if (rb) {                                        // remainder bias, as in fwd_bf16_kernel
             const float rem = fast_exp2(-a);
-            const float rc = __builtin_bit_cast(float, (uint32_t)rb[head * D + 32 * wave + n] << 16);
+            const float rc = __builtin_bit_cast(float, (uint32_t)rb[head * D + 32 * cols + n] << 16);
 #pragma unroll
             for (int r = 0; r < 16; ++r) oacc[r] += __shfl(rem, 8 * (r >> 2) + 4 * hh + (r & 3)) * rc;
         }
+        uint16_t* const Og = reinterpret_cast<uint16_t*>(scalar_base(o + (row0 + q0) * D + 32 * cols));
+        // two columns a store, as in fwd_bf16_kernel
+        const uint32_t pick = (n & 1) ? 0x03020706u : 0x05040100u;
+        const int at = (4 * hh + (n & 1)) * D + (n & ~1);
+        auto store = [&](auto whole) __attribute__((always_inline)) {
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int row = q0 + 8 * (r >> 2) + 4 * hh + (r & 3);
-            const __bf16 val = (__bf16)oacc[r];
-            if (row < T) o[(row0 + row) * D + 32 * wave + n] = __builtin_bit_cast(uint16_t, val);
-        }
+            for (int r = 0; r < 16; r += 2) {
+                typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
+                const bf16x2 two = {(__bf16)oacc[r], (__bf16)oacc[r + 1]};
+                const uint32_t x = __builtin_bit_cast(uint32_t, two);
+                const uint32_t y = __builtin_amdgcn_mov_dpp(x, 0xB1, 0xF, 0xF, true);      // of lane n ^ 1
+                const int row = 8 * (r >> 2) + (r & 3);
+                if (decltype(whole)::value || row + 4 * hh + (n & 1) < nlast)
+                    *reinterpret_cast<uint32_t*>(Og + row * D + at) = __builtin_amdgcn_perm(y, x, pick);
+            }
+        };
+        if (nlast == 32) store(bc<true>{});
+        else store(bc<false>{});
     }
-    if (m && tid < 32 && q0 + n < T) m[row0 + q0 + n] = -a * SB_LN2;
+    if (m && tid < 32 && n < nlast) m[row0 + q0 + n] = -a * SB_LN2;
     if (clock) {
         clocks[2] = (unsigned long long)clock64();
         clocks[3] = (unsigned long long)wall_clock64();
@@ -833,7 +910,7 @@ hipError_t launch_one(const uint16_t* q, const uint16_t* k, const uint16_t* v, c
     const long strips = pieces(BH / H, H, T, 32, VL, Ttot);
     if (!TRI && enough == CARRY_EXHAUSTED && (WRITE_M || !tile_counts) && small_fwd_grid(strips, T, D)) {     // halting sweeps stop by blocks
         const int heads = VL ? H : BH, n = VL ? BH / H : (T + 31) / 32;
-        hipLaunchKernelGGL((fwd_small_kernel<D>), dim3((unsigned)strips), dim3(64 * FwdSmallCfg<D>::NWS), 0, stream,
+        hipLaunchKernelGGL((fwd_small_kernel<D>), dim3((unsigned)strips), dim3(FwdSmallCfg<D>::NTHR), 0, stream,
                            q, k, v, rb, o, m, T, heads, H, G, n, tile_counts, cu, Ttot);
         return hipGetLastError();
     }

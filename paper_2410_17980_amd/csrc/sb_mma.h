@@ -180,35 +180,44 @@ __device__ __forceinline__ uint64_t scalar_base(const void* gbase)
 // in are written out: one between a scalar write of M0 and the load, five between a vector
 // instruction's write of a scalar register (v_readfirstlane, v_readlane of a spilled one)
 // and a memory instruction that takes its base from it.
-__device__ __forceinline__ void dma16_to_lds_saddr(const void* gbase, int lane_off, const char* lds_base)
+__device__ __forceinline__ void dma16_to_lds_at(uint64_t sb, int lane_off, uint32_t lds)
 {
-    const uint32_t lds = __builtin_amdgcn_readfirstlane(lds_offset(lds_base));
-    asm volatile("s_nop 4\n\tglobal_load_lds_dwordx4 %1, %2"
-                 :: "{m0}"(lds), "v"(lane_off), "s"(scalar_base(gbase)) : "memory");
+    asm volatile("s_nop 4\n\tglobal_load_lds_dwordx4 %1, %2" :: "{m0}"(lds), "v"(lane_off), "s"(sb) : "memory");
 }
 
-// N of them from one base, to N consecutive KB of LDS: the wait states for the base once
-template <int N>
-__device__ __forceinline__ void dma16_to_lds_run(const void* gbase, const int (&off)[N], const char* lds_base)
+// the same from a pointer to a pointer, both wave-uniform
+__device__ __forceinline__ void dma16_to_lds_saddr(const void* gbase, int lane_off, const char* lds_base)
 {
-    static_assert(N == 1 || N == 2 || N == 4, "loads per wave and matrix");
-    if constexpr (N == 1) {
-        dma16_to_lds_saddr(gbase, off[0], lds_base);
-        return;
-    }
-    uint32_t lds = __builtin_amdgcn_readfirstlane(lds_offset(lds_base));
-    const uint64_t sb = scalar_base(gbase);
+    dma16_to_lds_at(scalar_base(gbase), lane_off, __builtin_amdgcn_readfirstlane(lds_offset(lds_base)));
+}
+
+// N of them from one base, to N consecutive KB of LDS from address `lds` on (both wave-uniform): the wait states for the base once
+template <int N>
+__device__ __forceinline__ void dma16_to_lds_run_at(uint64_t sb, const int (&off)[N], uint32_t lds)
+{
+    static_assert(N == 2 || N == 4 || N == 8, "loads per wave and matrix");
     if constexpr (N == 2) {
         asm volatile("s_nop 4\n\tglobal_load_lds_dwordx4 %1, %3\n\t"
                      "s_add_u32 m0, m0, 0x400\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %3"
                      : "+{m0}"(lds) : "v"(off[0]), "v"(off[1]), "s"(sb) : "memory", "scc");
-    } else if constexpr (N == 4) {
+    } else {
+        uint32_t at = lds;
         asm volatile("s_nop 4\n\tglobal_load_lds_dwordx4 %1, %5\n\t"
                      "s_add_u32 m0, m0, 0x400\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %5\n\t"
                      "s_add_u32 m0, m0, 0x400\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %3, %5\n\t"
                      "s_add_u32 m0, m0, 0x400\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %4, %5"
-                     : "+{m0}"(lds) : "v"(off[0]), "v"(off[1]), "v"(off[2]), "v"(off[3]), "s"(sb) : "memory", "scc");
+                     : "+{m0}"(at) : "v"(off[0]), "v"(off[1]), "v"(off[2]), "v"(off[3]), "s"(sb) : "memory", "scc");
+        if constexpr (N == 8) {
+            const int rest[4] = {off[4], off[5], off[6], off[7]};
+            dma16_to_lds_run_at(sb, rest, lds + 0x1000);
+        }
     }
+}
+template <int N>
+__device__ __forceinline__ void dma16_to_lds_run(const void* gbase, const int (&off)[N], const char* lds_base)
+{
+    if constexpr (N == 1) dma16_to_lds_saddr(gbase, off[0], lds_base);
+    else dma16_to_lds_run_at(scalar_base(gbase), off, __builtin_amdgcn_readfirstlane(lds_offset(lds_base)));
 }
 
 // are all four flags (16-byte aligned, in LDS) set
