@@ -1445,7 +1445,7 @@ bwd_dkv_pair_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
 // ------------------------------------------------------------------ small grids
 // Where the 128-row blocks leave most of the chip idle, what counts is the length of one row's chain of
 // subtiles.  Here a workgroup takes one strip of 32 rows, and its waves share the other side's subtiles, each
-// staging its own, without a barrier for the tiles.  Still bound by the chain: B2 H4 T777 d32 takes 11 + 8 us,
+// staging its own, without a barrier for the tiles.  Still bound by the chain: B2 H4 T777 d32 takes 8 + 8 us,
 // of which 4 to 5 each are a launch and its first loads.  Which grids: small_grid().
 template <int D> struct SmallCfg {
     static constexpr int NWS = D == 128 ? 4 : 8;        // waves
@@ -1453,7 +1453,36 @@ template <int D> struct SmallCfg {
     static constexpr int SUB = 32 * ROW;                // one 32-row subtile of one matrix
     static constexpr int WAVE = 4 * SUB;                // two matrices, double buffered
     static constexpr int MAXSUB = SMALL_T / 32;         // subtiles of a strip
+    static constexpr int LOADS = SUB / 1024;            // of 16 bytes a lane, for a subtile
 };
+
+// byte offsets inside a 32-row subtile of what a lane fetches with its loads
+template <int D, bool PERM>
+__device__ __forceinline__ void subtile_offsets(int (&off)[SmallCfg<D>::LOADS], int lane)
+{
+    using C = SmallCfg<D>;
+    constexpr int CPR = C::ROW / 16;
+#pragma unroll
+    for (int i = 0; i < C::LOADS; ++i) {
+        const int row = i * (1024 / C::ROW) + lane / CPR;
+        off[i] = PERM ? tile_off_perm<D>(row, lane % CPR) : tile_off_nat<D>(row, lane % CPR);
+    }
+}
+// the subtile that begins at `src` (wave-uniform), by one wave, to LDS address `lds`; only `rows` of its rows exist: those past
+// them are clamped
+template <int D>
+__device__ __forceinline__ void stage_rows(const uint16_t* src, int rows, uint32_t lds, const int (&off)[SmallCfg<D>::LOADS], int lane)
+{
+    using C = SmallCfg<D>;
+    if (rows >= 32) {
+        dma16_to_lds_run_at(scalar_base(src), off, lds);
+        return;
+    }
+    int o[C::LOADS];
+#pragma unroll
+    for (int i = 0; i < C::LOADS; ++i) o[i] = off[i] - max(i * (1024 / C::ROW) + lane / (C::ROW / 16) - (rows - 1), 0) * C::ROW;
+    dma16_to_lds_run_at(scalar_base(src), o, lds);
+}
 
 // one 32-row subtile of X (rows 32*sub ..), by one wave; rows past `last` are clamped
 template <int D, bool PERM>
@@ -1468,6 +1497,21 @@ __device__ __forceinline__ void stage_subtile(const uint16_t* X, int sub, int T,
         const int row = i * (1024 / C::ROW) + lane / CPR;
         const int swz = PERM ? swz_perm<D>(row) : swz_nat<D>(row);
         dma16_to_lds_saddr(xb, (min(row, last) * D + (((lane % CPR) ^ swz) << 3)) * 2, dst + i * 1024);
+    }
+}
+
+// The strip's own 32 rows of two matrices, into the places x_at and y_at in LDS: whole rows and once, every wave its share.  (As
+// operands from memory, 32 bytes of 32 rows an instruction and all of it by every wave, the two took a CU 2000, 4800 and 7000 clocks
+// at d = 32, 64 and 128: a tenth to a third of a near strip's time.)
+template <int D>
+__device__ __forceinline__ void stage_strip(const uint16_t* X, const uint16_t* Y, int rows, uint32_t x_at, uint32_t y_at, int wave, int lane)
+{
+    using C = SmallCfg<D>;
+    constexpr int CPR = C::ROW / 16;
+    for (int i = wave; i < 2 * C::LOADS; i += C::NWS) {
+        const bool x = i < C::LOADS;
+        const int j = x ? i : i - C::LOADS, row = j * (1024 / C::ROW) + lane / CPR;
+        dma16_to_lds_at(scalar_base(x ? X : Y), min(row, rows - 1) * C::ROW + (((lane % CPR) ^ swz_perm<D>(row)) << 4), (x ? x_at : y_at) + j * 1024);
     }
 }
 
@@ -1711,7 +1755,7 @@ bwd_dkv_small_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict_
     constexpr int NWS = C::NWS, NTHR = 64 * NWS;
     constexpr int WAVE = C::WAVE + 2 * SCR_MAT;          // Q and dO subtiles, double buffered; A and dZ scratch
     __shared__ __attribute__((aligned(1024))) char smem[NWS * WAVE];
-    static_assert(NWS * WAVE <= 160 * 1024 && NWS * 32 * D * 4 <= NWS * WAVE, "LDS budget; the partial gradients fit");
+    static_assert(NWS * WAVE <= 160 * 1024, "LDS budget");
 
     asm volatile("" :: "s"(q), "s"(k), "s"(v), "s"(dout), "s"(ca), "s"(cb), "s"(first), "s"(T_arg));
     const Share sh = in_scalars(share_of(blockIdx.x, BH, -1));
@@ -1730,60 +1774,77 @@ bwd_dkv_small_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict_
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n = lane & 31, hh = lane >> 5, gg = lane >> 4, li = lane & 15;
     const int k0 = ks * 32;
-    char* const mine = smem + wave * WAVE;
+    const int nq = nstrip - ks;                          // query strips from the keys' own on
+    const int nlast = T - (nstrip - 1) * 32;             // rows of the last
 
-    // the query strips of head g that reach the keys, as bits; wave w takes strips ks + w, ks + w + NWS, ... of
-    // all heads in turn
-    const int nq = nstrip - ks;
-    struct Item {
-        int g, r;                                        // head, strip - ks
-    };
-    int mask_g = -1;
-    unsigned long long mask[2];
-    static_assert(C::MAXSUB <= 128, "two masks");
-    auto next_item = [&](Item i) __attribute__((always_inline)) {
-        for (;; i.r += NWS) {
-            while (i.r >= nq) { i.r -= nq; ++i.g; }
-            if (i.g >= G) return i;
-            if (i.g != mask_g) {
-                mask_g = i.g;
-                const uint16_t* f = first + (kh.qhead0 + i.g) * nqb_arg * 4 + ks;
-#pragma unroll
-                for (int x = 0; x < 2; ++x) {
-                    const int r = 64 * x + lane;
-                    mask[x] = __builtin_amdgcn_ballot_w64(r < nq && f[min(r, nq - 1)] <= ks);
-                }
+    // Which of them reach the keys, as bits, 64 strips of a head at a time: `todo` holds those left of the wave's
+    // share, strips ks + w, ks + w + NWS, ... of all heads one after the other.  The words to come are fetched
+    // one ahead.  (With head, strip and addresses worked out anew for every strip, all heads far, us: B1 H8 Hkv1 T1000 d128 124 -> 103,
+    // T4096 d64 203 -> 185, near 34 -> 25; B1 H8 T700 d128 18.6 -> 17.0.)
+    constexpr unsigned long long EVERY = NWS == 8 ? 0x0101010101010101ull : 0x1111111111111111ull;
+    static_assert(NWS == 4 || NWS == 8, "strips of a wave");
+    int g = -1, w0 = 0, gn = 0, w0n = 0, turn = wave;    // head and first strip (from ks on) of this word, and of the next one
+    unsigned long long todo = 0;
+    const uint16_t* fg = first + kh.qhead0 * nqb_arg * 4 + ks;
+    int fn = lane < nq ? fg[lane] : 0x7fffffff;
+    const uint16_t *Qg = nullptr, *Gg = nullptr;         // head g's rows from the keys' own strip on, and its carries
+    const float *cag = nullptr, *cbg = nullptr;
+    auto next = [&](int& r) __attribute__((always_inline)) {
+        while (todo == 0) {
+            if (gn >= G) return false;
+            todo = __builtin_amdgcn_ballot_w64(fn <= ks) & (EVERY << turn);
+            w0 = w0n;
+            if (gn != g) {
+                g = gn;
+                const long r0 = (kh.qrow0 + g * kh.qrow_step + k0) * D, c0 = kh.cbase + g * kh.cbase_step + ks * kh.cstride + k0;
+                Qg = q + r0;
+                Gg = dout + r0;
+                cag = ca + c0;
+                cbg = cb + c0;
             }
-            if (mask[i.r >> 6] >> (i.r & 63) & 1) return i;
+            w0n += 64;
+            if (w0n >= nq) {
+                w0n = 0;
+                ++gn;
+                turn = (turn - nq) & (NWS - 1);
+                fg += (long)nqb_arg * 4;
+            }
+            if (gn < G) fn = w0n + lane < nq ? fg[w0n + lane] : 0x7fffffff;
         }
+        r = w0 + __builtin_ctzll(todo);
+        todo &= todo - 1;
+        return true;
     };
+    const uint32_t base = lds_offset(smem) + wave * WAVE;
+    int off[C::LOADS];
+    subtile_offsets<D, false>(off, lane);
     float cn0 = 0.0f, cn1 = 0.0f;
-    auto fetch = [&](Item it, int st) __attribute__((always_inline)) {
-        const float* cag = ca + kh.cbase + it.g * kh.cbase_step + ks * kh.cstride;
-        const float* cbg = cb + kh.cbase + it.g * kh.cbase_step + ks * kh.cstride;
-        const int j = (ks + it.r) * 32 + n;
-        cn0 = j < T ? cag[j] : INFINITY;                 // rows past T: A, G and dZ are zero
-        cn1 = j < T ? cbg[j] : 0.0f;
-        const long r0 = kh.qrow0 + it.g * kh.qrow_step;
-        stage_subtile<D, false>(q + r0 * D, ks + it.r, T, mine + st * 2 * C::SUB, lane);
-        stage_subtile<D, false>(dout + r0 * D, ks + it.r, T, mine + st * 2 * C::SUB + C::SUB, lane);
+    auto fetch = [&](int r, int st) __attribute__((always_inline)) {
+        const int rows = r == nq - 1 ? nlast : 32;
+        const unsigned at = r * 32 + min(n, rows - 1);
+        cn0 = cag[at];
+        cn1 = cbg[at];
+        stage_rows<D>(Qg + (long)r * 32 * D, rows, base + st * 2 * C::SUB, off, lane);
+        stage_rows<D>(Gg + (long)r * 32 * D, rows, base + st * 2 * C::SUB + C::SUB, off, lane);
     };
-    Item it = next_item(Item{0, wave});
-    if (it.g < G) fetch(it, 0);
-    bf16x8 kf[D / 16], vf[D / 16];
+    // K and V pass through the second buffer of the first wave
+    const uint32_t k_at = lds_offset(smem) + 2 * C::SUB, v_at = k_at + C::SUB;
+    stage_strip<D>(k + kh.base + (long)k0 * D, v + kh.base + (long)k0 * D, min(T - k0, 32), k_at, v_at, wave, lane);
+    int r = 0;
+    bool more = next(r);
+    if (more) fetch(r, 0);
+    own_landed();
+    barrier_nofence();
+    bf16x8 kf[D / 16], vf[D / 16];                       // A operands: MFMA row n <- key perm_row(n)
     {
-        const long kr = min(k0 + perm_row(n), T - 1);
-        const u32x4* kp = reinterpret_cast<const u32x4*>(k + kh.base + kr * D + 8 * hh);
-        const u32x4* vp = reinterpret_cast<const u32x4*>(v + kh.base + kr * D + 8 * hh);
+        const uint32_t at = tile_off_perm<D>(perm_row(n), hh);
 #pragma unroll
         for (int s = 0; s < D / 16; ++s) {
-            kf[s] = __builtin_bit_cast(bf16x8, kp[2 * s]);
-            vf[s] = __builtin_bit_cast(bf16x8, vp[2 * s]);
+            kf[s] = __builtin_bit_cast(bf16x8, lds_load16((k_at + at) ^ (s << 5)));
+            vf[s] = __builtin_bit_cast(bf16x8, lds_load16((v_at + at) ^ (s << 5)));
         }
     }
-#pragma unroll
-    for (int s = 0; s < D / 16; ++s) { asm volatile("" :: "v"(kf[s])); asm volatile("" :: "v"(vf[s])); }
-    const uint32_t base = lds_offset(mine);
+    barrier_lds();                                       // the buffer is free
     const uint32_t qb = base + tile_off_nat<D>(n, hh);                  // B operands, ^ (s << 5)
     uint32_t qtr[2];                                                    // transposing reads, ^ (b << 6)
 #pragma unroll
@@ -1803,14 +1864,16 @@ bwd_dkv_small_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict_
 #pragma unroll
         for (int r = 0; r < 16; ++r) { dkacc[b][r] = 0.0f; dvacc[b][r] = 0.0f; }
 
-    for (int st = 0; it.g < G; st ^= 1) {
+    for (int st = 0; more; st ^= 1) {
         own_landed();
         float car = cn0, cbl = cn1;
         asm volatile("" : "+v"(car), "+v"(cbl));
-        const Item nx = next_item(Item{it.g, it.r + NWS});
-        if (nx.g < G) fetch(nx, st ^ 1);
         const uint32_t buf = st * 2 * C::SUB;
-        const bool diag = it.r == 0;
+        const bool diag = r == 0;
+        if (r == nq - 1 && n >= nlast) {                 // rows past T: A, G and dZ are zero
+            car = INFINITY;
+            cbl = 0.0f;
+        }
         if (diag && n == 0) car = cbl = 0.0f;            // as in bwd_dkv_kernel
         u32x4 qw[D / 16], gw[D / 16];
 #pragma unroll
@@ -1818,6 +1881,8 @@ bwd_dkv_small_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict_
             qw[s] = lds_load16((qb + buf) ^ (s << 5));
             gw[s] = lds_load16(((qb + buf) ^ (s << 5)) + C::SUB);
         }
+        more = next(r);                                  // while the operands are on their way
+        if (more) fetch(r, st ^ 1);
         f32x16 sacc, pacc;
 #pragma unroll
         for (int r = 0; r < 16; ++r) { sacc[r] = 0.0f; pacc[r] = 0.0f; }
@@ -1826,6 +1891,16 @@ bwd_dkv_small_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict_
             sacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[s], __builtin_bit_cast(bf16x8, qw[s]), sacc, 0, 0, 0);
             pacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[s], __builtin_bit_cast(bf16x8, gw[s]), pacc, 0, 0, 0);
         }
+        // the second products' operands land during the element-wise work
+        bf16x8 gop[D / 16], qop[D / 16];
+#pragma unroll
+        for (int b = 0; b < D / 32; ++b)
+#pragma unroll
+            for (int s2 = 0; s2 < 2; ++s2) {
+                const uint32_t x0 = ((qtr[0] + buf) ^ (b << 6)) + 16 * s2 * C::ROW, x1 = ((qtr[1] + buf) ^ (b << 6)) + 16 * s2 * C::ROW;
+                gop[2 * b + s2] = tr_pair_at(x0 + C::SUB, x1 + C::SUB);
+                qop[2 * b + s2] = tr_pair_at(x0, x1);
+            }
         Chain ch;
         const bool fits = diag ? subtile_stage1<true>(ch, sacc, c2, n, hh) : subtile_stage1<false>(ch, sacc, c2, n, hh);
         if (__builtin_expect(__builtin_amdgcn_ballot_w64(!fits) != 0, 0)) {
@@ -1857,32 +1932,33 @@ bwd_dkv_small_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict_
         for (int b = 0; b < D / 32; ++b)
 #pragma unroll
             for (int s2 = 0; s2 < 2; ++s2) {
-                const uint32_t x0 = ((qtr[0] + buf) ^ (b << 6)) + 16 * s2 * C::ROW, x1 = ((qtr[1] + buf) ^ (b << 6)) + 16 * s2 * C::ROW;
-                dvacc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(at[s2], tr_pair_at(x0 + C::SUB, x1 + C::SUB), dvacc[b], 0, 0, 0);
-                dkacc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(zt[s2], tr_pair_at(x0, x1), dkacc[b], 0, 0, 0);
+                dvacc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(at[s2], gop[2 * b + s2], dvacc[b], 0, 0, 0);
+                dkacc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(zt[s2], qop[2 * b + s2], dkacc[b], 0, 0, 0);
             }
-        it = nx;
     }
 
-    // ---- the waves' shares added up, in a fixed order: dV, then dK
-    float* const red = reinterpret_cast<float*>(smem);
+    // ---- the waves' shares added up, in a fixed order
+    float* const red = reinterpret_cast<float*>(smem);   // [matrix][wave][32][D]
+    static_assert(2 * NWS * 32 * D * 4 <= NWS * WAVE, "the partial gradients fit");
+    barrier_lds();                                       // everyone is done with the tiles
 #pragma unroll
-    for (int mat = 0; mat < 2; ++mat) {
-        barrier_lds();                                   // everyone is done with the tiles, or with dV
+    for (int b = 0; b < D / 32; ++b)
 #pragma unroll
-        for (int b = 0; b < D / 32; ++b)
+        for (int r = 0; r < 16; ++r) {
+            const int at = (wave * 32 + 8 * (r >> 2) + 4 * hh + (r & 3)) * D + 32 * b + n;
+            red[at] = dvacc[b][r];
+            red[NWS * 32 * D + at] = dkacc[b][r];
+        }
+    barrier_lds();
 #pragma unroll
-            for (int r = 0; r < 16; ++r)
-                red[(wave * 32 + 8 * (r >> 2) + 4 * hh + (r & 3)) * D + 32 * b + n] = mat == 0 ? dvacc[b][r] : dkacc[b][r];
-        barrier_lds();
+    for (int mat = 0; mat < 2; ++mat)
         for (int i = tid; i < 32 * D / 4; i += NTHR) {
             const int row = i / (D / 4), c = 4 * (i % (D / 4));
             f32x4 x = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-            for (int w = 0; w < NWS; ++w) x += *reinterpret_cast<const f32x4*>(&red[(w * 32 + row) * D + c]);
+            for (int w = 0; w < NWS; ++w) x += *reinterpret_cast<const f32x4*>(&red[((mat * NWS + w) * 32 + row) * D + c]);
             if (k0 + row < T) *reinterpret_cast<f32x4*>((mat == 0 ? dv : dk) + kh.base + (long)(k0 + row) * D + c) = mat == 0 ? x : x * scale;
         }
-    }
 }
 
 // ------------------------------------------------------------------ gradient of the remainder bias

@@ -43,6 +43,13 @@ def test_strips_of_groups(sb, oracle, gen, H, Hkv, T, d):
     run(sb, oracle, gen, H, Hkv, T, d, range(Hkv), seed=40)
 
 
+@pytest.mark.parametrize("H,Hkv,T", [(2, 2, 2049), (4, 2, 2111), (3, 1, 2080)])
+@pytest.mark.parametrize("d", [32, 64, 128])
+def test_strips_of_two_words(sb, oracle, gen, H, Hkv, T, d):
+    """More than 64 strips of queries reach a strip of keys, in some heads; in the near one none of the second 64 does."""
+    run(sb, oracle, gen, H, Hkv, T, d, range(Hkv), seed=60)
+
+
 @pytest.mark.parametrize("d", [32, 64, 128])
 def test_longest_strips(sb, oracle, gen, d):
     """128 subtiles a row, the most the kernels' arrays hold; one more row takes the 128-row blocks."""
