@@ -1484,22 +1484,6 @@ __device__ __forceinline__ void stage_rows(const uint16_t* src, int rows, uint32
     dma16_to_lds_run_at(scalar_base(src), o, lds);
 }
 
-// one 32-row subtile of X (rows 32*sub ..), by one wave; rows past `last` are clamped
-template <int D, bool PERM>
-__device__ __forceinline__ void stage_subtile(const uint16_t* X, int sub, int T, char* dst, int lane)
-{
-    using C = SmallCfg<D>;
-    constexpr int CPR = C::ROW / 16;
-    const uint16_t* xb = X + (long)sub * 32 * D;
-    const int last = T - 1 - sub * 32;
-#pragma unroll
-    for (int i = 0; i < C::SUB / 1024; ++i) {
-        const int row = i * (1024 / C::ROW) + lane / CPR;
-        const int swz = PERM ? swz_perm<D>(row) : swz_nat<D>(row);
-        dma16_to_lds_saddr(xb, (min(row, last) * D + (((lane % CPR) ^ swz) << 3)) * 2, dst + i * 1024);
-    }
-}
-
 // The strip's own 32 rows of two matrices, into the places x_at and y_at in LDS: whole rows and once, every wave its share.  (As
 // operands from memory, 32 bytes of 32 rows an instruction and all of it by every wave, the two took a CU 2000, 4800 and 7000 clocks
 // at d = 32, 64 and 128: a tenth to a third of a near strip's time.)
@@ -1518,10 +1502,12 @@ __device__ __forceinline__ void stage_strip(const uint16_t* X, const uint16_t* Y
 // what a wave has staged has landed, and its reads of the buffer to be refilled have returned
 __device__ __forceinline__ void own_landed() { asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory"); }
 
-// Query-stationary pass.  First the softplus totals of all subtiles, from the logits alone, every wave its
-// share; their sums from the diagonal on are every subtile's carry, and say where the rows are exhausted.
-// Then the sweep from there to the diagonal, a round of one subtile per wave at a time: A and G of the round, one barrier
-// to add up the G of the subtiles further left, dZ.
+// Query-stationary pass: a sweep from the left to the diagonal, a round of one subtile per wave at a time: logits and chains;
+// one barrier to add up the softplus totals; A and G; one barrier to add up the G of the subtiles further left; dZ.  What the
+// carries start from is m.  Where m says that the rows are exhausted on the way, the totals are taken first, from the diagonal
+// on, until they are: that is where the sweep starts, and the sums are its carries.
+// Against totals of all subtiles first, in every strip, and one wave adding them up one after the other, all heads far, then none, us:
+// B2 H4 T777 d32 12.5 -> 9.1, 7.3 -> 6.7; B1 H4 T4000 d64 56 -> 38, 22.5 -> 13.3; B1 H8 T700 d128 21.3 -> 16.6, 14.2 -> 12.5.
 template <int D>
 __global__ void __launch_bounds__(64 * SmallCfg<D>::NWS)
 bwd_dq_small_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
@@ -1535,9 +1521,8 @@ bwd_dq_small_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
     using C = SmallCfg<D>;
     constexpr int NWS = C::NWS, NTHR = 64 * NWS;
     __shared__ __attribute__((aligned(1024))) char smem[NWS * C::WAVE];
-    __shared__ float s_car[C::MAXSUB][32];              // totals, then carries, per subtile and row
-    __shared__ float s_g[2][NWS][32];                   // a round's sums of G
-    __shared__ int s_start;
+    __shared__ __attribute__((aligned(1024))) float s_car[C::MAXSUB][32];      // carries per subtile and row
+    __shared__ float s_l[2][NWS][32], s_g[2][NWS][32];  // a round's softplus totals, and sums of G
     static_assert(NWS * 32 * D * 4 <= NWS * C::WAVE, "the partial gradients fit");
 
     asm volatile("" :: "s"(q), "s"(k), "s"(v), "s"(m), "s"(dout), "s"(T_arg), "s"(G));
@@ -1563,10 +1548,10 @@ bwd_dq_small_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
     const int n = lane & 31, hh = lane >> 5, gg = lane >> 4, li = lane & 15;
     const int strip = nstrip - 1 - i;
     const int q0 = strip * 32;
+    const int nlast = min(T - q0, 32);                  // rows of the strip, and of the subtile on the diagonal
     const uint16_t* Kg = k + kvrow0 * D;
     const uint16_t* Vg = v + kvrow0 * D;
-    char* const mine = smem + wave * C::WAVE;
-    const uint32_t base = lds_offset(mine);
+    const uint32_t base = lds_offset(smem) + wave * C::WAVE;
     const uint32_t ka = base + tile_off_perm<D>(perm_row(n), hh);       // A operands, ^ (s << 5)
     uint32_t ktr[2];                                                    // transposing reads, ^ (b << 6)
 #pragma unroll
@@ -1574,19 +1559,32 @@ bwd_dq_small_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
         ktr[t] = base + tile_off_perm<D>(16 * (gg >> 1) + (li >> 2) + 4 * t, 2 * (gg & 1) + ((li & 3) >> 1)) + 8 * (li & 1);
     const float scale = 1.0f / sqrtf((float)D);
     const float c2 = SB_LOG2E * scale;
+    int off[C::LOADS];
+    subtile_offsets<D, true>(off, lane);
+    auto stage_k = [&](int sub, int st) __attribute__((always_inline)) {
+        stage_rows<D>(Kg + (long)sub * 32 * D, sub == strip ? nlast : 32, base + st * 2 * C::SUB, off, lane);
+    };
+    auto stage_v = [&](int sub, int st) __attribute__((always_inline)) {
+        stage_rows<D>(Vg + (long)sub * 32 * D, sub == strip ? nlast : 32, base + st * 2 * C::SUB + C::SUB, off, lane);
+    };
 
-    if (wave <= strip) stage_subtile<D, true>(Kg, wave, T, mine, lane);
+    // all that is needed whatever m says, at once; Q and dO pass through the place of the carries
+    float a2 = -m[row0 + min(q0 + n, T - 1)] * SB_LOG2E;
+    static_assert(2 * C::SUB <= (int)sizeof(s_car), "the strip's rows fit");
+    const uint32_t x_at = lds_offset(reinterpret_cast<const char*>(s_car)), y_at = x_at + C::SUB;
+    stage_strip<D>(q + (row0 + q0) * D, dout + (row0 + q0) * D, nlast, x_at, y_at, wave, lane);
+    if (wave <= strip) stage_k(wave, 0);
+    own_landed();
+    barrier_nofence();
     bf16x8 qf[D / 16], gf[D / 16];
-    const int jq = min(q0 + n, T - 1);
     {
-        const u32x4* qs = reinterpret_cast<const u32x4*>(q + (row0 + jq) * D + 8 * hh);
-        const u32x4* gs = reinterpret_cast<const u32x4*>(dout + (row0 + jq) * D + 8 * hh);
+        const uint32_t at = tile_off_perm<D>(n, hh);
 #pragma unroll
         for (int s = 0; s < D / 16; ++s) {
-            u32x4 a = qs[2 * s], g = gs[2 * s];
-            if (q0 + n >= T) g = u32x4{0u, 0u, 0u, 0u};   // rows past T contribute nothing
-            qf[s] = __builtin_bit_cast(bf16x8, a);
-            gf[s] = __builtin_bit_cast(bf16x8, g);
+            qf[s] = __builtin_bit_cast(bf16x8, lds_load16((x_at + at) ^ (s << 5)));
+            u32x4 x = lds_load16((y_at + at) ^ (s << 5));
+            if (n >= nlast) x = u32x4{0u, 0u, 0u, 0u};   // rows past T contribute nothing
+            gf[s] = __builtin_bit_cast(bf16x8, x);
         }
     }
     float bsum = 0.0f;                      // sum of G over the keys left of the round
@@ -1601,10 +1599,8 @@ bwd_dq_small_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
         }
         float d_lo, d_hi;
         both_halves(dot, d_lo, d_hi);
-        bsum = fast_exp2(m[row0 + jq] * SB_LOG2E) * (d_lo + d_hi);
+        bsum = fast_exp2(-a2) * (d_lo + d_hi);
     }
-#pragma unroll
-    for (int s = 0; s < D / 16; ++s) { asm volatile("" :: "v"(qf[s])); asm volatile("" :: "v"(gf[s])); }
     asm volatile("" :: "v"(bsum));
 
     auto rows_by = [&](uint32_t rows, const bf16x8 (&f)[D / 16]) __attribute__((always_inline)) {
@@ -1619,45 +1615,54 @@ bwd_dq_small_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
             acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, w[s]), f[s], acc, 0, 0, 0);
         return acc;
     };
+    auto sums_of = [&](const float (&a)[NWS][32], float (&x)[NWS]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int w = 0; w < NWS; ++w) x[w] = a[w][n];
+    };
 
-    // ---- totals
-    for (int sub = wave, st = 0; sub <= strip; sub += NWS, st ^= 1) {
-        own_landed();
-        if (sub + NWS <= strip) stage_subtile<D, true>(Kg, sub + NWS, T, mine + (st ^ 1) * 2 * C::SUB, lane);
-        const f32x16 s = rows_by(ka + st * 2 * C::SUB, qf);
-        const float l = sub == strip ? sp2_total<true>(s, c2, n, hh) : sp2_total<false>(s, c2, n, hh);
-        float l_lo, l_hi;
-        both_halves(l, l_lo, l_hi);
-        if (hh == 0) s_car[sub][n] = l_lo + l_hi;
-    }
-    barrier_lds();
-    if (wave == 0) {                                     // both halves alike
+    int start = 0;
+    const bool ends = __builtin_amdgcn_ballot_w64(!(a2 < CARRY_EXHAUSTED)) != 0;     // some row is exhausted on the way: all may be
+    if (!ends) {
+        if (wave <= strip) stage_v(wave, 0);
+    } else {
+        // ---- totals from the diagonal on.  A round takes subtiles lo .. lo + NWS - 1
         float right = 0.0f;
-        int start = strip;
-        // four totals are fetched at a time: one LDS latency for them, not one for each (B1 H4 T4000 d64 52.0 -> 49.9 us)
         bool more = true;
-        for (int top = strip; more && top >= 0; top -= 4) {
-            float t[4];
+        for (int top = strip, st = 0; more && top >= 0; top -= NWS, st ^= 1) {
+            const int lo = max(top - (NWS - 1), 0), sub = lo + wave;
+            float l = 0.0f;
+            if (sub <= top) {
+                if (top == strip && lo > 0) stage_k(sub, 0);
+                own_landed();
+                if (lo > 0 && max(lo - NWS, 0) + wave < lo) stage_k(max(lo - NWS, 0) + wave, st ^ 1);
+                const f32x16 s = rows_by(ka + st * 2 * C::SUB, qf);
+                l = sub == strip ? sp2_total<true>(s, c2, n, hh) : sp2_total<false>(s, c2, n, hh);
+            }
+            float l_lo, l_hi, t[NWS];
+            both_halves(l, l_lo, l_hi);
+            if (hh == 0) s_l[st][wave][n] = l_lo + l_hi;
+            barrier_lds();                               // (the first: Q and dO have been read)
+            sums_of(s_l[st], t);
 #pragma unroll
-            for (int x = 0; x < 4; ++x) t[x] = s_car[max(top - x, 0)][n];
-#pragma unroll
-            for (int x = 0; x < 4; ++x) {
-                const int sub = top - x;
-                more = more && sub >= 0;
+            for (int w = NWS - 1; w >= 0; --w) {
+                if (lo + w > top) continue;
                 if (more) {
-                    if (hh == 0) s_car[sub][n] = right;
-                    more = __builtin_amdgcn_ballot_w64(!(right >= CARRY_EXHAUSTED)) != 0;
+                    if (wave == 0 && hh == 0) s_car[lo + w][n] = right;
+                    more = __builtin_amdgcn_ballot_w64(!(right >= CARRY_EXHAUSTED)) != 0;      // alike in all waves
                 }
                 if (more) {
-                    start = sub;
-                    right += t[x];
+                    start = lo + w;
+                    right += t[w];
                 }
             }
         }
-        if (lane == 0) s_start = start;
+        own_landed();                                    // a subtile asked for before the end was found
+        if (start + wave <= strip) {
+            stage_k(start + wave, 0);
+            stage_v(start + wave, 0);
+        }
+        barrier_lds();                                   // the carries are there
     }
-    barrier_lds();
-    const int start = __builtin_amdgcn_readfirstlane(s_start);
     // (where this pass takes strips the key-stationary one does too, so that nobody reads the places of strips that do not exist)
     if (tid == 0) first[(long)bh * nqb_arg * 4 + strip] = (uint16_t)start;
 
@@ -1669,23 +1674,20 @@ bwd_dq_small_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
         for (int r = 0; r < 16; ++r) dqacc[b][r] = 0.0f;
     float* const cag = ca + cbase;
     float* const cbg = cb + cbase;
-    auto stage = [&](int sub, int st) __attribute__((always_inline)) {
-        stage_subtile<D, true>(Kg, sub, T, mine + st * 2 * C::SUB, lane);
-        stage_subtile<D, true>(Vg, sub, T, mine + st * 2 * C::SUB + C::SUB, lane);
-    };
-    if (start + wave <= strip) stage(start + wave, 0);
     for (int sub0 = start, st = 0; sub0 <= strip; sub0 += NWS, st ^= 1) {
         const int sub = sub0 + wave;
         const bool there = sub <= strip;
         Chain ch;
         SubtileOut so;
         so.g_tot = 0.0f;
-        float car = 0.0f;
+        float car = 0.0f, l_tot = 0.0f;
         const uint32_t buf = st * 2 * C::SUB;
         if (there) {
             own_landed();
-            if (sub + NWS <= strip) stage(sub + NWS, st ^ 1);
-            car = s_car[sub][n];
+            if (sub + NWS <= strip) {
+                stage_k(sub + NWS, st ^ 1);
+                stage_v(sub + NWS, st ^ 1);
+            }
             const f32x16 s = rows_by(ka + buf, qf);
             const bool fits = sub == strip ? subtile_stage1<true>(ch, s, c2, n, hh) : subtile_stage1<false>(ch, s, c2, n, hh);
             if (__builtin_expect(__builtin_amdgcn_ballot_w64(!fits) != 0, 0)) {
@@ -1693,28 +1695,48 @@ bwd_dq_small_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
                 if (sub == strip) subtile_stage1_log<true>(ch, again, c2, n, hh);
                 else subtile_stage1_log<false>(ch, again, c2, n, hh);
             }
-            subtile_g<false, false>(so, ch, rows_by(ka + buf + C::SUB, gf), car, hh);
+            float l_lo, l_hi;
+            both_halves(ch.l, l_lo, l_hi);
+            l_tot = l_lo + l_hi;
         }
-        if (hh == 0) s_g[st][wave][n] = so.g_tot;
-        barrier_lds();
-        float left = bsum;
-        for (int w = 0; w < NWS; ++w) {
-            if (w == wave) left = bsum;
-            bsum += s_g[st][w][n];
-        }
-        if (there) {
-            if (hh == 0 && q0 + n < T) {
-                const long ci = (long)sub * cstride + q0 + n;
-                cag[ci] = car;
-                cbg[ci] = left;
+        if (ends) {
+            car = s_car[min(sub, strip)][n];
+        } else {
+            float t[NWS];
+            if (hh == 0) s_l[st][wave][n] = l_tot;
+            barrier_lds();
+            sums_of(s_l[st], t);
+#pragma unroll
+            for (int w = 0; w < NWS; ++w) {
+                a2 -= t[w];
+                if (w == wave) car = a2;
             }
-            subtile_dz(so, ch, left, hh);
-            bf16x8 kt[D / 16];
+        }
+        bf16x8 kt[D / 16];
+        if (there) {
+            subtile_g<false, false>(so, ch, rows_by(ka + buf + C::SUB, gf), car, hh);
 #pragma unroll
             for (int b = 0; b < D / 32; ++b)
 #pragma unroll
                 for (int s = 0; s < 2; ++s)
                     kt[2 * b + s] = tr_pair_at(((ktr[0] + buf) ^ (b << 6)) + 8 * s * C::ROW, ((ktr[1] + buf) ^ (b << 6)) + 8 * s * C::ROW);
+        }
+        if (hh == 0) s_g[st][wave][n] = so.g_tot;
+        barrier_lds();
+        float left = bsum, t[NWS];
+        sums_of(s_g[st], t);
+#pragma unroll
+        for (int w = 0; w < NWS; ++w) {
+            if (w == wave) left = bsum;
+            bsum += t[w];
+        }
+        if (there) {
+            if (hh == 0 && n < nlast) {
+                const long ci = (long)sub * cstride + q0 + n;
+                cag[ci] = car;
+                cbg[ci] = left;
+            }
+            subtile_dz(so, ch, left, hh);
 #pragma unroll
             for (int b = 0; b < D / 32; ++b)
 #pragma unroll
