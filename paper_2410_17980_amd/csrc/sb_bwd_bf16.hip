@@ -264,6 +264,96 @@ __device__ __forceinline__ void store_strip(float* out, int rows, const f32x16 (
     }
 }
 
+// ------------------------------------------------------------------ gradient of the remainder bias
+// dr[h][c] = sum over the batch and the rows j of exp(m_j) dO[j][c] (Appendix C: the
+// output holds (stick left of row j) * r_h).  Two deterministic steps: per (batch entry,
+// head, 128-row chunk) partial sums, then, per head, their sum in a fixed order.  They are the last workgroups of the launches of
+// the two passes, the first step's behind the query-stationary blocks, the second's behind the key-stationary ones, and fill CUs
+// that have no block left: as launches of their own they took 5 us of 25 (B2 H4 T124 d64), 10 us of 220 (B4 H12 T2048 d128).
+// Rows that used up their stick (exp(m) = 0 in fp32) are not read (nor is a NaN in them).  Both steps are a few memory
+// latencies long, all loads of a thread in flight at once.
+constexpr int DR_ROWS = 128;
+struct BiasGrad {
+    float* part;              // [BH][nchunk][D]
+    float* dr;                // [H][D]
+    int work;                 // workgroups of the pass; those from here on are the bias's
+    int B, H, nchunk;
+};
+
+// part of head bh's rows from m, dout on, of which `rows` (at most DR_ROWS) exist; red: (NTHR * 8 / D) * (D + 4) floats of LDS
+template <int D, int NTHR>
+__device__ __forceinline__ void bias_partial(float* red, const float* __restrict__ m, const uint16_t* __restrict__ dout, float* __restrict__ out,
+                                             int rows, int tid)
+{
+    constexpr int CG = D / 8;                 // lanes per row, eight columns each
+    constexpr int RG = NTHR / CG;             // rows per pass
+    constexpr int NP = DR_ROWS / RG;
+    static_assert(NP * RG == DR_ROWS && D <= NTHR, "whole passes");
+    const int cg = tid % CG, rg = tid / CG;
+    float w[NP];
+    u32x4 g[NP];
+#pragma unroll
+    for (int i = 0; i < NP; ++i) w[i] = i * RG + rg < rows ? __expf(m[i * RG + rg]) : 0.0f;
+#pragma unroll
+    for (int i = 0; i < NP; ++i) {
+        g[i] = u32x4{0u, 0u, 0u, 0u};
+        if (w[i] != 0.0f) g[i] = *reinterpret_cast<const u32x4*>(dout + (i * RG + rg) * D + 8 * cg);
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        float a0 = 0.0f, a1 = 0.0f;
+#pragma unroll
+        for (int i = 0; i < NP; ++i) {
+            a0 += w[i] * __builtin_bit_cast(float, g[i][e] << 16);
+            a1 += w[i] * __builtin_bit_cast(float, g[i][e] & 0xffff0000u);
+        }
+        red[rg * (D + 4) + 8 * cg + 2 * e] = a0;
+        red[rg * (D + 4) + 8 * cg + 2 * e + 1] = a1;
+    }
+    __syncthreads();
+    if (tid < D) {
+        float s = 0.0f;
+#pragma unroll 16
+        for (int i = 0; i < RG; ++i) s += red[i * (D + 4) + tid];
+        out[tid] = s;
+    }
+}
+// chunk `at` of the launch, of all heads and (sequences of a packed batch: cu) batch entries
+template <int D, int NTHR>
+__device__ __forceinline__ void bias_partial_at(float* red, int at, const BiasGrad& bias, const float* __restrict__ m, const uint16_t* __restrict__ dout,
+                                                int T, const int* __restrict__ cu, int Ttot, int tid)
+{
+    const int bh = at / bias.nchunk, chunk = at - bh * bias.nchunk;
+    long row0 = (long)bh * T;
+    if (cu) {                                 // bh = sequence * H + head; chunks past the sequence's end give 0
+        const int c0 = cu[bh / bias.H];
+        T = c0 < 0 ? 0 : min(min(cu[bh / bias.H + 1], Ttot) - c0, T);
+        row0 = (bh % bias.H) * (long)Ttot + c0;
+    }
+    row0 += chunk * DR_ROWS;
+    bias_partial<D, NTHR>(red, m + row0, dout + row0 * D, bias.part + (long)at * D, min(T - chunk * DR_ROWS, DR_ROWS), tid);
+}
+
+// head h's partial sums; red: NTHR floats of LDS
+template <int D, int NTHR>
+__device__ __forceinline__ void bias_sum(float* red, const BiasGrad& bias, int h, int tid)
+{
+    constexpr int NG = NTHR / D;              // groups of threads share the (batch entry, chunk) pairs
+    const int c = tid % D, n = bias.B * bias.nchunk;
+    float s = 0.0f;
+#pragma unroll 16
+    for (int i = tid / D; i < n; i += NG)
+        s += bias.part[((long)(i / bias.nchunk * bias.H + h) * bias.nchunk + i % bias.nchunk) * D + c];
+    red[tid] = s;
+    __syncthreads();
+    if (tid < D) {
+        float t = 0.0f;
+#pragma unroll
+        for (int i = 0; i < NG; ++i) t += red[i * D + tid];
+        bias.dr[h * D + tid] = t;
+    }
+}
+
 // ------------------------------------------------------------------ dQ kernel
 // VL (both kernels): packed variable-length batch, tensors [H][Ttot][D] ([H/G][Ttot][D] for
 // k, v, dk, dv) with sequence s at rows cu[s] .. cu[s+1]-1.  BH counts (sequence, head)
@@ -278,7 +368,7 @@ bwd_dq_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
               const uint16_t* __restrict__ dout, float* __restrict__ dq,
               float* __restrict__ ca, float* __restrict__ cb, uint16_t* __restrict__ first,
               int T_arg, int BH, int H, int G, int nqb_arg, int nt32, const int* __restrict__ cu, int Ttot,
-              int run, int first_wg)
+              int run, BiasGrad bias, int first_wg)
 {
     using C = StageCfg<D>;
     __shared__ __attribute__((aligned(1024))) char smem[2 * C::STAGE];
@@ -287,6 +377,13 @@ bwd_dq_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     // what the first loads need is fetched together with the share, not behind the branches of share_of()
     asm volatile("" :: "s"(q), "s"(k), "s"(v), "s"(m), "s"(dout), "s"(T_arg), "s"(G));
     const int wg = first_wg + blockIdx.x;
+    if constexpr (RB) {
+        static_assert(NTHREADS * 8 / D * (D + 4) * 4 <= 2 * C::STAGE, "the partial sums fit");
+        if (wg >= bias.work) {
+            bias_partial_at<D, NTHREADS>(reinterpret_cast<float*>(smem), wg - bias.work, bias, m, dout, T_arg, VL ? cu : nullptr, Ttot, threadIdx.x);
+            return;
+        }
+    }
     const Share sh = in_scalars(share_of(wg, BH, run));
     const int bh = sh.bh;
     int T = T_arg, nqb = nqb_arg;
@@ -714,7 +811,7 @@ bwd_dkv_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
                const float* __restrict__ ca, const float* __restrict__ cb,
                float* __restrict__ dk, float* __restrict__ dv, const uint32_t* __restrict__ first,
                int T_arg, int BH, int H, int G_arg, int nkb_arg, int nt32, const int* __restrict__ cu, int Ttot,
-               int run, int first_wg)
+               int run, BiasGrad bias, int first_wg)
 {
     using C = StageCfg<D>;
     using CK = DkvCfg<D, SP>;
@@ -723,6 +820,10 @@ bwd_dkv_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
 
     asm volatile("" :: "s"(q), "s"(k), "s"(v), "s"(dout), "s"(ca), "s"(cb), "s"(first), "s"(T_arg));   // as in bwd_dq_kernel
     const int wg = first_wg + blockIdx.x;
+    if (wg >= bias.work) {
+        bias_sum<D, SP * NTHREADS>(reinterpret_cast<float*>(smem), bias, wg - bias.work, threadIdx.x);
+        return;
+    }
     const Share sh = in_scalars(share_of(wg, BH, run));
     const int bh = sh.bh;
 
@@ -1052,7 +1153,7 @@ bwd_dkv_pair_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
                     const float* __restrict__ ca, const float* __restrict__ cb,
                     float* __restrict__ dk, float* __restrict__ dv, const uint32_t* __restrict__ first,
                     int T_arg, int BH, int H, int G_arg, int nkb_arg, int nqb_arg, int nt32,
-                    const int* __restrict__ cu, int Ttot, int first_wg)
+                    const int* __restrict__ cu, int Ttot, BiasGrad bias, int first_wg)
 {
     using C = StageCfg<D>;
     using CK = Dkv3Cfg<D, KS>;
@@ -1062,6 +1163,10 @@ bwd_dkv_pair_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
     __shared__ __attribute__((aligned(1024))) char smem[CK::LDS_BYTES];
 
     const int wg = first_wg + blockIdx.x;
+    if (wg >= bias.work) {
+        bias_sum<D, 64 * NW2>(reinterpret_cast<float*>(smem), bias, wg - bias.work, threadIdx.x);
+        return;
+    }
     const Share sh = in_scalars(PAIRS ? share_in_pairs(wg, nkb_arg) : share_of(wg, BH, -1));
     const int bh = sh.bh;
     if (bh >= BH) return;
@@ -1516,7 +1621,7 @@ bwd_dq_small_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
                     const uint16_t* __restrict__ dout, float* __restrict__ dq,
                     float* __restrict__ ca, float* __restrict__ cb, uint16_t* __restrict__ first,
                     int T_arg, int BH, int H, int G, int n_arg, int nqb_arg, int nt32,       // n_arg: strips a head; packed batch: sequences
-                    const int* __restrict__ cu, int Ttot)
+                    const int* __restrict__ cu, int Ttot, BiasGrad bias)
 {
     using C = SmallCfg<D>;
     constexpr int NWS = C::NWS, NTHR = 64 * NWS;
@@ -1527,6 +1632,11 @@ bwd_dq_small_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
 
     asm volatile("" :: "s"(q), "s"(k), "s"(v), "s"(m), "s"(dout), "s"(T_arg), "s"(G));
     const int tid = threadIdx.x, lane = tid & 63;
+    static_assert(NTHR * 8 / D * (D + 4) * 4 <= (int)sizeof(smem), "the partial sums fit");
+    if ((int)blockIdx.x >= bias.work) {
+        bias_partial_at<D, NTHR>(reinterpret_cast<float*>(smem), blockIdx.x - bias.work, bias, m, dout, T_arg, cu, Ttot, tid);
+        return;
+    }
     const Share sh = in_scalars(share_of(blockIdx.x, BH, -1));
     const int head = sh.bh % H;
     int bh = sh.bh, T = T_arg, nstrip = n_arg, i = sh.i;
@@ -1771,7 +1881,7 @@ bwd_dkv_small_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict_
                      const float* __restrict__ ca, const float* __restrict__ cb,
                      float* __restrict__ dk, float* __restrict__ dv, const uint16_t* __restrict__ first,
                      int T_arg, int BH, int H, int G, int n_arg, int nqb_arg, int nt32,       // n_arg: strips a head; packed batch: sequences
-                     const int* __restrict__ cu, int Ttot)
+                     const int* __restrict__ cu, int Ttot, BiasGrad bias)
 {
     using C = SmallCfg<D>;
     constexpr int NWS = C::NWS, NTHR = 64 * NWS;
@@ -1780,8 +1890,12 @@ bwd_dkv_small_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict_
     static_assert(NWS * WAVE <= 160 * 1024, "LDS budget");
 
     asm volatile("" :: "s"(q), "s"(k), "s"(v), "s"(dout), "s"(ca), "s"(cb), "s"(first), "s"(T_arg));
-    const Share sh = in_scalars(share_of(blockIdx.x, BH, -1));
     const int tid = threadIdx.x, lane = tid & 63;
+    if ((int)blockIdx.x >= bias.work) {
+        bias_sum<D, NTHR>(reinterpret_cast<float*>(smem), bias, blockIdx.x - bias.work, tid);
+        return;
+    }
+    const Share sh = in_scalars(share_of(blockIdx.x, BH, -1));
     KvHead kh;
     int ks = sh.i;                                       // the strip; small ones have the most queries
     if (cu) {                                            // packed batch: sh.bh is the head alone, sh.i its place
@@ -1983,93 +2097,6 @@ bwd_dkv_small_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict_
         }
 }
 
-// ------------------------------------------------------------------ gradient of the remainder bias
-// dr[h][c] = sum over the batch and the rows j of exp(m_j) dO[j][c] (Appendix C: the
-// output holds (stick left of row j) * r_h).  Two deterministic steps: per (batch entry,
-// head, 128-row chunk) partial sums, then one workgroup per head adds them in a fixed order.
-// Rows that used up their stick (exp(m) = 0 in fp32) are not read (nor is a NaN in them).  Both steps are a few memory
-// latencies long, all loads of a thread in flight at once (B4 H12 T2048 d128: 31 -> 11 us; with a
-// thread per column walking over the chunks one by one the second step alone took 18).
-constexpr int DR_ROWS = 128;
-
-template <int D, bool VL>
-__global__ void __launch_bounds__(NTHREADS)
-bwd_drb_partial_kernel(const float* __restrict__ m, const uint16_t* __restrict__ dout,
-                       float* __restrict__ part, int T_arg, int nchunk, int H,
-                       const int* __restrict__ cu, int Ttot, int first_wg)
-{
-    constexpr int CG = D / 8;                 // lanes per row, eight columns each
-    constexpr int RG = NTHREADS / CG;         // rows per pass
-    constexpr int NP = DR_ROWS / RG;
-    __shared__ float red[RG][D + 4];
-    const int wg = first_wg + blockIdx.x;     // one grid dimension: no 65535 limit on the heads
-    const int bh = wg / nchunk;
-    const int chunk = wg % nchunk;
-    const int cg = threadIdx.x % CG, rg = threadIdx.x / CG;
-    int T = T_arg;
-    long row0 = (long)bh * T;
-    if constexpr (VL) {                       // bh = sequence * H + head; chunks past the sequence's end give 0
-        const int c0 = cu[bh / H];
-        T = c0 < 0 ? 0 : min(min(cu[bh / H + 1], Ttot) - c0, T_arg);
-        row0 = (bh % H) * (long)Ttot + c0;
-    }
-    float w[NP];
-    u32x4 g[NP];
-#pragma unroll
-    for (int i = 0; i < NP; ++i) {
-        const int j = chunk * DR_ROWS + i * RG + rg;
-        w[i] = j < T ? __expf(m[row0 + j]) : 0.0f;
-    }
-#pragma unroll
-    for (int i = 0; i < NP; ++i) {
-        g[i] = u32x4{0u, 0u, 0u, 0u};
-        if (w[i] != 0.0f)
-            g[i] = *reinterpret_cast<const u32x4*>(dout + (row0 + chunk * DR_ROWS + i * RG + rg) * D + 8 * cg);
-    }
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        float a0 = 0.0f, a1 = 0.0f;
-#pragma unroll
-        for (int i = 0; i < NP; ++i) {
-            a0 += w[i] * __builtin_bit_cast(float, g[i][e] << 16);
-            a1 += w[i] * __builtin_bit_cast(float, g[i][e] & 0xffff0000u);
-        }
-        red[rg][8 * cg + 2 * e] = a0;
-        red[rg][8 * cg + 2 * e + 1] = a1;
-    }
-    __syncthreads();
-    if (threadIdx.x < D) {
-        float s = 0.0f;
-#pragma unroll
-        for (int i = 0; i < RG; ++i) s += red[i][threadIdx.x];
-        part[((long)bh * nchunk + chunk) * D + threadIdx.x] = s;
-    }
-}
-
-constexpr int DR_SUM = 1024;
-
-template <int D>
-__global__ void __launch_bounds__(DR_SUM)
-bwd_drb_sum_kernel(const float* __restrict__ part, float* __restrict__ drb, int B, int H, int nchunk)
-{
-    constexpr int NG = DR_SUM / D;            // groups of threads share the (batch entry, chunk) pairs
-    __shared__ float red[NG][D];
-    const int h = blockIdx.x, c = threadIdx.x % D, grp = threadIdx.x / D;
-    const int n = B * nchunk;
-    float s = 0.0f;
-#pragma unroll 8
-    for (int i = grp; i < n; i += NG)
-        s += part[((long)(i / nchunk * H + h) * nchunk + i % nchunk) * D + c];
-    red[grp][c] = s;
-    __syncthreads();
-    if (threadIdx.x < D) {
-        float t = 0.0f;
-#pragma unroll
-        for (int i = 0; i < NG; ++i) t += red[i][c];
-        drb[h * D + c] = t;
-    }
-}
-
 // workspace layout: ca[BH][nt32][T], cb[BH][nt32][T] (fp32; [H][nt32][Ttot] for a packed
 // batch), then the start strips of the queries' 32-row strips (16 bits): [BH][nqb][4], then the
 // partial sums of the remainder-bias gradient (fp32): [BH][nchunk][D].  B, T: batch size and
@@ -2095,11 +2122,14 @@ hipError_t launch_one(const uint16_t* q, const uint16_t* k, const uint16_t* v, c
     float* part = reinterpret_cast<float*>(first + (long)BH * nqb * 4);
     const int nchunk = (T + DR_ROWS - 1) / DR_ROWS;
     const Keys keys = keys_of(B, H, Hkv, T, D, VL, Ttot);
-    const long gq = share_grid(BH, nqb, false), gk = share_grid(BHkv, nkb, keys == Keys::PAIRS);
+    const long gq = share_grid(BH, nqb, false), gk = share_grid(BHkv, nkb, keys == Keys::PAIRS), gk64 = share_grid(BHkv, nkb64, false);
     const long strips_q = pieces(B, H, T, 32, VL, Ttot), strips_k = pieces(B, Hkv, T, 32, VL, Ttot);
     const int run_q = VL || G > 1 ? -1 : share_run(BH, nqb), run_k = VL || G > 1 ? -1 : share_run(BHkv, nkb);
     // checked before the first launch, so that an error leaves nothing enqueued
-    if (gq > 0x7fffffffL || gk > 0x7fffffffL || nchunk * (long)BH > 0x7fffffffL) return hipErrorInvalidValue;
+    // workgroups of the bias's gradient behind those of the passes
+    const long bias_q = drb ? nchunk * (long)BH : 0, bias_k = drb ? H : 0;
+    if (gq + bias_q > 0x7fffffffL || gk + bias_k > 0x7fffffffL) return hipErrorInvalidValue;
+    auto bias = [&](long work) { return BiasGrad{part, drb, (int)work, B, H, nchunk}; };
     hipError_t e = hipSuccess;
 #define SB_LAUNCH(WGS, THREADS, KERNEL, ...)                                                                    \
     {                                                                                                           \
@@ -2110,47 +2140,40 @@ hipError_t launch_one(const uint16_t* q, const uint16_t* k, const uint16_t* v, c
     }
 #define SB_DQ(RBV)                                                                                              \
     if (query_strips(B, H, T, D, VL, Ttot)) {                                                                   \
-        hipLaunchKernelGGL((bwd_dq_small_kernel<D>), dim3((unsigned)strips_q), dim3(64 * SmallCfg<D>::NWS), 0, stream, \
-                           q, k, v, rb, m, dout, dq, ca, cb, first, T, VL ? H : BH, H, G, VL ? B : nt32, nqb, nt32, cu, Ttot); \
+        hipLaunchKernelGGL((bwd_dq_small_kernel<D>), dim3((unsigned)(strips_q + bias_q)), dim3(64 * SmallCfg<D>::NWS), 0, stream, \
+                           q, k, v, rb, m, dout, dq, ca, cb, first, T, VL ? H : BH, H, G, VL ? B : nt32, nqb, nt32, cu, Ttot, bias(strips_q)); \
         if ((e = hipGetLastError()) != hipSuccess) return e;                                                    \
-    } else SB_LAUNCH(gq, NTHREADS, (bwd_dq_kernel<D, RBV, VL>),                                                        \
-              q, k, v, rb, m, dout, dq, ca, cb, first, T, BH, H, G, nqb, nt32, cu, Ttot, run_q)
+    } else SB_LAUNCH(gq + bias_q, NTHREADS, (bwd_dq_kernel<D, RBV, VL>),                                        \
+              q, k, v, rb, m, dout, dq, ca, cb, first, T, BH, H, G, nqb, nt32, cu, Ttot, run_q, bias(gq))
 // d = 128 takes the paired-wave kernel (two waves per SIMD instead of one); smaller head
 // dimensions leave room for two workgroups of the one-wave-per-strip kernel per CU, which
 // is faster there (measured).
 #define SB_DKV(GQAV)                                                                                            \
     if (keys == Keys::STRIPS) {                                                                                 \
-        hipLaunchKernelGGL((bwd_dkv_small_kernel<D>), dim3((unsigned)strips_k), dim3(64 * SmallCfg<D>::NWS), 0, stream, \
-                           q, k, v, dout, ca, cb, dk, dv, first, T, VL ? Hkv : BHkv, H, G, VL ? B : nt32, nqb, nt32, cu, Ttot); \
+        hipLaunchKernelGGL((bwd_dkv_small_kernel<D>), dim3((unsigned)(strips_k + bias_k)), dim3(64 * SmallCfg<D>::NWS), 0, stream, \
+                           q, k, v, dout, ca, cb, dk, dv, first, T, VL ? Hkv : BHkv, H, G, VL ? B : nt32, nqb, nt32, cu, Ttot, bias(strips_k)); \
         if ((e = hipGetLastError()) != hipSuccess) return e;                                                    \
     } else if constexpr (D == 128) {                                                                            \
         constexpr bool CAN = !VL && !GQAV;                                                                      \
         if (keys == Keys::KEYS_64)                                                                              \
-            SB_LAUNCH(share_grid(BHkv, nkb64, false), 256, (bwd_dkv_pair_kernel<D, 2, GQAV, VL, false>),        \
-                      q, k, v, dout, ca, cb, dk, dv, first2, T, BHkv, H, G, nkb64, nqb, nt32, cu, Ttot)         \
+            SB_LAUNCH(gk64 + bias_k, 256, (bwd_dkv_pair_kernel<D, 2, GQAV, VL, false>),                         \
+                      q, k, v, dout, ca, cb, dk, dv, first2, T, BHkv, H, G, nkb64, nqb, nt32, cu, Ttot, bias(gk64)) \
         else if (CAN && keys == Keys::PAIRS)                                                                    \
-            SB_LAUNCH(gk, 512, (bwd_dkv_pair_kernel<D, 4, GQAV, VL, CAN>),                                      \
-                      q, k, v, dout, ca, cb, dk, dv, first2, T, BHkv, H, G, nkb, nqb, nt32, cu, Ttot)           \
+            SB_LAUNCH(gk + bias_k, 512, (bwd_dkv_pair_kernel<D, 4, GQAV, VL, CAN>),                             \
+                      q, k, v, dout, ca, cb, dk, dv, first2, T, BHkv, H, G, nkb, nqb, nt32, cu, Ttot, bias(gk)) \
         else                                                                                                    \
-            SB_LAUNCH(gk, 512, (bwd_dkv_pair_kernel<D, 4, GQAV, VL, false>),                                    \
-                      q, k, v, dout, ca, cb, dk, dv, first2, T, BHkv, H, G, nkb, nqb, nt32, cu, Ttot)           \
+            SB_LAUNCH(gk + bias_k, 512, (bwd_dkv_pair_kernel<D, 4, GQAV, VL, false>),                           \
+                      q, k, v, dout, ca, cb, dk, dv, first2, T, BHkv, H, G, nkb, nqb, nt32, cu, Ttot, bias(gk)) \
     } else if (keys == Keys::TWO_GROUPS) {                                                                      \
-        SB_LAUNCH(gk, 2 * NTHREADS, (bwd_dkv_kernel<D, GQAV, VL, 2>),                                           \
-                  q, k, v, dout, ca, cb, dk, dv, first2, T, BHkv, H, G, nkb, nt32, cu, Ttot, run_k);            \
+        SB_LAUNCH(gk + bias_k, 2 * NTHREADS, (bwd_dkv_kernel<D, GQAV, VL, 2>),                                  \
+                  q, k, v, dout, ca, cb, dk, dv, first2, T, BHkv, H, G, nkb, nt32, cu, Ttot, run_k, bias(gk));  \
     } else {                                                                                                    \
-        SB_LAUNCH(gk, NTHREADS, (bwd_dkv_kernel<D, GQAV, VL, 1>),                                               \
-                  q, k, v, dout, ca, cb, dk, dv, first2, T, BHkv, H, G, nkb, nt32, cu, Ttot, run_k);            \
+        SB_LAUNCH(gk + bias_k, NTHREADS, (bwd_dkv_kernel<D, GQAV, VL, 1>),                                      \
+                  q, k, v, dout, ca, cb, dk, dv, first2, T, BHkv, H, G, nkb, nt32, cu, Ttot, run_k, bias(gk));  \
     }
     if (passes & 1) {
         if (rb) { SB_DQ(true); }
         else    { SB_DQ(false); }
-        if (drb) {
-            SB_LAUNCH(nchunk * (long)BH, NTHREADS, (bwd_drb_partial_kernel<D, VL>),
-                      m, dout, part, T, nchunk, H, cu, Ttot);
-            hipLaunchKernelGGL((bwd_drb_sum_kernel<D>), dim3((unsigned)H), dim3(DR_SUM), 0, stream,
-                               part, drb, B, H, nchunk);
-            if ((e = hipGetLastError()) != hipSuccess) return e;
-        }
     }
     if (passes & 2) {
         // a packed batch always takes the grouped variant (a group of one included)
