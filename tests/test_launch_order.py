@@ -48,7 +48,7 @@ def order(tmp_path_factory):
     return get
 
 
-SHAPES = [(h, n) for h, n in itertools.product((1, 2, 3, 5, 7, 8, 9, 12, 24, 30, 32, 40, 63, 64, 65, 67, 72, 96, 128, 130, 512),
+SHAPES = [(h, n) for h, n in itertools.product((1, 2, 3, 4, 5, 6, 7, 8, 9, 12, 24, 30, 32, 40, 63, 64, 65, 67, 72, 96, 128, 130, 512),
                                                (1, 2, 3, 4, 12, 16, 31, 32, 33, 64, 128)) if h * n <= 16384]
 
 
@@ -82,6 +82,14 @@ def test_small_or_short_launches_turn_with_every_block(order, heads, nblk):
     x, got = xcds(order, heads, nblk)
     assert got == 0
     assert (x[:, 1:] != x[:, :-1]).mean() >= 0.8
+
+
+def test_few_heads_meet_every_xcd(order):
+    """Also one head alone keeps all XCDs busy."""
+    for heads in range(1, 9):
+        x, _ = xcds(order, heads, 128)
+        for h in range(heads):
+            assert np.bincount(x[h], minlength=8).max() <= 24, (heads, h)
 
 
 def test_costly_heads_are_spread(order):
