@@ -1557,7 +1557,7 @@ template <int D> struct SmallCfg {
     static constexpr int ROW = D * 2;
     static constexpr int SUB = 32 * ROW;                // one 32-row subtile of one matrix
     static constexpr int WAVE = 4 * SUB;                // two matrices, double buffered
-    static constexpr int MAXSUB = SMALL_T / 32;         // subtiles of a strip
+    static constexpr int MAXSUB = 128;                  // subtiles of a strip for whose carries there is room
     static constexpr int LOADS = SUB / 1024;            // of 16 bytes a lane, for a subtile
 };
 
@@ -1626,7 +1626,7 @@ bwd_dq_small_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
     using C = SmallCfg<D>;
     constexpr int NWS = C::NWS, NTHR = 64 * NWS;
     __shared__ __attribute__((aligned(1024))) char smem[NWS * C::WAVE];
-    __shared__ __attribute__((aligned(1024))) float s_car[C::MAXSUB][32];      // carries per subtile and row
+    __shared__ __attribute__((aligned(1024))) float s_car[C::MAXSUB][32];      // carries per subtile, from the diagonal on, and row
     __shared__ float s_l[2][NWS][32], s_g[2][NWS][32];  // a round's softplus totals, and sums of G
     static_assert(NWS * 32 * D * 4 <= NWS * C::WAVE, "the partial gradients fit");
 
@@ -1731,14 +1731,15 @@ bwd_dq_small_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
     };
 
     int start = 0;
-    const bool ends = __builtin_amdgcn_ballot_w64(!(a2 < CARRY_EXHAUSTED)) != 0;     // some row is exhausted on the way: all may be
+    bool ends = __builtin_amdgcn_ballot_w64(!(a2 < CARRY_EXHAUSTED)) != 0;     // some row is exhausted on the way: all may be
     if (!ends) {
         if (wave <= strip) stage_v(wave, 0);
     } else {
         // ---- totals from the diagonal on.  A round takes subtiles lo .. lo + NWS - 1
         float right = 0.0f;
         bool more = true;
-        for (int top = strip, st = 0; more && top >= 0; top -= NWS, st ^= 1) {
+        int top = strip;
+        for (int st = 0; more && top >= 0 && strip - top < C::MAXSUB; top -= NWS, st ^= 1) {
             const int lo = max(top - (NWS - 1), 0), sub = lo + wave;
             float l = 0.0f;
             if (sub <= top) {
@@ -1757,7 +1758,7 @@ bwd_dq_small_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
             for (int w = NWS - 1; w >= 0; --w) {
                 if (lo + w > top) continue;
                 if (more) {
-                    if (wave == 0 && hh == 0) s_car[lo + w][n] = right;
+                    if (wave == 0 && hh == 0) s_car[strip - (lo + w)][n] = right;
                     more = __builtin_amdgcn_ballot_w64(!(right >= CARRY_EXHAUSTED)) != 0;      // alike in all waves
                 }
                 if (more) {
@@ -1765,6 +1766,10 @@ bwd_dq_small_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
                     right += t[w];
                 }
             }
+        }
+        if (more && top >= 0) {                          // not among those there is room for: from the left and m, as the others
+            ends = false;
+            start = 0;
         }
         own_landed();                                    // a subtile asked for before the end was found
         if (start + wave <= strip) {
@@ -1810,7 +1815,7 @@ bwd_dq_small_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
             l_tot = l_lo + l_hi;
         }
         if (ends) {
-            car = s_car[min(sub, strip)][n];
+            car = s_car[max(strip - sub, 0)][n];
         } else {
             float t[NWS];
             if (hh == 0) s_l[st][wave][n] = l_tot;

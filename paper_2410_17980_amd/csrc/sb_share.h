@@ -48,20 +48,44 @@ inline bool take_pairs(long heads, int nblk)
 // Grids of the backward that take one strip of 32 rows a workgroup, its waves sharing the strip's other side
 // (bwd_dq_small_kernel, bwd_dkv_small_kernel), in place of 128-row blocks whose every wave has the
 // whole other side to itself.  What bounds the blocks there is one chain, what bounds the strips from a round or two of the
-// chip on is their tiles, which no other wave shares.  Blocks / strips, us, query-stationary, then key-stationary:
-//   B2 H4 T777 d32 (200 strips) 19.1 / 10.9, 19.2 / 7.7; B1 H4 T4000 d64 (500) 98 / 50, 96 / 38;
-//   B1 H12 T2000 d64 (756) 52 / 48, 52 / 37;
-//   B1 H8 T700 d128 (176) 28 / 21.5, 24.4 / 17.9; B1 H16 T500 d128 (256) 23 / 16.7, 21 / 15.2;
-//   B1 H16 T100 d64 (64) 6.9 / 6.3, 8.2 / 6.5; both B1 H6 Hkv2 T4000 d32 320 / 125
-// and not B4 H8 T700 d64 (704) 21.5 / 25.9, 23.2 / 23.2; B4 H16 T300 d64 (640) 11.6 / 19.9, 14.4 / 19.2;
-// B1 H24 T1000 d128 (768) 40 / 55; B1 H4 T64 d64 5.0 / 6.1, 6.4 / 6.3.  (All heads far; where they are near the
-// strips gain more.)  One line serves both passes and, below d = 128, both head sizes: B2 H12 T1000 d32 (768), just beyond it,
-// would gain too, 24.7 / 24.2, 24.2 / 18.0.  4096: the kernels' arrays hold 128 strips.
-constexpr int SMALL_T = 4096;
-inline bool small_grid(long strips, int T, int d)
+// chip on is their tiles, which no other wave shares: the longer the chain, the more strips are still worth it.
+// Blocks / strips, us, query-stationary, then key-stationary (the better of its block kernels), all heads far, then a third, then none:
+//   d = 32   B1 H16 T500 (256) 14 / 6, 14 / 7;  T1000 H24 (768) 25 / 18, 25 / 17, 13 / 16 and 24 / 18, 24 / 16, 12 / 13;  T2048 H14 (896) 46 / 32,
+//            45 / 25, 12 / 20 and 44 / 31, 44 / 22, 12 / 17;  T4096 H12 (1536) 89 / 83, 88 / 51, 16 / 31 and 84 / 81, 84 / 45, 17 / 27
+//   d = 64   T500 H32 (512) 17 / 11, 17 / 12, 14 / 13 and 18 / 13, 18 / 13, 15 / 12;  T1000 H24 (768) 30 / 22, 29 / 21, 15 / 20 and 30 / 26, 30 / 22,
+//            16 / 20;  T3000 H16 (1504) 77 / 80, 77 / 53, 20 / 37 and 77 / 85, 75 / 50, 22 / 37;  T8192 H1 (256) 200 / 56 and 189 / 52
+//   d = 128  T500 H16 (256) 22 / 13, 22 / 13, 18 / 11 and 19 / 14, 19 / 14, 15 / 11;  T2000 H8 (504) 70 / 43, 69 / 37, 19 / 23 and 50 / 43, 48 / 34,
+//            18 / 23;  T3000 H8 (752) 101 / 91, 100 / 61, 20 / 33 and 73 / 85, 67 / 57, 22 / 33;  T8192 H1 (256) 263 / 130 and 162 / 108
+// and not    d = 32 T500 H48 (768) 14.5 / 13.5, 14 / 15, 13 / 15 and 14 / 14.5, 14 / 14, 12 / 13;  T4096 H16 (2048) 89 / 109, 89 / 67, 17 / 40 and 92 / 105,
+//            84 / 60, 18 / 36;  d = 64 T1000 H32 (1024) 30 / 31, 30 / 27, 15 / 26 and 31 / 35, 31 / 27, 17 / 25;  d = 128 T500 H32 (512) 23 / 20, 22 / 22,
+//            19 / 22 and 21 / 24, 21 / 22, 18 / 22;  T1000 H24 (768) 39 / 42, 39 / 38, 20 / 33 and 35 / 46, 31 / 37, 22 / 32;  T3000 H10 (940) 101 / 106,
+//            100 / 71, 21 / 42 and 82 / 102, 68 / 64, 23 / 41
+// The limits lie where neither far heads nor near ones lose more by it than a mix gains.  One line serves both passes and, below d = 128, both
+// head sizes: T320 H26 d32 (260), just beyond it, would gain too, 9.4 / 7.7 and 10 / 8.  What is due to long chains goes by the mean length of
+// a packed batch's sequences: one long one among many short ones leaves the rest of the strips short.  Beyond 8192 rows not measured.
+constexpr int SMALL_T = 4096, LONG_T = 8192;
+inline bool small_grid(long strips, int T, int mean, int d)
 {
-    const long limit = d == 128 ? 256 : T >= 1024 ? 768 : T > 341 ? 3L * T / 4 : 256;
-    return T > 64 && T <= SMALL_T && strips <= limit;
+    long limit = T > 64 && T <= SMALL_T ? (d == 128 ? 256 : T >= 1024 ? 768 : T > 341 ? 3L * T / 4 : 256) : 0;
+    if (mean >= 1536 && T <= LONG_T) limit = std::max(limit, d == 128 ? std::clamp(mean / 4L, 512L, 768L) : std::clamp(mean / 2L, 768L, 1536L));
+    return strips <= limit;
+}
+// The key-stationary pass of G query heads to a kv head: G times as long a chain for every strip of keys, and the strip's first loads, K, V and
+// stores are shared by as many.  Whole backward with blocks / strips of keys, us, all heads far, then a third, then none:
+//   d = 32   B1 H32 Hkv8 T3870 (968 strips) 421 / 278, 388 / 182, 64 / 62;  B8 H32 Hkv4 T800 (800) 181 / 119, 180 / 96, 103 / 77;  B4 H32 Hkv4 T3672 (1840)
+//            942 / 953, 805 / 541, 186 / 172;  B1 H16 Hkv4 T8192 (1024) 881 / 594, 875 / 562, 64 / 69
+//   d = 64   B1 H24 Hkv12 T3000 (1128) 228 / 196, 224 / 135, 68 / 63;  B8 H16 Hkv4 T1500 (1504) 242 / 268, 211 / 149, 120 / 108;  B16 H32 Hkv4 T300 (640)
+//            108 / 79 in all three;  B16 H32 Hkv8 T100 (512) 33 / 28 in all three;  B2 H24 Hkv12 T2048 (1536) 176 / 189, 159 / 124, 71 / 73
+//   d = 128  B1 H32 Hkv8 T2048 (512) 258 / 231, 251 / 184, 81 / 74;  B3 H16 Hkv4 T1600 (600) 217 / 207, 203 / 148, 103 / 90;  B2 H6 Hkv3 T2000 (378) 164 / 129,
+//            162 / 127, 49 / 46;  B12 H12 Hkv4 T256 (384) 49 / 43 in all three;  B1 H8 Hkv2 T8192 (512) 937 / 743, 81 / 77, 81 / 77
+// and not    d = 32 B11 H20 Hkv5 T2770 (4785) 876 / 989, 437 / 377, 197 / 240;  B8 H32 Hkv16 T400 (1664) 49 / 60, 49 / 59, 47 / 59;  d = 64 B4 H24 Hkv8 T2048
+//            (2048) 296 / 364, 217 / 173, 109 / 118;  B12 H9 Hkv3 T1500 (1692) 202 / 232, 166 / 158, 102 / 102;  d = 128 B4 H12 Hkv4 T2048 (1024) 276 / 317,
+//            212 / 204, 117 / 108;  B16 H8 Hkv1 T1500 (752) 428 / 485, 260 / 178, 260 / 178
+inline bool grouped_strips(long strips, int G, int T, int mean, int d)
+{
+    if (G == 1 || mean <= 64 || T > LONG_T) return false;
+    if (d == 128) return strips <= (G == 2 ? std::clamp(2L * mean / 7, 328L, 576L) : 640L);
+    return strips <= std::clamp(3L * G * mean / 8, 512L, d == 64 ? 1536L : 1920L);
 }
 
 // How many strips or blocks of `rows` rows there are: exactly, or in a packed batch of nseq sequences, whose
@@ -71,6 +95,9 @@ inline long pieces(int B, int H, int T, int rows, bool packed, int Ttot)
     const long all = (long)B * H * ((T + rows - 1) / rows);
     return packed ? std::min(all, (long)H * (Ttot / rows + B)) : all;
 }
+
+// Rows of a sequence, in the mean
+inline int mean_T(int B, int T, bool packed, int Ttot) { return packed ? Ttot / B : T; }
 
 // A packed batch's strips are launched as pieces() counts them, T (max_T) being at least the longest sequence's length and perhaps far
 // more; place_of() finds a workgroup's.  Each that T leaves room for, in every sequence, cost 2 us a thousand: 64 sequences of 32 rows,
@@ -118,18 +145,22 @@ __device__ __forceinline__ Place place_of(int place, const int* __restrict__ cu,
 }
 
 // Grids of the forward that take one strip of 32 rows a workgroup, its waves taking the strip's subtiles in rounds
-// (fwd_small_kernel), in place of 128-row blocks whose every wave has its rows' chain to itself.  Blocks / strips, us,
-// without m, then with it:
-//   all heads far   B1 H16 T100 d64 (64 strips) 5.2 / 4.6, 5.2 / 4.7; B2 H4 T777 d32 (200) 12.2 / 7.7, 12.4 / 7.8;
-//                   B1 H8 T700 d128 (176) 18.9 / 11.9, 19.1 / 12.2; B2 H12 T500 d128 (384) 15.8 / 12.5, 15.9 / 12.6;
-//                   B1 H4 T4000 d64 (500) 58 / 33, 58 / 33
-//   none far        12.2 / 7.0 and 17.2 / 9.4 for B1 H8 T700 d128, 8.9 / 10.2 and 41 / 17 for B1 H4 T4000 d64
-// and not, a third far, B4 H8 T700 d64 (704) 13.5 / 16.2, 13.6 / 17.6; B1 H24 T1000 d128 (768) 26.4 / 28.1, 26.5 / 31.8;
-// B4 H16 T300 d32 (640) 6.9 / 9.8, 7.0 / 10.1.  At d = 32 a chain of 10 subtiles is not worth the rounds' barriers.
+// (fwd_small_kernel), in place of 128-row blocks whose every wave has its rows' chain to itself.  Blocks / strips, us, without m (with it,
+// where it matters, in brackets), all heads far, then a third, then none:
+//   d = 32   B1 H32 T500 (512 strips) 9.2 / 8.2, 8.9 / 8.1, 7.1 / 7.5 (9.0 / 7.7);  T3000 H10 (940) 39 / 34, 38 / 23, 7 / 14 (22 / 20);  T8192 H1 100 / 37
+//   d = 64   H64 T100 (256) 5.7 / 5.0;  H24 T500 (384) 10.6 / 8.5, 10.5 / 8.0, 8.2 / 8.0;  T2000 H12 (756) 32 / 26, 31 / 19, 9 / 14 (20 / 17.5);
+//            T3000 H10 (940) 45 / 41, 44 / 28, 9 / 18 (26 / 25);  T8192 H1 114 / 44;  T16384 H1 225 / 100
+//   d = 128  H37 T200 (259) 8.4 / 6.9;  H24 T500 (384) 14.6 / 11.1, 14.5 / 10.5, 11.3 / 10.5;  T1000 H12 (384) 24.5 / 15.3, 24 / 15, 11.4 / 11.9;
+//            T2048 H10 (640) 45 / 38, 44 / 26, 13 / 18 (26 / 26);  T8192 H1 161 / 82;  T16384 H1 319 / 180
+// and not, d = 32 H37 T200 (259) 5.7 / 6.4;  T2048 H18 (1152) 28 / 32, 27 / 23, 8 / 17 (17 / 22);  d = 64 H96 T100 (384) 5.8 / 7.1;  T500 H48 (768) 11.1 / 14.8,
+//            10.8 / 13.9, 8.6 / 13.4;  T2000 H16 (1008) 32 / 33, 32 / 24, 9 / 18 (20 / 22.5);  T4096 H12 (1536) 62 / 78, 60 / 45, 12 / 25 (34 / 44);
+//            d = 128 T500 H48 (768) 16 / 21, 16 / 19, 13 / 19;  T1000 H24 (768) 25 / 30, 25 / 23, 13 / 19;  T4096 H9 (1152) 87 / 109, 86 / 55, 18 / 29 (44 / 63)
+// At d = 32 a chain of 10 subtiles is not worth the rounds' barriers.
 inline bool small_fwd_grid(long strips, int T, int d)
 {
-    const long limit = T < 256 ? 256 : T < 512 || d == 128 ? 384 : 512;
-    return T > (d == 32 ? 320 : 64) && T <= SMALL_T && strips <= limit;
+    if (T <= (d == 32 ? 320 : 64)) return false;
+    const long least = T < 256 ? 256 : T < 512 || d == 128 ? 384 : 512;
+    return strips <= std::max(least, d == 128 ? std::min(2L * T / 5, 704L) : std::min(3L * T / 8, 1000L));
 }
 
 // Grids of the key-stationary pass at d <= 64 whose blocks are taken by two groups of four waves (bwd_dkv_kernel<.., 2>): where a
@@ -188,7 +219,7 @@ constexpr long small_kv_grid(int nkb) { return std::clamp(64L + 16L * nkb, 256L,
 // The kernels of the backward's passes.
 inline bool query_strips(int B, int H, int T, int d, bool packed, int Ttot)
 {
-    return small_grid(pieces(B, H, T, 32, packed, Ttot), T, d);
+    return small_grid(pieces(B, H, T, 32, packed, Ttot), T, mean_T(B, T, packed, Ttot), d);
 }
 enum class Keys {
     STRIPS,                               // bwd_dkv_small_kernel
@@ -200,7 +231,9 @@ inline Keys keys_of(int B, int H, int Hkv, int T, int d, bool packed, int Ttot)
     const long heads = (long)B * Hkv;
     const int nkb = (T + 127) / 128;
     const long blocks = pieces(B, Hkv, T, 128, packed, Ttot);
-    if (small_grid(pieces(B, Hkv, T, 32, packed, Ttot), T, d)) return Keys::STRIPS;
+    const long strips = pieces(B, Hkv, T, 32, packed, Ttot);
+    const int mean = mean_T(B, T, packed, Ttot);
+    if (small_grid(strips, T, mean, d) || grouped_strips(strips, H / Hkv, T, mean, d)) return Keys::STRIPS;
     if (d < 128) return take_in_turn(B, H, Hkv, T, packed, Ttot) ? Keys::TWO_GROUPS : Keys::ONE_GROUP;
     if (blocks <= small_kv_grid(nkb)) return Keys::KEYS_64;
     return !packed && H == Hkv && take_pairs(heads, nkb) ? Keys::PAIRS : Keys::KEYS_128;
