@@ -26,9 +26,9 @@
 // launch then takes the nearest keys as well.
 //
 // Measured without m, a third of the kv heads reaching far / all of them / all keys in one pass over the
-// chip, whatever they take (this kernel's predecessor), us: B8 H16 T16384 d128 68 / 167 / 180 (all keys at
-// 6.4 TB/s), B1 H32 Hkv8 T65000 d128 29 / 54 / 47, B32 H16 T1800 d64 34 / 50 / 37, B16 H32 Hkv8 T4096 d128
-// 28 / 55 / 45: where every head reaches far the launch in front is 5 to 13 us lost.
+// chip, whatever they take (the first form of this kernel), us: B8 H16 T16384 d128 63 / 164 / 180 (all keys at
+// 6.5 TB/s), B1 H32 Hkv8 T65000 d128 25.6 / 51 / 47, B32 H16 T1800 d64 27.6 / 43 / 37, B16 H32 Hkv8 T4096 d128
+// 26 / 52 / 45: where every head reaches far the launch in front is 4 to 10 us lost.
 #include <mutex>
 #include <type_traits>
 
@@ -44,17 +44,21 @@ constexpr int GMAX = 16;               // query heads of a group per workgroup: 
 constexpr int COMBINE_THREADS = 256;
 
 
-// sum of v over the lanes above this one, and over all lanes in `total`
-__device__ __forceinline__ float wave_suffix_excl(float v, float& total)
+// sum of v over the lanes below this one, and over all lanes in `total` (by DPP: the same through LDS shuffles took 800 clocks)
+template <int CTRL, int ROWS> __device__ __forceinline__ float dpp_or_zero(float x)
 {
-    const int lane = threadIdx.x & 63;
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, ROWS, 0xF, false));
+}
+__device__ __forceinline__ float wave_prefix_excl(float v, float& total)
+{
     float inc = v;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const float y = __shfl_down(inc, off);
-        if (lane + off < 64) inc += y;
-    }
-    total = __shfl(inc, 0);
+    inc += dpp_or_zero<0x111, 0xF>(inc);                  // row_shr:1, 2, 4, 8
+    inc += dpp_or_zero<0x112, 0xF>(inc);
+    inc += dpp_or_zero<0x114, 0xF>(inc);
+    inc += dpp_or_zero<0x118, 0xF>(inc);
+    inc += dpp_or_zero<0x142, 0xA>(inc);                  // row_bcast:15 into rows 1 and 3
+    inc += dpp_or_zero<0x143, 0xC>(inc);                  // row_bcast:31 into rows 2 and 3
+    total = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, inc), 63));
     return inc - v;
 }
 
@@ -77,41 +81,47 @@ __device__ __forceinline__ void store_out(const uint16_t* rb, uint16_t* o, float
 }
 
 // A workgroup takes its keys from the nearest down in passes of KEYS, 32 keys per wave.
-//   logits   z[key][head] = K q: 16x16x32 bf16 MFMA, A = 16 rows of K as they lie in memory (lane:
-//            row lane%16, 16-byte chunk 4s + lane/16), B = the query heads of the group.  A lane
-//            gets four consecutive keys of one head.
-//   weights  through LDS: wave g takes head g (and g + NW), NW/2 consecutive keys per lane.
+//   logits   z[key][head] = K q: 16x16x32 bf16 MFMA, A = 16 rows of K (lane: row lane%16, 16-byte chunk
+//            4s + lane/16), B = the query heads of the group.  A lane gets four consecutive keys of one head.
+//   weights  through LDS: wave g takes head g (and g + NW), NW/2 consecutive keys per lane, lane 0 the nearest.
 //   output   O^T[c][head] += V^T w: a lane loads D/16 columns of the 8 rows 8*(lane/16) + i, and an
 //            in-register transposition (one v_perm per packed pair) makes them the A operand of
 //            D/16 MFMAs, rows = columns of V, 32 keys deep.  B = the weights, each split exactly
 //            into three bf16 (8 + 8 + 8 bits of mantissa), so that nothing of the fp32 weight is lost.
 // On the vector ALU the same two products cost 35 instructions per 16-byte word and head, which
 // bound groups of 4 heads (B1 H32 Hkv8 T65000 d128: 78 us against 48 us of memory time; this way 55).
-// The K registers of a pass are free after its logits and the V registers after its output, and are
-// refilled there and then with the next pass's rows: loads stay in flight across the barriers.
+// K comes through LDS, whole rows at a time, every wave its own: a CU takes in 55 bytes a clock where a load's lanes lie
+// side by side, and 15 where they are the rows of an operand, which bound a CU that has the cache's keys to itself
+// (pass of 256 keys, d = 128: 5200 of 8000 clocks).  K's place and V's registers (two sets) are asked for again as soon as a
+// pass has its logits, one pass ahead.  At d = 128 two far workgroups a CU read faster than three (all heads far, B8 H16 T16384 174 / 167 us,
+// B1 H32 Hkv8 T65000 55 / 51).
 template <int D, bool FAR>
-__global__ void __launch_bounds__(64 * (FAR ? FAR_NW : NEAR_NW), FAR ? 3 : 2)
+__global__ void __launch_bounds__(64 * (FAR ? FAR_NW : NEAR_NW), FAR && D < 128 ? 3 : 2)
 decode_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
               const uint16_t* __restrict__ rb, uint16_t* __restrict__ o, float* __restrict__ m,
               float* __restrict__ part_o, float* __restrict__ part_a,
-              int T, int Tcap, int H, int G, int near, int C, int nfar)
+              int T, int Tcap, int Hkv, int G, int near, int C, int nfar)
 {
     constexpr int NW = FAR ? FAR_NW : NEAR_NW;
     constexpr int NTHR = 64 * NW;
     constexpr int KEYS = KW * NW;          // keys per pass
     constexpr int ZS = KEYS + 4;           // row stride of the logits in LDS (heads apart by 4 banks)
     constexpr int CW = D / 16;             // columns of V per lane
+    constexpr int ROW = 2 * D, CPR = ROW / 16;
+    constexpr int NK = KW * ROW / 1024;    // loads of K per wave and pass
+    constexpr int NV = 8;                  // and of V
     typedef __attribute__((ext_vector_type(CW / 2))) unsigned int vword;
     constexpr int HB = 4;                  // heads per round of the reduction over the waves
+    __shared__ __attribute__((aligned(1024))) char kbuf[KEYS * ROW];
     __shared__ __attribute__((aligned(16))) float zs[2][GMAX][ZS];   // per pass parity: logits (base 2), then weights
-    __shared__ __attribute__((aligned(16))) float ored[NW * HB * D];
     __shared__ float s_carry[GMAX];
     __shared__ int s_left[2];              // per pass parity: heads not exhausted
+    float* const ored = reinterpret_cast<float*>(kbuf);              // once the keys are done
+    static_assert(NW * HB * D * 4 <= KEYS * ROW, "the waves' shares fit");
 
+    asm volatile("" :: "s"(q), "s"(k), "s"(v), "s"(T), "s"(Tcap), "s"(G), "s"(near), "s"(C));
     const int bkv = FAR ? blockIdx.y : blockIdx.x;     // batch entry * Hkv + kv head
     const int g0 = blockIdx.z * GMAX;      // first query head (inside the group) of this workgroup
-    const int Hkv = H / G;
-    const int b = bkv / Hkv, hkv = bkv % Hkv;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l16 = lane & 15, lq = lane >> 4;
@@ -119,9 +129,8 @@ decode_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, co
     const int chunk = FAR ? blockIdx.x : nfar;
     const int kend = FAR ? min(T - near, (chunk + 1) * C) : T;
     const int k0 = FAR ? chunk * C : T - near;
-    const long kvbase = (long)bkv * Tcap * D;
-    const long hq0 = (long)b * H + hkv * G + g0;       // first query head of this workgroup
-    const int live = min(GMAX, G - g0);                // and how many there are
+    const long hq0 = (long)bkv * G + g0;   // first query head of this workgroup
+    const int live = min(GMAX, G - g0);    // and how many there are
     const float c2 = SB_LOG2E / sqrtf((float)D);
 
     if constexpr (FAR) {
@@ -132,21 +141,27 @@ decode_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, co
     }
 
     // rows hi - KEYS + 32 wave .. + 31; those before k0 are loaded as k0 and masked
-    u32x4 kw[2][D / 32];
-    vword vw[8];
     const int r0 = wave * KW - KEYS;
+    const char* const kg = reinterpret_cast<const char*>(k) + (long)bkv * Tcap * ROW;
+    const char* const vg = reinterpret_cast<const char*>(v) + (long)bkv * Tcap * ROW;
+    const uint32_t mine = lds_offset(kbuf) + wave * KW * ROW;
     auto fetch_k = [&](int hi) __attribute__((always_inline)) {
+        const uint64_t base = scalar_base(kg + (long)(hi + r0) * ROW);
+        const int lo = k0 - (hi + r0);
 #pragma unroll
-        for (int t = 0; t < 2; ++t) {
-            const uint16_t* row = k + kvbase + (long)max(hi + r0 + 16 * t + l16, k0) * D + 8 * lq;
-#pragma unroll
-            for (int s = 0; s < D / 32; ++s) kw[t][s] = stream_load<FAR>(reinterpret_cast<const u32x4*>(row + 32 * s));
+        for (int i = 0; i < NK; ++i) {
+            const int row = i * (1024 / ROW) + lane / CPR;
+            const int off = max(row, lo) * ROW + (((lane % CPR) ^ swz_nat<D>(row)) << 4);
+            if constexpr (FAR) dma16_to_lds_at_nt(base, off, mine + i * 1024);
+            else dma16_to_lds_at(base, off, mine + i * 1024);
         }
     };
-    auto fetch_v = [&](int hi) __attribute__((always_inline)) {
+    auto fetch_v = [&](int hi, vword (&vw)[NV]) __attribute__((always_inline)) {
+        const char* const base = vg + (long)(hi + r0) * ROW;
+        const int lo = k0 - (hi + r0);
 #pragma unroll
-        for (int i = 0; i < 8; ++i)
-            vw[i] = stream_load<FAR>(reinterpret_cast<const vword*>(v + kvbase + (long)max(hi + r0 + 8 * lq + i, k0) * D + CW * l16));
+        for (int i = 0; i < NV; ++i)
+            vw[i] = stream_load<FAR>(reinterpret_cast<const vword*>(base + (unsigned)(max(8 * lq + i, lo) * ROW + l16 * 2 * CW)));
     };
     bf16x8 qw[D / 32];                     // B operand: head l16 (columns past `live` repeat the last one)
     {
@@ -154,44 +169,59 @@ decode_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, co
 #pragma unroll
         for (int s = 0; s < D / 32; ++s) qw[s] = *reinterpret_cast<const bf16x8*>(row + 32 * s);
     }
+    vword va[NV], vb[NV];
     fetch_k(kend);
-    fetch_v(kend);
+    fetch_v(kend, va);
     f32x4 acc[CW];                         // O^T: row 4 lq + r of MFMA e is column CW * (4 lq + r) + e, head l16
 #pragma unroll
     for (int e = 0; e < CW; ++e) acc[e] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
     if (tid < GMAX) s_carry[tid] = 0.0f;   // sp2 of the keys already passed, per head
     if (tid == 0) s_left[0] = 0;
-    barrier_lds();
-    int par = 0;
-    for (int hi = kend;; hi -= KEYS, par ^= 1) {
+    const uint32_t ka = mine + tile_off_nat<D>(l16, lq);             // A operand: rows 16t + l16, chunks 4s + lq: + 16t ROW, ^ (s << 6)
+    int par = 0, hi = kend;
+    // one pass; whether another follows.  vw: this pass's V, vn: the next one's
+    auto pass = [&](vword (&vw)[NV], vword (&vn)[NV]) __attribute__((always_inline)) {
         const bool more = hi - KEYS > k0;
         // ---- logits
+        dma_wait<NV>();                    // K has landed, V was asked for behind it
 #pragma unroll
         for (int t = 0; t < 2; ++t) {
             f32x4 z = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
             for (int s = 0; s < D / 32; ++s)
-                z = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kw[t][s]), qw[s], z, 0, 0, 0);
+                z = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, lds_load16((ka + 16 * t * ROW) ^ (s << 6))), qw[s], z, 0, 0, 0);
             const int i = wave * KW + 16 * t + 4 * lq;
 #pragma unroll
             for (int r = 0; r < 4; ++r) z[r] = hi - KEYS + i + r >= k0 ? z[r] * c2 : -INFINITY;
             if (l16 < live) *reinterpret_cast<f32x4*>(&zs[par][l16][i]) = z;
         }
-        if (more) fetch_k(hi - KEYS);
         barrier_lds();
+        // V has landed (nothing is asked for between it and here that the compiler does not count)
+#pragma unroll
+        for (int i = 0; i < NV; ++i)
+#pragma unroll
+            for (int e = 0; e < CW / 2; ++e) {
+                unsigned int x = vw[i][e];
+                asm volatile("" : "+v"(x));
+                vw[i][e] = x;
+            }
+        if (more) {
+            fetch_k(hi - KEYS);
+            fetch_v(hi - KEYS, vn);
+        }
         if (tid == 0) s_left[par ^ 1] = 0;                   // everyone has read it, in the pass before
         // ---- weights: w[i] = 2^(x_i - carry - sum_{i' >= i} sp2(x_i'))  (Eq. 2)
         for (int g = wave; g < live; g += NW) {
             constexpr int EPL = KEYS / 64;
             typedef __attribute__((ext_vector_type(EPL))) float zvec;
-            zvec* z = reinterpret_cast<zvec*>(&zs[par][g][EPL * lane]);
+            zvec* z = reinterpret_cast<zvec*>(&zs[par][g][EPL * (63 - lane)]);
             zvec x = *z;
-            float sp[EPL], mine = 0.0f;
+            float sp[EPL], own = 0.0f;
 #pragma unroll
-            for (int e = 0; e < EPL; ++e) { sp[e] = sp2(x[e]); mine += sp[e]; }
+            for (int e = 0; e < EPL; ++e) { sp[e] = sp2(x[e]); own += sp[e]; }
             float total;
             const float carry = s_carry[g];
-            float run = wave_suffix_excl(mine, total) + carry;
+            float run = wave_prefix_excl(own, total) + carry;
 #pragma unroll
             for (int e = EPL - 1; e >= 0; --e) {
                 run += sp[e];
@@ -231,9 +261,15 @@ decode_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, co
                 acc[e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, w0, acc[e], 0, 0, 0);
             }
         }
-        if (!more || (!m && s_left[par] == 0)) break;
-        fetch_v(hi - KEYS);
-    }
+        const bool on = more && (m || s_left[par] != 0);
+        hi -= KEYS;
+        par ^= 1;
+        return on;
+    };
+    barrier_lds();
+    while (pass(va, vb) && pass(vb, va)) {}
+    dma_wait<0>();                         // keys asked for before the end was known
+    barrier_lds();                         // (theirs is the place of the shares)
 
     // ---- the waves' shares, HB heads at a time
     for (int gb = 0; gb < live; gb += HB) {
@@ -252,7 +288,8 @@ decode_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, co
 #pragma unroll
             for (int w = 0; w < NW; ++w) s += ored[(w * HB) * D + i];
             const float a = s_carry[g];
-            if (!FAR && (nfar == 0 || (!m && a >= CARRY_EXHAUSTED))) store_out(rb ? rb + (hkv * G + g0 + g) * D : nullptr, o + (hq0 + g) * D, m ? m + hq0 + g : nullptr, c, s, a);
+            if (!FAR && (nfar == 0 || (!m && a >= CARRY_EXHAUSTED)))
+                store_out(rb ? rb + ((bkv % Hkv) * G + g0 + g) * D : nullptr, o + (hq0 + g) * D, m ? m + hq0 + g : nullptr, c, s, a);
             if (nfar > 0) {
                 part_o[((hq0 + g) * nch + chunk) * D + c] = s;
                 if (c == 0) part_a[(hq0 + g) * nch + chunk] = a;
@@ -274,11 +311,12 @@ decode_combine_kernel(const float* __restrict__ part_o, const float* __restrict_
     const int tid = threadIdx.x, lane = tid & 63;
     const int c4 = tid % NV, grp = tid / NV;
     const float* pa = part_a + bh * nch;
+    // chunk i is shifted by everything the nearer (higher) chunks took; lane l holds chunks 2(63 - l), 2(63 - l) + 1
+    const int ch = 2 * (63 - lane);
     if (!m && near && pa[nch - 1] >= CARRY_EXHAUSTED) return;      // finished by the first launch
-    // chunk i is shifted by everything the nearer (higher) chunks took; lane l holds chunks 2l, 2l + 1
     float a[2];
 #pragma unroll
-    for (int e = 0; e < 2; ++e) a[e] = 2 * lane + e < nch ? pa[2 * lane + e] : 0.0f;
+    for (int e = 0; e < 2; ++e) a[e] = ch + e < nch ? pa[ch + e] : 0.0f;
     const f32x4* po = reinterpret_cast<const f32x4*>(part_o + bh * (long)nch * D) + c4;
     // all of a thread's share is in flight at once
     constexpr int N = (MAXFAR + NG) / NG;
@@ -286,11 +324,11 @@ decode_combine_kernel(const float* __restrict__ part_o, const float* __restrict_
 #pragma unroll
     for (int i = 0; i < N; ++i) x[i] = po[(long)min(grp + i * NG, nch - 1) * NV];
     float total;
-    float above = wave_suffix_excl(a[0] + a[1], total);
+    float above = wave_prefix_excl(a[0] + a[1], total);
     if (tid < 64)
 #pragma unroll
         for (int e = 1; e >= 0; --e) {
-            ws[2 * lane + e] = 2 * lane + e < nch ? fast_exp2(-above) : 0.0f;
+            ws[ch + e] = ch + e < nch ? fast_exp2(-above) : 0.0f;
             above += a[e];
         }
     __syncthreads();
@@ -320,12 +358,12 @@ hipError_t launch_d(const uint16_t* q, const uint16_t* k, const uint16_t* v, con
     hipError_t e = hipSuccess;
     if (s.near > 0) {
         hipLaunchKernelGGL((decode_kernel<D, false>), dim3((unsigned)(B * Hkv), 1u, (unsigned)nz), dim3(64 * NEAR_NW), 0, stream,
-                           q, k, v, rb, o, m, part_o, part_a, T, Tcap, H, G, s.near, s.C, s.nfar);
+                           q, k, v, rb, o, m, part_o, part_a, T, Tcap, Hkv, G, s.near, s.C, s.nfar);
         e = hipGetLastError();
     }
     if (e != hipSuccess || s.nfar == 0) return e;
     hipLaunchKernelGGL((decode_kernel<D, true>), dim3((unsigned)s.nfar, (unsigned)(B * Hkv), (unsigned)nz), dim3(64 * FAR_NW), 0, stream,
-                       q, k, v, rb, o, m, part_o, part_a, T, Tcap, H, G, s.near, s.C, s.nfar);
+                       q, k, v, rb, o, m, part_o, part_a, T, Tcap, Hkv, G, s.near, s.C, s.nfar);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL((decode_combine_kernel<D>), dim3((unsigned)heads), dim3(COMBINE_THREADS), 0, stream,

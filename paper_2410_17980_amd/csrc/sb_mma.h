@@ -185,6 +185,11 @@ __device__ __forceinline__ void dma16_to_lds_at(uint64_t sb, int lane_off, uint3
     asm volatile("s_nop 4\n\tglobal_load_lds_dwordx4 %1, %2" :: "{m0}"(lds), "v"(lane_off), "s"(sb) : "memory");
 }
 
+// past the caches, for data that is read once
+__device__ __forceinline__ void dma16_to_lds_at_nt(uint64_t sb, int lane_off, uint32_t lds)
+{
+    asm volatile("s_nop 4\n\tglobal_load_lds_dwordx4 %1, %2 nt" :: "{m0}"(lds), "v"(lane_off), "s"(sb) : "memory");
+}
 // the same from a pointer to a pointer, both wave-uniform
 __device__ __forceinline__ void dma16_to_lds_saddr(const void* gbase, int lane_off, const char* lds_base)
 {

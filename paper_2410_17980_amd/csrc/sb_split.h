@@ -5,13 +5,14 @@
 namespace sb {
 
 constexpr int NEAR_NW = 8;             // waves of a workgroup, first launch
-constexpr int FAR_NW = 4;              // and second: smaller, so that three share a CU
+constexpr int FAR_NW = 4;              // and second: smaller, so that two or three share a CU
 constexpr int KW = 32;                 // keys per wave and pass
 constexpr int NEAR = KW * NEAR_NW;     // keys of a first launch that has a second one behind it
 constexpr int ALONE = 6 * NEAR;        // a cache that is not spread is the first launch's alone up to here: longer, two more are faster than its passes
 constexpr int MAXFAR = 127;            // chunks beyond the nearest keys: with those, two per lane of a wave
 constexpr int FAR_KEYS = KW * FAR_NW;  // keys of a pass of the second launch
-constexpr long FAR_WGS = 2048;         // workgroups of the second launch, all heads together
+constexpr long FAR_WGS = 4096;         // workgroups of the second launch, all heads together (2048 / 4096 / 8192, a third of the heads far: B8 H16
+                                       // T16384 d128 69 / 63 / 62 us, B32 H16 T1800 d64 29.7 / 27.5 / 27.5; all far 167 / 164 / 167, 44 / 44 / 43)
 constexpr long ALL_WGS = 8192;         // the same where it takes all keys (see split_of())
 
 // Partial results there is room for in decode_workspace_bytes: one per 64 keys, or per 64 * 2^i where
