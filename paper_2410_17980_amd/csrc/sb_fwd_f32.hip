@@ -1,7 +1,7 @@
 // fp32 forward of causal stick-breaking attention on the fp32 matrix instructions.
 //
 // This path exists for full-precision checks: every operation is fp32 (the 16x16x4 fp32 MFMA is a
-// fused multiply-add chain per element), exp and log1p are the library's.  The shapes it
+// fused multiply-add chain per element), exponential and logarithm are good to an ulp.  The shapes it
 // is called at are small (one head of a few hundred rows), so what bounds it is the length of the
 // serial chain of a row and how much of the chip has work, not a throughput:
 //   - a workgroup takes 16 query rows, so that T = 256 already gives 16 workgroups per head;
@@ -10,25 +10,55 @@
 //     results of key ranges combine without any rescaling by a maximum,
 //         o = sum_w exp(-(softplus total of the ranges nearer than w)) o_w,
 //     which is done once at the end through LDS, in a fixed order;
-//   - K and V go from L2 straight into the operand registers, 16 bytes per lane, no staging and no
-//     barrier in the sweep; the next subtile's K is fetched during the element-wise work.
+//   - V goes from L2 straight into the operand registers, whole rows a load, K through LDS, every wave its own subtile,
+//     asked for again as soon as it is in registers; no barrier in the sweep.  (A load whose lanes are the rows of
+//     the operand brings a CU 15 bytes a clock, one whose lanes lie side by side 55.)
 // Measured, B1 H1 T256 d64: 228 us with one lane per query row walking the keys one by one -> 9.8 us;
-// B1 H1 T2048 d128 5163 -> 67 us, B4 H8 T2048 d128 5715 -> 611 us (56 TFLOP/s).
+// B1 H1 T2048 d128 5163 -> 66 us, B4 H8 T2048 d128 5715 -> 603 us.  With K and Q by whole rows and exponential and logarithm
+// of its own: 9.8 -> 6.4, 66 -> 51, 603 -> 445 us (77 TFLOP/s); B4 H8 T2048 d32 277 -> 167 us.  Against fp64 the error of o
+// is at most what it was with the library's functions, a third less where logits are of the order of 1.
 #include "sb_kernels.h"
+#include "sb_mma.h"
 
 namespace sb {
 namespace {
-
-typedef __attribute__((ext_vector_type(4))) float f32x4;
 
 constexpr int F32_BQ = 16;   // query rows per workgroup
 constexpr int F32_NW = 8;    // waves that share their keys
 constexpr int F32_THREADS = 64 * F32_NW;
 
-__device__ __forceinline__ float softplus_f32(float z)
+// e^x for the x <= 0 that occur here, to about an ulp: what the rounding of x log2(e) and of log2(e) itself leaves
+// over is put back to first order.  (The library's expf and log1pf, 30 and 100 instructions with branches, took half the
+// time of a subtile.)
+__device__ __forceinline__ float exp_f32(float x)
 {
-    // log(1 + e^z) = max(z, 0) + log1p(e^{-|z|}): no overflow on either side
-    return fmaxf(z, 0.0f) + log1pf(expf(-fabsf(z)));
+    constexpr float L = 1.44269504088896340736f, LO = (float)(1.44269504088896340736 - (double)L);
+    const float p = x * L;
+    const float rest = __builtin_fmaf(x, LO, __builtin_fmaf(x, L, -p));
+    const float r = fast_exp2(p);
+    return r == 0.0f ? 0.0f : __builtin_fmaf(r * rest, SB_LN2, r);       // (x = -inf: rest is not a number)
+}
+// log(1 + e), 0 <= e <= 1: 2 atanh(s), s = e / (2 + e) <= 1/3, by its series up to s^15 / 15 (the next term: 1.4e-9 of the sum)
+__device__ __forceinline__ float log1p_f32(float e)
+{
+    const float d = 2.0f + e, low = e - (d - 2.0f);                       // 2 + e = d + low
+    const float r = __builtin_amdgcn_rcpf(d), s0 = e * r;
+    const float rest = (__builtin_fmaf(-d, s0, e) - low * s0) * r;        // s = s0 + rest
+    const float t = s0 * s0;
+    float p = 1.0f / 15;
+    p = __builtin_fmaf(p, t, 1.0f / 13);
+    p = __builtin_fmaf(p, t, 1.0f / 11);
+    p = __builtin_fmaf(p, t, 1.0f / 9);
+    p = __builtin_fmaf(p, t, 1.0f / 7);
+    p = __builtin_fmaf(p, t, 1.0f / 5);
+    p = __builtin_fmaf(p, t, 1.0f / 3);
+    return 2.0f * (s0 + __builtin_fmaf(s0 * t, p, rest));                 // one rounding of the size of the result
+}
+// Rows of fp32 in LDS: byte offset of 16-byte chunk c of row `row`, the chunk xor-ed so that 16 lanes that read the same chunk of
+// 16 rows meet different banks.
+template <int D> __device__ __forceinline__ int f32_off(int row, int c)
+{
+    return row * (4 * D) + ((c ^ (D >= 64 ? row & 15 : (row >> 1) & 7)) << 4);
 }
 
 // S^T = K Q^T with A = 16 key rows, B = 16 query rows: in the accumulator a lane (n = lane % 16,
@@ -45,17 +75,22 @@ fwd_f32_kernel(const float* __restrict__ q, const float* __restrict__ k, const f
     constexpr int VEC = D >= 64 ? 4 : 2;
     constexpr int NV = D / (16 * VEC);
     typedef __attribute__((ext_vector_type(VEC))) float vec;
-    __shared__ float s_tot[F32_NW][F32_BQ];
-    __shared__ __attribute__((aligned(16))) float s_o[F32_NW][F32_BQ][D];
+    constexpr int RB = 4 * D, CPR = RB / 16;              // bytes and 16-byte chunks of a row
+    constexpr int SUB = 16 * RB, LOADS = SUB / 1024;      // of a subtile of 16 rows; its loads by a wave
+    __shared__ __attribute__((aligned(16))) float s_tot[F32_NW][F32_BQ];
+    __shared__ __attribute__((aligned(1024))) char s_q[SUB];
+    __shared__ __attribute__((aligned(1024))) char s_k[F32_NW * SUB];       // the waves' subtiles, later their partial results
+    float (*const s_o)[F32_BQ][D] = reinterpret_cast<float (*)[F32_BQ][D]>(s_k);
+    static_assert(SUB == F32_BQ * D * 4, "a wave's partial result takes the place of its subtile");
 
     // consecutive workgroup ids go round the 8 XCDs: give each XCD one contiguous eighth of the
     // (head, query block) list, so that a head's K and V are read into one or two L2s only
-    const long per_xcd = (nblocks + 7) >> 3;
-    const long wg = (long)first_wg + blockIdx.x;
-    const long lin = (wg & 7) * per_xcd + (wg >> 3);
+    const unsigned per_xcd = (unsigned)((nblocks + 7) >> 3), wg = (unsigned)first_wg + blockIdx.x;      // (the grid is below 2^31)
+    const unsigned lin = (wg & 7) * per_xcd + (wg >> 3);
     if (lin >= nblocks) return;
-    const long bh = lin / nqb;
-    const int q0 = (nqb - 1 - (int)(lin % nqb)) * F32_BQ;      // longest rows first
+    const unsigned head = __builtin_amdgcn_readfirstlane(lin / (unsigned)nqb);
+    const long bh = head;
+    const int q0 = (nqb - 1 - (int)(lin - head * (unsigned)nqb)) * F32_BQ;      // longest rows first
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int n = lane & 15, g = lane >> 4;
@@ -63,11 +98,6 @@ fwd_f32_kernel(const float* __restrict__ q, const float* __restrict__ k, const f
     const float* Q = q + bh * (long)T * D;
     const float* K = k + bh * (long)T * D;
     const float* V = v + bh * (long)T * D;
-
-    f32x4 qf[D / 16];
-#pragma unroll
-    for (int j = 0; j < D / 16; ++j)
-        qf[j] = *reinterpret_cast<const f32x4*>(Q + (long)min(q0 + n, T - 1) * D + 16 * j + 4 * g);
 
     // keys 0 .. kmax-1 are visible to some row; wave 0 takes the nearest range of subtiles
     const int kmax = min(T, q0 + F32_BQ) - 1;
@@ -79,20 +109,39 @@ fwd_f32_kernel(const float* __restrict__ q, const float* __restrict__ k, const f
     f32x4 acc[D / 16];
 #pragma unroll
     for (int b = 0; b < D / 16; ++b) acc[b] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-    f32x4 kf[D / 16];
-    auto load_k = [&](int sub) __attribute__((always_inline)) {
-        const float* row = K + (long)min(16 * sub + n, T - 1) * D + 4 * g;
-#pragma unroll
-        for (int j = 0; j < D / 16; ++j) kf[j] = *reinterpret_cast<const f32x4*>(row + 16 * j);
+    // load i of the 16 rows from `row0` of X on (those past T clamped)
+    auto stage = [&](const float* X, int row0, int i, uint32_t at) __attribute__((always_inline)) {
+        const int row = i * (1024 / RB) + lane / CPR;
+        const int off = min(row, T - 1 - row0) * RB + (((lane % CPR) ^ (D >= 64 ? row & 15 : (row >> 1) & 7)) << 4);
+        dma16_to_lds_at(scalar_base(X + (long)row0 * D), off, at + i * 1024);
     };
-    if (hi >= 0) load_k(hi);
+    const uint32_t q_at = lds_offset(s_q), k_at = lds_offset(s_k) + wave * SUB;
+    auto load_k = [&](int sub) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < LOADS; ++i) stage(K, 16 * sub, i, k_at);
+    };
+    for (int i = wave; i < LOADS; i += F32_NW) stage(Q, q0, i, q_at);
+    if (hi >= lo) load_k(hi);
+    dma_wait<0>();
+    barrier_nofence();
+    f32x4 qf[D / 16], kf[D / 16];
+    const uint32_t row_at = f32_off<D>(n, g);                 // chunk 4j + g: ^ (j << 6)
+#pragma unroll
+    for (int j = 0; j < D / 16; ++j) qf[j] = __builtin_bit_cast(f32x4, lds_load16((q_at + row_at) ^ (j << 6)));
     for (int sub = hi; sub >= lo; --sub) {
+        dma_wait<0>();                                        // K has landed
         vec vf[4][NV];
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const float* row = V + (long)min(16 * sub + 4 * g + r, T - 1) * D + VEC * n;
 #pragma unroll
             for (int j = 0; j < NV; ++j) vf[r][j] = *reinterpret_cast<const vec*>(row + 16 * VEC * j);
+        }
+#pragma unroll
+        for (int j = 0; j < D / 16; ++j) kf[j] = __builtin_bit_cast(f32x4, lds_load16((k_at + row_at) ^ (j << 6)));
+        if (sub > lo) {
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");       // ... and is in registers
+            load_k(sub - 1);
         }
         f32x4 z0 = {0.0f, 0.0f, 0.0f, 0.0f}, z1 = z0;         // two chains: half the dependent latency
 #pragma unroll
@@ -102,15 +151,18 @@ fwd_f32_kernel(const float* __restrict__ q, const float* __restrict__ k, const f
             z0 = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[j][2], qf[j][2], z0, 0, 0, 0);
             z1 = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[j][3], qf[j][3], z1, 0, 0, 0);
         }
-        if (sub > lo) load_k(sub - 1);
-        float z[4], c[4], run = 0.0f;
+        float x[4], c[4], run = 0.0f;                          // log sigmoid(z); this lane's keys r+1..3
         bool seen[4];
 #pragma unroll
         for (int r = 3; r >= 0; --r) {
-            z[r] = (z0[r] + z1[r]) * scale;
+            float z = (z0[r] + z1[r]) * scale;
+            asm("" : "+v"(z));                                 // rounded, the same in every use
             seen[r] = 16 * sub + 4 * g + r < q0 + n;
-            run += seen[r] ? softplus_f32(z[r]) : 0.0f;
-            c[r] = run;                                        // this lane's keys r..3
+            // softplus(z) = max(z, 0) + log(1 + e^{-|z|}); z less that, each part by itself, loses nothing where z is large
+            const float over = fmaxf(z, 0.0f), l = log1p_f32(exp_f32(-fabsf(z)));
+            x[r] = (z - over) - l;
+            c[r] = run;
+            run += seen[r] ? over + l : 0.0f;
         }
         // the lane groups of higher g hold nearer keys
         const float x1 = __shfl_xor(run, 16);
@@ -120,7 +172,10 @@ fwd_f32_kernel(const float* __restrict__ q, const float* __restrict__ k, const f
         s += pair + x2;
         float w[4];
 #pragma unroll
-        for (int r = 0; r < 4; ++r) w[r] = seen[r] ? expf(z[r] - (off + c[r])) : 0.0f;
+        for (int r = 0; r < 4; ++r) {
+            const float a = exp_f32(x[r] - (off + c[r]));
+            w[r] = seen[r] ? a : 0.0f;
+        }
 #pragma unroll
         for (int r = 0; r < 4; ++r)
 #pragma unroll
@@ -133,11 +188,15 @@ fwd_f32_kernel(const float* __restrict__ q, const float* __restrict__ k, const f
     // ---- combine the waves' ranges.  acc[b][r] is query row 4g + r.
     if (g == 0) s_tot[wave][n] = s;
     __syncthreads();
+    f32x4 tot[F32_NW], nearer = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int w = 0; w < F32_NW; ++w) tot[w] = *reinterpret_cast<const f32x4*>(&s_tot[w][4 * g]);
+#pragma unroll
+    for (int w = 0; w < F32_NW; ++w)
+        if (w < wave) nearer += tot[w];
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-        float nearer = 0.0f;
-        for (int w = 0; w < wave; ++w) nearer += s_tot[w][4 * g + r];
-        const float f = expf(-nearer);
+        const float f = exp_f32(-nearer[r]);
 #pragma unroll
         for (int j = 0; j < NV; ++j) {
             vec x;

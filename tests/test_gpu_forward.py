@@ -290,3 +290,48 @@ def test_streaming_read_diagnostic_runs(sb):
     gbs = sb.sb_diag_stream_read(x, iters=5)
     print(f"streaming read: {gbs:.0f} GB/s")
     assert 500.0 < gbs < 8500.0
+
+
+def one_key_logits(z):
+    """Two rows a head, d = 64: row 1 sees key 0 alone, whose logit is z exactly (8 z / sqrt(64)); v = 1."""
+    q = torch.zeros(1, len(z), 2, 64, device="cuda")
+    k, v = torch.zeros_like(q), torch.ones_like(q)
+    q[..., 0], k[0, :, 0, 0] = 8.0, z
+    return q, k, v
+
+
+def test_f32_weight_of_one_key(sb):
+    """sigmoid(z) and softplus(z) over the whole range of z, against fp64.  The weight's exponent, as large as |z|, carries
+    a rounding of |z| 2^-24; exponential, logarithm and the two products around them an ulp each."""
+    z = torch.cat([torch.linspace(-85, 85, 3001), torch.tensor([0.0, -0.0, 1e-30, -1e-30, 1e4, 1e37])]).cuda()
+    o, m = sb.sb_attn_fwd_f32(*one_key_logits(z), want_m=True)
+    w, sp = torch.sigmoid(z.double()), torch.nn.functional.softplus(z.double(), threshold=1e9)
+    sp = torch.where(z > 700, z.double(), sp)
+    assert ((o[0, :, 1].double() / w[:, None] - 1).abs().amax(1) <= 2.0 ** -23 * (3 + z.double().abs() / 2).clamp(max=60)).all()
+    assert ((m[0, :, 1].double() / -sp - 1).abs() <= 2.0 ** -23 * (3 + (-z.double()).clamp(min=0) / 2)).all()
+    far = torch.tensor([-90.0, -104.0, -1e4, -3e38, -float("inf")]).cuda()
+    o, m = sb.sb_attn_fwd_f32(*one_key_logits(far), want_m=True)
+    assert (o[0, :, 1].abs() <= 1e-38).all() and (m.abs() <= 1e-38).all()
+
+
+@pytest.mark.parametrize("z", [float("nan"), float("inf"), -float("inf")])
+def test_f32_logit_not_finite(sb, z):
+    """One such key: rows before it know nothing of it; those after it are not a number, or, at -inf, pass it by."""
+    T, j = 70, 33
+    g = torch.Generator().manual_seed(3)
+    q, k, v = (torch.randn(1, 1, T, 64, generator=g).cuda() for _ in range(3))
+    q[..., 0] = 8.0
+    k[..., 0] = 0.0
+    q[..., 1] = k[..., 1] = 0.0
+    o0, m0 = sb.sb_attn_fwd_f32(q, k, v, want_m=True)
+    k[0, 0, j] = 0.0
+    k[0, 0, j, 0] = z
+    o, m = sb.sb_attn_fwd_f32(q, k, v, want_m=True)
+    assert torch.equal(o[:, :, :j + 1], o0[:, :, :j + 1]) and torch.equal(m[:, :, :j + 1], m0[:, :, :j + 1])
+    if z < 0:
+        k[0, 0, j, 0] = -200.0
+        o2, m2 = sb.sb_attn_fwd_f32(q, k, v, want_m=True)
+        assert torch.equal(o, o2) and torch.equal(m, m2)
+    else:
+        assert torch.isnan(o[:, :, j + 1:]).all()
+        assert (m[:, :, j + 1:] == -z).all() if z == z else torch.isnan(m[:, :, j + 1:]).all()
