@@ -356,11 +356,10 @@ __device__ __forceinline__ void bias_sum(float* red, const BiasGrad& bias, int h
 
 // ------------------------------------------------------------------ dQ kernel
 // VL (both kernels): packed variable-length batch, tensors [H][Ttot][D] ([H/G][Ttot][D] for
-// k, v, dk, dv) with sequence s at rows cu[s] .. cu[s+1]-1.  BH counts (sequence, head)
-// pairs; T_arg and the block counts describe the longest sequence (they size the grid, the
-// array `first` and the carries, which are then laid out [head][strip][Ttot]); a workgroup
-// whose blocks lie beyond its own sequence's end returns at once.
-template <int D, bool RB, bool VL>
+// k, v, dk, dv) with sequence s at rows cu[s] .. cu[s+1]-1.  BH counts sequences; T_arg
+// and the block counts describe the longest one (they size the array `first` and the
+// carries, which are then laid out [head][strip][Ttot]).
+template <int D, bool RB, Packed VL>
 __global__ void __launch_bounds__(NTHREADS, 2)
 bwd_dq_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
               const uint16_t* __restrict__ v, const uint16_t* __restrict__ rb,
@@ -380,29 +379,29 @@ bwd_dq_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     if constexpr (RB) {
         static_assert(NTHREADS * 8 / D * (D + 4) * 4 <= 2 * C::STAGE, "the partial sums fit");
         if (wg >= bias.work) {
-            bias_partial_at<D, NTHREADS>(reinterpret_cast<float*>(smem), wg - bias.work, bias, m, dout, T_arg, VL ? cu : nullptr, Ttot, threadIdx.x);
+            bias_partial_at<D, NTHREADS>(reinterpret_cast<float*>(smem), wg - bias.work, bias, m, dout, T_arg, VL != Packed::NO ? cu : nullptr, Ttot, threadIdx.x);
             return;
         }
     }
-    const Share sh = in_scalars(share_of(wg, BH, run));
-    const int bh = sh.bh;
-    int T = T_arg, nqb = nqb_arg;
+    Share sh;
+    int bh, T = T_arg, nqb = nqb_arg;
     long row0, kvrow0, cbase, cstride;      // first q / k row of this head; carries: base and strip stride
     int head;
-    if constexpr (VL) {
-        const int seq = bh / H;
-        head = bh % H;
-        const int c0 = cu[seq];
-        T = min(min(cu[seq + 1], Ttot) - c0, T_arg);      // never past the packed rows or the stated maximum
-        if (c0 < 0) return;
+    if constexpr (VL != Packed::NO) {
+        const Place at = block_of<BQ, VL == Packed::BY_LENGTH>(head, wg, H, G, cu, BH, Ttot, T_arg, threadIdx.x & 63);
+        if (at.T == 0) return;
+        bh = at.seq * H + head;
+        sh.i = at.i;
+        T = at.T;
         nqb = (T + BQ - 1) / BQ;
-        if (sh.i >= nqb) return;
-        row0 = (long)head * Ttot + c0;
-        kvrow0 = (long)(head / G) * Ttot + c0;
-        cbase = (long)head * nt32 * Ttot + c0;
+        row0 = (long)head * Ttot + at.c0;
+        kvrow0 = (long)(head / G) * Ttot + at.c0;
+        cbase = (long)head * nt32 * Ttot + at.c0;
         cstride = Ttot;
     } else {
         // grouped kv heads: G consecutive query heads read the same K and V
+        sh = in_scalars(share_of(wg, BH, run));
+        bh = sh.bh;
         head = bh % H;
         row0 = bh * (long)T;
         kvrow0 = (long)(G == 1 ? bh : (int)((unsigned)bh / (unsigned)G)) * T;
@@ -697,8 +696,7 @@ bwd_dq_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
 }
 
 // Where a kv head's rows and its query heads' rows and carries live (key-stationary kernels).
-// bh counts kv heads (B * H / G of them); its G query heads are qh0 .. qh0+G-1.  Returns
-// false when the workgroup has nothing to do (packed batch: blocks beyond its sequence).
+// A share's heads are kv heads (B * H / G of them); the G query heads of one are qh0 .. qh0+G-1.
 struct KvHead {
     int T, nkb;                             // rows and key blocks (of `keys` keys) of this head's sequence
     long base;                              // first element of the kv head's K / V / dK / dV rows
@@ -707,44 +705,55 @@ struct KvHead {
     long qhead0;                            // index of head qh0 in `first`
 };
 
-// rows c0 .. c1 of a packed batch
+// the sequence found at a place of a packed batch
 template <int D>
-__device__ __forceinline__ bool packed_kv_head(KvHead& kh, int seq, int hkv, int c0, int c1, int T_arg, int keys, int H, int G,
-                                               int nt32, int Ttot)
+__device__ __forceinline__ void packed_kv_head(KvHead& kh, const Place& at, int hkv, int keys, int H, int G, int nt32, int Ttot)
 {
-    kh.T = min(min(c1, Ttot) - c0, T_arg);                // never past the packed rows or the stated maximum
-    if (c0 < 0) return false;
+    kh.T = at.T;
     kh.nkb = (kh.T + keys - 1) / keys;
-    kh.base = ((long)hkv * Ttot + c0) * D;
-    kh.qrow0 = (long)hkv * G * Ttot + c0;
+    kh.base = ((long)hkv * Ttot + at.c0) * D;
+    kh.qrow0 = (long)hkv * G * Ttot + at.c0;
     kh.qrow_step = Ttot;
-    kh.qhead0 = (long)seq * H + hkv * G;
-    kh.cbase = (long)hkv * G * nt32 * Ttot + c0;
+    kh.qhead0 = (long)at.seq * H + hkv * G;
+    kh.cbase = (long)hkv * G * nt32 * Ttot + at.c0;
     kh.cbase_step = (long)nt32 * Ttot;
     kh.cstride = Ttot;
-    return true;
 }
 
-template <int D, bool VL>
-__device__ __forceinline__ bool kv_head(KvHead& kh, int bh, int T_arg, int nkb_arg, int keys, int H, int G,
-                                        int nt32, const int* __restrict__ cu, int Ttot)
+// Head `bh` of a batch
+__device__ __forceinline__ void kv_head(KvHead& kh, int bh, int D, int T, int nkb, int G, int nt32)
 {
-    if constexpr (VL) {
-        const int seq = bh / (H / G);
-        return packed_kv_head<D>(kh, seq, bh % (H / G), cu[seq], cu[seq + 1], T_arg, keys, H, G, nt32, Ttot);
+    const long qh0 = (long)bh * G;
+    kh.T = T;
+    kh.nkb = nkb;
+    kh.base = (long)bh * T * D;
+    kh.qrow0 = qh0 * (long)T;
+    kh.qhead0 = qh0;
+    kh.qrow_step = T;
+    kh.cbase = qh0 * (long)nt32 * T;
+    kh.cbase_step = (long)nt32 * T;
+    kh.cstride = T;
+}
+
+// Workgroup wg's kv head and block of KEYS keys (.i < 0: none is left for it), and of a packed batch the sequence.  What follows
+// from them, kv_head_of(), comes after the lane's own numbers: all at once, the paired kernel spills four times as much.
+template <Packed VL, bool PAIRS, int KEYS>
+__device__ __forceinline__ Share kv_block(Place& at, unsigned wg, int BH, int run, int T_arg, int nkb_arg, int Hkv, const int* __restrict__ cu, int Ttot)
+{
+    if constexpr (VL != Packed::NO) {
+        int hkv;
+        at = block_of<KEYS, VL == Packed::BY_LENGTH>(hkv, wg, Hkv, 1, cu, BH, Ttot, T_arg, threadIdx.x & 63);
+        return {hkv, at.T == 0 ? -1 : at.i};
     } else {
-        const long qh0 = (long)bh * G;
-        kh.T = T_arg;
-        kh.nkb = nkb_arg;
-        kh.base = (long)bh * T_arg * D;
-        kh.qrow0 = qh0 * (long)T_arg;
-        kh.qhead0 = qh0;
-        kh.qrow_step = T_arg;
-        kh.cbase = qh0 * (long)nt32 * T_arg;
-        kh.cbase_step = (long)nt32 * T_arg;
-        kh.cstride = T_arg;
+        const Share sh = in_scalars(PAIRS ? share_in_pairs(wg, nkb_arg) : share_of(wg, BH, run));
+        return {sh.bh, PAIRS && sh.bh >= BH ? -1 : sh.i};
     }
-    return true;
+}
+template <int D, Packed VL, int KEYS>
+__device__ __forceinline__ void kv_head_of(KvHead& kh, const Share& sh, const Place& at, int T_arg, int nkb_arg, int H, int G, int nt32, int Ttot)
+{
+    if constexpr (VL != Packed::NO) packed_kv_head<D>(kh, at, sh.bh, KEYS, H, G, nt32, Ttot);
+    else kv_head(kh, sh.bh, D, T_arg, nkb_arg, G, nt32);
 }
 
 // Which query tiles reach the 32-key strips lo .. hi, a block's, from the start strips that the
@@ -804,7 +813,7 @@ template <int D, int SP> struct DkvCfg {
     static_assert(SP == 1 || NW * 2 * 32 * D * 4 <= LDS_BYTES, "the second group's accumulators fit");
 };
 
-template <int D, bool GQA, bool VL, int SP>
+template <int D, bool GQA, Packed VL, int SP, bool DR>
 __global__ void __launch_bounds__(SP * NTHREADS, 2)
 bwd_dkv_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
                const uint16_t* __restrict__ v, const uint16_t* __restrict__ dout,
@@ -820,12 +829,15 @@ bwd_dkv_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
 
     asm volatile("" :: "s"(q), "s"(k), "s"(v), "s"(dout), "s"(ca), "s"(cb), "s"(first), "s"(T_arg));   // as in bwd_dq_kernel
     const int wg = first_wg + blockIdx.x;
-    if (wg >= bias.work) {
-        bias_sum<D, SP * NTHREADS>(reinterpret_cast<float*>(smem), bias, wg - bias.work, threadIdx.x);
-        return;
+    if constexpr (DR) {
+        if (wg >= bias.work) {
+            bias_sum<D, SP * NTHREADS>(reinterpret_cast<float*>(smem), bias, wg - bias.work, threadIdx.x);
+            return;
+        }
     }
-    const Share sh = in_scalars(share_of(wg, BH, run));
-    const int bh = sh.bh;
+    Place at;
+    const Share sh = kv_block<VL, false, BKW>(at, wg, BH, run, T_arg, nkb_arg, H / G, cu, Ttot);
+    if (sh.i < 0) return;
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -835,9 +847,8 @@ bwd_dkv_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     const int n = lane & 31, hh = lane >> 5;
     const int gg = lane >> 4, li = lane & 15;
 
-    // bh counts kv heads here (BH = B * H / G of them)
     KvHead kh;
-    if (!kv_head<D, VL>(kh, bh, T_arg, nkb_arg, BKW, H, G, nt32, cu, Ttot) || sh.i >= kh.nkb) return;
+    kv_head_of<D, VL, BKW>(kh, sh, at, T_arg, nkb_arg, H, G, nt32, Ttot);
     const int T = kh.T, nkb = kh.nkb;
     const long base = kh.base, qrow0 = kh.qrow0, qrow_step = kh.qrow_step;
     const long cbase = kh.cbase, cbase_step = kh.cbase_step, cstride = kh.cstride;
@@ -1146,7 +1157,7 @@ template <int D, int KS> struct Dkv3Cfg {
     static constexpr int NPW = (LOADS + NW2 - 1) / NW2;
 };
 
-template <int D, int KS, bool GQA, bool VL, bool PAIRS>
+template <int D, int KS, bool GQA, Packed VL, bool PAIRS, bool DR>
 __global__ void __launch_bounds__(128 * KS, 1)
 bwd_dkv_pair_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
                     const uint16_t* __restrict__ v, const uint16_t* __restrict__ dout,
@@ -1163,13 +1174,15 @@ bwd_dkv_pair_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
     __shared__ __attribute__((aligned(1024))) char smem[CK::LDS_BYTES];
 
     const int wg = first_wg + blockIdx.x;
-    if (wg >= bias.work) {
-        bias_sum<D, 64 * NW2>(reinterpret_cast<float*>(smem), bias, wg - bias.work, threadIdx.x);
-        return;
+    if constexpr (DR) {
+        if (wg >= bias.work) {
+            bias_sum<D, 64 * NW2>(reinterpret_cast<float*>(smem), bias, wg - bias.work, threadIdx.x);
+            return;
+        }
     }
-    const Share sh = in_scalars(PAIRS ? share_in_pairs(wg, nkb_arg) : share_of(wg, BH, -1));
-    const int bh = sh.bh;
-    if (bh >= BH) return;
+    Place at;
+    const Share sh = kv_block<VL, PAIRS, CK::KEYS>(at, wg, BH, -1, T_arg, nkb_arg, H / G, cu, Ttot);
+    if (sh.i < 0) return;
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -1180,7 +1193,7 @@ bwd_dkv_pair_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
     const int gg = lane >> 4, li = lane & 15;
 
     KvHead kh;
-    if (!kv_head<D, VL>(kh, bh, T_arg, nkb_arg, CK::KEYS, H, G, nt32, cu, Ttot) || sh.i >= (PAIRS ? (kh.nkb + 1) >> 1 : kh.nkb)) return;
+    kv_head_of<D, VL, CK::KEYS>(kh, sh, at, T_arg, nkb_arg, H, G, nt32, Ttot);
     const int T = kh.T, nkb = kh.nkb;
     const long base = kh.base, qrow0 = kh.qrow0, qrow_step = kh.qrow_step;
     const long cbase = kh.cbase, cbase_step = kh.cbase_step, cstride = kh.cstride;
@@ -1643,7 +1656,7 @@ bwd_dq_small_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
     long row0 = bh * (long)T, kvrow0 = (long)(G == 1 ? bh : (int)((unsigned)bh / (unsigned)G)) * T;
     long cbase = (long)bh * nt32 * T, cstride = T;
     if (cu) {                                           // packed batch: sh.bh is the head alone, sh.i its place
-        const Place at = place_of(sh.i, cu, n_arg, Ttot, T_arg, lane);
+        const Place at = place_of<32>(sh.i, cu, n_arg, Ttot, T_arg, lane);
         if (at.T == 0) return;
         T = at.T;
         nstrip = (T + 31) / 32;
@@ -1904,12 +1917,12 @@ bwd_dkv_small_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict_
     KvHead kh;
     int ks = sh.i;                                       // the strip; small ones have the most queries
     if (cu) {                                            // packed batch: sh.bh is the head alone, sh.i its place
-        const Place at = place_of(sh.i, cu, n_arg, Ttot, T_arg, lane);
+        const Place at = place_of<32>(sh.i, cu, n_arg, Ttot, T_arg, lane);
         if (at.T == 0) return;
-        packed_kv_head<D>(kh, at.seq, sh.bh, at.c0, at.c0 + at.T, T_arg, 32, H, G, nt32, Ttot);
+        packed_kv_head<D>(kh, at, sh.bh, 32, H, G, nt32, Ttot);
         ks = at.i;
     } else {
-        kv_head<D, false>(kh, sh.bh, T_arg, n_arg, 32, H, G, nt32, cu, Ttot);
+        kv_head(kh, sh.bh, D, T_arg, n_arg, G, nt32);
     }
     const int T = kh.T, nstrip = kh.nkb;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -2105,13 +2118,14 @@ bwd_dkv_small_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict_
 // workspace layout: ca[BH][nt32][T], cb[BH][nt32][T] (fp32; [H][nt32][Ttot] for a packed
 // batch), then the start strips of the queries' 32-row strips (16 bits): [BH][nqb][4], then the
 // partial sums of the remainder-bias gradient (fp32): [BH][nchunk][D].  B, T: batch size and
-// length, or for a packed batch (VL) the number of sequences and the longest length.
-template <int D, bool VL>
+// length, or for a packed batch the number of sequences and the longest length.
+template <int D, Packed PK>
 hipError_t launch_one(const uint16_t* q, const uint16_t* k, const uint16_t* v, const uint16_t* rb,
                       const float* m, const uint16_t* dout, float* dq, float* dk, float* dv,
                       float* drb, float* workspace, int B, int H, int Hkv, int T, int passes, hipStream_t stream,
                       const int* cu, int Ttot)
 {
+    constexpr bool VL = PK != Packed::NO;
     const int BH = B * H;
     const int BHkv = B * Hkv;
     const int G = H / Hkv;
@@ -2127,7 +2141,9 @@ hipError_t launch_one(const uint16_t* q, const uint16_t* k, const uint16_t* v, c
     float* part = reinterpret_cast<float*>(first + (long)BH * nqb * 4);
     const int nchunk = (T + DR_ROWS - 1) / DR_ROWS;
     const Keys keys = keys_of(B, H, Hkv, T, D, VL, Ttot);
-    const long gq = share_grid(BH, nqb, false), gk = share_grid(BHkv, nkb, keys == Keys::PAIRS), gk64 = share_grid(BHkv, nkb64, false);
+    const long gq = block_grid(B, H, T, BQ, PK, Ttot), gk64 = block_grid(B, Hkv, T, 64, PK, Ttot);
+    const long gk = keys == Keys::PAIRS ? share_grid(BHkv, nkb, true) : block_grid(B, Hkv, T, BKW, PK, Ttot);
+    const int shared = VL ? B : BHkv;                    // what the key-stationary kernels' BH counts
     const long strips_q = pieces(B, H, T, 32, VL, Ttot), strips_k = pieces(B, Hkv, T, 32, VL, Ttot);
     const int run_q = VL || G > 1 ? -1 : share_run(BH, nqb), run_k = VL || G > 1 ? -1 : share_run(BHkv, nkb);
     // checked before the first launch, so that an error leaves nothing enqueued
@@ -2148,12 +2164,12 @@ hipError_t launch_one(const uint16_t* q, const uint16_t* k, const uint16_t* v, c
         hipLaunchKernelGGL((bwd_dq_small_kernel<D>), dim3((unsigned)(strips_q + bias_q)), dim3(64 * SmallCfg<D>::NWS), 0, stream, \
                            q, k, v, rb, m, dout, dq, ca, cb, first, T, VL ? H : BH, H, G, VL ? B : nt32, nqb, nt32, cu, Ttot, bias(strips_q)); \
         if ((e = hipGetLastError()) != hipSuccess) return e;                                                    \
-    } else SB_LAUNCH(gq + bias_q, NTHREADS, (bwd_dq_kernel<D, RBV, VL>),                                        \
-              q, k, v, rb, m, dout, dq, ca, cb, first, T, BH, H, G, nqb, nt32, cu, Ttot, run_q, bias(gq))
+    } else SB_LAUNCH(gq + bias_q, NTHREADS, (bwd_dq_kernel<D, RBV, PK>),                                        \
+              q, k, v, rb, m, dout, dq, ca, cb, first, T, VL ? B : BH, H, G, nqb, nt32, cu, Ttot, run_q, bias(gq))
 // d = 128 takes the paired-wave kernel (two waves per SIMD instead of one); smaller head
 // dimensions leave room for two workgroups of the one-wave-per-strip kernel per CU, which
 // is faster there (measured).
-#define SB_DKV(GQAV)                                                                                            \
+#define SB_DKV(GQAV, DRV)                                                                                       \
     if (keys == Keys::STRIPS) {                                                                                 \
         hipLaunchKernelGGL((bwd_dkv_small_kernel<D>), dim3((unsigned)(strips_k + bias_k)), dim3(64 * SmallCfg<D>::NWS), 0, stream, \
                            q, k, v, dout, ca, cb, dk, dv, first, T, VL ? Hkv : BHkv, H, G, VL ? B : nt32, nqb, nt32, cu, Ttot, bias(strips_k)); \
@@ -2161,20 +2177,20 @@ hipError_t launch_one(const uint16_t* q, const uint16_t* k, const uint16_t* v, c
     } else if constexpr (D == 128) {                                                                            \
         constexpr bool CAN = !VL && !GQAV;                                                                      \
         if (keys == Keys::KEYS_64)                                                                              \
-            SB_LAUNCH(gk64 + bias_k, 256, (bwd_dkv_pair_kernel<D, 2, GQAV, VL, false>),                         \
-                      q, k, v, dout, ca, cb, dk, dv, first2, T, BHkv, H, G, nkb64, nqb, nt32, cu, Ttot, bias(gk64)) \
+            SB_LAUNCH(gk64 + bias_k, 256, (bwd_dkv_pair_kernel<D, 2, GQAV, PK, false, DRV>),                    \
+                      q, k, v, dout, ca, cb, dk, dv, first2, T, shared, H, G, nkb64, nqb, nt32, cu, Ttot, bias(gk64)) \
         else if (CAN && keys == Keys::PAIRS)                                                                    \
-            SB_LAUNCH(gk + bias_k, 512, (bwd_dkv_pair_kernel<D, 4, GQAV, VL, CAN>),                             \
-                      q, k, v, dout, ca, cb, dk, dv, first2, T, BHkv, H, G, nkb, nqb, nt32, cu, Ttot, bias(gk)) \
+            SB_LAUNCH(gk + bias_k, 512, (bwd_dkv_pair_kernel<D, 4, GQAV, PK, CAN, DRV>),                        \
+                      q, k, v, dout, ca, cb, dk, dv, first2, T, shared, H, G, nkb, nqb, nt32, cu, Ttot, bias(gk)) \
         else                                                                                                    \
-            SB_LAUNCH(gk + bias_k, 512, (bwd_dkv_pair_kernel<D, 4, GQAV, VL, false>),                           \
-                      q, k, v, dout, ca, cb, dk, dv, first2, T, BHkv, H, G, nkb, nqb, nt32, cu, Ttot, bias(gk)) \
+            SB_LAUNCH(gk + bias_k, 512, (bwd_dkv_pair_kernel<D, 4, GQAV, PK, false, DRV>),                      \
+                      q, k, v, dout, ca, cb, dk, dv, first2, T, shared, H, G, nkb, nqb, nt32, cu, Ttot, bias(gk)) \
     } else if (keys == Keys::TWO_GROUPS) {                                                                      \
-        SB_LAUNCH(gk + bias_k, 2 * NTHREADS, (bwd_dkv_kernel<D, GQAV, VL, 2>),                                  \
-                  q, k, v, dout, ca, cb, dk, dv, first2, T, BHkv, H, G, nkb, nt32, cu, Ttot, run_k, bias(gk));  \
+        SB_LAUNCH(gk + bias_k, 2 * NTHREADS, (bwd_dkv_kernel<D, GQAV, PK, 2, DRV>),                             \
+                  q, k, v, dout, ca, cb, dk, dv, first2, T, shared, H, G, nkb, nt32, cu, Ttot, run_k, bias(gk)); \
     } else {                                                                                                    \
-        SB_LAUNCH(gk + bias_k, NTHREADS, (bwd_dkv_kernel<D, GQAV, VL, 1>),                                      \
-                  q, k, v, dout, ca, cb, dk, dv, first2, T, BHkv, H, G, nkb, nt32, cu, Ttot, run_k, bias(gk));  \
+        SB_LAUNCH(gk + bias_k, NTHREADS, (bwd_dkv_kernel<D, GQAV, PK, 1, DRV>),                                 \
+                  q, k, v, dout, ca, cb, dk, dv, first2, T, shared, H, G, nkb, nt32, cu, Ttot, run_k, bias(gk)); \
     }
     if (passes & 1) {
         if (rb) { SB_DQ(true); }
@@ -2182,9 +2198,13 @@ hipError_t launch_one(const uint16_t* q, const uint16_t* k, const uint16_t* v, c
     }
     if (passes & 2) {
         // a packed batch always takes the grouped variant (a group of one included)
-        if constexpr (VL) { SB_DKV(true) }
-        else if (G > 1)   { SB_DKV(true) }
-        else              { SB_DKV(false) }
+        if (VL || G > 1) {
+            if (drb) { SB_DKV(true, true) }
+            else     { SB_DKV(true, false) }
+        } else if constexpr (!VL) {
+            if (drb) { SB_DKV(false, true) }
+            else     { SB_DKV(false, false) }
+        }
     }
 #undef SB_LAUNCH
 #undef SB_DQ
@@ -2216,7 +2236,7 @@ hipError_t launch_bwd_bf16(const uint16_t* q, const uint16_t* k, const uint16_t*
                            float* drb, float* workspace,
                            int B, int H, int Hkv, int T, int d, int passes, hipStream_t stream)
 {
-#define SB_BWD(DD) launch_one<DD, false>(q, k, v, rb, m, dout, dq, dk, dv, drb, workspace, B, H, Hkv, T, passes, stream, nullptr, 0)
+#define SB_BWD(DD) launch_one<DD, Packed::NO>(q, k, v, rb, m, dout, dq, dk, dv, drb, workspace, B, H, Hkv, T, passes, stream, nullptr, 0)
     if (d == 32) return SB_BWD(32);
     if (d == 64) return SB_BWD(64);
     return SB_BWD(128);
@@ -2228,10 +2248,15 @@ hipError_t launch_bwd_bf16_varlen(const uint16_t* q, const uint16_t* k, const ui
                                   float* drb, float* workspace, const int* cu, int nseq, int H, int Hkv,
                                   int Ttot, int max_T, int d, hipStream_t stream)
 {
-#define SB_BWD(DD) launch_one<DD, true>(q, k, v, rb, m, dout, dq, dk, dv, drb, workspace, nseq, H, Hkv, max_T, 3, stream, cu, Ttot)
-    if (d == 32) return SB_BWD(32);
-    if (d == 64) return SB_BWD(64);
-    return SB_BWD(128);
+#define SB_BWD(DD, PK) launch_one<DD, PK>(q, k, v, rb, m, dout, dq, dk, dv, drb, workspace, nseq, H, Hkv, max_T, 3, stream, cu, Ttot)
+    if (packed_as(nseq, max_T, Ttot) == Packed::ALIKE) {
+        if (d == 32) return SB_BWD(32, Packed::ALIKE);
+        if (d == 64) return SB_BWD(64, Packed::ALIKE);
+        return SB_BWD(128, Packed::ALIKE);
+    }
+    if (d == 32) return SB_BWD(32, Packed::BY_LENGTH);
+    if (d == 64) return SB_BWD(64, Packed::BY_LENGTH);
+    return SB_BWD(128, Packed::BY_LENGTH);
 #undef SB_BWD
 }
 

@@ -135,13 +135,11 @@ __device__ __forceinline__ void weights_of(const float (&g)[16], float t_lo, flo
 }
 
 // VL: packed variable-length batch.  The tensors are [H][Ttot][D] ([H/G][Ttot][D] for k, v),
-// sequence s occupies rows cu[s] .. cu[s+1]-1, BH counts (sequence, head) pairs and T_arg,
-// nqb_arg describe the longest sequence (they size the grid); a workgroup whose
-// blocks lies beyond its own sequence's end returns at once.
+// sequence s occupies rows cu[s] .. cu[s+1]-1, T_arg is at least the longest sequence's length and BH the number of sequences.
 // TRI: measurement variant of the element-wise path.  The in-tile reverse cumulative sum of
 // Algorithm 1 is taken on the matrix pipe, as a product with a triangular matrix of ones,
 // instead of the in-lane chain (see ew_tri()); everything else is the same kernel.
-template <int D, bool WRITE_M, bool RB, bool VL, bool TRI = false>
+template <int D, bool WRITE_M, bool RB, Packed VL, bool TRI = false>
 __global__ void __launch_bounds__(64 * NW, wgs_per_cu(D))
 fwd_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
                 const uint16_t* __restrict__ v, const uint16_t* __restrict__ rb,
@@ -159,23 +157,22 @@ fwd_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     // the branches of share_of(): a short prompt is a chain of such latencies.
     asm volatile("" :: "s"(q), "s"(k), "s"(v), "s"(T_arg), "s"(G));
     const int wg = first_wg + blockIdx.x;
-    const Share sh = in_scalars(share_of(wg, BH, run));
-    const int bh = sh.bh;
+    Share sh;
     int T = T_arg, nqb = nqb_arg;
     long row0, kvrow0;                                  // first row of this head's q / k rows
     int head;
-    if constexpr (VL) {
-        const int seq = bh / H;
-        head = bh % H;
-        const int c0 = cu[seq];
-        T = min(min(cu[seq + 1], Ttot) - c0, T_arg);      // never past the packed rows or the stated maximum
-        if (c0 < 0) return;
+    if constexpr (VL != Packed::NO) {
+        const Place at = block_of<BQ, VL == Packed::BY_LENGTH>(head, wg, H, G, cu, BH, Ttot, T_arg, threadIdx.x & 63);
+        if (at.T == 0) return;
+        sh.i = at.i;
+        T = at.T;
         nqb = (T + BQ - 1) / BQ;
-        if (sh.i >= nqb) return;
-        row0 = (long)head * Ttot + c0;
-        kvrow0 = (long)(head / G) * Ttot + c0;
+        row0 = (long)head * Ttot + at.c0;
+        kvrow0 = (long)(head / G) * Ttot + at.c0;
     } else {
         // grouped kv heads: G consecutive query heads read the same K and V
+        sh = in_scalars(share_of(wg, BH, run));
+        const int bh = sh.bh;
         head = bh % H;
         row0 = bh * (long)T;
         kvrow0 = (long)(G == 1 ? bh : (int)((unsigned)bh / (unsigned)G)) * T;
@@ -665,7 +662,7 @@ fwd_small_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     int T = T_arg, nstrip = n_arg, i = sh.i;
     long row0 = bh * (long)T, kvrow0 = (long)(G == 1 ? bh : (int)((unsigned)bh / (unsigned)G)) * T;
     if (cu) {                                           // packed batch: bh is the head alone, sh.i its place
-        const Place at = place_of(sh.i, cu, n_arg, Ttot, T_arg, lane);
+        const Place at = place_of<32>(sh.i, cu, n_arg, Ttot, T_arg, lane);
         if (at.T == 0) return;
         T = at.T;
         nstrip = (T + 31) / 32;
@@ -901,12 +898,13 @@ fwd_small_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     }
 }
 
-template <int D, bool WRITE_M, bool RB, bool VL = false, bool TRI = false>
+template <int D, bool WRITE_M, bool RB, Packed PK = Packed::NO, bool TRI = false>
 hipError_t launch_one(const uint16_t* q, const uint16_t* k, const uint16_t* v, const uint16_t* rb,
                       uint16_t* o, float* m, int BH, int H, int G, int T, float enough,
                       unsigned long long* tile_counts, hipStream_t stream,
                       const int* cu = nullptr, int Ttot = 0)
 {
+    constexpr bool VL = PK != Packed::NO;
     const long strips = pieces(BH / H, H, T, 32, VL, Ttot);
     if (!TRI && enough == CARRY_EXHAUSTED && (WRITE_M || !tile_counts) && small_fwd_grid(strips, T, D)) {     // halting sweeps stop by blocks
         const int heads = VL ? H : BH, n = VL ? BH / H : (T + 31) / 32;
@@ -915,11 +913,11 @@ hipError_t launch_one(const uint16_t* q, const uint16_t* k, const uint16_t* v, c
         return hipGetLastError();
     }
     const int nqb = (T + BQ - 1) / BQ;
-    const long grid = share_grid(BH, nqb, false);
+    const long grid = block_grid(BH / H, H, T, BQ, PK, Ttot);
     if (grid > 0x7fffffffL) return hipErrorInvalidValue;
     return launch_workgroups(grid, 64 * NW, [&](unsigned n, int first_wg) {
-        hipLaunchKernelGGL((fwd_bf16_kernel<D, WRITE_M, RB, VL, TRI>), dim3(n), dim3(64 * NW), 0, stream,
-                           q, k, v, rb, o, m, T, BH, H, G, nqb, enough, tile_counts, cu, Ttot, VL || G > 1 ? -1 : share_run(BH, nqb), first_wg);
+        hipLaunchKernelGGL((fwd_bf16_kernel<D, WRITE_M, RB, PK, TRI>), dim3(n), dim3(64 * NW), 0, stream,
+                           q, k, v, rb, o, m, T, VL ? BH / H : BH, H, G, nqb, enough, tile_counts, cu, Ttot, VL || G > 1 ? -1 : share_run(BH, nqb), first_wg);
     });
 }
 
@@ -948,7 +946,7 @@ hipError_t launch_fwd_bf16(const uint16_t* q, const uint16_t* k, const uint16_t*
 hipError_t launch_fwd_bf16_tri(const uint16_t* q, const uint16_t* k, const uint16_t* v, uint16_t* o, float* m,
                                int B, int H, int T, hipStream_t stream)
 {
-    return launch_one<128, true, false, false, true>(q, k, v, nullptr, o, m, B * H, H, 1, T, CARRY_EXHAUSTED, nullptr, stream);
+    return launch_one<128, true, false, Packed::NO, true>(q, k, v, nullptr, o, m, B * H, H, 1, T, CARRY_EXHAUSTED, nullptr, stream);
 }
 
 hipError_t launch_fwd_bf16_varlen(const uint16_t* q, const uint16_t* k, const uint16_t* v, const uint16_t* rb,
@@ -957,8 +955,10 @@ hipError_t launch_fwd_bf16_varlen(const uint16_t* q, const uint16_t* k, const ui
 {
     const int BH = nseq * H;
     const int G = H / Hkv;
-#define SB_FWD(DD, WM, RBV) \
-    launch_one<DD, WM, RBV, true>(q, k, v, rb, o, m, BH, H, G, max_T, CARRY_EXHAUSTED, nullptr, stream, cu, Ttot)
+#define SB_FWD(DD, WM, RBV)                                                                                     \
+    (packed_as(nseq, max_T, Ttot) == Packed::ALIKE                                                              \
+         ? launch_one<DD, WM, RBV, Packed::ALIKE>(q, k, v, rb, o, m, BH, H, G, max_T, CARRY_EXHAUSTED, nullptr, stream, cu, Ttot) \
+         : launch_one<DD, WM, RBV, Packed::BY_LENGTH>(q, k, v, rb, o, m, BH, H, G, max_T, CARRY_EXHAUSTED, nullptr, stream, cu, Ttot))
     if (d == 32) {
         if (rb) return m ? SB_FWD(32, true, true) : SB_FWD(32, false, true);
         return m ? SB_FWD(32, true, false) : SB_FWD(32, false, false);

@@ -96,6 +96,31 @@ inline long pieces(int B, int H, int T, int rows, bool packed, int Ttot)
     return packed ? std::min(all, (long)H * (Ttot / rows + B)) : all;
 }
 
+// The 128-row blocks of a packed batch.  ALIKE: every sequence gets as many workgroups as the longest may need, and those beyond its end
+// have nothing to do; block 0 of all sequences and heads, then block 1, ... is longest first as long as the lengths are much the same.
+// BY_LENGTH: as many as pieces() counts, a workgroup looking up its block among all sequences' (longest_first(), below).  With
+// lengths that differ it is the order that counts, and by some heads the empty workgroups.  ALIKE / BY_LENGTH, a third of the heads far, us, forward,
+// backward (`of` the workgroups that ALIKE takes for one of pieces()):
+//   d = 64   H24, 19 of 26 to 4096 rows (4.1) 160 / 150, 430 / 363;  H32 Hkv4, 15 up to 5931 (4.6) 262 / 238, 1920 / 1700;  H2, 5000 and 300 of 16 (32) 46 / 37, 75 / 35;
+//            H16, 2000 and 20 of 700 to 900 (2.1) 68 / 59, 227 / 192;  H16, 8 up to 3341 (1.8) 93 / 79, 269 / 234;  H16, 16 up to 1881 (1.5) 76 / 71, 221 / 213
+//   d = 128  H16, 31 up to 2048 (3.1) 118 / 108, 386 / 340;  H32 Hkv8, 16 up to 2000 (2.7) 130 / 129, 511 / 391;  H12, 8 up to 8000 (2.6) 548 / 425, 1203 / 910;
+//            H16, 40 up to 991 (1.7) 100 / 101, 378 / 346
+//   d = 32   H12, 24 up to 1500 (2.4) 32 / 27, 102 / 87;  H12 Hkv6, 22 up to 8192 (5.1) 185 / 143, 805 / 616;  H16, 40 up to 977 (1.7) 39 / 36, 119 / 107
+// The look-up is 0.3 to 0.9 us ahead of a block's first load.  Not worth it for short sequences, unless they differ much, less so for many:
+//   H24      d64 60 of 300, one of 600 (1.5) 60 / 59, 233 / 239;  d32 60 of 16 to 299 (1.3) 24.2 / 24.5, 78 / 83;  d64 200 of 16 to 399 (1.6) 127 / 138, 481 / 505;  240
+//            of 16 to 200, one of 600 (2.8) 82 / 87, 316 / 323;  but 60 of 16 to 99, one of 260 (2.1) 17.4 / 15.2, 60 / 51;  100 of 16 to 300, one of 800
+//            (3.2) 53 / 48, 208 / 197
+enum class Packed { NO, ALIKE, BY_LENGTH };
+inline Packed packed_as(int nseq, int T, int Ttot)
+{
+    const int least = nseq > 64 ? 15 : Ttot < 512L * nseq ? 10 : 6;
+    return 5L * nseq * ((T + 127) / 128) > least * pieces(nseq, 1, T, 128, true, Ttot) ? Packed::BY_LENGTH : Packed::ALIKE;
+}
+inline long block_grid(int B, int H, int T, int rows, Packed as, int Ttot)
+{
+    return as == Packed::BY_LENGTH ? pieces(B, H, T, rows, true, Ttot) : (long)B * H * ((T + rows - 1) / rows);
+}
+
 // Rows of a sequence, in the mean
 inline int mean_T(int B, int T, bool packed, int Ttot) { return packed ? Ttot / B : T; }
 
@@ -121,8 +146,9 @@ __device__ __forceinline__ int sum_up_to_lane(int x)
     x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xC, 0xF, false);       // row_bcast:31 into rows 2 and 3
     return x;
 }
-// The strips of sequence 0, then of sequence 1, ...: what has nothing to do comes last.  (Among the others, with the offsets alone to say
-// where a sequence's places begin, it takes a CU's turn: the batch above 8.2 and 25.9 us.)
+// The strips (or blocks, of ROWS rows) of sequence 0, then of sequence 1, ...: what has nothing to do comes last.  (Among the others, with the
+// offsets alone to say where a sequence's places begin, it takes a CU's turn: the batch above 8.2 and 25.9 us.)
+template <int ROWS>
 __device__ __forceinline__ Place place_of(int place, const int* __restrict__ cu, int nseq, int Ttot, int T_arg, int lane)
 {
     int s = min(lane, nseq - 1), n0 = cu[s], n1 = cu[s + 1];
@@ -132,7 +158,7 @@ __device__ __forceinline__ Place place_of(int place, const int* __restrict__ cu,
         n0 = cu[s];
         n1 = cu[s + 1];
         const int T = b + lane < nseq && c0 >= 0 && c1 > c0 ? min(c1 - c0, T_arg) : 0;     // never past the packed rows or the stated maximum
-        const int n = (T + 31) >> 5;
+        const int n = (T + ROWS - 1) / ROWS;
         const int upto = sum_up_to_lane(n);
         const unsigned long long beyond = __builtin_amdgcn_ballot_w64(upto > place);
         if (beyond) {
@@ -143,7 +169,6 @@ __device__ __forceinline__ Place place_of(int place, const int* __restrict__ cu,
     }
     return {0, 0, 0, 0};
 }
-
 // Grids of the forward that take one strip of 32 rows a workgroup, its waves taking the strip's subtiles in rounds
 // (fwd_small_kernel), in place of 128-row blocks whose every wave has its rows' chain to itself.  Blocks / strips, us, without m (with it,
 // where it matters, in brackets), all heads far, then a third, then none:
@@ -287,6 +312,78 @@ __host__ __device__ __forceinline__ Share share_of(unsigned wg, unsigned heads, 
 __device__ __forceinline__ Share in_scalars(Share s)
 {
     return {__builtin_amdgcn_readfirstlane(s.bh), __builtin_amdgcn_readfirstlane(s.i)};
+}
+
+// A sequence of n blocks has one of every length 1 .. n (the forward's and the query-stationary pass's chains run to its first row, the
+// key-stationary pass's to its last), block i from the long end one of n - i.  So sum_s max(n_s - x, 0) blocks are longer than x; a bisection
+// over x finds the length of the one at `place`, its rank among those of that length the sequence.  Up to 256 sequences,
+// four to a lane; with more, sequence by sequence (place_of()).
+template <int ROWS>
+__device__ __forceinline__ Place longest_first(int place, const int* __restrict__ cu, int nseq, int Ttot, int T_arg, int lane)
+{
+    constexpr int MOST = 4;
+    if (nseq > 64 * MOST) return place_of<ROWS>(place, cu, nseq, Ttot, T_arg, lane);
+    int c0[MOST], T[MOST], n[MOST];
+#pragma unroll
+    for (int b = 0; b < MOST; ++b) {
+        n[b] = 0;
+        if (64 * b >= nseq) continue;
+        const int s = min(64 * b + lane, nseq - 1);
+        c0[b] = cu[s];
+        const int c1 = min(cu[s + 1], Ttot);
+        T[b] = 64 * b + lane < nseq && c0[b] >= 0 && c1 > c0[b] ? min(c1 - c0[b], T_arg) : 0;
+        n[b] = (T[b] + ROWS - 1) / ROWS;
+    }
+    auto longer = [&](int x) __attribute__((always_inline)) {
+        int sum = max(n[0] - x, 0);
+#pragma unroll
+        for (int b = 1; b < MOST; ++b)
+            if (64 * b < nseq) sum += max(n[b] - x, 0);
+        return __builtin_amdgcn_readlane(sum_up_to_lane(sum), 63);
+    };
+    int x = 0, behind = 0;                              // more than `place` blocks are longer than x, `behind` of them longer than x + 1
+    if (longer(0) <= place) return {0, 0, 0, 0};
+    for (int step = 1 << (31 - __builtin_clz((T_arg + ROWS - 1) / ROWS)); step > 0; step >>= 1) {
+        const int more = longer(x + step);
+        if (more > place) x += step;
+        else behind = more;
+    }
+    int rank = place - behind;
+    Place at = {0, 0, 0, 0};
+#pragma unroll
+    for (int b = 0; b < MOST; ++b) {
+        if (64 * b >= nseq) continue;
+        const unsigned long long has = __builtin_amdgcn_ballot_w64(n[b] > x);
+        const int before = __builtin_amdgcn_mbcnt_hi((unsigned)(has >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)has, 0));
+        const unsigned long long it = __builtin_amdgcn_ballot_w64(n[b] > x && before == rank);
+        if (it) {
+            const int l = __builtin_ctzll(it);
+            at = {64 * b + l, __builtin_amdgcn_readlane(n[b], l) - 1 - x, __builtin_amdgcn_readlane(c0[b], l), __builtin_amdgcn_readlane(T[b], l)};
+        }
+        rank -= __builtin_popcountll(has);              // (below 0 once it is found)
+    }
+    return at;
+}
+// Workgroup wg's block: its head in `head`, its sequence and the rest in the result (T = 0: none).  H heads, G of which share keys and values
+template <int ROWS, bool BY_LENGTH>
+__device__ __forceinline__ Place block_of(int& head, unsigned wg, int H, int G, const int* __restrict__ cu, int nseq, int Ttot, int T_arg, int lane)
+{
+    if constexpr (BY_LENGTH) {
+        // Heads that turn with every block meet every XCD; turning with every fourth, neighbouring blocks of a sequence, which sweep the
+        // same tiles, meet on one: with every block / every fourth, backward H8 d128, 5 up to 5653 rows 500 / 440, H24 d64 above 371 / 363, H7 d64, 31 up
+        // to 5000 310 / 302.  Where four heads are over, a head changes its XCD with every block anyway (H12 d32, 24 up to 1500 84 / 90), and query heads that
+        // share a kv head find its tiles on any (H32 Hkv4 d64 above 1700 / 1840).
+        Share sh = share_of(wg, H, -1);
+        if (G == 1 && H > 4 && H % 8 != 4) sh.bh = (wg + (sh.i >> 2)) % (unsigned)H;
+        sh = in_scalars(sh);
+        head = sh.bh;
+        return longest_first<ROWS>(sh.i, cu, nseq, Ttot, T_arg, lane);
+    } else {
+        const Share sh = in_scalars(share_of(wg, nseq * H, -1));
+        const int seq = sh.bh / H, c0 = cu[seq], T = min(min(cu[seq + 1], Ttot) - c0, T_arg);     // never past the packed rows or the stated maximum
+        head = sh.bh - seq * H;
+        return {seq, sh.i, c0, c0 >= 0 && sh.i * ROWS < T ? T : 0};
+    }
 }
 
 }  // namespace sb

@@ -113,3 +113,49 @@ def test_argument_errors(sb, gen):
         sb.sb_attn_varlen_fwd(qd, kd, vd, cud, 91)
     with pytest.raises(sb.SbAttnError):
         sb.sb_attn_varlen_fwd(qd, kd, vd, cud.to(torch.int64), 50)
+
+
+# lengths of 1 to 5 blocks and a long one, so that blocks are looked up by their length; 1, 2 and 4 sequences to a lane, and more than a
+# wave holds; blocks that end with the sequence, empty sequences, one that takes everything
+BY_LENGTH = {
+    "few": [1900, 5, 128, 0, 384, 385, 127, 1, 640, 33],
+    "64": [1700] + [1 + 37 * i % 200 for i in range(63)],
+    "65": [1 + 53 * i % 200 for i in range(64)] + [2000],
+    "200": [1 + 11 * i % 90 for i in range(120)] + [3000] + [0, 129] * 40,
+    "300": [20] * 150 + [2800] + [9] * 149,
+    "first": [4000] + [0] * 9,
+}
+
+
+@pytest.mark.parametrize("H,Hkv,d", [(16, 16, 32), (9, 9, 64), (12, 12, 128), (4, 4, 64), (24, 12, 128), (20, 5, 32)])
+@pytest.mark.parametrize("lens", BY_LENGTH)
+def test_blocks_by_length(sb, lens, H, Hkv, d):
+    """Every block is found once: all rows are written, and as by a call for each sequence alone.  The weights are those of the same
+    tiles in the same order, so o is the same to the bit where that call takes blocks as well; it may take strips, which round
+    the partial sums of m differently (some 2^-20 of its size) and, with their other carries, the bfloat16 operands of the gradients: two
+    results within the gradients' tolerance differ by at most twice that."""
+    lens = BY_LENGTH[lens]
+    T, g = sum(lens), torch.Generator(device="cuda").manual_seed(7)
+    q, do = (torch.randn(H, T, d, generator=g, device="cuda").bfloat16() for _ in range(2))
+    k, v = (torch.randn(Hkv, T, d, generator=g, device="cuda").bfloat16() for _ in range(2))
+    k[-1] *= 0.05                                            # weights that reach over hundreds of keys
+    cu = torch.tensor([0] + lens, device="cuda").cumsum(0).int()
+    o, m = torch.full_like(q, float("nan")), torch.full((H, T), float("nan"), device="cuda")
+    grads = [torch.full(x.shape, float("nan"), device="cuda") for x in (q, k, v)]
+    sb.sb_attn_varlen_fwd(q, k, v, cu, max(lens), o=o, m=m)
+    sb.sb_attn_varlen_bwd(q, k, v, m, do, cu, max(lens), dq=grads[0], dk=grads[1], dv=grads[2])
+    assert torch.isfinite(m).all()
+    at = 0
+    for n in lens:
+        x = slice(at, at + n)
+        at += n
+        if n == 0 or (n < 100 and x.start % 3):              # (of the many short ones, some)
+            continue
+        one = [t[None, :, x].contiguous() for t in (q, k, v)]
+        o1, m1 = sb.sb_attn_fwd_gqa(*one, want_m=True)
+        assert torch.equal(o[:, x], o1[0]), n
+        assert torch.allclose(m[:, x], m1[0], rtol=1e-5, atol=1e-5), n
+        ref = sb.sb_attn_bwd_gqa(*one, m1, do[None, :, x].contiguous())
+        for a, b in zip(grads, ref):
+            assert (a[:, x] - b[0]).abs().max() <= 2 * max(2e-2, 2.0 ** -8 * b.abs().max()), n
+    assert all(torch.isfinite(a).all() for a in grads) and torch.isfinite(o.float()).all()
