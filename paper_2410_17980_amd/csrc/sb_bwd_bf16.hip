@@ -1626,7 +1626,7 @@ __device__ __forceinline__ void own_landed() { asm volatile("s_waitcnt vmcnt(0) 
 // on, until they are: that is where the sweep starts, and the sums are its carries.
 // Against totals of all subtiles first, in every strip, and one wave adding them up one after the other, all heads far, then none, us:
 // B2 H4 T777 d32 12.5 -> 9.1, 7.3 -> 6.7; B1 H4 T4000 d64 56 -> 38, 22.5 -> 13.3; B1 H8 T700 d128 21.3 -> 16.6, 14.2 -> 12.5.
-template <int D>
+template <int D, bool RB>
 __global__ void __launch_bounds__(64 * SmallCfg<D>::NWS)
 bwd_dq_small_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
                     const uint16_t* __restrict__ v, const uint16_t* __restrict__ rb,
@@ -1646,7 +1646,7 @@ bwd_dq_small_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
     asm volatile("" :: "s"(q), "s"(k), "s"(v), "s"(m), "s"(dout), "s"(T_arg), "s"(G));
     const int tid = threadIdx.x, lane = tid & 63;
     static_assert(NTHR * 8 / D * (D + 4) * 4 <= (int)sizeof(smem), "the partial sums fit");
-    if ((int)blockIdx.x >= bias.work) {
+    if (RB && (int)blockIdx.x >= bias.work) {
         bias_partial_at<D, NTHR>(reinterpret_cast<float*>(smem), blockIdx.x - bias.work, bias, m, dout, T_arg, cu, Ttot, tid);
         return;
     }
@@ -1711,7 +1711,7 @@ bwd_dq_small_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
         }
     }
     float bsum = 0.0f;                      // sum of G over the keys left of the round
-    if (rb) {                               // remainder bias, as in bwd_dq_kernel
+    if constexpr (RB) {                     // remainder bias, as in bwd_dq_kernel
         const u32x4* rs = reinterpret_cast<const u32x4*>(rb + head * D + 8 * hh);
         float dot = 0.0f;
 #pragma unroll
@@ -1892,7 +1892,7 @@ bwd_dq_small_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
 
 // Key-stationary pass: a strip of 32 keys a workgroup, whose waves take its query subtiles (of all
 // query heads of the group) in turn and add their accumulators up at the end.
-template <int D>
+template <int D, bool DR>
 __global__ void __launch_bounds__(64 * SmallCfg<D>::NWS)
 bwd_dkv_small_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
                      const uint16_t* __restrict__ v, const uint16_t* __restrict__ dout,
@@ -1909,7 +1909,7 @@ bwd_dkv_small_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict_
 
     asm volatile("" :: "s"(q), "s"(k), "s"(v), "s"(dout), "s"(ca), "s"(cb), "s"(first), "s"(T_arg));
     const int tid = threadIdx.x, lane = tid & 63;
-    if ((int)blockIdx.x >= bias.work) {
+    if (DR && (int)blockIdx.x >= bias.work) {
         bias_sum<D, NTHR>(reinterpret_cast<float*>(smem), bias, blockIdx.x - bias.work, tid);
         return;
     }
@@ -2161,7 +2161,7 @@ hipError_t launch_one(const uint16_t* q, const uint16_t* k, const uint16_t* v, c
     }
 #define SB_DQ(RBV)                                                                                              \
     if (query_strips(B, H, T, D, VL, Ttot)) {                                                                   \
-        hipLaunchKernelGGL((bwd_dq_small_kernel<D>), dim3((unsigned)(strips_q + bias_q)), dim3(64 * SmallCfg<D>::NWS), 0, stream, \
+        hipLaunchKernelGGL((bwd_dq_small_kernel<D, RBV>), dim3((unsigned)(strips_q + bias_q)), dim3(64 * SmallCfg<D>::NWS), 0, stream, \
                            q, k, v, rb, m, dout, dq, ca, cb, first, T, VL ? H : BH, H, G, VL ? B : nt32, nqb, nt32, cu, Ttot, bias(strips_q)); \
         if ((e = hipGetLastError()) != hipSuccess) return e;                                                    \
     } else SB_LAUNCH(gq + bias_q, NTHREADS, (bwd_dq_kernel<D, RBV, PK>),                                        \
@@ -2171,7 +2171,7 @@ hipError_t launch_one(const uint16_t* q, const uint16_t* k, const uint16_t* v, c
 // is faster there (measured).
 #define SB_DKV(GQAV, DRV)                                                                                       \
     if (keys == Keys::STRIPS) {                                                                                 \
-        hipLaunchKernelGGL((bwd_dkv_small_kernel<D>), dim3((unsigned)(strips_k + bias_k)), dim3(64 * SmallCfg<D>::NWS), 0, stream, \
+        hipLaunchKernelGGL((bwd_dkv_small_kernel<D, DRV>), dim3((unsigned)(strips_k + bias_k)), dim3(64 * SmallCfg<D>::NWS), 0, stream, \
                            q, k, v, dout, ca, cb, dk, dv, first, T, VL ? Hkv : BHkv, H, G, VL ? B : nt32, nqb, nt32, cu, Ttot, bias(strips_k)); \
         if ((e = hipGetLastError()) != hipSuccess) return e;                                                    \
     } else if constexpr (D == 128) {                                                                            \
