@@ -1931,42 +1931,53 @@ bwd_dkv_small_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict_
     const int nq = nstrip - ks;                          // query strips from the keys' own on
     const int nlast = T - (nstrip - 1) * 32;             // rows of the last
 
-    // Which of them reach the keys, as bits, 64 strips of a head at a time: `todo` holds those left of the wave's
-    // share, strips ks + w, ks + w + NWS, ... of all heads one after the other.  The words to come are fetched
-    // one ahead.  (With head, strip and addresses worked out anew for every strip, all heads far, us: B1 H8 Hkv1 T1000 d128 124 -> 103,
-    // T4096 d64 203 -> 185, near 34 -> 25; B1 H8 T700 d128 18.6 -> 17.0.)
+    // Which of them reach the keys, as bits, 64 strips at a time of all heads' one after the other: `todo` holds those left of the
+    // wave's share, every NWS-th.  The words to come are fetched one ahead.  (With head, strip and addresses worked out anew for
+    // every strip, all heads far, us: B1 H8 Hkv1 T1000 d128 124 -> 103, T4096 d64 203 -> 185, near 34 -> 25; B1 H8 T700 d128 18.6 -> 17.0.
+    // With a word for each head, a memory latency each, B2 H8 Hkv2 T90 d32 6.6 us in place of 5.7, B8 H32 Hkv4 T800 51 in place of 47, near 44 in place of 39.)
     constexpr unsigned long long EVERY = NWS == 8 ? 0x0101010101010101ull : 0x1111111111111111ull;
     static_assert(NWS == 4 || NWS == 8, "strips of a wave");
-    int g = -1, w0 = 0, gn = 0, w0n = 0, turn = wave;    // head and first strip (from ks on) of this word, and of the next one
+    const int all = G * nq;
+    int w0 = 0, wn = 0, g = 0, x0 = 0;                   // first strip of this word, and of the next one; head, and where its strips begin
     unsigned long long todo = 0;
-    const uint16_t* fg = first + kh.qhead0 * nqb_arg * 4 + ks;
-    int fn = lane < nq ? fg[lane] : 0x7fffffff;
-    const uint16_t *Qg = nullptr, *Gg = nullptr;         // head g's rows from the keys' own strip on, and its carries
-    const float *cag = nullptr, *cbg = nullptr;
+    const uint16_t* const fg = first + kh.qhead0 * nqb_arg * 4 + ks;
+    auto word = [&](int x) __attribute__((always_inline)) {
+        int head = 0, i = x;
+        if (G > 1) {                                     // (from a quotient good to less than one)
+            head = (int)((float)x * __builtin_amdgcn_rcpf((float)nq));
+            i = x - head * nq;
+            const int up = i >= nq ? 1 : i < 0 ? -1 : 0;
+            head += up;
+            i -= up * nq;
+        }
+        return x < all ? (int)fg[(long)head * (nqb_arg * 4) + i] : 0x7fffffff;
+    };
+    int fn = word(lane);
+    const uint16_t *Qg, *Gg;                             // head g's rows from the keys' own strip on, and its carries
+    const float *cag, *cbg;
+    auto at_head = [&]() __attribute__((always_inline)) {
+        const long r0 = (kh.qrow0 + g * kh.qrow_step + k0) * D, c0 = kh.cbase + g * kh.cbase_step + ks * kh.cstride + k0;
+        Qg = q + r0;
+        Gg = dout + r0;
+        cag = ca + c0;
+        cbg = cb + c0;
+    };
+    at_head();
     auto next = [&](int& r) __attribute__((always_inline)) {
         while (todo == 0) {
-            if (gn >= G) return false;
-            todo = __builtin_amdgcn_ballot_w64(fn <= ks) & (EVERY << turn);
-            w0 = w0n;
-            if (gn != g) {
-                g = gn;
-                const long r0 = (kh.qrow0 + g * kh.qrow_step + k0) * D, c0 = kh.cbase + g * kh.cbase_step + ks * kh.cstride + k0;
-                Qg = q + r0;
-                Gg = dout + r0;
-                cag = ca + c0;
-                cbg = cb + c0;
-            }
-            w0n += 64;
-            if (w0n >= nq) {
-                w0n = 0;
-                ++gn;
-                turn = (turn - nq) & (NWS - 1);
-                fg += (long)nqb_arg * 4;
-            }
-            if (gn < G) fn = w0n + lane < nq ? fg[w0n + lane] : 0x7fffffff;
+            if (wn >= all) return false;
+            todo = __builtin_amdgcn_ballot_w64(fn <= ks) & (EVERY << wave);
+            w0 = wn;
+            wn += 64;
+            if (wn < all) fn = word(wn + lane);
         }
-        r = w0 + __builtin_ctzll(todo);
+        const int x = w0 + __builtin_ctzll(todo);
         todo &= todo - 1;
+        if (x - x0 >= nq) {
+            do { x0 += nq; ++g; } while (x - x0 >= nq);
+            at_head();
+        }
+        r = x - x0;
         return true;
     };
     const uint32_t base = lds_offset(smem) + wave * WAVE;
@@ -1984,9 +1995,16 @@ bwd_dkv_small_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict_
     // K and V pass through the second buffer of the first wave
     const uint32_t k_at = lds_offset(smem) + 2 * C::SUB, v_at = k_at + C::SUB;
     stage_strip<D>(k + kh.base + (long)k0 * D, v + kh.base + (long)k0 * D, min(T - k0, 32), k_at, v_at, wave, lane);
+    // Behind them, before it is known whether it reaches the keys, the first strip of the first two waves' shares: the two nearest
+    // ones nearly always do, and where they are all there is they are what bounds the strip.
+    const bool ahead = wave < 2 && wave < nq;
+    if (ahead) fetch(wave, 0);
     int r = 0;
     bool more = next(r);
-    if (more) fetch(r, 0);
+    if (more && !(ahead && g == 0 && r == wave)) {
+        own_landed();                                    // nothing is still on its way into the buffer
+        fetch(r, 0);
+    }
     own_landed();
     barrier_nofence();
     bf16x8 kf[D / 16], vf[D / 16];                       // A operands: MFMA row n <- key perm_row(n)
