@@ -647,7 +647,7 @@ __global__ void __launch_bounds__(FwdSmallCfg<D>::NTHR)
 fwd_small_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
                  const uint16_t* __restrict__ v, const uint16_t* __restrict__ rb,
                  uint16_t* __restrict__ o, float* __restrict__ m,
-                 int T_arg, int BH, int H, int G, int n_arg,       // n_arg: strips a head; packed batch: sequences
+                 int T_arg, int BH, int H, int G, int n_arg, float enough,       // n_arg: strips a head; packed batch: sequences
                  unsigned long long* __restrict__ clocks, const int* __restrict__ cu, int Ttot)
 {
     using C = FwdSmallCfg<D>;
@@ -729,7 +729,7 @@ fwd_small_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
         for (int w = 0; w < NWS; ++w) t[w] = s_tot[st][w][n];
     };
     auto ended = [&]() __attribute__((always_inline)) {          // alike in all waves
-        done = __builtin_amdgcn_ballot_w64(!(a >= CARRY_EXHAUSTED)) == 0;
+        done = __builtin_amdgcn_ballot_w64(!(a >= enough)) == 0;
         return done || top < NWS;
     };
     // Both kinds of waves pass the same barriers.
@@ -906,10 +906,14 @@ hipError_t launch_one(const uint16_t* q, const uint16_t* k, const uint16_t* v, c
 {
     constexpr bool VL = PK != Packed::NO;
     const long strips = pieces(BH / H, H, T, 32, VL, Ttot);
-    if (!TRI && enough == CARRY_EXHAUSTED && (WRITE_M || !tile_counts) && small_fwd_grid(strips, T, D)) {     // halting sweeps stop by blocks
+    // What tile_counts counts are the blocks' tiles.  A halting sweep: strips where every one has a CU to itself, whatever the heads' reach: blocks /
+    // strips, us, eps 1e-9, a third of the heads far, then none: B1 H8 T1000 d64 17.4 / 8.3, 6.5 / 5.2; B1 H2 T4000 d64 6.6 / 5.2 (none); B2 H3 T1300 d128 29 / 16,
+    // 8.8 / 5.3; B1 H3 T2700 d32 35 / 14.5, 5.4 / 4.7; with more, near heads lose: B1 H4 T4000 d64 57 / 23.5, 6.6 / 9.0; B1 H10 T3000 d32 39 / 23, 5.6 / 14.3.
+    const bool fits = small_fwd_grid(strips, T, D) && (enough == CARRY_EXHAUSTED || strips <= 256);
+    if (!TRI && (WRITE_M || !tile_counts) && fits) {
         const int heads = VL ? H : BH, n = VL ? BH / H : (T + 31) / 32;
         hipLaunchKernelGGL((fwd_small_kernel<D>), dim3((unsigned)strips), dim3(FwdSmallCfg<D>::NTHR), 0, stream,
-                           q, k, v, rb, o, m, T, heads, H, G, n, tile_counts, cu, Ttot);
+                           q, k, v, rb, o, m, T, heads, H, G, n, enough, tile_counts, cu, Ttot);
         return hipGetLastError();
     }
     const int nqb = (T + BQ - 1) / BQ;

@@ -157,3 +157,21 @@ def test_packed_places(sb, oracle, gen, lens, H, Hkv, max_T, d):
     ref = oracle.bwd_varlen(to64(q), to64(k), to64(v), to64(g), cu, r=to64(r))
     for name, a, x in zip(("dq", "dk", "dv", "dr"), got, ref):
         check_grad(name, to64(a), x)
+
+
+@pytest.mark.parametrize("B,H,T,d", [(1, 1, 321, 32), (1, 3, 1500, 32), (1, 1, 65, 64), (2, 1, 700, 64), (1, 1, 8192, 64), (1, 8, 1024, 128), (1, 8, 1025, 128)])
+@pytest.mark.parametrize("shift", [-3.0, -6.0])
+def test_halting_strips(sb, gen, B, H, T, d, shift):
+    """A halting sweep of a small grid, against the whole one: off by at most eps max|v| and a rounding of each to bfloat16, whatever is
+    skipped; and what nothing may be skipped of is the same to the bit, counted (by blocks) or not."""
+    q, k, v = dev(*gen.biased_gaussian(B, H, T, d, seed=T, shift=shift, dtype="bf16"))
+    whole = sb.sb_attn_fwd(q, k, v)
+    for eps in (1e-2, 1e-6):
+        o = sb.sb_attn_fwd_halt(q, k, v, eps)
+        assert (o.float() - whole.float()).abs().max() <= eps * v.float().abs().max() + 2.0 ** -8 * whole.float().abs().max(), eps
+    k[..., -1] = -200.0 * d ** 0.5                            # logits of -200 and below: no stick is used up
+    q[..., -1] = 1.0
+    k[..., :-1] = 0.0
+    counts = torch.zeros(2, dtype=torch.int64, device="cuda")
+    o = sb.sb_attn_fwd_halt(q, k, v, 1e-6)
+    assert torch.equal(o, sb.sb_attn_fwd(q, k, v)) and torch.equal(o, sb.sb_attn_fwd_halt(q, k, v, 1e-6, tile_counts=counts))
