@@ -18,9 +18,9 @@ MAIN = r"""
 #include "sb_share.h"
 int main(int argc, char** argv)
 {
-    int heads, nblk, pairs;
-    while (scanf("%d %d %d", &heads, &nblk, &pairs) == 3) {
-        const int grid = (int)sb::share_grid(heads, nblk, pairs), run = sb::share_run(heads, nblk);
+    int heads, nblk, pairs, d;                                   // d: of the forward and the query-stationary pass, or 0
+    while (scanf("%d %d %d %d", &heads, &nblk, &pairs, &d) == 4) {
+        const int grid = (int)sb::share_grid(heads, nblk, pairs), run = d ? sb::query_run(heads, nblk, d) : sb::share_run(heads, nblk);
         printf("%d %d\n", grid, run);
         for (int wg = 0; wg < grid; ++wg) {
             const sb::Share s = pairs ? sb::share_in_pairs(wg, nblk) : sb::share_of(wg, heads, run);
@@ -40,8 +40,8 @@ def order(tmp_path_factory):
     subprocess.run([HIPCC, "-std=c++17", "-O1", "--offload-host-only", f"-I{CSRC}", "main.hip", "-o", "main"],
                    cwd=tmp, check=True, stdout=subprocess.DEVNULL, stderr=subprocess.DEVNULL)
 
-    def get(heads, nblk, pairs=False):
-        out = subprocess.run([str(tmp / "main")], input=f"{heads} {nblk} {int(pairs)}\n", text=True, check=True,
+    def get(heads, nblk, pairs=False, d=0):
+        out = subprocess.run([str(tmp / "main")], input=f"{heads} {nblk} {int(pairs)} {d}\n", text=True, check=True,
                              stdout=subprocess.PIPE).stdout.split()
         grid, run = int(out[0]), int(out[1])
         return np.array(out[2:], dtype=np.int64).reshape(grid, 2), 1 << run if run >= 0 else 0
@@ -107,3 +107,19 @@ def test_costly_heads_are_spread(order):
             load = np.array([cost[x == c].sum() for c in range(8)])
             worst.append(load.max() / load.mean())
         assert np.mean(worst) <= 1.35, (B, H, nblk, np.mean(worst))
+
+
+@pytest.mark.parametrize("heads,nblk,d,run", [(128, 16, 64, 2), (96, 8, 128, 2), (96, 7, 128, 0), (128, 16, 32, 0), (48, 32, 64, 4), (32, 32, 32, 4), (32, 32, 128, 2),
+                                              (24, 47, 128, 4), (40, 20, 64, 2), (24, 31, 64, 0), (24, 32, 64, 4), (24, 64, 128, 2), (24, 64, 64, 4), (32, 128, 128, 4)])
+def test_runs_of_the_forward(order, heads, nblk, d, run):
+    """Every block once, the longest first, a head's blocks on one XCD for a run and on all eight over the launch."""
+    got, r = order(heads, nblk, d=d)
+    assert r == run
+    assert sorted(map(tuple, got)) == [(h, i) for h in range(heads) for i in range(nblk)]
+    assert np.all(np.diff(got[:, 1]) >= 0)
+    x = np.empty((heads, nblk), dtype=np.int64)
+    x[got[:, 0], got[:, 1]] = np.arange(len(got)) % 8
+    for i in range(nblk - 1 if run else 0):
+        assert np.array_equal(x[:, i] == x[:, i + 1], np.full(heads, (i + 1) % run != 0)), i
+    if nblk >= 8 * max(run, 1):
+        assert all(len(set(x[h])) == 8 for h in range(heads))
