@@ -60,8 +60,9 @@ int sb_attn_fwd(const void* q, const void* k, const void* v, void* o,
 
 /*
  * Inference forward with early halt (the paper's "conditional computation",
- * section 4.1): as sb_attn_fwd, but a block of 128 query rows stops sweeping keys
- * once every one of its rows has less than eps of its stick left
+ * section 4.1): as sb_attn_fwd, but a block of 128 query rows (in small grids, unless
+ * tiles are counted, a strip of 32) stops sweeping keys once every one of its rows has
+ * less than eps of its stick left
  * (prod (1 - beta) < eps over the keys swept so far).  No skipped key can weigh more
  * than what is left, so |o_j - exact o_j| <= eps * max_i |v_i| per component.
  * 0 < eps < 1 (SB_ERR_SHAPE otherwise).  How much is skipped depends on the data.
