@@ -127,3 +127,19 @@ def test_argument_errors(sb, gen):
     q, k, v = make(gen, 1, 2, 2, 40, 64, seed=14)
     with pytest.raises(sb.SbAttnError):
         sb.sb_attn_decode(*dev(q, k, v), T=41)                 # more valid rows than the cache holds
+
+
+@pytest.mark.parametrize("H,Hkv,T,d", [(200, 200, 2047, 64), (200, 200, 2048, 64), (200, 200, 2049, 64), (260, 260, 2048, 32), (384, 128, 1793, 32), (260, 260, 2049, 32)])
+def test_many_heads_alone_or_not(sb, H, Hkv, T, d):
+    """Caches at the edge between one workgroup a head and three launches, against the same call with m, which reads every key by the
+    second launch: the same fp32 sums in another order, rounded to bfloat16 once."""
+    g = torch.Generator(device="cuda").manual_seed(T)
+    q = torch.randn(1, H, d, generator=g, device="cuda").bfloat16()
+    k, v = (torch.randn(1, Hkv, T, d, generator=g, device="cuda") for _ in range(2))
+    k[:, 2::3] *= 0.02                                       # half of the stick that is left a key,
+    k[:, 1::3, :, 0] -= 8.0                                  # or hardly any, or all, by the sign of the first component of q
+    k, v = k.bfloat16(), v.bfloat16()
+    o = sb.sb_attn_decode(q, k, v)
+    o2, m = sb.sb_attn_decode(q, k, v, want_m=True)
+    assert torch.isfinite(m).all()
+    assert (o.float() - o2.float()).abs().max() <= 2.0 ** -8 * max(1.0, float(o2.float().abs().max()))

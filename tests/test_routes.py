@@ -178,6 +178,20 @@ def test_decode_routes(ask):
     assert all(kind(r, g) == SPREAD for r, g in zip(rows, ask(rows)))
 
 
+def test_decode_of_many_heads(ask):
+    """Larger caches: one workgroup a head up to 2048 keys at d = 32, and at d = 64 where the heads are most of a round of the chip; spread
+    up to 45 MB beyond.  With m every key is taken by the second launch from 1537 keys on."""
+    want = {ONE: [(16, 16, 16, 2048, 32), (32, 16, 16, 2048, 32), (24, 24, 8, 1600, 32), (16, 16, 16, 2048, 64), (24, 24, 8, 2048, 64), (16, 16, 16, 1536, 128)],
+            SPREAD: [(6, 20, 20, 2048, 32), (6, 20, 20, 2560, 32), (4, 16, 16, 2560, 64), (2, 16, 16, 2500, 128)],
+            FAR_AND_NEAR: [(16, 16, 16, 2049, 32), (33, 16, 16, 2048, 32), (16, 16, 16, 2049, 64), (12, 12, 12, 2000, 64), (17, 16, 16, 2000, 64), (16, 16, 16, 1537, 128),
+                           (4, 16, 16, 2800, 64)]}
+    for name, shapes in want.items():
+        rows = [decode(*s) for s in shapes]
+        assert [kind(r, g) for r, g in zip(rows, ask(rows))] == [name] * len(rows), name
+    rows = [decode(*s, True) for s in ((16, 16, 16, 1537, 32), (16, 16, 16, 2048, 64))]
+    assert all(kind(r, g) == SPREAD for r, g in zip(rows, ask(rows)))
+
+
 def test_decode_chunks_cover_the_keys_and_fit(ask):
     rng = random.Random(5)
     rows = []
