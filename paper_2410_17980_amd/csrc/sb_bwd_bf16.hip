@@ -1565,12 +1565,12 @@ bwd_dkv_pair_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
 // subtiles.  Here a workgroup takes one strip of 32 rows, and its waves share the other side's subtiles, each
 // staging its own, without a barrier for the tiles.  Still bound by the chain: B2 H4 T777 d32 takes 8 + 8 us,
 // of which 4 to 5 each are a launch and its first loads.  Which grids: small_grid().
-template <int D> struct SmallCfg {
-    static constexpr int NWS = D == 128 ? 4 : 8;        // waves
+template <int D, int NW_ = D == 128 ? 4 : 8> struct SmallCfg {
+    static constexpr int NWS = NW_;                     // waves (four at d <= 64: four_waves())
     static constexpr int ROW = D * 2;
     static constexpr int SUB = 32 * ROW;                // one 32-row subtile of one matrix
     static constexpr int WAVE = 4 * SUB;                // two matrices, double buffered
-    static constexpr int MAXSUB = 128;                  // subtiles of a strip for whose carries there is room
+    static constexpr int MAXSUB = D == 64 && NWS == 4 ? 96 : 128;      // (two workgroups a CU) subtiles of a strip for whose carries there is room
     static constexpr int LOADS = SUB / 1024;            // of 16 bytes a lane, for a subtile
 };
 
@@ -1605,12 +1605,12 @@ __device__ __forceinline__ void stage_rows(const uint16_t* src, int rows, uint32
 // The strip's own 32 rows of two matrices, into the places x_at and y_at in LDS: whole rows and once, every wave its share.  (As
 // operands from memory, 32 bytes of 32 rows an instruction and all of it by every wave, the two took a CU 2000, 4800 and 7000 clocks
 // at d = 32, 64 and 128: a tenth to a third of a near strip's time.)
-template <int D>
+template <int D, int NWS>
 __device__ __forceinline__ void stage_strip(const uint16_t* X, const uint16_t* Y, int rows, uint32_t x_at, uint32_t y_at, int wave, int lane)
 {
     using C = SmallCfg<D>;
     constexpr int CPR = C::ROW / 16;
-    for (int i = wave; i < 2 * C::LOADS; i += C::NWS) {
+    for (int i = wave; i < 2 * C::LOADS; i += NWS) {
         const bool x = i < C::LOADS;
         const int j = x ? i : i - C::LOADS, row = j * (1024 / C::ROW) + lane / CPR;
         dma16_to_lds_at(scalar_base(x ? X : Y), min(row, rows - 1) * C::ROW + (((lane % CPR) ^ swz_perm<D>(row)) << 4), (x ? x_at : y_at) + j * 1024);
@@ -1626,8 +1626,8 @@ __device__ __forceinline__ void own_landed() { asm volatile("s_waitcnt vmcnt(0) 
 // on, until they are: that is where the sweep starts, and the sums are its carries.
 // Against totals of all subtiles first, in every strip, and one wave adding them up one after the other, all heads far, then none, us:
 // B2 H4 T777 d32 12.5 -> 9.1, 7.3 -> 6.7; B1 H4 T4000 d64 56 -> 38, 22.5 -> 13.3; B1 H8 T700 d128 21.3 -> 16.6, 14.2 -> 12.5.
-template <int D, bool RB>
-__global__ void __launch_bounds__(64 * SmallCfg<D>::NWS)
+template <int D, bool RB, int NWS>
+__global__ void __launch_bounds__(64 * NWS)
 bwd_dq_small_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
                     const uint16_t* __restrict__ v, const uint16_t* __restrict__ rb,
                     const float* __restrict__ m,
@@ -1636,8 +1636,8 @@ bwd_dq_small_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
                     int T_arg, int BH, int H, int G, int n_arg, int nqb_arg, int nt32,       // n_arg: strips a head; packed batch: sequences
                     const int* __restrict__ cu, int Ttot, BiasGrad bias)
 {
-    using C = SmallCfg<D>;
-    constexpr int NWS = C::NWS, NTHR = 64 * NWS;
+    using C = SmallCfg<D, NWS>;
+    constexpr int NTHR = 64 * NWS;
     __shared__ __attribute__((aligned(1024))) char smem[NWS * C::WAVE];
     __shared__ __attribute__((aligned(1024))) float s_car[C::MAXSUB][32];      // carries per subtile, from the diagonal on, and row
     __shared__ float s_l[2][NWS][32], s_g[2][NWS][32];  // a round's softplus totals, and sums of G
@@ -1695,7 +1695,7 @@ bwd_dq_small_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
     float a2 = -m[row0 + min(q0 + n, T - 1)] * SB_LOG2E;
     static_assert(2 * C::SUB <= (int)sizeof(s_car), "the strip's rows fit");
     const uint32_t x_at = lds_offset(reinterpret_cast<const char*>(s_car)), y_at = x_at + C::SUB;
-    stage_strip<D>(q + (row0 + q0) * D, dout + (row0 + q0) * D, nlast, x_at, y_at, wave, lane);
+    stage_strip<D, NWS>(q + (row0 + q0) * D, dout + (row0 + q0) * D, nlast, x_at, y_at, wave, lane);
     if (wave <= strip) stage_k(wave, 0);
     own_landed();
     barrier_nofence();
@@ -1892,8 +1892,8 @@ bwd_dq_small_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
 
 // Key-stationary pass: a strip of 32 keys a workgroup, whose waves take its query subtiles (of all
 // query heads of the group) in turn and add their accumulators up at the end.
-template <int D, bool DR>
-__global__ void __launch_bounds__(64 * SmallCfg<D>::NWS)
+template <int D, bool DR, int NWS>
+__global__ void __launch_bounds__(64 * NWS)
 bwd_dkv_small_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
                      const uint16_t* __restrict__ v, const uint16_t* __restrict__ dout,
                      const float* __restrict__ ca, const float* __restrict__ cb,
@@ -1901,9 +1901,10 @@ bwd_dkv_small_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict_
                      int T_arg, int BH, int H, int G, int n_arg, int nqb_arg, int nt32,       // n_arg: strips a head; packed batch: sequences
                      const int* __restrict__ cu, int Ttot, BiasGrad bias)
 {
-    using C = SmallCfg<D>;
-    constexpr int NWS = C::NWS, NTHR = 64 * NWS;
-    constexpr int WAVE = C::WAVE + 2 * SCR_MAT;          // Q and dO subtiles, double buffered; A and dZ scratch
+    using C = SmallCfg<D, NWS>;
+    constexpr int NTHR = 64 * NWS;
+    constexpr int WAVE = C::WAVE;                        // Q and dO subtiles, double buffered; A and dZ take their place in turn
+    static_assert(2 * SCR_MAT <= 2 * C::SUB, "A and dZ fit");
     __shared__ __attribute__((aligned(1024))) char smem[NWS * WAVE];
     static_assert(NWS * WAVE <= 160 * 1024, "LDS budget");
 
@@ -1994,7 +1995,7 @@ bwd_dkv_small_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict_
     };
     // K and V pass through the second buffer of the first wave
     const uint32_t k_at = lds_offset(smem) + 2 * C::SUB, v_at = k_at + C::SUB;
-    stage_strip<D>(k + kh.base + (long)k0 * D, v + kh.base + (long)k0 * D, min(T - k0, 32), k_at, v_at, wave, lane);
+    stage_strip<D, NWS>(k + kh.base + (long)k0 * D, v + kh.base + (long)k0 * D, min(T - k0, 32), k_at, v_at, wave, lane);
     // Behind them, before it is known whether it reaches the keys, the first strip of the first two waves' shares: the two nearest
     // ones nearly always do, and where they are all there is they are what bounds the strip.
     const bool ahead = wave < 2 && wave < nq;
@@ -2022,7 +2023,9 @@ bwd_dkv_small_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict_
 #pragma unroll
     for (int t = 0; t < 2; ++t)
         qtr[t] = base + tile_off_nat<D>(8 * (gg >> 1) + (li >> 2) + 4 * t, 2 * (gg & 1) + ((li & 3) >> 1)) + 8 * (li & 1);
-    const uint32_t scr = base + C::WAVE;
+    // A and dZ on their way to the second products' operands: in the place of the subtiles they come from, whose operands
+    // have all been asked for by then (a wave's LDS accesses stay in order)
+    const uint32_t scr = base;
     const uint32_t sw_off = scr + scr_off(n, 2 * hh);
     uint32_t st_off[2];
 #pragma unroll
@@ -2088,16 +2091,17 @@ bwd_dkv_small_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict_
         SubtileOut so;
         subtile_stage2<false, true>(so, ch, pacc, car, cbl, hh);
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        lds_store16(sw_off, so.pa[0]);
-        lds_store16(sw_off ^ 16, so.pa[1]);
-        lds_store16(sw_off + SCR_MAT, so.pz[0]);
-        lds_store16((sw_off ^ 16) + SCR_MAT, so.pz[1]);
+        lds_store16(sw_off + buf, so.pa[0]);
+        lds_store16((sw_off ^ 16) + buf, so.pa[1]);
+        lds_store16(sw_off + buf + SCR_MAT, so.pz[0]);
+        lds_store16((sw_off ^ 16) + buf + SCR_MAT, so.pz[1]);
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         bf16x8 at[2], zt[2];
 #pragma unroll
         for (int s2 = 0; s2 < 2; ++s2) {
-            at[s2] = tr_pair_at(st_off[0] + 16 * s2 * 64, st_off[1] + 16 * s2 * 64);
-            zt[s2] = tr_pair_at(st_off[0] + 16 * s2 * 64 + SCR_MAT, st_off[1] + 16 * s2 * 64 + SCR_MAT);
+            const uint32_t x0 = st_off[0] + buf + 16 * s2 * 64, x1 = st_off[1] + buf + 16 * s2 * 64;
+            at[s2] = tr_pair_at(x0, x1);
+            zt[s2] = tr_pair_at(x0 + SCR_MAT, x1 + SCR_MAT);
         }
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
 #pragma unroll
@@ -2159,6 +2163,7 @@ hipError_t launch_one(const uint16_t* q, const uint16_t* k, const uint16_t* v, c
     float* part = reinterpret_cast<float*>(first + (long)BH * nqb * 4);
     const int nchunk = (T + DR_ROWS - 1) / DR_ROWS;
     const Keys keys = keys_of(B, H, Hkv, T, D, VL, Ttot);
+    const int mean = mean_T(B, T, VL, Ttot);
     const long gq = block_grid(B, H, T, BQ, PK, Ttot), gk64 = block_grid(B, Hkv, T, 64, PK, Ttot);
     const long gk = keys == Keys::PAIRS ? share_grid(BHkv, nkb, true) : block_grid(B, Hkv, T, BKW, PK, Ttot);
     const int shared = VL ? B : BHkv;                    // what the key-stationary kernels' BH counts
@@ -2179,8 +2184,13 @@ hipError_t launch_one(const uint16_t* q, const uint16_t* k, const uint16_t* v, c
     }
 #define SB_DQ(RBV)                                                                                              \
     if (query_strips(B, H, T, D, VL, Ttot)) {                                                                   \
-        hipLaunchKernelGGL((bwd_dq_small_kernel<D, RBV>), dim3((unsigned)(strips_q + bias_q)), dim3(64 * SmallCfg<D>::NWS), 0, stream, \
-                           q, k, v, rb, m, dout, dq, ca, cb, first, T, VL ? H : BH, H, G, VL ? B : nt32, nqb, nt32, cu, Ttot, bias(strips_q)); \
+        auto go = [&](auto waves) {                                                                             \
+            constexpr int NW = decltype(waves)::value;                                                          \
+            hipLaunchKernelGGL((bwd_dq_small_kernel<D, RBV, NW>), dim3((unsigned)(strips_q + bias_q)), dim3(64 * NW), 0, stream, \
+                               q, k, v, rb, m, dout, dq, ca, cb, first, T, VL ? H : BH, H, G, VL ? B : nt32, nqb, nt32, cu, Ttot, bias(strips_q)); \
+        };                                                                                                      \
+        if (four_waves(strips_q, 1, mean, D)) go(std::integral_constant<int, 4>());                                      \
+        else go(std::integral_constant<int, SmallCfg<D>::NWS>());                                               \
         if ((e = hipGetLastError()) != hipSuccess) return e;                                                    \
     } else SB_LAUNCH(gq + bias_q, NTHREADS, (bwd_dq_kernel<D, RBV, PK>),                                        \
               q, k, v, rb, m, dout, dq, ca, cb, first, T, VL ? B : BH, H, G, nqb, nt32, cu, Ttot, run_q, bias(gq))
@@ -2189,8 +2199,13 @@ hipError_t launch_one(const uint16_t* q, const uint16_t* k, const uint16_t* v, c
 // is faster there (measured).
 #define SB_DKV(GQAV, DRV)                                                                                       \
     if (keys == Keys::STRIPS) {                                                                                 \
-        hipLaunchKernelGGL((bwd_dkv_small_kernel<D, DRV>), dim3((unsigned)(strips_k + bias_k)), dim3(64 * SmallCfg<D>::NWS), 0, stream, \
-                           q, k, v, dout, ca, cb, dk, dv, first, T, VL ? Hkv : BHkv, H, G, VL ? B : nt32, nqb, nt32, cu, Ttot, bias(strips_k)); \
+        auto go = [&](auto waves) {                                                                             \
+            constexpr int NW = decltype(waves)::value;                                                          \
+            hipLaunchKernelGGL((bwd_dkv_small_kernel<D, DRV, NW>), dim3((unsigned)(strips_k + bias_k)), dim3(64 * NW), 0, stream, \
+                               q, k, v, dout, ca, cb, dk, dv, first, T, VL ? Hkv : BHkv, H, G, VL ? B : nt32, nqb, nt32, cu, Ttot, bias(strips_k)); \
+        };                                                                                                      \
+        if (four_waves(strips_k, G, mean, D)) go(std::integral_constant<int, 4>());                                      \
+        else go(std::integral_constant<int, SmallCfg<D>::NWS>());                                               \
         if ((e = hipGetLastError()) != hipSuccess) return e;                                                    \
     } else if constexpr (D == 128) {                                                                            \
         constexpr bool CAN = !VL && !GQAV;                                                                      \

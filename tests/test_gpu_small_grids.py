@@ -50,6 +50,13 @@ def test_strips_of_two_words(sb, oracle, gen, H, Hkv, T, d):
     run(sb, oracle, gen, H, Hkv, T, d, range(Hkv), seed=60)
 
 
+@pytest.mark.parametrize("H,Hkv,T", [(21, 21, 993), (15, 15, 2200), (11, 11, 3105), (72, 24, 1750)])
+@pytest.mark.parametrize("d", [32, 64])
+def test_strips_of_four_waves(sb, oracle, gen, H, Hkv, T, d):
+    """Enough strips for the workgroups of four waves, in the query-stationary pass or (the groups) the key-stationary one."""
+    run(sb, oracle, gen, H, Hkv, T, d, range(3), seed=70)
+
+
 @pytest.mark.parametrize("d", [32, 64, 128])
 def test_longest_strips(sb, oracle, gen, d):
     """128 subtiles a row, the most the kernels' arrays hold; one more row takes the 128-row blocks."""

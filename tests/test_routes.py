@@ -28,6 +28,11 @@ int main()
             continue;
         }
         const long strips = pieces(B, H, T, 32, packed, Ttot);
+        if (packed == 3) {                              // waves of a strip's workgroup
+            printf("%d %d\n", query_strips(B, H, T, d, false, 0) && four_waves(pieces(B, H, T, 32, false, 0), 1, T, d),
+                   keys_of(B, H, Hkv, T, d, false, 0) == Keys::STRIPS && four_waves(pieces(B, Hkv, T, 32, false, 0), H / Hkv, T, d));
+            continue;
+        }
         printf("%d %d %ld %d\n", small_fwd_grid(strips, T, d), query_strips(B, H, T, d, packed, Ttot), strips,
                (int)keys_of(B, H, Hkv, T, d, packed, Ttot));
     }
@@ -101,6 +106,13 @@ def test_shapes_of_the_gpu_tests(ask):
                                 ([100] * 13, 4, 2, 1300)):
         for d in (32, 64, 128):
             assert strips(ask, packed(lens, H, d, max_T, Hkv)) == (d > 32 or max_T > 320, True, True), (lens, d)
+
+
+def test_shapes_of_four_waves(ask):
+    """test_gpu_small_grids.py, test_strips_of_four_waves."""
+    for d in (32, 64):
+        assert ask([(1, H, Hkv, T, d, 3, 0) for H, Hkv, T in ((21, 21, 993), (15, 15, 2200), (11, 11, 3105), (72, 24, 1750))]) == \
+            [(1, 1)] * 3 + [(0, 1)], d
 
 
 def test_block_shapes(ask):
