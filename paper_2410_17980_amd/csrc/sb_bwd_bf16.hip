@@ -1893,7 +1893,7 @@ bwd_dq_small_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
 // Key-stationary pass: a strip of 32 keys a workgroup, whose waves take its query subtiles (of all
 // query heads of the group) in turn and add their accumulators up at the end.
 template <int D, bool DR, int NWS>
-__global__ void __launch_bounds__(64 * NWS)
+__global__ void __launch_bounds__(64 * NWS, D == 32 && NWS == 4 ? 3 : 1)        // (three workgroups a CU: left alone it takes registers for two)
 bwd_dkv_small_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
                      const uint16_t* __restrict__ v, const uint16_t* __restrict__ dout,
                      const float* __restrict__ ca, const float* __restrict__ cb,

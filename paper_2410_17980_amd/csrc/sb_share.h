@@ -241,15 +241,15 @@ inline bool take_in_turn(int B, int H, int Hkv, int T, bool packed, int Ttot)
 //   beyond             B1 H14 T4096 (448) 152 / 185, 121 / 105; B1 H16 T4096 (512) 172 / 209, 121 / 116
 constexpr long small_kv_grid(int nkb) { return std::clamp(64L + 16L * nkb, 256L, 384L); }
 
-// Strips of the backward at d <= 64 whose workgroups have four waves in place of eight: two share a CU (of the query-stationary ones at d = 32 three).  A near
+// Strips of the backward at d <= 64 whose workgroups have four waves in place of eight: two (d = 64) or three (d = 32) share a CU.  A near
 // strip has two or three tiles and keeps no more waves busy, whatever there are; a far one's chain takes twice the rounds, which counts until
 // there are two of them for every CU.  Whole step, eight / four waves, us, none far, then a third, then all:
-//   d = 32   B1 H21 T993 (672 strips) 41 / 32, 45 / 41, 49 / 43;  B1 H12 T4096 (1536) 85 / 64, 148 / 131, 212 / 189;  B5 H2 T3480 (1090) 70 / 54, - , 150 / 137;
-//            B1 H9 T4096 (1152) 75 / 59, 124 / 130, 176 / 163
+//   d = 32   B1 H21 T993 (672 strips) 41 / 29, 45 / 40, 49 / 41;  B1 H12 T4096 (1536) 85 / 60, 148 / 127, 212 / 189 (two a CU, as all figures of all heads far but the first);  B5 H2 T3480 (1090) 70 / 51, - , 150 / 137;
+//            B1 H9 T4096 (1152) 75 / 59 (two a CU), 124 / 125, 176 / 163
 //   d = 64   B1 H21 T993 51 / 45, 55 / 52, 64 / 57;  B1 H14 T2500 (1106) 83 / 69, 122 / 108, 156 / 142
 // and not    d = 32 B1 H10 T2100 (660) 43 / 34, 56 / 63, 71 / 67;  B1 H8 T2000 (504) all 51 / 58;  d = 64 B1 H12 T900 (348) all 35 / 41
 // The key-stationary pass of grouped heads, whose chains are G times as long: B2 H36 Hkv12 T1750 d64 (1320) 120 / 116, 180 / 175;  B8 H16 Hkv4 T1500 d32
-// (1504) 113 / 108, 184 / 182, d64 all 333 / 310;  not B1 H33 Hkv11 T3870 d32 (1331) 114 / 108, 278 / 307;  B1 H24 Hkv12 T3000 d64 (1128) 96 / 89, 185 / 194;  B4 H32
+// (1504) 113 / 108 (two a CU), 184 / 171, d64 all 333 / 310;  not B1 H33 Hkv11 T3870 d32 (1331) 114 / 108, 278 / 307;  B1 H24 Hkv12 T3000 d64 (1128) 96 / 89, 185 / 194;  B4 H32
 // Hkv4 T800 d32 (800) all 82 / 104
 inline bool four_waves(long strips, int G, int mean, int d)
 {
