@@ -15,7 +15,7 @@
 //     the operand brings a CU 15 bytes a clock, one whose lanes lie side by side 55.)
 // Measured, B1 H1 T256 d64: 228 us with one lane per query row walking the keys one by one -> 9.8 us;
 // B1 H1 T2048 d128 5163 -> 66 us, B4 H8 T2048 d128 5715 -> 603 us.  With K and Q by whole rows and exponential and logarithm
-// of its own: 9.8 -> 6.4, 66 -> 51, 603 -> 445 us (77 TFLOP/s); B4 H8 T2048 d32 277 -> 167 us.  Against fp64 the error of o
+// of its own: 9.8 -> 6.5, 66 -> 50, 605 -> 443 us (78 TFLOP/s); B4 H8 T2048 d32 279 -> 166 us.  Against fp64 the error of o
 // is at most what it was with the library's functions, a third less where logits are of the order of 1.
 #include "sb_kernels.h"
 #include "sb_mma.h"
@@ -29,14 +29,29 @@ constexpr int F32_THREADS = 64 * F32_NW;
 
 // e^x for the x <= 0 that occur here, to about an ulp: what the rounding of x log2(e) and of log2(e) itself leaves
 // over is put back to first order.  (The library's expf and log1pf, 30 and 100 instructions with branches, took half the
-// time of a subtile.)
-__device__ __forceinline__ float exp_f32(float x)
+// time of a subtile.)  v_exp_f32 gives no subnormals: with LOW, where the result may be one, it is taken 2^64 times as large.
+template <bool LOW> __device__ __forceinline__ float exp_f32(float x)
 {
     constexpr float L = 1.44269504088896340736f, LO = (float)(1.44269504088896340736 - (double)L);
     const float p = x * L;
     const float rest = __builtin_fmaf(x, LO, __builtin_fmaf(x, L, -p));
-    const float r = fast_exp2(p);
-    return r == 0.0f ? 0.0f : __builtin_fmaf(r * rest, SB_LN2, r);       // (x = -inf: rest is not a number)
+    const bool low = LOW && p < -126.0f;
+    const float r = fast_exp2(low ? p + 64.0f : p);
+    const float e = __builtin_fmaf(r * rest, SB_LN2, r);
+    if constexpr (!LOW) return e;
+    return r == 0.0f ? 0.0f : __builtin_amdgcn_ldexpf(e, low ? -64 : 0);      // (x = -inf: rest is not a number)
+}
+// of four: with LOW where one of a wave's is below log(2^-126) (in every case, us: B1 H1 T256 d64 6.9 in place of 6.5)
+__device__ __forceinline__ void exp_of_four(float (&x)[4])
+{
+    const bool low = fminf(fminf(x[0], x[1]), fminf(x[2], x[3])) < -87.3f;
+    if (__builtin_expect(__builtin_amdgcn_ballot_w64(low) != 0, 0)) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) x[r] = exp_f32<true>(x[r]);
+        return;
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) x[r] = exp_f32<false>(x[r]);
 }
 // log(1 + e), 0 <= e <= 1: 2 atanh(s), s = e / (2 + e) <= 1/3, by its series up to s^15 / 15 (the next term: 1.4e-9 of the sum)
 __device__ __forceinline__ float log1p_f32(float e)
@@ -151,16 +166,21 @@ fwd_f32_kernel(const float* __restrict__ q, const float* __restrict__ k, const f
             z0 = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[j][2], qf[j][2], z0, 0, 0, 0);
             z1 = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[j][3], qf[j][3], z1, 0, 0, 0);
         }
-        float x[4], c[4], run = 0.0f;                          // log sigmoid(z); this lane's keys r+1..3
+        float z[4], e[4], x[4], c[4], run = 0.0f;              // x: log sigmoid(z); c: this lane's keys r+1..3
         bool seen[4];
 #pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            z[r] = (z0[r] + z1[r]) * scale;
+            asm("" : "+v"(z[r]));                              // rounded, the same in every use
+            e[r] = -fabsf(z[r]);
+        }
+        exp_of_four(e);
+#pragma unroll
         for (int r = 3; r >= 0; --r) {
-            float z = (z0[r] + z1[r]) * scale;
-            asm("" : "+v"(z));                                 // rounded, the same in every use
             seen[r] = 16 * sub + 4 * g + r < q0 + n;
             // softplus(z) = max(z, 0) + log(1 + e^{-|z|}); z less that, each part by itself, loses nothing where z is large
-            const float over = fmaxf(z, 0.0f), l = log1p_f32(exp_f32(-fabsf(z)));
-            x[r] = (z - over) - l;
+            const float over = fmaxf(z[r], 0.0f), l = log1p_f32(e[r]);
+            x[r] = (z[r] - over) - l;
             c[r] = run;
             run += seen[r] ? over + l : 0.0f;
         }
@@ -172,10 +192,10 @@ fwd_f32_kernel(const float* __restrict__ q, const float* __restrict__ k, const f
         s += pair + x2;
         float w[4];
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const float a = exp_f32(x[r] - (off + c[r]));
-            w[r] = seen[r] ? a : 0.0f;
-        }
+        for (int r = 0; r < 4; ++r) w[r] = x[r] - (off + c[r]);
+        exp_of_four(w);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) w[r] = seen[r] ? w[r] : 0.0f;
 #pragma unroll
         for (int r = 0; r < 4; ++r)
 #pragma unroll
@@ -194,14 +214,15 @@ fwd_f32_kernel(const float* __restrict__ q, const float* __restrict__ k, const f
 #pragma unroll
     for (int w = 0; w < F32_NW; ++w)
         if (w < wave) nearer += tot[w];
+    float f[4] = {-nearer[0], -nearer[1], -nearer[2], -nearer[3]};
+    exp_of_four(f);
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-        const float f = exp_f32(-nearer[r]);
 #pragma unroll
         for (int j = 0; j < NV; ++j) {
             vec x;
 #pragma unroll
-            for (int e = 0; e < VEC; ++e) x[e] = f * acc[j * VEC + e][r];
+            for (int e = 0; e < VEC; ++e) x[e] = f[r] * acc[j * VEC + e][r];
             *reinterpret_cast<vec*>(&s_o[wave][4 * g + r][16 * VEC * j + VEC * n]) = x;
         }
     }

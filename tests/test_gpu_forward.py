@@ -309,9 +309,13 @@ def test_f32_weight_of_one_key(sb):
     sp = torch.where(z > 700, z.double(), sp)
     assert ((o[0, :, 1].double() / w[:, None] - 1).abs().amax(1) <= 2.0 ** -23 * (3 + z.double().abs() / 2).clamp(max=60)).all()
     assert ((m[0, :, 1].double() / -sp - 1).abs() <= 2.0 ** -23 * (3 + (-z.double()).clamp(min=0) / 2)).all()
-    far = torch.tensor([-90.0, -104.0, -1e4, -3e38, -float("inf")]).cuda()
+    # below 2^-126 results are subnormal, 2^-149 apart, and rounded twice
+    far = torch.cat([torch.linspace(-104, -86, 181), torch.tensor([-1e4, -3e38, -float("inf")])]).cuda()
     o, m = sb.sb_attn_fwd_f32(*one_key_logits(far), want_m=True)
-    assert (o[0, :, 1].abs() <= 1e-38).all() and (m.abs() <= 1e-38).all()
+    w = torch.exp(far.double())
+    bound = w * 2.0 ** -23 * (3 + far.double().abs().clamp(max=200) / 2) + 2.0 ** -148
+    assert ((o[0, :, 1].double() - w[:, None]).abs() <= bound[:, None]).all()
+    assert ((m[0, :, 1].double() + w).abs() <= bound).all()
 
 
 @pytest.mark.parametrize("z", [float("nan"), float("inf"), -float("inf")])
