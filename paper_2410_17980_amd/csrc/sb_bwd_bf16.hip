@@ -1617,6 +1617,9 @@ __device__ __forceinline__ void stage_strip(const uint16_t* X, const uint16_t* Y
     }
 }
 
+// by how much a row's carries are too large, `left` being the one of the diagonal's subtile: rounding, if it is that small
+__device__ __forceinline__ float overshoot(float left) { return fabsf(left) < 16.0f ? left : 0.0f; }
+
 // what a wave has staged has landed, and its reads of the buffer to be refilled have returned
 __device__ __forceinline__ void own_landed() { asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory"); }
 
@@ -1624,6 +1627,11 @@ __device__ __forceinline__ void own_landed() { asm volatile("s_waitcnt vmcnt(0) 
 // one barrier to add up the softplus totals; A and G; one barrier to add up the G of the subtiles further left; dZ.  What the
 // carries start from is m.  Where m says that the rows are exhausted on the way, the totals are taken first, from the diagonal
 // on, until they are: that is where the sweep starts, and the sums are its carries.
+// Counting down from m, a row's carries are all off by what is left at the diagonal, where nothing should be: the roundings of m and
+// of the sums on the way, of numbers as large as m, 2e-5 of a weight where m is near exhaustion.  Every weight, and all that is linear in them,
+// is off by the same factor; overshoot() takes it out, here of dQ, in the key-stationary pass of A and dZ.  (Share of the bf16 weights above 2^-12 that
+// are rounded otherwise than in fp64, rows with 80 to 130 bits of their stick used up, H8 T1000 d128: 1.5e-3 -> 9e-4, as with totals from the diagonal.
+// Costs up to 1 % of a step, 2 % where the heads of a group of 8 share a kv head.)
 // Against totals of all subtiles first, in every strip, and one wave adding them up one after the other, all heads far, then none, us:
 // B2 H4 T777 d32 12.5 -> 9.1, 7.3 -> 6.7; B1 H4 T4000 d64 56 -> 38, 22.5 -> 13.3; B1 H8 T700 d128 21.3 -> 16.6, 14.2 -> 12.5.
 template <int D, bool RB, int NWS>
@@ -1876,6 +1884,8 @@ bwd_dq_small_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
     // ---- the waves' shares added up, in a fixed order.  dqacc[b][r] is query row 8*(r/4) + 4*hh + r%4, column 32b + n
     barrier_lds();                                       // everyone is done with the tiles
     float* const red = reinterpret_cast<float*>(smem);
+    float* const right = s_l[0][0];                      // factor of a row
+    if (wave == 0 && hh == 0) right[n] = ends ? 1.0f : fast_exp2(overshoot(a2));
 #pragma unroll
     for (int b = 0; b < D / 32; ++b)
 #pragma unroll
@@ -1886,7 +1896,7 @@ bwd_dq_small_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
         f32x4 x = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
         for (int w = 0; w < NWS; ++w) x += *reinterpret_cast<const f32x4*>(&red[(w * 32 + row) * D + c]);
-        if (q0 + row < T) *reinterpret_cast<f32x4*>(dq + (row0 + q0 + row) * D + c) = x * scale;
+        if (q0 + row < T) *reinterpret_cast<f32x4*>(dq + (row0 + q0 + row) * D + c) = x * (scale * right[row]);
     }
 }
 
@@ -1899,7 +1909,7 @@ bwd_dkv_small_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict_
                      const float* __restrict__ ca, const float* __restrict__ cb,
                      float* __restrict__ dk, float* __restrict__ dv, const uint16_t* __restrict__ first,
                      int T_arg, int BH, int H, int G, int n_arg, int nqb_arg, int nt32,       // n_arg: strips a head; packed batch: sequences
-                     const int* __restrict__ cu, int Ttot, BiasGrad bias)
+                     const int* __restrict__ cu, int Ttot, bool strips_q, BiasGrad bias)       // strips_q: the carries are bwd_dq_small_kernel's
 {
     using C = SmallCfg<D, NWS>;
     constexpr int NTHR = 64 * NWS;
@@ -1984,12 +1994,13 @@ bwd_dkv_small_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict_
     const uint32_t base = lds_offset(smem) + wave * WAVE;
     int off[C::LOADS];
     subtile_offsets<D, false>(off, lane);
-    float cn0 = 0.0f, cn1 = 0.0f;
+    float cn0 = 0.0f, cn1 = 0.0f, cn2 = 0.0f;
     auto fetch = [&](int r, int st) __attribute__((always_inline)) {
         const int rows = r == nq - 1 ? nlast : 32;
         const unsigned at = r * 32 + min(n, rows - 1);
         cn0 = cag[at];
         cn1 = cbg[at];
+        if (strips_q) cn2 = (cag + (long)r * kh.cstride)[at];          // of the diagonal's subtile (blocks do not always leave one)
         stage_rows<D>(Qg + (long)r * 32 * D, rows, base + st * 2 * C::SUB, off, lane);
         stage_rows<D>(Gg + (long)r * 32 * D, rows, base + st * 2 * C::SUB + C::SUB, off, lane);
     };
@@ -2041,7 +2052,8 @@ bwd_dkv_small_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict_
 
     for (int st = 0; more; st ^= 1) {
         own_landed();
-        float car = cn0, cbl = cn1;
+        const float over = overshoot(cn2);
+        float car = cn0 - over, cbl = cn1 * fast_exp2(over);
         asm volatile("" : "+v"(car), "+v"(cbl));
         const uint32_t buf = st * 2 * C::SUB;
         const bool diag = r == 0;
@@ -2202,7 +2214,8 @@ hipError_t launch_one(const uint16_t* q, const uint16_t* k, const uint16_t* v, c
         auto go = [&](auto waves) {                                                                             \
             constexpr int NW = decltype(waves)::value;                                                          \
             hipLaunchKernelGGL((bwd_dkv_small_kernel<D, DRV, NW>), dim3((unsigned)(strips_k + bias_k)), dim3(64 * NW), 0, stream, \
-                               q, k, v, dout, ca, cb, dk, dv, first, T, VL ? Hkv : BHkv, H, G, VL ? B : nt32, nqb, nt32, cu, Ttot, bias(strips_k)); \
+                               q, k, v, dout, ca, cb, dk, dv, first, T, VL ? Hkv : BHkv, H, G, VL ? B : nt32, nqb, nt32, cu, Ttot, \
+                               query_strips(B, H, T, D, VL, Ttot), bias(strips_k));                             \
         };                                                                                                      \
         if (four_waves(strips_k, G, mean, D)) go(std::integral_constant<int, 4>());                                      \
         else go(std::integral_constant<int, SmallCfg<D>::NWS>());                                               \

@@ -113,6 +113,17 @@ def test_shapes_of_four_waves(ask):
     for d in (32, 64):
         assert ask([(1, H, Hkv, T, d, 3, 0) for H, Hkv, T in ((21, 21, 993), (15, 15, 2200), (11, 11, 3105), (72, 24, 1750))]) == \
             [(1, 1)] * 3 + [(0, 1)], d
+    assert ask([(1, 12, 12, 3200, 64, 3, 0)]) == [(1, 1)]               # test_sharp_and_far_rows_in_one_strip
+
+
+def test_shapes_of_the_tests_of_carries(ask):
+    """test_gpu_small_grids.py: strips in both passes."""
+    import test_gpu_small_grids as t
+    rows = [(1, p[0], p[0], p[1], p[2], 0, 0) for f in (t.test_weights_of_rows_that_are_nearly_exhausted, t.test_sharp_and_far_rows_in_one_strip)
+            for p in f.pytestmark[0].args[1]]
+    assert len(rows) == 12
+    for row, (_, dq, _, keys) in zip(rows, ask(rows)):
+        assert dq and KEYS[keys] == "strips", row
 
 
 def test_block_shapes(ask):
