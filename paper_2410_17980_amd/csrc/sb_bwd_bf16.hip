@@ -271,13 +271,14 @@ __device__ __forceinline__ void store_strip(float* out, int rows, const f32x16 (
 // the two passes, the first step's behind the query-stationary blocks, the second's behind the key-stationary ones, and fill CUs
 // that have no block left: as launches of their own they took 5 us of 25 (B2 H4 T124 d64), 10 us of 220 (B4 H12 T2048 d128).
 // Rows that used up their stick (exp(m) = 0 in fp32) are not read (nor is a NaN in them).  Both steps are a few memory
-// latencies long, all loads of a thread in flight at once.
-constexpr int DR_ROWS = 128;
+// latencies long, all loads of a thread in flight at once.  A packed batch is one batch entry whose chunks are those of its sequences, one
+// sequence after the other, found as its strips are (place_of()): as many as pieces() counts, not as max_T leaves room for in every sequence (64 of 32
+// rows, H4 d64, max_T 2048, whole backward 47.7 -> 18.8 us; H24 d64, 19 up to 4096, 385 -> 359).
 struct BiasGrad {
-    float* part;              // [BH][nchunk][D]
+    float* part;              // [B * H][nchunk][D]
     float* dr;                // [H][D]
     int work;                 // workgroups of the pass; those from here on are the bias's
-    int B, H, nchunk;
+    int B, H, nchunk;         // packed batch: B = 1
 };
 
 // part of head bh's rows from m, dout on, of which `rows` (at most DR_ROWS) exist; red: (NTHR * 8 / D) * (D + 4) floats of LDS
@@ -318,17 +319,19 @@ __device__ __forceinline__ void bias_partial(float* red, const float* __restrict
         out[tid] = s;
     }
 }
-// chunk `at` of the launch, of all heads and (sequences of a packed batch: cu) batch entries
+// chunk `at` of the launch, of all heads and batch entries (packed batch: cu, of nseq sequences)
 template <int D, int NTHR>
 __device__ __forceinline__ void bias_partial_at(float* red, int at, const BiasGrad& bias, const float* __restrict__ m, const uint16_t* __restrict__ dout,
-                                                int T, const int* __restrict__ cu, int Ttot, int tid)
+                                                int T, const int* __restrict__ cu, int nseq, int Ttot, int tid)
 {
-    const int bh = at / bias.nchunk, chunk = at - bh * bias.nchunk;
+    const int bh = at / bias.nchunk;
+    int chunk = at - bh * bias.nchunk;
     long row0 = (long)bh * T;
-    if (cu) {                                 // bh = sequence * H + head; chunks past the sequence's end give 0
-        const int c0 = cu[bh / bias.H];
-        T = c0 < 0 ? 0 : min(min(cu[bh / bias.H + 1], Ttot) - c0, T);
-        row0 = (bh % bias.H) * (long)Ttot + c0;
+    if (cu) {
+        const Place p = place_of<DR_ROWS>(chunk, cu, nseq, Ttot, T, tid & 63);     // (none: T = 0, a sum of no rows)
+        chunk = p.i;
+        T = p.T;
+        row0 = (long)bh * Ttot + p.c0;
     }
     row0 += chunk * DR_ROWS;
     bias_partial<D, NTHR>(red, m + row0, dout + row0 * D, bias.part + (long)at * D, min(T - chunk * DR_ROWS, DR_ROWS), tid);
@@ -379,7 +382,7 @@ bwd_dq_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     if constexpr (RB) {
         static_assert(NTHREADS * 8 / D * (D + 4) * 4 <= 2 * C::STAGE, "the partial sums fit");
         if (wg >= bias.work) {
-            bias_partial_at<D, NTHREADS>(reinterpret_cast<float*>(smem), wg - bias.work, bias, m, dout, T_arg, VL != Packed::NO ? cu : nullptr, Ttot, threadIdx.x);
+            bias_partial_at<D, NTHREADS>(reinterpret_cast<float*>(smem), wg - bias.work, bias, m, dout, T_arg, VL != Packed::NO ? cu : nullptr, BH, Ttot, threadIdx.x);
             return;
         }
     }
@@ -1655,7 +1658,7 @@ bwd_dq_small_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
     const int tid = threadIdx.x, lane = tid & 63;
     static_assert(NTHR * 8 / D * (D + 4) * 4 <= (int)sizeof(smem), "the partial sums fit");
     if (RB && (int)blockIdx.x >= bias.work) {
-        bias_partial_at<D, NTHR>(reinterpret_cast<float*>(smem), blockIdx.x - bias.work, bias, m, dout, T_arg, cu, Ttot, tid);
+        bias_partial_at<D, NTHR>(reinterpret_cast<float*>(smem), blockIdx.x - bias.work, bias, m, dout, T_arg, cu, n_arg, Ttot, tid);
         return;
     }
     const Share sh = in_scalars(share_of(blockIdx.x, BH, -1));
@@ -2151,7 +2154,7 @@ bwd_dkv_small_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict_
 
 // workspace layout: ca[BH][nt32][T], cb[BH][nt32][T] (fp32; [H][nt32][Ttot] for a packed
 // batch), then the start strips of the queries' 32-row strips (16 bits): [BH][nqb][4], then the
-// partial sums of the remainder-bias gradient (fp32): [BH][nchunk][D].  B, T: batch size and
+// partial sums of the remainder-bias gradient (fp32): [BH][nchunk][D], [H][nchunk][D] for a packed batch.  B, T: batch size and
 // length, or for a packed batch the number of sequences and the longest length.
 template <int D, Packed PK>
 hipError_t launch_one(const uint16_t* q, const uint16_t* k, const uint16_t* v, const uint16_t* rb,
@@ -2173,7 +2176,8 @@ hipError_t launch_one(const uint16_t* q, const uint16_t* k, const uint16_t* v, c
     uint16_t* first = reinterpret_cast<uint16_t*>(cb + ncarry);
     const uint32_t* first2 = reinterpret_cast<const uint32_t*>(first);     // of a tile's two strips
     float* part = reinterpret_cast<float*>(first + (long)BH * nqb * 4);
-    const int nchunk = (T + DR_ROWS - 1) / DR_ROWS;
+    const int entries = VL ? 1 : B;                      // of the bias's gradient
+    const int nchunk = bias_chunks(B, T, VL, Ttot);
     const Keys keys = keys_of(B, H, Hkv, T, D, VL, Ttot);
     const int mean = mean_T(B, T, VL, Ttot);
     const long gq = block_grid(B, H, T, BQ, PK, Ttot), gk64 = block_grid(B, Hkv, T, 64, PK, Ttot);
@@ -2183,9 +2187,9 @@ hipError_t launch_one(const uint16_t* q, const uint16_t* k, const uint16_t* v, c
     const int run_q = VL || G > 1 ? -1 : query_run(BH, nqb, D), run_k = VL || G > 1 ? -1 : share_run(BHkv, nkb);
     // checked before the first launch, so that an error leaves nothing enqueued
     // workgroups of the bias's gradient behind those of the passes
-    const long bias_q = drb ? nchunk * (long)BH : 0, bias_k = drb ? H : 0;
+    const long bias_q = drb ? (long)nchunk * entries * H : 0, bias_k = drb ? H : 0;
     if (gq + bias_q > 0x7fffffffL || gk + bias_k > 0x7fffffffL) return hipErrorInvalidValue;
-    auto bias = [&](long work) { return BiasGrad{part, drb, (int)work, B, H, nchunk}; };
+    auto bias = [&](long work) { return BiasGrad{part, drb, (int)work, entries, H, nchunk}; };
     hipError_t e = hipSuccess;
 #define SB_LAUNCH(WGS, THREADS, KERNEL, ...)                                                                    \
     {                                                                                                           \

@@ -96,6 +96,10 @@ inline long pieces(int B, int H, int T, int rows, bool packed, int Ttot)
     return packed ? std::min(all, (long)H * (Ttot / rows + B)) : all;
 }
 
+// Gradient of the remainder bias: chunks of DR_ROWS rows, of one batch entry or of all of a packed batch's sequences
+constexpr int DR_ROWS = 128;
+inline int bias_chunks(int B, int T, bool packed, int Ttot) { return (int)pieces(packed ? B : 1, 1, T, DR_ROWS, packed, Ttot); }
+
 // The 128-row blocks of a packed batch.  ALIKE: every sequence gets as many workgroups as the longest may need, and those beyond its end
 // have nothing to do; block 0 of all sequences and heads, then block 1, ... is longest first as long as the lengths are much the same.
 // BY_LENGTH: as many as pieces() counts, a workgroup looking up its block among all sequences' (longest_first(), below).  With

@@ -87,6 +87,16 @@ def test_loose_length_bound_gives_the_same_result(sb, oracle, gen):
         assert torch.equal(a, b)
 
 
+@pytest.mark.parametrize("H,lens", [(3, [0] * 3 + [1, 128, 129, 0, 300, 127]), (1, [0] * 4 + [1, 0, 129, 33])])
+@pytest.mark.parametrize("d", [32, 64, 128])
+def test_bias_gradient_of_many_sequences(sb, oracle, gen, H, lens, d):
+    """Chunks of 128 rows at the sequences' ends, none for empty ones, more sequences than a wave has lanes, and a bound on their
+    lengths that leaves room for many times as many; blocks and (one head) strips."""
+    lens = lens * 9
+    q, k, v, g, cu = packed(gen, H, H, lens, d, seed=12, kind="biased_gaussian", shift=-4.0)
+    check(sb, oracle, q, k, v, g, cu, max_T=1400, r=gen.remainder_embedding(H, d, seed=13))
+
+
 def test_equal_lengths_match_the_batched_call(sb, gen):
     """Packing B equal sequences gives, bit for bit, the batched entry points' results."""
     B, H, T, d = 3, 2, 200, 128

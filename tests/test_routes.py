@@ -33,6 +33,10 @@ int main()
                    keys_of(B, H, Hkv, T, d, false, 0) == Keys::STRIPS && four_waves(pieces(B, Hkv, T, 32, false, 0), H / Hkv, T, d));
             continue;
         }
+        if (packed == 4) {                              // packed batch: chunks a head of the remainder bias's gradient
+            printf("%d\n", bias_chunks(B, T, true, Ttot));
+            continue;
+        }
         printf("%d %d %ld %d\n", small_fwd_grid(strips, T, d), query_strips(B, H, T, d, packed, Ttot), strips,
                (int)keys_of(B, H, Hkv, T, d, packed, Ttot));
     }
@@ -81,6 +85,26 @@ def test_packed_strips_are_counted_and_launched_as_they_exist(ask):
             least.append(H * sum((n + 31) // 32 for n in lens))
     for row, strips, got in zip(rows, least, ask(rows)):
         assert strips <= got[2] <= strips + row[0] * row[1]
+
+
+def test_chunks_of_the_bias_in_packed_batches(ask):
+    """Every row once, however loose max_T is; no more than one chunk a sequence too many."""
+    rng = random.Random(7)
+    rows, least = [], []
+    for _ in range(200):
+        lens = [rng.choice((0, 1, 127, 128, 129, rng.randrange(1, 3000))) for _ in range(rng.randrange(1, 200))] + [5]
+        for max_T in {max(lens), sum(lens)}:
+            rows.append((len(lens), 1, 1, max_T, 64, 4, sum(lens)))
+            least.append(sum((n + 127) // 128 for n in lens))
+    for row, chunks, (got,) in zip(rows, least, ask(rows)):
+        assert chunks <= got <= chunks + row[0]
+
+
+def test_routes_of_the_bias_in_packed_batches(ask):
+    """test_gpu_varlen.py, test_bias_gradient_of_many_sequences."""
+    import test_gpu_varlen as t
+    for (H, lens), want in zip(t.test_bias_gradient_of_many_sequences.pytestmark[1].args[1], (False, True)):
+        assert all(strips(ask, packed(lens * 9, H, d, 1400))[1:] == (want, want) for d in (32, 64, 128))
 
 
 def test_strips_of_packed_batches(ask):
