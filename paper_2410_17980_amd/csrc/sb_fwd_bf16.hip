@@ -906,23 +906,26 @@ hipError_t launch_one(const uint16_t* q, const uint16_t* k, const uint16_t* v, c
 {
     constexpr bool VL = PK != Packed::NO;
     const long strips = pieces(BH / H, H, T, 32, VL, Ttot);
-    // What tile_counts counts are the blocks' tiles.  A halting sweep: strips where every one has a CU to itself, whatever the heads' reach: blocks /
+    // A halting sweep: strips where every one has a CU to itself, whatever the heads' reach: blocks /
     // strips, us, eps 1e-9, a third of the heads far, then none: B1 H8 T1000 d64 17.4 / 8.3, 6.5 / 5.2; B1 H2 T4000 d64 6.6 / 5.2 (none); B2 H3 T1300 d128 29 / 16,
     // 8.8 / 5.3; B1 H3 T2700 d32 35 / 14.5, 5.4 / 4.7; with more, near heads lose: B1 H4 T4000 d64 57 / 23.5, 6.6 / 9.0; B1 H10 T3000 d32 39 / 23, 5.6 / 14.3.
-    const bool fits = small_fwd_grid(strips, T, D) && (enough == CARRY_EXHAUSTED || strips <= 256);
-    if (!TRI && (WRITE_M || !tile_counts) && fits) {
-        const int heads = VL ? H : BH, n = VL ? BH / H : (T + 31) / 32;
-        hipLaunchKernelGGL((fwd_small_kernel<D>), dim3((unsigned)strips), dim3(FwdSmallCfg<D>::NTHR), 0, stream,
-                           q, k, v, rb, o, m, T, heads, H, G, n, enough, tile_counts, cu, Ttot);
-        return hipGetLastError();
+    const bool fits = !TRI && small_fwd_grid(strips, T, D) && (enough == CARRY_EXHAUSTED || strips <= 256);
+    // What tile_counts counts (without m) are the blocks' tiles.  Where strips are taken the blocks sweep for the counts alone: how far o's sweep goes
+    // does not depend on whether anyone counts.
+    if (!fits || (!WRITE_M && tile_counts)) {
+        const int nqb = (T + BQ - 1) / BQ;
+        const long grid = block_grid(BH / H, H, T, BQ, PK, Ttot);
+        if (grid > 0x7fffffffL) return hipErrorInvalidValue;
+        const hipError_t e = launch_workgroups(grid, 64 * NW, [&](unsigned n, int first_wg) {
+            hipLaunchKernelGGL((fwd_bf16_kernel<D, WRITE_M, RB, PK, TRI>), dim3(n), dim3(64 * NW), 0, stream,
+                               q, k, v, rb, o, m, T, VL ? BH / H : BH, H, G, nqb, enough, tile_counts, cu, Ttot, VL || G > 1 ? -1 : query_run(BH, nqb, D), first_wg);
+        });
+        if (!fits || e != hipSuccess) return e;
     }
-    const int nqb = (T + BQ - 1) / BQ;
-    const long grid = block_grid(BH / H, H, T, BQ, PK, Ttot);
-    if (grid > 0x7fffffffL) return hipErrorInvalidValue;
-    return launch_workgroups(grid, 64 * NW, [&](unsigned n, int first_wg) {
-        hipLaunchKernelGGL((fwd_bf16_kernel<D, WRITE_M, RB, PK, TRI>), dim3(n), dim3(64 * NW), 0, stream,
-                           q, k, v, rb, o, m, T, VL ? BH / H : BH, H, G, nqb, enough, tile_counts, cu, Ttot, VL || G > 1 ? -1 : query_run(BH, nqb, D), first_wg);
-    });
+    const int heads = VL ? H : BH, n = VL ? BH / H : (T + 31) / 32;
+    hipLaunchKernelGGL((fwd_small_kernel<D>), dim3((unsigned)strips), dim3(FwdSmallCfg<D>::NTHR), 0, stream,
+                       q, k, v, rb, o, m, T, heads, H, G, n, enough, WRITE_M ? tile_counts : nullptr, cu, Ttot);
+    return hipGetLastError();
 }
 
 }  // namespace

@@ -226,12 +226,16 @@ def test_packed_places(sb, oracle, gen, lens, H, Hkv, max_T, d):
 @pytest.mark.parametrize("shift", [-3.0, -6.0])
 def test_halting_strips(sb, gen, B, H, T, d, shift):
     """A halting sweep of a small grid, against the whole one: off by at most eps max|v| and a rounding of each to bfloat16, whatever is
-    skipped; and what nothing may be skipped of is the same to the bit, counted (by blocks) or not."""
+    skipped; the same to the bit where tiles are counted (by blocks), and as the whole one where nothing may be skipped."""
     q, k, v = dev(*gen.biased_gaussian(B, H, T, d, seed=T, shift=shift, dtype="bf16"))
     whole = sb.sb_attn_fwd(q, k, v)
     for eps in (1e-2, 1e-6):
         o = sb.sb_attn_fwd_halt(q, k, v, eps)
         assert (o.float() - whole.float()).abs().max() <= eps * v.float().abs().max() + 2.0 ** -8 * whole.float().abs().max(), eps
+        counts = torch.zeros(2, dtype=torch.int64, device="cuda")
+        assert torch.equal(o, sb.sb_attn_fwd_halt(q, k, v, eps, tile_counts=counts))
+        swept, all_of_them = counts.tolist()
+        assert 0 < swept <= all_of_them == B * H * sum((min(T, 128 * i + 128) + 62) // 64 for i in range((T + 127) // 128))
     k[..., -1] = -200.0 * d ** 0.5                            # logits of -200 and below: no stick is used up
     q[..., -1] = 1.0
     k[..., :-1] = 0.0
