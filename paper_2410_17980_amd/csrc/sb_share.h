@@ -252,13 +252,21 @@ constexpr long small_kv_grid(int nkb) { return std::clamp(64L + 16L * nkb, 256L,
 //            B1 H9 T4096 (1152) 75 / 59 (two a CU), 124 / 125, 176 / 163
 //   d = 64   B1 H21 T993 51 / 45, 55 / 52, 64 / 57;  B1 H14 T2500 (1106) 83 / 69, 122 / 108, 156 / 142
 // and not    d = 32 B1 H10 T2100 (660) 43 / 34, 56 / 63, 71 / 67;  B1 H8 T2000 (504) all 51 / 58;  d = 64 B1 H12 T900 (348) all 35 / 41
+// From 768 to 1024 strips, where there was one block kernel before there were strips so long, which near heads alone are faster in, the backward
+// with blocks / eight / four waves:
+//   d = 32   B1 H14 T2048 (896) 25 / 37 / 25, 88 / 46 / 43, 89 / 63 / 49;  B1 H10 T2500 (790) 24 / 34 / 20, 107 / 46 / 50, 108 / 64 / 55;  B1 H10 T2800 (880)
+//            25 / 37 / 24, 119 / 53 / 54, 119 / 75 / 63
+//   d = 64   B1 H14 T2048 32 / 48 / 35, 107 / 58 / 56, 108 / 84 / 78;  B1 H10 T2500 31 / 45 / 34, 130 / 59 / 64, 130 / 85 / 81;  B1 H12 T2600 (984) 32 / 49 / 38,
+//            134 / 68 / 68, 135 / 108 / 99
+// and not    d = 32 B1 H9 T2900 (819) 24 / 35 / 23, 122 / 46 / 56, 123 / 72 / 63;  d = 64 32 / 46 / 36, 148 / 58 / 73, 148 / 95 / 91:  the more of a strip's subtiles to
+// a wave of eight, the more a lone far head's longest chain counts
 // The key-stationary pass of grouped heads, whose chains are G times as long: B2 H36 Hkv12 T1750 d64 (1320) 120 / 116, 180 / 175;  B8 H16 Hkv4 T1500 d32
 // (1504) 113 / 108 (two a CU), 184 / 171, d64 all 333 / 310;  not B1 H33 Hkv11 T3870 d32 (1331) 114 / 108, 278 / 307;  B1 H24 Hkv12 T3000 d64 (1128) 96 / 89, 185 / 194;  B4 H32
 // Hkv4 T800 d32 (800) all 82 / 104
 inline bool four_waves(long strips, int G, int mean, int d)
 {
     if (d == 128) return false;
-    return strips > (G > 1 ? std::max(1280, 5 * (mean / 8)) : mean > 1024 ? 1024 : 640);
+    return strips > (G > 1 ? std::max(1280, 5 * (mean / 8)) : mean > 1024 ? std::clamp(3 * (mean / 10), 768, 1024) : 640);
 }
 
 // The kernels of the backward's passes.

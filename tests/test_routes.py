@@ -140,6 +140,14 @@ def test_shapes_of_four_waves(ask):
     assert ask([(1, 12, 12, 3200, 64, 3, 0)]) == [(1, 1)]               # test_sharp_and_far_rows_in_one_strip
 
 
+def test_waves_of_strips(ask):
+    """Four waves in place of eight where they are faster whatever the heads' reach, or nearly so: not where a lone far head's chain is long."""
+    for d in (32, 64):
+        for H, T, four in ((14, 2048, 1), (13, 1990, 1), (10, 2500, 1), (10, 2800, 1), (10, 3300, 1), (12, 2600, 1), (9, 4096, 1), (12, 4096, 1),
+                           (8, 2000, 0), (12, 2048, 0), (9, 2900, 0), (8, 3100, 0), (9, 3400, 0), (8, 4096, 0)):
+            assert ask([(1, H, H, T, d, 3, 0)]) == [(four, four)], (H, T, d)
+
+
 def test_shapes_of_the_tests_of_carries(ask):
     """test_gpu_small_grids.py: strips in both passes."""
     import test_gpu_small_grids as t
