@@ -631,27 +631,26 @@ fwd_bf16_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
 // fwd_bf16_kernel: o is the same, bit for bit (m too, unless the rows are exhausted on the way).  Which grids: small_fwd_grid().
 // Against O += A V by the first of the waves between two rounds, and Q read by all of them, all heads far, then none, us: B2 H4 T777 d32
 // 8.4 -> 7.3, 6.0 -> 5.2; B1 H4 T4000 d64 36 -> 30, 18.7 -> 16.1; B1 H8 T700 d128 13.0 -> 10.9, 10.1 -> 8.3; B1 H16 T100 d64 5.0 -> 4.5.
-template <int D> struct FwdSmallCfg {
-    static constexpr int NWS = D == 128 ? 4 : 8;        // waves that take subtiles
+template <int D, int NWS> struct FwdSmallCfg {          // NWS: waves that take subtiles
     static constexpr int NWO = D / 32;                  // and waves that take O += A V
     static constexpr int NTHR = 64 * (NWS + NWO);
     static constexpr int ROW = D * 2;
     static constexpr int SUB = 32 * ROW;                // one 32-row subtile of K (or V)
     static constexpr int LOADS = SUB / 1024;            // of 16 bytes a lane, for a subtile
+    static constexpr int Q_OFF = 3 * SUB;               // Q passes through a buffer of V that the second round is the first to fill
     static constexpr int W_OFF = NWS * 4 * SUB;         // after the waves' K and V, double buffered: weights
     static constexpr int W_SUB = 2 * 1024;              // of a subtile: two operands of 16 bytes a lane
 };
 
-template <int D>
-__global__ void __launch_bounds__(FwdSmallCfg<D>::NTHR)
+template <int D, int NWS>
+__global__ void __launch_bounds__((FwdSmallCfg<D, NWS>::NTHR))
 fwd_small_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
                  const uint16_t* __restrict__ v, const uint16_t* __restrict__ rb,
                  uint16_t* __restrict__ o, float* __restrict__ m,
                  int T_arg, int BH, int H, int G, int n_arg, float enough,       // n_arg: strips a head; packed batch: sequences
                  unsigned long long* __restrict__ clocks, const int* __restrict__ cu, int Ttot)
 {
-    using C = FwdSmallCfg<D>;
-    constexpr int NWS = C::NWS;
+    using C = FwdSmallCfg<D, NWS>;
     __shared__ __attribute__((aligned(1024))) char smem[C::W_OFF + NWS * C::W_SUB];
     __shared__ float s_tot[2][NWS][32];                 // per round parity: softplus totals of its subtiles (base 2), per row
 
@@ -703,13 +702,12 @@ fwd_small_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
             dma16_to_lds_run_at(xb, o, dst);
         }
     };
-    // Q passes through the place of the weights: whole rows and once, every wave its share.  (As operands from
+    // Q by whole rows and once, every wave its share.  (As operands from
     // memory, 32 bytes of 32 rows an instruction, all of it by every wave: 1700, 2200 and 4500 clocks at d = 32, 64 and 128.)
-    static_assert(C::SUB <= NWS * C::W_SUB, "the rows fit");
     for (int i = wave; i < C::LOADS; i += C::NTHR / 64) {
         const int row = i * (1024 / C::ROW) + lane / CPR;
         dma16_to_lds_at(scalar_base(q + (row0 + q0) * D), min(row, nlast - 1) * C::ROW + (((lane % CPR) ^ swz_perm<D>(row)) << 4),
-                        smem0 + C::W_OFF + i * 1024);
+                        smem0 + C::Q_OFF + i * 1024);
     }
     if (!sums && strip - wave >= 0) {
         stage(Kg, strip - wave, mine);
@@ -780,7 +778,7 @@ fwd_small_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     } else {
         bf16x8 qf[D / 16];
         {
-            const uint32_t at = smem0 + C::W_OFF + tile_off_perm<D>(n, hh);
+            const uint32_t at = smem0 + C::Q_OFF + tile_off_perm<D>(n, hh);
 #pragma unroll
             for (int s = 0; s < D / 16; ++s) qf[s] = __builtin_bit_cast(bf16x8, lds_load16(at ^ (s << 5)));
         }
@@ -923,8 +921,18 @@ hipError_t launch_one(const uint16_t* q, const uint16_t* k, const uint16_t* v, c
         if (!fits || e != hipSuccess) return e;
     }
     const int heads = VL ? H : BH, n = VL ? BH / H : (T + 31) / 32;
-    hipLaunchKernelGGL((fwd_small_kernel<D>), dim3((unsigned)strips), dim3(FwdSmallCfg<D>::NTHR), 0, stream,
-                       q, k, v, rb, o, m, T, heads, H, G, n, enough, WRITE_M ? tile_counts : nullptr, cu, Ttot);
+    auto go = [&](auto waves) {
+        constexpr int NWS = decltype(waves)::value;
+        hipLaunchKernelGGL((fwd_small_kernel<D, NWS>), dim3((unsigned)strips), dim3(FwdSmallCfg<D, NWS>::NTHR), 0, stream,
+                           q, k, v, rb, o, m, T, heads, H, G, n, enough, WRITE_M ? tile_counts : nullptr, cu, Ttot);
+    };
+    if constexpr (D == 32) {
+        if (four_fwd_waves(strips, T)) {
+            go(ic<4>());
+            return hipGetLastError();
+        }
+    }
+    go(ic<D == 128 ? 4 : 8>());
     return hipGetLastError();
 }
 

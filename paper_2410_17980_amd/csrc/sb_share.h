@@ -192,6 +192,16 @@ inline bool small_fwd_grid(long strips, int T, int d)
     return strips <= std::max(least, d == 128 ? std::min(2L * T / 5, 704L) : std::min(3L * T / 8, 1000L));
 }
 
+// Its strips at d = 32 whose workgroups have four waves for the subtiles in place of eight, three of them to a CU in place of one: as four_waves().
+// Blocks / eight / four waves, us, without m, none far, then a third, then all:
+//            B1 H10 T2500 (790 strips) 7.1 / 13.1 / 7.9, 33 / 18.2 / 19.0, 33 / 26 / 20;  H10 T3000 (940) 7.0 / 14.3 / 10.5, 39 / 23.3 / 22.3, 39 / 34 / 27
+// and not    H9 T2753 (783) none 13.0 / 7.6 of the strips, a third 17.4 / 20.5, all 27 / 21;  H7 T3000 (658) 6.9 / 10.5 / 7.3, 39 / 15.7 / 22.2, 39 / 26 / 22;  H7 T4096 (896) 7.0 / 14.3 / 10.2, 52 / 22 / 29, 52 / 40 / 33;  H5 T6000 (940) 7.1 / 14.6 /
+//            10.5, 74 / 28 / 41, 75 / 57 / 47;  H1 T16384 (512) all 196 / 77 / 107
+// At d = 64, two workgroups to a CU, and d = 128 (of two waves in place of four) far heads lose as much as near ones gain, or more: H10 T3000 d64 9.0 / 18.4 / 15.3,
+// 45 / 27.9 / 29.2, 45 / 41 / 49;  H10 T2048 d128 12.8 / 17.5 / 16.0, 45 / 25 / 36, 45 / 38 / 53.  Nor does the backward gain by two waves at d = 128: B1 H8 T2000 37 /
+// 45 / 34, 117 / 72 / 119, 118 / 88 / 122.
+inline bool four_fwd_waves(long strips, int T) { return strips > std::max(768, 3 * (T / 10)); }
+
 // Grids of the key-stationary pass at d <= 64 whose blocks are taken by two groups of four waves (bwd_dkv_kernel<.., 2>): where a
 // block has a CU to itself anyway (one wave per SIMD issues an instruction every five clocks at best, two keep it busy), and
 // for some more blocks, of which few are left once some heads turn out near: what counts then is the longest block's chain.

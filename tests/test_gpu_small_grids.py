@@ -177,6 +177,25 @@ def test_forward_strips(sb, oracle, gen, T, d):
         check_m(to64(m), rem)
 
 
+@pytest.mark.parametrize("H,T", [(10, 2500), (10, 2753), (11, 2273), (10, 3008)])
+def test_forward_strips_of_four_waves(sb, oracle, gen, H, T):
+    """d = 32, enough strips for the workgroups of four waves (two batch entries: 128-row blocks, which give the same o): rows that end within a subtile, heads
+    that are exhausted within a round and heads that never are."""
+    d = 32
+    q, k, v = mixed(gen, 1, H, T, d, seed=500 + T)
+    r = gen.remainder_embedding(H, d, seed=10)
+    qd, kd, vd, rd = dev(q, k, v, r)
+    o, m = sb.sb_attn_fwd_gqa(qd, kd, vd, r=rd)
+    o2 = sb.sb_attn_fwd(qd, kd, vd)
+    om, mm = sb.sb_attn_fwd_gqa(*(torch.cat([t] * 2) for t in (qd, kd, vd)), r=rd)
+    assert torch.equal(o, om[:1]) and torch.allclose(m, mm[:1], rtol=1e-5, atol=1e-4)
+    assert torch.equal(o2, sb.sb_attn_fwd(*(torch.cat([t] * 2) for t in (qd, kd, vd)))[:1])
+    h = slice(0, 3)
+    ref, rem = oracle.fwd(*(to64(t[:, h]) for t in (q, k, v)), r=to64(r[h]))
+    assert np.all(np.abs(to64(o[:, h]) - ref) <= fwd_bound(ref, to64(v[:, h])))
+    check_m(to64(m[:, h]), rem)
+
+
 @pytest.mark.parametrize("d", [32, 64, 128])
 def test_forward_packed(sb, gen, d):
     """Sequences of all kinds of lengths in one small grid: each as it is alone."""

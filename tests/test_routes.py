@@ -37,6 +37,11 @@ int main()
             printf("%d\n", bias_chunks(B, T, true, Ttot));
             continue;
         }
+        if (packed == 5) {                              // forward: waves that take a strip's subtiles
+            const long n = pieces(B, H, T, 32, false, 0);
+            printf("%d\n", !small_fwd_grid(n, T, d) ? 0 : d == 128 || (d == 32 && four_fwd_waves(n, T)) ? 4 : 8);
+            continue;
+        }
         printf("%d %d %ld %d\n", small_fwd_grid(strips, T, d), query_strips(B, H, T, d, packed, Ttot), strips,
                (int)keys_of(B, H, Hkv, T, d, packed, Ttot));
     }
@@ -138,6 +143,9 @@ def test_shapes_of_four_waves(ask):
         assert ask([(1, H, Hkv, T, d, 3, 0) for H, Hkv, T in ((21, 21, 993), (15, 15, 2200), (11, 11, 3105), (72, 24, 1750))]) == \
             [(1, 1)] * 3 + [(0, 1)], d
     assert ask([(1, 12, 12, 3200, 64, 3, 0)]) == [(1, 1)]               # test_sharp_and_far_rows_in_one_strip
+    import test_gpu_small_grids as t
+    for H, T in t.test_forward_strips_of_four_waves.pytestmark[0].args[1]:
+        assert ask([(1, H, H, T, 32, 5, 0), (2, H, H, T, 32, 5, 0)]) == [(4,), (0,)], (H, T)
 
 
 def test_waves_of_strips(ask):
@@ -146,6 +154,9 @@ def test_waves_of_strips(ask):
         for H, T, four in ((14, 2048, 1), (13, 1990, 1), (10, 2500, 1), (10, 2800, 1), (10, 3300, 1), (12, 2600, 1), (9, 4096, 1), (12, 4096, 1),
                            (8, 2000, 0), (12, 2048, 0), (9, 2900, 0), (8, 3100, 0), (9, 3400, 0), (8, 4096, 0)):
             assert ask([(1, H, H, T, d, 3, 0)]) == [(four, four)], (H, T, d)
+    for H, T, waves in ((10, 2500, 4), (10, 3000, 4), (8, 3100, 8), (9, 2753, 8), (7, 3000, 8), (7, 4096, 8), (5, 6000, 8), (4, 7900, 8), (1, 16384, 8), (13, 1990, 0)):
+        assert ask([(1, H, H, T, 32, 5, 0)]) == [(waves,)], (H, T)
+    assert ask([(1, 10, 10, 3000, 64, 5, 0), (1, 10, 10, 2048, 128, 5, 0)]) == [(8,), (4,)]
 
 
 def test_shapes_of_the_tests_of_carries(ask):
