@@ -50,18 +50,23 @@ inline bool take_pairs(long heads, int nblk)
 // whole other side to itself.  What bounds the blocks there is one chain, what bounds the strips from a round or two of the
 // chip on is their tiles, which no other wave shares: the longer the chain, the more strips are still worth it.
 // Blocks / strips, us, query-stationary, then key-stationary (the better of its block kernels), all heads far, then a third, then none:
-//   d = 32   B1 H16 T500 (256) 14 / 6, 14 / 7;  T1000 H24 (768) 25 / 18, 25 / 17, 13 / 16 and 24 / 18, 24 / 16, 12 / 13;  T2048 H14 (896) 46 / 32,
-//            45 / 25, 12 / 20 and 44 / 31, 44 / 22, 12 / 17;  T4096 H12 (1536) 89 / 83, 88 / 51, 16 / 31 and 84 / 81, 84 / 45, 17 / 27
-//   d = 64   T500 H32 (512) 17 / 11, 17 / 12, 14 / 13 and 18 / 13, 18 / 13, 15 / 12;  T1000 H24 (768) 30 / 22, 29 / 21, 15 / 20 and 30 / 26, 30 / 22,
-//            16 / 20;  T3000 H16 (1504) 77 / 80, 77 / 53, 20 / 37 and 77 / 85, 75 / 50, 22 / 37;  T8192 H1 (256) 200 / 56 and 189 / 52
+//   d = 32   B1 H16 T500 (256) 14 / 6, 14 / 7;  T2048 H14 (896) 46 / 32, 45 / 25, 12 / 20 and 44 / 31, 44 / 22, 12 / 17 (eight waves; four_waves());  T4096 H12 (1536)
+//            89 / 83, 88 / 51, 16 / 31 and 84 / 81, 84 / 45, 17 / 27
+//   d = 64   T8192 H1 (256) 200 / 56 and 189 / 52
 //   d = 128  T500 H16 (256) 22 / 13, 22 / 13, 18 / 11 and 19 / 14, 19 / 14, 15 / 11;  T2000 H8 (504) 70 / 43, 69 / 37, 19 / 23 and 50 / 43, 48 / 34,
-//            18 / 23;  T3000 H8 (752) 101 / 91, 100 / 61, 20 / 33 and 73 / 85, 67 / 57, 22 / 33;  T8192 H1 (256) 263 / 130 and 162 / 108
+//            18 / 23;  T8192 H1 (256) 263 / 130 and 162 / 108
 // and not    d = 32 T500 H48 (768) 14.5 / 13.5, 14 / 15, 13 / 15 and 14 / 14.5, 14 / 14, 12 / 13;  T4096 H16 (2048) 89 / 109, 89 / 67, 17 / 40 and 92 / 105,
 //            84 / 60, 18 / 36;  d = 64 T1000 H32 (1024) 30 / 31, 30 / 27, 15 / 26 and 31 / 35, 31 / 27, 17 / 25;  d = 128 T500 H32 (512) 23 / 20, 22 / 22,
 //            19 / 22 and 21 / 24, 21 / 22, 18 / 22;  T1000 H24 (768) 39 / 42, 39 / 38, 20 / 33 and 35 / 46, 31 / 37, 22 / 32;  T3000 H10 (940) 101 / 106,
 //            100 / 71, 21 / 42 and 82 / 102, 68 / 64, 23 / 41
-// The limits lie where neither far heads nor near ones lose more by it than a mix gains.  One line serves both passes and, below d = 128, both
-// head sizes: T320 H26 d32 (260), just beyond it, would gain too, 9.4 / 7.7 and 10 / 8.  What is due to long chains goes by the mean length of
+// and, just beyond the line, not  d = 64 T3000 H16 (1504) 77 / 80, 77 / 53, 20 / 37 and 77 / 85, 75 / 50, 22 / 37;  d = 128 T3000 H8 (752) 101 / 91, 100 / 61, 20 / 33
+//            and 73 / 85, 67 / 57, 22 / 33;  nor what would gain by it:  d = 32 T1000 H24 (768) 25 / 18, 25 / 17, 13 / 16 and 24 / 18, 24 / 16, 12 / 13;  T320 H26 (260)
+//            9.4 / 7.7 and 10 / 8;  d = 64 T500 H32 (512) 17 / 11, 17 / 12, 14 / 13 and 18 / 13, 18 / 13, 15 / 12;  T1000 H24 30 / 22, 29 / 21, 15 / 20 and 30 / 26,
+//            30 / 22, 16 / 20
+// The limits are where a mix gains more by strips than near heads, and beyond them far ones, lose.  From 256 strips on at d = 128 and from 768 on below,
+// near heads alone do lose: whole backward, blocks / strips, none far, then a third, B1 H8 T2000 d128 37 / 45, 117 / 72;  H5 T4096 44 / 61, 218 / 131;  H2 T8192 37 / 46;
+// H14 T2500 d64 40 / 45, 131 / 69;  H12 T2600 d64 32 / 38, 134 / 68;  H12 T4096 d32 35 / 31, 169 / 77.
+// One line serves both passes and, below d = 128, both head sizes.  What is due to long chains goes by the mean length of
 // a packed batch's sequences: one long one among many short ones leaves the rest of the strips short.  Beyond 8192 rows not measured.
 constexpr int SMALL_T = 4096, LONG_T = 8192;
 inline bool small_grid(long strips, int T, int mean, int d)
@@ -176,14 +181,16 @@ __device__ __forceinline__ Place place_of(int place, const int* __restrict__ cu,
 // Grids of the forward that take one strip of 32 rows a workgroup, its waves taking the strip's subtiles in rounds
 // (fwd_small_kernel), in place of 128-row blocks whose every wave has its rows' chain to itself.  Blocks / strips, us, without m (with it,
 // where it matters, in brackets), all heads far, then a third, then none:
-//   d = 32   B1 H32 T500 (512 strips) 9.2 / 8.2, 8.9 / 8.1, 7.1 / 7.5 (9.0 / 7.7);  T3000 H10 (940) 39 / 34, 38 / 23, 7 / 14 (22 / 20);  T8192 H1 100 / 37
-//   d = 64   H64 T100 (256) 5.7 / 5.0;  H24 T500 (384) 10.6 / 8.5, 10.5 / 8.0, 8.2 / 8.0;  T2000 H12 (756) 32 / 26, 31 / 19, 9 / 14 (20 / 17.5);
-//            T3000 H10 (940) 45 / 41, 44 / 28, 9 / 18 (26 / 25);  T8192 H1 114 / 44;  T16384 H1 225 / 100
-//   d = 128  H37 T200 (259) 8.4 / 6.9;  H24 T500 (384) 14.6 / 11.1, 14.5 / 10.5, 11.3 / 10.5;  T1000 H12 (384) 24.5 / 15.3, 24 / 15, 11.4 / 11.9;
-//            T2048 H10 (640) 45 / 38, 44 / 26, 13 / 18 (26 / 26);  T8192 H1 161 / 82;  T16384 H1 319 / 180
+//   d = 32   T3000 H10 (940) 39 / 34, 38 / 23, 7 / 14 (22 / 20) (eight waves; four_fwd_waves());  T8192 H1 100 / 37
+//   d = 64   H64 T100 (256) 5.7 / 5.0;  H24 T500 (384) 10.6 / 8.5, 10.5 / 8.0, 8.2 / 8.0;  T3000 H10 (940) 45 / 41, 44 / 28, 9 / 18 (26 / 25);  T8192 H1
+//            114 / 44;  T16384 H1 225 / 92, none 8.5 / 9.7
+//   d = 128  H24 T500 (384) 14.6 / 11.1, 14.5 / 10.5, 11.3 / 10.5;  T1000 H12 (384) 24.5 / 15.3, 24 / 15, 11.4 / 11.9;
+//            T2048 H10 (640) 45 / 38, 44 / 26, 13 / 18 (26 / 26);  T8192 H1 161 / 82;  T16384 H1 318 / 175, none 12 / 16
 // and not, d = 32 H37 T200 (259) 5.7 / 6.4;  T2048 H18 (1152) 28 / 32, 27 / 23, 8 / 17 (17 / 22);  d = 64 H96 T100 (384) 5.8 / 7.1;  T500 H48 (768) 11.1 / 14.8,
 //            10.8 / 13.9, 8.6 / 13.4;  T2000 H16 (1008) 32 / 33, 32 / 24, 9 / 18 (20 / 22.5);  T4096 H12 (1536) 62 / 78, 60 / 45, 12 / 25 (34 / 44);
 //            d = 128 T500 H48 (768) 16 / 21, 16 / 19, 13 / 19;  T1000 H24 (768) 25 / 30, 25 / 23, 13 / 19;  T4096 H9 (1152) 87 / 109, 86 / 55, 18 / 29 (44 / 63)
+// nor, just beyond the line, what would gain by it:  d = 32 H32 T500 (512) 9.2 / 8.2, 8.9 / 8.1, 7.1 / 7.5 (9.0 / 7.7);  d = 64 T2000 H12 (756) 32 / 26, 31 / 19, 9 / 14
+//            (20 / 17.5);  d = 128 H37 T200 (259) 8.4 / 6.9
 // At d = 32 a chain of 10 subtiles is not worth the rounds' barriers.
 inline bool small_fwd_grid(long strips, int T, int d)
 {
@@ -306,7 +313,7 @@ inline Keys keys_of(int B, int H, int Hkv, int T, int d, bool packed, int Ttot)
 // there are enough runs to even the XCDs out: 32 of them, or 16 where 64 heads and more can be turned
 // among each other as well, by o(o+1)/2 inside each octet o of heads (over octets 8x to 8x + 7 these are all 8
 // turns, so that heads which are costly in every batch entry do not meet on one XCD).  Query heads that
-// share a kv head, for which runs were not measured, and packed batches, where a run is cut short by the
+// share a kv head, where runs win 10 to 30 % or lose as much by which heads are far, and packed batches, where a run is cut short by the
 // sequences' ends, turn with every block.
 // Every block / runs, us, all heads far, then a third, then none: forward B8 H16 T4096 d128 698 / 669,
 // 331 / 329, 160 / 150; B1 H32 T16384 d128 2422 / 2266, 883 / 880, 165 / 154; B1 H24 T16384 d64 1078 / 1032,

@@ -148,6 +148,23 @@ def test_shapes_of_four_waves(ask):
         assert ask([(1, H, H, T, 32, 5, 0), (2, H, H, T, 32, 5, 0)]) == [(4,), (0,)], (H, T)
 
 
+def test_limits_of_strips(ask):
+    """The shapes that the limits were measured at, on the sides where the comments beside them list them."""
+    backward = {True: [(16, 500, 32), (14, 2048, 32), (12, 4096, 32), (1, 8192, 64), (14, 2500, 64), (12, 2600, 64), (16, 500, 128), (8, 2000, 128), (5, 4096, 128),
+                       (2, 8192, 128), (1, 8192, 128)],
+                False: [(48, 500, 32), (16, 4096, 32), (32, 1000, 64), (32, 500, 128), (24, 1000, 128), (10, 3000, 128), (16, 3000, 64), (8, 3000, 128),
+                        (24, 1000, 32), (26, 320, 32), (32, 500, 64), (24, 1000, 64)]}
+    forward = {True: [(10, 3000, 32), (1, 8192, 32), (64, 100, 64), (24, 500, 64), (10, 3000, 64), (1, 8192, 64), (1, 16384, 64), (24, 500, 128), (12, 1000, 128),
+                      (10, 2048, 128), (1, 8192, 128), (1, 16384, 128)],
+               False: [(37, 200, 32), (18, 2048, 32), (96, 100, 64), (48, 500, 64), (16, 2000, 64), (12, 4096, 64), (48, 500, 128), (24, 1000, 128), (9, 4096, 128),
+                       (32, 500, 32), (12, 2000, 64), (37, 200, 128)]}
+    for side in (True, False):
+        for H, T, d in backward[side]:
+            assert strips(ask, (1, H, H, T, d, 0, 0))[1:] == (side, side), (H, T, d)
+        for H, T, d in forward[side]:
+            assert strips(ask, (1, H, H, T, d, 0, 0))[0] == side, (H, T, d)
+
+
 def test_waves_of_strips(ask):
     """Four waves in place of eight where they are faster whatever the heads' reach, or nearly so: not where a lone far head's chain is long."""
     for d in (32, 64):
