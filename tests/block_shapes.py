@@ -49,7 +49,15 @@ PACKED = [(5, 8, 8, 1300, 64, LENS, "blocks", "two groups"), (5, 24, 24, 1300, 6
           (5, 38, 38, 1887, 64, LONG_AND_SHORT, "blocks", "one group"), (5, 13, 13, 1887, 32, LONG_AND_SHORT, "blocks", "two groups"),
           (5, 5, 5, 1887, 128, LONG_AND_SHORT, "blocks", "64 keys")]
 
-ALL = [s[:2] + (s[2] or s[1],) + s[3:] for s in LOOPS + LONG + GROUPED + PACKED]
+# packed sequences of much the same length, each of which gets as many workgroups as the longest may need; those above look
+# their blocks up by length
+ALIKE_LENS = [900, 1100, 1000, 1041]
+ALIKE = [(4, H, Hkv, 1100, d, ALIKE_LENS, "blocks", keys) for H, Hkv, d, keys in
+         ((8, 8, 64, "two groups"), (16, 16, 64, "one group"), (12, 6, 64, "two groups"), (48, 24, 64, "one group"), (16, 4, 64, "strips"),
+          (8, 8, 32, "two groups"), (16, 16, 32, "one group"), (12, 6, 32, "two groups"),
+          (5, 5, 128, "64 keys"), (12, 6, 128, "64 keys"), (8, 8, 128, "128 keys"), (16, 8, 128, "128 keys"), (16, 4, 128, "strips"))]
+
+ALL = [s[:2] + (s[2] or s[1],) + s[3:] for s in LOOPS + LONG + GROUPED + PACKED + ALIKE]
 
 
 def name(s):

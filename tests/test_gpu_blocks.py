@@ -94,7 +94,7 @@ def test_starts_and_groups(sb, oracle, gen, shape, bias):
 
 
 @pytest.mark.parametrize("bias", [False, True])
-@pytest.mark.parametrize("shape", block_shapes.PACKED, ids=block_shapes.name)
+@pytest.mark.parametrize("shape", block_shapes.PACKED + block_shapes.ALIKE, ids=block_shapes.name)
 def test_packed(sb, oracle, gen, shape, bias):
     B, H, Hkv, max_T, d, lens = shape[:6]
     Ttot = sum(lens)

@@ -37,6 +37,10 @@ int main()
             printf("%d\n", bias_chunks(B, T, true, Ttot));
             continue;
         }
+        if (packed == 6) {                              // packed batch: its blocks are looked up by their length
+            printf("%d\n", packed_as(B, T, Ttot) == Packed::BY_LENGTH);
+            continue;
+        }
         if (packed == 5) {                              // forward: waves that take a strip's subtiles
             const long n = pieces(B, H, T, 32, false, 0);
             printf("%d\n", !small_fwd_grid(n, T, d) ? 0 : d == 128 || (d == 32 && four_fwd_waves(n, T)) ? 4 : 8);
@@ -191,6 +195,10 @@ def test_block_shapes(ask):
     rows = [packed(lens, H, d, T, Hkv) if lens else (B, H, Hkv, T, d, 0, 0) for B, H, Hkv, T, d, lens, _, _ in block_shapes.ALL]
     for shape, (_, dq, _, keys) in zip(block_shapes.ALL, ask(rows)):
         assert ("strips" if dq else "blocks", KEYS[keys]) == shape[6:], shape
+    by_length = lambda shapes: [x for x, in ask([(s[0], 1, 1, s[3], s[4], 6, sum(s[5])) for s in shapes])]
+    assert by_length(block_shapes.PACKED) == [1] * len(block_shapes.PACKED) and by_length(block_shapes.ALIKE) == [0] * len(block_shapes.ALIKE)
+    import test_gpu_varlen as varlen
+    assert all(x for x, in ask([(len(lens), 1, 1, max(lens), 64, 6, sum(lens)) for lens in varlen.BY_LENGTH.values()]))
     import test_gpu_blocks
     rest = [s[:5] + (0, 0) for s in test_gpu_blocks.random_shapes()] + \
            [(1, H, H, T, d, 0, 0) for H, T, d in ((19, 1300, 64), (48, 1300, 64), (19, 1300, 32), (7, 1300, 128), (28, 1300, 128),
