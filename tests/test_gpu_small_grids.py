@@ -61,8 +61,9 @@ def test_strips_of_four_waves(sb, oracle, gen, H, Hkv, T, d):
 
 @pytest.mark.parametrize("d", [32, 64, 128])
 def test_longest_strips(sb, oracle, gen, d):
-    """128 subtiles a row, the most the kernels' arrays hold; one more row takes the 128-row blocks."""
-    for T in (4096, 4097):
+    """128 subtiles a row, for which the kernels' arrays have room, and one more; the most rows that strips take, and one more, which takes the
+    128-row blocks."""
+    for T in (4096, 4097, 8192, 8193):
         q, k, v = mixed(gen, 1, 3, T, d, seed=T)
         g = gen.gaussian(1, 3, T, d, seed=T + 1, dtype="bf16")[0]
         h = slice(2, 3)                                    # the far one
@@ -154,6 +155,11 @@ def test_packed(sb, oracle, gen, d):
                 check_grad(f"{name} of {n}", to64(a[:, s]), r)
 
 
+def beyond_small_grids(T):
+    """How many times three heads of T rows are beyond the forward's largest small grid, 1000 strips."""
+    return 1000 // (3 * ((T + 31) // 32)) + 1
+
+
 @pytest.mark.parametrize("T", [65, 96, 97, 128, 129, 255, 257, 321, 500, 1000, 4096])
 @pytest.mark.parametrize("d", [32, 64, 128])
 def test_forward_strips(sb, oracle, gen, T, d):
@@ -163,7 +169,7 @@ def test_forward_strips(sb, oracle, gen, T, d):
     qd, kd, vd, rd = dev(q, k, v, r)
     o, m = sb.sb_attn_fwd_gqa(qd, kd, vd, r=rd)
     o2 = sb.sb_attn_fwd(qd, kd, vd)
-    times = 520 // (3 * ((T + 31) // 32)) + 1                 # beyond the largest of the small grids
+    times = beyond_small_grids(T)
     many = [torch.cat([t] * times) for t in (qd, kd, vd)]
     om, mm = sb.sb_attn_fwd_gqa(*many, r=rd)
     torch.cuda.synchronize()

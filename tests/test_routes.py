@@ -152,6 +152,19 @@ def test_shapes_of_four_waves(ask):
         assert ask([(1, H, H, T, 32, 5, 0), (2, H, H, T, 32, 5, 0)]) == [(4,), (0,)], (H, T)
 
 
+def test_shapes_of_the_longest_strips(ask):
+    """test_gpu_small_grids.py, test_longest_strips: strips up to 8192 rows."""
+    for d in (32, 64, 128):
+        for T in (4096, 4097, 8192):
+            assert strips(ask, (1, 1, 1, T, d, 0, 0)) == (True, True, True), (T, d)
+        assert strips(ask, (1, 1, 1, 8193, d, 0, 0))[1:] == (False, False), d
+    import test_gpu_small_grids as t
+    for T in (65, 96, 97, 128, 129, 255, 257, 321, 500, 1000, 4096):
+        for d in (32, 64, 128):
+            once, often = ask([(B, 3, 3, T, d, 5, 0) for B in (1, t.beyond_small_grids(T))])
+            assert (once > (0,) or (d == 32 and T <= 320)) and often == (0,), (T, d)
+
+
 def test_limits_of_strips(ask):
     """The shapes that the limits were measured at, on the sides where the comments beside them list them."""
     backward = {True: [(16, 500, 32), (14, 2048, 32), (12, 4096, 32), (1, 8192, 64), (14, 2500, 64), (12, 2600, 64), (16, 500, 128), (8, 2000, 128), (5, 4096, 128),
