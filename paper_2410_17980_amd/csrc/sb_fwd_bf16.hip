@@ -642,6 +642,28 @@ template <int D, int NWS> struct FwdSmallCfg {          // NWS: waves that take 
     static constexpr int W_SUB = 2 * 1024;              // of a subtile: two operands of 16 bytes a lane
 };
 
+// 32 columns of a strip of `rows` rows, to `out` (wave-uniform): oacc[r] is row 8*(r/4) + 4*hh + r%4, column n.  Two columns a store, as in fwd_bf16_kernel
+template <int D>
+__device__ __forceinline__ void store_strip_rows(uint16_t* out, const f32x16& oacc, int rows, int n, int hh)
+{
+    const uint32_t pick = (n & 1) ? 0x03020706u : 0x05040100u;
+    const int at = (4 * hh + (n & 1)) * D + (n & ~1);
+    auto store = [&](auto whole) __attribute__((always_inline)) {
+#pragma unroll
+        for (int r = 0; r < 16; r += 2) {
+            typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
+            const bf16x2 two = {(__bf16)oacc[r], (__bf16)oacc[r + 1]};
+            const uint32_t x = __builtin_bit_cast(uint32_t, two);
+            const uint32_t y = __builtin_amdgcn_mov_dpp(x, 0xB1, 0xF, 0xF, true);      // of lane n ^ 1
+            const int row = 8 * (r >> 2) + (r & 3);
+            if (decltype(whole)::value || row + 4 * hh + (n & 1) < rows)
+                *reinterpret_cast<uint32_t*>(out + row * D + at) = __builtin_amdgcn_perm(y, x, pick);
+        }
+    };
+    if (rows == 32) store(bc<true>{});
+    else store(bc<false>{});
+}
+
 template <int D, int NWS>
 __global__ void __launch_bounds__((FwdSmallCfg<D, NWS>::NTHR))
 fwd_small_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
@@ -870,30 +892,238 @@ fwd_small_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
 #pragma unroll
             for (int r = 0; r < 16; ++r) oacc[r] += __shfl(rem, 8 * (r >> 2) + 4 * hh + (r & 3)) * rc;
         }
-        uint16_t* const Og = reinterpret_cast<uint16_t*>(scalar_base(o + (row0 + q0) * D + 32 * cols));
-        // two columns a store, as in fwd_bf16_kernel
-        const uint32_t pick = (n & 1) ? 0x03020706u : 0x05040100u;
-        const int at = (4 * hh + (n & 1)) * D + (n & ~1);
-        auto store = [&](auto whole) __attribute__((always_inline)) {
-#pragma unroll
-            for (int r = 0; r < 16; r += 2) {
-                typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
-                const bf16x2 two = {(__bf16)oacc[r], (__bf16)oacc[r + 1]};
-                const uint32_t x = __builtin_bit_cast(uint32_t, two);
-                const uint32_t y = __builtin_amdgcn_mov_dpp(x, 0xB1, 0xF, 0xF, true);      // of lane n ^ 1
-                const int row = 8 * (r >> 2) + (r & 3);
-                if (decltype(whole)::value || row + 4 * hh + (n & 1) < nlast)
-                    *reinterpret_cast<uint32_t*>(Og + row * D + at) = __builtin_amdgcn_perm(y, x, pick);
-            }
-        };
-        if (nlast == 32) store(bc<true>{});
-        else store(bc<false>{});
+        store_strip_rows<D>(reinterpret_cast<uint16_t*>(scalar_base(o + (row0 + q0) * D + 32 * cols)), oacc, nlast, n, hh);
     }
     if (m && tid < 32 && n < nlast) m[row0 + q0 + n] = -a * SB_LN2;
     if (clock) {
         clocks[2] = (unsigned long long)clock64();
         clocks[3] = (unsigned long long)wall_clock64();
     }
+}
+
+// Two adjacent strips a workgroup, without m: both sweep the same subtiles, from the diagonal of the second one on, NWS to a round, each with waves
+// of its own for the logits, chains and weights and for O += A V, as above: sixteen waves in all, the most there can be.  The first strip's waves stage K,
+// the second's V; what one stages others read, so that K too lands before a barrier.  The sums are the same in the same order: o is the same, bit for bit.
+// Bound by the rounds' latencies as fwd_small_kernel is, with half as many workgroups for near heads to wait for.  Which grids, and what it measured: two_strips().
+template <int D> struct FwdTwoCfg {
+    static constexpr int NWS = D == 64 ? 6 : 4;         // subtiles of a round, and a strip's waves for them
+    static constexpr int NWO = D / 32;                  // and its waves for O += A V
+    static constexpr int NTHR = 64 * 2 * (NWS + NWO);
+    static constexpr int ROW = D * 2;
+    static constexpr int SUB = 32 * ROW;
+    static constexpr int LOADS = SUB / 1024;
+    static constexpr int V_OFF = 2 * NWS * SUB;         // K and V by round parity, subtile
+    static constexpr int Q_OFF = V_OFF + NWS * SUB;     // Q of both strips passes through V of the second round
+    static constexpr int W_OFF = 4 * NWS * SUB;         // weights by strip, subtile
+    static constexpr int W_SUB = 2 * 1024;
+    static constexpr int LDS_BYTES = W_OFF + 2 * NWS * W_SUB;
+};
+
+template <int D>
+__global__ void __launch_bounds__(FwdTwoCfg<D>::NTHR)
+fwd_two_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
+               const uint16_t* __restrict__ v, const uint16_t* __restrict__ rb, uint16_t* __restrict__ o,
+               int T_arg, int BH, int H, int G, int n_arg,         // n_arg: pairs of strips a head; packed batch: sequences
+               const int* __restrict__ cu, int Ttot)
+{
+    using C = FwdTwoCfg<D>;
+    constexpr int NWS = C::NWS;
+    __shared__ __attribute__((aligned(1024))) char smem[C::LDS_BYTES];
+    __shared__ float s_tot[2][2][NWS][32];              // per round parity and strip: softplus totals of the subtiles (base 2), per row
+
+    asm volatile("" :: "s"(q), "s"(k), "s"(v), "s"(T_arg), "s"(G));
+    const int tid = threadIdx.x, lane = tid & 63;
+    const Share sh = in_scalars(share_of(blockIdx.x, BH, -1));
+    const int bh = sh.bh, head = bh % H;
+    int T = T_arg, npair = n_arg, i = sh.i;
+    long row0 = bh * (long)T, kvrow0 = (long)(G == 1 ? bh : (int)((unsigned)bh / (unsigned)G)) * T;
+    if (cu) {                                           // packed batch: bh is the head alone, sh.i its place
+        const Place at = place_of<64>(sh.i, cu, n_arg, Ttot, T_arg, lane);
+        if (at.T == 0) return;
+        T = at.T;
+        npair = (T + 63) / 64;
+        i = at.i;
+        row0 = (long)head * Ttot + at.c0;
+        kvrow0 = (long)(head / G) * Ttot + at.c0;
+    }
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const bool sums = wave >= 2 * NWS;                  // one of the waves that take O += A V
+    const bool second = sums ? wave >= 2 * NWS + C::NWO : wave >= NWS;
+    const int w = wave - (second ? NWS : 0);            // subtile of a round
+    const int cols = wave - 2 * NWS - (second ? C::NWO : 0);         // columns 32 cols ..
+    const int n = lane & 31, hh = lane >> 5, gg = lane >> 4, li = lane & 15;
+    const int q0 = (npair - 1 - i) * 64;
+    const int rows = min(T - q0, 64);                   // of both strips
+    const int last = (q0 + rows - 1) >> 5;              // the last subtile there is
+    const int nlast = min(T - 32 * last, 32);           // and its rows
+    const int strip = (q0 >> 5) + (second ? 1 : 0);
+    const bool live = strip <= last;                    // (a second strip may have no rows)
+    const uint16_t* Kg = reinterpret_cast<const uint16_t*>(scalar_base(k + kvrow0 * D));
+    const uint16_t* Vg = reinterpret_cast<const uint16_t*>(scalar_base(v + kvrow0 * D));
+    const uint32_t smem0 = lds_offset(smem);
+
+    constexpr int CPR = C::ROW / 16;
+    int off[C::LOADS];
+#pragma unroll
+    for (int i = 0; i < C::LOADS; ++i) off[i] = tile_off_perm<D>(i * (1024 / C::ROW) + lane / CPR, lane % CPR);
+    auto stage = [&](const uint16_t* X, int sub, uint32_t dst) __attribute__((always_inline)) {
+        const uint64_t xb = scalar_base(X + (long)sub * 32 * D);
+        if (sub < last || nlast == 32) {
+            dma16_to_lds_run_at(xb, off, dst);
+        } else {                                        // rows past T are clamped (causality masks them)
+            int o[C::LOADS];
+#pragma unroll
+            for (int i = 0; i < C::LOADS; ++i) o[i] = off[i] - max(i * (1024 / C::ROW) + lane / CPR - (nlast - 1), 0) * C::ROW;
+            dma16_to_lds_run_at(xb, o, dst);
+        }
+    };
+    for (int i = wave; i < 2 * C::LOADS; i += C::NTHR / 64) {
+        const int r = i * (1024 / C::ROW) + lane / CPR;              // of both strips' 64
+        dma16_to_lds_at(scalar_base(q + (row0 + q0) * D), min(r, rows - 1) * C::ROW + (((lane % CPR) ^ swz_perm<D>(r & 31)) << 4),
+                        smem0 + C::Q_OFF + i * 1024);
+    }
+    const uint16_t* const Xg = second ? Vg : Kg;        // what this wave stages, and where: by parity NWS * SUB apart
+    const uint32_t mine = smem0 + (second ? C::V_OFF : 0) + w * C::SUB;
+    if (!sums && w <= last) {
+        stage(Xg, last - w, mine);
+        if (second) dma_wait<C::LOADS>();               // all but V
+        else dma_wait<0>();
+    } else {
+        dma_wait<0>();
+    }
+    barrier_nofence();
+    const float c2 = SB_LOG2E / sqrtf((float)D);
+    float a[2] = {0.0f, last > (q0 >> 5) ? 0.0f : INFINITY};         // carries of the round, of both strips in all waves
+    int st = 0, top = last;
+    auto add_up = [&](float& mine_a) __attribute__((always_inline)) {
+        float t[2][NWS];
+#pragma unroll
+        for (int s = 0; s < 2; ++s)
+#pragma unroll
+            for (int x = 0; x < NWS; ++x) t[s][x] = s_tot[st][s][x][n];
+#pragma unroll
+        for (int s = 0; s < 2; ++s)
+#pragma unroll
+            for (int x = 0; x < NWS; ++x) {
+                if (x == w && (s == 1) == second) mine_a = a[s];
+                a[s] += t[s][x];
+            }
+    };
+    auto ended = [&]() __attribute__((always_inline)) {              // alike in all waves
+        return top < NWS || __builtin_amdgcn_ballot_w64(!(a[0] >= CARRY_EXHAUSTED && a[1] >= CARRY_EXHAUSTED)) == 0;
+    };
+    // Both kinds of waves pass the same barriers.
+    if (!sums) {
+        bf16x8 qf[D / 16];
+        {
+            const uint32_t at = smem0 + C::Q_OFF + (second ? C::SUB : 0) + tile_off_perm<D>(n, hh);
+#pragma unroll
+            for (int s = 0; s < D / 16; ++s) qf[s] = __builtin_bit_cast(bf16x8, lds_load16(at ^ (s << 5)));
+        }
+        const uint32_t ka = smem0 + w * C::SUB + tile_off_perm<D>(perm_row(n), hh);          // K as A operand, ^ (s << 5)
+        const uint32_t wts = smem0 + C::W_OFF + wave * C::W_SUB + lane * 16;
+        for (;; top -= NWS, st ^= 1) {
+            const int sub = top - w;
+            float g[16], t_lo = 0.0f, t_hi = 0.0f;
+            bool linear = true;
+            // K(sub) has landed.  Where the next one goes was read before the last round's first barrier
+            if (!second && sub >= NWS) stage(Xg, sub - NWS, mine + (st ^ 1) * NWS * C::SUB);
+            const bool work = sub >= 0 && sub <= strip && live;
+            if (work) {
+                u32x4 kop[D / 16];
+#pragma unroll
+                for (int s = 0; s < D / 16; ++s) kop[s] = lds_load16((ka + st * NWS * C::SUB) ^ (s << 5));
+                f32x16 acc;
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
+#pragma unroll
+                for (int s = 0; s < D / 16; ++s)
+                    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, kop[s]), qf[s], acc, 0, 0, 0);
+                auto keep = [&](auto lin, const float (&x)[16], float x_lo, float x_hi) __attribute__((always_inline)) {
+                    linear = decltype(lin)::value;
+                    t_lo = x_lo;
+                    t_hi = x_hi;
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) g[r] = x[r];
+                };
+                if (sub == strip) chain_of<true>(acc, c2, n, hh, keep);
+                else chain_of<false>(acc, c2, n, hh, keep);
+            }
+            if (second) dma_wait<0>();                   // V(sub) has landed
+            if (hh == 0) s_tot[st][second ? 1 : 0][w][n] = t_lo + t_hi;
+            barrier_lds();                               // totals and V have landed, the weights before have been used
+            float mine_a = 0.0f;
+            add_up(mine_a);
+            if (second && sub >= NWS) stage(Xg, sub - NWS, mine + (st ^ 1) * NWS * C::SUB);
+            if (work) {
+                bf16x8 p[2];
+                if (linear) weights_of<true>(g, t_lo, t_hi, mine_a, hh, p);
+                else weights_of<false>(g, t_lo, t_hi, mine_a, hh, p);
+                lds_store16(wts, p[0]);
+                lds_store16(wts + 1024, p[1]);
+            }
+            if (!second) dma_wait<0>();                  // the next K has landed
+            barrier_lds();
+            if (ended()) break;
+        }
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); // subtiles staged before the sweep stopped
+        return;
+    }
+    uint32_t vtr[2];                                     // V of the first subtile, this wave's columns, through the transposing load
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+        vtr[t] = smem0 + C::V_OFF + tile_off_perm<D>(16 * (gg >> 1) + (li >> 2) + 4 * t, 4 * cols + 2 * (gg & 1) + ((li & 3) >> 1)) + 8 * (li & 1);
+    const uint32_t wts = smem0 + C::W_OFF + (second ? NWS * C::W_SUB : 0) + lane * 16;
+    f32x16 oacc;                                         // columns 32 cols ..
+#pragma unroll
+    for (int r = 0; r < 16; ++r) oacc[r] = 0.0f;
+    bf16x8 p[2 * NWS], x[2 * NWS];
+    auto ask = [&](int st, int count) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < 2 * NWS; ++i) {
+            const int w = min(i >> 1, count - 1), s = i & 1;
+            const uint32_t vs = (st * NWS + w) * C::SUB + 8 * s * C::ROW;
+            p[i] = __builtin_bit_cast(bf16x8, lds_load16(wts + w * C::W_SUB + s * 1024));
+            x[i] = tr_pair_at(vtr[0] + vs, vtr[1] + vs);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    auto multiply = [&](int from, int to) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < 2 * NWS; ++i)
+            if (i >= from && i < to) oacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(p[i], x[i], oacc, 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    int from = last > strip ? 2 : 0;                     // (the first strip has no weights for the subtile on the second one's diagonal)
+    for (;; top -= NWS, st ^= 1) {
+        if (top != last && live) {                       // the round before: half of it beside the logits of this one
+            ask(st ^ 1, NWS);
+            multiply(from, NWS);
+        }
+        barrier_lds();
+        if (top != last && live) {
+            multiply(NWS, 2 * NWS);
+            from = 0;
+        }
+        float none = 0.0f;
+        add_up(none);
+        barrier_lds();
+        if (ended()) break;
+    }
+    if (!live) return;
+    const int count = min(NWS, top + 1);                 // the last round
+    ask(st, count);
+    multiply(from, 2 * count);
+
+    // ---- store.  oacc[r] is query row 8*(r/4) + 4*hh + r%4, column 32 cols + n.
+    const int own = second ? rows - 32 : min(rows, 32);  // rows of the strip
+    if (rb) {                                            // remainder bias, as in fwd_bf16_kernel
+        const float rem = fast_exp2(-(second ? a[1] : a[0]));
+        const float rc = __builtin_bit_cast(float, (uint32_t)rb[head * D + 32 * cols + n] << 16);
+#pragma unroll
+        for (int r = 0; r < 16; ++r) oacc[r] += __shfl(rem, 8 * (r >> 2) + 4 * hh + (r & 3)) * rc;
+    }
+    store_strip_rows<D>(reinterpret_cast<uint16_t*>(scalar_base(o + (row0 + 32 * strip) * D + 32 * cols)), oacc, own, n, hh);
 }
 
 template <int D, bool WRITE_M, bool RB, Packed PK = Packed::NO, bool TRI = false>
@@ -921,6 +1151,14 @@ hipError_t launch_one(const uint16_t* q, const uint16_t* k, const uint16_t* v, c
         if (!fits || e != hipSuccess) return e;
     }
     const int heads = VL ? H : BH, n = VL ? BH / H : (T + 31) / 32;
+    if constexpr (!WRITE_M && D >= 64) {
+        if (enough == CARRY_EXHAUSTED && two_strips(strips, T, D)) {
+            const long pairs = pieces(BH / H, H, T, 64, VL, Ttot);
+            hipLaunchKernelGGL((fwd_two_kernel<D>), dim3((unsigned)pairs), dim3(FwdTwoCfg<D>::NTHR), 0, stream,
+                               q, k, v, rb, o, T, heads, H, G, VL ? BH / H : (T + 63) / 64, cu, Ttot);
+            return hipGetLastError();
+        }
+    }
     auto go = [&](auto waves) {
         constexpr int NWS = decltype(waves)::value;
         hipLaunchKernelGGL((fwd_small_kernel<D, NWS>), dim3((unsigned)strips), dim3(FwdSmallCfg<D, NWS>::NTHR), 0, stream,

@@ -205,9 +205,26 @@ inline bool small_fwd_grid(long strips, int T, int d)
 // and not    H9 T2753 (783) none 13.0 / 7.6 of the strips, a third 17.4 / 20.5, all 27 / 21;  H7 T3000 (658) 6.9 / 10.5 / 7.3, 39 / 15.7 / 22.2, 39 / 26 / 22;  H7 T4096 (896) 7.0 / 14.3 / 10.2, 52 / 22 / 29, 52 / 40 / 33;  H5 T6000 (940) 7.1 / 14.6 /
 //            10.5, 74 / 28 / 41, 75 / 57 / 47;  H1 T16384 (512) all 196 / 77 / 107
 // At d = 64, two workgroups to a CU, and d = 128 (of two waves in place of four) far heads lose as much as near ones gain, or more: H10 T3000 d64 9.0 / 18.4 / 15.3,
-// 45 / 27.9 / 29.2, 45 / 41 / 49;  H10 T2048 d128 12.8 / 17.5 / 16.0, 45 / 25 / 36, 45 / 38 / 53.  Nor does the backward gain by two waves at d = 128: B1 H8 T2000 37 /
-// 45 / 34, 117 / 72 / 119, 118 / 88 / 122.
+// 45 / 27.9 / 29.2, 45 / 41 / 49;  H10 T2048 d128 12.8 / 17.5 / 16.0, 45 / 25 / 36, 45 / 38 / 53 (two_strips()).  Nor does the backward gain by two waves at d = 128: B1 H8
+// T2000 37 / 45 / 34, 117 / 72 / 119, 118 / 88 / 122.
 inline bool four_fwd_waves(long strips, int T) { return strips > std::max(768, 3 * (T / 10)); }
+
+// Grids without m whose strips go two to a workgroup (fwd_two_kernel): near heads are bound by how many rounds of workgroups the chip takes, a CU having room for
+// one, and were slower in strips than in blocks; a lone far strip's rounds take 10 to 15 % longer beside another's at d = 128, a third longer at d = 64, with
+// six subtiles to a round in place of eight.  Blocks / one strip / two, us, none far, then a third, then all:
+//   d = 64   B1 H12 T2080 (780 strips) 8.8 / 15.9 / 11.6, 32 / 19.5 / 19.2, 32 / 27 / 20;  H10 T2500 (790) 8.7 / 16.1 / 12.1, 38 / 22.4 / 22.4, 38 / 31 / 23;  H9 T2752 (774)
+//            8.7 / 15.8 / 12.3, 41 / 21.3 / 24.3, 41 / 32 / 25;  H10 T3000 (940) 9.0 / 18.4 / 13.4, 45 / 27.8 / 26.3, 45 / 41 / 30;  H9 T3500 (990) 9.1 / 19.2 / 13.6,
+//            52 / 28.3 / 29.8, 52 / 48 / 35
+//   d = 128  H12 T1200 (456) 12.0 / 12.7 / 8.2, 28 / 16.7 / 18.5, 28 / 19 / 18;  H8 T2000 (504) 12.0 / 14.6 / 10.1, 43 / 24.4 / 27.7, 43 / 29 / 28;  H6 T2500 (474) 11.8 / 13.2 /
+//            8.4, 53 / 28.4 / 32.4, 53 / 32 / 32;  H2 T8192 (512) 12.1 / 16.0 / 10.5, all 162 / 92 / 100
+// and not    d = 64 H7 T3000 (658) 8.5 / 14.6 / 11.2, 44 / 19.9 / 25.8, 44 / 31 / 26;  H7 T3500 (770) 8.7 / 16.0 / 12.4, 51 / 23 / 30, 51 / 39 / 30;  H5 T6000 (940) 9.1 / 19.5 / 13.3,
+//            85 / 35 / 47, 86 / 69 / 52;  d = 128 beyond two rounds of single strips, where near heads gain less: H9 T2000 (567) 12.3 / 16.5 / 14.9, 43 / 24.7 / 28.2, 44 / 36 / 30;
+//            nor where strips were always faster than blocks, H12 T1000 (384) 14.0 / 11.3 / 7.6, 16.9 / 14.2 / 15.3, 17.7 / 14.5 / 15.7;  d = 32 (four subtiles to a round)
+//            H7 T3000 6.9 / 10.4 / 8.0, 39 / 15.7 / 24.9, 39 / 26 / 25
+inline bool two_strips(long strips, int T, int d)
+{
+    return d == 128 ? strips > 384 && strips <= 512 : d == 64 && strips > std::max(768, T / 4);
+}
 
 // Grids of the key-stationary pass at d <= 64 whose blocks are taken by two groups of four waves (bwd_dkv_kernel<.., 2>): where a
 // block has a CU to itself anyway (one wave per SIMD issues an instruction every five clocks at best, two keep it busy), and

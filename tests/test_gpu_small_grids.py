@@ -7,7 +7,7 @@ import pytest
 import torch
 
 from helpers import check_grad, check_m, dev, fwd_bound, nan_bytes, to64
-from test_gpu_exhausted import gen, mixed, sb  # noqa: F401  (fixtures)
+from test_gpu_exhausted import gen, mixed, mixed_grouped, sb  # noqa: F401  (fixtures)
 
 pytestmark = pytest.mark.gpu
 
@@ -200,6 +200,46 @@ def test_forward_strips_of_four_waves(sb, oracle, gen, H, T):
     ref, rem = oracle.fwd(*(to64(t[:, h]) for t in (q, k, v)), r=to64(r[h]))
     assert np.all(np.abs(to64(o[:, h]) - ref) <= fwd_bound(ref, to64(v[:, h])))
     check_m(to64(m[:, h]), rem)
+
+
+# last pairs of one row, of one strip, of one row behind a whole strip; shared kv heads
+@pytest.mark.parametrize("H,Hkv,T,d", [(10, 10, 2500, 64), (12, 12, 2080, 64), (10, 5, 2529, 64), (9, 9, 3489, 64), (10, 10, 3009, 64),
+                                       (12, 12, 1057, 128), (8, 8, 2000, 128), (10, 10, 1600, 128), (12, 4, 1281, 128), (2, 2, 8190, 128)])
+def test_forward_two_strips(sb, oracle, gen, H, Hkv, T, d):
+    """Two strips a workgroup, without m: o is what the 128-row blocks of twice as large a grid give, bit for bit, and what is given with m; with a remainder bias
+    as well, and against the oracle.  Heads that are exhausted within a round, both strips or one after the other, and heads that never are."""
+    q, k, v, _ = mixed_grouped(gen, 1, H, Hkv, T, d, seed=700 + T)
+    r = gen.remainder_embedding(H, d, seed=11)
+    qd, kd, vd, rd = dev(q, k, v, r)
+    twice = [torch.cat([t] * 2) for t in (qd, kd, vd)]
+    for bias in (None, rd):
+        o = sb.sb_attn_fwd_gqa(qd, kd, vd, r=bias, want_m=False)
+        assert torch.equal(o, sb.sb_attn_fwd_gqa(qd, kd, vd, r=bias)[0])
+        assert torch.equal(o, sb.sb_attn_fwd_gqa(*twice, r=bias, want_m=False)[:1])
+    h, G = slice(0, min(3, Hkv)), H // Hkv
+    heads = slice(0, h.stop * G)
+    if T <= 4000:
+        ref = oracle.fwd_gqa(to64(q[:, heads]), to64(k[:, h]), to64(v[:, h]), r=to64(r[heads]))[0]
+        assert np.all(np.abs(to64(o[:, heads]) - ref) <= fwd_bound(ref, to64(v[:, h])))
+
+
+TWO_STRIPS_LENS = [2500, 33, 64, 65, 1, 0, 31, 96, 97]
+
+
+@pytest.mark.parametrize("H,d", [(9, 64), (5, 128)])
+def test_forward_two_strips_packed(sb, gen, H, d):
+    """Sequences of all kinds of lengths, two strips a workgroup: each as it is alone."""
+    lens = TWO_STRIPS_LENS
+    q, k, v = dev(*(t[0] for t in mixed(gen, 1, H, sum(lens), d, seed=18)))
+    cu = torch.tensor(np.cumsum([0] + lens), dtype=torch.int32).cuda()
+    o = torch.full_like(q, float("nan"))
+    sb.sb_attn_varlen_fwd(q, k, v, cu, max(lens), o=o, want_m=False)
+    at = 0
+    for n in lens:
+        s = slice(at, at + n)
+        at += n
+        if n:
+            assert torch.equal(o[:, s], sb.sb_attn_fwd_train(*(t[None, :, s].contiguous() for t in (q, k, v)))[0][0]), n
 
 
 @pytest.mark.parametrize("d", [32, 64, 128])

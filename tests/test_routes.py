@@ -41,9 +41,9 @@ int main()
             printf("%d\n", packed_as(B, T, Ttot) == Packed::BY_LENGTH);
             continue;
         }
-        if (packed == 5) {                              // forward: waves that take a strip's subtiles
+        if (packed == 5) {                              // forward: waves that take a strip's subtiles; Ttot: without m, 2 where two strips share a workgroup
             const long n = pieces(B, H, T, 32, false, 0);
-            printf("%d\n", !small_fwd_grid(n, T, d) ? 0 : d == 128 || (d == 32 && four_fwd_waves(n, T)) ? 4 : 8);
+            printf("%d\n", !small_fwd_grid(n, T, d) ? 0 : Ttot && two_strips(n, T, d) ? 2 : d == 128 || (d == 32 && four_fwd_waves(n, T)) ? 4 : 8);
             continue;
         }
         printf("%d %d %ld %d\n", small_fwd_grid(strips, T, d), query_strips(B, H, T, d, packed, Ttot), strips,
@@ -150,6 +150,12 @@ def test_shapes_of_four_waves(ask):
     import test_gpu_small_grids as t
     for H, T in t.test_forward_strips_of_four_waves.pytestmark[0].args[1]:
         assert ask([(1, H, H, T, 32, 5, 0), (2, H, H, T, 32, 5, 0)]) == [(4,), (0,)], (H, T)
+    for H, Hkv, T, d in t.test_forward_two_strips.pytestmark[0].args[1]:
+        assert ask([(1, H, Hkv, T, d, 5, 1), (2, H, Hkv, T, d, 5, 1)]) == [(2,), (0,)], (H, T, d)
+    for H, d in t.test_forward_two_strips_packed.pytestmark[0].args[1]:
+        n = H * sum((x + 31) // 32 for x in t.TWO_STRIPS_LENS)
+        got = ask([packed(t.TWO_STRIPS_LENS, H, d)])[0]
+        assert got[0] and n <= got[2] and (384 < got[2] <= 512 if d == 128 else got[2] > 768), (H, d)
 
 
 def test_shapes_of_the_longest_strips(ask):
@@ -191,6 +197,10 @@ def test_waves_of_strips(ask):
     for H, T, waves in ((10, 2500, 4), (10, 3000, 4), (8, 3100, 8), (9, 2753, 8), (7, 3000, 8), (7, 4096, 8), (5, 6000, 8), (4, 7900, 8), (1, 16384, 8), (13, 1990, 0)):
         assert ask([(1, H, H, T, 32, 5, 0)]) == [(waves,)], (H, T)
     assert ask([(1, 10, 10, 3000, 64, 5, 0), (1, 10, 10, 2048, 128, 5, 0)]) == [(8,), (4,)]
+    for H, T, d, two in ((12, 2080, 64, 1), (10, 2500, 64, 1), (9, 2752, 64, 1), (10, 3000, 64, 1), (9, 3500, 64, 1), (12, 1200, 128, 1), (8, 2000, 128, 1),
+                         (6, 2500, 128, 1), (2, 8192, 128, 1), (1, 16384, 128, 1), (7, 3000, 64, 0), (7, 3500, 64, 0), (5, 6000, 64, 0), (9, 2000, 128, 0),
+                         (12, 1000, 128, 0), (7, 3000, 32, 0), (10, 3000, 32, 0)):
+        assert (ask([(1, H, H, T, d, 5, 1)]) == [(2,)]) == bool(two), (H, T, d)
 
 
 def test_shapes_of_the_tests_of_carries(ask):
