@@ -446,17 +446,20 @@ __device__ __forceinline__ Place longest_first(int place, const int* __restrict_
     }
     return at;
 }
+// Heads of a packed batch whose blocks are looked up by length, in turn with every fourth block.  Eight, sixteen or twenty-four heads that turn with every block
+// meet every XCD; turning with every fourth, neighbouring blocks of a sequence, which sweep the same tiles, meet on one.  With every block / every
+// fourth, a third of the heads far, backward, us: H8 d64, longest 5000 413 / 373, d128 622 / 539, longest 2048 d128 197 / 189; H16 d64, longest 5000 708 / 685; H24
+// d128, longest 2048 520 / 508, others of 16 and 24 heads alike.  Not for more (H32 d64 434 / 458, 1340 / 1374, d128 651 / 674), nor for other numbers,
+// which change their XCD with every block anyway (H9 d128 653 / 753, H13 963 / 1075, H11 252 / 262; H6, H10 and H14 alike or 1 to 2 % slower; H12 d32, 24 up to 1500
+// 84 / 90), nor where query heads share a kv head, whose tiles they find on any (H32 Hkv4 d64 1700 / 1840).
+__host__ __device__ __forceinline__ bool turn_with_every_fourth(int H, int G) { return G == 1 && H % 8 == 0 && H <= 24; }
 // Workgroup wg's block: its head in `head`, its sequence and the rest in the result (T = 0: none).  H heads, G of which share keys and values
 template <int ROWS, bool BY_LENGTH>
 __device__ __forceinline__ Place block_of(int& head, unsigned wg, int H, int G, const int* __restrict__ cu, int nseq, int Ttot, int T_arg, int lane)
 {
     if constexpr (BY_LENGTH) {
-        // Heads that turn with every block meet every XCD; turning with every fourth, neighbouring blocks of a sequence, which sweep the
-        // same tiles, meet on one: with every block / every fourth, backward H8 d128, 5 up to 5653 rows 500 / 440, H24 d64 above 371 / 363, H7 d64, 31 up
-        // to 5000 310 / 302.  Where four heads are over, a head changes its XCD with every block anyway (H12 d32, 24 up to 1500 84 / 90), and query heads that
-        // share a kv head find its tiles on any (H32 Hkv4 d64 above 1700 / 1840).
         Share sh = share_of(wg, H, -1);
-        if (G == 1 && H > 4 && H % 8 != 4) sh.bh = (wg + (sh.i >> 2)) % (unsigned)H;
+        if (turn_with_every_fourth(H, G)) sh.bh = (wg + (sh.i >> 2)) % (unsigned)H;
         sh = in_scalars(sh);
         head = sh.bh;
         return longest_first<ROWS>(sh.i, cu, nseq, Ttot, T_arg, lane);

@@ -37,6 +37,10 @@ int main()
             printf("%d\n", bias_chunks(B, T, true, Ttot));
             continue;
         }
+        if (packed == 7) {                              // packed batch: its heads turn with every fourth block
+            printf("%d\n", turn_with_every_fourth(H, H / Hkv));
+            continue;
+        }
         if (packed == 6) {                              // packed batch: its blocks are looked up by their length
             printf("%d\n", packed_as(B, T, Ttot) == Packed::BY_LENGTH);
             continue;
@@ -249,6 +253,12 @@ def test_strips_of_queries_come_with_strips_of_keys(ask):
     assert any(dq for _, dq, _, _ in got)
     for row, (_, dq, _, keys) in zip(rows, got):
         assert not dq or KEYS[keys] == "strips", row
+
+
+def test_turns_of_packed_heads(ask):
+    """Every fourth block only where all heads would keep to one XCD, and are not many."""
+    assert [H for H in range(1, 65) if ask([(4, H, H, 2000, 64, 7, 8000)]) == [(1,)]] == [8, 16, 24]
+    assert ask([(4, H, H // 2, 2000, 64, 7, 8000) for H in (8, 16, 24)]) == [(0,)] * 3
 
 
 def test_two_wave_groups(ask):
