@@ -2184,7 +2184,7 @@ hipError_t launch_one(const uint16_t* q, const uint16_t* k, const uint16_t* v, c
     const long gk = keys == Keys::PAIRS ? share_grid(BHkv, nkb, true) : block_grid(B, Hkv, T, BKW, PK, Ttot);
     const int shared = VL ? B : BHkv;                    // what the key-stationary kernels' BH counts
     const long strips_q = pieces(B, H, T, 32, VL, Ttot), strips_k = pieces(B, Hkv, T, 32, VL, Ttot);
-    const int run_q = VL || G > 1 ? -1 : query_run(BH, nqb, D), run_k = VL || G > 1 ? -1 : share_run(BHkv, nkb);
+    const int run_q = VL || G > 1 ? -1 : query_run(BH, nqb, D, true), run_k = VL || G > 1 ? -1 : share_run(BHkv, nkb);
     // checked before the first launch, so that an error leaves nothing enqueued
     // workgroups of the bias's gradient behind those of the passes
     const long bias_q = drb ? (long)nchunk * entries * H : 0, bias_k = drb ? H : 0;

@@ -1146,7 +1146,7 @@ hipError_t launch_one(const uint16_t* q, const uint16_t* k, const uint16_t* v, c
         if (grid > 0x7fffffffL) return hipErrorInvalidValue;
         const hipError_t e = launch_workgroups(grid, 64 * NW, [&](unsigned n, int first_wg) {
             hipLaunchKernelGGL((fwd_bf16_kernel<D, WRITE_M, RB, PK, TRI>), dim3(n), dim3(64 * NW), 0, stream,
-                               q, k, v, rb, o, m, T, VL ? BH / H : BH, H, G, nqb, enough, tile_counts, cu, Ttot, VL || G > 1 ? -1 : query_run(BH, nqb, D), first_wg);
+                               q, k, v, rb, o, m, T, VL ? BH / H : BH, H, G, nqb, enough, tile_counts, cu, Ttot, VL || G > 1 ? -1 : query_run(BH, nqb, D, false), first_wg);
         });
         if (!fits || e != hipSuccess) return e;
     }

@@ -348,21 +348,25 @@ inline int share_run(long heads, int nblk)
 // The forward and the query-stationary pass take runs in shorter launches too: blocks that sweep the same tiles one tile apart meet in
 // an L2, and a far head's blocks no longer come at the same CUs in every round of the launch.
 // Every block / runs of 2 (below 64 heads from 24 blocks on of 4), us, forward with m, then this pass, every third head far, a third drawn at random, all far:
-//   from 64 heads    B8 H16 T2048 d64 84 / 81, 87 / 81, 102 / 99 and 95 / 93, 103 / 95, 169 / 166;  B4 H24 T1024 d128 43 / 40, 43 / 40, 44 / 42 and 51 / 49,
-//                    51 / 49, 64 / 62;  B5 H16 T1500 d128 61 / 57, 63 / 57, 70 / 67 and 71 / 67, 73 / 69, 106 / 102;  the worst: B10 H16 T3000 d64
-//                    206 / 207, 206 / 205, 268 / 264 and 224 / 230, 233 / 234, 457 / 450
+//   from 64 heads    B8 H16 T2048 d64 84 / 81, 87 / 81, 102 / 99 and 95 / 93, 103 / 95, 169 / 166 (of the whole step, one third far, 2 of 314);  B4 H24 T1024 d128 43 / 40,
+//                    43 / 40, 44 / 42 and 51 / 49, 51 / 49, 64 / 62;  B5 H16 T1500 d128 61 / 57, 63 / 57, 70 / 67 and 71 / 67, 73 / 69, 106 / 102;  the worst: B10 H16
+//                    T3000 d64 206 / 207, 206 / 205, 268 / 264 and 224 / 230, 233 / 234, 457 / 450
 //   fewer            B2 H24 T4096 d64 114 / 105, 114 / 108, 144 / 137 and 164 / 129, 163 / 149, 240 / 236;  B4 H8 T4096 d32 75 / 59, 74 / 60, 77 / 76 and
 //                    122 / 90, 123 / 91, 130 / 129;  B3 H8 T6000 d64 122 / 118, 112 / 104, 154 / 147 and 179 / 174, 155 / 154, 257 / 250;  B2 H20 T2500 d64
 //                    (of 2) 50 / 47, 51 / 47, 55 / 55 and 74 / 70, 77 / 70, 89 / 88;  B1 H32 T4096 d128 (of 2) 129 / 119, 127 / 126, 168 / 162 and 164 / 146,
 //                    164 / 160, 266 / 260, of 4 121, 129, 157 and 145, 181, 251;  B1 H24 T12000 d32 (of 2 / of 4) 313 / 305, 318 / 303, 408 / 401 and
 //                    417 / 354, 488 / 397, 742 / 730, but B1 H24 T8192 d128 319 / 317, 327 / 314, 450 / 443 and 361 / 359, 352 / 360, 720 / 712
+// Whose heads are far counts for as much: over 76 shapes with a third of them drawn at random the forward is 4 % faster in the mean, the whole backward 1 %, single
+// ones from 9 % slower (B1 H40 T6000 d32) to 15 % faster.  This pass not at d = 64 with 64 to 127 heads, backward, every third far, at random, all, none: B6 H12 T2307
+// 164 / 179, 189 / 188, 291 / 289, 94 / 95; B10 H8 T2307 180 / 190, 189 / 199, 319 / 316, 99.5 / 98; B8 H11 T1500 110 / 114, 123 / 120, 165 / 161, 74 / 73; B9 H8 T1800
+// 121 / 134, 137 / 139, 194 / 190, 74 / 74 (the forward there 45.2 / 45.2, 45.2 / 45.9, 52 / 51, 41 / 36).
 // Not at d = 32 from 64 heads on, where tiles are small (B8 H16 T2048 59 / 59, 61 / 59, 71 / 72 and 69 / 73, 78 / 77, 127 / 124), with fewer than 8 blocks (B8 H24
 // T700 d64, this pass, at random, 37 / 39), nor for the key-stationary pass, whose blocks outnumber their places less (B4 H8 T4096 d32, runs of 4, 84 / 90).
-inline int query_run(long heads, int nblk, int d)
+inline int query_run(long heads, int nblk, int d, bool backward)
 {
     if (heads % 8 != 0 || heads * nblk < 768 || nblk < 8) return -1;
     if (nblk >= 64) return std::max(share_run(heads, nblk), heads < 64 && d < 128 ? 2 : 1);
-    if (heads >= 64) return d == 32 ? share_run(heads, nblk) : 1;
+    if (heads >= 64) return d == 32 || (d == 64 && backward && heads < 128) ? share_run(heads, nblk) : 1;
     return nblk >= (d == 128 ? 40 : 24) ? 2 : 1;
 }
 

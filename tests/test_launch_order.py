@@ -18,9 +18,9 @@ MAIN = r"""
 #include "sb_share.h"
 int main(int argc, char** argv)
 {
-    int heads, nblk, pairs, d;                                   // d: of the forward and the query-stationary pass, or 0
-    while (scanf("%d %d %d %d", &heads, &nblk, &pairs, &d) == 4) {
-        const int grid = (int)sb::share_grid(heads, nblk, pairs), run = d ? sb::query_run(heads, nblk, d) : sb::share_run(heads, nblk);
+    int heads, nblk, pairs, d, backward;                         // d: of the forward and the query-stationary pass, or 0
+    while (scanf("%d %d %d %d %d", &heads, &nblk, &pairs, &d, &backward) == 5) {
+        const int grid = (int)sb::share_grid(heads, nblk, pairs), run = d ? sb::query_run(heads, nblk, d, backward) : sb::share_run(heads, nblk);
         printf("%d %d\n", grid, run);
         for (int wg = 0; wg < grid; ++wg) {
             const sb::Share s = pairs ? sb::share_in_pairs(wg, nblk) : sb::share_of(wg, heads, run);
@@ -40,8 +40,8 @@ def order(tmp_path_factory):
     subprocess.run([HIPCC, "-std=c++17", "-O1", "--offload-host-only", f"-I{CSRC}", "main.hip", "-o", "main"],
                    cwd=tmp, check=True, stdout=subprocess.DEVNULL, stderr=subprocess.DEVNULL)
 
-    def get(heads, nblk, pairs=False, d=0):
-        out = subprocess.run([str(tmp / "main")], input=f"{heads} {nblk} {int(pairs)} {d}\n", text=True, check=True,
+    def get(heads, nblk, pairs=False, d=0, backward=False):
+        out = subprocess.run([str(tmp / "main")], input=f"{heads} {nblk} {int(pairs)} {d} {int(backward)}\n", text=True, check=True,
                              stdout=subprocess.PIPE).stdout.split()
         grid, run = int(out[0]), int(out[1])
         return np.array(out[2:], dtype=np.int64).reshape(grid, 2), 1 << run if run >= 0 else 0
@@ -123,3 +123,12 @@ def test_runs_of_the_forward(order, heads, nblk, d, run):
         assert np.array_equal(x[:, i] == x[:, i + 1], np.full(heads, (i + 1) % run != 0)), i
     if nblk >= 8 * max(run, 1):
         assert all(len(set(x[h])) == 8 for h in range(heads))
+
+
+def test_runs_of_middling_head_counts(order):
+    """d = 64, query-stationary pass: not from 64 heads on until there are 128; otherwise as the forward."""
+    runs = lambda **k: [h for h in range(64, 200, 8) if order(h, 20, **k)[1] > 1]
+    assert runs(d=64, backward=True) == list(range(128, 200, 8))
+    assert runs(d=64) == runs(d=128) == runs(d=128, backward=True) == list(range(64, 200, 8))
+    for d, nblk in ((32, 24), (64, 24), (128, 40)):
+        assert all(order(h, nblk, d=d)[1] == order(h, nblk, d=d, backward=True)[1] > 1 for h in (32, 40, 48, 56))
