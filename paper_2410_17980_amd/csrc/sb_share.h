@@ -182,8 +182,8 @@ __device__ __forceinline__ Place place_of(int place, const int* __restrict__ cu,
 // (fwd_small_kernel), in place of 128-row blocks whose every wave has its rows' chain to itself.  Blocks / strips, us, without m (with it,
 // where it matters, in brackets), all heads far, then a third, then none:
 //   d = 32   T3000 H10 (940) 39 / 34, 38 / 23, 7 / 14 (22 / 20) (eight waves; four_fwd_waves());  T8192 H1 100 / 37
-//   d = 64   H64 T100 (256) 5.7 / 5.0;  H24 T500 (384) 10.6 / 8.5, 10.5 / 8.0, 8.2 / 8.0;  T3000 H10 (940) 45 / 41, 44 / 28, 9 / 18 (26 / 25);  T8192 H1
-//            114 / 44;  T16384 H1 225 / 92, none 8.5 / 9.7
+//   d = 64   H64 T100 (256) 5.7 / 5.0;  H24 T500 (384) 10.6 / 8.5, 10.5 / 8.0, 8.2 / 8.0;  T3000 H10 (940) 45 / 41, 44 / 28, 9 / 18 (26 / 25) (one to a
+//            workgroup; two_strips());  T8192 H1 114 / 44;  T16384 H1 225 / 92, none 8.5 / 9.7
 //   d = 128  H24 T500 (384) 14.6 / 11.1, 14.5 / 10.5, 11.3 / 10.5;  T1000 H12 (384) 24.5 / 15.3, 24 / 15, 11.4 / 11.9;
 //            T2048 H10 (640) 45 / 38, 44 / 26, 13 / 18 (26 / 26);  T8192 H1 161 / 82;  T16384 H1 318 / 175, none 12 / 16
 // and not, d = 32 H37 T200 (259) 5.7 / 6.4;  T2048 H18 (1152) 28 / 32, 27 / 23, 8 / 17 (17 / 22);  d = 64 H96 T100 (384) 5.8 / 7.1;  T500 H48 (768) 11.1 / 14.8,

@@ -28,7 +28,8 @@ inline int room(int T)
 // near heads have for nothing.  Alone / three launches, us, no head far, then a third, then all:
 //   d = 32   B24 H24 Hkv8 T2048 5.5 / 11.6, 12.0 / 13.4, 12.3 / 18.2;  B30 H10 T2048 6.0 / 12.0, 15.9 / 17.2, 16.8 / 21.8;  B32 H16 T2048 7.0 / 11.7, 17.7 / 20.7,
 //            26.5 / 28.9;  not B30 H10 T2560 5.7 / 11.6, 19.0 / 16.9, 20.3 / 24.1
-//   d = 64   B24 H24 Hkv8 T2048 6.3 / 11.7, 16.1 / 17.7, 21.1 / 24.9;  B16 H16 T2048 7.1 / 12.1, 18.6 / 19.4, 25.5 / 28.6;  not beyond a round of the chip:
+//   d = 64   B24 H24 Hkv8 T2048 6.3 / 11.7, 16.1 / 17.7, 21.1 / 24.9;  B13 H16 T2048 5.2 / 12.1, 15.9 / 18.7, 17.8 / 24.7;  B16 H16 T2048 7.1 / 12.1, 18.6 / 19.4,
+//            25.5 / 28.6;  not beyond a round of the chip:
 //            B32 H16 T2048 11.4 / 13.6, 32.7 / 29.1, 47.1 / 47.9, nor where few workgroups leave the far keys' launch room: B12 H12 T1800 5.3 / 9.6,
 //            15.0 / 13.5, 16.0 / 18.4
 //   d = 128  not B16 H16 T2048 11.7 / 13.7, 32.8 / 30.3, 46.9 / 48.5
