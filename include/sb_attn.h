@@ -156,12 +156,17 @@ int sb_attn_bwd_rb(const void* q, const void* k, const void* v, const void* r, c
  * kv head h / (H / Hkv).  These are the general forms of the calls above:
  *   sb_attn_fwd_gqa  forward; r (remainder bias, [H, d] bf16) and m may each be NULL.
  *   sb_attn_bwd_gqa  backward; r and dr both NULL or both given; dk, dv are summed over
- *                    the query heads of each group inside one workgroup's registers (no
- *                    atomics, bit-reproducible).  Workspace as for sb_attn_bwd with the
- *                    number of query heads: sb_attn_bwd_workspace_bytes(B, H, T, d).
+ *                    the query heads of each group in a fixed order (bit-reproducible).
+ *                    Workspace as for sb_attn_bwd with the number of query heads:
+ *                    sb_attn_bwd_workspace_bytes(B, H, T, d).  With
+ *                    sb_attn_bwd_gqa_workspace_bytes(B, H, Hkv, T, d), at most 210 MB more,
+ *                    a far-reaching group's heads can be shared out over the chip, up to twice
+ *                    as fast where only some heads reach far (the sums over the group are then
+ *                    taken in another fixed order).  0 for a bad shape.
  */
 int sb_attn_fwd_gqa(const void* q, const void* k, const void* v, const void* r, void* o, float* m,
                     int B, int H, int Hkv, int T, int d, void* stream);
+size_t sb_attn_bwd_gqa_workspace_bytes(int B, int H, int Hkv, int T, int d);
 int sb_attn_bwd_gqa(const void* q, const void* k, const void* v, const void* r, const float* m,
                     const void* dout, float* dq, float* dk, float* dv, float* dr,
                     void* workspace, size_t workspace_bytes, int B, int H, int Hkv, int T, int d, void* stream);
@@ -181,11 +186,14 @@ int sb_attn_bwd_gqa(const void* q, const void* k, const void* v, const void* r, 
  * Otherwise exactly sb_attn_fwd_gqa / sb_attn_bwd_gqa per sequence, in one launch each;
  * dr adds up over all sequences in a fixed order.
  * Workspace: sb_attn_varlen_bwd_workspace_bytes(nseq, H, Ttot, max_T, d) bytes
- * = 8*H*Ttot*ceil(max_T/32) + nseq*H*(8 + 4*d)*ceil(max_T/128).
+ * = 8*H*Ttot*ceil(max_T/32) + nseq*H*(8 + 4*d)*ceil(max_T/128); with grouped kv heads
+ * sb_attn_varlen_bwd_gqa_workspace_bytes(nseq, H, Hkv, Ttot, max_T, d) does what
+ * sb_attn_bwd_gqa_workspace_bytes does above.
  */
 int sb_attn_varlen_fwd(const void* q, const void* k, const void* v, const void* r, void* o, float* m,
                        const int* cu_seqlens, int nseq, int H, int Hkv, int Ttot, int max_T, int d, void* stream);
 size_t sb_attn_varlen_bwd_workspace_bytes(int nseq, int H, int Ttot, int max_T, int d);
+size_t sb_attn_varlen_bwd_gqa_workspace_bytes(int nseq, int H, int Hkv, int Ttot, int max_T, int d);
 int sb_attn_varlen_bwd(const void* q, const void* k, const void* v, const void* r, const float* m,
                        const void* dout, float* dq, float* dk, float* dv, float* dr,
                        const int* cu_seqlens, int nseq, int H, int Hkv, int Ttot, int max_T, int d,

@@ -23,9 +23,9 @@ EXT_PATH = os.path.join(_HERE, "_sbtorch.so")
 
 EXPORTS = (
     "sb_attn_fwd", "sb_attn_fwd_halt", "sb_attn_fwd_train", "sb_attn_fwd_f32",
-    "sb_attn_bwd_workspace_bytes", "sb_attn_bwd", "sb_attn_bwd_dq", "sb_attn_bwd_dkdv",
+    "sb_attn_bwd_workspace_bytes", "sb_attn_bwd_gqa_workspace_bytes", "sb_attn_bwd", "sb_attn_bwd_dq", "sb_attn_bwd_dkdv",
     "sb_attn_fwd_rb", "sb_attn_bwd_rb", "sb_attn_fwd_gqa", "sb_attn_bwd_gqa",
-    "sb_attn_varlen_fwd", "sb_attn_varlen_bwd_workspace_bytes", "sb_attn_varlen_bwd",
+    "sb_attn_varlen_fwd", "sb_attn_varlen_bwd_workspace_bytes", "sb_attn_varlen_bwd_gqa_workspace_bytes", "sb_attn_varlen_bwd",
     "sb_attn_decode_workspace_bytes", "sb_attn_decode", "sb_attn_decode_static",
     "sb_diag_mfma_rate", "sb_diag_stream_read", "sb_diag_fwd_clock", "sb_diag_fwd_tri",
     "sb_status_string", "sb_version",
@@ -62,6 +62,8 @@ def load(build_if_missing: bool = True):
     lib.sb_attn_fwd_f32.restype = ci
     lib.sb_attn_bwd_workspace_bytes.argtypes = [ci, ci, ci, ci]
     lib.sb_attn_bwd_workspace_bytes.restype = ctypes.c_size_t
+    lib.sb_attn_bwd_gqa_workspace_bytes.argtypes = [ci, ci, ci, ci, ci]
+    lib.sb_attn_bwd_gqa_workspace_bytes.restype = ctypes.c_size_t
     lib.sb_attn_bwd.argtypes = [vp, vp, vp, fp, vp, fp, fp, fp, vp, ctypes.c_size_t, ci, ci, ci, ci, vp]
     lib.sb_attn_bwd.restype = ci
     lib.sb_attn_bwd_dq.argtypes = [vp, vp, vp, fp, vp, fp, vp, ctypes.c_size_t, ci, ci, ci, ci, vp]
@@ -81,6 +83,8 @@ def load(build_if_missing: bool = True):
     lib.sb_attn_varlen_fwd.restype = ci
     lib.sb_attn_varlen_bwd_workspace_bytes.argtypes = [ci, ci, ci, ci, ci]
     lib.sb_attn_varlen_bwd_workspace_bytes.restype = ctypes.c_size_t
+    lib.sb_attn_varlen_bwd_gqa_workspace_bytes.argtypes = [ci, ci, ci, ci, ci, ci]
+    lib.sb_attn_varlen_bwd_gqa_workspace_bytes.restype = ctypes.c_size_t
     lib.sb_attn_varlen_bwd.argtypes = [vp, vp, vp, vp, fp, vp, fp, fp, fp, fp, vp, ci, ci, ci, ci, ci, ci,
                                        vp, ctypes.c_size_t, vp]
     lib.sb_attn_varlen_bwd.restype = ci
@@ -218,6 +222,11 @@ def sb_attn_fwd_gqa(q, k, v, r=None, o=None, m=None, want_m=True, stream=None):
     return (_ext or _load_ext()).forward("sb_attn_fwd_gqa", True, q, k, v, r, o, m, want_m, stream)
 
 
+def sb_attn_bwd_gqa_workspace_bytes(B, H, Hkv, T, d) -> int:
+    """What sb_attn_bwd_gqa allocates itself: with it a far-reaching group's heads are shared out over the chip."""
+    return int(load().sb_attn_bwd_gqa_workspace_bytes(B, H, Hkv, T, d))
+
+
 def sb_attn_bwd_gqa(q, k, v, m, dout, r=None, dq=None, dk=None, dv=None, dr=None, workspace=None, stream=None):
     """bf16 backward with grouped kv heads.  Returns (dq, dk, dv) in fp32 (dk, dv [B,Hkv,T,d]),
     and dr [H,d] as a fourth item when r is given."""
@@ -233,6 +242,10 @@ def sb_attn_varlen_fwd(q, k, v, cu_seqlens, max_T, r=None, o=None, m=None, want_
 
 def sb_attn_varlen_bwd_workspace_bytes(nseq, H, Ttot, max_T, d) -> int:
     return int(load().sb_attn_varlen_bwd_workspace_bytes(nseq, H, Ttot, max_T, d))
+
+
+def sb_attn_varlen_bwd_gqa_workspace_bytes(nseq, H, Hkv, Ttot, max_T, d) -> int:
+    return int(load().sb_attn_varlen_bwd_gqa_workspace_bytes(nseq, H, Hkv, Ttot, max_T, d))
 
 
 def sb_attn_varlen_bwd(q, k, v, m, dout, cu_seqlens, max_T, r=None, dq=None, dk=None, dv=None, dr=None,

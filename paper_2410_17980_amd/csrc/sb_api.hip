@@ -103,6 +103,12 @@ size_t sb_attn_bwd_workspace_bytes(int B, int H, int T, int d)
     return sb::bwd_workspace_bytes(B, H, T, d);
 }
 
+size_t sb_attn_bwd_gqa_workspace_bytes(int B, int H, int Hkv, int T, int d)
+{
+    if (check_shape(B, H, T, d) != SB_OK || Hkv < 1 || H % Hkv != 0) return 0;
+    return sb::bwd_gqa_workspace_bytes(B, H, Hkv, T, d);
+}
+
 }  // extern "C"
 
 namespace {
@@ -126,7 +132,8 @@ int bwd_checked(const void* q, const void* k, const void* v, const void* r, cons
                                        static_cast<const uint16_t*>(v), static_cast<const uint16_t*>(r), m,
                                        static_cast<const uint16_t*>(dout), dq, dk, dv, dr,
                                        static_cast<float*>(workspace),
-                                       B, H, Hkv, T, d, passes, static_cast<hipStream_t>(stream));
+                                       B, H, Hkv, T, d, passes, static_cast<hipStream_t>(stream),
+                                       H > Hkv && workspace_bytes >= sb::bwd_gqa_workspace_bytes(B, H, Hkv, T, d));
     return e == hipSuccess ? SB_OK : SB_ERR_LAUNCH;
 }
 
@@ -203,6 +210,12 @@ size_t sb_attn_varlen_bwd_workspace_bytes(int nseq, int H, int Ttot, int max_T, 
     return sb::bwd_varlen_workspace_bytes(nseq, H, Ttot, max_T, d);
 }
 
+size_t sb_attn_varlen_bwd_gqa_workspace_bytes(int nseq, int H, int Hkv, int Ttot, int max_T, int d)
+{
+    if (check_varlen(nseq, H, Hkv, Ttot, max_T, d) != SB_OK) return 0;
+    return sb::bwd_varlen_gqa_workspace_bytes(nseq, H, Hkv, Ttot, max_T, d);
+}
+
 int sb_attn_varlen_bwd(const void* q, const void* k, const void* v, const void* r, const float* m,
                        const void* dout, float* dq, float* dk, float* dv, float* dr,
                        const int* cu_seqlens, int nseq, int H, int Hkv, int Ttot, int max_T, int d,
@@ -221,7 +234,8 @@ int sb_attn_varlen_bwd(const void* q, const void* k, const void* v, const void* 
                                               static_cast<const uint16_t*>(v), static_cast<const uint16_t*>(r), m,
                                               static_cast<const uint16_t*>(dout), dq, dk, dv, dr,
                                               static_cast<float*>(workspace), cu_seqlens, nseq, H, Hkv,
-                                              Ttot, max_T, d, static_cast<hipStream_t>(stream));
+                                              Ttot, max_T, d, static_cast<hipStream_t>(stream),
+                                              H > Hkv && workspace_bytes >= sb::bwd_varlen_gqa_workspace_bytes(nseq, H, Hkv, Ttot, max_T, d));
     return e == hipSuccess ? SB_OK : SB_ERR_LAUNCH;
 }
 

@@ -244,7 +244,13 @@ __device__ __forceinline__ void stage_tile(const uint16_t* X, const uint16_t* Y,
 // A strip's accumulators, times f, to its 32 rows from `out` on (wave-uniform), of which `rows` exist: acc[b][r] is
 // row 8*(r/4) + 4*hh + r%4, column 32b + n.  Whole strips without a test per element: 64 tests with their
 // addresses, reloaded from scratch each, took as long as the stores (bwd_dkv_pair_kernel, see there).
-template <int D>
+// With SHARED for other workgroups of the launch, on any XCD, to read.
+template <bool SHARED> __device__ __forceinline__ void store_float(float* p, float x)
+{
+    if constexpr (SHARED) __hip_atomic_store(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    else *p = x;
+}
+template <int D, bool SHARED = false>
 __device__ __forceinline__ void store_strip(float* out, int rows, const f32x16 (&acc)[D / 32], float f, int n, int hh)
 {
     float* const o = reinterpret_cast<float*>(scalar_base(out));
@@ -253,14 +259,14 @@ __device__ __forceinline__ void store_strip(float* out, int rows, const f32x16 (
 #pragma unroll
         for (int r = 0; r < 16; ++r)
 #pragma unroll
-            for (int b = 0; b < D / 32; ++b) o[(8 * (r >> 2) + (r & 3)) * D + 32 * b + at] = acc[b][r] * f;
+            for (int b = 0; b < D / 32; ++b) store_float<SHARED>(&o[(8 * (r >> 2) + (r & 3)) * D + 32 * b + at], acc[b][r] * f);
         return;
     }
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
         if (8 * (r >> 2) + 4 * hh + (r & 3) < rows)
 #pragma unroll
-            for (int b = 0; b < D / 32; ++b) o[(8 * (r >> 2) + (r & 3)) * D + 32 * b + at] = acc[b][r] * f;
+            for (int b = 0; b < D / 32; ++b) store_float<SHARED>(&o[(8 * (r >> 2) + (r & 3)) * D + 32 * b + at], acc[b][r] * f);
     }
 }
 
@@ -370,7 +376,7 @@ bwd_dq_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
               const uint16_t* __restrict__ dout, float* __restrict__ dq,
               float* __restrict__ ca, float* __restrict__ cb, uint16_t* __restrict__ first,
               int T_arg, int BH, int H, int G, int nqb_arg, int nt32, const int* __restrict__ cu, int Ttot,
-              int run, BiasGrad bias, int first_wg)
+              int run, BiasGrad bias, int* __restrict__ arrived, int first_wg)      // arrived: of the key-stationary pass's parts, or null
 {
     using C = StageCfg<D>;
     __shared__ __attribute__((aligned(1024))) char smem[2 * C::STAGE];
@@ -592,6 +598,7 @@ bwd_dq_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
 
     const int qb = nqb - 1 - sh.i;
     const int Q0 = qb * BQ;
+    if (arrived && head % G == 0 && tid < 4 && 4 * qb + tid < nt32) arrived[(long)(bh / G) * nt32 + 4 * qb + tid] = 0;
     q0 = Q0 + wave * 32;
     const bool wave_live = q0 < T;
     const int jq = min(q0 + n, T - 1);
@@ -759,6 +766,86 @@ __device__ __forceinline__ void kv_head_of(KvHead& kh, const Share& sh, const Pl
     else kv_head(kh, sh.bh, D, T_arg, nkb_arg, G, nt32);
 }
 
+// Key-stationary pass of grouped heads in parts: a block of keys is n workgroups', each with G / n of the group's query heads, if the
+// block's weights reach far; else the first one takes all of them and the others have nothing to do.  Every part leaves its sums in `sums`: dV's
+// of all heads, then dK's, laid out as dv and dk are with n kv heads in place of one; behind them a count for every kv head and strip of 32 keys of the
+// parts that have come, cleared by the query-stationary pass.  The last of a block's adds them up, in their order whichever it is.
+// Without parts a far group's heads are one chain, and what the launch waits for: figures beside parts_of().
+// The sums pass from XCD to XCD: stored past the caches, a wait for them, one count a workgroup, loaded past the caches.  (With fences in their place, which
+// write a whole L2 back for every workgroup, B4 H12 Hkv4 T2048 d128, a third of the heads far, 215 -> 304 us instead of 188.)
+struct Parts {
+    float* sums;
+    int n, beyond, blocks;                  // parts, see in_parts(), workgroups of a part
+};
+// The sums of kv head `kv` in part 0: where element x of dk and dv is, and the counts.  rows: of a kv head (of a packed batch all)
+template <int D> struct PartSums {
+    float *dv, *dk;
+    int* arrived;
+    long step;                              // from part to part
+    __device__ __forceinline__ PartSums(const Parts& parts, int kv, int heads, long rows)
+    {
+        const long all = heads * rows * D * parts.n;
+        step = rows * D;
+        dv = parts.sums + kv * (parts.n - 1) * step;
+        dk = dv + all;
+        arrived = reinterpret_cast<int*>(parts.sums + 2 * all);
+    }
+};
+// The part that workgroup `wg` takes of the block of the workgroup of that number in one part; the first part's come last, behind those that have nothing to do
+__device__ __forceinline__ int take_part(int& wg, const Parts& parts)
+{
+    int part = parts.n - 1;
+    for (; part > 0 && wg >= parts.blocks; --part) wg -= parts.blocks;
+    return part;
+}
+// Of a block whose first 32-key strip is `lo`: do the queries `beyond` strips further on still attend to it, in any head of the group?
+__device__ __forceinline__ bool in_parts(const Parts& parts, const uint16_t* __restrict__ first, long qhead0, int G, int nqb, int lo, int T, int lane)
+{
+    if (parts.beyond == 0) return true;
+    const int at = lo + parts.beyond;
+    if (32 * at >= T) return false;
+    const int f = lane < G ? first[(qhead0 + lane) * nqb * 4 + at] : 0x7fffffff;
+    return __builtin_amdgcn_ballot_w64(f <= lo) != 0;
+}
+typedef __attribute__((ext_vector_type(2))) unsigned long long u64x2;
+__device__ __forceinline__ f32x4 load_shared4(const float* p)
+{
+    const auto* q = reinterpret_cast<const unsigned long long*>(p);
+    return __builtin_bit_cast(f32x4, u64x2{__hip_atomic_load(q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT),
+                                           __hip_atomic_load(q + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)});
+}
+__device__ __forceinline__ void store_shared4(float* p, f32x4 x)
+{
+    const u64x2 v = __builtin_bit_cast(u64x2, x);
+    auto* q = reinterpret_cast<unsigned long long*>(p);
+    __hip_atomic_store(q, v[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(q + 1, v[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// The workgroup's sums of `rows` rows from element `at` of dk and dv on have been stored; count: the block's in `arrived`
+template <int D, int NTHR>
+__device__ __forceinline__ void add_parts(const PartSums<D>& sums, int n, char* smem, long at, long count, int rows, float* __restrict__ dk,
+                                          float* __restrict__ dv, float scale, int tid)
+{
+    int* const last = reinterpret_cast<int*>(smem);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (tid == 0) *last = __hip_atomic_fetch_add(&sums.arrived[count], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == n - 1;
+    __syncthreads();
+    if (!*last) return;
+#pragma unroll 1
+    for (int mat = 0; mat < 2; ++mat) {
+        const float* const s = (mat == 0 ? sums.dv : sums.dk) + at;
+        float* const out = (mat == 0 ? dv : dk) + at;
+        const float f = mat == 0 ? 1.0f : scale;
+        for (int i = tid; i < rows * (D / 4); i += NTHR) {
+            f32x4 x = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll 4
+            for (int p = 0; p < n; ++p) x += load_shared4(s + p * sums.step + 4 * i);
+            *reinterpret_cast<f32x4*>(out + 4 * i) = x * f;
+        }
+    }
+}
+
 // Which query tiles reach the 32-key strips lo .. hi, a block's, from the start strips that the
 // query-stationary pass left: f[jt] holds those of tile jt's two strips of queries.  None from tile `end` on;
 // in all tiles before `sure` both strips reach every one of the keys.  In between strip u of a tile
@@ -816,22 +903,23 @@ template <int D, int SP> struct DkvCfg {
     static_assert(SP == 1 || NW * 2 * 32 * D * 4 <= LDS_BYTES, "the second group's accumulators fit");
 };
 
-template <int D, bool GQA, Packed VL, int SP, bool DR>
-__global__ void __launch_bounds__(SP * NTHREADS, 2)
+template <int D, bool GQA, Packed VL, int SP, bool DR, bool PARTS>
+__global__ void __launch_bounds__(SP * NTHREADS, D == 32 && SP == 1 ? 3 : 2)
 bwd_dkv_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
                const uint16_t* __restrict__ v, const uint16_t* __restrict__ dout,
                const float* __restrict__ ca, const float* __restrict__ cb,
                float* __restrict__ dk, float* __restrict__ dv, const uint32_t* __restrict__ first,
                int T_arg, int BH, int H, int G_arg, int nkb_arg, int nt32, const int* __restrict__ cu, int Ttot,
-               int run, BiasGrad bias, int first_wg)
+               int run, BiasGrad bias, Parts parts, int first_wg)
 {
     using C = StageCfg<D>;
     using CK = DkvCfg<D, SP>;
     const int G = GQA ? G_arg : 1;                      // query heads per kv head
+    static_assert(GQA || !PARTS, "a part has some of a group's query heads");
     __shared__ __attribute__((aligned(1024))) char smem[CK::LDS_BYTES];
 
     asm volatile("" :: "s"(q), "s"(k), "s"(v), "s"(dout), "s"(ca), "s"(cb), "s"(first), "s"(T_arg));   // as in bwd_dq_kernel
-    const int wg = first_wg + blockIdx.x;
+    int wg = first_wg + blockIdx.x;
     if constexpr (DR) {
         if (wg >= bias.work) {
             bias_sum<D, SP * NTHREADS>(reinterpret_cast<float*>(smem), bias, wg - bias.work, threadIdx.x);
@@ -839,6 +927,8 @@ bwd_dkv_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
         }
     }
     Place at;
+    int part = 0;
+    if constexpr (PARTS) part = take_part(wg, parts);
     const Share sh = kv_block<VL, false, BKW>(at, wg, BH, run, T_arg, nkb_arg, H / G, cu, Ttot);
     if (sh.i < 0) return;
 
@@ -853,6 +943,16 @@ bwd_dkv_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     KvHead kh;
     kv_head_of<D, VL, BKW>(kh, sh, at, T_arg, nkb_arg, H, G, nt32, Ttot);
     const int T = kh.T, nkb = kh.nkb;
+    int g0 = 0, g1 = G;                                 // the workgroup's query heads
+    bool alone = true;
+    if constexpr (PARTS) {
+        alone = !in_parts(parts, reinterpret_cast<const uint16_t*>(first), kh.qhead0, G, nkb_arg, sh.i * (BKW / 32), T, lane);
+        if (alone && part > 0) return;
+        if (!alone) {
+            g0 = part * (G / parts.n);
+            g1 = g0 + G / parts.n;
+        }
+    }
     const long base = kh.base, qrow0 = kh.qrow0, qrow_step = kh.qrow_step;
     const long cbase = kh.cbase, cbase_step = kh.cbase_step, cstride = kh.cstride;
     const uint16_t* Qg = nullptr;
@@ -1011,7 +1111,7 @@ bwd_dkv_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
         load_carries(cn, jt0 + grp, wave_live);
         if (SP == 1 || (jt0 + grp) * TK < T) stage_tile<D, false>(Qg, Gg, jt0 + grp, T, tiles, goff, wave, lane);
     };
-    first_tile(0);                                       // fetched together with the stationary rows
+    first_tile(g0);                                      // fetched together with the stationary rows
     {
         const long kr = min(k0 + perm_row(n), T - 1);
         const u32x4* ks = reinterpret_cast<const u32x4*>(k + base + kr * D + 8 * hh);
@@ -1030,8 +1130,8 @@ bwd_dkv_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
 #pragma unroll
         for (int r = 0; r < 16; ++r) { dkacc[b][r] = 0.0f; dvacc[b][r] = 0.0f; }
     // the query heads of the group one after the other, into the same accumulators
-    for (int g = 0; g < G; ++g) {
-    if (g > 0) {
+    for (int g = g0; g < g1; ++g) {
+    if (g > g0) {
         barrier_nofence();                               // everyone is done with the stages of the head before
         first_tile(g);
     }
@@ -1114,6 +1214,15 @@ bwd_dkv_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
         }
     }
 
+    if (PARTS && !alone) {
+        const PartSums<D> sums(parts, sh.bh, VL != Packed::NO ? H / G : BH, VL != Packed::NO ? Ttot : T_arg);
+        if (wave_live) {
+            store_strip<D, true>(sums.dk + part * sums.step + base + (long)k0 * D, T - k0, dkacc, 1.0f, n, hh);
+            store_strip<D, true>(sums.dv + part * sums.step + base + (long)k0 * D, T - k0, dvacc, 1.0f, n, hh);
+        }
+        add_parts<D, NTHREADS>(sums, parts.n, smem, base + (long)K0 * D, kh.qhead0 / G * nt32 + (K0 >> 5), min(T - K0, BKW), dk, dv, scale, tid);
+        return;
+    }
     if (wave_live) {
         store_strip<D>(dk + base + (long)k0 * D, T - k0, dkacc, scale, n, hh);
         store_strip<D>(dv + base + (long)k0 * D, T - k0, dvacc, 1.0f, n, hh);
@@ -1160,23 +1269,24 @@ template <int D, int KS> struct Dkv3Cfg {
     static constexpr int NPW = (LOADS + NW2 - 1) / NW2;
 };
 
-template <int D, int KS, bool GQA, Packed VL, bool PAIRS, bool DR>
+template <int D, int KS, bool GQA, Packed VL, bool PAIRS, bool DR, bool PARTS>
 __global__ void __launch_bounds__(128 * KS, 1)
 bwd_dkv_pair_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
                     const uint16_t* __restrict__ v, const uint16_t* __restrict__ dout,
                     const float* __restrict__ ca, const float* __restrict__ cb,
                     float* __restrict__ dk, float* __restrict__ dv, const uint32_t* __restrict__ first,
                     int T_arg, int BH, int H, int G_arg, int nkb_arg, int nqb_arg, int nt32,
-                    const int* __restrict__ cu, int Ttot, BiasGrad bias, int first_wg)
+                    const int* __restrict__ cu, int Ttot, BiasGrad bias, Parts parts, int first_wg)
 {
     using C = StageCfg<D>;
     using CK = Dkv3Cfg<D, KS>;
     constexpr int NW2 = CK::NW2;
     static_assert(CK::LDS_BYTES <= 160 * 1024, "LDS budget");
     const int G = GQA ? G_arg : 1;                      // query heads per kv head
+    static_assert(GQA || !PARTS, "a part has some of a group's query heads");
     __shared__ __attribute__((aligned(1024))) char smem[CK::LDS_BYTES];
 
-    const int wg = first_wg + blockIdx.x;
+    int wg = first_wg + blockIdx.x;
     if constexpr (DR) {
         if (wg >= bias.work) {
             bias_sum<D, 64 * NW2>(reinterpret_cast<float*>(smem), bias, wg - bias.work, threadIdx.x);
@@ -1184,6 +1294,8 @@ bwd_dkv_pair_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
         }
     }
     Place at;
+    int part_of = 0;
+    if constexpr (PARTS) part_of = take_part(wg, parts);
     const Share sh = kv_block<VL, PAIRS, CK::KEYS>(at, wg, BH, -1, T_arg, nkb_arg, H / G, cu, Ttot);
     if (sh.i < 0) return;
 
@@ -1198,6 +1310,16 @@ bwd_dkv_pair_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
     KvHead kh;
     kv_head_of<D, VL, CK::KEYS>(kh, sh, at, T_arg, nkb_arg, H, G, nt32, Ttot);
     const int T = kh.T, nkb = kh.nkb;
+    int g0 = 0, g1 = G;                                 // the workgroup's query heads
+    bool alone = true;
+    if constexpr (PARTS) {
+        alone = !in_parts(parts, reinterpret_cast<const uint16_t*>(first), kh.qhead0, G, nqb_arg, sh.i * KS, T, lane);
+        if (alone && part_of > 0) return;
+        if (!alone) {
+            g0 = part_of * (G / parts.n);
+            g1 = g0 + G / parts.n;
+        }
+    }
     const long base = kh.base, qrow0 = kh.qrow0, qrow_step = kh.qrow_step;
     const long cbase = kh.cbase, cbase_step = kh.cbase_step, cstride = kh.cstride;
     const uint16_t* Qg = nullptr;
@@ -1415,7 +1537,7 @@ bwd_dkv_pair_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
     auto begin = [&](int kb, int b, int p) __attribute__((always_inline)) {
         buf0 = b;
         vhalf = p;
-        first_tile(0, kb, b);
+        first_tile(g0, kb, b);
         constexpr int KLOADS = CK::KEYS * C::ROW / 1024 / NW2;
         const int K0 = kb * CK::KEYS;
         char* const kp = smem + (b == 2 ? 0 : b + 1) * C::STAGE;
@@ -1456,8 +1578,8 @@ bwd_dkv_pair_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
             for (int r = 0; r < 16; ++r) acc[b][r] = 0.0f;
 
         // the query heads of the group one after the other, into the same accumulators
-        for (int g = 0; g < G; ++g) {
-        if (g > 0) {
+        for (int g = g0; g < g1; ++g) {
+        if (g > g0) {
             dma_wait<0>();                                   // the steady state's last staging, read by nobody
             barrier_lds();                                   // everyone is done with the LDS of the head before
             first_tile(g, kb, buf0);
@@ -1530,7 +1652,7 @@ bwd_dkv_pair_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
                 load_carries(jt, live);
                 word_next = start_word(fg, jt, reach.sure);
                 stage(jt, smem + bnext * C::STAGE);
-            } else if (it == ntile && more && g == G - 1) {
+            } else if (it == ntile && more && g == g1 - 1) {
                 begin(nkb - 1 - kb, bcur, it & 1);
             }
             const int jbase = (jt0 + it) * TK;
@@ -1558,6 +1680,12 @@ bwd_dkv_pair_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
         }
         }
 
+        if (PARTS && !alone) {
+            const PartSums<D> sums(parts, sh.bh, VL != Packed::NO ? H / G : BH, VL != Packed::NO ? Ttot : T_arg);
+            if (live) store_strip<D, true>((role == 0 ? sums.dv : sums.dk) + part_of * sums.step + base + (long)k0 * D, T - k0, acc, 1.0f, n, hh);
+            add_parts<D, 64 * NW2>(sums, parts.n, smem, base + (long)K0 * D, kh.qhead0 / G * nt32 + (K0 >> 5), min(T - K0, CK::KEYS), dk, dv, scale, tid);
+            return;
+        }
         if (live) store_strip<D>((role == 0 ? dv : dk) + base + (long)k0 * D, T - k0, acc, role == 0 ? 1.0f : scale, n, hh);
         if (!more) break;
     }
@@ -1645,7 +1773,7 @@ bwd_dq_small_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
                     const uint16_t* __restrict__ dout, float* __restrict__ dq,
                     float* __restrict__ ca, float* __restrict__ cb, uint16_t* __restrict__ first,
                     int T_arg, int BH, int H, int G, int n_arg, int nqb_arg, int nt32,       // n_arg: strips a head; packed batch: sequences
-                    const int* __restrict__ cu, int Ttot, BiasGrad bias)
+                    const int* __restrict__ cu, int Ttot, BiasGrad bias, int* __restrict__ arrived)
 {
     using C = SmallCfg<D, NWS>;
     constexpr int NTHR = 64 * NWS;
@@ -1803,7 +1931,10 @@ bwd_dq_small_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
         barrier_lds();                                   // the carries are there
     }
     // (where this pass takes strips the key-stationary one does too, so that nobody reads the places of strips that do not exist)
-    if (tid == 0) first[(long)bh * nqb_arg * 4 + strip] = (uint16_t)start;
+    if (tid == 0) {
+        first[(long)bh * nqb_arg * 4 + strip] = (uint16_t)start;
+        if (arrived && head % G == 0) arrived[(long)(bh / G) * nt32 + strip] = 0;
+    }
 
     // ---- the sweep
     f32x16 dqacc[D / 32];
@@ -1905,14 +2036,14 @@ bwd_dq_small_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
 
 // Key-stationary pass: a strip of 32 keys a workgroup, whose waves take its query subtiles (of all
 // query heads of the group) in turn and add their accumulators up at the end.
-template <int D, bool DR, int NWS>
+template <int D, bool DR, int NWS, bool PARTS>
 __global__ void __launch_bounds__(64 * NWS, D == 32 && NWS == 4 ? 3 : 1)        // (three workgroups a CU: left alone it takes registers for two)
 bwd_dkv_small_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
                      const uint16_t* __restrict__ v, const uint16_t* __restrict__ dout,
                      const float* __restrict__ ca, const float* __restrict__ cb,
                      float* __restrict__ dk, float* __restrict__ dv, const uint16_t* __restrict__ first,
-                     int T_arg, int BH, int H, int G, int n_arg, int nqb_arg, int nt32,       // n_arg: strips a head; packed batch: sequences
-                     const int* __restrict__ cu, int Ttot, bool strips_q, BiasGrad bias)       // strips_q: the carries are bwd_dq_small_kernel's
+                     int T_arg, int BH, int H, int G_arg, int n_arg, int nqb_arg, int nt32,       // n_arg: strips a head; packed batch: sequences
+                     const int* __restrict__ cu, int Ttot, bool strips_q, BiasGrad bias, Parts parts)       // strips_q: the carries are bwd_dq_small_kernel's
 {
     using C = SmallCfg<D, NWS>;
     constexpr int NTHR = 64 * NWS;
@@ -1927,16 +2058,19 @@ bwd_dkv_small_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict_
         bias_sum<D, NTHR>(reinterpret_cast<float*>(smem), bias, blockIdx.x - bias.work, tid);
         return;
     }
-    const Share sh = in_scalars(share_of(blockIdx.x, BH, -1));
+    int wg = blockIdx.x;
+    int part = 0;
+    if constexpr (PARTS) part = take_part(wg, parts);
+    const Share sh = in_scalars(share_of(wg, BH, -1));
     KvHead kh;
     int ks = sh.i;                                       // the strip; small ones have the most queries
     if (cu) {                                            // packed batch: sh.bh is the head alone, sh.i its place
         const Place at = place_of<32>(sh.i, cu, n_arg, Ttot, T_arg, lane);
         if (at.T == 0) return;
-        packed_kv_head<D>(kh, at, sh.bh, 32, H, G, nt32, Ttot);
+        packed_kv_head<D>(kh, at, sh.bh, 32, H, G_arg, nt32, Ttot);
         ks = at.i;
     } else {
-        kv_head(kh, sh.bh, D, T_arg, n_arg, G, nt32);
+        kv_head(kh, sh.bh, D, T_arg, n_arg, G_arg, nt32);
     }
     const int T = kh.T, nstrip = kh.nkb;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1951,10 +2085,23 @@ bwd_dkv_small_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict_
     // With a word for each head, a memory latency each, B2 H8 Hkv2 T90 d32 6.6 us in place of 5.7, B8 H32 Hkv4 T800 51 in place of 47, near 44 in place of 39.)
     constexpr unsigned long long EVERY = NWS == 8 ? 0x0101010101010101ull : 0x1111111111111111ull;
     static_assert(NWS == 4 || NWS == 8, "strips of a wave");
+    bool alone = true;
+    int G = G_arg;
+    long qhead0 = kh.qhead0;
+    if constexpr (PARTS) {
+        alone = !in_parts(parts, first, kh.qhead0, G_arg, nqb_arg, ks, T, lane);
+        if (alone && part > 0) return;
+        if (!alone) {                                    // the part's heads are the strip's
+            G /= parts.n;
+            qhead0 += part * G;
+            kh.qrow0 += part * G * kh.qrow_step;
+            kh.cbase += part * G * kh.cbase_step;
+        }
+    }
     const int all = G * nq;
     int w0 = 0, wn = 0, g = 0, x0 = 0;                   // first strip of this word, and of the next one; head, and where its strips begin
     unsigned long long todo = 0;
-    const uint16_t* const fg = first + kh.qhead0 * nqb_arg * 4 + ks;
+    const uint16_t* const fg = first + qhead0 * nqb_arg * 4 + ks;
     auto word = [&](int x) __attribute__((always_inline)) {
         int head = 0, i = x;
         if (G > 1) {                                     // (from a quotient good to less than one)
@@ -2141,6 +2288,7 @@ bwd_dkv_small_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict_
             red[NWS * 32 * D + at] = dkacc[b][r];
         }
     barrier_lds();
+    const PartSums<D> sums(parts, sh.bh, cu ? H / G_arg : BH, cu ? Ttot : T_arg);
 #pragma unroll
     for (int mat = 0; mat < 2; ++mat)
         for (int i = tid; i < 32 * D / 4; i += NTHR) {
@@ -2148,19 +2296,23 @@ bwd_dkv_small_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict_
             f32x4 x = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
             for (int w = 0; w < NWS; ++w) x += *reinterpret_cast<const f32x4*>(&red[((mat * NWS + w) * 32 + row) * D + c]);
-            if (k0 + row < T) *reinterpret_cast<f32x4*>((mat == 0 ? dv : dk) + kh.base + (long)(k0 + row) * D + c) = mat == 0 ? x : x * scale;
+            if (k0 + row >= T) continue;
+            if (!PARTS || alone) *reinterpret_cast<f32x4*>((mat == 0 ? dv : dk) + kh.base + (long)(k0 + row) * D + c) = mat == 0 ? x : x * scale;
+            else store_shared4((mat == 0 ? sums.dv : sums.dk) + part * sums.step + kh.base + (long)(k0 + row) * D + c, x);
         }
+    if (PARTS && !alone) add_parts<D, NTHR>(sums, parts.n, smem, kh.base + (long)k0 * D, kh.qhead0 / G_arg * nt32 + ks, min(T - k0, 32), dk, dv, scale, tid);
 }
 
 // workspace layout: ca[BH][nt32][T], cb[BH][nt32][T] (fp32; [H][nt32][Ttot] for a packed
 // batch), then the start strips of the queries' 32-row strips (16 bits): [BH][nqb][4], then the
-// partial sums of the remainder-bias gradient (fp32): [BH][nchunk][D], [H][nchunk][D] for a packed batch.  B, T: batch size and
+// partial sums of the remainder-bias gradient (fp32): [BH][nchunk][D], [H][nchunk][D] for a packed batch; then, 16-byte aligned, where there is
+// `room` for them, what Parts says.  B, T: batch size and
 // length, or for a packed batch the number of sequences and the longest length.
 template <int D, Packed PK>
 hipError_t launch_one(const uint16_t* q, const uint16_t* k, const uint16_t* v, const uint16_t* rb,
                       const float* m, const uint16_t* dout, float* dq, float* dk, float* dv,
                       float* drb, float* workspace, int B, int H, int Hkv, int T, int passes, hipStream_t stream,
-                      const int* cu, int Ttot)
+                      const int* cu, int Ttot, bool room)
 {
     constexpr bool VL = PK != Packed::NO;
     const int BH = B * H;
@@ -2178,7 +2330,22 @@ hipError_t launch_one(const uint16_t* q, const uint16_t* k, const uint16_t* v, c
     float* part = reinterpret_cast<float*>(first + (long)BH * nqb * 4);
     const int entries = VL ? 1 : B;                      // of the bias's gradient
     const int nchunk = bias_chunks(B, T, VL, Ttot);
-    const Keys keys = keys_of(B, H, Hkv, T, D, VL, Ttot);
+    Keys keys = keys_of(B, H, Hkv, T, D, VL, Ttot);
+    Parts parts = {nullptr, 1, 8, 0};
+    int* arrived = nullptr;
+    if (room) {
+        const KeyPlan plan = key_plan(B, H, Hkv, T, D, VL, Ttot);
+        keys = plan.keys;
+        parts.n = plan.parts;
+        parts.beyond = plan.beyond;
+        if (parts.n > 1) {
+            const size_t base = VL ? bwd_varlen_workspace_bytes(B, H, Ttot, T, D) : bwd_workspace_bytes(B, H, T, D);
+            parts.sums = reinterpret_cast<float*>(reinterpret_cast<char*>(workspace) + (base + 15) / 16 * 16);
+            parts.blocks = (int)(keys == Keys::STRIPS ? pieces(B, Hkv, T, 32, VL, Ttot) : block_grid(B, Hkv, T, BKW, PK, Ttot));
+            arrived = reinterpret_cast<int*>(parts.sums + 2 * parts.n * (VL ? (long)Hkv * Ttot : (long)BHkv * T) * D);
+        }
+    }
+    const int NP = parts.n;
     const int mean = mean_T(B, T, VL, Ttot);
     const long gq = block_grid(B, H, T, BQ, PK, Ttot), gk64 = block_grid(B, Hkv, T, 64, PK, Ttot);
     const long gk = keys == Keys::PAIRS ? share_grid(BHkv, nkb, true) : block_grid(B, Hkv, T, BKW, PK, Ttot);
@@ -2188,7 +2355,7 @@ hipError_t launch_one(const uint16_t* q, const uint16_t* k, const uint16_t* v, c
     // checked before the first launch, so that an error leaves nothing enqueued
     // workgroups of the bias's gradient behind those of the passes
     const long bias_q = drb ? (long)nchunk * entries * H : 0, bias_k = drb ? H : 0;
-    if (gq + bias_q > 0x7fffffffL || gk + bias_k > 0x7fffffffL) return hipErrorInvalidValue;
+    if (gq + bias_q > 0x7fffffffL || gk * NP + bias_k > 0x7fffffffL) return hipErrorInvalidValue;
     auto bias = [&](long work) { return BiasGrad{part, drb, (int)work, entries, H, nchunk}; };
     hipError_t e = hipSuccess;
 #define SB_LAUNCH(WGS, THREADS, KERNEL, ...)                                                                    \
@@ -2203,57 +2370,59 @@ hipError_t launch_one(const uint16_t* q, const uint16_t* k, const uint16_t* v, c
         auto go = [&](auto waves) {                                                                             \
             constexpr int NW = decltype(waves)::value;                                                          \
             hipLaunchKernelGGL((bwd_dq_small_kernel<D, RBV, NW>), dim3((unsigned)(strips_q + bias_q)), dim3(64 * NW), 0, stream, \
-                               q, k, v, rb, m, dout, dq, ca, cb, first, T, VL ? H : BH, H, G, VL ? B : nt32, nqb, nt32, cu, Ttot, bias(strips_q)); \
+                               q, k, v, rb, m, dout, dq, ca, cb, first, T, VL ? H : BH, H, G, VL ? B : nt32, nqb, nt32, cu, Ttot, bias(strips_q), arrived); \
         };                                                                                                      \
         if (four_waves(strips_q, 1, mean, D)) go(std::integral_constant<int, 4>());                                      \
         else go(std::integral_constant<int, SmallCfg<D>::NWS>());                                               \
         if ((e = hipGetLastError()) != hipSuccess) return e;                                                    \
     } else SB_LAUNCH(gq + bias_q, NTHREADS, (bwd_dq_kernel<D, RBV, PK>),                                        \
-              q, k, v, rb, m, dout, dq, ca, cb, first, T, VL ? B : BH, H, G, nqb, nt32, cu, Ttot, run_q, bias(gq))
+              q, k, v, rb, m, dout, dq, ca, cb, first, T, VL ? B : BH, H, G, nqb, nt32, cu, Ttot, run_q, bias(gq), arrived)
 // d = 128 takes the paired-wave kernel (two waves per SIMD instead of one); smaller head
 // dimensions leave room for two workgroups of the one-wave-per-strip kernel per CU, which
 // is faster there (measured).
-#define SB_DKV(GQAV, DRV)                                                                                       \
+#define SB_DKV(GQAV, DRV, PARTS)                                                                                       \
     if (keys == Keys::STRIPS) {                                                                                 \
         auto go = [&](auto waves) {                                                                             \
             constexpr int NW = decltype(waves)::value;                                                          \
-            hipLaunchKernelGGL((bwd_dkv_small_kernel<D, DRV, NW>), dim3((unsigned)(strips_k + bias_k)), dim3(64 * NW), 0, stream, \
+            hipLaunchKernelGGL((bwd_dkv_small_kernel<D, DRV, NW, PARTS>), dim3((unsigned)(strips_k * NP + bias_k)), dim3(64 * NW), 0, stream, \
                                q, k, v, dout, ca, cb, dk, dv, first, T, VL ? Hkv : BHkv, H, G, VL ? B : nt32, nqb, nt32, cu, Ttot, \
-                               query_strips(B, H, T, D, VL, Ttot), bias(strips_k));                             \
+                               query_strips(B, H, T, D, VL, Ttot), bias(strips_k * NP), parts);                             \
         };                                                                                                      \
         if (four_waves(strips_k, G, mean, D)) go(std::integral_constant<int, 4>());                                      \
         else go(std::integral_constant<int, SmallCfg<D>::NWS>());                                               \
         if ((e = hipGetLastError()) != hipSuccess) return e;                                                    \
     } else if constexpr (D == 128) {                                                                            \
         constexpr bool CAN = !VL && !GQAV;                                                                      \
-        if (keys == Keys::KEYS_64)                                                                              \
-            SB_LAUNCH(gk64 + bias_k, 256, (bwd_dkv_pair_kernel<D, 2, GQAV, PK, false, DRV>),                    \
-                      q, k, v, dout, ca, cb, dk, dv, first2, T, shared, H, G, nkb64, nqb, nt32, cu, Ttot, bias(gk64)) \
+        if (!PARTS && keys == Keys::KEYS_64)                                                                              \
+            SB_LAUNCH(gk64 + bias_k, 256, (bwd_dkv_pair_kernel<D, 2, GQAV, PK, false, DRV, false>),                    \
+                      q, k, v, dout, ca, cb, dk, dv, first2, T, shared, H, G, nkb64, nqb, nt32, cu, Ttot, bias(gk64), parts) \
         else if (CAN && keys == Keys::PAIRS)                                                                    \
-            SB_LAUNCH(gk + bias_k, 512, (bwd_dkv_pair_kernel<D, 4, GQAV, PK, CAN, DRV>),                        \
-                      q, k, v, dout, ca, cb, dk, dv, first2, T, shared, H, G, nkb, nqb, nt32, cu, Ttot, bias(gk)) \
+            SB_LAUNCH(gk * NP + bias_k, 512, (bwd_dkv_pair_kernel<D, 4, GQAV, PK, CAN, DRV, false>),                        \
+                      q, k, v, dout, ca, cb, dk, dv, first2, T, shared, H, G, nkb, nqb, nt32, cu, Ttot, bias(gk * NP), parts) \
         else                                                                                                    \
-            SB_LAUNCH(gk + bias_k, 512, (bwd_dkv_pair_kernel<D, 4, GQAV, PK, false, DRV>),                      \
-                      q, k, v, dout, ca, cb, dk, dv, first2, T, shared, H, G, nkb, nqb, nt32, cu, Ttot, bias(gk)) \
-    } else if (keys == Keys::TWO_GROUPS) {                                                                      \
-        SB_LAUNCH(gk + bias_k, 2 * NTHREADS, (bwd_dkv_kernel<D, GQAV, PK, 2, DRV>),                             \
-                  q, k, v, dout, ca, cb, dk, dv, first2, T, shared, H, G, nkb, nt32, cu, Ttot, run_k, bias(gk)); \
+            SB_LAUNCH(gk * NP + bias_k, 512, (bwd_dkv_pair_kernel<D, 4, GQAV, PK, false, DRV, PARTS>),                      \
+                      q, k, v, dout, ca, cb, dk, dv, first2, T, shared, H, G, nkb, nqb, nt32, cu, Ttot, bias(gk * NP), parts) \
+    } else if (!PARTS && keys == Keys::TWO_GROUPS) {                                                                      \
+        SB_LAUNCH(gk * NP + bias_k, 2 * NTHREADS, (bwd_dkv_kernel<D, GQAV, PK, 2, DRV, false>),                             \
+                  q, k, v, dout, ca, cb, dk, dv, first2, T, shared, H, G, nkb, nt32, cu, Ttot, run_k, bias(gk * NP), parts); \
     } else {                                                                                                    \
-        SB_LAUNCH(gk + bias_k, NTHREADS, (bwd_dkv_kernel<D, GQAV, PK, 1, DRV>),                                 \
-                  q, k, v, dout, ca, cb, dk, dv, first2, T, shared, H, G, nkb, nt32, cu, Ttot, run_k, bias(gk)); \
+        SB_LAUNCH(gk * NP + bias_k, NTHREADS, (bwd_dkv_kernel<D, GQAV, PK, 1, DRV, PARTS>),                                 \
+                  q, k, v, dout, ca, cb, dk, dv, first2, T, shared, H, G, nkb, nt32, cu, Ttot, run_k, bias(gk * NP), parts); \
     }
     if (passes & 1) {
         if (rb) { SB_DQ(true); }
         else    { SB_DQ(false); }
     }
     if (passes & 2) {
-        // a packed batch always takes the grouped variant (a group of one included)
-        if (VL || G > 1) {
-            if (drb) { SB_DKV(true, true) }
-            else     { SB_DKV(true, false) }
-        } else if constexpr (!VL) {
-            if (drb) { SB_DKV(false, true) }
-            else     { SB_DKV(false, false) }
+        if (NP > 1) {
+            if (drb) { SB_DKV(true, true, true) }
+            else     { SB_DKV(true, false, true) }
+        } else if (G > 1) {
+            if (drb) { SB_DKV(true, true, false) }
+            else     { SB_DKV(true, false, false) }
+        } else {
+            if (drb) { SB_DKV(false, true, false) }
+            else     { SB_DKV(false, false, false) }
         }
     }
 #undef SB_LAUNCH
@@ -2272,6 +2441,26 @@ size_t bwd_workspace_bytes(int B, int H, int T, int d)
     return (2 * sizeof(float) * nt32 * T + 4 * sizeof(uint16_t) * nblk + sizeof(float) * nchunk * d) * (size_t)B * H;
 }
 
+// of Parts: the sums of all kv heads' rows, and the counts (these in any case: what is larger than the other size has room for parts)
+static size_t part_bytes(const KeyPlan& plan, size_t heads, size_t rows, int T, int d)
+{
+    return (plan.parts > 1 ? 2 * sizeof(float) * plan.parts * rows * d : 0) + sizeof(int) * heads * ((T + 31) / 32);
+}
+
+size_t bwd_gqa_workspace_bytes(int B, int H, int Hkv, int T, int d)
+{
+    const size_t base = bwd_workspace_bytes(B, H, T, d);
+    if (H == Hkv) return base;
+    return (base + 15) / 16 * 16 + part_bytes(key_plan(B, H, Hkv, T, d, false, 0), (size_t)B * Hkv, (size_t)B * Hkv * T, T, d);
+}
+
+size_t bwd_varlen_gqa_workspace_bytes(int nseq, int H, int Hkv, int Ttot, int max_T, int d)
+{
+    const size_t base = bwd_varlen_workspace_bytes(nseq, H, Ttot, max_T, d);
+    if (H == Hkv) return base;
+    return (base + 15) / 16 * 16 + part_bytes(key_plan(nseq, H, Hkv, max_T, d, true, Ttot), (size_t)nseq * Hkv, (size_t)Hkv * Ttot, max_T, d);
+}
+
 size_t bwd_varlen_workspace_bytes(int nseq, int H, int Ttot, int max_T, int d)
 {
     const size_t nt32 = (size_t)(max_T + 31) / 32;
@@ -2284,9 +2473,9 @@ size_t bwd_varlen_workspace_bytes(int nseq, int H, int Ttot, int max_T, int d)
 hipError_t launch_bwd_bf16(const uint16_t* q, const uint16_t* k, const uint16_t* v, const uint16_t* rb,
                            const float* m, const uint16_t* dout, float* dq, float* dk, float* dv,
                            float* drb, float* workspace,
-                           int B, int H, int Hkv, int T, int d, int passes, hipStream_t stream)
+                           int B, int H, int Hkv, int T, int d, int passes, hipStream_t stream, bool room)
 {
-#define SB_BWD(DD) launch_one<DD, Packed::NO>(q, k, v, rb, m, dout, dq, dk, dv, drb, workspace, B, H, Hkv, T, passes, stream, nullptr, 0)
+#define SB_BWD(DD) launch_one<DD, Packed::NO>(q, k, v, rb, m, dout, dq, dk, dv, drb, workspace, B, H, Hkv, T, passes, stream, nullptr, 0, room)
     if (d == 32) return SB_BWD(32);
     if (d == 64) return SB_BWD(64);
     return SB_BWD(128);
@@ -2296,9 +2485,9 @@ hipError_t launch_bwd_bf16(const uint16_t* q, const uint16_t* k, const uint16_t*
 hipError_t launch_bwd_bf16_varlen(const uint16_t* q, const uint16_t* k, const uint16_t* v, const uint16_t* rb,
                                   const float* m, const uint16_t* dout, float* dq, float* dk, float* dv,
                                   float* drb, float* workspace, const int* cu, int nseq, int H, int Hkv,
-                                  int Ttot, int max_T, int d, hipStream_t stream)
+                                  int Ttot, int max_T, int d, hipStream_t stream, bool room)
 {
-#define SB_BWD(DD, PK) launch_one<DD, PK>(q, k, v, rb, m, dout, dq, dk, dv, drb, workspace, nseq, H, Hkv, max_T, 3, stream, cu, Ttot)
+#define SB_BWD(DD, PK) launch_one<DD, PK>(q, k, v, rb, m, dout, dq, dk, dv, drb, workspace, nseq, H, Hkv, max_T, 3, stream, cu, Ttot, room)
     if (packed_as(nseq, max_T, Ttot) == Packed::ALIKE) {
         if (d == 32) return SB_BWD(32, Packed::ALIKE);
         if (d == 64) return SB_BWD(64, Packed::ALIKE);

@@ -51,10 +51,11 @@ hipError_t launch_fwd_bf16_halt(const uint16_t* q, const uint16_t* k, const uint
 // rb, drb: remainder-bias embeddings and their gradient, both nullptr without the bias.
 // H query heads, Hkv kv heads: k, v, dk, dv are [B][Hkv][T][d].
 size_t bwd_workspace_bytes(int B, int H, int T, int d);
+size_t bwd_gqa_workspace_bytes(int B, int H, int Hkv, int T, int d);      // with room for the key-stationary pass's parts
 hipError_t launch_bwd_bf16(const uint16_t* q, const uint16_t* k, const uint16_t* v, const uint16_t* rb,
                            const float* m, const uint16_t* dout, float* dq, float* dk, float* dv,
                            float* drb, float* workspace,
-                           int B, int H, int Hkv, int T, int d, int passes, hipStream_t stream);
+                           int B, int H, int Hkv, int T, int d, int passes, hipStream_t stream, bool room);
 
 // Packed variable-length batches: tensors [H][Ttot][d] ([Hkv][Ttot][d] for k, v, dk, dv), m
 // [H][Ttot]; cu: nseq + 1 ints on the device, cu[0] = 0 <= ... <= cu[nseq] = Ttot; max_T: an
@@ -63,10 +64,11 @@ hipError_t launch_fwd_bf16_varlen(const uint16_t* q, const uint16_t* k, const ui
                                   uint16_t* o, float* m, const int* cu, int nseq, int H, int Hkv,
                                   int Ttot, int max_T, int d, hipStream_t stream);
 size_t bwd_varlen_workspace_bytes(int nseq, int H, int Ttot, int max_T, int d);
+size_t bwd_varlen_gqa_workspace_bytes(int nseq, int H, int Hkv, int Ttot, int max_T, int d);
 hipError_t launch_bwd_bf16_varlen(const uint16_t* q, const uint16_t* k, const uint16_t* v, const uint16_t* rb,
                                   const float* m, const uint16_t* dout, float* dq, float* dk, float* dv,
                                   float* drb, float* workspace, const int* cu, int nseq, int H, int Hkv,
-                                  int Ttot, int max_T, int d, hipStream_t stream);
+                                  int Ttot, int max_T, int d, hipStream_t stream, bool room);
 
 // Single-token decode: q, o [B][H][d], k, v [B][Hkv][Tcap][d] of which the first T rows are
 // valid, m [B][H] or nullptr, rb [H][d] or nullptr; workspace: decode_workspace_bytes bytes.

@@ -326,6 +326,61 @@ inline Keys keys_of(int B, int H, int Hkv, int T, int d, bool packed, int Ttot)
     return !packed && H == Hkv && take_pairs(heads, nkb) ? Keys::PAIRS : Keys::KEYS_128;
 }
 
+// The key-stationary pass of grouped heads where the workspace has room for parts (Parts in sb_bwd_bf16.hip): the query heads of a block of keys
+// over `parts` workgroups, if the queries `beyond` strips further on attend to it (0: in any case).
+// One block's G heads are one chain, and where some kv heads reach far their blocks' chains are what the launch waits for; splitting them costs a part's
+// K, V and sums (4 to 5 us of a launch), and where nothing is far the parts that have nothing to do (2 to 5 us).
+// Whole backward in one part with the kernel that keys_of() names / as here, us, all heads far, then a third, then none:
+//   strips, in any case    few of them, of 3.5 rounds and more a part: d = 128 B1 H12 Hkv3 T462 (45 strips) 44 / 32, 44 / 31, 31 / 27;  B1 H8 Hkv1 T1059 (34) 153 / 73,
+//            65 / 42, 65 / 42;  packed H8 Hkv1, 9 up to 211 (32) 43 / 31 in all three;  d = 32 B2 H8 Hkv1 T535 (34) 34 / 20, 22.5 / 17.3, 22.5 / 17.2;  not
+//            d = 128 B2 H6 Hkv2 T333 (44) 32 / 31, 27 / 29;  B7 H6 Hkv2 T95 (42) 18 / 24
+//   strips, if far         d = 128 B1 H24 Hkv3 T2836 (267) 414 / 318, 388 / 217, 86 / 89;  packed H8 Hkv1, 9 up to 2904 (187) 398 / 263, 78 / 79;  d = 64 B1 H4 Hkv1 T5564 (174)
+//            204 / 143, 33 / 35;  d = 32 packed H24 Hkv3, 26 up to 2961 (2268) 864 / 646, 748 / 337, 225 / 181;  B1 H24 Hkv6 T2572 (486) 124 / 134, 115 / 98, 34 / 38;  at worst
+//            B2 H16 Hkv2 T2539 (320) 172 / 160, 49 / 53
+//   blocks                 d = 128 B4 H12 Hkv4 T2048 (256 blocks) 310 / 267, 213 / 187, 119 / 114;  packed H12 Hkv6, 8 up to 4441 (430) 462 / 407, 402 / 301, 124 / 128;  packed H20
+//            Hkv5, 18 up to 1746 334 / 302, 287 / 205, 181 / 182;  not B16 H32 Hkv4 T1024 (512, of four parts) 740 / 806, 558 / 604, 443 / 458;  B8 H16 Hkv4 T4096 (1024, of two)
+//            2287 / 2372, 997 / 1019, 445 / 449
+//            d = 64 packed H24 Hkv8, 25 up to 2146 (850) 404 / 398, 299 / 218, 165 / 164;  packed H24 Hkv3, 28 up to 3544 (640) 1313 / 1035, 1088 / 547, 321 / 310;  B3 H9 Hkv3
+//            T7789 (549) 1236 / 1175, 946 / 580, 128 / 127;  B4 H32 Hkv8 T3000 (768) 858 / 856, 570 / 380, 187 / 186;  not packed H28 Hkv14, 41 up to 2437 (2280)
+//            582 / 648, 353 / 396, 267 / 292
+//            d = 32 B2 H18 Hkv9 T5580 (792) 595 / 589, 499 / 380, 87 / 88
+// Strips in one part where that rule, made for batches of one length, takes blocks, packed ones going by their mean: packed, d = 32 H27 Hkv9, 6 up to 1681 (954) 148 / 90,
+// 147 / 75, 52 / 47;  H15 Hkv5, 19 up to 1222 (1150) 114 / 78, 113 / 72, 59 / 54;  H8 Hkv4, 28 up to 1408 (1288) 97 / 70, 97 / 66, 49 / 38;  H20 Hkv10, 20 up to 3075 (4920) 372 / 356,
+// 251 / 201, 116 / 108;  d = 64 H28 Hkv14, 17 up to 522 (1722) 78 / 69, 75 / 67, 67 / 65;  d = 128 H28 Hkv7, 8 up to 788 (728) 157 / 123, 141 / 115, 131 / 100;  not H18 Hkv9,
+// 17 up to 472 (1143) 90 / 95 in all three;  of one length, d = 128 B11 H6 Hkv3 T364 (396) 51 / 45 in all three
+struct KeyPlan {
+    Keys keys;
+    int parts, beyond;
+};
+inline KeyPlan key_plan(int B, int H, int Hkv, int T, int d, bool packed, int Ttot)
+{
+    const int G = H / Hkv, mean = mean_T(B, T, packed, Ttot), nq = (T + 31) / 32, waves = d == 128 ? 4 : 8;
+    const long strips = pieces(B, Hkv, T, 32, packed, Ttot), blocks = pieces(B, Hkv, T, 128, packed, Ttot);
+    KeyPlan p = {keys_of(B, H, Hkv, T, d, packed, Ttot), 1, 8};
+    if (G == 1) return p;
+    auto most = [&](auto fits) {
+        int n = 1;
+        for (int x = 2; x <= std::min(G, 8); ++x)
+            if (G % x == 0 && fits((long)x)) n = x;
+        return n;
+    };
+    const bool more = T > 64 && mean > 64 && T <= LONG_T && (d == 128 ? strips <= 768 : packed && packed_as(B, T, Ttot) == Packed::BY_LENGTH && strips <= (d == 64 ? 2048 : 5120));
+    if (p.keys == Keys::STRIPS || more) {
+        p.keys = Keys::STRIPS;
+        p.parts = most([&](long n) { return strips * n <= 200 && 2L * G * nq >= 7 * waves * n; });
+        if (p.parts > 1) {
+            p.beyond = 0;
+            return p;
+        }
+        const long far = packed ? strips * mean / T : strips;
+        p.parts = most([&](long n) { return far * n <= (d == 32 ? 3000 : 1200) && (long)G * nq >= 14 * waves * n; });
+    } else if (T >= 1400) {
+        p.parts = most([&](long n) { return blocks * n <= (d == 128 ? 1024 : 3200); });
+        if (p.parts > 1) p.keys = d == 128 ? Keys::KEYS_128 : Keys::ONE_GROUP;
+    }
+    return p;
+}
+
 // log2 of the run, -1: turn with every block.  A run pays where the launch is several rounds deep and
 // there are enough runs to even the XCDs out: 32 of them, or 16 where 64 heads and more can be turned
 // among each other as well, by o(o+1)/2 inside each octet o of heads (over octets 8x to 8x + 7 these are all 8

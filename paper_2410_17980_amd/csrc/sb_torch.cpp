@@ -349,7 +349,7 @@ PyObject* backward(PyObject* const* a)
     void* g = ptr(a[7], BF, s.q, "dout");
     const Launch on = launch_on(a[13]);
     Out dq(a[8], F32, s.q, like, "dq", on), dk(a[9], F32, s.kv, like, "dk", on), dv(a[10], F32, s.kv, like, "dv", on);
-    Workspace ws(a[12], sb_attn_bwd_workspace_bytes(s.B, s.H, s.T, s.d), like, on);
+    Workspace ws(a[12], sb_attn_bwd_gqa_workspace_bytes(s.B, s.H, s.Hkv, s.T, s.d), like, on);
     auto go = [&](float* dr) {
         call(what, [&] {
             return sb_attn_bwd_gqa(q, k, v, r, m, g, dq.p<float>(), dk.p<float>(), dv.p<float>(), dr, ws.p(), ws.bytes(),
@@ -444,7 +444,7 @@ PyObject* varlen_backward(PyObject* const* a)
     void* r = ptr(a[7], BF, s.hd, "r");
     const Launch on = launch_on(a[13]);
     Out dq(a[8], F32, s.q, like, "dq", on), dk(a[9], F32, s.kv, like, "dk", on), dv(a[10], F32, s.kv, like, "dv", on);
-    Workspace ws(a[12], sb_attn_varlen_bwd_workspace_bytes(nseq, s.H, s.T, max_T, s.d), like, on);
+    Workspace ws(a[12], sb_attn_varlen_bwd_gqa_workspace_bytes(nseq, s.H, s.Hkv, s.T, max_T, s.d), like, on);
     auto go = [&](float* dr) {
         call("sb_attn_varlen_bwd", [&] {
             return sb_attn_varlen_bwd(q, k, v, r, m, g, dq.p<float>(), dk.p<float>(), dv.p<float>(), dr, cu, nseq,

@@ -1,0 +1,46 @@
+"""Key-stationary pass of grouped heads whose query heads are several workgroups' (key_plan() in csrc/sb_share.h), against the oracle as in
+test_gpu_blocks.py, twice on one workspace, which at first reads as NaN; the plans named here are asked for in test_routes.py."""
+import numpy as np
+import pytest
+import torch
+
+from helpers import dev, nan_bytes
+from test_gpu_blocks import compare
+from test_gpu_exhausted import gen, mixed_grouped, sb  # noqa: F401  (fixtures)
+
+pytestmark = pytest.mark.gpu
+
+APART, ALIKE, HARDLY = [2, 700, 1025, 31, 129], [900, 1100, 1000, 1041], [1409, 0, 33, 1, 1280]
+# B, H, Hkv, T, d, lengths or None, kernel, parts, beyond
+SHAPES = [(1, 12, 3, 462, 128, None, "strips", 4, 0), (2, 8, 1, 535, 32, None, "strips", 4, 0), (1, 16, 2, 449, 64, None, "strips", 4, 0),
+          (1, 24, 3, 1500, 128, None, "strips", 4, 8), (1, 9, 3, 1889, 128, None, "strips", 3, 8), (1, 32, 4, 1300, 64, None, "strips", 2, 8),
+          (1, 32, 4, 1300, 32, None, "strips", 2, 8), (1, 58, 29, 1409, 128, None, "128 keys", 2, 8), (1, 96, 48, 1409, 64, None, "one group", 2, 8),
+          (1, 96, 48, 1409, 32, None, "one group", 2, 8),
+          (5, 16, 4, 1887, 128, APART, "strips", 4, 8), (5, 26, 13, 1887, 128, APART, "128 keys", 2, 8), (5, 66, 33, 1887, 64, APART, "one group", 2, 8),
+          (5, 164, 82, 1887, 32, APART, "one group", 2, 8), (4, 16, 4, 1100, 128, ALIKE, "strips", 2, 8), (5, 90, 30, 1409, 128, HARDLY, "128 keys", 1, 8),
+          (5, 36, 18, 1409, 128, HARDLY, "128 keys", 2, 8)]
+
+
+@pytest.mark.parametrize("bias", [False, True])
+@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "B%d_H%d_Hkv%d_T%d_d%d%s" % (*s[:5], "_packed" if s[5] else ""))
+def test_parts(sb, oracle, gen, shape, bias):
+    B, H, Hkv, T, d, lens = shape[:6]
+    q, k, v, g = mixed_grouped(gen, 1 if lens else B, H, Hkv, sum(lens) if lens else T, d, seed=7000 + T + d)
+    r = gen.remainder_embedding(H, d, seed=9) if bias else None
+    rd, cu = r.cuda() if bias else None, None
+    if lens:
+        q, k, v, g = (t[0] for t in (q, k, v, g))
+        cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+        qd, kd, vd, gd, cud = dev(q, k, v, g, torch.from_numpy(cu))
+        _, m = sb.sb_attn_varlen_fwd(qd, kd, vd, cud, T, r=rd)
+        ws = nan_bytes(sb.sb_attn_varlen_bwd_gqa_workspace_bytes(B, H, Hkv, sum(lens), T, d))
+        go = lambda w: sb.sb_attn_varlen_bwd(qd, kd, vd, m, gd, cud, T, r=rd, workspace=w)
+    else:
+        qd, kd, vd, gd = dev(q, k, v, g)
+        _, m = sb.sb_attn_fwd_gqa(qd, kd, vd, r=rd)
+        ws = nan_bytes(sb.sb_attn_bwd_gqa_workspace_bytes(B, H, Hkv, T, d))
+        go = lambda w: sb.sb_attn_bwd_gqa(qd, kd, vd, m, gd, r=rd, workspace=w)
+    got = go(ws)
+    for a, b, c in zip(got, go(ws), go(None)):
+        assert torch.equal(a, b) and torch.equal(a, c)
+    compare(oracle, [t.cpu() for t in got], q, k, v, g, r, cu)

@@ -27,6 +27,11 @@ int main()
             printf("%d %d %d %d\n", s.near, s.C, s.nfar, room(T));
             continue;
         }
+        if (packed == 8 || packed == 9) {               // grouped heads' key-stationary pass where there is room for parts, of a batch or packed
+            const KeyPlan p = key_plan(B, H, Hkv, T, d, packed == 9, Ttot);
+            printf("%d %d %d\n", (int)p.keys, p.parts, p.beyond);
+            continue;
+        }
         const long strips = pieces(B, H, T, 32, packed, Ttot);
         if (packed == 3) {                              // waves of a strip's workgroup
             printf("%d %d\n", query_strips(B, H, T, d, false, 0) && four_waves(pieces(B, H, T, 32, false, 0), 1, T, d),
@@ -326,3 +331,27 @@ def test_decode_chunks_cover_the_keys_and_fit(ask):
         T = row[3]
         assert near + C * nfar >= T and near + C * (nfar - 1) < T and nfar <= 127, row
         assert nfar == 0 or nfar + (near > 0) <= room, row
+
+
+def test_parts_of_grouped_heads(ask):
+    """test_gpu_parts.py; and no parts without groups, a divisor of the group's heads, with sums that stay below 210 MB."""
+    import test_gpu_parts as t
+    rows = [(B, H, Hkv, T, d, 8 if lens is None else 9, 0 if lens is None else sum(lens)) for B, H, Hkv, T, d, lens, *_ in t.SHAPES]
+    for shape, got in zip(t.SHAPES, ask(rows)):
+        assert (KEYS[got[0]],) + got[1:] == shape[6:], shape
+    rng = random.Random(11)
+    rows = []
+    for _ in range(3000):
+        G, Hkv, B, T = rng.choice((1, 2, 3, 4, 5, 6, 8, 12, 16)), rng.randrange(1, 40), rng.randrange(1, 40), int(2 ** rng.uniform(0, 14))
+        rows.append((B, G * Hkv, Hkv, T, rng.choice((32, 64, 128)), *((8, 0) if rng.random() < 0.5 else (9, max(T, rng.randrange(1, T * B + 1))))))
+    for row, (keys, parts, beyond) in zip(rows, ask(rows)):
+        B, H, Hkv, T, d, packed, Ttot = row
+        assert parts == 1 or (H // Hkv) % parts == 0 and parts * Hkv * (Ttot or B * T) * d * 8 <= 211e6, row
+
+
+def test_equal_lengths_take_the_plan_of_the_batched_call(ask):
+    rng = random.Random(12)
+    shapes = [(rng.randrange(1, 9), rng.randrange(2, 9), rng.randrange(1, 12), rng.randrange(1, 4200), rng.choice((32, 64, 128))) for _ in range(600)]
+    batched = ask([(B, G * H, H, T, d, 8, 0) for B, G, H, T, d in shapes])
+    for shape, a, b in zip(shapes, batched, ask([(B, G * H, H, T, d, 9, B * T) for B, G, H, T, d in shapes])):
+        assert a[1:] == b[1:] and (KEYS[a[0]] == "strips") == (KEYS[b[0]] == "strips"), shape
