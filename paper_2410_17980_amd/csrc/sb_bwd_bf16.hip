@@ -776,6 +776,7 @@ __device__ __forceinline__ void kv_head_of(KvHead& kh, const Share& sh, const Pl
 struct Parts {
     float* sums;
     int n, beyond, blocks;                  // parts, see in_parts(), workgroups of a part
+    bool last;                              // see take_part()
 };
 // The sums of kv head `kv` in part 0: where element x of dk and dv is, and the counts.  rows: of a kv head (of a packed batch all)
 template <int D> struct PartSums {
@@ -791,22 +792,22 @@ template <int D> struct PartSums {
         arrived = reinterpret_cast<int*>(parts.sums + 2 * all);
     }
 };
-// The part that workgroup `wg` takes of the block of the workgroup of that number in one part; the first part's come last, behind those that have nothing to do
+// The part that workgroup `wg` takes of the block of the workgroup of that number in one part.  The first part's come last (parts.last), behind those that
+// have nothing to do: far blocks' parts start at once, and near blocks fill up what they leave.
 __device__ __forceinline__ int take_part(int& wg, const Parts& parts)
 {
-    int part = parts.n - 1;
-    for (; part > 0 && wg >= parts.blocks; --part) wg -= parts.blocks;
-    return part;
+    int at = 0;
+    for (; at < parts.n - 1 && wg >= parts.blocks; ++at) wg -= parts.blocks;
+    return parts.last ? parts.n - 1 - at : at;
 }
-// Of a block whose first 32-key strip is `lo`: do the queries `beyond` strips further on still attend to it, in any head of the group?
-__device__ __forceinline__ bool in_parts(const Parts& parts, const uint16_t* __restrict__ first, long qhead0, int G, int nqb, int lo, int T, int lane)
+// Of a block whose first 32-key strip is `lo`: do the queries `beyond` strips further on still attend to it, in any head of the group?  In two steps: the
+// first part asks together with what it needs first.
+__device__ __forceinline__ int start_beyond(const Parts& parts, const uint16_t* __restrict__ first, long qhead0, int G, int nqb, int lo, int T, int lane)
 {
-    if (parts.beyond == 0) return true;
     const int at = lo + parts.beyond;
-    if (32 * at >= T) return false;
-    const int f = lane < G ? first[(qhead0 + lane) * nqb * 4 + at] : 0x7fffffff;
-    return __builtin_amdgcn_ballot_w64(f <= lo) != 0;
+    return parts.beyond == 0 ? 0 : 32 * at < T && lane < G ? first[(qhead0 + lane) * nqb * 4 + at] : 0x7fffffff;
 }
+__device__ __forceinline__ bool in_parts(int start, int lo) { return __builtin_amdgcn_ballot_w64(start <= lo) != 0; }
 typedef __attribute__((ext_vector_type(2))) unsigned long long u64x2;
 __device__ __forceinline__ f32x4 load_shared4(const float* p)
 {
@@ -945,10 +946,12 @@ bwd_dkv_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     const int T = kh.T, nkb = kh.nkb;
     int g0 = 0, g1 = G;                                 // the workgroup's query heads
     bool alone = true;
+    int beyond = 0;
     if constexpr (PARTS) {
-        alone = !in_parts(parts, reinterpret_cast<const uint16_t*>(first), kh.qhead0, G, nkb_arg, sh.i * (BKW / 32), T, lane);
-        if (alone && part > 0) return;
-        if (!alone) {
+        beyond = start_beyond(parts, reinterpret_cast<const uint16_t*>(first), kh.qhead0, G, nkb_arg, sh.i * (BKW / 32), T, lane);
+        if (part > 0) {
+            if (!in_parts(beyond, sh.i * (BKW / 32))) return;
+            alone = false;
             g0 = part * (G / parts.n);
             g1 = g0 + G / parts.n;
         }
@@ -1125,6 +1128,10 @@ bwd_dkv_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
 #pragma unroll
     for (int s = 0; s < D / 16; ++s) { asm volatile("" :: "v"(kf[s])); asm volatile("" :: "v"(vf[s])); }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    if (PARTS && part == 0 && in_parts(beyond, sh.i * (BKW / 32))) {
+        alone = false;
+        g1 = G / parts.n;
+    }
 #pragma unroll
     for (int b = 0; b < D / 32; ++b)
 #pragma unroll
@@ -1312,10 +1319,12 @@ bwd_dkv_pair_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
     const int T = kh.T, nkb = kh.nkb;
     int g0 = 0, g1 = G;                                 // the workgroup's query heads
     bool alone = true;
+    int beyond = 0;
     if constexpr (PARTS) {
-        alone = !in_parts(parts, reinterpret_cast<const uint16_t*>(first), kh.qhead0, G, nqb_arg, sh.i * KS, T, lane);
-        if (alone && part_of > 0) return;
-        if (!alone) {
+        beyond = start_beyond(parts, reinterpret_cast<const uint16_t*>(first), kh.qhead0, G, nqb_arg, sh.i * KS, T, lane);
+        if (part_of > 0) {
+            if (!in_parts(beyond, sh.i * KS)) return;
+            alone = false;
             g0 = part_of * (G / parts.n);
             g1 = g0 + G / parts.n;
         }
@@ -1562,6 +1571,10 @@ bwd_dkv_pair_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
         const int nqb = (T + BQ - 1) / BQ;
         dma_wait<0>();
         barrier_lds();
+        if (PARTS && part_of == 0 && in_parts(beyond, sh.i * KS)) {
+            alone = false;
+            g1 = G / parts.n;
+        }
         {
             const uint32_t at = strip * 32 * C::ROW + tile_off_perm<D>(perm_row(n), hh);
             const uint32_t ka = smem0 + (buf0 == 2 ? 0 : buf0 + 1) * C::STAGE + at;
@@ -2088,17 +2101,19 @@ bwd_dkv_small_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict_
     bool alone = true;
     int G = G_arg;
     long qhead0 = kh.qhead0;
+    int beyond = 0;
     if constexpr (PARTS) {
-        alone = !in_parts(parts, first, kh.qhead0, G_arg, nqb_arg, ks, T, lane);
-        if (alone && part > 0) return;
-        if (!alone) {                                    // the part's heads are the strip's
-            G /= parts.n;
+        beyond = start_beyond(parts, first, kh.qhead0, G, nqb_arg, ks, T, lane);
+        if (part > 0) {
+            if (!in_parts(beyond, ks)) return;
+            alone = false;
+            G /= parts.n;                                // the part's heads are the strip's
             qhead0 += part * G;
             kh.qrow0 += part * G * kh.qrow_step;
             kh.cbase += part * G * kh.cbase_step;
         }
     }
-    const int all = G * nq;
+    int all = G * nq;
     int w0 = 0, wn = 0, g = 0, x0 = 0;                   // first strip of this word, and of the next one; head, and where its strips begin
     unsigned long long todo = 0;
     const uint16_t* const fg = first + qhead0 * nqb_arg * 4 + ks;
@@ -2161,6 +2176,12 @@ bwd_dkv_small_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict_
     // ones nearly always do, and where they are all there is they are what bounds the strip.
     const bool ahead = wave < 2 && wave < nq;
     if (ahead) fetch(wave, 0);
+    if (PARTS && part == 0 && in_parts(beyond, ks)) {    // (the first part's heads are the first of all)
+        alone = false;
+        G /= parts.n;
+        all = G * nq;
+        if (lane >= all) fn = 0x7fffffff;
+    }
     int r = 0;
     bool more = next(r);
     if (more && !(ahead && g == 0 && r == wave)) {
@@ -2331,13 +2352,14 @@ hipError_t launch_one(const uint16_t* q, const uint16_t* k, const uint16_t* v, c
     const int entries = VL ? 1 : B;                      // of the bias's gradient
     const int nchunk = bias_chunks(B, T, VL, Ttot);
     Keys keys = keys_of(B, H, Hkv, T, D, VL, Ttot);
-    Parts parts = {nullptr, 1, 8, 0};
+    Parts parts = {nullptr, 1, 8, 0, true};
     int* arrived = nullptr;
     if (room) {
         const KeyPlan plan = key_plan(B, H, Hkv, T, D, VL, Ttot);
         keys = plan.keys;
         parts.n = plan.parts;
         parts.beyond = plan.beyond;
+        parts.last = plan.last;
         if (parts.n > 1) {
             const size_t base = VL ? bwd_varlen_workspace_bytes(B, H, Ttot, T, D) : bwd_workspace_bytes(B, H, T, D);
             parts.sums = reinterpret_cast<float*>(reinterpret_cast<char*>(workspace) + (base + 15) / 16 * 16);

@@ -344,6 +344,8 @@ inline Keys keys_of(int B, int H, int Hkv, int T, int d, bool packed, int Ttot)
 //            T7789 (549) 1236 / 1175, 946 / 580, 128 / 127;  B4 H32 Hkv8 T3000 (768) 858 / 856, 570 / 380, 187 / 186;  not packed H28 Hkv14, 41 up to 2437 (2280)
 //            582 / 648, 353 / 396, 267 / 292
 //            d = 32 B2 H18 Hkv9 T5580 (792) 595 / 589, 499 / 380, 87 / 88
+// The first parts' workgroups come behind those that may have nothing to do, or before them where they leave CUs free: d = 32 B2 H16 Hkv2 T2539 160 / 157, 53 / 49;  d = 64
+// B1 H4 Hkv1 T5564 34.8 / 33.8;  not d = 32 B1 H24 Hkv6 T2572 132 / 132, 98 / 108;  d = 128 B1 H24 Hkv3 T2836 323 / 316, 216 / 233;  B4 H12 Hkv4 T2048 269 / 271, 187 / 204, 114 / 129.
 // Strips in one part where that rule, made for batches of one length, takes blocks, packed ones going by their mean: packed, d = 32 H27 Hkv9, 6 up to 1681 (954) 148 / 90,
 // 147 / 75, 52 / 47;  H15 Hkv5, 19 up to 1222 (1150) 114 / 78, 113 / 72, 59 / 54;  H8 Hkv4, 28 up to 1408 (1288) 97 / 70, 97 / 66, 49 / 38;  H20 Hkv10, 20 up to 3075 (4920) 372 / 356,
 // 251 / 201, 116 / 108;  d = 64 H28 Hkv14, 17 up to 522 (1722) 78 / 69, 75 / 67, 67 / 65;  d = 128 H28 Hkv7, 8 up to 788 (728) 157 / 123, 141 / 115, 131 / 100;  not H18 Hkv9,
@@ -351,12 +353,13 @@ inline Keys keys_of(int B, int H, int Hkv, int T, int d, bool packed, int Ttot)
 struct KeyPlan {
     Keys keys;
     int parts, beyond;
+    bool last;                            // the first part's workgroups behind the others'
 };
 inline KeyPlan key_plan(int B, int H, int Hkv, int T, int d, bool packed, int Ttot)
 {
     const int G = H / Hkv, mean = mean_T(B, T, packed, Ttot), nq = (T + 31) / 32, waves = d == 128 ? 4 : 8;
     const long strips = pieces(B, Hkv, T, 32, packed, Ttot), blocks = pieces(B, Hkv, T, 128, packed, Ttot);
-    KeyPlan p = {keys_of(B, H, Hkv, T, d, packed, Ttot), 1, 8};
+    KeyPlan p = {keys_of(B, H, Hkv, T, d, packed, Ttot), 1, 8, true};
     if (G == 1) return p;
     auto most = [&](auto fits) {
         int n = 1;
@@ -374,6 +377,7 @@ inline KeyPlan key_plan(int B, int H, int Hkv, int T, int d, bool packed, int Tt
         }
         const long far = packed ? strips * mean / T : strips;
         p.parts = most([&](long n) { return far * n <= (d == 32 ? 3000 : 1200) && (long)G * nq >= 14 * waves * n; });
+        p.last = strips > (d == 32 ? 400 : 256);
     } else if (T >= 1400) {
         p.parts = most([&](long n) { return blocks * n <= (d == 128 ? 1024 : 3200); });
         if (p.parts > 1) p.keys = d == 128 ? Keys::KEYS_128 : Keys::ONE_GROUP;
