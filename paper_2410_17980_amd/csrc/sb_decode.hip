@@ -80,6 +80,22 @@ __device__ __forceinline__ void store_out(const uint16_t* rb, uint16_t* o, float
     if (m && c == 0) *m = -total * SB_LN2;
 }
 
+// the same of columns c .. c + 3
+__device__ __forceinline__ void store_out4(const uint16_t* rb, uint16_t* o, float* m, int c, f32x4 r, float total)
+{
+    typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
+    typedef __attribute__((ext_vector_type(4))) uint16_t u16x4;
+    if (rb) {
+        const u16x4 e = *reinterpret_cast<const u16x4*>(rb + c);
+        const float left = fast_exp2(-total);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) r[i] += left * __builtin_bit_cast(float, (uint32_t)e[i] << 16);
+    }
+    const bf16x4 v = {(__bf16)r[0], (__bf16)r[1], (__bf16)r[2], (__bf16)r[3]};
+    *reinterpret_cast<bf16x4*>(o + c) = v;
+    if (m && c == 0) *m = -total * SB_LN2;
+}
+
 // A workgroup takes its keys from the nearest down in passes of KEYS, 32 keys per wave.
 //   logits   z[key][head] = K q: 16x16x32 bf16 MFMA, A = 16 rows of K (lane: row lane%16, 16-byte chunk
 //            4s + lane/16), B = the query heads of the group.  A lane gets four consecutive keys of one head.
@@ -111,13 +127,13 @@ decode_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, co
     constexpr int NK = KW * ROW / 1024;    // loads of K per wave and pass
     constexpr int NV = 8;                  // and of V
     typedef __attribute__((ext_vector_type(CW / 2))) unsigned int vword;
-    constexpr int HB = 4;                  // heads per round of the reduction over the waves
+    constexpr int CH = D / 4;              // 16-byte chunks of a head's columns
     __shared__ __attribute__((aligned(1024))) char kbuf[KEYS * ROW];
     __shared__ __attribute__((aligned(16))) float zs[2][GMAX][ZS];   // per pass parity: logits (base 2), then weights
     __shared__ float s_carry[GMAX];
     __shared__ int s_left[2];              // per pass parity: heads not exhausted
-    float* const ored = reinterpret_cast<float*>(kbuf);              // once the keys are done
-    static_assert(NW * HB * D * 4 <= KEYS * ROW, "the waves' shares fit");
+    f32x4* const ored = reinterpret_cast<f32x4*>(kbuf);              // once the keys are done
+    static_assert(NW * GMAX * D * 4 <= KEYS * ROW, "the waves' shares fit");
 
     asm volatile("" :: "s"(q), "s"(k), "s"(v), "s"(T), "s"(Tcap), "s"(G), "s"(near), "s"(C));
     const int bkv = FAR ? blockIdx.y : blockIdx.x;     // batch entry * Hkv + kv head
@@ -140,7 +156,7 @@ decode_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, co
         }
     }
 
-    // rows hi - KEYS + 32 wave .. + 31; those before k0 are loaded as k0 and masked
+    // rows hi - KEYS + 32 wave .. + 31; those before k0 are loaded as k0 and masked, and not at all where they are all a wave has
     const int r0 = wave * KW - KEYS;
     const char* const kg = reinterpret_cast<const char*>(k) + (long)bkv * Tcap * ROW;
     const char* const vg = reinterpret_cast<const char*>(v) + (long)bkv * Tcap * ROW;
@@ -148,6 +164,7 @@ decode_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, co
     auto fetch_k = [&](int hi) __attribute__((always_inline)) {
         const uint64_t base = scalar_base(kg + (long)(hi + r0) * ROW);
         const int lo = k0 - (hi + r0);
+        if (lo >= KW) return;
 #pragma unroll
         for (int i = 0; i < NK; ++i) {
             const int row = i * (1024 / ROW) + lane / CPR;
@@ -159,6 +176,11 @@ decode_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, co
     auto fetch_v = [&](int hi, vword (&vw)[NV]) __attribute__((always_inline)) {
         const char* const base = vg + (long)(hi + r0) * ROW;
         const int lo = k0 - (hi + r0);
+        if (lo >= KW) {                                              // (their weights are zero)
+#pragma unroll
+            for (int i = 0; i < NV; ++i) vw[i] = vword(0u);
+            return;
+        }
 #pragma unroll
         for (int i = 0; i < NV; ++i)
             vw[i] = stream_load<FAR>(reinterpret_cast<const vword*>(base + (unsigned)(max(8 * lq + i, lo) * ROW + l16 * 2 * CW)));
@@ -271,29 +293,32 @@ decode_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, co
     dma_wait<0>();                         // keys asked for before the end was known
     barrier_lds();                         // (theirs is the place of the shares)
 
-    // ---- the waves' shares, HB heads at a time
-    for (int gb = 0; gb < live; gb += HB) {
-        if (gb > 0) barrier_lds();
-        if (l16 >= gb && l16 < gb + HB) {
-            float* r = ored + (wave * HB + l16 - gb) * D + CW * 4 * lq;
+    // ---- the waves' shares, all heads at once: a lane holds 4 CW columns of its head, CW chunks of 16 bytes.  The chunk's place is xor-ed with
+    // the head, so that heads, whose rows begin in the same bank, do not meet in one.  (Float by float, four heads at a time with two barriers each, this took
+    // 2300 clocks of 9600 for up to four heads and 5200 for eight, d = 128; now 2000.  With the loads of waves that have no keys left out, us: B9 H24 Hkv3 T476
+    // d128 8.9 -> 7.7, B1 H12 Hkv4 T333 d128 6.8 -> 6.2, B1 H64 Hkv8 T3000 d128 9.0 -> 8.5, B2 H16 Hkv2 T70 d128 6.6 -> 5.3.)
+    if (l16 < live) {
+        f32x4* const r = ored + (wave * live + l16) * CH;
 #pragma unroll
-            for (int rr = 0; rr < 4; ++rr)
+        for (int j = 0; j < CW; ++j) {
+            f32x4 x;
 #pragma unroll
-                for (int e = 0; e < CW; ++e) r[CW * rr + e] = acc[e][rr];
+            for (int i = 0; i < 4; ++i) x[i] = acc[(4 * j + i) % CW][(4 * j + i) / CW];
+            r[(CW * lq + j) ^ (l16 & 7)] = x;
         }
-        barrier_lds();
-        for (int i = tid; i < min(HB, live - gb) * D; i += NTHR) {
-            const int g = gb + i / D, c = i % D;
-            float s = 0.0f;
+    }
+    barrier_lds();
+    for (int i = tid; i < live * CH; i += NTHR) {
+        const int g = i / CH, c = i % CH;
+        f32x4 s = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-            for (int w = 0; w < NW; ++w) s += ored[(w * HB) * D + i];
-            const float a = s_carry[g];
-            if (!FAR && (nfar == 0 || (!m && a >= CARRY_EXHAUSTED)))
-                store_out(rb ? rb + ((bkv % Hkv) * G + g0 + g) * D : nullptr, o + (hq0 + g) * D, m ? m + hq0 + g : nullptr, c, s, a);
-            if (nfar > 0) {
-                part_o[((hq0 + g) * nch + chunk) * D + c] = s;
-                if (c == 0) part_a[(hq0 + g) * nch + chunk] = a;
-            }
+        for (int w = 0; w < NW; ++w) s += ored[(w * live + g) * CH + (c ^ (g & 7))];
+        const float a = s_carry[g];
+        if (!FAR && (nfar == 0 || (!m && a >= CARRY_EXHAUSTED)))
+            store_out4(rb ? rb + ((bkv % Hkv) * G + g0 + g) * D : nullptr, o + (hq0 + g) * D, m ? m + hq0 + g : nullptr, 4 * c, s, a);
+        if (nfar > 0) {
+            *reinterpret_cast<f32x4*>(&part_o[((hq0 + g) * nch + chunk) * D + 4 * c]) = s;
+            if (c == 0) part_a[(hq0 + g) * nch + chunk] = a;
         }
     }
 }

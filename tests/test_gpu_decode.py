@@ -154,3 +154,15 @@ def test_many_heads_alone_or_not(sb, oracle, H, Hkv, T, d):
         assert np.all(np.abs(to64(o[:, x]) - ref) <= 2.0 ** -8 * np.abs(ref) + 1e-4), h
         ok = rem > 1e-290
         assert np.allclose(to64(m[:, x])[ok], np.log(rem[ok]), rtol=1e-5, atol=1e-4), h
+
+
+@pytest.mark.parametrize("d", [32, 64, 128])
+@pytest.mark.parametrize("G,T", [(1, 32), (8, 33), (9, 224), (16, 225), (20, 257), (3, 289), (20, 1600)])
+def test_waves_without_keys_and_all_heads_at_once(sb, oracle, gen, G, T, d):
+    """Where a wave of a pass has no keys of its own, and one to all of a workgroup's sixteen heads; the cache beyond T reads as NaN."""
+    q, k, v = make(gen, 2, 2 * G, 2, T + 300, d, seed=G + T, kind="biased_gaussian", shift=-4.0)
+    k[:, :, T:] = v[:, :, T:] = float("nan")
+    check(sb, oracle, q, k, v, T=T, r=gen.remainder_embedding(2 * G, d, seed=4))
+    o = sb.sb_attn_decode(*dev(q, k, v), T=T)
+    ref, _ = oracle.decode(to64(q), to64(k)[:, :, :T], to64(v)[:, :, :T])
+    assert max_abs(to64(o), ref) <= BF16_TOL
