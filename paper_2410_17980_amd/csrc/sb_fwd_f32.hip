@@ -16,9 +16,13 @@
 // Measured, B1 H1 T256 d64: 228 us with one lane per query row walking the keys one by one -> 9.8 us;
 // B1 H1 T2048 d128 5163 -> 66 us, B4 H8 T2048 d128 5715 -> 603 us.  With K and Q by whole rows and exponential and logarithm
 // of its own: 9.8 -> 6.5, 66 -> 50, 605 -> 443 us (78 TFLOP/s); B4 H8 T2048 d32 279 -> 166 us.  Against fp64 the error of o
-// is at most what it was with the library's functions, a third less where logits are of the order of 1.
+// is at most what it was with the library's functions, a third less where logits are of the order of 1.  With the logarithm as a polynomial, the longest rows of all
+// heads first and masks on the diagonal alone (d <= 64): 6.5 -> 6.1, 49.7 -> 48.3, 442 -> 440, 166 -> 131 us; B1 H3 T1984 d32 37 -> 24.
+#include <type_traits>
+
 #include "sb_kernels.h"
 #include "sb_mma.h"
+#include "sb_share.h"
 
 namespace sb {
 namespace {
@@ -53,21 +57,23 @@ __device__ __forceinline__ void exp_of_four(float (&x)[4])
 #pragma unroll
     for (int r = 0; r < 4; ++r) x[r] = exp_f32<false>(x[r]);
 }
-// log(1 + e), 0 <= e <= 1: 2 atanh(s), s = e / (2 + e) <= 1/3, by its series up to s^15 / 15 (the next term: 1.4e-9 of the sum)
+// log(1 + e), 0 <= e <= 1, as e - e^2 P(e): P of degree 9 with the least error relative to the sum (9e-10 of it; fitted with its coefficients
+// rounded one after the other).  With rounding 2.8e-8 of the result in the mean square, 9.7e-8 at most; 2 atanh(e / (2 + e)) by its series has 2.6e-8 and
+// 6.8e-8 and takes a reciprocal and nine instructions more, a fifth of what a logit costs on the vector ALU: B4 H8 T2048 d32 149 -> 131 us, B1 H1 T256 d64 6.3 -> 6.1.  The
+// error of o against fp64 is no larger with it (d 32 to 128, T 256 to 1500, logits near 0, of order 1, times three and ten, far: 0.99 to 1.00 of it).
 __device__ __forceinline__ float log1p_f32(float e)
 {
-    const float d = 2.0f + e, low = e - (d - 2.0f);                       // 2 + e = d + low
-    const float r = __builtin_amdgcn_rcpf(d), s0 = e * r;
-    const float rest = (__builtin_fmaf(-d, s0, e) - low * s0) * r;        // s = s0 + rest
-    const float t = s0 * s0;
-    float p = 1.0f / 15;
-    p = __builtin_fmaf(p, t, 1.0f / 13);
-    p = __builtin_fmaf(p, t, 1.0f / 11);
-    p = __builtin_fmaf(p, t, 1.0f / 9);
-    p = __builtin_fmaf(p, t, 1.0f / 7);
-    p = __builtin_fmaf(p, t, 1.0f / 5);
-    p = __builtin_fmaf(p, t, 1.0f / 3);
-    return 2.0f * (s0 + __builtin_fmaf(s0 * t, p, rest));                 // one rounding of the size of the result
+    float p = -0.00208444008604f;
+    p = __builtin_fmaf(p, e, 0.01369118690491f);
+    p = __builtin_fmaf(p, e, -0.04211390763521f);
+    p = __builtin_fmaf(p, e, 0.08323805034161f);
+    p = __builtin_fmaf(p, e, -0.12479481101036f);
+    p = __builtin_fmaf(p, e, 0.16135157644749f);
+    p = __builtin_fmaf(p, e, -0.19899621605873f);
+    p = __builtin_fmaf(p, e, 0.24988864362240f);
+    p = __builtin_fmaf(p, e, -0.33332714438438f);
+    p = __builtin_fmaf(p, e, 0.49999988079071f);
+    return __builtin_fmaf(-(e * e), p, e);
 }
 // Rows of fp32 in LDS: byte offset of 16-byte chunk c of row `row`, the chunk xor-ed so that 16 lanes that read the same chunk of
 // 16 rows meet different banks.
@@ -85,7 +91,7 @@ template <int D> __device__ __forceinline__ int f32_off(int row, int c)
 template <int D>
 __global__ void __launch_bounds__(F32_THREADS)
 fwd_f32_kernel(const float* __restrict__ q, const float* __restrict__ k, const float* __restrict__ v,
-               float* __restrict__ o, float* __restrict__ m, int T, int nqb, long nblocks, int first_wg)
+               float* __restrict__ o, float* __restrict__ m, int T, int nqb, int heads, int run, int first_wg)
 {
     constexpr int VEC = D >= 64 ? 4 : 2;
     constexpr int NV = D / (16 * VEC);
@@ -98,14 +104,9 @@ fwd_f32_kernel(const float* __restrict__ q, const float* __restrict__ k, const f
     float (*const s_o)[F32_BQ][D] = reinterpret_cast<float (*)[F32_BQ][D]>(s_k);
     static_assert(SUB == F32_BQ * D * 4, "a wave's partial result takes the place of its subtile");
 
-    // consecutive workgroup ids go round the 8 XCDs: give each XCD one contiguous eighth of the
-    // (head, query block) list, so that a head's K and V are read into one or two L2s only
-    const unsigned per_xcd = (unsigned)((nblocks + 7) >> 3), wg = (unsigned)first_wg + blockIdx.x;      // (the grid is below 2^31)
-    const unsigned lin = (wg & 7) * per_xcd + (wg >> 3);
-    if (lin >= nblocks) return;
-    const unsigned head = __builtin_amdgcn_readfirstlane(lin / (unsigned)nqb);
-    const long bh = head;
-    const int q0 = (nqb - 1 - (int)(lin - head * (unsigned)nqb)) * F32_BQ;      // longest rows first
+    const Share sh = in_scalars(share_of((unsigned)first_wg + blockIdx.x, heads, run));
+    const long bh = sh.bh;
+    const int q0 = (nqb - 1 - sh.i) * F32_BQ;                  // longest rows first
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int n = lane & 15, g = lane >> 4;
@@ -143,7 +144,7 @@ fwd_f32_kernel(const float* __restrict__ q, const float* __restrict__ k, const f
     const uint32_t row_at = f32_off<D>(n, g);                 // chunk 4j + g: ^ (j << 6)
 #pragma unroll
     for (int j = 0; j < D / 16; ++j) qf[j] = __builtin_bit_cast(f32x4, lds_load16((q_at + row_at) ^ (j << 6)));
-    for (int sub = hi; sub >= lo; --sub) {
+    auto step = [&](auto masked, int sub) __attribute__((always_inline)) {
         dma_wait<0>();                                        // K has landed
         vec vf[4][NV];
 #pragma unroll
@@ -177,7 +178,7 @@ fwd_f32_kernel(const float* __restrict__ q, const float* __restrict__ k, const f
         exp_of_four(e);
 #pragma unroll
         for (int r = 3; r >= 0; --r) {
-            seen[r] = 16 * sub + 4 * g + r < q0 + n;
+            seen[r] = !decltype(masked)::value || 16 * sub + 4 * g + r < q0 + n;
             // softplus(z) = max(z, 0) + log(1 + e^{-|z|}); z less that, each part by itself, loses nothing where z is large
             const float over = fmaxf(z[r], 0.0f), l = log1p_f32(e[r]);
             x[r] = (z[r] - over) - l;
@@ -203,7 +204,11 @@ fwd_f32_kernel(const float* __restrict__ q, const float* __restrict__ k, const f
 #pragma unroll
                 for (int e = 0; e < VEC; ++e)
                     acc[j * VEC + e] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[r], vf[r][j][e], acc[j * VEC + e], 0, 0, 0);
-    }
+    };
+    int sub = hi;
+    if constexpr (D < 128)                                     // (the matrix pipe bounds d = 128: twice the code cost 3 % of a short call there)
+        if (sub >= lo && 16 * sub == q0) step(std::true_type(), sub--);       // the one subtile that not every row sees all of
+    for (; sub >= lo; --sub) step(std::bool_constant<D == 128>(), sub);
 
     // ---- combine the waves' ranges.  acc[b][r] is query row 4g + r.
     if (g == 0) s_tot[wave][n] = s;
@@ -247,18 +252,22 @@ fwd_f32_kernel(const float* __restrict__ q, const float* __restrict__ k, const f
 hipError_t launch_fwd_f32(const float* q, const float* k, const float* v, float* o, float* m,
                           int B, int H, int T, int d, hipStream_t stream)
 {
-    const int nqb = (T + F32_BQ - 1) / F32_BQ;
-    const long nblocks = (long)B * H * nqb;
-    const long grid = (nblocks + 7) / 8 * 8;
+    const int heads = B * H, nqb = (T + F32_BQ - 1) / F32_BQ;
+    const long grid = (long)heads * nqb;
     if (grid > 0x7fffffffL) return hipErrorInvalidValue;
+    // The longest rows of all heads first, over all XCDs; heads in eights stay on one XCD each, whose L2 then holds their K and V.  Against a contiguous eighth
+    // of the (head, rows) list for each XCD, which left some with the longest rows of a head and others with the shortest, us: B1 H3 T1984 d32 37 / 27,
+    // B2 H3 T1854 d128 92 / 80, B2 H5 T965 d64 38.5 / 25.5, B3 H4 T1500 d64 69 / 52, d128 121 / 110, B4 H8 T2048 d32 166 / 158, d64 232 / 223 (turning 301), d128
+    // 442 / 444 (turning 610).
+    const int run = heads % 8 == 0 ? 31 : -1;
     return launch_workgroups(grid, F32_THREADS, [&](unsigned wgs, int first_wg) {
         const dim3 g(wgs), block(F32_THREADS);
         if (d == 32)
-            hipLaunchKernelGGL(fwd_f32_kernel<32>, g, block, 0, stream, q, k, v, o, m, T, nqb, nblocks, first_wg);
+            hipLaunchKernelGGL(fwd_f32_kernel<32>, g, block, 0, stream, q, k, v, o, m, T, nqb, heads, run, first_wg);
         else if (d == 64)
-            hipLaunchKernelGGL(fwd_f32_kernel<64>, g, block, 0, stream, q, k, v, o, m, T, nqb, nblocks, first_wg);
+            hipLaunchKernelGGL(fwd_f32_kernel<64>, g, block, 0, stream, q, k, v, o, m, T, nqb, heads, run, first_wg);
         else
-            hipLaunchKernelGGL(fwd_f32_kernel<128>, g, block, 0, stream, q, k, v, o, m, T, nqb, nblocks, first_wg);
+            hipLaunchKernelGGL(fwd_f32_kernel<128>, g, block, 0, stream, q, k, v, o, m, T, nqb, heads, run, first_wg);
     });
 }
 

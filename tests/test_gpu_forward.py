@@ -339,3 +339,14 @@ def test_f32_logit_not_finite(sb, z):
     else:
         assert torch.isnan(o[:, :, j + 1:]).all()
         assert (m[:, :, j + 1:] == -z).all() if z == z else torch.isnan(m[:, :, j + 1:]).all()
+
+
+@pytest.mark.parametrize("d", [32, 64, 128])
+@pytest.mark.parametrize("B,H,T", [(1, 8, 16), (2, 8, 145), (3, 3, 17), (2, 2, 130), (1, 64, 33)])
+def test_f32_orders_of_heads_and_the_diagonal(sb, oracle, gen, B, H, T, d):
+    """Heads in eights, each on one XCD, and others, in turn over all; m beside o, of all heads."""
+    q, k, v = gen.biased_gaussian(B, H, T, d, seed=T + H, shift=-3.0, dtype="f32")
+    o, m = sb.sb_attn_fwd_f32(*dev(q, k, v), want_m=True)
+    ref, rem = oracle.fwd(to64(q), to64(k), to64(v))
+    assert max_abs(to64(o), ref) <= F32_TOL
+    check_m(to64(m), rem, rtol=1e-5, atol=1e-5)
