@@ -99,6 +99,21 @@ def test_bwd_sharp_logits(sb, oracle, gen, gain):
     check(sb, oracle, q, k, v, g)
 
 
+@pytest.mark.parametrize("many", [1, 64])
+@pytest.mark.parametrize("logit", [3.25, 3.4, 3.48, 6.0, 6.2])
+@pytest.mark.parametrize("d", [32, 64, 128])
+def test_bwd_where_a_lane_leaves_the_linear_domain(sb, oracle, gen, d, logit, many):
+    """16 keys' softplus sums on both sides of 80 bits (logits of 3.43; query-stationary pass) and of 140 (6.06), in strips and in blocks,
+    with an upstream gradient of ordinary size and with one that leaves no room for a factor above 1 beside it (dq and dk are linear in it)."""
+    q, k, v, g = gen.constant_logit(1, 2, 300, d, seed=23, kval=logit * d ** 0.5, dtype="bf16", with_dout=True)
+    ref = oracle.bwd(to64(q), to64(k), to64(v), to64(g))
+    for scale in (1.0, 2.0 ** 110):
+        dq, dk, dv = gpu_grads(sb, *(t.repeat(many, 1, 1, 1) for t in (q, k, v, (g * scale).to(g.dtype))))
+        for b in {0, many - 1}:
+            for name, a, r in (("dq", dq, ref[0]), ("dk", dk, ref[1]), ("dv", dv, ref[2])):
+                check_grad(name, a[b:b + 1] / scale, r)
+
+
 def test_bwd_twice_agrees_and_overwrites(sb, gen):
     q, k, v, g = dev(*gen.gaussian(2, 4, 257, 128, seed=16, dtype="bf16", with_dout=True))
     o, m = sb.sb_attn_fwd_train(q, k, v)
