@@ -62,6 +62,41 @@ def test_training_step_in_a_graph(sb, gen):
         torch.cuda.synchronize()
 
 
+@pytest.mark.parametrize("B,H,Hkv,T,d", [(1, 12, 3, 462, 128), (1, 24, 3, 1500, 128), (1, 58, 29, 1409, 128), (1, 96, 48, 1409, 64)])
+def test_parts_of_grouped_heads_in_a_graph(sb, B, H, Hkv, T, d):
+    """Plans of more than one part (test_gpu_parts.py), whose counts every replay finds as something left them."""
+    from test_gpu_exhausted import mixed_grouped
+    from paper_2410_17980_amd import inputs
+    q, k, v, g = dev(*mixed_grouped(inputs, B, H, Hkv, T, d, seed=T + d))
+    _, m = sb.sb_attn_fwd_gqa(q, k, v)
+    out = [torch.empty(x.shape, dtype=torch.float32, device="cuda") for x in (q, k, v)]
+    ws = torch.empty(sb.sb_attn_bwd_gqa_workspace_bytes(B, H, Hkv, T, d), dtype=torch.uint8, device="cuda")
+
+    def step():
+        sb.sb_attn_bwd_gqa(q, k, v, m, g, dq=out[0], dk=out[1], dv=out[2], workspace=ws)
+
+    step()
+    torch.cuda.synchronize()
+    want = [t.clone() for t in out]
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        step()
+    torch.cuda.current_stream().wait_stream(side)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        step()
+    for rep in range(3):
+        for t in out:
+            t.fill_(float("nan"))
+        ws.random_(0, 255)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        for name, a, b in zip(("dq", "dk", "dv"), out, want):
+            assert torch.equal(a, b), f"replay {rep}: {name} differs from the eager result"
+
+
 def test_decode_in_a_graph(sb, gen):
     B, H, Hkv, T, d = 2, 8, 2, 3000, 128
     q, _, _ = gen.gaussian(B, H, 1, d, seed=3)
