@@ -335,8 +335,14 @@ inline Keys keys_of(int B, int H, int Hkv, int T, int d, bool packed, int Ttot)
 //            65 / 42, 65 / 42;  packed H8 Hkv1, 9 up to 211 (32) 43 / 31 in all three;  d = 32 B2 H8 Hkv1 T535 (34) 34 / 20, 22.5 / 17.3, 22.5 / 17.2;  not
 //            d = 128 B2 H6 Hkv2 T333 (44) 32 / 31, 27 / 29;  B7 H6 Hkv2 T95 (42) 18 / 24
 //   strips, if far         d = 128 B1 H24 Hkv3 T2836 (267) 414 / 318, 388 / 217, 86 / 89;  packed H8 Hkv1, 9 up to 2904 (187) 398 / 263, 78 / 79;  d = 64 B1 H4 Hkv1 T5564 (174)
-//            204 / 143, 33 / 35;  d = 32 packed H24 Hkv3, 26 up to 2961 (2268) 864 / 646, 748 / 337, 225 / 181;  B1 H24 Hkv6 T2572 (486) 124 / 134, 115 / 98, 34 / 38;  at worst
-//            B2 H16 Hkv2 T2539 (320) 172 / 160, 49 / 53
+//            204 / 143, 33 / 35;  d = 32 packed H24 Hkv3, 26 up to 2961 (2268) 864 / 646, 748 / 337, 225 / 181;  B1 H24 Hkv3 T2537 (240) 158 / 128, 156 / 104, 37 / 40
+//     not    where the strips fill the chip by themselves: what the parts read and add up is then more than the shorter chains save, but for long chains at d = 64 and 128.
+//            d = 32 B3 H8 Hkv1 T3638 (342) 228 / 240, 47 / 54 (none);  B2 H6 Hkv2 T3644 (456) 110 / 129, 94 / 116, 31 / 34;  B3 H6 Hkv3 T3711 (1044) 169 / 195, 126 / 139,
+//            41 / 47;  packed H8 Hkv1, 15 up to 3607 (458) 240 / 253, 57 / 70;  B5 H12 Hkv3 T2931 (1380) 293 / 327, 164 / 181, 74 / 81;  but B1 H24 Hkv6 T2572 (486) 124 / 134, 115 / 98, 34 / 38
+//            d = 64 B7 H4 Hkv1 T2520 (553, chains of 316 strips of queries) 159 / 176, 51 / 54;  B1 H24 Hkv6 T2512 (474, 316) 141 / 155, 129 / 113, 43 / 45;  but B2 H24 Hkv3
+//            T2861 (540, 720) 310 / 318, 232 / 192, 75 / 82
+//            d = 128 B7 H2 Hkv1 T2458 (539, 154) 181 / 207, 58 / 62;  B4 H8 Hkv2 T1954 (496, 248) 217 / 225, 189 / 219, 69 / 74;  B6 H24 Hkv3 T576 (324, 144) 117 / 120, 105 / 104,
+//            89 / 100;  packed H8 Hkv2, 10 up to 877 (286, 112) 91 / 98, 91 / 96, 55 / 65;  but B3 H24 Hkv3 T1220 (351, 312) 212 / 205, 185 / 140, 99 / 105;  B2 H12 Hkv3 T2806 (528, 352) 289 / 310, 248 / 204, 77 / 83
 //   blocks                 d = 128 B4 H12 Hkv4 T2048 (256 blocks) 310 / 267, 213 / 187, 119 / 114;  packed H12 Hkv6, 8 up to 4441 (430) 462 / 407, 402 / 301, 124 / 128;  packed H20
 //            Hkv5, 18 up to 1746 334 / 302, 287 / 205, 181 / 182;  not B16 H32 Hkv4 T1024 (512, of four parts) 740 / 806, 558 / 604, 443 / 458;  B8 H16 Hkv4 T4096 (1024, of two)
 //            2287 / 2372, 997 / 1019, 445 / 449
@@ -344,6 +350,8 @@ inline Keys keys_of(int B, int H, int Hkv, int T, int d, bool packed, int Ttot)
 //            T7789 (549) 1236 / 1175, 946 / 580, 128 / 127;  B4 H32 Hkv8 T3000 (768) 858 / 856, 570 / 380, 187 / 186;  not packed H28 Hkv14, 41 up to 2437 (2280)
 //            582 / 648, 353 / 396, 267 / 292
 //            d = 32 B2 H18 Hkv9 T5580 (792) 595 / 589, 499 / 380, 87 / 88
+//     not    two heads a group in many blocks of a batch at d = 128, B6 H12 Hkv6 T1478 (432) 215 / 256, 168 / 196, 121 / 120, H58 Hkv29 T2049 (493) 314 / 374, 233 / 262, 127 / 127;  but B1 H18 Hkv9
+//            T3493 (252) 315 / 291, 276 / 243, 80 / 90, B3 H6 Hkv3 T4366 (309) 467 / 435, 339 / 294, 109 / 106;  nor so many at d = 64, B6 H24 Hkv12 T2158 (1224) 495 / 546, 266 / 281, 146 / 150;  but B6 H12 Hkv6 T3307 (936) 562 / 589, 349 / 299, 119 / 120
 // The first parts' workgroups come behind those that may have nothing to do, or before them where they leave CUs free: d = 32 B2 H16 Hkv2 T2539 160 / 157, 53 / 49;  d = 64
 // B1 H4 Hkv1 T5564 34.8 / 33.8;  not d = 32 B1 H24 Hkv6 T2572 132 / 132, 98 / 108;  d = 128 B1 H24 Hkv3 T2836 323 / 316, 216 / 233;  B4 H12 Hkv4 T2048 269 / 271, 187 / 204, 114 / 129.
 // Strips in one part where that rule, made for batches of one length, takes blocks, packed ones going by their mean: packed, d = 32 H27 Hkv9, 6 up to 1681 (954) 148 / 90,
@@ -367,8 +375,10 @@ inline KeyPlan key_plan(int B, int H, int Hkv, int T, int d, bool packed, int Tt
             if (G % x == 0 && fits((long)x)) n = x;
         return n;
     };
-    const bool more = T > 64 && mean > 64 && T <= LONG_T && (d == 128 ? strips <= 768 : packed && packed_as(B, T, Ttot) == Packed::BY_LENGTH && strips <= (d == 64 ? 2048 : 5120));
+    const bool lengths = packed && packed_as(B, T, Ttot) == Packed::BY_LENGTH;
+    const bool more = T > 64 && mean > 64 && T <= LONG_T && (d == 128 ? strips <= 768 : lengths && strips <= (d == 64 ? 2048 : 5120));
     if (p.keys == Keys::STRIPS || more) {
+        const bool few = p.keys != Keys::STRIPS || (d == 32 ? strips <= 300 : strips <= (d == 64 ? 400 : 256) || G * nq >= (d == 64 ? 400 : 300));
         p.keys = Keys::STRIPS;
         p.parts = most([&](long n) { return strips * n <= 200 && 2L * G * nq >= 7 * waves * n; });
         if (p.parts > 1) {
@@ -376,10 +386,10 @@ inline KeyPlan key_plan(int B, int H, int Hkv, int T, int d, bool packed, int Tt
             return p;
         }
         const long far = packed ? strips * mean / T : strips;
-        p.parts = most([&](long n) { return far * n <= (d == 32 ? 3000 : 1200) && (long)G * nq >= 14 * waves * n; });
+        p.parts = most([&](long n) { return few && far * n <= (d == 32 ? 3000 : 1200) && (long)G * nq >= 14 * waves * n; });
         p.last = strips > (d == 32 ? 400 : 256);
     } else if (T >= 1400) {
-        p.parts = most([&](long n) { return blocks * n <= (d == 128 ? 1024 : 3200); });
+        p.parts = most([&](long n) { return blocks * n <= (d == 128 ? G == 2 && !lengths ? 640 : 1024 : d == 64 && !lengths ? 2300 : 3200); });
         if (p.parts > 1) p.keys = d == 128 ? Keys::KEYS_128 : Keys::ONE_GROUP;
     }
     return p;

@@ -14,10 +14,10 @@ APART, ALIKE, HARDLY = [2, 700, 1025, 31, 129], [900, 1100, 1000, 1041], [1409, 
 # B, H, Hkv, T, d, lengths or None, kernel, parts, beyond
 SHAPES = [(1, 12, 3, 462, 128, None, "strips", 4, 0), (2, 8, 1, 535, 32, None, "strips", 4, 0), (1, 16, 2, 449, 64, None, "strips", 4, 0),
           (1, 24, 3, 1500, 128, None, "strips", 4, 8), (1, 9, 3, 1889, 128, None, "strips", 3, 8), (1, 32, 4, 1300, 64, None, "strips", 2, 8),
-          (1, 32, 4, 1300, 32, None, "strips", 2, 8), (1, 58, 29, 1409, 128, None, "128 keys", 2, 8), (1, 96, 48, 1409, 64, None, "one group", 2, 8),
+          (1, 32, 4, 1300, 32, None, "strips", 2, 8), (1, 38, 19, 2000, 128, None, "128 keys", 2, 8), (1, 96, 48, 1409, 64, None, "one group", 2, 8),
           (1, 96, 48, 1409, 32, None, "one group", 2, 8),
           (5, 16, 4, 1887, 128, APART, "strips", 4, 8), (5, 26, 13, 1887, 128, APART, "128 keys", 2, 8), (5, 66, 33, 1887, 64, APART, "one group", 2, 8),
-          (5, 164, 82, 1887, 32, APART, "one group", 2, 8), (4, 16, 4, 1100, 128, ALIKE, "strips", 2, 8), (5, 90, 30, 1409, 128, HARDLY, "128 keys", 1, 8),
+          (5, 164, 82, 1887, 32, APART, "one group", 2, 8), (4, 40, 4, 1100, 128, ALIKE, "strips", 2, 8), (5, 90, 30, 1409, 128, HARDLY, "128 keys", 1, 8),
           (5, 36, 18, 1409, 128, HARDLY, "128 keys", 2, 8)]
 
 
