@@ -78,8 +78,7 @@ template <bool B> using bc = std::integral_constant<bool, B>;
 struct SubtileOut {
     bf16x8 pa[2];    // A, as MFMA operand (K-dim element e of half s <-> key 16hh + 8s + e)
     bf16x8 pz[2];    // dZ (without the 1/sqrt(d)), same layout
-};
-struct SubtileSums {
+    float ca_right;  // sum of sp2 over the keys right of the subtile
     float g_tot;     // sum of G over the subtile's 32 keys
     float g_lo;      // and over its first 16
 };
@@ -94,7 +93,9 @@ struct SubtileSums {
 //   stage 1 (logits only): sigma, chain.  Returns false in a lane whose chain left its range.
 //   stage 2 (needs dO.v): A, G, dZ.
 // sacc: q.k accumulator, pacc: dO.v accumulator.  cb: sum of G over the keys left
-// of the subtile.  ca: sum of sp2 over the keys right of the subtile.  With MASK, key 16hh + r is
+// of the subtile.  ca: sum of sp2 over the keys right of the subtile, or, with
+// CA_INCLUDES_SUBTILE, over the subtile's own keys as well (Algorithm 2 carries
+// that and subtracts the subtile's total before use).  With MASK, key 16hh + r is
 // visible to query n iff 16hh + r < n (the subtile on the diagonal).
 struct Chain {
     float be[16];    // sigma(z)
@@ -149,108 +150,46 @@ __device__ __forceinline__ void subtile_stage1_log(Chain& ch, const f32x16& sacc
     ch.norm = 0.0f;
 }
 
-__device__ __forceinline__ void subtile_stage2(SubtileOut& out, Chain& ch, const f32x16& pacc, float ca, float cb, int hh)
+// subtile_g() up to the sums of G, subtile_dz() with cb in hand.
+template <bool CA_INCLUDES_SUBTILE, bool NEED_A>
+__device__ __forceinline__ void subtile_g(SubtileOut& out, Chain& ch, const f32x16& pacc, float ca, int hh)
 {
     float l_lo, l_hi;
     both_halves(ch.l, l_lo, l_hi);
+    const float car = CA_INCLUDES_SUBTILE ? ca - (l_lo + l_hi) : ca;
+    out.ca_right = car;
     // keys 16..31 (hh = 1) are nearer to the query than keys 0..15
-    const float kf = fast_exp2(-(ca + (hh == 0 ? l_hi : 0.0f) + ch.norm));
+    const float kf = fast_exp2(-(car + (hh == 0 ? l_hi : 0.0f) + ch.norm));
     // dZ = G - sigma * (prefix of G + boff), boff = cb + the partner half's total for the
     // nearer half: the part that needs boff is added once boff is known
     float grun = 0.0f;
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
         const float w = ch.t[r] * kf;                      // A
-        out.pa[r >> 3][r & 7] = (__bf16)w;
+        if (NEED_A) out.pa[r >> 3][r & 7] = (__bf16)w;
         const float g = w * pacc[r];                       // G = dL/dlogA = A * dL/dA
         grun += g;                                         // inclusive prefix inside the lane
         ch.t[r] = g - ch.be[r] * grun;
     }
-    float g_lo, g_hi;
-    both_halves(grun, g_lo, g_hi);
-    const float boff = cb + (hh == 1 ? g_lo : 0.0f);
+    float g_hi;
+    both_halves(grun, out.g_lo, g_hi);
+    out.g_tot = out.g_lo + g_hi;
+}
+__device__ __forceinline__ void subtile_dz(SubtileOut& out, const Chain& ch, float cb, int hh)
+{
+    const float boff = cb + (hh == 1 ? out.g_lo : 0.0f);
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
         const float dz = ch.t[r] - ch.be[r] * boff;        // Eq. 4
         out.pz[r >> 3][r & 7] = (__bf16)dz;
     }
 }
-
-// The same for the query-stationary pass, which needs dZ but not A.  With A_r = t_r kf and sigma_r = t_r / W_{r+1}, t_r is a
-// factor of all of dZ_r = A_r p_r - sigma_r P_r (p: dO.v, P: the prefix of G):
-//     dZ_r = t_r (kf p_r - P_r / W_{r+1}),
-// ten multiply/adds a logit in place of eleven (beside the exponential and half a conversion): at d <= 64, where the vector ALU binds.
-// W_0 is 1 here, so that neither kf nor 1/W exceeds 1 and no bracket is larger than what it comes from; a chain may then sum to 55 nats, not 97, which is
-// where a row is a third of the way to exhausted, of 16 keys.  Whole training step, us: B8 H16 T2048 d64 304.6 -> 302.0, packed H24 d64, 16384 rows up to 4096, 472 -> 468; error of dq against 64 bits the same to four digits.
-struct RowChain {
-    float t[16];     // chain terms, as in Chain
-    float inv[16];   // 1 / W_{r+1}
-    float x[16];     // the bracket, without what boff adds
-    float l, norm;   // as in Chain
-};
-
-template <bool MASK>
-__device__ __forceinline__ bool row_stage1(RowChain& ch, const f32x16& sacc, float c2, int n, int hh)
+template <bool CA_INCLUDES_SUBTILE, bool NEED_A>
+__device__ __forceinline__ void subtile_stage2(SubtileOut& out, Chain& ch, const f32x16& pacc,
+                                               float ca, float cb, int hh)
 {
-    float W = 1.0f;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-        float e = fast_exp2(sacc[r] * c2);
-        if (MASK) e = (16 * hh + r < n) ? e : 0.0f;
-        ch.t[r] = W * e;
-        W += ch.t[r];
-        ch.inv[r] = e;                                     // kept for the backward chain below
-    }
-    ch.l = fast_log2(W * 0x1p-60f) + 60.0f;                // with the rounding of the forward, whose sum of these is counted down
-    ch.norm = ch.l;
-    float inv = __builtin_amdgcn_rcpf(W);
-#pragma unroll
-    for (int r = 15; r >= 0; --r) {
-        const float e = ch.inv[r];
-        ch.inv[r] = inv;
-        inv = __builtin_fmaf(inv, e, inv);                 // 1 / W_r
-    }
-    return W < 0x1p80f;
-}
-
-// in the log form of Eq. 2: 1 / W_{r+1} = 2^(sum of sp2 over this lane's keys nearer than r), up to where t is nothing in fp32
-template <bool MASK>
-__device__ __forceinline__ void row_stage1_log(RowChain& ch, const f32x16& sacc, float c2, int n, int hh)
-{
-    float run = 0.0f;
-#pragma unroll
-    for (int r = 15; r >= 0; --r) {
-        float x = sacc[r] * c2;
-        if (MASK) x = (16 * hh + r < n) ? x : -INFINITY;
-        ch.inv[r] = fast_exp2(fminf(run, 100.0f));
-        run += sp2(x);
-        ch.t[r] = fast_exp2(x - run);
-    }
-    ch.l = run;
-    ch.norm = 0.0f;
-}
-
-// up to the sums of G: ca is the sum of sp2 over the keys right of the subtile, l_hi of its nearer half
-__device__ __forceinline__ void row_stage2(SubtileSums& out, RowChain& ch, const f32x16& pacc, float ca, float l_hi, int hh)
-{
-    const float kf = fast_exp2(-(ca + (hh == 0 ? l_hi : 0.0f) + ch.norm));
-    float P = 0.0f;                                        // inclusive prefix of G inside the lane
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-        const float u = kf * pacc[r];
-        P = __builtin_fmaf(ch.t[r], u, P);
-        ch.x[r] = __builtin_fmaf(-ch.inv[r], P, u);
-    }
-    float g_hi;
-    both_halves(P, out.g_lo, g_hi);
-    out.g_tot = out.g_lo + g_hi;
-}
-// dZ as MFMA operand, with cb in hand
-__device__ __forceinline__ void row_dz(bf16x8 (&pz)[2], const SubtileSums& sums, const RowChain& ch, float cb, int hh)
-{
-    const float boff = cb + (hh == 1 ? sums.g_lo : 0.0f);
-#pragma unroll
-    for (int r = 0; r < 16; ++r) pz[r >> 3][r & 7] = (__bf16)(ch.t[r] * __builtin_fmaf(-ch.inv[r], boff, ch.x[r]));       // Eq. 4
+    subtile_g<CA_INCLUDES_SUBTILE, NEED_A>(out, ch, pacc, ca, hh);
+    subtile_dz(out, ch, cb, hh);
 }
 
 // ------------------------------------------------------------------ staging
@@ -549,24 +488,20 @@ bwd_dq_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
                 acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, vw[s]), gf[s], acc, 0, 0, 0);
             return acc;
         };
-        RowChain ch;
-        const bool fits = row_stage1<MASK>(ch, s_mfma(), c2, n, hh);
-        if (__builtin_expect(__builtin_amdgcn_ballot_w64(!fits) != 0, 0)) row_stage1_log<MASK>(ch, s_mfma(), c2, n, hh);
+        SubtileOut so;
+        Chain ch;
+        const bool fits = subtile_stage1<MASK>(ch, s_mfma(), c2, n, hh);
+        if (__builtin_expect(__builtin_amdgcn_ballot_w64(!fits) != 0, 0)) subtile_stage1_log<MASK>(ch, s_mfma(), c2, n, hh);
         const f32x16 pacc = p_mfma();
-        float l_lo, l_hi;
-        both_halves(ch.l, l_lo, l_hi);
-        a2 -= l_lo + l_hi;                               // Algorithm 2 subtracts the subtile's total before use
-        SubtileSums sums;
-        row_stage2(sums, ch, pacc, a2, l_hi, hh);
-        bf16x8 pz[2];
-        row_dz(pz, sums, ch, bsum, hh);
+        subtile_stage2<true, false>(so, ch, pacc, a2, bsum, hh);
         // carries of this (subtile, query) for the key-stationary kernel
         if (hh == 0 && q0 + n < T) {
             const long ci = (long)(key0 >> 5) * cstride + q0 + n;
-            cag[ci] = a2;
+            cag[ci] = so.ca_right;
             cbg[ci] = bsum;
         }
-        bsum += sums.g_tot;
+        a2 = so.ca_right;
+        bsum += so.g_tot;
         // dQ += dZ K: dZ from registers, K (rows = keys) through the transposing load
         bf16x8 kt[D / 16];
         const uint32_t k0a = ktile + ktr0[0], k1a = ktile + ktr0[1];
@@ -581,7 +516,7 @@ bwd_dq_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
         for (int b = 0; b < D / 32; ++b)
 #pragma unroll
             for (int s = 0; s < 2; ++s)
-                dqacc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(pz[s], kt[2 * b + s], dqacc[b], 0, 0, 0);
+                dqacc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(so.pz[s], kt[2 * b + s], dqacc[b], 0, 0, 0);
     };
 
     // Where the sweep of the block at Q0 has to start.  Every wave looks for the 32-key strip beyond which
@@ -1153,7 +1088,7 @@ bwd_dkv_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
                 again = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[s], *reinterpret_cast<const bf16x8*>(qtile + boff[s]), again, 0, 0, 0);
             subtile_stage1_log<MASK>(ch, again, c2, n, hh);
         }
-        subtile_stage2(so, ch, pacc, car, cbl, hh);
+        subtile_stage2<false, true>(so, ch, pacc, car, cbl, hh);
         bf16x8 at[2], zt[2];
         transpose(so, at, zt);
         mm2(gop, qop, at, zt);
@@ -1496,7 +1431,7 @@ bwd_dkv_pair_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
         Chain ch;
         if (__builtin_expect(__builtin_amdgcn_ballot_w64(!subtile_stage1<MASK>(ch, sacc, c2, n, hh)) != 0, 0))
             subtile_stage1_log<MASK>(ch, logits(qa), c2, n, hh);
-        subtile_stage2(so, ch, pacc, car, cbl, hh);
+        subtile_stage2<false, true>(so, ch, pacc, car, cbl, hh);
         const uint32_t w = sc + role * CK::W_BYTES + sw_off;
         lds_store16(w, so.pa[0]);
         lds_store16(w ^ 16, so.pa[1]);
@@ -1569,7 +1504,7 @@ bwd_dkv_pair_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
         __builtin_amdgcn_s_setprio(1);
         // part C: A, G, dZ (vector) beside the back of subtile 1 (matrix)
         SubtileOut so;
-        subtile_stage2(so, ch, pacc, car, cbl, hh);
+        subtile_stage2<false, true>(so, ch, pacc, car, cbl, hh);
         back(ptile, scp, 1);
         const uint32_t w = sc + role * CK::W_BYTES + sw_off;
         lds_store16(w, so.pa[0]);
@@ -1844,7 +1779,7 @@ __device__ __forceinline__ void own_landed() { asm volatile("s_waitcnt vmcnt(0) 
 // Against totals of all subtiles first, in every strip, and one wave adding them up one after the other, all heads far, then none, us:
 // B2 H4 T777 d32 12.5 -> 9.1, 7.3 -> 6.7; B1 H4 T4000 d64 56 -> 38, 22.5 -> 13.3; B1 H8 T700 d128 21.3 -> 16.6, 14.2 -> 12.5.
 template <int D, bool RB, int NWS>
-__global__ void __launch_bounds__(64 * NWS, D == 32 && NWS == 4 ? 3 : 1)        // (three workgroups a CU: left alone it takes registers for two)
+__global__ void __launch_bounds__(64 * NWS)
 bwd_dq_small_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
                     const uint16_t* __restrict__ v, const uint16_t* __restrict__ rb,
                     const float* __restrict__ m,
@@ -2025,10 +1960,10 @@ bwd_dq_small_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
     for (int sub0 = start, st = 0; sub0 <= strip; sub0 += NWS, st ^= 1) {
         const int sub = sub0 + wave;
         const bool there = sub <= strip;
-        RowChain ch;
-        SubtileSums sums;
-        sums.g_tot = 0.0f;
-        float car = 0.0f, l_tot = 0.0f, l_hi = 0.0f;
+        Chain ch;
+        SubtileOut so;
+        so.g_tot = 0.0f;
+        float car = 0.0f, l_tot = 0.0f;
         const uint32_t buf = st * 2 * C::SUB;
         if (there) {
             own_landed();
@@ -2037,13 +1972,13 @@ bwd_dq_small_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
                 stage_v(sub + NWS, st ^ 1);
             }
             const f32x16 s = rows_by(ka + buf, qf);
-            const bool fits = sub == strip ? row_stage1<true>(ch, s, c2, n, hh) : row_stage1<false>(ch, s, c2, n, hh);
+            const bool fits = sub == strip ? subtile_stage1<true>(ch, s, c2, n, hh) : subtile_stage1<false>(ch, s, c2, n, hh);
             if (__builtin_expect(__builtin_amdgcn_ballot_w64(!fits) != 0, 0)) {
                 const f32x16 again = rows_by(ka + buf, qf);
-                if (sub == strip) row_stage1_log<true>(ch, again, c2, n, hh);
-                else row_stage1_log<false>(ch, again, c2, n, hh);
+                if (sub == strip) subtile_stage1_log<true>(ch, again, c2, n, hh);
+                else subtile_stage1_log<false>(ch, again, c2, n, hh);
             }
-            float l_lo;
+            float l_lo, l_hi;
             both_halves(ch.l, l_lo, l_hi);
             l_tot = l_lo + l_hi;
         }
@@ -2062,14 +1997,14 @@ bwd_dq_small_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
         }
         bf16x8 kt[D / 16];
         if (there) {
-            row_stage2(sums, ch, rows_by(ka + buf + C::SUB, gf), car, l_hi, hh);
+            subtile_g<false, false>(so, ch, rows_by(ka + buf + C::SUB, gf), car, hh);
 #pragma unroll
             for (int b = 0; b < D / 32; ++b)
 #pragma unroll
                 for (int s = 0; s < 2; ++s)
                     kt[2 * b + s] = tr_pair_at(((ktr[0] + buf) ^ (b << 6)) + 8 * s * C::ROW, ((ktr[1] + buf) ^ (b << 6)) + 8 * s * C::ROW);
         }
-        if (hh == 0) s_g[st][wave][n] = sums.g_tot;
+        if (hh == 0) s_g[st][wave][n] = so.g_tot;
         barrier_lds();
         float left = bsum, t[NWS];
         sums_of(s_g[st], t);
@@ -2084,13 +2019,12 @@ bwd_dq_small_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
                 cag[ci] = car;
                 cbg[ci] = left;
             }
-            bf16x8 pz[2];
-            row_dz(pz, sums, ch, left, hh);
+            subtile_dz(so, ch, left, hh);
 #pragma unroll
             for (int b = 0; b < D / 32; ++b)
 #pragma unroll
                 for (int s = 0; s < 2; ++s)
-                    dqacc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(pz[s], kt[2 * b + s], dqacc[b], 0, 0, 0);
+                    dqacc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(so.pz[s], kt[2 * b + s], dqacc[b], 0, 0, 0);
         }
     }
 
@@ -2338,7 +2272,7 @@ bwd_dkv_small_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict_
             else subtile_stage1_log<false>(ch, again, c2, n, hh);
         }
         SubtileOut so;
-        subtile_stage2(so, ch, pacc, car, cbl, hh);
+        subtile_stage2<false, true>(so, ch, pacc, car, cbl, hh);
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         lds_store16(sw_off + buf, so.pa[0]);
         lds_store16((sw_off ^ 16) + buf, so.pa[1]);

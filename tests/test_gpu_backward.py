@@ -13,7 +13,7 @@ import numpy as np
 import pytest
 import torch
 
-from helpers import check_grad, dev, nan_bytes, to64
+from helpers import check_grad, dev, max_abs, nan_bytes, to64
 
 pytestmark = pytest.mark.gpu
 
@@ -112,6 +112,21 @@ def test_bwd_where_a_lane_leaves_the_linear_domain(sb, oracle, gen, d, logit, ma
         for b in {0, many - 1}:
             for name, a, r in (("dq", dq, ref[0]), ("dk", dk, ref[1]), ("dv", dv, ref[2])):
                 check_grad(name, a[b:b + 1] / scale, r)
+
+
+@pytest.mark.parametrize("many", [1, 64])
+@pytest.mark.parametrize("logit", [2.0, 3.25, 3.4, 3.48, 6.0, 6.2])
+@pytest.mark.parametrize("d", [32, 64, 128])
+def test_bwd_of_small_upstream_gradients(sb, gen, d, logit, many):
+    """All three gradients are linear in dout, and a power of two scales them exactly but for what falls below 2^-126: at 2^-100 less than
+    2^-26 of a term of ordinary size, of which an entry adds up 299, times |k| <= 71 in dq: 3e-4, and 5e-6 in dk, where the largest entries are about 1 and 0.03 at least."""
+    q, k, v, g = (t.repeat(many, 1, 1, 1) for t in gen.constant_logit(1, 2, 300, d, seed=23, kval=logit * d ** 0.5, dtype="bf16", with_dout=True))
+    want = gpu_grads(sb, q, k, v, g)
+    for power in (-60, -80, -100):
+        got = gpu_grads(sb, q, k, v, (g * 2.0 ** power).to(g.dtype))
+        for name, a, r in zip(("dq", "dk", "dv"), got, want):
+            err, top = max_abs(a * 2.0 ** -power, r), float(np.abs(r).max())
+            assert err <= 2.0 ** -10 * top, f"{name} at 2^{power}: {err} of {top}"
 
 
 def test_bwd_twice_agrees_and_overwrites(sb, gen):
