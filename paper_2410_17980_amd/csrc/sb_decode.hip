@@ -190,11 +190,6 @@ decode_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, co
 #pragma unroll
         for (int s = 0; s < D / 32; ++s) qw[s] = *reinterpret_cast<const bf16x8*>(row + 32 * s);
     }
-    // the thread's columns of the embeddings, asked for ahead of the keys (a call with them takes no longer than one without: B16 H22 Hkv11 T491 d64 5.78 / 5.77 us, B1 H12 Hkv4 T333 d128 6.2 / 6.3)
-    static_assert(FAR || GMAX * CH <= NTHR, "one round of the loop that stores the output");
-    u16x4 bias = u16x4(0);
-    if (!FAR && rb && tid < live * CH)
-        bias = *reinterpret_cast<const u16x4*>(rb + ((bkv % Hkv) * G + g0 + tid / CH) * D + 4 * (tid % CH));
     vword va[NV], vb[NV];
     fetch_k(kend);
     fetch_v(kend, va);
@@ -297,6 +292,14 @@ decode_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, co
     dma_wait<0>();                         // keys asked for before the end was known
     barrier_lds();                         // (theirs is the place of the shares)
 
+    // the thread's columns of the embeddings, asked for ahead of the waves' shares, which take as long as the load.  (Asked for ahead of the keys they held two registers
+    // through the sweep, with a bias or without: at d = 32 82 in place of 79, two workgroups a CU in place of three.  With the output in hand / ahead of the keys / here, us, with
+    // bias, then without: B32 H24 T300 d32 6.4 / 8.2 / 6.2, 6.2 / 8.2 / 6.1;  B24 H64 Hkv32 T500 d32 9.7 / 10.4 / 9.5, 10.2 / 10.7 / 10.2;  B16 H22 Hkv11 T491 d64 5.9 / 5.8 / 5.7,
+    // 5.6 / 5.7 / 5.6;  B1 H12 Hkv4 T333 d128 6.4 / 6.3 / 6.2, 6.2 in all three.)
+    static_assert(FAR || GMAX * CH <= NTHR, "one round of the loop that stores the output");
+    u16x4 bias = u16x4(0);
+    if (!FAR && rb && tid < live * CH)
+        bias = *reinterpret_cast<const u16x4*>(rb + ((bkv % Hkv) * G + g0 + tid / CH) * D + 4 * (tid % CH));
     // ---- the waves' shares, all heads at once: a lane holds 4 CW columns of its head, CW chunks of 16 bytes.  The chunk's place is xor-ed with
     // the head, so that heads, whose rows begin in the same bank, do not meet in one.  (Float by float, four heads at a time with two barriers each, this took
     // 2300 clocks of 9600 for up to four heads and 5200 for eight, d = 128; now 2000.  With the loads of waves that have no keys left out, us: B9 H24 Hkv3 T476
