@@ -770,7 +770,7 @@ __device__ __forceinline__ void kv_head_of(KvHead& kh, const Share& sh, const Pl
 // block's weights reach far; else the first one takes all of them and the others have nothing to do.  Every part leaves its sums in `sums`: dV's
 // of all heads, then dK's, laid out as dv and dk are with n kv heads in place of one; behind them a count for every kv head and strip of 32 keys of the
 // parts that have come, cleared by the query-stationary pass.  The last of a block's adds them up, in their order whichever it is.
-// Without parts a far group's heads are one chain, and what the launch waits for: figures beside parts_of().
+// Without parts a far group's heads are one chain, and what the launch waits for: figures beside key_plan().
 // The sums pass from XCD to XCD: stored past the caches, a wait for them, one count a workgroup, loaded past the caches.  (With fences in their place, which
 // write a whole L2 back for every workgroup, B4 H12 Hkv4 T2048 d128, a third of the heads far, 215 -> 304 us instead of 188.)
 struct Parts {
@@ -801,11 +801,15 @@ __device__ __forceinline__ int take_part(int& wg, const Parts& parts)
     return parts.last ? parts.n - 1 - at : at;
 }
 // Of a block whose first 32-key strip is `lo`: do the queries `beyond` strips further on still attend to it, in any head of the group?  In two steps: the
-// first part asks together with what it needs first.
+// first part asks together with what it needs first (and waits for it here where the group has more heads than the wave lanes).
 __device__ __forceinline__ int start_beyond(const Parts& parts, const uint16_t* __restrict__ first, long qhead0, int G, int nqb, int lo, int T, int lane)
 {
     const int at = lo + parts.beyond;
-    return parts.beyond == 0 ? 0 : 32 * at < T && lane < G ? first[(qhead0 + lane) * nqb * 4 + at] : 0x7fffffff;
+    if (parts.beyond == 0) return 0;
+    if (32 * at >= T) return 0x7fffffff;
+    int start = lane < G ? first[(qhead0 + lane) * nqb * 4 + at] : 0x7fffffff;
+    for (int h = lane + 64; h < G; h += 64) start = min(start, (int)first[(qhead0 + h) * nqb * 4 + at]);
+    return start;
 }
 __device__ __forceinline__ bool in_parts(int start, int lo) { return __builtin_amdgcn_ballot_w64(start <= lo) != 0; }
 typedef __attribute__((ext_vector_type(2))) unsigned long long u64x2;

@@ -44,3 +44,30 @@ def test_parts(sb, oracle, gen, shape, bias):
     for a, b, c in zip(got, go(ws), go(None)):
         assert torch.equal(a, b) and torch.equal(a, c)
     compare(oracle, [t.cpu() for t in got], q, k, v, g, r, cu)
+
+
+@pytest.mark.parametrize("far", [0, 71])
+def test_any_head_of_a_large_group_counts(sb, gen, far):
+    """72 query heads to a kv head, more than a wave has lanes, one of them far: its blocks are shared out all the same, as the counts at the end of the
+    workspace say, and the sums are those of the call without parts, each of 72 heads' times 3300 queries' terms added up in another order."""
+    B, H, Hkv, T, d = 1, 72, 1, 3300, 32
+    q, k, v, g = gen.gaussian(B, H, T, d, seed=5, dtype="bf16", with_dout=True)
+    k, v = k[:, :Hkv].clone(), v[:, :Hkv].contiguous()
+    f = (6.0 * d ** 0.5) ** 0.5
+    q[..., d - 1] = 0.0
+    q[:, far, :, d - 1], k[..., d - 1] = f, -f
+    qd, kd, vd, gd = dev(q, k, v, g)
+    _, m = sb.sb_attn_fwd_gqa(qd, kd, vd)
+    need = sb.sb_attn_bwd_gqa_workspace_bytes(B, H, Hkv, T, d)
+    strips = (T + 31) // 32
+    parts = (need - sb.sb_attn_bwd_workspace_bytes(B, H, T, d)) // (8 * B * Hkv * T * d)
+    assert parts > 1
+    ws = nan_bytes(need)
+    got = sb.sb_attn_bwd_gqa(qd, kd, vd, m, gd, workspace=ws)
+    one = sb.sb_attn_bwd_gqa(qd, kd, vd, m, gd, workspace=nan_bytes(sb.sb_attn_bwd_workspace_bytes(B, H, T, d)))
+    torch.cuda.synchronize()
+    counts = ws[-4 * strips:].view(torch.int32)
+    assert (counts[:strips // 2] == parts).all(), counts
+    assert torch.equal(got[0], one[0])
+    for a, b in zip(got[1:], one[1:]):
+        assert (a - b).norm() <= 1e-5 * b.norm()
