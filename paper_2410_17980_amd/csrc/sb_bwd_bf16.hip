@@ -2467,24 +2467,19 @@ size_t bwd_workspace_bytes(int B, int H, int T, int d)
     return (2 * sizeof(float) * nt32 * T + 4 * sizeof(uint16_t) * nblk + sizeof(float) * nchunk * d) * (size_t)B * H;
 }
 
-// of Parts: the sums of all kv heads' rows, and the counts (these in any case: what is larger than the other size has room for parts)
-static size_t part_bytes(const KeyPlan& plan, size_t heads, size_t rows, int T, int d)
-{
-    return (plan.parts > 1 ? 2 * sizeof(float) * plan.parts * rows * d : 0) + sizeof(int) * heads * ((T + 31) / 32);
-}
+// Behind the bytes of one part those of Parts, 16 in any case: what is larger than the other size has room for the plan that key_plan() makes
+static size_t gqa_bytes(size_t base, size_t parts) { return (base + 15) / 16 * 16 + std::max<size_t>(16, parts); }
 
 size_t bwd_gqa_workspace_bytes(int B, int H, int Hkv, int T, int d)
 {
-    const size_t base = bwd_workspace_bytes(B, H, T, d);
-    if (H == Hkv) return base;
-    return (base + 15) / 16 * 16 + part_bytes(key_plan(B, H, Hkv, T, d, false, 0), (size_t)B * Hkv, (size_t)B * Hkv * T, T, d);
+    const size_t base = bwd_workspace_bytes(B, H, T, d), heads = (size_t)B * Hkv;
+    return H == Hkv ? base : gqa_bytes(base, part_bytes(key_plan(B, H, Hkv, T, d, false, 0).parts, heads * T, heads, T, d));
 }
 
 size_t bwd_varlen_gqa_workspace_bytes(int nseq, int H, int Hkv, int Ttot, int max_T, int d)
 {
     const size_t base = bwd_varlen_workspace_bytes(nseq, H, Ttot, max_T, d);
-    if (H == Hkv) return base;
-    return (base + 15) / 16 * 16 + part_bytes(key_plan(nseq, H, Hkv, max_T, d, true, Ttot), (size_t)nseq * Hkv, (size_t)Hkv * Ttot, max_T, d);
+    return H == Hkv ? base : gqa_bytes(base, part_bytes(key_plan(nseq, H, Hkv, max_T, d, true, Ttot).parts, (size_t)Hkv * Ttot, (size_t)nseq * Hkv, max_T, d));
 }
 
 size_t bwd_varlen_workspace_bytes(int nseq, int H, int Ttot, int max_T, int d)

@@ -363,16 +363,23 @@ struct KeyPlan {
     int parts, beyond;
     bool last;                            // the first part's workgroups behind the others'
 };
+// bytes of `parts` sums of `rows` rows (of all kv heads) and of the counts of `heads` kv heads of up to T rows
+inline size_t part_bytes(int parts, size_t rows, size_t heads, int T, int d)
+{
+    return parts > 1 ? 2 * sizeof(float) * parts * rows * d + sizeof(int) * heads * ((T + 31) / 32) : 0;
+}
+constexpr size_t MOST_PART_BYTES = 210u * 1000 * 1000 - 16;      // (with what rounds the rest up to 16, what the header says)
 inline KeyPlan key_plan(int B, int H, int Hkv, int T, int d, bool packed, int Ttot)
 {
     const int G = H / Hkv, mean = mean_T(B, T, packed, Ttot), nq = (T + 31) / 32, waves = d == 128 ? 4 : 8;
     const long strips = pieces(B, Hkv, T, 32, packed, Ttot), blocks = pieces(B, Hkv, T, 128, packed, Ttot);
     KeyPlan p = {keys_of(B, H, Hkv, T, d, packed, Ttot), 1, 8, true};
     if (G == 1) return p;
+    const size_t rows = packed ? (size_t)Hkv * Ttot : (size_t)B * Hkv * T;
     auto most = [&](auto fits) {
         int n = 1;
         for (int x = 2; x <= std::min(G, 8); ++x)
-            if (G % x == 0 && fits((long)x)) n = x;
+            if (G % x == 0 && fits((long)x) && part_bytes(x, rows, (size_t)B * Hkv, T, d) <= MOST_PART_BYTES) n = x;
         return n;
     };
     const bool lengths = packed && packed_as(B, T, Ttot) == Packed::BY_LENGTH;

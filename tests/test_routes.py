@@ -1,5 +1,6 @@
 """Which kernels a call takes (csrc/sb_share.h, csrc/sb_split.h), compiled for the host: the rules' edges, and the routes that the GPU
 tests name for their shapes."""
+import math
 import os
 import random
 import shutil
@@ -347,6 +348,21 @@ def test_parts_of_grouped_heads(ask):
     for row, (keys, parts, beyond) in zip(rows, ask(rows)):
         B, H, Hkv, T, d, packed, Ttot = row
         assert parts == 1 or (H // Hkv) % parts == 0 and parts * Hkv * (Ttot or B * T) * d * 8 <= 211e6, row
+
+
+def test_memory_of_parts_is_bounded(ask):
+    """What sb_attn.h says of the larger workspace, 210 MB more at most with counts and rounding, for batches of many sequences and lengths that differ by far too."""
+    from paper_2410_17980_amd import binding as sb
+    rng = random.Random(21)
+    log = lambda lo, hi: int(math.exp(rng.uniform(math.log(lo), math.log(hi))))
+    rows = [(272, 16, 1, 8004, 32, 154768), (113, 8, 1, 8049, 64, 61811)]
+    while len(rows) < 20000:
+        G, Hkv, n, T = rng.choice((2, 3, 4, 6, 8, 16)), log(1, 33), log(1, 1001), log(32, 16385)
+        rows.append((n, G * Hkv, Hkv, T, rng.choice((32, 64, 128)), max(T, int(n * T * math.exp(rng.uniform(-math.log(100), 0.0))))))
+    for B, H, Hkv, T, d, Ttot in rows:
+        for more in (sb.sb_attn_varlen_bwd_gqa_workspace_bytes(B, H, Hkv, Ttot, T, d) - sb.sb_attn_varlen_bwd_workspace_bytes(B, H, Ttot, T, d),
+                     sb.sb_attn_bwd_gqa_workspace_bytes(B, H, Hkv, T, d) - sb.sb_attn_bwd_workspace_bytes(B, H, T, d)):
+            assert 0 < more <= 210e6, (B, H, Hkv, T, d, Ttot, more)
 
 
 def test_equal_lengths_take_the_plan_of_the_batched_call(ask):
