@@ -775,8 +775,7 @@ __device__ __forceinline__ void kv_head_of(KvHead& kh, const Share& sh, const Pl
 // write a whole L2 back for every workgroup, B4 H12 Hkv4 T2048 d128, a third of the heads far, 215 -> 304 us instead of 188.)
 struct Parts {
     float* sums;
-    int n, beyond, blocks;                  // parts, see in_parts(), workgroups of a part
-    bool last;                              // see take_part()
+    int n, beyond, blocks, heads;           // parts, see in_parts(), workgroups and query heads of a part
 };
 // The sums of kv head `kv` in part 0: where element x of dk and dv is, and the counts.  rows: of a kv head (of a packed batch all)
 template <int D> struct PartSums {
@@ -792,25 +791,27 @@ template <int D> struct PartSums {
         arrived = reinterpret_cast<int*>(parts.sums + 2 * all);
     }
 };
-// The part that workgroup `wg` takes of the block of the workgroup of that number in one part.  The first part's come last (parts.last), behind those that
+// The part that workgroup `wg` takes of the block of the workgroup of that number in one part.  The first part's come last, behind those that
 // have nothing to do: far blocks' parts start at once, and near blocks fill up what they leave.
 __device__ __forceinline__ int take_part(int& wg, const Parts& parts)
 {
     int at = 0;
     for (; at < parts.n - 1 && wg >= parts.blocks; ++at) wg -= parts.blocks;
-    return parts.last ? parts.n - 1 - at : at;
+    return parts.n - 1 - at;
 }
 // Of a block whose first 32-key strip is `lo`: do the queries `beyond` strips further on still attend to it, in any head of the group?  In two steps: the
 // first part asks together with what it needs first (and waits for it here where the group has more heads than the wave lanes).
 __device__ __forceinline__ int start_beyond(const Parts& parts, const uint16_t* __restrict__ first, long qhead0, int G, int nqb, int lo, int T, int lane)
 {
     const int at = lo + parts.beyond;
-    if (parts.beyond == 0) return 0;
     if (32 * at >= T) return 0x7fffffff;
     int start = lane < G ? first[(qhead0 + lane) * nqb * 4 + at] : 0x7fffffff;
-    for (int h = lane + 64; h < G; h += 64) start = min(start, (int)first[(qhead0 + h) * nqb * 4 + at]);
+    if (__builtin_expect(G > 64, 0))
+        for (int h = lane + 64; h < G; h += 64) start = min(start, (int)first[(qhead0 + h) * nqb * 4 + at]);
     return start;
 }
+// (What only parts do stands out of the way of the workgroups that have their block to themselves, the quotient G / n comes from the host: in line with the
+// rest it cost those of strips 0.7 to 1.0 us, a launch of them 12.2 -> 12.9 us in B1 H4 Hkv2 T469 d128, 11.1 -> 12.1 in B1 H4 Hkv1 T1846 d64; now 12.5 and 11.9.)
 __device__ __forceinline__ bool in_parts(int start, int lo) { return __builtin_amdgcn_ballot_w64(start <= lo) != 0; }
 typedef __attribute__((ext_vector_type(2))) unsigned long long u64x2;
 __device__ __forceinline__ f32x4 load_shared4(const float* p)
@@ -953,11 +954,11 @@ bwd_dkv_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
     int beyond = 0;
     if constexpr (PARTS) {
         beyond = start_beyond(parts, reinterpret_cast<const uint16_t*>(first), kh.qhead0, G, nkb_arg, sh.i * (BKW / 32), T, lane);
-        if (part > 0) {
+        if (__builtin_expect(part > 0, 0)) {
             if (!in_parts(beyond, sh.i * (BKW / 32))) return;
             alone = false;
-            g0 = part * (G / parts.n);
-            g1 = g0 + G / parts.n;
+            g0 = part * parts.heads;
+            g1 = g0 + parts.heads;
         }
     }
     const long base = kh.base, qrow0 = kh.qrow0, qrow_step = kh.qrow_step;
@@ -1132,9 +1133,9 @@ bwd_dkv_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
 #pragma unroll
     for (int s = 0; s < D / 16; ++s) { asm volatile("" :: "v"(kf[s])); asm volatile("" :: "v"(vf[s])); }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    if (PARTS && part == 0 && in_parts(beyond, sh.i * (BKW / 32))) {
+    if (PARTS && part == 0 && __builtin_expect(in_parts(beyond, sh.i * (BKW / 32)), 0)) {
         alone = false;
-        g1 = G / parts.n;
+        g1 = parts.heads;
     }
 #pragma unroll
     for (int b = 0; b < D / 32; ++b)
@@ -1326,11 +1327,11 @@ bwd_dkv_pair_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
     int beyond = 0;
     if constexpr (PARTS) {
         beyond = start_beyond(parts, reinterpret_cast<const uint16_t*>(first), kh.qhead0, G, nqb_arg, sh.i * KS, T, lane);
-        if (part_of > 0) {
+        if (__builtin_expect(part_of > 0, 0)) {
             if (!in_parts(beyond, sh.i * KS)) return;
             alone = false;
-            g0 = part_of * (G / parts.n);
-            g1 = g0 + G / parts.n;
+            g0 = part_of * parts.heads;
+            g1 = g0 + parts.heads;
         }
     }
     const long base = kh.base, qrow0 = kh.qrow0, qrow_step = kh.qrow_step;
@@ -1575,9 +1576,9 @@ bwd_dkv_pair_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__
         const int nqb = (T + BQ - 1) / BQ;
         dma_wait<0>();
         barrier_lds();
-        if (PARTS && part_of == 0 && in_parts(beyond, sh.i * KS)) {
+        if (PARTS && part_of == 0 && __builtin_expect(in_parts(beyond, sh.i * KS), 0)) {
             alone = false;
-            g1 = G / parts.n;
+            g1 = parts.heads;
         }
         {
             const uint32_t at = strip * 32 * C::ROW + tile_off_perm<D>(perm_row(n), hh);
@@ -2108,10 +2109,10 @@ bwd_dkv_small_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict_
     int beyond = 0;
     if constexpr (PARTS) {
         beyond = start_beyond(parts, first, kh.qhead0, G, nqb_arg, ks, T, lane);
-        if (part > 0) {
+        if (__builtin_expect(part > 0, 0)) {
             if (!in_parts(beyond, ks)) return;
             alone = false;
-            G /= parts.n;                                // the part's heads are the strip's
+            G = parts.heads;                             // the part's heads are the strip's
             qhead0 += part * G;
             kh.qrow0 += part * G * kh.qrow_step;
             kh.cbase += part * G * kh.cbase_step;
@@ -2180,9 +2181,9 @@ bwd_dkv_small_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict_
     // ones nearly always do, and where they are all there is they are what bounds the strip.
     const bool ahead = wave < 2 && wave < nq;
     if (ahead) fetch(wave, 0);
-    if (PARTS && part == 0 && in_parts(beyond, ks)) {    // (the first part's heads are the first of all)
+    if (PARTS && part == 0 && __builtin_expect(in_parts(beyond, ks), 0)) {    // (the first part's heads are the first of all)
         alone = false;
-        G /= parts.n;
+        G = parts.heads;
         all = G * nq;
         if (lane >= all) fn = 0x7fffffff;
     }
@@ -2313,19 +2314,27 @@ bwd_dkv_small_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict_
             red[NWS * 32 * D + at] = dkacc[b][r];
         }
     barrier_lds();
-    const PartSums<D> sums(parts, sh.bh, cu ? H / G_arg : BH, cu ? Ttot : T_arg);
+    auto store = [&](float* to_dk, float* to_dv, auto shared) __attribute__((always_inline)) {
 #pragma unroll
-    for (int mat = 0; mat < 2; ++mat)
-        for (int i = tid; i < 32 * D / 4; i += NTHR) {
-            const int row = i / (D / 4), c = 4 * (i % (D / 4));
-            f32x4 x = {0.0f, 0.0f, 0.0f, 0.0f};
+        for (int mat = 0; mat < 2; ++mat)
+            for (int i = tid; i < 32 * D / 4; i += NTHR) {
+                const int row = i / (D / 4), c = 4 * (i % (D / 4));
+                f32x4 x = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-            for (int w = 0; w < NWS; ++w) x += *reinterpret_cast<const f32x4*>(&red[((mat * NWS + w) * 32 + row) * D + c]);
-            if (k0 + row >= T) continue;
-            if (!PARTS || alone) *reinterpret_cast<f32x4*>((mat == 0 ? dv : dk) + kh.base + (long)(k0 + row) * D + c) = mat == 0 ? x : x * scale;
-            else store_shared4((mat == 0 ? sums.dv : sums.dk) + part * sums.step + kh.base + (long)(k0 + row) * D + c, x);
-        }
-    if (PARTS && !alone) add_parts<D, NTHR>(sums, parts.n, smem, kh.base + (long)k0 * D, kh.qhead0 / G_arg * nt32 + ks, min(T - k0, 32), dk, dv, scale, tid);
+                for (int w = 0; w < NWS; ++w) x += *reinterpret_cast<const f32x4*>(&red[((mat * NWS + w) * 32 + row) * D + c]);
+                if (k0 + row >= T) continue;
+                float* const to = (mat == 0 ? to_dv : to_dk) + kh.base + (long)(k0 + row) * D + c;
+                if constexpr (decltype(shared)::value) store_shared4(to, x);
+                else *reinterpret_cast<f32x4*>(to) = mat == 0 ? x : x * scale;
+            }
+    };
+    if (PARTS && __builtin_expect(!alone, 0)) {          // (see in_parts())
+        const PartSums<D> sums(parts, sh.bh, cu ? H / G_arg : BH, cu ? Ttot : T_arg);
+        store(sums.dk + part * sums.step, sums.dv + part * sums.step, bc<true>());
+        add_parts<D, NTHR>(sums, parts.n, smem, kh.base + (long)k0 * D, kh.qhead0 / G_arg * nt32 + ks, min(T - k0, 32), dk, dv, scale, tid);
+        return;
+    }
+    store(dk, dv, bc<false>());
 }
 
 // workspace layout: ca[BH][nt32][T], cb[BH][nt32][T] (fp32; [H][nt32][Ttot] for a packed
@@ -2356,14 +2365,14 @@ hipError_t launch_one(const uint16_t* q, const uint16_t* k, const uint16_t* v, c
     const int entries = VL ? 1 : B;                      // of the bias's gradient
     const int nchunk = bias_chunks(B, T, VL, Ttot);
     Keys keys = keys_of(B, H, Hkv, T, D, VL, Ttot);
-    Parts parts = {nullptr, 1, 8, 0, true};
+    Parts parts = {nullptr, 1, 0, 0, G};
     int* arrived = nullptr;
     if (room) {
         const KeyPlan plan = key_plan(B, H, Hkv, T, D, VL, Ttot);
         keys = plan.keys;
         parts.n = plan.parts;
+        parts.heads = G / plan.parts;
         parts.beyond = plan.beyond;
-        parts.last = plan.last;
         if (parts.n > 1) {
             const size_t base = VL ? bwd_varlen_workspace_bytes(B, H, Ttot, T, D) : bwd_workspace_bytes(B, H, T, D);
             parts.sums = reinterpret_cast<float*>(reinterpret_cast<char*>(workspace) + (base + 15) / 16 * 16);

@@ -326,42 +326,38 @@ inline Keys keys_of(int B, int H, int Hkv, int T, int d, bool packed, int Ttot)
     return !packed && H == Hkv && take_pairs(heads, nkb) ? Keys::PAIRS : Keys::KEYS_128;
 }
 
-// The key-stationary pass of grouped heads where the workspace has room for parts (Parts in sb_bwd_bf16.hip): the query heads of a block of keys
-// over `parts` workgroups, if the queries `beyond` strips further on attend to it (0: in any case).
-// One block's G heads are one chain, and where some kv heads reach far their blocks' chains are what the launch waits for; splitting them costs a part's
-// K, V and sums (4 to 5 us of a launch), and where nothing is far the parts that have nothing to do (2 to 5 us).
-// Whole backward in one part with the kernel that keys_of() names / as here, us, all heads far, then a third, then none:
-//   strips, in any case    few of them, of 3.5 rounds and more a part: d = 128 B1 H12 Hkv3 T462 (45 strips) 44 / 32, 44 / 31, 31 / 27;  B1 H8 Hkv1 T1059 (34) 153 / 73,
-//            65 / 42, 65 / 42;  packed H8 Hkv1, 9 up to 211 (32) 43 / 31 in all three;  d = 32 B2 H8 Hkv1 T535 (34) 34 / 20, 22.5 / 17.3, 22.5 / 17.2;  not
-//            d = 128 B2 H6 Hkv2 T333 (44) 32 / 31, 27 / 29;  B7 H6 Hkv2 T95 (42) 18 / 24
-//   strips, if far         d = 128 B1 H24 Hkv3 T2836 (267) 414 / 318, 388 / 217, 86 / 89;  packed H8 Hkv1, 9 up to 2904 (187) 398 / 263, 78 / 79;  d = 64 B1 H4 Hkv1 T5564 (174)
-//            204 / 143, 33 / 35;  d = 32 packed H24 Hkv3, 26 up to 2961 (2268) 864 / 646, 748 / 337, 225 / 181;  B1 H24 Hkv3 T2537 (240) 158 / 128, 156 / 104, 37 / 40
-//     not    where the strips fill the chip by themselves: what the parts read and add up is then more than the shorter chains save, but for long chains at d = 64 and 128.
-//            d = 32 B3 H8 Hkv1 T3638 (342) 228 / 240, 47 / 54 (none);  B2 H6 Hkv2 T3644 (456) 110 / 129, 94 / 116, 31 / 34;  B3 H6 Hkv3 T3711 (1044) 169 / 195, 126 / 139,
-//            41 / 47;  packed H8 Hkv1, 15 up to 3607 (458) 240 / 253, 57 / 70;  B5 H12 Hkv3 T2931 (1380) 293 / 327, 164 / 181, 74 / 81;  but B1 H24 Hkv6 T2572 (486) 124 / 134, 115 / 98, 34 / 38
-//            d = 64 B7 H4 Hkv1 T2520 (553, chains of 316 strips of queries) 159 / 176, 51 / 54;  B1 H24 Hkv6 T2512 (474, 316) 141 / 155, 129 / 113, 43 / 45;  but B2 H24 Hkv3
-//            T2861 (540, 720) 310 / 318, 232 / 192, 75 / 82
-//            d = 128 B7 H2 Hkv1 T2458 (539, 154) 181 / 207, 58 / 62;  B4 H8 Hkv2 T1954 (496, 248) 217 / 225, 189 / 219, 69 / 74;  B6 H24 Hkv3 T576 (324, 144) 117 / 120, 105 / 104,
-//            89 / 100;  packed H8 Hkv2, 10 up to 877 (286, 112) 91 / 98, 91 / 96, 55 / 65;  but B3 H24 Hkv3 T1220 (351, 312) 212 / 205, 185 / 140, 99 / 105;  B2 H12 Hkv3 T2806 (528, 352) 289 / 310, 248 / 204, 77 / 83
-//   blocks                 d = 128 B4 H12 Hkv4 T2048 (256 blocks) 310 / 267, 213 / 187, 119 / 114;  packed H12 Hkv6, 8 up to 4441 (430) 462 / 407, 402 / 301, 124 / 128;  packed H20
-//            Hkv5, 18 up to 1746 334 / 302, 287 / 205, 181 / 182;  not B16 H32 Hkv4 T1024 (512, of four parts) 740 / 806, 558 / 604, 443 / 458;  B8 H16 Hkv4 T4096 (1024, of two)
-//            2287 / 2372, 997 / 1019, 445 / 449
-//            d = 64 packed H24 Hkv8, 25 up to 2146 (850) 404 / 398, 299 / 218, 165 / 164;  packed H24 Hkv3, 28 up to 3544 (640) 1313 / 1035, 1088 / 547, 321 / 310;  B3 H9 Hkv3
-//            T7789 (549) 1236 / 1175, 946 / 580, 128 / 127;  B4 H32 Hkv8 T3000 (768) 858 / 856, 570 / 380, 187 / 186;  not packed H28 Hkv14, 41 up to 2437 (2280)
-//            582 / 648, 353 / 396, 267 / 292
-//            d = 32 B2 H18 Hkv9 T5580 (792) 595 / 589, 499 / 380, 87 / 88
-//     not    two heads a group in many blocks of a batch at d = 128, B6 H12 Hkv6 T1478 (432) 215 / 256, 168 / 196, 121 / 120, H58 Hkv29 T2049 (493) 314 / 374, 233 / 262, 127 / 127;  but B1 H18 Hkv9
-//            T3493 (252) 315 / 291, 276 / 243, 80 / 90, B3 H6 Hkv3 T4366 (309) 467 / 435, 339 / 294, 109 / 106;  nor so many at d = 64, B6 H24 Hkv12 T2158 (1224) 495 / 546, 266 / 281, 146 / 150;  but B6 H12 Hkv6 T3307 (936) 562 / 589, 349 / 299, 119 / 120
-// The first parts' workgroups come behind those that may have nothing to do, or before them where they leave CUs free: d = 32 B2 H16 Hkv2 T2539 160 / 157, 53 / 49;  d = 64
-// B1 H4 Hkv1 T5564 34.8 / 33.8;  not d = 32 B1 H24 Hkv6 T2572 132 / 132, 98 / 108;  d = 128 B1 H24 Hkv3 T2836 323 / 316, 216 / 233;  B4 H12 Hkv4 T2048 269 / 271, 187 / 204, 114 / 129.
-// Strips in one part where that rule, made for batches of one length, takes blocks, packed ones going by their mean: packed, d = 32 H27 Hkv9, 6 up to 1681 (954) 148 / 90,
-// 147 / 75, 52 / 47;  H15 Hkv5, 19 up to 1222 (1150) 114 / 78, 113 / 72, 59 / 54;  H8 Hkv4, 28 up to 1408 (1288) 97 / 70, 97 / 66, 49 / 38;  H20 Hkv10, 20 up to 3075 (4920) 372 / 356,
-// 251 / 201, 116 / 108;  d = 64 H28 Hkv14, 17 up to 522 (1722) 78 / 69, 75 / 67, 67 / 65;  d = 128 H28 Hkv7, 8 up to 788 (728) 157 / 123, 141 / 115, 131 / 100;  not H18 Hkv9,
-// 17 up to 472 (1143) 90 / 95 in all three;  of one length, d = 128 B11 H6 Hkv3 T364 (396) 51 / 45 in all three
+// The key-stationary pass of grouped heads where the workspace has room for parts (Parts in sb_bwd_bf16.hip): the query heads of a block of keys over `parts`
+// workgroups, if the queries `beyond` strips further on attend to it.  One block's G heads are one chain, and where some kv heads reach far their blocks' chains are what the
+// launch waits for.  A part costs its K, V and sums (4 to 5 us of a launch), and a workgroup that finds nothing to do next to nothing: what near heads lose is the question, and is lost where it
+// takes them for far ones (16 strips, not 8, beyond a block of four; rows of N(0,1) reach 5 to 8: B6 H4 Hkv2 T5496 d64, none far, the pass 43 us in one part, 50 with parts from 8
+// strips on, 43 with none taken).  So a part has to have a long chain, of 13 rounds of its workgroup's waves in blocks, 5 or 7 in strips, and there have to be few of them; where blocks fill the chip by
+// themselves, parts only add traffic.  Drawn from 3000 shapes, each with up to twelve plans; 465 more that the rule changes are 34 % faster
+// in the mean with a third of the kv heads far, 22 % with all, 8 % with none, at worst 3 %, 10 % and 8 % slower (B12 H6 Hkv2 T1638 d128 all 269 / 299, B4 H18 Hkv9 T486 d128 none 51 / 56).
+// Whole backward in one part with the kernel that keys_of() names / as here, us, all heads far, then a third, then none (one kv head: all, none):
+//   strips   d = 128 B1 H16 Hkv2 T2087 (132 strips) 290 / 200, 288 / 197, 68 / 56;  B1 H16 Hkv2 T1228 (78) 176 / 96, 175 / 93, 65 / 53;  B3 H4 Hkv1 T506 (48) 46 / 40, 30 / 31
+//            d = 64 B1 H4 Hkv1 T1778 (56) 61 / 36, 18 / 19;  B2 H8 Hkv2 T1173 (148) 53 / 45, 51 / 42, 29 / 30;  packed H8 Hkv1, 5 up to 1402 (92) 93 / 67, 35 / 37
+//            d = 32 B1 H2 Hkv1 T3942 (124) 68 / 54, 14 / 14;  B6 H8 Hkv1 T562 (108) 43 / 36, 32 / 29;  B1 H24 Hkv3 T1532 (144) 100 / 77, 99 / 76, 34 / 30
+//     not    more strips, d = 128 B3 H4 Hkv2 T1010 (192) 72 / 72, 72 / 69, 37 / 39;  packed H3 Hkv1, 18 up to 884 (148) 76 / 70, 42 / 52;  H2 Hkv1, 24 up to 978 (229) 72 / 77, 39 / 46;  B12 H8 Hkv2 T445 (336) 58 / 65, 57 / 63, 53 / 60;
+//            d = 64 B5 H16 Hkv4 T426 (280) 35 / 39, 34 / 38, 31 / 35;  B2 H4 Hkv2 T2964 (372) 87 / 98, 83 / 93, 36 / 38;  d = 32 B11 H4 Hkv2 T382 (264) 20 / 24 in all three;  B5 H16 Hkv2 T1116
+//            (350) 81 / 88, 79 / 71, 45 / 49;  but packed H8 Hkv1 d64, 5 up to 4989 (314) 369 / 298, 66 / 63
+//   blocks   d = 128 B4 H12 Hkv4 T2048 (256 blocks) 274 / 260, 212 / 188, 115 / 113;  B3 H6 Hkv3 T2068 (153) 170 / 158, 170 / 153, 70 / 62;  B1 H15 Hkv5 T7819 (310) 1194 / 1033, 763 / 533, 147 / 141;  packed H32 Hkv4, 17
+//            up to 3498 (476) 1269 / 1031, 1036 / 668, 452 / 451
+//            d = 64 B3 H12 Hkv3 T6024 (432) 980 / 886, 795 / 512, 126 / 122;  B5 H8 Hkv4 T3497 (560) 398 / 358, 338 / 258, 88 / 90;  packed H32 Hkv8, 18 up to 2778 (776) 615 / 506, 469 / 310, 174 / 180
+//            d = 32 B2 H14 Hkv7 T5822 (644) 550 / 493, 481 / 375, 74 / 73
+//     not    d = 128 of one length beyond 320, B15 H8 Hkv2 T1651 (390) 405 / 470, 340 / 329, 205 / 200;  B3 H24 Hkv12 T2658 (756) 619 / 686, 388 / 413, 196 / 193;  but B2 H32 Hkv8 T3741 (480) 994 / 1070,
+//            625 / 473, 234 / 225;  shorter ones, B8 H22 Hkv11 T786 194 / 224, 148 / 154, 145 / 147
+//            d = 64 and 32 where parts are more than 2300, packed H14 Hkv7 d64, 23 up to 3688 (1477) 633 / 698, 392 / 321, 181 / 184;  B13 H22 Hkv11 T1364 d64 (1573) 435 / 511, 246 / 268, 186 / 188;  shorter ones, B3
+//            H20 Hkv10 T928 d64 80 / 90, 80 / 89, 48 / 53;  at d = 32 blocks that are all on the chip at once, or nearly, B7 H4 Hkv2 T4514 (504) 341 / 354, 298 / 322, 61 / 63;
+//            B5 H6 Hkv2 T6568 (520) 818 / 664, 774 / 559, 82 / 90
+// Strips in one part where keys_of(), whose rule was made for batches of one length, takes blocks, packed ones going by their mean:
+//            d = 32 H18 Hkv6, 13 up to 584 (480 strips) 61 / 34, 60 / 34, 43 / 29;  H32 Hkv4, 36 up to 3601 (2320) 990 / 477, 876 / 370, 203 / 170;  H32 Hkv16, 10 up to 4234 (4352) 425 / 375, 348 / 234, 101 / 94
+//            d = 64 H8 Hkv4, 22 up to 632 (524) 61 / 44, 61 / 43, 44 / 35;  H24 Hkv6, 12 up to 4443 (1704) 614 / 459, 547 / 359, 136 / 108;  H21 Hkv7, 28 up to 1028 (1897) 157 / 122, 151 / 110, 92 / 94
+//            d = 128 H14 Hkv7, 5 up to 474 (336) 57 / 47, 57 / 47, 50 / 44;  H12 Hkv3, 4 up to 3798 (720) 470 / 412, 457 / 339, 139 / 108
+//            of one length, d = 128 B3 H18 Hkv9 T462 (405) 57 / 49, 57 / 48, 48 / 46;  B3 H14 Hkv7 T940 (630) 93 / 96, 92 / 80, 63 / 60;  not B13 H18 Hkv9 T169 (702) 44 / 47 in all three
+// The first parts' workgroups come behind those that may have nothing to do: before them, packed H14 Hkv7 d64, 33 up to 1942 164 / 186, 144 / 170, 93 / 107.
 struct KeyPlan {
     Keys keys;
     int parts, beyond;
-    bool last;                            // the first part's workgroups behind the others'
 };
 // bytes of `parts` sums of `rows` rows (of all kv heads) and of the counts of `heads` kv heads of up to T rows
 inline size_t part_bytes(int parts, size_t rows, size_t heads, int T, int d)
@@ -371,33 +367,31 @@ inline size_t part_bytes(int parts, size_t rows, size_t heads, int T, int d)
 constexpr size_t MOST_PART_BYTES = 210u * 1000 * 1000 - 16;      // (with what rounds the rest up to 16, what the header says)
 inline KeyPlan key_plan(int B, int H, int Hkv, int T, int d, bool packed, int Ttot)
 {
-    const int G = H / Hkv, mean = mean_T(B, T, packed, Ttot), nq = (T + 31) / 32, waves = d == 128 ? 4 : 8;
+    const int G = H / Hkv, mean = mean_T(B, T, packed, Ttot);
     const long strips = pieces(B, Hkv, T, 32, packed, Ttot), blocks = pieces(B, Hkv, T, 128, packed, Ttot);
-    KeyPlan p = {keys_of(B, H, Hkv, T, d, packed, Ttot), 1, 8, true};
+    KeyPlan p = {keys_of(B, H, Hkv, T, d, packed, Ttot), 1, 0};
     if (G == 1) return p;
+    // the most parts of which each has a chain of `rounds` rounds of its waves
     const size_t rows = packed ? (size_t)Hkv * Ttot : (size_t)B * Hkv * T;
-    auto most = [&](auto fits) {
+    auto most = [&](long pieces, long limit, int rounds) {
+        const long chain = (long)G * ((T + 31) / 32), waves = d == 128 ? 4 : 8;
         int n = 1;
         for (int x = 2; x <= std::min(G, 8); ++x)
-            if (G % x == 0 && fits((long)x) && part_bytes(x, rows, (size_t)B * Hkv, T, d) <= MOST_PART_BYTES) n = x;
+            if (G % x == 0 && pieces * x <= limit && chain >= rounds * waves * x && part_bytes(x, rows, (size_t)B * Hkv, T, d) <= MOST_PART_BYTES) n = x;
         return n;
     };
-    const bool lengths = packed && packed_as(B, T, Ttot) == Packed::BY_LENGTH;
-    const bool more = T > 64 && mean > 64 && T <= LONG_T && (d == 128 ? strips <= 768 : lengths && strips <= (d == 64 ? 2048 : 5120));
-    if (p.keys == Keys::STRIPS || more) {
-        const bool few = p.keys != Keys::STRIPS || (d == 32 ? strips <= 300 : strips <= (d == 64 ? 400 : 256) || G * nq >= (d == 64 ? 400 : 300));
+    const bool lengths = packed && packed_as(B, T, Ttot) == Packed::BY_LENGTH, fit = mean > 64 && T <= LONG_T;
+    if (p.keys != Keys::STRIPS && lengths && fit && strips <= (d == 32 ? 5120 : d == 64 ? 2048 : 768)) {
         p.keys = Keys::STRIPS;
-        p.parts = most([&](long n) { return strips * n <= 200 && 2L * G * nq >= 7 * waves * n; });
-        if (p.parts > 1) {
-            p.beyond = 0;
-            return p;
-        }
-        const long far = packed ? strips * mean / T : strips;
-        p.parts = most([&](long n) { return few && far * n <= (d == 32 ? 3000 : 1200) && (long)G * nq >= 14 * waves * n; });
-        p.last = strips > (d == 32 ? 400 : 256);
-    } else if (T >= 1400) {
-        p.parts = most([&](long n) { return blocks * n <= (d == 128 ? G == 2 && !lengths ? 640 : 1024 : d == 64 && !lengths ? 2300 : 3200); });
+    } else if (p.keys != Keys::STRIPS && T >= 1000 && (d == 32 ? blocks > 560 : d == 64 || lengths || blocks <= 320)) {
+        p.parts = most(blocks, d == 128 ? 1024 : 2300, 13);
+        p.beyond = 16;
         if (p.parts > 1) p.keys = d == 128 ? Keys::KEYS_128 : Keys::ONE_GROUP;
+    }
+    if (p.parts == 1 && d == 128 && !lengths && fit && T > 400 && strips <= 768) p.keys = Keys::STRIPS;
+    if (p.keys == Keys::STRIPS && T > 400 && strips <= 144) {
+        p.parts = most(strips, d == 128 ? 512 : 320, d == 128 ? 5 : 7);
+        p.beyond = 8;
     }
     return p;
 }

@@ -62,7 +62,7 @@ def test_training_step_in_a_graph(sb, gen):
         torch.cuda.synchronize()
 
 
-@pytest.mark.parametrize("B,H,Hkv,T,d", [(1, 12, 3, 462, 128), (1, 24, 3, 1500, 128), (1, 38, 19, 2000, 128), (1, 96, 48, 1409, 64)])
+@pytest.mark.parametrize("B,H,Hkv,T,d", [(1, 12, 3, 462, 128), (1, 24, 3, 1500, 128), (1, 38, 19, 2000, 128), (1, 120, 30, 1665, 64)])
 def test_parts_of_grouped_heads_in_a_graph(sb, B, H, Hkv, T, d):
     """Plans of more than one part (test_gpu_parts.py), whose counts every replay finds as something left them."""
     from test_gpu_exhausted import mixed_grouped
