@@ -104,7 +104,9 @@ fwd_f32_kernel(const float* __restrict__ q, const float* __restrict__ k, const f
     float (*const s_o)[F32_BQ][D] = reinterpret_cast<float (*)[F32_BQ][D]>(s_k);
     static_assert(SUB == F32_BQ * D * 4, "a wave's partial result takes the place of its subtile");
 
-    const Share sh = in_scalars(share_of((unsigned)first_wg + blockIdx.x, heads, run));
+    const unsigned wg = (unsigned)first_wg + blockIdx.x;
+    const Share sh = in_scalars(run == EIGHTHS ? share_in_eighths(wg, heads, nqb) : share_of(wg, heads, run));
+    if (sh.bh >= heads) return;
     const long bh = sh.bh;
     const int q0 = (nqb - 1 - sh.i) * F32_BQ;                  // longest rows first
     const int lane = threadIdx.x & 63;
@@ -253,13 +255,9 @@ hipError_t launch_fwd_f32(const float* q, const float* k, const float* v, float*
                           int B, int H, int T, int d, hipStream_t stream)
 {
     const int heads = B * H, nqb = (T + F32_BQ - 1) / F32_BQ;
-    const long grid = (long)heads * nqb;
+    const int run = f32_run(heads, nqb, T, d);
+    const long grid = run == EIGHTHS ? ((long)heads * nqb + 7) / 8 * 8 : (long)heads * nqb;
     if (grid > 0x7fffffffL) return hipErrorInvalidValue;
-    // The longest rows of all heads first, over all XCDs; heads in eights stay on one XCD each, whose L2 then holds their K and V.  Against a contiguous eighth
-    // of the (head, rows) list for each XCD, which left some with the longest rows of a head and others with the shortest, us: B1 H3 T1984 d32 37 / 27,
-    // B2 H3 T1854 d128 92 / 80, B2 H5 T965 d64 38.5 / 25.5, B3 H4 T1500 d64 69 / 52, d128 121 / 110, B4 H8 T2048 d32 166 / 158, d64 232 / 223 (turning 301), d128
-    // 442 / 444 (turning 610).
-    const int run = heads % 8 == 0 ? 31 : -1;
     return launch_workgroups(grid, F32_THREADS, [&](unsigned wgs, int first_wg) {
         const dim3 g(wgs), block(F32_THREADS);
         if (d == 32)

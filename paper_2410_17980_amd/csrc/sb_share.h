@@ -463,6 +463,26 @@ __host__ __device__ __forceinline__ Share share_of(unsigned wg, unsigned heads, 
     return {(int)(8 * o + ((w + turn + ((o * (o + 1)) >> 1)) & 7)), (int)i};
 }
 
+// Orders of the fp32 forward, 16 rows a block.  The longest rows of all heads come first, over all XCDs; heads in eights stay on one XCD each, whose L2 then holds their K and V.  In
+// short launches, whose blocks are all on the chip at once or wait for one of the shortest, and where the L2s do not hold K and V of heads that go round the XCDs, each XCD takes
+// a contiguous eighth of the (head, rows) list in place, and with it one or two heads.  In eighths / longest first, us, inputs in turn from six sets:
+//   short          d = 128 H28 T117 (224 blocks) 7.2 / 8.0;  H18 T183 (216) 10.1 / 11.2;  H12 T350 (264) 14.4 / 15.4;  H7 T471 (210) 16.9 / 17.5;  d = 64 H15 T213 (210) 6.9 / 7.3;  d = 32 H15 T250 (240) 5.6 / 5.9
+//     not          d = 128 H10 T419 (270) 18.5 / 16.1 (inputs in L2);  d = 64 H5 T870 (275) 18.7 / 15.8;  H10 T401 (260) 13.6 / 10.2;  d = 32 H9 T471 (270) 11.3 / 7.9;  B1 H3 T1984 37 / 27
+//   K and V        d = 128 H18 T1206 (22 MB) 114 / 120;  H14 T1911 (27 MB) 187 / 215;  H28 T1944 (56 MB) 377 / 469;  d = 64 H28 T1504 (22 MB) 124 / 128;  H28 T1737 (25 MB) 157 / 175
+//     not          d = 128 H10 T1928 (19.7 MB) 167 / 149;  H14 T695 (10 MB) 41 / 37;  d = 64 H20 T1958 (20 MB) 146 / 143;  H14 T1797 (13 MB) 97 / 82;  in eights, d = 128 H16 T1668 (27 MB) 159 / 156;  d = 64 H24
+//                  T1948 (24 MB) 149 / 143 (B4 H8 T2048 turning 301 us, d = 128 610)
+constexpr int EIGHTHS = -2;
+inline int f32_run(long heads, int nblk, int T, int d)
+{
+    if (heads * nblk <= 264) return EIGHTHS;
+    return heads % 8 == 0 ? 31 : 8.0 * heads * T * d > 20e6 ? EIGHTHS : -1;
+}
+__host__ __device__ __forceinline__ Share share_in_eighths(unsigned wg, unsigned heads, unsigned nblk)     // bh >= heads: nothing to do
+{
+    const unsigned all = heads * nblk, at = (wg & 7) * ((all >> 3) + ((all & 7) != 0)) + (wg >> 3), bh = at / nblk;
+    return {(int)(at < all ? bh : heads), (int)(at - bh * nblk)};
+}
+
 // the divisions above pass through vector registers: back into scalar ones, and with it everything
 // that a kernel derives from its share
 __device__ __forceinline__ Share in_scalars(Share s)

@@ -350,3 +350,13 @@ def test_f32_orders_of_heads_and_the_diagonal(sb, oracle, gen, B, H, T, d):
     ref, rem = oracle.fwd(to64(q), to64(k), to64(v))
     assert max_abs(to64(o), ref) <= F32_TOL
     check_m(to64(m), rem, rtol=1e-5, atol=1e-5)
+
+
+@pytest.mark.parametrize("B,H,T,d", [(1, 8, 545, 64), (3, 3, 481, 32), (1, 9, 2200, 128)])
+def test_f32_orders_of_longer_launches(sb, oracle, gen, B, H, T, d):
+    """Longest rows first with heads in eights and not, and each XCD's eighth of the list with more blocks than are on the chip at once."""
+    q, k, v = gen.biased_gaussian(B, H, T, d, seed=T + H, shift=-3.0, dtype="f32")
+    o, m = sb.sb_attn_fwd_f32(*dev(q, k, v), want_m=True)
+    ref, rem = oracle.fwd(to64(q), to64(k), to64(v))
+    assert max_abs(to64(o), ref) <= F32_TOL
+    check_m(to64(m), rem, rtol=1e-5, atol=1e-5)

@@ -20,6 +20,15 @@ int main(int argc, char** argv)
 {
     int heads, nblk, pairs, d, backward;                         // d: of the forward and the query-stationary pass, or 0
     while (scanf("%d %d %d %d %d", &heads, &nblk, &pairs, &d, &backward) == 5) {
+        if (pairs == 2) {                                        // fp32 forward
+            const int run = sb::f32_run(heads, nblk, 16 * nblk, d), grid = run == sb::EIGHTHS ? (heads * nblk + 7) / 8 * 8 : heads * nblk;
+            printf("%d %d\n", grid, run);
+            for (int wg = 0; wg < grid; ++wg) {
+                const sb::Share s = run == sb::EIGHTHS ? sb::share_in_eighths(wg, heads, nblk) : sb::share_of(wg, heads, run);
+                printf("%d %d\n", s.bh, s.i);
+            }
+            continue;
+        }
         const int grid = (int)sb::share_grid(heads, nblk, pairs), run = d ? sb::query_run(heads, nblk, d, backward) : sb::share_run(heads, nblk);
         printf("%d %d\n", grid, run);
         for (int wg = 0; wg < grid; ++wg) {
@@ -132,3 +141,17 @@ def test_runs_of_middling_head_counts(order):
     assert runs(d=64) == runs(d=128) == runs(d=128, backward=True) == list(range(64, 200, 8))
     for d, nblk in ((32, 24), (64, 24), (128, 40)):
         assert all(order(h, nblk, d=d)[1] == order(h, nblk, d=d, backward=True)[1] > 1 for h in (32, 40, 48, 56))
+
+
+@pytest.mark.parametrize("heads,nblk,d,eighths", [(1, 1, 32, True), (3, 5, 64, True), (28, 8, 128, True), (8, 33, 64, True), (12, 22, 128, True), (7, 30, 128, True),
+                                                  (5, 53, 64, False), (8, 34, 128, False), (10, 120, 128, False), (16, 128, 128, False), (18, 76, 128, True), (28, 109, 64, True)])
+def test_orders_of_the_fp32_forward(order, heads, nblk, d, eighths):
+    """Every block once; in eighths an XCD's blocks lie side by side in the list of all heads' blocks, otherwise the longest come first."""
+    got, _ = order(heads, nblk, pairs=2, d=d)
+    there = got[:, 0] < heads
+    assert sorted(map(tuple, got[there])) == [(h, i) for h in range(heads) for i in range(nblk)]
+    if eighths:
+        at, xcd = got[:, 0] * nblk + got[:, 1], np.arange(len(got)) % 8
+        assert all(np.all(np.diff(at[there & (xcd == x)]) == 1) for x in range(8))
+    else:
+        assert there.all() and np.all(np.diff(got[:, 1]) >= 0)
