@@ -360,3 +360,16 @@ def test_f32_orders_of_longer_launches(sb, oracle, gen, B, H, T, d):
     ref, rem = oracle.fwd(to64(q), to64(k), to64(v))
     assert max_abs(to64(o), ref) <= F32_TOL
     check_m(to64(m), rem, rtol=1e-5, atol=1e-5)
+
+
+def test_f32_logarithm_of_one_key(sb):
+    """One visible key and exact logits: -m is log(1 + e^z), e^z good to an ulp (2^-23 of the result at most) and the logarithm to 1e-7."""
+    n, d = 1 << 14, 64
+    gen = torch.Generator().manual_seed(5)
+    for lo, hi in ((0.0, 1e-3), (0.0, 1.0), (0.0, 4.0), (4.0, 12.0)):
+        z = -(torch.rand(n, generator=gen) * (hi - lo) + lo)
+        q, k = torch.zeros(1, n, 2, d), torch.zeros(1, n, 2, d)
+        q[0, :, 1, 0], k[0, :, 0, 0] = z, d ** 0.5
+        _, m = sb.sb_attn_fwd_f32(*dev(q, k, torch.zeros(1, n, 2, d)), want_m=True)
+        want = np.log1p(np.exp(z.double().numpy()))
+        assert np.all(np.abs(-to64(m)[0, :, 1] - want) <= 2.2e-7 * want), (lo, hi)
