@@ -14,9 +14,9 @@
 // In a large cache the nearest keys come first, in a launch of their own: they take most of the stick,
 // and where they take all of it (CARRY_EXHAUSTED: every farther weight is zero in fp32) the
 // rest of the cache is not read at all.  A small one is read whole by the second launch (split_of()).
-//   decode_kernel<.., false>  grid (kv head, block of query heads): the nearest keys, all of a
+//   decode_kernel<.., false, ..>  grid (kv head, block of query heads): the nearest keys, all of a
 //       short cache.  Finishes the heads that are exhausted, or all if that was all.
-//   decode_kernel<.., true>   grid (chunk, kv head, block of query heads): the keys before
+//   decode_kernel<.., true, ..>   grid (chunk, kv head, block of query heads): the keys before
 //       those.  Returns at once where the heads are finished.
 //   decode_combine_kernel     one workgroup per query head that is not finished: adds the
 //       chunks up, in a fixed order.  (Done by the last workgroup of the second launch to arrive
@@ -110,7 +110,7 @@ __device__ __forceinline__ void store_out4(bool rb, u16x4 e, uint16_t* o, float*
 // (pass of 256 keys, d = 128: 5200 of 8000 clocks).  K's place and V's registers (two sets) are asked for again as soon as a
 // pass has its logits, one pass ahead.  At d = 128 two far workgroups a CU read faster than three (all heads far, B8 H16 T16384 174 / 167 us,
 // B1 H32 Hkv8 T65000 55 / 51).
-template <int D, bool FAR>
+template <int D, bool FAR, bool SKIP>
 __global__ void __launch_bounds__(64 * (FAR ? FAR_NW : NEAR_NW), FAR && D < 128 ? 3 : 2)
 decode_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
               const uint16_t* __restrict__ rb, uint16_t* __restrict__ o, float* __restrict__ m,
@@ -155,7 +155,7 @@ decode_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, co
         }
     }
 
-    // rows hi - KEYS + 32 wave .. + 31; those before k0 are loaded as k0 and masked, and not at all where they are all a wave has
+    // rows hi - KEYS + 32 wave .. + 31; those before k0 are loaded as k0 and masked, with SKIP not at all where they are all a wave has (skip_rows())
     const int r0 = wave * KW - KEYS;
     const char* const kg = reinterpret_cast<const char*>(k) + (long)bkv * Tcap * ROW;
     const char* const vg = reinterpret_cast<const char*>(v) + (long)bkv * Tcap * ROW;
@@ -163,7 +163,7 @@ decode_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, co
     auto fetch_k = [&](int hi) __attribute__((always_inline)) {
         const uint64_t base = scalar_base(kg + (long)(hi + r0) * ROW);
         const int lo = k0 - (hi + r0);
-        if (lo >= KW) return;
+        if (SKIP && lo >= KW) return;
 #pragma unroll
         for (int i = 0; i < NK; ++i) {
             const int row = i * (1024 / ROW) + lane / CPR;
@@ -175,7 +175,7 @@ decode_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, co
     auto fetch_v = [&](int hi, vword (&vw)[NV]) __attribute__((always_inline)) {
         const char* const base = vg + (long)(hi + r0) * ROW;
         const int lo = k0 - (hi + r0);
-        if (lo >= KW) {                                              // (their weights are zero)
+        if (SKIP && lo >= KW) {                                              // (their weights are zero)
 #pragma unroll
             for (int i = 0; i < NV; ++i) vw[i] = vword(0u);
             return;
@@ -377,6 +377,16 @@ decode_combine_kernel(const float* __restrict__ part_o, const float* __restrict_
     }
 }
 
+// Whether waves without keys of their own in the last pass of the first launch leave their loads out.  Where the launch is one round of workgroups they are what the others
+// wait for; in later passes and rounds, and in the far launch, the branch costs more than the loads.  Loads / left out, us: d = 128 B1 H12 Hkv4 T333 6.8 / 6.3, B2 H16 Hkv2 T70 5.1 / 4.5;  d = 64 B2 H16
+// Hkv4 T333 5.4 / 5.1;  d = 32 B32 H24 T300 6.4 / 6.1;  not d = 128 B14 H50 Hkv25 T495 17.5 / 18.1, B16 H64 Hkv32 T400 19.7 / 20.2;  far launch B2 H28 Hkv7 T6248 11.0 / 11.8;  d = 64 B5 H8 T36294 24.7 / 25.3;
+// d = 32 B27 H8 Hkv4 T2893 10.5 / 10.8;  but d = 128 B8 H16 T16384 61.5 / 61.1
+inline bool skip_rows(long wgs, int keys, int d)
+{
+    constexpr int KEYS = KW * NEAR_NW;
+    return wgs <= (d == 32 ? 768 : d == 64 ? 512 : 256) && (keys - 1) % KEYS < KEYS - KW;
+}
+
 template <int D>
 hipError_t launch_d(const uint16_t* q, const uint16_t* k, const uint16_t* v, const uint16_t* rb,
                     uint16_t* o, float* m, float* workspace, int B, int H, int Hkv, int T, int Tcap, hipStream_t stream)
@@ -389,12 +399,16 @@ hipError_t launch_d(const uint16_t* q, const uint16_t* k, const uint16_t* v, con
     float* part_a = part_o + heads * s.chunks() * D;                      // [heads][chunks]
     hipError_t e = hipSuccess;
     if (s.near > 0) {
-        hipLaunchKernelGGL((decode_kernel<D, false>), dim3((unsigned)(B * Hkv), 1u, (unsigned)nz), dim3(64 * NEAR_NW), 0, stream,
-                           q, k, v, rb, o, m, part_o, part_a, T, Tcap, Hkv, G, s.near, s.C, s.nfar);
+        auto go = [&](auto skip) {
+            hipLaunchKernelGGL((decode_kernel<D, false, decltype(skip)::value>), dim3((unsigned)(B * Hkv), 1u, (unsigned)nz), dim3(64 * NEAR_NW), 0, stream,
+                               q, k, v, rb, o, m, part_o, part_a, T, Tcap, Hkv, G, s.near, s.C, s.nfar);
+        };
+        if (skip_rows((long)B * Hkv * nz, s.near, D)) go(std::true_type());
+        else go(std::false_type());
         e = hipGetLastError();
     }
     if (e != hipSuccess || s.nfar == 0) return e;
-    hipLaunchKernelGGL((decode_kernel<D, true>), dim3((unsigned)s.nfar, (unsigned)(B * Hkv), (unsigned)nz), dim3(64 * FAR_NW), 0, stream,
+    hipLaunchKernelGGL((decode_kernel<D, true, false>), dim3((unsigned)s.nfar, (unsigned)(B * Hkv), (unsigned)nz), dim3(64 * FAR_NW), 0, stream,
                        q, k, v, rb, o, m, part_o, part_a, T, Tcap, Hkv, G, s.near, s.C, s.nfar);
     e = hipGetLastError();
     if (e != hipSuccess) return e;

@@ -29,5 +29,6 @@ def remarks():
 @pytest.mark.parametrize("d", list(WAVES))
 def test_decode_kernels_keep_their_workgroups_a_cu(remarks, d, far):
     got = [v for k, v in remarks.items() if f"decode_kernelILi{d}ELb{far}E" in k]
-    assert len(got) == 1
-    assert got[0]["Occupancy [waves/SIMD]"] >= WAVES[d] and got[0]["VGPRs Spill"] == 0 and got[0]["SGPRs Spill"] == 0, got[0]
+    assert got
+    for g in got:
+        assert g["Occupancy [waves/SIMD]"] >= WAVES[d] and g["VGPRs Spill"] == 0 and g["SGPRs Spill"] == 0, g
